@@ -364,7 +364,7 @@ int splitzip_decompress_batch_paged(const splitzip_ditem* items, uint32_t n_item
  * 256-element chunks with 8-bit positions, 32-bit absolute positions without
  * chunks, and E4M3 words.  These calls exist to measure those formats beside
  * the main one on the same device; they run through one generic set of kernels
- * (dense pass with per-chunk counts and staged escape records, sums, finishing
+ * (dense pass with per-chunk counts and staged escape records, finishing
  * pass; dense decode with the correction applied in LDS) that is NOT the tuned
  * path of splitzip_compress
  * and splitzip_decompress.  The main format is one of the variants, so all of
@@ -424,10 +424,11 @@ int splitzip_variant_codebook_from_dec(const uint8_t* dec, const splitzip_varian
  * the sizes record (total_bytes, n_escapes, status; OVERFLOW and BAD_STREAM as
  * for the main calls) and the error codes are those of splitzip_compress and
  * splitzip_decompress; d_workspace needs splitzip_variant_workspace_bytes and
- * 16-byte alignment.  Three kernel launches per compress call (dense pass
- * that also stages the escape records, sums of the per-chunk counts, finishing
- * pass; a fourth packs values narrower than a byte), one per decompress call
- * (two in the absolute mode), all on `stream`. */
+ * 16-byte alignment.  Two kernel launches per compress call (dense pass that
+ * also stages the escape records, finishing pass; above 64 Mi elements a
+ * third between them sums the counts, and one more packs values narrower than
+ * a byte), one per decompress call (two in the absolute mode), all on
+ * `stream`. */
 int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip_variant* v,
                               const splitzip_codebook* cb, void* d_out, size_t out_capacity, void* d_workspace,
                               size_t workspace_bytes, splitzip_sizes* d_sizes, void* stream);

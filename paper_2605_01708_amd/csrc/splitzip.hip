@@ -186,6 +186,17 @@ void variant_tables(const splitzip_variant* v, const splitzip_codebook* cb, VArg
     }                                                                                                              \
   } while (0)
 
+template <int DT>
+void launch_v_finish(dim3 g, hipStream_t st, const VArgs& a) {
+  const dim3 b(kThreads);
+  switch (a.pos_bytes) {
+    case 0: hipLaunchKernelGGL((v_finish_kernel<DT, 0>), g, b, 0, st, a); break;
+    case 1: hipLaunchKernelGGL((v_finish_kernel<DT, 1>), g, b, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((v_finish_kernel<DT, 2>), g, b, 0, st, a); break;
+    default: hipLaunchKernelGGL((v_finish_kernel<DT, 4>), g, b, 0, st, a); break;
+  }
+}
+
 template <int DT, int CB>
 void launch_v_decode(unsigned grid, hipStream_t st, const VArgs& a) {
   const dim3 g(grid), b(kThreads);
@@ -301,15 +312,28 @@ int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip
   a.slots = reinterpret_cast<uint32_t*>(ws + a256(4 * a.n_chunks + 4) + a256(4 * (a.n_chunks + 1)) + a256(4 * (uint64_t)a.n_tiles));
   a.val_stage = reinterpret_cast<uint8_t*>(a.slots) + a256(4ull * kVSlotCap * blocks);
   variant_tables(v, cb, &a);
-  const uint8_t escape = (uint8_t)(0x80u | (v->escape_mode == SPLITZIP_ESC_SENTINEL ? (1u << v->code_bits) - 1u : 0u));
-  for (unsigned e = 0; e < 256; ++e) a.lut[e] = cb->member[e] ? cb->enc[e] : escape;
+  a.escape_code = v->escape_mode == SPLITZIP_ESC_SENTINEL ? (1u << v->code_bits) - 1u : 0u;
 
   const hipStream_t st = static_cast<hipStream_t>(stream);
   const unsigned grid = (unsigned)((blocks + kWaves - 1) / kWaves);
+  // A tensor of up to kVDirectSums workgroups needs no launch between the two passes (64 MiB of BF16: 4.7 us and the
+  // gap in front of it); the sums of the workgroups lie where the absolute mode has its one word at [n_chunks] and
+  // the other modes nothing.
+  a.wg_sums = reinterpret_cast<uint32_t*>(ws + a256(4 * a.n_chunks + 4));
+  const bool direct = grid <= kVDirectSums;
+  a.sums = direct ? a.wg_sums : a.tile_sums;
+  a.n_sums = direct ? grid : a.n_tiles;
+  a.sum_shift = direct ? 2u + (10u - a.chunk_shift) : 10u;
+  a.ahead = v->k <= 8 ? 64u : 16u;   // a top-8 codebook leaves about 60 records per block, a larger one one or two
   if (grid) SPLITZIP_V_DISPATCH2(v_dense_kernel, dim3(grid), dim3(kThreads), st, a);
-  hipLaunchKernelGGL(v_tile_sum_kernel, dim3(a.n_tiles), dim3(1024), 0, st, a);
+  if (!direct) hipLaunchKernelGGL(v_tile_sum_kernel, dim3(a.n_tiles), dim3(1024), 0, st, a);
   const unsigned fgrid = (unsigned)((blocks + kVFinishBlocks - 1) / kVFinishBlocks);
-  SPLITZIP_V_DISPATCH1(v_finish_kernel, dim3(fgrid ? fgrid : 1u), dim3(kThreads), st, a);
+  const dim3 fg(fgrid ? fgrid : 1u);
+  switch (a.dtype) {
+    case SPLITZIP_BF16: launch_v_finish<SPLITZIP_BF16>(fg, st, a); break;
+    case SPLITZIP_FP8_E5M2: launch_v_finish<SPLITZIP_FP8_E5M2>(fg, st, a); break;
+    default: launch_v_finish<SPLITZIP_FP8_E4M3>(fg, st, a); break;
+  }
   if (grid && a.val_bits != 8) {
     // M is known to the device only: a grid that strides over however many bytes the section has
     uint64_t g = (v_val_bytes(n_elems, a.val_bits) + kThreads - 1) / kThreads;

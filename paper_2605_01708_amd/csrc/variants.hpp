@@ -4,14 +4,13 @@
 // splitzip.hip (included inside its anonymous namespace).
 //
 // These kernels follow the structure of the tuned path: a dense pass that also counts the escapes of every chunk
-// and stages the escape records of every block of 1024 elements in a slot of the workspace, sums of the counts,
-// and a short finishing pass that ranks the records and moves them to their final place (the paper's own
-// structure, appendix "Quad64 Vectorized Encoding", counts in the dense pass and reads the input a second time
-// to write the records; the first version of these kernels did that).  They are deliberately plain --
-// a block of 1024 elements per wave, eight elements per lane and step, both planes packed as
-// LSB-first bit streams of any width and staged through LDS so that global accesses stay whole
-// dwords -- because their job is to compare the formats with one another on equal terms, the main
-// format included.  The tuned path for the main format is compress.hpp / decompress.hpp.
+// and stages the escape records of every block of 1024 elements in a slot of the workspace, and a short finishing
+// pass that ranks the records and moves them to their final place (the paper's own structure, appendix "Quad64
+// Vectorized Encoding", counts in the dense pass and reads the input a second time to write the records).  One set
+// of templates serves all formats, the main one included, so that they can be compared with one another on equal
+// terms: a block of 1024 elements per wave, eight elements per lane and step, both planes packed as LSB-first bit
+// streams of 3, 4 or 8 bits in registers (a quad of lanes exchanges the bytes of a 3-bit group by DPP, so every
+// global access is a whole dword).  The tuned path for the main format is compress.hpp / decompress.hpp.
 #ifndef SPLITZIP_VARIANTS_HPP
 #define SPLITZIP_VARIANTS_HPP
 
@@ -19,29 +18,74 @@ constexpr uint32_t kVBlock = 1024;   // elements a wave handles at a time
 constexpr uint32_t kVStep = 512;     // ... in two steps of 8 elements per lane
 constexpr uint32_t kVSlotCap = 128;  // escape records a block's slot holds (one in eight elements: a block with more is encoded again by the finishing pass)
 
-// per-format field arithmetic: e, a and the inverse (eq. (1) and (2); FP8 by analogy)
+// Per-format field arithmetic: e, a and the inverse (eq. (1) and (2); FP8 by analogy), element by element and for
+// a lane's eight elements (NW dwords of words) at a time:
+//   pack    the eight sign+mantissa fields, LSB first: 8 SB bits in sm (sm[1] for BF16 only)
+//   unpack  their inverse, exponent fields zero
+//   pair    two exponents in place, as an entry of the decode table; VPair dwords of them make the words
 template <int DT>
 struct VFmt;
 template <>
 struct VFmt<SPLITZIP_BF16> {
-  static constexpr int ES = 2, SB = 8, EXPS = 256;
+  static constexpr int ES = 2, SB = 8, EXPS = 256, NW = 4, LO = 7;
   __device__ static inline uint32_t exponent(uint32_t x) { return (x >> 7) & 0xffu; }
   __device__ static inline uint32_t signmant(uint32_t x) { return ((x >> 8) & 0x80u) | (x & 0x7fu); }
   __device__ static inline uint32_t combine(uint32_t a, uint32_t e) { return ((a & 0x80u) << 8) | (e << 7) | (a & 0x7fu); }
+  __device__ static inline void pack(const uint32_t (&w)[4], uint32_t (&sm)[2]) {
+    uint32_t t[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) t[d] = (w[d] & 0x007f007fu) | ((w[d] >> 8) & 0x00800080u);
+    sm[0] = byte_perm(t[1], t[0], 0x06040200u);
+    sm[1] = byte_perm(t[3], t[2], 0x06040200u);
+  }
+  __device__ static inline void unpack(const uint32_t (&sm)[2], uint32_t (&w)[4]) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) w[d] = byte_perm(0u, sm[d >> 1], (d & 1) ? 0x03030202u : 0x01010000u) & 0x807f807fu;
+  }
+  __device__ static inline uint32_t pair(uint32_t e0, uint32_t e1) { return (e0 << 7) | (e1 << 23); }
 };
 template <>
 struct VFmt<SPLITZIP_FP8_E5M2> {
-  static constexpr int ES = 1, SB = 3, EXPS = 32;
+  static constexpr int ES = 1, SB = 3, EXPS = 32, NW = 2, LO = 2;
   __device__ static inline uint32_t exponent(uint32_t x) { return (x >> 2) & 0x1fu; }
   __device__ static inline uint32_t signmant(uint32_t x) { return ((x >> 5) & 0x4u) | (x & 0x3u); }
   __device__ static inline uint32_t combine(uint32_t a, uint32_t e) { return ((a & 0x4u) << 5) | (e << 2) | (a & 0x3u); }
+  __device__ static inline void pack(const uint32_t (&w)[2], uint32_t (&sm)[2]) {
+    sm[0] = pack3_e5m2(w[0]) | (pack3_e5m2(w[1]) << 12);
+    sm[1] = 0;
+  }
+  __device__ static inline void unpack(const uint32_t (&sm)[2], uint32_t (&w)[2]) {
+    w[0] = unpack3_e5m2(sm[0] & 0xfffu);
+    w[1] = unpack3_e5m2((sm[0] >> 12) & 0xfffu);
+  }
+  __device__ static inline uint32_t pair(uint32_t e0, uint32_t e1) { return (e0 << 2) | (e1 << 10); }
 };
 template <>
 struct VFmt<SPLITZIP_FP8_E4M3> {
-  static constexpr int ES = 1, SB = 4, EXPS = 16;
+  static constexpr int ES = 1, SB = 4, EXPS = 16, NW = 2, LO = 3;
   __device__ static inline uint32_t exponent(uint32_t x) { return (x >> 3) & 0xfu; }
   __device__ static inline uint32_t signmant(uint32_t x) { return ((x >> 4) & 0x8u) | (x & 0x7u); }
   __device__ static inline uint32_t combine(uint32_t a, uint32_t e) { return ((a & 0x8u) << 4) | (e << 3) | (a & 0x7u); }
+  // the fields of four bytes in their low nibbles <-> 16 bits
+  __device__ static inline uint32_t pack4(uint32_t w) {
+    const uint32_t t = ((w >> 4) & 0x08080808u) | (w & 0x07070707u);
+    const uint32_t u = t | (t >> 4);            // bytes 0 and 2 hold a pair each
+    return byte_perm(0u, u, 0x0c0c0200u);
+  }
+  __device__ static inline uint32_t unpack4(uint32_t r) {
+    const uint32_t u = byte_perm(0u, r, 0x0c010c00u);
+    const uint32_t t = (u | (u << 4)) & 0x0f0f0f0fu;
+    return ((t & 0x08080808u) << 4) | (t & 0x07070707u);
+  }
+  __device__ static inline void pack(const uint32_t (&w)[2], uint32_t (&sm)[2]) {
+    sm[0] = pack4(w[0]) | (pack4(w[1]) << 16);
+    sm[1] = 0;
+  }
+  __device__ static inline void unpack(const uint32_t (&sm)[2], uint32_t (&w)[2]) {
+    w[0] = unpack4(sm[0] & 0xffffu);
+    w[1] = unpack4(sm[0] >> 16);
+  }
+  __device__ static inline uint32_t pair(uint32_t e0, uint32_t e1) { return (e0 << 3) | (e1 << 11); }
 };
 
 __host__ __device__ inline uint32_t v_sm_bits(uint32_t dtype) { return dtype == SPLITZIP_BF16 ? 8u : dtype == SPLITZIP_FP8_E5M2 ? 3u : 4u; }
@@ -69,140 +113,263 @@ struct VArgs {
   uint64_t off_tab, off_sm, off_code, off_pos;
   uint32_t* counts;      // workspace: escapes per chunk
   uint32_t* offs;        // exclusive offsets, n_chunks + 1: in the stream, or in the workspace in the absolute mode
+  uint32_t* wg_sums;     // workspace: escapes per workgroup of the dense pass (kWaves blocks)
   uint32_t* tile_sums;   // workspace: escapes per tile of kVScanTile chunks
   uint32_t n_tiles;
+  const uint32_t* sums;  // what the finishing pass sums up: wg_sums, or tile_sums for tensors of many workgroups
+  uint32_t n_sums;
+  uint32_t sum_shift;    // log2 of the chunks per sum
+  uint32_t ahead;        // records per block that the finishing pass fetches before it knows the counts
   uint32_t* slots;       // workspace: per block of 1024 elements kVSlotCap records, position in the block | exponent << 16
 
   splitzip_sizes* sizes;
   uint32_t hdr[16];      // the header of a stream of this call, words 6..9 (M, total) left 0
   uint8_t dec[16];
-  uint8_t lut[256];      // exponent -> code, | 0x80 for an escape
+  uint32_t escape_code;  // the code of an escaped element: 0, or all ones in the sentinel mode
 };
 
-// eight elements of a lane: words beyond N read as zero
-template <int DT>
-__device__ inline void v_load8(const VArgs& a, uint64_t g0, uint32_t (&x)[8]) {
-  using F = VFmt<DT>;
-  if (g0 + 8 <= a.n) {
-    if (F::ES == 2) {
-      const u32x4 v = *reinterpret_cast<const u32x4*>(a.in + 2 * g0);
-      x[0] = v.x & 0xffffu; x[1] = v.x >> 16; x[2] = v.y & 0xffffu; x[3] = v.y >> 16;
-      x[4] = v.z & 0xffffu; x[5] = v.z >> 16; x[6] = v.w & 0xffffu; x[7] = v.w >> 16;
-    } else {
-      const u32x2 v = *reinterpret_cast<const u32x2*>(a.in + g0);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { x[j] = (v.x >> (8 * j)) & 0xffu; x[4 + j] = (v.y >> (8 * j)) & 0xffu; }
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      x[j] = 0;
-      if (g0 + j < a.n) x[j] = F::ES == 2 ? reinterpret_cast<const uint16_t*>(a.in)[g0 + j] : a.in[g0 + j];
-    }
-  }
+// The 16 decode entries of the kernel's arguments as opaque scalars: a choice between the four words by a lane's own
+// index (dec16_at) must stay a choice between registers.  Left to itself the compiler turns it into one load from a
+// chosen address of the argument block and makes that a scalar load, with the first lane's address for all lanes.
+// (The tuned kernels choose between arguments and device memory first, which keeps the words in registers.)
+__device__ inline u32x4 v_dec16(const VArgs& a) {
+  u32x4 d = dec16_from(a.dec);
+  uint32_t w[4] = {d.x, d.y, d.z, d.w};
+  asm("" : "+s"(w[0]), "+s"(w[1]), "+s"(w[2]), "+s"(w[3]));
+  return u32x4{w[0], w[1], w[2], w[3]};
 }
-
-// A wave's LDS accesses are carried out in program order; this keeps the compiler from reordering
-// accesses it takes for unrelated because they go through different types, and waits for the data.
-__device__ inline void v_lds_settle() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // how many of the eight elements starting at g0 exist (the valid ones are always a prefix of the group)
 __device__ inline uint32_t v_nvalid(const VArgs& a, uint64_t g0) {
   return g0 >= a.n ? 0u : (a.n - g0 < 8 ? (uint32_t)(a.n - g0) : 8u);
 }
 
-// NB bytes of v to / from a lane's slot in LDS (slot = lane * NB; 8 and 4 are aligned)
-template <int NB>
-__device__ inline void v_lds_put(uint8_t* p, uint64_t v) {
-  if (NB == 8) *reinterpret_cast<uint64_t*>(p) = v;
-  else if (NB == 4) *reinterpret_cast<uint32_t*>(p) = (uint32_t)v;
-  else { p[0] = (uint8_t)v; p[1] = (uint8_t)(v >> 8); p[2] = (uint8_t)(v >> 16); }
-}
-template <int NB>
-__device__ inline uint64_t v_lds_get(const uint8_t* p) {
-  if (NB == 8) return *reinterpret_cast<const uint64_t*>(p);
-  if (NB == 4) return *reinterpret_cast<const uint32_t*>(p);
-  return (uint64_t)p[0] | ((uint64_t)p[1] << 8) | ((uint64_t)p[2] << 16);
-}
-
-// split + encode of a lane's eight elements: packed a, packed codes, escape mask (bit j = element j).  Words beyond
-// N were loaded as zero; their codes and escape bits are masked off at the end (no per-element branches).
-template <int DT, int CB>
-__device__ inline void v_encode8(const VArgs& a, const uint8_t* lut, uint64_t g0, const uint32_t (&x)[8], uint64_t& smw,
-                                 uint32_t& cw, uint32_t& esc) {
+// the words of a lane's eight elements from g0 on; words beyond N read as zero
+template <int DT, bool FULL>
+__device__ inline void v_load8(const VArgs& a, uint64_t g0, uint32_t (&w)[VFmt<DT>::NW]) {
   using F = VFmt<DT>;
-  smw = 0; cw = 0; esc = 0;
+  const uint32_t nv = FULL ? 8u : v_nvalid(a, g0);
+  if (nv == 8) {
+    if (F::ES == 2) {
+      const u32x4 v = ld_stream(reinterpret_cast<const u32x4*>(a.in + 2 * g0));
+      w[0] = v.x; w[1] = v.y; w[F::NW - 2] = v.z; w[F::NW - 1] = v.w;
+    } else {
+      const u32x2 v = ld_stream(reinterpret_cast<const u32x2*>(a.in + g0));
+      w[0] = v.x; w[1] = v.y;
+    }
+  } else {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const uint32_t t = lut[F::exponent(x[j])];
-    smw |= (uint64_t)F::signmant(x[j]) << (F::SB * j);   // zero for words beyond N
-    cw |= (t & 0x7fu) << (CB * j);
-    esc |= (t >> 7) << j;
+    for (int d = 0; d < F::NW; ++d) w[d] = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if ((uint32_t)j < nv) {
+        if (F::ES == 2) w[j >> 1] |= (uint32_t)reinterpret_cast<const uint16_t*>(a.in)[g0 + j] << (16 * (j & 1));
+        else w[j >> 2] |= (uint32_t)a.in[g0 + j] << (8 * (j & 3));
+      }
   }
-  const uint32_t nv = v_nvalid(a, g0);
-  if (nv < 8) {
-    cw &= (1u << (CB * nv)) - 1u;
-    esc &= (1u << nv) - 1u;
+}
+// exponent of element j of a lane's eight
+template <int DT>
+__device__ inline uint32_t v_exponent_of(const uint32_t (&w)[VFmt<DT>::NW], int j) {
+  using F = VFmt<DT>;
+  return F::ES == 2 ? (w[j >> 1] >> (F::LO + 16 * (j & 1))) & (F::EXPS - 1) : (w[(j >> 2) & (F::NW - 1)] >> (F::LO + 8 * (j & 3))) & (F::EXPS - 1);
+}
+
+// A wave's LDS accesses are carried out in program order; this keeps the compiler from reordering
+// accesses it takes for unrelated because they go through different types, and waits for the data.
+__device__ inline void v_lds_settle() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Groups of eight 3-bit fields are 24 bits: a quad of lanes shares 12 bytes.  v_pack24: the dword of them that lane
+// q < 3 of the quad stores (lane 3 stores none); v_unpack24: a lane's 24 bits back, dword q held by lane q < 3 of the
+// quad and any value by lane 3 (bits 24..31 of the result are not defined).
+__device__ inline uint32_t v_pack24(uint32_t c, uint32_t q) {
+  const uint32_t next = __builtin_amdgcn_mov_dpp(c, 0xF9, 0xf, 0xf, false);   // quad_perm [1,2,3,3]
+  return (c >> (8 * q)) | (next << (24 - 8 * q));
+}
+__device__ inline uint32_t v_unpack24(uint32_t d, uint32_t q) {
+  const uint32_t prev = __builtin_amdgcn_mov_dpp(d, 0x90, 0xf, 0xf, false);   // quad_perm [0,0,1,2]
+  return __builtin_amdgcn_alignbit(d, prev, 32 - 8 * q);                      // lane 0: a shift by 0 of its own dword
+}
+
+// A step's 512 fields of NB bits, one lane's eight in v: global accesses of whole dwords at byte offset off of the
+// plane (off = 64 NB per step); bytes at or beyond end, the padded end of the section, are left alone.
+template <int NB, bool FULL>
+__device__ inline void v_store_plane(uint8_t* plane, uint64_t off, uint64_t end, uint32_t lane, const uint32_t (&v)[2]) {
+  if (NB == 8) {
+    if (FULL || off + 8 * lane < end) st_stream(reinterpret_cast<u32x2*>(plane + off) + lane, u32x2{v[0], v[1]});
+  } else if (NB == 4) {
+    if (FULL || off + 4 * lane < end) st_stream(reinterpret_cast<uint32_t*>(plane + off) + lane, v[0]);
+  } else {
+    const uint32_t q = lane & 3u, at = (lane >> 2) * 12 + 4 * q, d = v_pack24(v[0], q);
+    if (q < 3 && (FULL || off + at < end)) st_stream(reinterpret_cast<uint32_t*>(plane + off + at), d);
+  }
+}
+// what v_store_plane wrote, as it comes from memory; v_plane_fields makes a lane's eight fields of it
+template <int NB, bool FULL>
+__device__ inline void v_load_plane(const uint8_t* plane, uint64_t off, uint64_t end, uint32_t lane, uint32_t (&v)[2]) {
+  v[0] = 0; v[1] = 0;
+  if (NB == 8) {
+    if (FULL || off + 8 * lane < end) {
+      const u32x2 x = ld_stream(reinterpret_cast<const u32x2*>(plane + off) + lane);
+      v[0] = x.x; v[1] = x.y;
+    }
+  } else if (NB == 4) {
+    if (FULL || off + 4 * lane < end) v[0] = ld_stream(reinterpret_cast<const uint32_t*>(plane + off) + lane);
+  } else {
+    const uint32_t q = lane & 3u, at = (lane >> 2) * 12 + 4 * (q < 3 ? q : 2u);   // lane 3 reads its neighbour's dword
+    if (FULL || off + at < end) v[0] = ld_stream(reinterpret_cast<const uint32_t*>(plane + off + at));
+  }
+}
+template <int NB>
+__device__ inline void v_plane_fields(uint32_t (&v)[2], uint32_t lane) {
+  if (NB == 3) v[0] = v_unpack24(v[0], lane & 3u) & 0xffffffu;
+}
+
+// Split + encode of a lane's eight elements: packed a, packed codes, and an escape mask with the codes' stride (bit
+// CB j = element j).  lut: exponent -> code, | 0x10000 for an escape: shifted by CB bits per element, four entries
+// add up to 4 CB bits of codes and, from bit 16 on, the flags in the same places.
+template <int DT, int CB>
+__device__ inline void v_encode8(const uint32_t* lut, uint32_t nv, const uint32_t (&w)[VFmt<DT>::NW], uint32_t (&sm)[2],
+                                 uint32_t (&code)[2], uint32_t& esc) {
+  VFmt<DT>::pack(w, sm);
+  uint32_t u[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    u[q] = lut[v_exponent_of<DT>(w, 4 * q)] + (lut[v_exponent_of<DT>(w, 4 * q + 1)] << CB) +
+           ((lut[v_exponent_of<DT>(w, 4 * q + 2)] + (lut[v_exponent_of<DT>(w, 4 * q + 3)] << CB)) << (2 * CB));
+  code[1] = 0;
+  if (CB == 4) {
+    code[0] = byte_perm(u[1], u[0], 0x05040100u);
+    esc = byte_perm(u[1], u[0], 0x07060302u);
+  } else {
+    code[0] = (u[0] & 0xfffu) | ((u[1] & 0xfffu) << 12);
+    esc = (u[0] >> 16) | ((u[1] >> 16) << 12);
+  }
+  if (nv < 8) {   // words beyond N were loaded as zero: their codes and escape bits go
+    code[0] &= (1u << (CB * nv)) - 1u;
+    esc &= (1u << (CB * nv)) - 1u;
   }
 }
 
-// compress pass 1: both planes and the escape count of every chunk
-template <int DT, int CB>
-__global__ __launch_bounds__(kThreads) void v_dense_kernel(const VArgs a) {
+// wave_sparse_excl with the total of the lower 32 lanes beside that of all
+__device__ inline uint32_t v_sparse_excl(uint32_t c, uint32_t& excl, uint32_t& low_total) {
+  uint32_t total = 0;
+  excl = 0;
+  low_total = 0;
+  for (uint32_t k = 1;; ++k) {
+    const uint64_t m = __ballot(c >= k);
+    if (!m) break;
+    excl = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, excl));
+    total += (uint32_t)__popcll(m);
+    low_total += (uint32_t)__popc((uint32_t)m);
+  }
+  return total;
+}
+
+// the encode table of v_encode8, by the first wave of the workgroup: escapes everywhere, the k codes on top
+__device__ inline void v_build_encode_table(const VArgs& a, uint32_t* lut, uint32_t tid) {
+  if (tid < 64) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) lut[q * 64 + tid] = 0x10000u | a.escape_code;
+    const uint32_t e = dec16_at(v_dec16(a), tid & 15u);
+    if (tid < a.k) lut[e] = tid;
+  }
+}
+
+// One block of 1024 elements by one wave, its words in w: planes out, the escape counts of its chunks, its escape
+// records (position in the block | exponent << 16, in element order) into its slot.  Returns the block's count.
+// The positions are ranked and collected in LDS first; the records then leave 64 at a time (with 6 % escapes a
+// block has 60, and a store per element and lane was half of the kernel's time).
+template <int DT, int CB, bool FULL>
+__device__ inline uint32_t v_dense_block(const VArgs& a, const uint32_t* lut, uint32_t* s_words, uint16_t* s_pos, uint64_t blk,
+                                         uint32_t lane, const uint32_t (&w)[2][VFmt<DT>::NW]) {
   using F = VFmt<DT>;
-  __shared__ uint8_t lut[256];
-  __shared__ __attribute__((aligned(16))) uint8_t s_sm[kWaves][64 * F::SB];
-  __shared__ __attribute__((aligned(16))) uint8_t s_code[kWaves][64 * CB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  lut[tid] = a.lut[tid];
-  __syncthreads();
-  const uint64_t blk = (uint64_t)blockIdx.x * kWaves + wave;
-  if (blk * kVBlock >= a.n) return;
-  uint32_t carry = 0;   // escapes of step 0, for 1024-element chunks
+  const uint64_t sm_end = a256(a.sm_bytes), code_end = a256(a.code_bytes);
+  uint32_t esc[2], excl[2], tot[2], low[2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
-    const uint64_t g = blk * kVBlock + s * kVStep, g0 = g + lane * 8;
-    uint32_t x[8];
-    v_load8<DT>(a, g0, x);
-    uint64_t smw;
-    uint32_t cw, esc;
-    v_encode8<DT, CB>(a, lut, g0, x, smw, cw, esc);
-    v_lds_put<F::SB>(&s_sm[wave][lane * F::SB], smw);
-    v_lds_put<CB>(&s_code[wave][lane * CB], cw);
-    v_lds_settle();
-    // the step's plane bytes leave as whole dwords, up to the padded end of the section
-    const uint64_t sm0 = g / 8 * F::SB, code0 = g / 8 * CB;
-    for (uint32_t i = lane; i < 16u * F::SB; i += 64)
-      if (sm0 + 4 * i < a256(a.sm_bytes))
-        st_stream(reinterpret_cast<uint32_t*>(a.out + a.off_sm + sm0) + i, reinterpret_cast<const uint32_t*>(s_sm[wave])[i]);
-    if ((uint32_t)lane < 16u * CB && code0 + 4 * lane < a256(a.code_bytes))
-      st_stream(reinterpret_cast<uint32_t*>(a.out + a.off_code + code0) + lane, reinterpret_cast<const uint32_t*>(s_code[wave])[lane]);
-    v_lds_settle();   // the staging is written again in the next step
-    const uint32_t incl = wave_incl_scan(__popc(esc));
-    const uint32_t t31 = __builtin_amdgcn_readlane(incl, 31), t63 = __builtin_amdgcn_readlane(incl, 63);
-    // the block's escape records, in element order, into its slot
-    if (esc) {
-      uint32_t r = (s == 0 ? 0u : carry) + incl - __popc(esc);
-      uint32_t* slot = a.slots + blk * kVSlotCap;
+    const uint64_t g = blk * kVBlock + s * kVStep;
+    uint32_t sm[2], code[2];
+    v_encode8<DT, CB>(lut, FULL ? 8u : v_nvalid(a, g + lane * 8), w[s], sm, code, esc[s]);
+    v_store_plane<F::SB, FULL>(a.out + a.off_sm, g / 8 * F::SB, sm_end, lane, sm);
+    v_store_plane<CB, FULL>(a.out + a.off_code, g / 8 * CB, code_end, lane, code);
+    tot[s] = v_sparse_excl(__popc(esc[s]), excl[s], low[s]);
+  }
+  const uint32_t total = tot[0] + tot[1];
+  if (total) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (!((esc >> j) & 1u)) continue;
-        if (r < kVSlotCap) slot[r] = (uint32_t)(s * kVStep + lane * 8 + j) | (F::exponent(x[j]) << 16);
+    for (int s = 0; s < 2; ++s) {
+      // the lane's words in its own bytes of the block's LDS copy
+      if (F::ES == 2) reinterpret_cast<u32x4*>(s_words)[s * 64 + lane] = u32x4{w[s][0], w[s][1], w[s][F::NW - 2], w[s][F::NW - 1]};
+      else reinterpret_cast<u32x2*>(s_words)[s * 64 + lane] = u32x2{w[s][0], w[s][1]};
+      uint32_t m = esc[s], r = (s ? tot[0] : 0u) + excl[s];
+      while (m) {
+        const uint32_t bit = (uint32_t)__ffs(m) - 1u, j = CB == 4 ? bit >> 2 : (bit * 11u) >> 5;   // bit / CB
+        m &= m - 1;
+        if (r < kVSlotCap) s_pos[r] = (uint16_t)(s * kVStep + lane * 8 + j);
         ++r;
       }
     }
-    if (a.chunk_shift == 10) {
-      if (s == 1 && lane == 0) a.counts[blk] = carry + t63;
-    } else if (lane == 0) {   // two 256-element chunks per step
-      const uint64_t c0 = g >> 8;
-      if (c0 < a.n_chunks) a.counts[c0] = t31;
-      if (c0 + 1 < a.n_chunks) a.counts[c0 + 1] = t63 - t31;
+    v_lds_settle();
+    uint32_t* slot = a.slots + blk * kVSlotCap;
+    for (uint32_t i = lane; i < (total < kVSlotCap ? total : kVSlotCap); i += 64) {
+      const uint32_t p = s_pos[i];
+      const uint32_t x = F::ES == 2 ? (uint32_t)reinterpret_cast<const uint16_t*>(s_words)[p] : (uint32_t)reinterpret_cast<const uint8_t*>(s_words)[p];
+      slot[i] = p | (F::exponent(x) << 16);
     }
-    if (s == 0) carry = t63;
+  }
+  if (a.chunk_shift == 10) {
+    if (lane == 0) a.counts[blk] = total;
+  } else if (lane < 4) {   // two 256-element chunks per step
+    const uint64_t c = blk * 4 + lane;
+    const uint32_t s_low = lane < 2 ? low[0] : low[1], s_tot = lane < 2 ? tot[0] : tot[1];
+    if (c < a.n_chunks) a.counts[c] = lane & 1u ? s_tot - s_low : s_low;
+  }
+  return total;
+}
+
+// Compress pass 1: both planes, the escape count of every chunk and of every workgroup, the escape records.
+// Bound by memory like the tuned dense pass: one 64 MiB BF16 tensor takes 24.8 us under 3-bit codes (29.8 us with the
+// planes staged through LDS in two dependent steps and a store per escape and lane) and 22.0 us in the main format.
+template <int DT, int CB>
+__global__ __launch_bounds__(kThreads) void v_dense_kernel(const VArgs a) {
+  using F = VFmt<DT>;
+  __shared__ uint32_t lut[256];
+  __shared__ __attribute__((aligned(16))) uint32_t s_words[kWaves][kVBlock * F::ES / 4];
+  __shared__ uint16_t s_pos[kWaves][kVSlotCap];
+  __shared__ uint32_t s_cnt[kWaves];
+  const uint32_t tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const uint64_t blk = (uint64_t)blockIdx.x * kWaves + wave;
+  const bool live = blk * kVBlock < a.n, full = (blk + 1) * kVBlock <= a.n;
+  uint32_t w[2][F::NW], cnt = 0;
+  // the block's words first, all of them: the table is built while they are on their way
+  if (full) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) v_load8<DT, true>(a, blk * kVBlock + s * kVStep + lane * 8, w[s]);
+    v_build_encode_table(a, lut, tid);
+    lds_barrier();
+    cnt = v_dense_block<DT, CB, true>(a, lut, s_words[wave], s_pos[wave], blk, lane, w);
+  } else {
+    if (live) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) v_load8<DT, false>(a, blk * kVBlock + s * kVStep + lane * 8, w[s]);
+    }
+    v_build_encode_table(a, lut, tid);
+    lds_barrier();
+    if (live) cnt = v_dense_block<DT, CB, false>(a, lut, s_words[wave], s_pos[wave], blk, lane, w);
+  }
+  if (lane == 0) s_cnt[wave] = cnt;
+  lds_barrier();
+  if (tid == 0) {
+    uint32_t sum = 0;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) sum += s_cnt[q];
+    a.wg_sums[blockIdx.x] = sum;
   }
 }
 
-constexpr uint32_t kVScanTile = 1024;   // counts per workgroup of the two scan kernels
+constexpr uint32_t kVScanTile = 1024;   // counts per workgroup of the summing kernel
 
 // sum of 1024 values, one per thread, in every thread (two barriers)
 __device__ inline uint32_t v_block_sum(uint32_t v, uint32_t* s_wave /*16*/, uint32_t& incl_out, uint32_t& before_out) {
@@ -221,7 +388,7 @@ __device__ inline uint32_t v_block_sum(uint32_t v, uint32_t* s_wave /*16*/, uint
   return all;
 }
 
-// compress pass 2a: the escapes of every tile of 1024 chunks
+// compress pass 2, for tensors of more than kVDirectSums workgroups: the escapes of every tile of 1024 chunks
 __global__ __launch_bounds__(1024) void v_tile_sum_kernel(const VArgs a) {
   __shared__ uint32_t s_wave[16];
   const uint64_t c = (uint64_t)blockIdx.x * kVScanTile + threadIdx.x;
@@ -230,54 +397,93 @@ __global__ __launch_bounds__(1024) void v_tile_sum_kernel(const VArgs a) {
   if (threadIdx.x == 0) a.tile_sums[blockIdx.x] = all;
 }
 
-constexpr uint32_t kVFinishBlocks = 64;   // blocks of 1024 elements per workgroup of the finishing pass
+constexpr uint32_t kVFinishBlocks = 32;   // blocks of 1024 elements per workgroup of the finishing pass
+// Up to this many workgroups of the dense pass (64 Mi elements) the finishing pass sums their counts itself; beyond
+// that its workgroups would together read more than 128 MB of them, and it is given sums of kVScanTile chunks.
+constexpr uint32_t kVDirectSums = 16384;
 
-// where record `rank` of the stream goes: its position in the variant's width (none in the sentinel mode) and its
-// exponent (as a byte of the stream, or of the workspace if values are narrower than a byte: v_pack_kernel)
-__device__ inline void v_put_record(const VArgs& a, uint64_t off_val, uint32_t rank, uint64_t elem, uint32_t e) {
-  if (a.mode == SPLITZIP_ESC_POS) {
-    const uint32_t p = (uint32_t)elem & ((1u << a.chunk_shift) - 1u);
-    const uint64_t at = a.off_pos + (uint64_t)a.pos_bytes * rank;
-    if (at + a.pos_bytes <= a.capacity) {
-      if (a.pos_bytes == 2) *reinterpret_cast<uint16_t*>(a.out + at) = (uint16_t)p;
-      else a.out[at] = (uint8_t)p;
-    }
-  } else if (a.mode == SPLITZIP_ESC_ABS32) {
-    const uint64_t at = a.off_pos + 4ull * rank;
-    if (at + 4 <= a.capacity) *reinterpret_cast<uint32_t*>(a.out + at) = (uint32_t)elem;
+// where the records of a stream go: positions of PB bytes (none in the sentinel mode), and exponents, as bytes of the
+// stream or, if values are narrower than a byte, of the workspace (v_pack_kernel); the rooms are in records
+template <int PB>
+struct VSink {
+  uint8_t* pos;
+  uint8_t* val;
+  uint64_t pos_room, val_room;
+  uint32_t pos_mask;   // of the element index: relative to the chunk, or (absolute mode) all of it
+  __device__ inline VSink(const VArgs& a, uint32_t M) {
+    const uint64_t off_val = a.off_pos + a256((uint64_t)PB * M);
+    pos = a.out + a.off_pos;
+    pos_room = PB == 0 ? 0 : a.capacity > a.off_pos ? (a.capacity - a.off_pos) / (PB ? PB : 1) : 0;
+    val = a.val_bits == 8 ? a.out + off_val : a.val_stage;
+    val_room = a.val_bits != 8 ? ~0ull : a.capacity > off_val ? a.capacity - off_val : 0;
+    pos_mask = PB == 4 ? ~0u : (1u << a.chunk_shift) - 1u;
   }
-  if (a.val_bits != 8) a.val_stage[rank] = (uint8_t)e;
-  else if (off_val + rank < a.capacity) a.out[off_val + rank] = (uint8_t)e;
-}
+  __device__ inline void put(uint32_t rank, uint32_t elem, uint32_t e) const {
+    const uint32_t p = elem & pos_mask;
+    if (PB != 0 && rank < pos_room) {
+      if (PB == 1) pos[rank] = (uint8_t)p;
+      if (PB == 2) reinterpret_cast<uint16_t*>(pos)[rank] = (uint16_t)p;
+      if (PB == 4) reinterpret_cast<uint32_t*>(pos)[rank] = p;
+    }
+    if (rank < val_room) val[rank] = (uint8_t)e;
+  }
+};
 
-// compress pass 3: one workgroup per kVFinishBlocks blocks.  It sums the counts (the whole tensor's: M; those before
+// Compress pass 3: one workgroup per kVFinishBlocks blocks.  It sums the counts (the whole tensor's: M; those before
 // its blocks: its first rank), writes its chunks' entries of the offset table, and moves its blocks' records from
-// their slots to their ranks; a block with more records than its slot holds is encoded once more from the words.
+// their slots to their ranks, a wave per block and eight blocks per wave: nothing but trips to memory, so the first
+// a.ahead records of every block are asked for before the counts are there and the others all at once behind them.
+// A block with more records than its slot holds is encoded once more from the words.  (Ranks searched and records
+// fetched one at a time per thread took 17.2 us for the two million records of a 64 MiB tensor under a top-8 codebook;
+// this takes 9.4 us, and 7.1 us with 0.1 % escapes.)
 // Workgroup 0 also writes the header, the sizes record and the zero padding.
-template <int DT>
+template <int DT, int PB>
 __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs a) {
   using F = VFmt<DT>;
-  __shared__ uint8_t lut[256];
+  constexpr uint32_t kPerWave = kVFinishBlocks / kWaves;
+  __shared__ uint32_t lut[256];
   __shared__ uint32_t s_part[3][kWaves];
   __shared__ uint32_t s_bp[kVFinishBlocks + 1];   // escapes of the group's blocks before each block
-  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = blockIdx.x;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, g = blockIdx.x;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   const uint32_t cpb_shift = 10u - a.chunk_shift;   // log2 of the chunks per block: 0 or 2
   const uint64_t n_blocks = (a.n + kVBlock - 1) / kVBlock;
   const uint64_t blk0 = (uint64_t)g * kVFinishBlocks, c0 = blk0 << cpb_shift;
-  lut[tid] = a.lut[tid];
-  // escapes before the group's first chunk and in the whole tensor: whole scan tiles by their sums, the rest by chunk
-  uint32_t before = 0, all = 0;
-  const uint64_t whole = c0 / kVScanTile;
-  for (uint32_t t = tid; t < a.n_tiles; t += kThreads) {
-    const uint32_t v = a.tile_sums[t];
-    all += v;
-    before += t < whole ? v : 0u;
+  const uint64_t blocks_here = n_blocks > blk0 ? (n_blocks - blk0 < kVFinishBlocks ? n_blocks - blk0 : kVFinishBlocks) : 0;
+  uint32_t rec[kPerWave], rec2[kPerWave];
+#pragma unroll
+  for (uint32_t q = 0; q < kPerWave; ++q) {
+    const uint32_t b = wave * kPerWave + q;
+    rec[q] = b < blocks_here && lane < a.ahead ? a.slots[(blk0 + b) * kVSlotCap + lane] : 0u;
   }
-  for (uint64_t c = whole * kVScanTile + tid; c < c0 && c < a.n_chunks; c += kThreads) before += a.counts[c];
-  // the group's chunks, one per thread (64 or 256 of them)
+  // the group's chunks, one per thread (32 or 128 of them)
   const uint64_t my_c = c0 + tid;
   const bool have = tid < (kVFinishBlocks << cpb_shift) && my_c < a.n_chunks;
   const uint32_t mine = have ? a.counts[my_c] : 0u;
+  // escapes before the group's first chunk and in the whole tensor: by the sums that lie before it entirely, the rest by chunk
+  uint32_t before = 0, all = 0;
+  const uint64_t whole = c0 >> a.sum_shift;
+  const u32x4* sv = reinterpret_cast<const u32x4*>(a.sums);   // 16-byte aligned, in a region of whole 256 bytes: the last vector may hold words of no meaning
+  for (uint32_t v0 = 0; 4 * v0 < a.n_sums; v0 += 4 * kThreads) {
+    u32x4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t idx = v0 + q * kThreads + tid;
+      v[q] = 4 * idx < a.n_sums ? sv[idx] : u32x4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t e = 4 * (v0 + q * kThreads + tid);
+      const uint32_t c[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+      for (uint32_t z = 0; z < 4; ++z) {
+        const uint32_t cz = e + z < a.n_sums ? c[z] : 0u;
+        all += cz;
+        before += e + z < whole ? cz : 0u;
+      }
+    }
+  }
+  for (uint64_t c = (whole << a.sum_shift) + tid; c < c0 && c < a.n_chunks; c += kThreads) before += a.counts[c];
   const uint32_t incl = wave_incl_scan(mine);
   before = wave_last(wave_incl_scan(before));
   all = wave_last(wave_incl_scan(all));
@@ -298,44 +504,66 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs a) {
   const uint32_t excl = waves_before + incl - mine;   // escapes of the group before this thread's chunk
   if (have && (tid & ((1u << cpb_shift) - 1u)) == 0) s_bp[tid >> cpb_shift] = excl;
   // blocks behind the tensor's last start where the group ends
-  const uint64_t blocks_here = n_blocks > blk0 ? (n_blocks - blk0 < kVFinishBlocks ? n_blocks - blk0 : kVFinishBlocks) : 0;
   if (tid >= blocks_here && tid <= kVFinishBlocks) s_bp[tid] = group_total;
+  v_build_encode_table(a, lut, tid);
   __syncthreads();
   if (have && a.mode != SPLITZIP_ESC_ABS32) a.offs[my_c] = first + excl;
-  const uint64_t off_val = a.off_pos + a256((uint64_t)a.pos_bytes * M);
+  const VSink<PB> sink(a, M);
 
-  // records that wait in their blocks' slots: rank r of the group belongs to the last block that starts at or before r
-  for (uint32_t r = tid; r < group_total; r += kThreads) {
-    uint32_t b = 0;
+  uint32_t bp[kPerWave + 1];   // wave-uniform: the wave's blocks
 #pragma unroll
-    for (uint32_t step = kVFinishBlocks / 2; step; step >>= 1)
-      if (s_bp[b + step] <= r) b += step;
-    if (s_bp[b + 1] - s_bp[b] > kVSlotCap) continue;
-    const uint32_t rec = a.slots[(blk0 + b) * kVSlotCap + (r - s_bp[b])];
-    v_put_record(a, off_val, first + r, (blk0 + b) * kVBlock + (rec & 0xffffu), rec >> 16);
+  for (uint32_t q = 0; q <= kPerWave; ++q) bp[q] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_bp[wave * kPerWave + q]);
+#pragma unroll
+  for (uint32_t q = 0; q < kPerWave; ++q) {
+    const uint32_t n_b = bp[q + 1] - bp[q], i = a.ahead + lane;
+    rec2[q] = 0;
+    if (n_b <= kVSlotCap && i < n_b) rec2[q] = a.slots[(blk0 + wave * kPerWave + q) * kVSlotCap + i];
   }
-  // blocks whose records did not fit their slots, a wave each
-  for (uint32_t b = wave; b < blocks_here; b += kWaves) {
-    if (s_bp[b + 1] - s_bp[b] <= kVSlotCap) continue;
-    uint32_t rank = first + s_bp[b];
+  const uint32_t elem0 = (uint32_t)(blk0 + wave * kPerWave) * kVBlock;   // fewer than 2^32 elements
+  uint32_t many = 0;   // a block with more records than the two fetches took, or more than its slot holds
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const uint64_t g0 = (blk0 + b) * kVBlock + s * kVStep + lane * 8;
-      uint32_t x[8];
-      v_load8<DT>(a, g0, x);
-      uint32_t esc = 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) esc |= (uint32_t)(lut[F::exponent(x[j])] >> 7) << j;
-      esc &= (1u << v_nvalid(a, g0)) - 1u;
-      const uint32_t cnt = __popc(esc), sc = wave_incl_scan(cnt);
-      uint32_t r = rank + sc - cnt;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (!((esc >> j) & 1u)) continue;
-        v_put_record(a, off_val, r, g0 + j, F::exponent(x[j]));
-        ++r;
+  for (uint32_t q = 0; q < kPerWave; ++q) {
+    const uint32_t n_b = bp[q + 1] - bp[q];
+    if (n_b <= kVSlotCap) {
+      if (lane < a.ahead && lane < n_b) sink.put(first + bp[q] + lane, elem0 + q * kVBlock + (rec[q] & 0xffffu), rec[q] >> 16);
+      if (a.ahead + lane < n_b) sink.put(first + bp[q] + a.ahead + lane, elem0 + q * kVBlock + (rec2[q] & 0xffffu), rec2[q] >> 16);
+    }
+    many |= n_b > a.ahead + 64 ? 1u : 0u;
+  }
+  if (many) {
+#pragma unroll 1
+    for (uint32_t q = 0; q < kPerWave; ++q) {
+      const uint32_t b = wave * kPerWave + q, from = s_bp[b], n_b = s_bp[b + 1] - from;
+      if (n_b > kVSlotCap) continue;
+      for (uint32_t i = a.ahead + 64 + lane; i < n_b; i += 64) {
+        const uint32_t r = a.slots[(blk0 + b) * kVSlotCap + i];
+        sink.put(first + from + i, elem0 + q * kVBlock + (r & 0xffffu), r >> 16);
       }
-      rank += __builtin_amdgcn_readlane(sc, 63);
+    }
+    // blocks whose records did not fit their slots
+#pragma unroll 1
+    for (uint32_t b = wave * kPerWave; b < (wave + 1) * kPerWave && b < blocks_here; ++b) {
+      if (s_bp[b + 1] - s_bp[b] <= kVSlotCap) continue;
+      uint32_t rank = first + s_bp[b];
+#pragma unroll 1
+      for (uint32_t s = 0; s < 2; ++s) {
+        const uint64_t g0 = (blk0 + b) * kVBlock + s * kVStep + lane * 8;
+        uint32_t w[F::NW];
+        v_load8<DT, false>(a, g0, w);
+        uint32_t esc = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) esc |= (lut[v_exponent_of<DT>(w, j)] >> 16) << j;
+        esc &= (1u << v_nvalid(a, g0)) - 1u;
+        const uint32_t cnt = __popc(esc), sc = wave_incl_scan(cnt);
+        uint32_t r = rank + sc - cnt;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if (!((esc >> j) & 1u)) continue;
+          sink.put(r, (uint32_t)g0 + j, v_exponent_of<DT>(w, j));
+          ++r;
+        }
+        rank += __builtin_amdgcn_readlane(sc, 63);
+      }
     }
   }
   if (g != 0) return;
@@ -400,197 +628,233 @@ __device__ inline void v_flag_bad(const VArgs& a) {
 }
 
 // The header as every wave reads it: lane i < 16 holds word i.  Words 6..9 (M, total) are checked against the
-// layout, the others against what the call expects.  Wave-uniform result; M through m_out.
-__device__ inline bool v_check_header(const VArgs& a, uint32_t hw, int lane, uint32_t* m_out) {
-  const bool word_ok = lane >= 16 || (lane >= 6 && lane <= 9) || hw == a.hdr[lane & 15];
-  const uint64_t M = __builtin_amdgcn_readlane(hw, 6) | ((uint64_t)__builtin_amdgcn_readlane(hw, 7) << 32);
-  const uint64_t total = __builtin_amdgcn_readlane(hw, 8) | ((uint64_t)__builtin_amdgcn_readlane(hw, 9) << 32);
+// layout, the others against what the call expects (word by word with scalar compares: the expected words are kernel
+// arguments, and a vector load of them would return behind the loads of the planes).  Wave-uniform result; M through
+// m_out.
+__device__ inline bool v_check_header(const VArgs& a, uint32_t hw, uint32_t* m_out) {
+  bool words_ok = true;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (i < 6 || i > 9) words_ok = words_ok && (uint32_t)__builtin_amdgcn_readlane(hw, i) == a.hdr[i];
+  const uint64_t M = (uint32_t)__builtin_amdgcn_readlane(hw, 6) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hw, 7) << 32);
+  const uint64_t total = (uint32_t)__builtin_amdgcn_readlane(hw, 8) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hw, 9) << 32);
   *m_out = (uint32_t)M;
-  return __builtin_amdgcn_ballot_w64(!word_ok) == 0 && M <= a.n &&
-         total == a.off_pos + a256(a.pos_bytes * M) + v_val_bytes(M, a.val_bits) && total <= a.capacity;
+  return words_ok && M <= a.n && total == a.off_pos + a256(a.pos_bytes * M) + v_val_bytes(M, a.val_bits) && total <= a.capacity;
 }
 
 // One block of 1024 elements per wave.  Everything that depends on nothing -- the header, the offsets of the
 // block's chunks, the block's slices of both planes -- is fetched at once; the escape records of the chunks
-// follow as soon as the offsets are known and travel while the planes are decoded into an LDS tile; the records
-// are applied to the tile (in the sentinel mode the exponent of every sentinel is fetched while decoding
-// instead), and the tile is stored.  In the absolute mode the correction is left to v_scatter_kernel.
+// follow as soon as the offsets are known and travel while the planes are decoded in registers, two elements per
+// table entry.  A block with records goes through an LDS tile, where they are applied a lane each (in the sentinel
+// mode by the lane that holds the sentinel, its exponent from the chunk's first 64 values in LDS); a block without
+// is stored from the registers.  In the absolute mode the correction is left to v_scatter_kernel.
+// One 64 MiB BF16 tensor: 24.1 us under 3-bit codes (32.0 us with the planes picked apart element by element from LDS),
+// 22.3 us in the main format.
 template <int DT, int CB, int MODE, int CS>
 __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
   using F = VFmt<DT>;
   // escape mode, chunk size and position width are compile-time here: none of the format's choices costs a branch
   constexpr uint32_t PB = MODE == SPLITZIP_ESC_POS ? (CS == 10 ? 2u : 1u) : MODE == SPLITZIP_ESC_ABS32 ? 4u : 0u;
-  __shared__ uint8_t s_dec[16];
-  __shared__ __attribute__((aligned(16))) uint8_t s_sm[kWaves][128 * F::SB];
-  __shared__ __attribute__((aligned(16))) uint8_t s_code[kWaves][128 * CB];
-  __shared__ __attribute__((aligned(16))) uint8_t s_tile[kWaves][kVBlock * F::ES];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid < 16) s_dec[tid] = (uint32_t)tid < a.k ? a.dec[tid] : 0;
+  constexpr uint32_t kPairs = 1u << (2 * CB), kPairMask = kPairs - 1u, per_blk = kVBlock >> CS, chunk = 1u << CS;
+  __shared__ uint32_t tbl[kPairs];
+  __shared__ __attribute__((aligned(16))) uint32_t s_tile[kWaves][kVBlock * F::ES / 4];
+  __shared__ uint8_t s_val[kWaves][MODE == SPLITZIP_ESC_SENTINEL ? 64 * per_blk : 1];
+  const uint32_t tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   const uint64_t blk = (uint64_t)blockIdx.x * kWaves + wave;
-  const bool live = blk * kVBlock < a.n;
-  const uint32_t per_blk = kVBlock >> CS, chunk = 1u << CS;
+  const bool live = blk * kVBlock < a.n, full = (blk + 1) * kVBlock <= a.n;
   const uint64_t c_first = blk * per_blk;
 
   const uint32_t hw = lane < 16 ? reinterpret_cast<const uint32_t*>(a.in)[lane] : 0u;
   uint32_t my_off = 0;   // lane q holds the offset of chunk c_first + q
-  if (live && MODE != SPLITZIP_ESC_ABS32 && (uint32_t)lane <= per_blk && c_first + lane <= a.n_chunks)
+  if (live && MODE != SPLITZIP_ESC_ABS32 && lane <= per_blk && c_first + lane <= a.n_chunks)
     my_off = a.offs[c_first + lane];
-  // The block's slices of both planes (whole dwords; the sections are padded, so nothing past them is read) are
-  // asked for now and kept in registers: they go to LDS further down, once the escape records -- whose addresses
-  // need the offsets and the header, asked for before the planes -- are on their way too.
-  constexpr uint32_t SMD = (32u * F::SB + 63u) / 64u, CDD = (32u * CB + 63u) / 64u;   // dwords per lane
-  uint32_t psm[SMD], pcd[CDD];
-  {
-    const uint64_t sm0 = blk * (kVBlock / 8) * F::SB, code0 = blk * (kVBlock / 8) * CB;
+  // the block's slices of both planes (the sections are padded, so nothing past them is read)
+  uint32_t sm[2][2], cd[2][2];
 #pragma unroll
-    for (uint32_t q = 0; q < SMD; ++q) {
-      const uint32_t i = lane + 64 * q;
-      psm[q] = live && i < 32u * F::SB && sm0 + 4 * i < a256(a.sm_bytes) ? ld_stream(reinterpret_cast<const uint32_t*>(a.in + a.off_sm + sm0) + i) : 0u;
-    }
-#pragma unroll
-    for (uint32_t q = 0; q < CDD; ++q) {
-      const uint32_t i = lane + 64 * q;
-      pcd[q] = live && i < 32u * CB && code0 + 4 * i < a256(a.code_bytes) ? ld_stream(reinterpret_cast<const uint32_t*>(a.in + a.off_code + code0) + i) : 0u;
+  for (uint32_t s = 0; s < 2; ++s) {
+    const uint64_t g = blk * kVBlock + s * kVStep;
+    if (full) {
+      v_load_plane<F::SB, true>(a.in + a.off_sm, g / 8 * F::SB, 0, lane, sm[s]);
+      v_load_plane<CB, true>(a.in + a.off_code, g / 8 * CB, 0, lane, cd[s]);
+    } else {
+      v_load_plane<F::SB, false>(a.in + a.off_sm, g / 8 * F::SB, a256(a.sm_bytes), lane, sm[s]);
+      v_load_plane<CB, false>(a.in + a.off_code, g / 8 * CB, a256(a.code_bytes), lane, cd[s]);
     }
   }
+  // the decode table: both exponents of a pair of codes in place (entries beyond k are zero)
+  if (tid < kPairs) {
+    const u32x4 d = v_dec16(a);
+    tbl[tid] = F::pair(dec16_at(d, tid & ((1u << CB) - 1u)), dec16_at(d, tid >> CB));
+  }
   uint32_t M;
-  const bool ok = v_check_header(a, hw, lane, &M);
+  const bool ok = v_check_header(a, hw, &M);
   if (blockIdx.x == 0 && tid == 0) {
     if (a.sizes) {
-      a.sizes->total_bytes = __builtin_amdgcn_readlane(hw, 8) | ((uint64_t)__builtin_amdgcn_readlane(hw, 9) << 32);
+      a.sizes->total_bytes = (uint32_t)__builtin_amdgcn_readlane(hw, 8) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hw, 9) << 32);
       a.sizes->n_escapes = M;
     }
     if (!ok) v_flag_bad(a);
   }
-  lds_barrier();            // s_dec (an LDS-only barrier: the planes stay on their way)
+  lds_barrier();            // the table (an LDS-only barrier: the planes stay on their way)
   if (!ok || !live) return;   // nothing of a stream with a bad header is followed
   const uint64_t off_val = a.off_pos + a256((uint64_t)PB * M);
-  const uint32_t sentinel = (1u << CB) - 1u;
+  constexpr uint32_t sentinel = (1u << CB) - 1u;
   // codes the codebook does not have can only occur if it leaves some unused (wave-uniform: no per-element work otherwise)
   const bool check_codes = a.k + (MODE == SPLITZIP_ESC_SENTINEL ? 1u : 0u) < (1u << CB);
   bool bad = false;
 
-  // chunk-relative records: the first 64 of every chunk of the block are fetched now
-  uint32_t rec_p[4] = {0, 0, 0, 0}, rec_e[4] = {0, 0, 0, 0}, rec_lo[4], rec_n[4] = {0, 0, 0, 0};
-  if (MODE == SPLITZIP_ESC_POS) {
+  // the first 64 records of every chunk of the block are fetched now (in the sentinel mode: values without positions)
+  uint32_t rec_p[per_blk], rec_e[per_blk], rec_lo[per_blk], rec_n[per_blk], any = 0;
 #pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-      rec_lo[q] = 0;
-      if (q >= per_blk || c_first + q >= a.n_chunks) continue;
-      const uint32_t lo = __builtin_amdgcn_readlane(my_off, q), hi = __builtin_amdgcn_readlane(my_off, q + 1);
-      const uint64_t first = (c_first + q) << CS, len = first + chunk <= a.n ? chunk : a.n - first;
-      if (hi < lo || hi - lo > len || hi > M) { bad = true; continue; }
-      rec_lo[q] = lo;
-      rec_n[q] = hi - lo;
-      if ((uint32_t)lane < hi - lo) {
+  for (uint32_t q = 0; q < per_blk; ++q) {
+    rec_p[q] = 0; rec_e[q] = 0; rec_lo[q] = 0; rec_n[q] = 0;
+    if (MODE == SPLITZIP_ESC_ABS32 || c_first + q >= a.n_chunks) continue;
+    const uint32_t lo = __builtin_amdgcn_readlane(my_off, q), hi = __builtin_amdgcn_readlane(my_off, q + 1);
+    const uint64_t first = (c_first + q) << CS, len = first + chunk <= a.n ? chunk : a.n - first;
+    rec_lo[q] = lo;
+    if (hi < lo || hi - lo > len || hi > M) {
+      bad = bad || MODE == SPLITZIP_ESC_POS;   // sentinels are looked at one by one
+      if (MODE == SPLITZIP_ESC_POS) continue;
+    }
+    rec_n[q] = hi - lo;
+    any |= hi - lo;
+    if (MODE == SPLITZIP_ESC_POS) {
+      if (lane < hi - lo) {
         rec_p[q] = PB == 2 ? reinterpret_cast<const uint16_t*>(a.in + a.off_pos)[lo + lane] : a.in[a.off_pos + lo + lane];
         rec_e[q] = v_value(a, off_val, lo + lane);
       }
+    } else if ((uint64_t)lo + lane < hi && (uint64_t)lo + lane < M) {
+      rec_e[q] = v_value(a, off_val, (uint64_t)lo + lane);
     }
   }
 
-  // the planes into LDS now (every lane its dwords), so that each lane can pick its elements' bits
+  // dense decode; the codes all ones are the sentinels
+  uint32_t o[2][F::NW], sent[2] = {0, 0};
 #pragma unroll
-  for (uint32_t q = 0; q < SMD; ++q)
-    if (lane + 64 * q < 32u * F::SB) reinterpret_cast<uint32_t*>(s_sm[wave])[lane + 64 * q] = psm[q];
+  for (uint32_t s = 0; s < 2; ++s) {
+    v_plane_fields<F::SB>(sm[s], lane);
+    v_plane_fields<CB>(cd[s], lane);
+    const uint32_t c = cd[s][0], nv = full ? 8u : v_nvalid(a, blk * kVBlock + s * kVStep + lane * 8);
+    F::unpack(sm[s], o[s]);
 #pragma unroll
-  for (uint32_t q = 0; q < CDD; ++q)
-    if (lane + 64 * q < 32u * CB) reinterpret_cast<uint32_t*>(s_code[wave])[lane + 64 * q] = pcd[q];
-  v_lds_settle();
-  uint32_t carry = 0;
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const uint64_t g = blk * kVBlock + s * kVStep, g0 = g + lane * 8;
-    const uint64_t smw = v_lds_get<F::SB>(&s_sm[wave][(s * 64 + lane) * F::SB]);
-    const uint32_t cw = (uint32_t)v_lds_get<CB>(&s_code[wave][(s * 64 + lane) * CB]);
-    const uint32_t vmask = (1u << v_nvalid(a, g0)) - 1u;   // bit j: element j exists
-    uint32_t w[8], sent = 0, unknown = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t av = (uint32_t)(smw >> (F::SB * j)) & ((1u << F::SB) - 1u), code = (cw >> (CB * j)) & sentinel;
-      sent |= (uint32_t)(code == sentinel) << j;
-      if (check_codes) unknown |= (uint32_t)(code >= a.k) << j;
-      w[j] = F::combine(av, s_dec[code & 15u]);
+    for (uint32_t b = 0; b < 4; ++b) {
+      const uint32_t t = tbl[(c >> (2 * CB * b)) & kPairMask];
+      if (F::ES == 2) o[s][b & (F::NW - 1)] |= t;
+      else o[s][b >> 1] |= t << (16 * (b & 1));
     }
-    sent = MODE == SPLITZIP_ESC_SENTINEL ? sent & vmask : 0u;
-    if (unknown & vmask & ~sent) bad = true;
     if (MODE == SPLITZIP_ESC_SENTINEL) {
-      // rank of every sentinel inside its chunk, then its exponent from the value array
-      const uint32_t cnt = __popc(sent), incl = wave_incl_scan(cnt);
-      const uint32_t t31 = __builtin_amdgcn_readlane(incl, 31), t63 = __builtin_amdgcn_readlane(incl, 63);
-      uint32_t r, r_end;
-      if (CS == 10) {
-        r = __builtin_amdgcn_readlane(my_off, 0) + carry + incl - cnt;
-        r_end = __builtin_amdgcn_readlane(my_off, 1);
-        carry = t63;
+      sent[s] = CB == 4 ? c & (c >> 1) & (c >> 2) & (c >> 3) & 0x11111111u : c & (c >> 1) & (c >> 2) & 0x249249u;
+      if (nv < 8) sent[s] &= (1u << (CB * nv)) - 1u;
+    }
+    if (check_codes) {
+#pragma unroll
+      for (uint32_t j = 0; j < 8; ++j) {
+        const uint32_t code = (c >> (CB * j)) & sentinel;
+        if (j < nv && code >= a.k && !(MODE == SPLITZIP_ESC_SENTINEL && code == sentinel)) bad = true;
+      }
+    }
+  }
+  if (MODE == SPLITZIP_ESC_SENTINEL) any = __ballot((sent[0] | sent[1]) != 0) != 0;
+
+  uint32_t* tile = s_tile[wave];
+  if (any || !full) {
+#pragma unroll
+    for (uint32_t s = 0; s < 2; ++s) {
+      if (F::ES == 2) reinterpret_cast<u32x4*>(tile)[s * 64 + lane] = u32x4{o[s][0], o[s][1], o[s][F::NW - 2], o[s][F::NW - 1]};
+      else reinterpret_cast<u32x2*>(tile)[s * 64 + lane] = u32x2{o[s][0], o[s][1]};
+    }
+    // one element of the tile gets the exponent e
+    auto patch = [&](uint32_t at, uint32_t e) {
+      if (F::ES == 2) {
+        uint16_t* t = reinterpret_cast<uint16_t*>(tile) + at;
+        *t = (uint16_t)F::combine(F::signmant(*t), e);
       } else {
-        const uint32_t q = 2 * s + (lane >> 5);   // the chunk of this half-wave, inside the block
-        const bool there = c_first + q < a.n_chunks;
-        const uint32_t o0 = __builtin_amdgcn_readlane(my_off, 2 * s), o1 = __builtin_amdgcn_readlane(my_off, 2 * s + 1),
-                       o2 = __builtin_amdgcn_readlane(my_off, 2 * s + 2);
-        r = there ? (lane < 32 ? o0 : o1) + incl - cnt - (lane >= 32 ? t31 : 0u) : 0u;
-        r_end = there ? (lane < 32 ? o1 : o2) : 0u;
+        uint8_t* t = reinterpret_cast<uint8_t*>(tile) + at;
+        *t = (uint8_t)F::combine(F::signmant(*t), e);
       }
+    };
+    if (MODE == SPLITZIP_ESC_SENTINEL) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if (!((sent >> j) & 1u)) continue;
-        uint32_t e = 0;
-        if (r < r_end && r < M) e = v_value(a, off_val, r);
-        else bad = true;
-        if (e >= (uint32_t)F::EXPS) { bad = true; e = 0; }
-        const uint32_t av = (uint32_t)(smw >> (F::SB * j)) & ((1u << F::SB) - 1u);
-        w[j] = F::combine(av, e);
-        ++r;
-      }
+      for (uint32_t q = 0; q < per_blk; ++q) s_val[wave][64 * q + lane] = (uint8_t)rec_e[q];
     }
-    if (F::ES == 2)
-      *reinterpret_cast<u32x4*>(&s_tile[wave][(s * kVStep + lane * 8) * 2]) =
-          u32x4{w[0] | (w[1] << 16), w[2] | (w[3] << 16), w[4] | (w[5] << 16), w[6] | (w[7] << 16)};
-    else
-      *reinterpret_cast<u32x2*>(&s_tile[wave][s * kVStep + lane * 8]) =
-          u32x2{w[0] | (w[1] << 8) | (w[2] << 16) | (w[3] << 24), w[4] | (w[5] << 8) | (w[6] << 16) | (w[7] << 24)};
-  }
-
-  v_lds_settle();
-  if (MODE == SPLITZIP_ESC_POS) {
-    // the records of the block's chunks, one lane each, straight into the tile
+    v_lds_settle();
+    if (MODE == SPLITZIP_ESC_SENTINEL) {
+      uint32_t carry = 0;
 #pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-      if (q >= per_blk || rec_n[q] == 0) continue;
-      const uint64_t first = (c_first + q) << CS, len = first + chunk <= a.n ? chunk : a.n - first;
-      for (uint32_t i = lane; i < rec_n[q]; i += 64) {
-        uint32_t p = rec_p[q], e = rec_e[q];
-        if (i >= 64) {   // a chunk with more than 64 escapes: the rest is fetched here
-          p = PB == 2 ? reinterpret_cast<const uint16_t*>(a.in + a.off_pos)[rec_lo[q] + i] : a.in[a.off_pos + rec_lo[q] + i];
-          e = v_value(a, off_val, rec_lo[q] + i);
-        }
-        // a chunk's positions ascend: the record before this one (the lane below holds it, or memory does)
-        uint32_t before = (uint32_t)__shfl_up((int)p, 1);
-        if (lane == 0 && i > 0) before = PB == 2 ? reinterpret_cast<const uint16_t*>(a.in + a.off_pos)[rec_lo[q] + i - 1] : a.in[a.off_pos + rec_lo[q] + i - 1];
-        if (p >= len || (i > 0 && p <= before) || e >= (uint32_t)F::EXPS) { bad = true; continue; }
-        const uint32_t at = q * chunk + p;
-        if (F::ES == 2) {
-          uint16_t* t = reinterpret_cast<uint16_t*>(s_tile[wave]) + at;
-          *t = (uint16_t)F::combine(F::signmant(*t), e);
+      for (uint32_t s = 0; s < 2; ++s) {
+        // rank of every sentinel inside its chunk, then its exponent from the chunk's values
+        uint32_t excl, low;
+        const uint32_t tot = v_sparse_excl(__popc(sent[s]), excl, low);
+        const uint32_t q = CS == 10 ? 0u : 2 * s + (lane >> 5);   // the lane's chunk inside the block
+        uint32_t lo = rec_lo[0], n_q = rec_n[0], rank = excl + carry;
+        if (CS == 8) {
+          const uint32_t q0 = (2 * s) & (per_blk - 1), q1 = (2 * s + 1) & (per_blk - 1);
+          lo = lane < 32 ? rec_lo[q0] : rec_lo[q1];
+          n_q = lane < 32 ? rec_n[q0] : rec_n[q1];
+          rank = lane < 32 ? excl : excl - low;
         } else {
-          uint8_t* t = s_tile[wave] + at;
-          *t = (uint8_t)F::combine(F::signmant(*t), e);
+          carry = tot;
         }
+        const uint64_t hi = c_first + q < a.n_chunks ? (uint64_t)(uint32_t)(lo + n_q) : 0u;   // the offset behind the chunk's
+        uint32_t m = sent[s];
+        while (m) {
+          const uint32_t bit = (uint32_t)__ffs(m) - 1u, j = CB == 4 ? bit >> 2 : (bit * 11u) >> 5;   // bit / CB
+          m &= m - 1;
+          const uint64_t r = (uint64_t)(uint32_t)(lo + rank);
+          uint32_t e = 0;
+          if (r < hi && r < M) e = rank < 64 && r >= lo ? (uint32_t)s_val[wave][64 * q + rank] : v_value(a, off_val, r);
+          else bad = true;
+          if (e >= (uint32_t)F::EXPS) { bad = true; e = 0; }
+          patch(s * kVStep + lane * 8 + j, e);
+          ++rank;
+        }
+      }
+    }
+    if (MODE == SPLITZIP_ESC_POS) {
+      // the records of the block's chunks, one lane each, straight into the tile
+#pragma unroll
+      for (uint32_t q = 0; q < per_blk; ++q) {
+        if (rec_n[q] == 0) continue;
+        const uint64_t first = (c_first + q) << CS, len = first + chunk <= a.n ? chunk : a.n - first;
+        for (uint32_t i = lane; i < rec_n[q]; i += 64) {
+          uint32_t p = rec_p[q], e = rec_e[q];
+          if (i >= 64) {   // a chunk with more than 64 escapes: the rest is fetched here
+            p = PB == 2 ? reinterpret_cast<const uint16_t*>(a.in + a.off_pos)[rec_lo[q] + i] : a.in[a.off_pos + rec_lo[q] + i];
+            e = v_value(a, off_val, rec_lo[q] + i);
+          }
+          // a chunk's positions ascend: the record before this one (the lane below holds it, or memory does)
+          uint32_t before = (uint32_t)__shfl_up((int)p, 1);
+          if (lane == 0 && i > 0) before = PB == 2 ? reinterpret_cast<const uint16_t*>(a.in + a.off_pos)[rec_lo[q] + i - 1] : a.in[a.off_pos + rec_lo[q] + i - 1];
+          if (p >= len || (i > 0 && p <= before) || e >= (uint32_t)F::EXPS) { bad = true; continue; }
+          patch(q * chunk + p, e);
+        }
+      }
+    }
+    v_lds_settle();
+#pragma unroll
+    for (uint32_t s = 0; s < 2; ++s) {
+      if (F::ES == 2) {
+        const u32x4 v = reinterpret_cast<const u32x4*>(tile)[s * 64 + lane];
+        o[s][0] = v.x; o[s][1] = v.y; o[s][F::NW - 2] = v.z; o[s][F::NW - 1] = v.w;
+      } else {
+        const u32x2 v = reinterpret_cast<const u32x2*>(tile)[s * 64 + lane];
+        o[s][0] = v.x; o[s][1] = v.y;
       }
     }
   }
 
-  v_lds_settle();
-  // the tile, 16 bytes per lane and step
   const uint64_t e0 = blk * kVBlock;
-  const uint32_t bytes = F::ES * kVBlock;
-  if (e0 + kVBlock <= a.n) {
-    for (uint32_t i = lane; i < bytes / 16; i += 64)
-      st_stream(reinterpret_cast<u32x4*>(a.out + e0 * F::ES) + i, reinterpret_cast<const u32x4*>(s_tile[wave])[i]);
+  if (full) {
+#pragma unroll
+    for (uint32_t s = 0; s < 2; ++s) {
+      if (F::ES == 2) st_stream(reinterpret_cast<u32x4*>(a.out + 2 * e0) + s * 64 + lane, u32x4{o[s][0], o[s][1], o[s][F::NW - 2], o[s][F::NW - 1]});
+      else st_stream(reinterpret_cast<u32x2*>(a.out + e0) + s * 64 + lane, u32x2{o[s][0], o[s][1]});
+    }
   } else {
     for (uint32_t i = lane; e0 + i < a.n; i += 64) {
-      if (F::ES == 2) reinterpret_cast<uint16_t*>(a.out)[e0 + i] = reinterpret_cast<const uint16_t*>(s_tile[wave])[i];
-      else a.out[e0 + i] = s_tile[wave][i];
+      if (F::ES == 2) reinterpret_cast<uint16_t*>(a.out)[e0 + i] = reinterpret_cast<const uint16_t*>(tile)[i];
+      else a.out[e0 + i] = reinterpret_cast<const uint8_t*>(tile)[i];
     }
   }
   if (bad) v_flag_bad(a);
@@ -602,7 +866,7 @@ __global__ __launch_bounds__(kThreads) void v_scatter_kernel(const VArgs a) {
   using F = VFmt<DT>;
   const int lane = threadIdx.x & 63;
   uint32_t M;
-  if (!v_check_header(a, lane < 16 ? reinterpret_cast<const uint32_t*>(a.in)[lane] : 0u, lane, &M)) return;
+  if (!v_check_header(a, lane < 16 ? reinterpret_cast<const uint32_t*>(a.in)[lane] : 0u, &M)) return;
   const uint64_t off_val = a.off_pos + a256(4ull * M);
   bool bad = false;
   for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < M; i += (uint64_t)gridDim.x * kThreads) {
