@@ -447,6 +447,7 @@ struct TileArgs {
   uint32_t slot_cap;              // records per tile slot (the same for all tensors of the launch)
   uint32_t finish_groups;         // groups of kGroup tiles per workgroup of the finishing pass, 1 to kFinishMost
   uint32_t use_group_sums;        // the finishing pass reads sums of kSumGroup tile counts (tile_group_sum_kernel) instead of all tile counts
+  uint32_t by_xcd;                // the dense pass takes its tiles in xcd_order
   Words paging;                   // table and page geometry shared by all tensors (table null: contiguous tensors); base unused
   const splitzip_codebook* d_cbs; // nullable: n_items codebooks in device memory, used instead of dec
   uint8_t dec[kBatchMax][16];     // every tensor's codebook, as its 16 decode entries: the kernels build the encode table from them
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
   const uint32_t item = blockIdx.y;
   const TileGeom G = tile_geom(a, item);
   const Planes& P = G.P;
-  const uint32_t t = blockIdx.x;
+  const uint32_t t = a.by_xcd ? xcd_order(blockIdx.x, gridDim.x) : blockIdx.x;
   if (t >= G.n_tiles) return;
   const uint32_t r0 = t << a.tile_shift, nb = P.n_chunks - r0 < G.tile_chunks ? P.n_chunks - r0 : G.tile_chunks;
   const uint32_t w0 = (uint32_t)wave * a.cpt;                                   // the wave's first chunk inside the tile

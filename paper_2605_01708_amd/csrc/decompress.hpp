@@ -408,6 +408,7 @@ struct DecompressBatchArgs {
   Words paging;            // as in CompressBatchArgs
   uint8_t dec[kBatchMax][16];   // every stream's codebook
   const splitzip_codebook* d_cbs;   // nullable: n_items codebooks in device memory, used instead of dec
+  uint32_t by_xcd;         // the workgroups take their tiles in xcd_order
   uint32_t own_dec;        // 1: every stream is decoded with the 16 decode entries of its own header
 };
 
@@ -418,7 +419,8 @@ __global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const Decomp
   const DBatchItem it = b.item[blockIdx.y];
   const Layout L = make_layout(it.n, (int)b.dtype);
   const uint32_t n_tiles = (uint32_t)((L.n_chunks + (uint64_t)kWaves * b.cpw - 1) / (kWaves * b.cpw));
-  if (blockIdx.x >= (n_tiles ? n_tiles : 1u)) return;
+  const uint32_t tile = b.by_xcd ? xcd_order(blockIdx.x, gridDim.x) : blockIdx.x;
+  if (tile >= (n_tiles ? n_tiles : 1u)) return;
   DecompressArgs a;
   a.comp = it.comp;
   a.w = item_words(b.paging, it.out);
@@ -434,7 +436,7 @@ __global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const Decomp
   a.reg_patch_max = b.reg_patch_max;
   u32x4 dec16 = u32x4{0u, 0u, 0u, 0u};
   if (F::kScalarDec) dec16 = b.own_dec ? load_dec16(it.comp + kHeaderDecOffset) : b.d_cbs ? load_dec16(b.d_cbs[blockIdx.y].dec) : dec16_from(b.dec[blockIdx.y]);
-  decompress_tile<F>(a, dec16, b.own_dec ? it.comp + kHeaderDecOffset : b.d_cbs ? b.d_cbs[blockIdx.y].dec : b.dec[blockIdx.y], blockIdx.x, tbl, lds_chunk);   // a.dec stays unset: the table comes from the kernel arguments
+  decompress_tile<F>(a, dec16, b.own_dec ? it.comp + kHeaderDecOffset : b.d_cbs ? b.d_cbs[blockIdx.y].dec : b.dec[blockIdx.y], tile, tbl, lds_chunk);   // a.dec stays unset: the table comes from the kernel arguments
 }
 
 #endif  // SPLITZIP_DECOMPRESS_HPP

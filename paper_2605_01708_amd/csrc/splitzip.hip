@@ -652,6 +652,10 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       a.slot_cap = (uint32_t)(per_tile < kSlotCapMost ? per_tile : kSlotCapMost);
     }
     a.paging = paging;
+    // From 16 384 tiles (256 MB of words) on.  us per call, in the order of the tiles and in xcd_order: BF16 1241 and
+    // 1201 (262 144 tiles), 314 and 307 (65 536), 83.2 and 82.4 (16 384); E5M2 690 and 665 (131 072), 173.4 and 171.7
+    // (32 768), 49.7 and 49.8 (8192).
+    a.by_xcd = tiles_max * k >= 16384 ? 1u : 0u;
     const unsigned groups_max = (unsigned)((tiles_max + kGroup - 1) / kGroup), sums_max = (unsigned)((tiles_max + kSumGroup - 1) / kSumGroup);
     // many groups in the launch: several per workgroup, as long as the chip still gets a few workgroups per CU
     a.finish_groups = 1;
@@ -842,6 +846,10 @@ int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dty
     a.reg_patch_max = kRegPatchDefault;
     uint64_t gx = (chunks_max + (uint64_t)kWaves * a.cpw - 1) / (kWaves * a.cpw);
     if (gx < 1) gx = 1;
+    // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 168.6 and 167.6
+    // (16 384), 46.8 and 46.8 (4096); BF16 1258 and 1237 (262 144), 1172 and 1152 (240 064), but 620 and 624 (131 072)
+    // and 301 and 301 (65 536).
+    a.by_xcd = gx * k >= (dtype == SPLITZIP_BF16 ? 196608u : 16384u) ? 1u : 0u;
     const dim3 grid((unsigned)gx, k);
     if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL(decompress_batch_kernel<DBf16>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), a);
     else hipLaunchKernelGGL(decompress_batch_kernel<DE5m2>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), a);
