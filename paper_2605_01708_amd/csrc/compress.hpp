@@ -328,12 +328,14 @@ struct Bf16 {
 #pragma unroll
       for (int d = 0; d < 4; ++d) asm volatile("" : "+v"(r.w[h][d]));
   }
-  // A workgroup of four waves takes a tile of 4 x kCpt chunks (16 KB of words).  Four workgroups per CU serve BF16
-  // best (one launch pair over 64 tensors of 64 MiB: 1245-1259 us against 1266-1268 us with five, 1298 us with
-  // eight and 1306 us with three); unused LDS asked for at the launch sets the number.
+  // A workgroup of four waves takes a tile of 4 x kCpt chunks (16 KB of words).  Eight workgroups per CU, what the
+  // registers allow, serve launches of few tiles best and five those of many: us per call with eight / five / four,
+  // 1219 / 1199 / 1203 (262 144 tiles), 309 / 306 / 307 (65 536), 81.6 / 81.6 / 82.2 (16 384), 45.1 / 45.5 / 46.0
+  // (8192), 26.5 / 26.9 / 27.1 (4096: one tensor), 17.4 / 18.1 / 18.0 (2048); unused LDS asked for at the launch sets
+  // the number (compress_launch).
   static constexpr uint32_t kCpt = 2;
   static constexpr int kWavesPerSimd = 8;
-  static constexpr uint32_t kTileLdsPad = 28000;
+  static constexpr uint32_t kTileLdsPad = 22000;   // five workgroups per CU
   static constexpr int kLutShift = 0;       // the LDS encode table holds the entry of exponent e in slot e
   // a chunk goes the fast way if it is complete (then nothing of a pad is its business: N is a multiple of 1024 there)
   __device__ static inline bool full(const Planes& a, uint64_t cbase) { return cbase + kChunk <= a.n; }
@@ -356,7 +358,6 @@ struct E5m2 {
   // against 750 us with six and 790 us with five)
   static constexpr uint32_t kCpt = 4;
   static constexpr int kWavesPerSimd = 8;
-  static constexpr uint32_t kTileLdsPad = 0;
   // The LDS encode table holds the entry of exponent e in slots 2 e and 2 e + 1: its byte offset is then
   // the word's byte with the sign and mantissa bits masked off, one instruction per element.
   static constexpr int kLutShift = 1;

@@ -652,10 +652,12 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       a.slot_cap = (uint32_t)(per_tile < kSlotCapMost ? per_tile : kSlotCapMost);
     }
     a.paging = paging;
-    // From 16 384 tiles (256 MB of words) on.  us per call, in the order of the tiles and in xcd_order: BF16 1241 and
+    // Launches of many tiles, from 16 384 (256 MB of words) on, take them in xcd_order, and BF16 with fewer workgroups
+    // per CU (Bf16::kTileLdsPad).  us per call, in the order of the tiles and in xcd_order: BF16 1241 and
     // 1201 (262 144 tiles), 314 and 307 (65 536), 83.2 and 82.4 (16 384); E5M2 690 and 665 (131 072), 173.4 and 171.7
     // (32 768), 49.7 and 49.8 (8192).
-    a.by_xcd = tiles_max * k >= 16384 ? 1u : 0u;
+    const bool many = tiles_max * k >= 16384;
+    a.by_xcd = many ? 1u : 0u;
     const unsigned groups_max = (unsigned)((tiles_max + kGroup - 1) / kGroup), sums_max = (unsigned)((tiles_max + kSumGroup - 1) / kSumGroup);
     // many groups in the launch: several per workgroup, as long as the chip still gets a few workgroups per CU
     a.finish_groups = 1;
@@ -670,8 +672,8 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     a.use_group_sums = tiles_max > kDirectTiles || (uint64_t)fgroups * k * tiles_max * 4 > direct_budget ? 1u : 0u;
     if (tiles_max) {
       const dim3 grid((unsigned)tiles_max, k);   // one workgroup per tile, started by the hardware in the tiles' order
-      if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL((compress_tile_kernel<Bf16, Bf16::kCpt>), grid, dim3(kTileThreads), Bf16::kTileLdsPad, st, a);
-      else hipLaunchKernelGGL((compress_tile_kernel<E5m2, E5m2::kCpt>), grid, dim3(kTileThreads), E5m2::kTileLdsPad, st, a);
+      if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL((compress_tile_kernel<Bf16, Bf16::kCpt>), grid, dim3(kTileThreads), many ? Bf16::kTileLdsPad : 0u, st, a);
+      else hipLaunchKernelGGL((compress_tile_kernel<E5m2, E5m2::kCpt>), grid, dim3(kTileThreads), 0, st, a);
       if (a.use_group_sums) hipLaunchKernelGGL(tile_group_sum_kernel, dim3(sums_max, k), dim3(64), 0, st, a);
     }
     const dim3 fgrid(fgroups ? fgroups : 1u, k);
