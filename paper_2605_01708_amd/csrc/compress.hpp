@@ -428,6 +428,7 @@ constexpr uint64_t kDirectBytes = 128ull << 20;   // ... if all its workgroups t
 constexpr uint32_t kSumGroup = 64;          // beyond: sums of this many tile counts, by tile_group_sum_kernel
 constexpr uint32_t kBatchMax = 64;          // tensors per launch: their descriptors travel as kernel arguments
 constexpr uint32_t kRedo = 0x80000000u;     // in a tile's count: its records are not in its slot
+constexpr uint32_t kMore = 1u;              // in a group's mark of the finishing pass, beside kRedo
 static_assert(kGroup * kSlotAhead == kTileThreads, "every thread fetches records of one tile ahead");
 
 struct TileItem {
@@ -614,7 +615,7 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
   __shared__ uint32_t s_cnt[kFinishMost][kGroup];       // the counts of the groups' tiles, redo mark included
   __shared__ uint32_t s_tp[kFinishMost][kGroup + 1];    // escapes of a group's tiles before each tile
   __shared__ uint32_t s_red[2 * NW];
-  __shared__ uint32_t s_more[kFinishMost];              // a group has a tile with more records than were fetched ahead
+  __shared__ uint32_t s_mark[kFinishMost];              // kMore: a group has a tile with more records than were fetched ahead; kRedo: one that is encoded again
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t item = blockIdx.y;
@@ -699,10 +700,11 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
       s_tp[wave][lane] = incl - (c & ~kRedo);
     }
     if (lane == 63) s_tp[wave][kGroup] = incl;
-    const uint64_t more = __ballot((c & ~kRedo) > 2 * kSlotAhead && !(c & kRedo));
-    if (lane == 0) s_more[wave] = more != 0;
+    const uint64_t more = __ballot((c & ~kRedo) > 2 * kSlotAhead && !(c & kRedo)), again = __ballot((c & kRedo) != 0);
+    if (lane == 0) s_mark[wave] = (more ? kMore : 0u) | (again ? kRedo : 0u);
+  } else if ((uint32_t)wave < kFinishMost && lane == 0) {
+    s_mark[wave] = 0;
   }
-  build_encode_table(lut, a.dec16_of(item), tid, F::kLutShift);
   __syncthreads();
   uint32_t first = 0, M = 0;   // the rank of the first record of the group at hand; all records of the tensor
 #pragma unroll
@@ -717,6 +719,43 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
   fin.val = P.out + off_val;
   fin.val_room = P.capacity > off_val ? P.capacity - off_val : 0;
 
+  // Tiles whose records are not in their slots: once more from the words, by the offsets inside the tile that the
+  // first pass left in the table.  Rare, and kept out of the way of the groups that have none: looking at every
+  // tile's count for the mark, one LDS read after the other, was half of this kernel's time.
+  uint32_t marks = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < kFinishMost; ++q) marks |= s_mark[q];
+  if (marks & kRedo) {
+    build_encode_table(lut, a.dec16_of(item), tid, F::kLutShift);
+    __syncthreads();
+    uint32_t group_first = first;
+#pragma unroll 1
+    for (uint32_t q = 0; q < ng; ++q) {
+#pragma unroll 1
+      for (uint32_t l = 0; l < kGroup; ++l) {
+        if (!(s_cnt[q][l] & kRedo)) continue;   // uniform: the counts are the same for every thread
+        const uint32_t r0 = ((g0 + q) * kGroup + l) << a.tile_shift;
+        const uint32_t nb = P.n_chunks - r0 < G.tile_chunks ? P.n_chunks - r0 : G.tile_chunks;
+        typename F::Regs w;
+#pragma unroll 1
+        for (uint32_t k = wave; k < nb; k += NW) {
+          const uint64_t cbase = (uint64_t)(r0 + k) * kChunk;
+          const uint32_t base = group_first + s_tp[q][l] + tab[r0 + k];
+          const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_chunk(P.w, r0 + k) : 0u);
+          if (F::full(P, cbase)) {
+            F::template load<true>(P, cptr, cbase, lane, w);
+            F::template process<true, false>(P, lut, park, cbase, lane, w, base, fin);
+          } else {
+            F::template load<false>(P, cptr, cbase, lane, w);
+            F::template process<false, false>(P, lut, park, cbase, lane, w, base, fin);
+          }
+        }
+      }
+      group_first += s_tp[q][kGroup];
+    }
+    __syncthreads();   // the table has been read by whoever needed its entries as offsets inside a tile
+  }
+
 #pragma unroll
   for (uint32_t q = 0; q < kFinishMost; ++q) {
     if (q >= ng) break;
@@ -724,29 +763,6 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
     const uint32_t entries = P.n_chunks > c0 ? (P.n_chunks - c0 < group_entries ? P.n_chunks - c0 : group_entries) : 0u;
     const uint32_t* cnt = s_cnt[q];
     const uint32_t* tp = s_tp[q];
-    // tiles whose records are not in their slots: once more from the words, by the offsets inside the tile that the
-    // first pass left in the table
-    bool any_redo = false;
-    for (uint32_t l = 0; l < kGroup; ++l) {
-      if (!(cnt[l] & kRedo)) continue;   // uniform: the counts are the same for every thread
-      any_redo = true;
-      const uint32_t r0 = (t0 + l) << a.tile_shift;
-      const uint32_t nb = P.n_chunks - r0 < G.tile_chunks ? P.n_chunks - r0 : G.tile_chunks;
-      typename F::Regs w;
-      for (uint32_t k = wave; k < nb; k += NW) {
-        const uint64_t cbase = (uint64_t)(r0 + k) * kChunk;
-        const uint32_t base = first + tp[l] + tab[r0 + k];
-        const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_chunk(P.w, r0 + k) : 0u);
-        if (F::full(P, cbase)) {
-          F::template load<true>(P, cptr, cbase, lane, w);
-          F::template process<true, false>(P, lut, park, cbase, lane, w, base, fin);
-        } else {
-          F::template load<false>(P, cptr, cbase, lane, w);
-          F::template process<false, false>(P, lut, park, cbase, lane, w, base, fin);
-        }
-      }
-    }
-    if (any_redo) __syncthreads();   // the table has been read by whoever needed its entries as offsets inside a tile
     // the table entries: what lies before the tile added to the offsets inside the tile
     if ((uint32_t)tid < entries) tab[c0 + tid] = my_entry[q] + first + tp[(uint32_t)tid >> a.tile_shift];
     for (uint32_t e = tid + kTileThreads; e < entries; e += kTileThreads) tab[c0 + e] += first + tp[e >> a.tile_shift];
@@ -757,7 +773,7 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
     // The rest of the slots of tiles with more records than that: rank r of the group belongs to the last tile that
     // starts at or before r.  Two records per thread are on their way at a time.
     const uint32_t group_total = tp[kGroup];
-    if (s_more[q]) {   // a tile of the group has more records than were fetched ahead
+    if (s_mark[q] & kMore) {   // a tile of the group has more records than were fetched ahead
       auto locate = [&](uint32_t r, uint32_t& l, uint32_t& j) -> bool {
         l = 0;
 #pragma unroll
