@@ -320,6 +320,7 @@ __device__ inline uint32_t process_chunk_e5m2(const Planes& a, const uint16_t* l
 
 // the two formats as seen by the compress kernel
 struct Bf16 {
+  static constexpr int DT = SPLITZIP_BF16;
   static constexpr int ES = 2;   // bytes per word
   struct Regs { uint32_t w[2][4]; };
   __device__ static inline void arrived(Regs& r) {
@@ -348,6 +349,7 @@ struct Bf16 {
   }
 };
 struct E5m2 {
+  static constexpr int DT = SPLITZIP_FP8_E5M2;
   static constexpr int ES = 1;
   struct Regs { uint32_t w[4]; };
   __device__ static inline void arrived(Regs& r) {
@@ -373,7 +375,7 @@ struct E5m2 {
 };
 
 // header, sizes record and the zero padding behind the positions: one wave, once M is known
-__device__ void compress_write_trailer(const Planes& a, const uint8_t* dec, splitzip_sizes* sizes, uint32_t M,
+__device__ void compress_write_trailer(const Planes& a, const u32x4& dec, splitzip_sizes* sizes, uint32_t M,
                                        uint32_t err_flags, int lane) {
   const uint64_t off_val = a.off_pos + a256(2ull * M);
   const uint64_t total = off_val + M;
@@ -392,9 +394,7 @@ __device__ void compress_write_trailer(const Planes& a, const uint8_t* dec, spli
     h[4] = (uint32_t)a.n; h[5] = (uint32_t)(a.n >> 32);
     h[6] = M;
     h[8] = (uint32_t)total; h[9] = (uint32_t)(total >> 32);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      h[10 + i] = dec[4 * i] | (dec[4 * i + 1] << 8) | (dec[4 * i + 2] << 16) | ((uint32_t)dec[4 * i + 3] << 24);
+    h[10] = dec.x; h[11] = dec.y; h[12] = dec.z; h[13] = dec.w;
     uint4* ho = reinterpret_cast<uint4*>(a.out);
 #pragma unroll
     for (int i = 0; i < 4; ++i) ho[i] = make_uint4(h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]);
@@ -431,31 +431,49 @@ constexpr uint32_t kRedo = 0x80000000u;     // in a tile's count: its records ar
 constexpr uint32_t kMore = 1u;              // in a group's mark of the finishing pass, beside kRedo
 static_assert(kGroup * kSlotAhead == kTileThreads, "every thread fetches records of one tile ahead");
 
+// The arguments of a launch: what all its tensors share, then the tensors.  A workgroup needs the first part and one
+// tensor's, 144 bytes; both are fetched whole before anything is done with them (args_arrived).
 struct TileItem {
   const uint8_t* in;
   uint8_t* out;
-  uint64_t n, capacity;
+  uint64_t capacity;
+  uint32_t n;
+  uint32_t status_off;            // where the tensor's counts start in `status`
+  uint8_t dec[16];                // its codebook, as its 16 decode entries: the kernels build the encode table from them
 };
-struct TileArgs {
-  TileItem item[kBatchMax];
-  splitzip_sizes* sizes;          // n_items records
+struct TileShared {
+  splitzip_sizes* sizes;          // one record per tensor
   uint8_t* status;                // per tensor: u32 count of every tile, then u32 sum of every kSumGroup tiles
   uint8_t* stage;                 // per tensor stage_cap bytes: the tiles' slots
   uint64_t stage_cap;
-  uint32_t status_off[kBatchMax]; // where a tensor's counts start in `status`
-  uint32_t n_items, dtype;
+  const splitzip_codebook* d_cbs; // nullable: codebooks in device memory, one per tensor, used instead of dec
+  Words paging;                   // table and page geometry shared by all tensors (table null: contiguous tensors); base unused
   uint32_t cpt;                   // chunks per wave and tile, a power of two
   uint32_t tile_shift;            // log2 of the chunks per tile (4 cpt)
   uint32_t slot_cap;              // records per tile slot (the same for all tensors of the launch)
   uint32_t finish_groups;         // groups of kGroup tiles per workgroup of the finishing pass, 1 to kFinishMost
   uint32_t use_group_sums;        // the finishing pass reads sums of kSumGroup tile counts (tile_group_sum_kernel) instead of all tile counts
-  uint32_t by_xcd;                // the dense pass takes its tiles in xcd_order
-  Words paging;                   // table and page geometry shared by all tensors (table null: contiguous tensors); base unused
-  const splitzip_codebook* d_cbs; // nullable: n_items codebooks in device memory, used instead of dec
-  uint8_t dec[kBatchMax][16];     // every tensor's codebook, as its 16 decode entries: the kernels build the encode table from them
-  __device__ inline const uint8_t* dec_of(uint32_t k) const { return d_cbs ? d_cbs[k].dec : dec[k]; }
-  __device__ inline u32x4 dec16_of(uint32_t k) const { return d_cbs ? load_dec16(d_cbs[k].dec) : dec16_from(dec[k]); }
+  uint32_t xcd_row;               // not 0: the dense pass takes its tiles in xcd_order, and this is its workgroups per tensor
+  __device__ inline u32x4 dec16_of(const TileItem& it, uint32_t k) const { return d_cbs ? load_dec16(d_cbs[k].dec) : dec16_from(it.dec); }
 };
+struct TileArgs {
+  TileShared shared;
+  TileItem item[kBatchMax];
+};
+static_assert(sizeof(TileShared) == 96 && sizeof(TileItem) == 48, "whole 16-byte words for args_arrived");
+
+// Copies of both parts, all of them waited for here and once.  Left to itself the compiler fetches an argument where
+// it is used first, which for these kernels meant four or five trips to the argument block one after the other --
+// and every launch has a new block that no cache holds -- before the first load of data was on its way.  With this,
+// and a group's counts asked for beside everything else, one tensor's finishing pass went from 3.8 to 3.1 us.
+__device__ inline void args_arrived(const TileArgs& args, uint32_t item, TileShared& a, TileItem& it) {
+  u32x4 x[6], y[3];
+  __builtin_memcpy(x, &args.shared, 96);
+  __builtin_memcpy(y, &args.item[item], 48);
+  asm volatile("" : "+s"(x[0]), "+s"(x[1]), "+s"(x[2]), "+s"(x[3]), "+s"(x[4]), "+s"(x[5]), "+s"(y[0]), "+s"(y[1]), "+s"(y[2]));
+  __builtin_memcpy(&a, x, 96);
+  __builtin_memcpy(&it, y, 48);
+}
 
 // what both passes derive from the arguments for one tensor
 struct TileGeom {
@@ -465,13 +483,12 @@ struct TileGeom {
   uint32_t* group_sums;  // ceil(n_tiles / kSumGroup)
   uint32_t* slots;       // n_tiles x slot_cap records
 };
-__device__ inline TileGeom tile_geom(const TileArgs& a, uint32_t item) {
+__device__ inline TileGeom tile_geom(const TileShared& a, const TileItem& it, uint32_t item, int dtype) {
   TileGeom g;
-  const TileItem it = a.item[item];
-  g.P = make_planes(item_words(a.paging, it.in), it.out, it.n, it.capacity, (int)a.dtype);
+  g.P = make_planes(item_words(a.paging, it.in), it.out, it.n, it.capacity, dtype);
   g.tile_chunks = 1u << a.tile_shift;
   g.n_tiles = (g.P.n_chunks + g.tile_chunks - 1) >> a.tile_shift;
-  g.counts = reinterpret_cast<uint32_t*>(a.status + a.status_off[item]);
+  g.counts = reinterpret_cast<uint32_t*>(a.status + it.status_off);
   g.group_sums = g.counts + g.n_tiles;
   g.slots = reinterpret_cast<uint32_t*>(a.stage + (uint64_t)item * a.stage_cap);
   return g;
@@ -497,7 +514,7 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 // CPT: chunks of a wave whose loads are issued together, before anything else happens in the workgroup.  Wave w of
 // the tile owns the chunks [w cpt, w cpt + cpt) of the tile.
 template <typename F, int CPT>
-__global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_kernel(const TileArgs a) {
+__global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_kernel(const TileArgs args) {
   constexpr int NW = kTileThreads / 64;
   __shared__ uint16_t lut[256];
   __shared__ uint16_t stage_pk[NW][kTileStageCap];
@@ -507,16 +524,19 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t item = blockIdx.y;
-  const TileGeom G = tile_geom(a, item);
+  TileShared a;
+  TileItem it;
+  args_arrived(args, item, a, it);
+  const TileGeom G = tile_geom(a, it, item, F::DT);
   const Planes& P = G.P;
-  const uint32_t t = a.by_xcd ? xcd_order(blockIdx.x, gridDim.x) : blockIdx.x;
+  const uint32_t t = a.xcd_row ? xcd_order(blockIdx.x, a.xcd_row) : blockIdx.x;
   if (t >= G.n_tiles) return;
   const uint32_t r0 = t << a.tile_shift, nb = P.n_chunks - r0 < G.tile_chunks ? P.n_chunks - r0 : G.tile_chunks;
   const uint32_t w0 = (uint32_t)wave * a.cpt;                                   // the wave's first chunk inside the tile
   const uint32_t mine = nb > w0 ? (nb - w0 < a.cpt ? nb - w0 : a.cpt) : 0u;     // and how many it has
   uint32_t* park = reinterpret_cast<uint32_t*>(&s_park[tid]);
 
-  uint32_t wave_count = 0, my_start = 0;   // lane it: escapes of the wave before its it-th chunk
+  uint32_t wave_count = 0, my_start = 0;   // lane c: escapes of the wave before its c-th chunk
   const LdsSink lds{stage_pk[wave], stage_val[wave], 0u, kTileStageCap};
   typename F::Regs w[CPT];
   // A tile all of whose chunks are complete (every tile but a tensor's last, as a rule) takes a path without a
@@ -534,7 +554,7 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
     };
     // the words first: the table is built while they are on their way
     fetch(0);
-    build_encode_table(lut, a.dec16_of(item), tid, F::kLutShift);
+    build_encode_table(lut, a.dec16_of(it, item), tid, F::kLutShift);
     lds_barrier();
     for (uint32_t it0 = 0; it0 < a.cpt; it0 += CPT) {
       if (it0 > 0) fetch(it0);   // tiles of more than CPT chunks per wave (very large tensors)
@@ -549,27 +569,27 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
     auto fetch = [&](uint32_t it0) {
 #pragma unroll
       for (int j = 0; j < CPT; ++j) {
-        const uint32_t it = it0 + j;
-        if (it < mine) {
-          const uint64_t cbase = (uint64_t)(r0 + w0 + it) * kChunk;
-          const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_chunk(P.w, r0 + w0 + it) : 0u);
+        const uint32_t c = it0 + j;
+        if (c < mine) {
+          const uint64_t cbase = (uint64_t)(r0 + w0 + c) * kChunk;
+          const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_chunk(P.w, r0 + w0 + c) : 0u);
           if (F::full(P, cbase)) F::template load<true>(P, cptr, cbase, lane, w[j]);
           else F::template load<false>(P, cptr, cbase, lane, w[j]);
         }
       }
     };
     fetch(0);
-    build_encode_table(lut, a.dec16_of(item), tid, F::kLutShift);
+    build_encode_table(lut, a.dec16_of(it, item), tid, F::kLutShift);
     lds_barrier();
     // dense pass; the wave's escape records into its LDS staging in element order, the chunks' counts kept in lanes
     for (uint32_t it0 = 0; it0 < mine; it0 += CPT) {
       if (it0 > 0) fetch(it0);
 #pragma unroll
       for (int j = 0; j < CPT; ++j) {
-        const uint32_t it = it0 + j;
-        if (it >= mine) break;
-        const uint64_t cbase = (uint64_t)(r0 + w0 + it) * kChunk;
-        if ((uint32_t)lane == it) my_start = wave_count;
+        const uint32_t c = it0 + j;
+        if (c >= mine) break;
+        const uint64_t cbase = (uint64_t)(r0 + w0 + c) * kChunk;
+        if ((uint32_t)lane == c) my_start = wave_count;
         wave_count += F::full(P, cbase) ? F::template process<true, true>(P, lut, park, cbase, lane, w[j], wave_count, lds)
                                         : F::template process<false, true>(P, lut, park, cbase, lane, w[j], wave_count, lds);
       }
@@ -595,11 +615,17 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
     for (uint32_t i = lane; i < wave_count; i += 64) slot[i] = (uint32_t)stage_pk[wave][i] | ((uint32_t)stage_val[wave][i] << 16);
   }
   if (tid == 0) G.counts[t] = total | (redo ? kRedo : 0u);
+  // the finishing pass reads whole vectors of four counts: the tensor's last tile clears what its vector holds behind it
+  if (t == G.n_tiles - 1 && tid > 0 && tid < 4 && (t & 3u) + tid < 4) G.counts[t + tid] = 0;
 }
 
 // sums of kSumGroup tile counts each, for tensors of more than kDirectTiles tiles (one wave per sum)
-__global__ __launch_bounds__(64) void tile_group_sum_kernel(const TileArgs a) {
-  const TileGeom G = tile_geom(a, blockIdx.y);
+template <typename F>
+__global__ __launch_bounds__(64) void tile_group_sum_kernel(const TileArgs args) {
+  TileShared a;
+  TileItem it;
+  args_arrived(args, blockIdx.y, a, it);
+  const TileGeom G = tile_geom(a, it, blockIdx.y, F::DT);
   const uint32_t g = blockIdx.x, t = g * kSumGroup + threadIdx.x;
   if (g * kSumGroup >= G.n_tiles) return;
   const uint32_t sum = wave_last(wave_incl_scan(t < G.n_tiles ? G.counts[t] & ~kRedo : 0u));
@@ -607,7 +633,7 @@ __global__ __launch_bounds__(64) void tile_group_sum_kernel(const TileArgs a) {
 }
 
 template <typename F>
-__global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const TileArgs a) {
+__global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const TileArgs args) {
   constexpr int NW = kTileThreads / 64;
   static_assert(kFinishMost <= NW, "one wave scans the counts of one group");
   __shared__ uint16_t lut[256];
@@ -619,7 +645,10 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t item = blockIdx.y;
-  const TileGeom G = tile_geom(a, item);
+  TileShared a;
+  TileItem it;
+  args_arrived(args, item, a, it);
+  const TileGeom G = tile_geom(a, it, item, F::DT);
   const Planes& P = G.P;
   const uint32_t n_groups = (G.n_tiles + kGroup - 1) / kGroup;
   // the workgroup's groups: [g0, g0 + ng) -- a.finish_groups of them in a row (1 to kFinishMost: a launch of many
@@ -635,6 +664,9 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
   // Everything whose address does not depend on the counts is fetched at once: the counts themselves, the
   // groups' table entries (one per thread and group, or a few) and the first 2 kSlotAhead records of every tile's slot
   // (two per thread: hardly a tile has more, so hardly a workgroup has to go to memory once more after the barrier).
+  // wave q: the counts of the tiles of group q
+  const uint32_t t_mine = (g0 + (uint32_t)wave) * kGroup + lane;
+  const uint32_t c_mine = (uint32_t)wave < ng && (uint32_t)lane < kGroup && t_mine < G.n_tiles ? G.counts[t_mine] : 0u;
   const uint32_t sl = (uint32_t)tid / kSlotAhead, sj = (uint32_t)tid % kSlotAhead;   // tile of a group, record of the tile
   uint32_t my_entry[kFinishMost], rec_ahead[kFinishMost], rec_ahead2[kFinishMost];
 #pragma unroll
@@ -660,10 +692,10 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
     }
     for (uint32_t i = whole * kSumGroup + tid; i < t_first; i += kTileThreads) before += G.counts[i] & ~kRedo;
   } else {
-    // four counts per load, four loads per thread on their way at a time (the counts start 256-byte aligned and
-    // the sums behind them pad the last vector)
+    // four counts per load, four loads per thread on their way at a time (the counts start 256-byte aligned, the dense
+    // pass has cleared what the last vector holds behind them, and the first group's tiles start with a vector)
     const u32x4* cv = reinterpret_cast<const u32x4*>(G.counts);
-    const uint32_t nvec = (G.n_tiles + 3) / 4;
+    const uint32_t nvec = (G.n_tiles + 3) / 4, v_first = t_first / 4;
     for (uint32_t v0 = 0; v0 < nvec; v0 += 4 * kTileThreads) {
       u32x4 v[4];
 #pragma unroll
@@ -673,14 +705,9 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const uint32_t e = 4 * (v0 + q * kTileThreads + tid);
-        const uint32_t c[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-        for (int z = 0; z < 4; ++z) {
-          const uint32_t cz = e + z < G.n_tiles ? c[z] & ~kRedo : 0u;
-          all += cz;
-          before += e + z < t_first ? cz : 0u;
-        }
+        const uint32_t sum = (v[q].x & ~kRedo) + (v[q].y & ~kRedo) + (v[q].z & ~kRedo) + (v[q].w & ~kRedo);
+        all += sum;
+        before += v0 + q * kTileThreads + tid < v_first ? sum : 0u;
       }
     }
   }
@@ -691,9 +718,8 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
     s_red[NW + wave] = all;
   }
   if ((uint32_t)wave < ng) {
-    // wave q: the counts of the tiles of group q, and what lies before each inside the group
-    const uint32_t t0 = (g0 + (uint32_t)wave) * kGroup;
-    const uint32_t c = (uint32_t)lane < kGroup && t0 + lane < G.n_tiles ? G.counts[t0 + lane] : 0u;
+    // what lies before each tile inside the group
+    const uint32_t c = c_mine;
     const uint32_t incl = wave_incl_scan(c & ~kRedo);
     if ((uint32_t)lane < kGroup) {
       s_cnt[wave][lane] = c;
@@ -719,6 +745,9 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
   fin.val = P.out + off_val;
   fin.val_room = P.capacity > off_val ? P.capacity - off_val : 0;
 
+  // header, pads and sizes by one wave of the first workgroup, which does it while the others place the records
+  if (g0 == 0 && wave == NW - 1) compress_write_trailer(P, a.dec16_of(it, item), a.sizes + item, M, 0u, lane);
+
   // Tiles whose records are not in their slots: once more from the words, by the offsets inside the tile that the
   // first pass left in the table.  Rare, and kept out of the way of the groups that have none: looking at every
   // tile's count for the mark, one LDS read after the other, was half of this kernel's time.
@@ -726,7 +755,7 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
 #pragma unroll
   for (uint32_t q = 0; q < kFinishMost; ++q) marks |= s_mark[q];
   if (marks & kRedo) {
-    build_encode_table(lut, a.dec16_of(item), tid, F::kLutShift);
+    build_encode_table(lut, a.dec16_of(it, item), tid, F::kLutShift);
     __syncthreads();
     uint32_t group_first = first;
 #pragma unroll 1
@@ -793,7 +822,6 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
     }
     first += group_total;
   }
-  if (g0 == 0 && wave == 0) compress_write_trailer(P, a.dec_of(item), a.sizes + item, M, 0u, lane);
 }
 
 #endif  // SPLITZIP_COMPRESS_HPP

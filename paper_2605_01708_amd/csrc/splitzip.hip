@@ -583,6 +583,17 @@ uint32_t pick_cpt(uint64_t chunks, uint32_t at_least, uint64_t status_bytes) {
   return 0;
 }
 
+// the launches of k tensors: dense pass (one workgroup per tile, started by the hardware in the tiles' order), sums if
+// the finishing pass wants them, finishing pass
+template <typename F>
+void launch_compress(unsigned tiles, unsigned finish_wgs, unsigned sums, unsigned k, unsigned lds_pad, hipStream_t st, const TileArgs& args) {
+  if (tiles) {
+    hipLaunchKernelGGL((compress_tile_kernel<F, F::kCpt>), dim3(tiles, k), dim3(kTileThreads), lds_pad, st, args);
+    if (args.shared.use_group_sums) hipLaunchKernelGGL(tile_group_sum_kernel<F>, dim3(sums, k), dim3(64), 0, st, args);
+  }
+  hipLaunchKernelGGL(compress_finish_kernel<F>, dim3(finish_wgs ? finish_wgs : 1u, k), dim3(kTileThreads), 0, st, args);
+}
+
 // The compress calls, all of them: n_items tensors (a host list), each under its own codebook -- the items' own (host)
 // or d_cbs[k] (device memory).  paging: table and page geometry shared by all items, or contiguous tensors (table null).
 // d_workspace: the caller's workspace, or null with own_scratch for the library's own array.
@@ -623,18 +634,20 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       cpt = need;
     }
     if (k == 0) return SPLITZIP_ERR_CAPACITY;   // cannot happen: every tensor fits alone
-    TileArgs a;
-    memset(&a, 0, sizeof a);
+    TileArgs args;   // the first k items are filled in, and no other is looked at
+    TileShared& a = args.shared;
     uint64_t off = 0, tiles_max = 0;
     for (uint32_t q = 0; q < k; ++q) {
       const splitzip_item& it = items[i + q];
-      if (!d_cbs) memcpy(a.dec[q], it.cb->dec, 16);   // codebook_ok has shown that dec and the encode table describe the same bijection
-      a.item[q].in = static_cast<const uint8_t*>(it.d_in);
-      a.item[q].out = static_cast<uint8_t*>(it.d_out);
-      a.item[q].n = it.n_elems;
-      a.item[q].capacity = it.out_capacity;
+      TileItem& to = args.item[q];
+      if (!d_cbs) memcpy(to.dec, it.cb->dec, 16);   // codebook_ok has shown that dec and the encode table describe the same bijection
+      else memset(to.dec, 0, 16);
+      to.in = static_cast<const uint8_t*>(it.d_in);
+      to.out = static_cast<uint8_t*>(it.d_out);
+      to.n = (uint32_t)it.n_elems;
+      to.capacity = it.out_capacity;
       const uint64_t tiles = tiles_of(chunks_of(it.n_elems), cpt);
-      a.status_off[q] = (uint32_t)off;
+      to.status_off = (uint32_t)off;
       off += status_need(tiles);
       if (tiles > tiles_max) tiles_max = tiles;
     }
@@ -643,8 +656,6 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     a.status = ws.base + kWsHeaderBytes;
     a.stage = ws.base + kWsHeaderBytes + ws.status_bytes;
     a.stage_cap = (ws.stage_bytes / k) & ~(uint64_t)255u;
-    a.n_items = k;
-    a.dtype = (uint32_t)dtype;
     a.cpt = cpt;
     a.tile_shift = 2u + (uint32_t)__builtin_ctz(cpt);
     {
@@ -657,7 +668,7 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     // 1201 (262 144 tiles), 314 and 307 (65 536), 83.2 and 82.4 (16 384); E5M2 690 and 665 (131 072), 173.4 and 171.7
     // (32 768), 49.7 and 49.8 (8192).
     const bool many = tiles_max * k >= 16384;
-    a.by_xcd = many ? 1u : 0u;
+    a.xcd_row = many ? (uint32_t)tiles_max : 0u;
     const unsigned groups_max = (unsigned)((tiles_max + kGroup - 1) / kGroup), sums_max = (unsigned)((tiles_max + kSumGroup - 1) / kSumGroup);
     // many groups in the launch: several per workgroup, as long as the chip still gets a few workgroups per CU
     a.finish_groups = 1;
@@ -670,15 +681,8 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     // beyond that they read sums of kSumGroup counts instead (tile_group_sum_kernel).
     const uint64_t direct_budget = g_hooks.direct_bytes.load() ? g_hooks.direct_bytes.load() : kDirectBytes;
     a.use_group_sums = tiles_max > kDirectTiles || (uint64_t)fgroups * k * tiles_max * 4 > direct_budget ? 1u : 0u;
-    if (tiles_max) {
-      const dim3 grid((unsigned)tiles_max, k);   // one workgroup per tile, started by the hardware in the tiles' order
-      if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL((compress_tile_kernel<Bf16, Bf16::kCpt>), grid, dim3(kTileThreads), many ? Bf16::kTileLdsPad : 0u, st, a);
-      else hipLaunchKernelGGL((compress_tile_kernel<E5m2, E5m2::kCpt>), grid, dim3(kTileThreads), 0, st, a);
-      if (a.use_group_sums) hipLaunchKernelGGL(tile_group_sum_kernel, dim3(sums_max, k), dim3(64), 0, st, a);
-    }
-    const dim3 fgrid(fgroups ? fgroups : 1u, k);
-    if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL(compress_finish_kernel<Bf16>, fgrid, dim3(kTileThreads), 0, st, a);
-    else hipLaunchKernelGGL(compress_finish_kernel<E5m2>, fgrid, dim3(kTileThreads), 0, st, a);
+    if (dtype == SPLITZIP_BF16) launch_compress<Bf16>((unsigned)tiles_max, fgroups, sums_max, k, many ? Bf16::kTileLdsPad : 0u, st, args);
+    else launch_compress<E5m2>((unsigned)tiles_max, fgroups, sums_max, k, 0u, st, args);
     if (hipGetLastError() != hipSuccess) return SPLITZIP_ERR_HIP;
     i += k;
   }
