@@ -291,9 +291,17 @@ def workspace_bytes(n: int, dtype: int) -> int:
     return int(lib().splitzip_workspace_bytes(n, dtype))
 
 
+# The handle of the current stream without a torch.cuda.Stream object around it: making one costs 2.7 us a call, as
+# much as a kernel launch; the handle alone 0.3 us.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if _raw_stream is not None:
+        return int(_raw_stream(torch.cuda.current_device()))
+    return int(torch.cuda.current_stream().cuda_stream)
 
 
 class Workspace:
