@@ -137,7 +137,8 @@ size_t splitzip_compress_bound(uint64_t n_elems, int dtype);
 /* Device scratch of a compress call of up to n_elems: a status area of 4 MiB
  * (the escape count of every 16 KB tile of the tensor) and a staging area of
  * n_elems bytes and a little more (the tiles' escape records until their rank
- * in the stream is known).  A compress call is two kernel launches: the first
+ * in the stream is known).  A compress call is two kernel launches (one for
+ * tensors of a few dozen chunks, which a workgroup does by itself): the first
  * does the dense work tile by tile, the second ranks and places the escape
  * records; no workgroup ever waits for another, so the calls run correctly
  * whatever else the device is doing and however little of a launch fits the
@@ -160,7 +161,8 @@ int splitzip_workspace_init(void* d_workspace, size_t workspace_bytes, void* str
  * enqueued.  If the fixed part fits but the escapes do not, everything that
  * fits is written, status gets SPLITZIP_STATUS_OVERFLOW and total_bytes is
  * the size a retry needs.  n_elems == 0 is valid (header and one offset).
- * Two launches on `stream` (three above 32 Mi elements of BF16).
+ * Two launches on `stream` (three above 32 Mi elements of BF16; one where no
+ * tensor of the call has more than 40 chunks of BF16 or 48 of E5M2).
  * The output is a pure function of (input, codebook): independent of
  * scheduling, capacity slack and earlier calls. */
 int splitzip_compress(const void* d_in, uint64_t n_elems, int dtype, const splitzip_codebook* cb,

@@ -337,6 +337,7 @@ struct Bf16 {
   static constexpr uint32_t kCpt = 2;
   static constexpr int kWavesPerSimd = 8;
   static constexpr uint32_t kTileLdsPad = 22000;   // five workgroups per CU
+  static constexpr uint32_t kSmallChunks = 40;
   static constexpr int kLutShift = 0;       // the LDS encode table holds the entry of exponent e in slot e
   // a chunk goes the fast way if it is complete (then nothing of a pad is its business: N is a multiple of 1024 there)
   __device__ static inline bool full(const Planes& a, uint64_t cbase) { return cbase + kChunk <= a.n; }
@@ -359,6 +360,7 @@ struct E5m2 {
   // a tile of 4 x kCpt chunks is 16 KB of words here too; eight workgroups per CU (730 us for 64 tensors of 32 MiB
   // against 750 us with six and 790 us with five)
   static constexpr uint32_t kCpt = 4;
+  static constexpr uint32_t kSmallChunks = 48;
   static constexpr int kWavesPerSimd = 8;
   // The LDS encode table holds the entry of exponent e in slots 2 e and 2 e + 1: its byte offset is then
   // the word's byte with the sign and mantissa bits masked off, one instruction per element.
@@ -431,7 +433,8 @@ constexpr uint32_t kRedo = 0x80000000u;     // in a tile's count: its records ar
 constexpr uint32_t kMore = 1u;              // in a group's mark of the finishing pass, beside kRedo
 static_assert(kGroup * kSlotAhead == kTileThreads, "every thread fetches records of one tile ahead");
 
-// The arguments of a launch: what all its tensors share, then the tensors.  A workgroup needs the first part and one
+// The arguments of a launch: what all its tensors share, then the tensors (N: room for kBatchMax of them, or for the
+// one of a single call, whose two launches then carry 144 bytes instead of 3.2 KB each).  A workgroup needs the first part and one
 // tensor's, 144 bytes; both are fetched whole before anything is done with them (args_arrived).
 struct TileItem {
   const uint8_t* in;
@@ -456,9 +459,10 @@ struct TileShared {
   uint32_t xcd_row;               // not 0: the dense pass takes its tiles in xcd_order, and this is its workgroups per tensor
   __device__ inline u32x4 dec16_of(const TileItem& it, uint32_t k) const { return d_cbs ? load_dec16(d_cbs[k].dec) : dec16_from(it.dec); }
 };
+template <uint32_t N>
 struct TileArgs {
   TileShared shared;
-  TileItem item[kBatchMax];
+  TileItem item[N];
 };
 static_assert(sizeof(TileShared) == 96 && sizeof(TileItem) == 48, "whole 16-byte words for args_arrived");
 
@@ -466,7 +470,8 @@ static_assert(sizeof(TileShared) == 96 && sizeof(TileItem) == 48, "whole 16-byte
 // it is used first, which for these kernels meant four or five trips to the argument block one after the other --
 // and every launch has a new block that no cache holds -- before the first load of data was on its way.  With this,
 // and a group's counts asked for beside everything else, one tensor's finishing pass went from 3.8 to 3.1 us.
-__device__ inline void args_arrived(const TileArgs& args, uint32_t item, TileShared& a, TileItem& it) {
+template <uint32_t N>
+__device__ inline void args_arrived(const TileArgs<N>& args, uint32_t item, TileShared& a, TileItem& it) {
   u32x4 x[6], y[3];
   __builtin_memcpy(x, &args.shared, 96);
   __builtin_memcpy(y, &args.item[item], 48);
@@ -513,8 +518,8 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 
 // CPT: chunks of a wave whose loads are issued together, before anything else happens in the workgroup.  Wave w of
 // the tile owns the chunks [w cpt, w cpt + cpt) of the tile.
-template <typename F, int CPT>
-__global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_kernel(const TileArgs args) {
+template <typename F, int CPT, uint32_t N>
+__global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_kernel(const TileArgs<N> args) {
   constexpr int NW = kTileThreads / 64;
   __shared__ uint16_t lut[256];
   __shared__ uint16_t stage_pk[NW][kTileStageCap];
@@ -620,8 +625,8 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
 }
 
 // sums of kSumGroup tile counts each, for tensors of more than kDirectTiles tiles (one wave per sum)
-template <typename F>
-__global__ __launch_bounds__(64) void tile_group_sum_kernel(const TileArgs args) {
+template <typename F, uint32_t N>
+__global__ __launch_bounds__(64) void tile_group_sum_kernel(const TileArgs<N> args) {
   TileShared a;
   TileItem it;
   args_arrived(args, blockIdx.y, a, it);
@@ -632,8 +637,8 @@ __global__ __launch_bounds__(64) void tile_group_sum_kernel(const TileArgs args)
   if (threadIdx.x == 0) G.group_sums[g] = sum;
 }
 
-template <typename F>
-__global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const TileArgs args) {
+template <typename F, uint32_t N>
+__global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const TileArgs<N> args) {
   constexpr int NW = kTileThreads / 64;
   static_assert(kFinishMost <= NW, "one wave scans the counts of one group");
   __shared__ uint16_t lut[256];
@@ -822,6 +827,82 @@ __global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const 
     }
     first += group_total;
   }
+}
+
+// ---- small tensors: one launch, one workgroup per tensor ----
+// Up to F::kSmallChunks chunks a tensor is one workgroup's work: 16 waves own consecutive runs of its chunks, so the
+// counts meet in LDS, every rank is known behind one barrier and nothing is staged outside the workgroup.  What bounds
+// such a call is the launch: the second one takes the host 2.7 us and the device 3.1 us.  Device us per call, this
+// kernel / two launches: BF16 5.2 / 6.8 (17 chunks), 6.4 / 6.7 (33), 7.3 / 6.6 (49), 10.6 / 6.6 (97); E5M2 5.6 / 7.6
+// (17), 6.8 / 7.9 (33), 7.6 / 7.8 (49), 8.8 / 7.8 (65); with the host's part, one call after the other, BF16 5.1 / 9.3
+// (17 chunks), 6.1 / 9.3 (33).
+constexpr uint32_t kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
+constexpr uint32_t kSmallStageCap = 384;   // escapes a wave stages in LDS; a wave with more goes over its chunks again
+
+template <typename F, uint32_t N>
+__global__ __launch_bounds__(kSmallThreads) void compress_small_kernel(const TileArgs<N> args) {
+  __shared__ uint16_t lut[256];
+  __shared__ uint16_t stage_pos[kSmallWaves][kSmallStageCap];
+  __shared__ uint8_t stage_val[kSmallWaves][kSmallStageCap];
+  __shared__ u32x4 s_park[kSmallThreads];
+  __shared__ uint32_t s_cnt[kSmallWaves];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t item = blockIdx.x;
+  TileShared a;
+  TileItem it;
+  args_arrived(args, item, a, it);
+  const Planes P = make_planes(item_words(a.paging, it.in), it.out, it.n, it.capacity, F::DT);
+  const uint32_t per = (P.n_chunks + kSmallWaves - 1) / kSmallWaves, c0 = (uint32_t)wave * per;   // the wave's chunks: [c0, c0 + mine)
+  const uint32_t mine = P.n_chunks > c0 ? (P.n_chunks - c0 < per ? P.n_chunks - c0 : per) : 0u;
+  uint32_t* park = reinterpret_cast<uint32_t*>(&s_park[tid]);
+
+  auto fetch = [&](uint32_t c, typename F::Regs& w) {
+    const uint64_t cbase = (uint64_t)(c0 + c) * kChunk;
+    const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_chunk(P.w, c0 + c) : 0u);
+    if (F::full(P, cbase)) F::template load<true>(P, cptr, cbase, lane, w);
+    else F::template load<false>(P, cptr, cbase, lane, w);
+  };
+  typename F::Regs cur, nxt;
+  if (mine > 0) fetch(0, cur);
+  const u32x4 dec = a.dec16_of(it, item);
+  build_encode_table(lut, dec, tid, F::kLutShift);
+  lds_barrier();
+  const LdsSink lds{stage_pos[wave], stage_val[wave], 0u, kSmallStageCap};
+  uint32_t count = 0, my_start = 0;   // lane c: escapes of the wave before its c-th chunk
+  for (uint32_t c = 0; c < mine; ++c) {
+    if (c + 1 < mine) fetch(c + 1, nxt);   // the next chunk's words travel while this one is worked on
+    const uint64_t cbase = (uint64_t)(c0 + c) * kChunk;
+    if ((uint32_t)lane == c) my_start = count;
+    count += F::full(P, cbase) ? F::template process<true, true>(P, lut, park, cbase, lane, cur, count, lds)
+                               : F::template process<false, true>(P, lut, park, cbase, lane, cur, count, lds);
+    cur = nxt;
+  }
+  if (lane == 0) s_cnt[wave] = count;
+  lds_barrier();
+  const uint32_t c_lane = (uint32_t)lane < kSmallWaves ? s_cnt[lane] : 0u, incl = wave_incl_scan(c_lane);
+  const uint32_t M = wave_last(incl), first = (uint32_t)__builtin_amdgcn_readlane(incl - c_lane, wave);
+  const uint64_t off_val = P.off_pos + a256(2ull * M);
+  FinalSink fin;
+  fin.pos = reinterpret_cast<uint16_t*>(P.out + P.off_pos);
+  fin.pos_room = P.capacity > P.off_pos ? (P.capacity - P.off_pos) / 2 : 0;
+  fin.val = P.out + off_val;
+  fin.val_room = P.capacity > off_val ? P.capacity - off_val : 0;
+  uint32_t* tab = reinterpret_cast<uint32_t*>(P.out + P.off_tab);
+  if ((uint32_t)lane < mine) tab[c0 + lane] = first + my_start;
+  if (count <= kSmallStageCap) {
+    for (uint32_t i = lane; i < count; i += 64) fin.put(first + i, stage_pos[wave][i], stage_val[wave][i]);
+  } else {
+#pragma unroll 1
+    for (uint32_t c = 0; c < mine; ++c) {
+      const uint64_t cbase = (uint64_t)(c0 + c) * kChunk;
+      const uint32_t base = first + (uint32_t)__builtin_amdgcn_readlane(my_start, c);
+      fetch(c, cur);
+      if (F::full(P, cbase)) F::template process<true, false>(P, lut, park, cbase, lane, cur, base, fin);
+      else F::template process<false, false>(P, lut, park, cbase, lane, cur, base, fin);
+    }
+  }
+  if (wave == kSmallWaves - 1) compress_write_trailer(P, dec, a.sizes + item, M, 0u, lane);   // the wave with the fewest chunks
 }
 
 #endif  // SPLITZIP_COMPRESS_HPP

@@ -98,6 +98,7 @@ struct TestHooks {
   std::atomic<uint64_t> status_bytes{0};
   std::atomic<uint32_t> finish_groups{0};
   std::atomic<uint64_t> direct_bytes{0};
+  bool any() const { return stage_bytes || status_bytes || finish_groups || direct_bytes; }   // the two-launch path is meant
 };
 TestHooks g_hooks;
 
@@ -585,13 +586,23 @@ uint32_t pick_cpt(uint64_t chunks, uint32_t at_least, uint64_t status_bytes) {
 
 // the launches of k tensors: dense pass (one workgroup per tile, started by the hardware in the tiles' order), sums if
 // the finishing pass wants them, finishing pass
-template <typename F>
-void launch_compress(unsigned tiles, unsigned finish_wgs, unsigned sums, unsigned k, unsigned lds_pad, hipStream_t st, const TileArgs& args) {
+template <typename F, uint32_t N>
+void launch_compress(unsigned tiles, unsigned finish_wgs, unsigned sums, unsigned k, unsigned lds_pad, hipStream_t st, const TileArgs<N>& args) {
   if (tiles) {
-    hipLaunchKernelGGL((compress_tile_kernel<F, F::kCpt>), dim3(tiles, k), dim3(kTileThreads), lds_pad, st, args);
-    if (args.shared.use_group_sums) hipLaunchKernelGGL(tile_group_sum_kernel<F>, dim3(sums, k), dim3(64), 0, st, args);
+    hipLaunchKernelGGL((compress_tile_kernel<F, F::kCpt, N>), dim3(tiles, k), dim3(kTileThreads), lds_pad, st, args);
+    if (args.shared.use_group_sums) hipLaunchKernelGGL((tile_group_sum_kernel<F, N>), dim3(sums, k), dim3(64), 0, st, args);
   }
-  hipLaunchKernelGGL(compress_finish_kernel<F>, dim3(finish_wgs ? finish_wgs : 1u, k), dim3(kTileThreads), 0, st, args);
+  hipLaunchKernelGGL((compress_finish_kernel<F, N>), dim3(finish_wgs ? finish_wgs : 1u, k), dim3(kTileThreads), 0, st, args);
+}
+
+template <typename F>
+void launch_small(unsigned k, hipStream_t st, const TileArgs<kBatchMax>& args) {
+  if (k == 1) {
+    const TileArgs<1> one = {args.shared, {args.item[0]}};
+    hipLaunchKernelGGL((compress_small_kernel<F, 1>), dim3(1), dim3(kSmallThreads), 0, st, one);
+  } else {
+    hipLaunchKernelGGL((compress_small_kernel<F, kBatchMax>), dim3(k), dim3(kSmallThreads), 0, st, args);
+  }
 }
 
 // The compress calls, all of them: n_items tensors (a host list), each under its own codebook -- the items' own (host)
@@ -634,7 +645,7 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       cpt = need;
     }
     if (k == 0) return SPLITZIP_ERR_CAPACITY;   // cannot happen: every tensor fits alone
-    TileArgs args;   // the first k items are filled in, and no other is looked at
+    TileArgs<kBatchMax> args;   // the first k items are filled in, and no other is looked at
     TileShared& a = args.shared;
     uint64_t off = 0, tiles_max = 0;
     for (uint32_t q = 0; q < k; ++q) {
@@ -681,8 +692,19 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     // beyond that they read sums of kSumGroup counts instead (tile_group_sum_kernel).
     const uint64_t direct_budget = g_hooks.direct_bytes.load() ? g_hooks.direct_bytes.load() : kDirectBytes;
     a.use_group_sums = tiles_max > kDirectTiles || (uint64_t)fgroups * k * tiles_max * 4 > direct_budget ? 1u : 0u;
-    if (dtype == SPLITZIP_BF16) launch_compress<Bf16>((unsigned)tiles_max, fgroups, sums_max, k, many ? Bf16::kTileLdsPad : 0u, st, args);
-    else launch_compress<E5m2>((unsigned)tiles_max, fgroups, sums_max, k, 0u, st, args);
+    const bool small = chunks_of(n_max) <= (dtype == SPLITZIP_BF16 ? Bf16::kSmallChunks : E5m2::kSmallChunks) && !g_hooks.any();
+    const unsigned pad = many && dtype == SPLITZIP_BF16 ? Bf16::kTileLdsPad : 0u;
+    if (small) {
+      if (dtype == SPLITZIP_BF16) launch_small<Bf16>(k, st, args);
+      else launch_small<E5m2>(k, st, args);
+    } else if (k == 1) {
+      const TileArgs<1> one = {args.shared, {args.item[0]}};
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>((unsigned)tiles_max, fgroups, sums_max, 1, pad, st, one);
+      else launch_compress<E5m2>((unsigned)tiles_max, fgroups, sums_max, 1, pad, st, one);
+    } else {
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>((unsigned)tiles_max, fgroups, sums_max, k, pad, st, args);
+      else launch_compress<E5m2>((unsigned)tiles_max, fgroups, sums_max, k, pad, st, args);
+    }
     if (hipGetLastError() != hipSuccess) return SPLITZIP_ERR_HIP;
     i += k;
   }
