@@ -14,12 +14,13 @@
 // lanes that count the same exponent -- most of them, the distribution being what it is -- to one bank: 39 % of
 // the LDS cycles were conflict cycles.)  The waves of a workgroup share the copies, hence atomic adds.
 // Non-zero totals go to the global bins at the end.
+// Workgroup wg of the n_wgs that share the sample.
 template <bool BF16>
-__device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* hist) {
+__device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* hist, uint32_t wg, uint32_t n_wgs) {
   constexpr int BINS = BF16 ? 256 : 32;
-  __shared__ uint32_t bins[BINS * 64];
+  __shared__ __attribute__((aligned(16))) uint32_t bins[BINS * 64];
   const int tid = threadIdx.x;
-  for (int i = tid; i < BINS * 64; i += 1024) bins[i] = 0;
+  for (int i = tid; i < BINS * 16; i += 1024) reinterpret_cast<u32x4*>(bins)[i] = u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
   uint32_t* mine = bins + (tid & 63);
   const uint64_t bytes = n * (BF16 ? 2 : 1), nvec = bytes / 16;
@@ -38,8 +39,8 @@ __device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* h
     }
   };
   // four vectors per thread in flight: the loads of a step are all issued before the first is counted
-  const uint64_t step = (uint64_t)gridDim.x * 1024;
-  uint64_t i = blockIdx.x * 1024ull + tid;
+  const uint64_t step = (uint64_t)n_wgs * 1024;
+  uint64_t i = wg * 1024ull + tid;
   for (; i + 3 * step < nvec; i += 4 * step) {
     u32x4 q[4];
 #pragma unroll
@@ -49,34 +50,47 @@ __device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* h
   }
   for (; i < nvec; i += step) count(ld_stream(v + i));
   // the words behind the last whole vector, by workgroup 0
-  if (blockIdx.x == 0) {
+  if (wg == 0) {
     for (uint64_t i = nvec * 16 + (uint64_t)tid * (BF16 ? 2 : 1); i < bytes; i += 1024 * (BF16 ? 2 : 1)) {
       const uint32_t e = BF16 ? ((uint32_t)(in[i] | (in[i + 1] << 8)) >> 7) & 0xffu : ((uint32_t)in[i] >> 2) & 31u;
       atomicAdd(&mine[e * 64], 1u);
     }
   }
   __syncthreads();
-  if (tid < BINS) {
-    uint64_t c = 0;
-#pragma unroll 8
-    for (int r = 0; r < 64; ++r) c += bins[tid * 64 + ((r + tid) & 63)];   // thread t starts at copy t: no two on one bank
-    if (c) atomicAdd(reinterpret_cast<unsigned long long*>(&hist[tid]), (unsigned long long)c);
+  // four threads per bin, sixteen copies each
+  if (tid < 4 * BINS) {
+    const uint32_t bin = (uint32_t)tid >> 2, q = (uint32_t)tid & 3u;
+    uint32_t c = 0;   // a workgroup counts fewer than 2^32 words
+#pragma unroll
+    for (uint32_t r = 0; r < 16; ++r) c += bins[bin * 64 + ((16 * q + r + bin) & 63u)];   // bin b starts at copy b: the lanes' reads spread over the banks
+    c += (uint32_t)__shfl_xor((int)c, 1);
+    c += (uint32_t)__shfl_xor((int)c, 2);
+    if (q == 0 && c) atomicAdd(reinterpret_cast<unsigned long long*>(&hist[bin]), (unsigned long long)c);
   }
 }
 
 template <bool BF16>
 __global__ __launch_bounds__(1024) void histogram_kernel(const uint8_t* in, uint64_t n, uint64_t* hist) {
-  histogram_body<BF16>(in, n, hist);
+  histogram_body<BF16>(in, n, hist, blockIdx.x, gridDim.x);
 }
 
-// the same for several samples in one launch: blockIdx.y picks the sample, its counts go to hists + 256 y
+// The same for several samples in one launch: the workgroups [first[k], first[k + 1]) count sample k into hists + 256 k.
+// As many workgroups as the chip has CUs, dealt out by the samples' lengths: a workgroup has 64 KB of bins to clear and
+// to add up, and a CU that streams for one workgroup reads faster than for two (64 BF16 tensors of 8 MiB: 82 us with
+// one workgroup per CU, 103-107 us with two, in one round or in two).
+constexpr uint32_t kHistMost = 64;
 struct HistBatchArgs {
-  const uint8_t* in[64];
-  uint64_t n[64];
+  const uint8_t* in[kHistMost];
+  uint64_t n[kHistMost];
+  uint32_t first[kHistMost + 1];   // behind the last sample: its end, up to the last entry
 };
 template <bool BF16>
 __global__ __launch_bounds__(1024) void histogram_batch_kernel(const HistBatchArgs a, uint64_t* hists) {
-  histogram_body<BF16>(a.in[blockIdx.y], a.n[blockIdx.y], hists + 256 * blockIdx.y);
+  uint32_t k = 0;   // the last sample that starts at or before this workgroup
+#pragma unroll
+  for (uint32_t step = kHistMost / 2; step; step >>= 1)
+    if (a.first[k + step] <= blockIdx.x) k += step;
+  histogram_body<BF16>(a.in[k], a.n[k], hists + 256 * k, blockIdx.x - a.first[k], a.first[k + 1] - a.first[k]);
 }
 
 __global__ void zero_words_kernel(uint64_t* p, uint64_t nwords) {
@@ -84,23 +98,59 @@ __global__ void zero_words_kernel(uint64_t* p, uint64_t nwords) {
 }
 
 // Section 3.3 on the device: the three tables from 256 exponent counts.  One workgroup per codebook
-// (workgroup b: counts hist + 256 b, tables cb + b); thread v ranks exponent v by (count descending,
-// exponent ascending) among the format's exponents, the 16 first ranks form the codebook.
-__global__ __launch_bounds__(256) void codebook_kernel(const uint64_t* hist, uint32_t n_values, uint32_t dtype,
-                                                       splitzip_codebook* cb) {
+// (workgroup b: counts hist + 256 b, tables cb + b); four threads rank exponent v by (count descending,
+// exponent ascending) among the format's exponents, a quarter of them each, the 16 first ranks form the codebook.
+// Bound by the compares of one CU: with counts below 2^31, as good as always, they are 32 bits wide (9.5 us a launch
+// with 64-bit ones).  The tables leave as whole words.
+__global__ __launch_bounds__(1024) void codebook_kernel(const uint64_t* hist, uint32_t n_values, uint32_t dtype,
+                                                        splitzip_codebook* cb) {
   hist += 256 * blockIdx.x;
   cb += blockIdx.x;
   __shared__ uint64_t h[256];
-  const uint32_t v = threadIdx.x;
-  h[v] = v < n_values ? hist[v] : 0;
-  __syncthreads();
+  __shared__ __attribute__((aligned(16))) uint32_t h2[256];   // twice the count
+  __shared__ uint32_t s_tab[sizeof(splitzip_codebook) / 4];
+  static_assert(sizeof(splitzip_codebook) == 532 && offsetof(splitzip_codebook, enc) == 16 && offsetof(splitzip_codebook, member) == 272, "tables as words");
+  const uint32_t tid = threadIdx.x;
+  bool wide = false;
+  if (tid < 256) {
+    const uint64_t c = tid < n_values ? hist[tid] : 0;
+    h[tid] = c;
+    h2[tid] = (uint32_t)c << 1;
+    wide = c >> 31;
+  }
+  if (tid < sizeof(splitzip_codebook) / 4) s_tab[tid] = tid == 132 ? dtype : 0u;
+  const bool any_wide = __syncthreads_or(wide) != 0;
+  const uint32_t v = tid >> 2, part = tid & 3u, each = n_values / 4;   // n_values is 256 or 32
   uint32_t rank = 0;
-  for (uint32_t u = 0; u < n_values; ++u) rank += (h[u] > h[v] || (h[u] == h[v] && u < v)) ? 1u : 0u;
-  const bool in = v < n_values && rank < 16;
-  cb->enc[v] = in ? (uint8_t)rank : (uint8_t)0;
-  cb->member[v] = in ? 1 : 0;
-  if (in) cb->dec[rank] = (uint8_t)v;
-  if (v == 0) cb->dtype = dtype;
+  if (!any_wide) {
+    // another exponent comes first if its count is larger, or equal and it is smaller: 2 c + (u < v) > 2 mine
+    const uint32_t mine = h2[v];
+#pragma unroll 4
+    for (uint32_t i = 0; i < each / 4; ++i) {
+      const uint32_t u = 4 * (4 * i + part);   // the four threads read 16 bytes each side by side
+      const u32x4 c = *reinterpret_cast<const u32x4*>(&h2[u]);
+      rank += c.x + (u < v ? 1u : 0u) > mine ? 1u : 0u;
+      rank += c.y + (u + 1 < v ? 1u : 0u) > mine ? 1u : 0u;
+      rank += c.z + (u + 2 < v ? 1u : 0u) > mine ? 1u : 0u;
+      rank += c.w + (u + 3 < v ? 1u : 0u) > mine ? 1u : 0u;
+    }
+  } else {
+    const uint64_t mine = h[v];
+    for (uint32_t i = 0; i < each; ++i) {
+      const uint32_t u = 4 * i + part;
+      rank += (h[u] > mine || (h[u] == mine && u < v)) ? 1u : 0u;
+    }
+  }
+  rank += (uint32_t)__shfl_xor((int)rank, 1);
+  rank += (uint32_t)__shfl_xor((int)rank, 2);
+  uint8_t* tab = reinterpret_cast<uint8_t*>(s_tab);
+  if (part == 0 && v < n_values && rank < 16) {
+    tab[rank] = (uint8_t)v;
+    tab[16 + v] = (uint8_t)rank;
+    tab[272 + v] = 1;
+  }
+  __syncthreads();
+  if (tid < sizeof(splitzip_codebook) / 4) reinterpret_cast<uint32_t*>(cb)[tid] = s_tab[tid];
 }
 
 __global__ void workspace_init_kernel(uint32_t* p, uint32_t nwords) {

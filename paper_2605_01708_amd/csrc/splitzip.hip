@@ -786,7 +786,7 @@ int splitzip_decompress(const void* d_comp, size_t comp_bytes, uint64_t n_elems,
 int splitzip_codebook_device(const uint64_t* d_hist, int dtype, splitzip_codebook* d_cb, void* stream) {
   if (!dtype_ok(dtype) || !d_hist || !d_cb || (reinterpret_cast<uintptr_t>(d_hist) & 7u) || (reinterpret_cast<uintptr_t>(d_cb) & 3u))
     return SPLITZIP_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(codebook_kernel, dim3(1), dim3(256), 0, static_cast<hipStream_t>(stream), d_hist, exp_values(dtype),
+  hipLaunchKernelGGL(codebook_kernel, dim3(1), dim3(1024), 0, static_cast<hipStream_t>(stream), d_hist, exp_values(dtype),
                      (uint32_t)dtype, d_cb);
   return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
 }
@@ -913,26 +913,29 @@ int splitzip_calibrate_batch_device(const splitzip_item* items, uint32_t n_items
   if (n_items == 0) return SPLITZIP_OK;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, d_hists, 256ull * n_items);
-  for (uint32_t i = 0; i < n_items; i += 64) {
+  for (uint32_t i = 0; i < n_items; i += kHistMost) {
     HistBatchArgs a;
     memset(&a, 0, sizeof a);
-    const uint32_t k = n_items - i < 64 ? n_items - i : 64;
-    uint64_t nvec_max = 1;
-    for (uint32_t q = 0; q < k; ++q) {
+    const uint32_t k = n_items - i < kHistMost ? n_items - i : kHistMost;
+    uint64_t all = 0;
+    for (uint32_t q = 0; q < k; ++q) all += items[i + q].n_elems;
+    uint32_t wgs = 0;
+    for (uint32_t q = 0; q < kHistMost; ++q) {
+      a.first[q] = wgs;
+      if (q >= k) continue;
       a.in[q] = static_cast<const uint8_t*>(items[i + q].d_in);
       a.n[q] = items[i + q].n_elems;
+      // its share of one workgroup per CU, but at least four vectors per thread of it, and one workgroup at least
       const uint64_t nvec = (a.n[q] * (dtype == SPLITZIP_BF16 ? 2 : 1) + 15) / 16;
-      if (nvec > nvec_max) nvec_max = nvec;
+      uint64_t w = all ? (uint64_t)cu_count() * a.n[q] / all : 0;
+      if (w > (nvec + 4 * 1024 - 1) / (4 * 1024)) w = (nvec + 4 * 1024 - 1) / (4 * 1024);
+      wgs += w ? (uint32_t)w : 1u;
     }
-    // workgroups per sample: at least sixteen vectors per thread, and about four workgroups per CU over the launch
-    uint64_t gx = (nvec_max + 16 * 1024 - 1) / (16 * 1024);
-    const uint64_t most = ((uint64_t)cu_count() * 4 + k - 1) / k;
-    if (gx > most) gx = most;
-    if (gx < 1) gx = 1;
-    if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL(histogram_batch_kernel<true>, dim3((unsigned)gx, k), dim3(1024), 0, st, a, d_hists + 256ull * i);
-    else hipLaunchKernelGGL(histogram_batch_kernel<false>, dim3((unsigned)gx, k), dim3(1024), 0, st, a, d_hists + 256ull * i);
+    a.first[kHistMost] = wgs;
+    if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL(histogram_batch_kernel<true>, dim3(wgs), dim3(1024), 0, st, a, d_hists + 256ull * i);
+    else hipLaunchKernelGGL(histogram_batch_kernel<false>, dim3(wgs), dim3(1024), 0, st, a, d_hists + 256ull * i);
   }
-  hipLaunchKernelGGL(codebook_kernel, dim3(n_items), dim3(256), 0, st, d_hists, exp_values(dtype), (uint32_t)dtype, d_cbs);
+  hipLaunchKernelGGL(codebook_kernel, dim3(n_items), dim3(1024), 0, st, d_hists, exp_values(dtype), (uint32_t)dtype, d_cbs);
   return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
 }
 
