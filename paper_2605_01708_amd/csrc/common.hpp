@@ -13,7 +13,6 @@ constexpr uint32_t kHeaderBytes = 64;
 constexpr uint32_t kHeaderDecOffset = 40;                 // the 16 decode entries inside the header
 constexpr int kThreads = 256;                             // decompress / helper kernels
 constexpr int kWaves = kThreads / 64;
-constexpr uint32_t kMaxCpw = 16;                          // decompress: chunks per wave per tile, at most
 constexpr uint32_t kMaxRange = 256;                       // compress: chunks per tile, at most
 constexpr uint32_t kWsHeaderBytes = 512;                  // workspace: reserved words in front (cleared by splitzip_workspace_init, read by nobody)
 constexpr uint32_t kStatusBytes = 4u << 20;               // workspace: the escape counts of the tiles and their sums

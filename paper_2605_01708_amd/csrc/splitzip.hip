@@ -54,22 +54,17 @@ int cu_count() {
   return cached[dev];
 }
 
-// chunks per wave: the largest power of two (up to `most`) that still leaves `want` tiles per CU
-uint32_t pick_cpw(uint64_t n_chunks, uint32_t most, uint32_t want_tiles_per_cu) {
-  const uint64_t want = (uint64_t)cu_count() * want_tiles_per_cu;
-  uint32_t cpw = most;
-  while (cpw > 1 && (n_chunks + (uint64_t)kWaves * cpw - 1) / (kWaves * cpw) < want) cpw >>= 1;
-  return cpw;
-}
-
-// Chunks per wave of a decompress launch over n_chunks chunks in all.  Measured on 64 MiB BF16 /
-// 32 MiB E5M2 tensors: BF16 wants two chunks per wave from 32 768 chunks in a launch on (with the planes of both
-// asked for at once: 23.7 us per 64 MiB tensor against 24.1 us with one) and one below; E5M2 wants four for a
-// single tensor and eight for a whole cache in one launch.
+// Chunks per wave of a decompress launch over n_chunks chunks in all; us per call with one / two chunks per wave, or
+// as said, one call after the other on one stream:
+//   BF16  4.1 / 4.8 (2048 chunks), 5.7 / 5.5 (4096), 8.1 / 7.5 (8192), 13.3 / 12.8 (16 384), 15.5 / 16.2 (20 000),
+//         22.5 / 23.0 (32 768), 59.5 / 60.0 (98 304), 81.9 / 79.5 (131 072), 1325 / 1229 (2 Mi); three: worse everywhere.
+//         Two up to what is resident at once (eight workgroups of eight chunks per CU) and again for long launches.
+//   E5M2  with one / two / four: 4.2 / 4.8 / 6.1 (2048), 6.8 / 6.8 / 7.3 (8192), 11.5 / 9.7 / 9.5 (16 384),
+//         19.8 / 15.9 / 14.2 (32 768); four / five / eight: 45.9 / 46.9 / 47.6 (131 072), 657 / 678 / 671 (2 Mi).
 uint32_t pick_decompress_cpw(uint64_t n_chunks, int dtype) {
-  const uint32_t most = dtype == SPLITZIP_BF16 ? 2 : 8;
-  const uint32_t want = dtype == SPLITZIP_BF16 ? 16u : 8u;
-  return pick_cpw(n_chunks, most, want);
+  const uint64_t round = (uint64_t)cu_count() * 8;   // workgroups resident at a time
+  if (dtype == SPLITZIP_BF16) return (n_chunks >= 2 * round && n_chunks <= 8 * round) || n_chunks >= 56 * round ? 2u : 1u;
+  return n_chunks >= 8 * round ? 4u : n_chunks >= 4 * round ? 2u : 1u;
 }
 
 // tables must describe one bijection between 16 codes and 16 distinct exponents
@@ -874,8 +869,8 @@ int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dty
     a.reg_patch_max = kRegPatchDefault;
     uint64_t gx = (chunks_max + (uint64_t)kWaves * a.cpw - 1) / (kWaves * a.cpw);
     if (gx < 1) gx = 1;
-    // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 168.6 and 167.6
-    // (16 384), 46.8 and 46.8 (4096); BF16 1258 and 1237 (262 144), 1172 and 1152 (240 064), but 620 and 624 (131 072)
+    // us per call, in the order of the tiles and in xcd_order: E5M2 670 and 656 (131 072 workgroups), 86.7 and 86.4
+    // (16 384), 46.0 and 45.9 (8192); BF16 1258 and 1237 (262 144), 1172 and 1152 (240 064), but 620 and 624 (131 072)
     // and 301 and 301 (65 536).
     a.by_xcd = gx * k >= (dtype == SPLITZIP_BF16 ? 196608u : 16384u) ? 1u : 0u;
     const dim3 grid((unsigned)gx, k);
