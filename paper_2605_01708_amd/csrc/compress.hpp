@@ -329,7 +329,8 @@ struct Bf16 {
 #pragma unroll
       for (int d = 0; d < 4; ++d) asm volatile("" : "+v"(r.w[h][d]));
   }
-  // A workgroup of four waves takes a tile of 4 x kCpt chunks (16 KB of words).  Eight workgroups per CU, what the
+  // A workgroup of four waves takes a tile of 4 cpt chunks (pick_base_cpt: 16 KB of words, less for short launches), at
+  // most kCpt of a wave's chunks at a time.  Eight workgroups per CU, what the
   // registers allow, serve launches of few tiles best and five those of many: us per call with eight / five / four,
   // 1219 / 1199 / 1203 (262 144 tiles), 309 / 306 / 307 (65 536), 81.6 / 81.6 / 82.2 (16 384), 45.1 / 45.5 / 46.0
   // (8192), 26.5 / 26.9 / 27.1 (4096: one tensor), 17.4 / 18.1 / 18.0 (2048); unused LDS asked for at the launch sets
@@ -357,7 +358,7 @@ struct E5m2 {
 #pragma unroll
     for (int d = 0; d < 4; ++d) asm volatile("" : "+v"(r.w[d]));
   }
-  // a tile of 4 x kCpt chunks is 16 KB of words here too; eight workgroups per CU (730 us for 64 tensors of 32 MiB
+  // a tile of 16 chunks is 16 KB of words here; eight workgroups per CU (730 us for 64 tensors of 32 MiB
   // against 750 us with six and 790 us with five)
   static constexpr uint32_t kCpt = 4;
   static constexpr uint32_t kSmallChunks = 48;

@@ -579,12 +579,27 @@ uint32_t pick_cpt(uint64_t chunks, uint32_t at_least, uint64_t status_bytes) {
   return 0;
 }
 
+// Chunks per wave and tile to begin with, by the chunks of a launch.  A tile's time is mostly the latency of one wave's
+// work, so short launches are split finer, down to where the tiles no longer fill whole rounds of the chip, and long
+// ones are bound by how 16 KB runs stream.  us per call (device), by chunks per wave:
+//   BF16  one / two: 6.3 / 6.9 (100 chunks), 7.3 / 7.8 (2048), 9.4 / 9.9 (6000), 10.6 / 10.5 (8192), 15.8 / 15.9
+//         (16 384), 18.2 / 18.6 (19 200), 27.7 / 25.2 (32 768)
+//   E5M2  one / two / four: 6.4 / 6.9 / 8.0 (100), 8.0 / 8.2 / 9.6 (4096), 9.3 / 9.1 / 10.9 (8192), 12.9 / 12.0 / 14.3
+//         (16 384), two / four: 17.6 / 18.8 (32 768), 167.6 / 170.1 (524 288), 338.3 / 336.3 (1 Mi), 666 / 661 (2 Mi)
+uint32_t pick_base_cpt(uint64_t chunks, int dtype) {
+  if (dtype == SPLITZIP_BF16) return chunks <= 20480 ? 1u : 2u;
+  return chunks <= 6144 ? 1u : chunks <= 786432 ? 2u : 4u;
+}
+
 // the launches of k tensors: dense pass (one workgroup per tile, started by the hardware in the tiles' order), sums if
 // the finishing pass wants them, finishing pass
 template <typename F, uint32_t N>
 void launch_compress(unsigned tiles, unsigned finish_wgs, unsigned sums, unsigned k, unsigned lds_pad, hipStream_t st, const TileArgs<N>& args) {
   if (tiles) {
-    hipLaunchKernelGGL((compress_tile_kernel<F, F::kCpt, N>), dim3(tiles, k), dim3(kTileThreads), lds_pad, st, args);
+    const dim3 grid(tiles, k), block(kTileThreads);
+    if (args.shared.cpt == 1) hipLaunchKernelGGL((compress_tile_kernel<F, 1, N>), grid, block, lds_pad, st, args);
+    else if (args.shared.cpt == 2 || F::kCpt == 2) hipLaunchKernelGGL((compress_tile_kernel<F, 2, N>), grid, block, lds_pad, st, args);
+    else hipLaunchKernelGGL((compress_tile_kernel<F, F::kCpt, N>), grid, block, lds_pad, st, args);
     if (args.shared.use_group_sums) hipLaunchKernelGGL((tile_group_sum_kernel<F, N>), dim3(sums, k), dim3(64), 0, st, args);
   }
   hipLaunchKernelGGL((compress_finish_kernel<F, N>), dim3(finish_wgs ? finish_wgs : 1u, k), dim3(kTileThreads), 0, st, args);
@@ -624,14 +639,15 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
   if (rc != SPLITZIP_OK) return rc;
   if (n_items == 0) return SPLITZIP_OK;
   if (!pick_cpt(chunks_of(n_max), 1, ws.status_bytes)) return SPLITZIP_ERR_CAPACITY;
-  const uint32_t base_cpt = dtype == SPLITZIP_BF16 ? Bf16::kCpt : E5m2::kCpt;
   const hipStream_t st = static_cast<hipStream_t>(stream);
 
   uint32_t i = 0;
   while (i < n_items) {
     // one pair of launches: as many of the next tensors (kBatchMax at most) as find room for their counts in the
     // status area; all of them share the tile size of the one that needs the largest
-    uint32_t k = 0, cpt = base_cpt;
+    uint64_t chunks_all = 0;
+    for (uint32_t q = i; q < n_items && q < i + kBatchMax; ++q) chunks_all += chunks_of(items[q].n_elems);
+    uint32_t k = 0, cpt = pick_base_cpt(chunks_all, dtype);
     for (; i + k < n_items && k < kBatchMax; ++k) {
       const uint32_t need = pick_cpt(chunks_of(items[i + k].n_elems), cpt, ws.status_bytes);
       uint64_t total = 0;
