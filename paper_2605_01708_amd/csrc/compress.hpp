@@ -51,11 +51,16 @@ struct SlotSink {
     if (r < cap) slot[r] = p | (e << 16);
   }
 };
+// records of 2^shift bytes between `from` and `capacity`, 2^32 - 1 at most (ranks are compared in 32 bits)
+__device__ inline uint32_t room32(uint64_t capacity, uint64_t from, int shift) {
+  const uint64_t room = capacity > from ? (capacity - from) >> shift : 0;
+  return room < 0xffffffffull ? (uint32_t)room : 0xffffffffu;
+}
 // the final place of the records of a tensor: positions and, behind them, values
 struct FinalSink {
   uint16_t* pos;
   uint8_t* val;
-  uint64_t pos_room, val_room;   // records that fit below the capacity
+  uint32_t pos_room, val_room;   // records that fit below the capacity (a tensor has fewer than 2^32)
   __device__ inline void put(uint32_t r, uint32_t p, uint32_t e) const {
     if (r < pos_room) pos[r] = (uint16_t)p;
     if (r < val_room) val[r] = (uint8_t)e;
@@ -747,9 +752,9 @@ __global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const 
   const uint64_t off_val = P.off_pos + a256(2ull * M);
   FinalSink fin;
   fin.pos = reinterpret_cast<uint16_t*>(P.out + P.off_pos);
-  fin.pos_room = P.capacity > P.off_pos ? (P.capacity - P.off_pos) / 2 : 0;
+  fin.pos_room = room32(P.capacity, P.off_pos, 1);
   fin.val = P.out + off_val;
-  fin.val_room = P.capacity > off_val ? P.capacity - off_val : 0;
+  fin.val_room = room32(P.capacity, off_val, 0);
 
   // header, pads and sizes by one wave of the first workgroup, which does it while the others place the records
   if (g0 == 0 && wave == NW - 1) compress_write_trailer(P, a.dec16_of(it, item), a.sizes + item, M, 0u, lane);
@@ -886,9 +891,9 @@ __global__ __launch_bounds__(kSmallThreads) void compress_small_kernel(const Til
   const uint64_t off_val = P.off_pos + a256(2ull * M);
   FinalSink fin;
   fin.pos = reinterpret_cast<uint16_t*>(P.out + P.off_pos);
-  fin.pos_room = P.capacity > P.off_pos ? (P.capacity - P.off_pos) / 2 : 0;
+  fin.pos_room = room32(P.capacity, P.off_pos, 1);
   fin.val = P.out + off_val;
-  fin.val_room = P.capacity > off_val ? P.capacity - off_val : 0;
+  fin.val_room = room32(P.capacity, off_val, 0);
   uint32_t* tab = reinterpret_cast<uint32_t*>(P.out + P.off_tab);
   if ((uint32_t)lane < mine) tab[c0 + lane] = first + my_start;
   if (count <= kSmallStageCap) {

@@ -367,6 +367,8 @@ __global__ __launch_bounds__(kThreads) void v_dense_kernel(const VArgs a) {
     for (int q = 0; q < kWaves; ++q) sum += s_cnt[q];
     a.wg_sums[blockIdx.x] = sum;
   }
+  // the finishing pass reads whole vectors of four sums
+  if (blockIdx.x == gridDim.x - 1 && tid > 0 && tid < 4 && (blockIdx.x & 3u) + tid < 4) a.wg_sums[blockIdx.x + tid] = 0;
 }
 
 constexpr uint32_t kVScanTile = 1024;   // counts per workgroup of the summing kernel
@@ -395,6 +397,8 @@ __global__ __launch_bounds__(1024) void v_tile_sum_kernel(const VArgs a) {
   uint32_t incl, before;
   const uint32_t all = v_block_sum(c < a.n_chunks ? a.counts[c] : 0u, s_wave, incl, before);
   if (threadIdx.x == 0) a.tile_sums[blockIdx.x] = all;
+  // the finishing pass reads whole vectors of four sums
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x > 0 && threadIdx.x < 4 && (blockIdx.x & 3u) + threadIdx.x < 4) a.tile_sums[blockIdx.x + threadIdx.x] = 0;
 }
 
 constexpr uint32_t kVFinishBlocks = 32;   // blocks of 1024 elements per workgroup of the finishing pass
@@ -408,14 +412,14 @@ template <int PB>
 struct VSink {
   uint8_t* pos;
   uint8_t* val;
-  uint64_t pos_room, val_room;
+  uint32_t pos_room, val_room;
   uint32_t pos_mask;   // of the element index: relative to the chunk, or (absolute mode) all of it
   __device__ inline VSink(const VArgs& a, uint32_t M) {
     const uint64_t off_val = a.off_pos + a256((uint64_t)PB * M);
     pos = a.out + a.off_pos;
-    pos_room = PB == 0 ? 0 : a.capacity > a.off_pos ? (a.capacity - a.off_pos) / (PB ? PB : 1) : 0;
+    pos_room = PB == 0 ? 0 : room32(a.capacity, a.off_pos, PB == 4 ? 2 : PB == 2 ? 1 : 0);
     val = a.val_bits == 8 ? a.out + off_val : a.val_stage;
-    val_room = a.val_bits != 8 ? ~0ull : a.capacity > off_val ? a.capacity - off_val : 0;
+    val_room = a.val_bits != 8 ? ~0u : room32(a.capacity, off_val, 0);
     pos_mask = PB == 4 ? ~0u : (1u << a.chunk_shift) - 1u;
   }
   __device__ inline void put(uint32_t rank, uint32_t elem, uint32_t e) const {
@@ -463,26 +467,23 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs a) {
   // escapes before the group's first chunk and in the whole tensor: by the sums that lie before it entirely, the rest by chunk
   uint32_t before = 0, all = 0;
   const uint64_t whole = c0 >> a.sum_shift;
-  const u32x4* sv = reinterpret_cast<const u32x4*>(a.sums);   // 16-byte aligned, in a region of whole 256 bytes: the last vector may hold words of no meaning
-  for (uint32_t v0 = 0; 4 * v0 < a.n_sums; v0 += 4 * kThreads) {
+  const u32x4* sv = reinterpret_cast<const u32x4*>(a.sums);   // 16-byte aligned; what the last vector holds behind the sums is zero
+  const uint32_t nvec = (a.n_sums + 3) / 4, v_first = (uint32_t)(whole / 4);
+  for (uint32_t v0 = 0; v0 < nvec; v0 += 4 * kThreads) {
     u32x4 v[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const uint32_t idx = v0 + q * kThreads + tid;
-      v[q] = 4 * idx < a.n_sums ? sv[idx] : u32x4{0u, 0u, 0u, 0u};
+      v[q] = idx < nvec ? sv[idx] : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const uint32_t e = 4 * (v0 + q * kThreads + tid);
-      const uint32_t c[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-      for (uint32_t z = 0; z < 4; ++z) {
-        const uint32_t cz = e + z < a.n_sums ? c[z] : 0u;
-        all += cz;
-        before += e + z < whole ? cz : 0u;
-      }
+      const uint32_t sum = v[q].x + v[q].y + v[q].z + v[q].w;
+      all += sum;
+      before += v0 + q * kThreads + tid < v_first ? sum : 0u;
     }
   }
+  if (tid < (whole & 3u)) before += a.sums[4 * v_first + tid];   // sums of the vector that the group starts in
   for (uint64_t c = (whole << a.sum_shift) + tid; c < c0 && c < a.n_chunks; c += kThreads) before += a.counts[c];
   const uint32_t incl = wave_incl_scan(mine);
   before = wave_last(wave_incl_scan(before));
