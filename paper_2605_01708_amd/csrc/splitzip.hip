@@ -60,11 +60,13 @@ int cu_count() {
 //         22.5 / 23.0 (32 768), 59.5 / 60.0 (98 304), 81.9 / 79.5 (131 072), 1325 / 1229 (2 Mi); three: worse everywhere.
 //         Two up to what is resident at once (eight workgroups of eight chunks per CU) and again for long launches.
 //   E5M2  with one / two / four: 4.2 / 4.8 / 6.1 (2048), 6.8 / 6.8 / 7.3 (8192), 11.5 / 9.7 / 9.5 (16 384),
-//         19.8 / 15.9 / 14.2 (32 768); four / five / eight: 45.9 / 46.9 / 47.6 (131 072), 657 / 678 / 671 (2 Mi).
+//         19.8 / 15.9 / 14.2 (32 768); four / five / eight: 45.9 / 46.9 / 47.6 (131 072), 657 / 678 / 671 (2 Mi).  The
+//         longest launches take eight all the same: in the first 20 ms of load after a pause four took 705 to 765 us
+//         there, eight 668 to 688.
 uint32_t pick_decompress_cpw(uint64_t n_chunks, int dtype) {
   const uint64_t round = (uint64_t)cu_count() * 8;   // workgroups resident at a time
   if (dtype == SPLITZIP_BF16) return (n_chunks >= 2 * round && n_chunks <= 8 * round) || n_chunks >= 56 * round ? 2u : 1u;
-  return n_chunks >= 8 * round ? 4u : n_chunks >= 4 * round ? 2u : 1u;
+  return n_chunks >= 512 * round ? 8u : n_chunks >= 8 * round ? 4u : n_chunks >= 4 * round ? 2u : 1u;
 }
 
 // tables must describe one bijection between 16 codes and 16 distinct exponents
@@ -885,7 +887,7 @@ int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dty
     a.reg_patch_max = kRegPatchDefault;
     uint64_t gx = (chunks_max + (uint64_t)kWaves * a.cpw - 1) / (kWaves * a.cpw);
     if (gx < 1) gx = 1;
-    // us per call, in the order of the tiles and in xcd_order: E5M2 670 and 656 (131 072 workgroups), 86.7 and 86.4
+    // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 86.7 and 86.4
     // (16 384), 46.0 and 45.9 (8192); BF16 1258 and 1237 (262 144), 1172 and 1152 (240 064), but 620 and 624 (131 072)
     // and 301 and 301 (65 536).
     a.by_xcd = gx * k >= (dtype == SPLITZIP_BF16 ? 196608u : 16384u) ? 1u : 0u;
