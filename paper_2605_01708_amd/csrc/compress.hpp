@@ -1,4 +1,4 @@
-// SplitZip for MI355X: the compress kernels (dense transform of both formats with escape staging, one tile per workgroup; the finishing pass that ranks and places the escape records; the trailer).
+// SplitZip for MI355X: the compress kernels (dense transform of both formats with escape staging, one tile per workgroup; the finishing pass that ranks and places the escape records; the trailer; the one-launch kernel for small tensors).
 // Part of the single translation unit splitzip.hip (included inside its anonymous namespace).
 #ifndef SPLITZIP_COMPRESS_HPP
 #define SPLITZIP_COMPRESS_HPP
@@ -414,9 +414,9 @@ __device__ void compress_write_trailer(const Planes& a, const u32x4& dec, splitz
 }
 
 // ---- the two passes of a compress call ----
-// Pass 1, compress_tile_kernel: one workgroup of four waves per tile of 4 x cpt chunks (16 KB of words), started by
-// the hardware in the order of the tiles -- the access pattern the memory system likes best, see
-// traffic_shape_kernel.  A workgroup waits for nobody: planes out; escapes of the tile staged in LDS, then written
+// Pass 1, compress_tile_kernel: one workgroup of four waves per tile of 4 x cpt chunks (16 KB of words in long
+// launches, less in short ones: pick_base_cpt), started by the hardware in the order of the tiles -- the access
+// pattern the memory system likes best, see traffic_shape_kernel -- or, in long launches, in xcd_order.  A workgroup waits for nobody: planes out; escapes of the tile staged in LDS, then written
 // as (position | exponent << 16) records, in element order, to the tile's slot of the staging area; the tile's
 // entries of the offset table as offsets inside the tile; the tile's escape count to the status area.
 // Pass 2, compress_finish_kernel: one workgroup per group of 16 tiles.  It sums the counts (all of the tensor's:
