@@ -129,6 +129,12 @@ def lib():
         L.splitzip_compress_noalloc.argtypes = [vp, u64, i, cbp, vp, sz, vp, vp]
         L.splitzip_internal_test_hooks.restype = None
         L.splitzip_internal_test_hooks.argtypes = [u64, u64, C.c_uint32, u64]
+        L.splitzip_internal_test_launch.restype = None
+        L.splitzip_internal_test_launch.argtypes = [C.c_uint32, C.c_uint32, C.c_uint32]
+        L.splitzip_internal_compress_plan.restype = None
+        L.splitzip_internal_compress_plan.argtypes = [C.POINTER(_CItem), C.c_uint32, i, C.POINTER(C.c_uint32)]
+        L.splitzip_internal_decompress_plan.restype = None
+        L.splitzip_internal_decompress_plan.argtypes = [C.POINTER(_CDItem), C.c_uint32, i, C.POINTER(C.c_uint32)]
         L.splitzip_traffic_probe.restype = i
         L.splitzip_traffic_probe.argtypes = [vp, sz, vp, sz, vp]
         L.splitzip_traffic_probe_shape.restype = i
@@ -343,6 +349,31 @@ def internal_test_hooks(stage_bytes: int = 0, status_bytes: int = 0, finish_grou
     than the workspace has, the groups of tiles per workgroup of the finishing pass (1, 2 or 4), and the bytes of tile
     counts a launch's finishing pass may read directly (beyond: sums of 64 counts).  0 = as built."""
     lib().splitzip_internal_test_hooks(stage_bytes, status_bytes, finish_groups, direct_bytes)
+
+
+def internal_test_launch(cpt: int = 0, cpw: int = 0, xcd: int = 0) -> None:
+    """Forces what the launch rules choose by size (not part of splitzip.h): chunks per wave of the compress tiles (cpt) and
+    of the decoders (cpw), 1, 2, 4 or 8, and the tiles' order in batch launches (xcd: 1 their own, 2 xcd_order).
+    0 = by the rules."""
+    lib().splitzip_internal_test_launch(cpt, cpw, xcd)
+
+
+def internal_compress_plan(n_elems, dtype: int) -> dict:
+    """How a compress call's first launch over tensors of these lengths is shaped (host only, for tests of the rules)."""
+    items, out = (_CItem * len(n_elems))(), (C.c_uint32 * 8)()
+    for it, n in zip(items, n_elems):
+        it.n_elems = n
+    lib().splitzip_internal_compress_plan(items, len(n_elems), dtype, out)
+    return dict(zip(("tensors", "cpt", "tiles_max", "launches", "by_xcd", "finish_groups", "group_sums", "small"), out))
+
+
+def internal_decompress_plan(n_elems, dtype: int) -> dict:
+    """The same for a batch decompress call."""
+    items, out = (_CDItem * len(n_elems))(), (C.c_uint32 * 3)()
+    for it, n in zip(items, n_elems):
+        it.n_elems = n
+    lib().splitzip_internal_decompress_plan(items, len(n_elems), dtype, out)
+    return dict(zip(("cpw", "workgroups", "by_xcd"), out))
 
 
 def noalloc_max_elems() -> int:

@@ -54,6 +54,25 @@ int cu_count() {
   return cached[dev];
 }
 
+// What the tests of the rarely taken paths turn: a staging area and a status area smaller than the workspace has
+// (tiles whose records do not fit their slots; batches that take several launches), and the number of groups a
+// workgroup of the finishing pass takes, which small launches would leave at one, and the bytes of tile counts the
+// finishing pass may read directly before it is given sums instead.  Set through
+// splitzip_internal_test_hooks (exported, not declared in splitzip.h); zero in normal use.
+// And what the launch rules choose by the sizes of a call, so that every choice can be tested at any size (set through
+// splitzip_internal_test_launch): chunks per wave of the compress tiles and of the decoders, and the tiles' order.
+struct TestHooks {
+  std::atomic<uint64_t> stage_bytes{0};
+  std::atomic<uint64_t> status_bytes{0};
+  std::atomic<uint32_t> finish_groups{0};
+  std::atomic<uint64_t> direct_bytes{0};
+  std::atomic<uint32_t> cpt{0};   // 1, 2, 4 or 8
+  std::atomic<uint32_t> cpw{0};   // 1, 2, 4 or 8
+  std::atomic<uint32_t> xcd{0};   // 1: batch launches keep the tiles' own order, 2: they take xcd_order
+  bool any() const { return stage_bytes || status_bytes || finish_groups || direct_bytes || cpt || xcd; }   // the two-launch path is meant
+};
+TestHooks g_hooks;
+
 // Chunks per wave of a decompress launch over n_chunks chunks in all; us per call with one / two chunks per wave, or
 // as said, one call after the other on one stream:
 //   BF16  4.1 / 4.8 (2048 chunks), 5.7 / 5.5 (4096), 8.1 / 7.5 (8192), 13.3 / 12.8 (16 384), 15.5 / 16.2 (20 000),
@@ -64,6 +83,7 @@ int cu_count() {
 //         longest launches take eight all the same: in the first 20 ms of load after a pause four took 705 to 765 us
 //         there, eight 668 to 688.
 uint32_t pick_decompress_cpw(uint64_t n_chunks, int dtype) {
+  if (const uint32_t forced = g_hooks.cpw.load()) return forced;
   const uint64_t round = (uint64_t)cu_count() * 8;   // workgroups resident at a time
   if (dtype == SPLITZIP_BF16) return (n_chunks >= 2 * round && n_chunks <= 8 * round) || n_chunks >= 56 * round ? 2u : 1u;
   return n_chunks >= 512 * round ? 8u : n_chunks >= 8 * round ? 4u : n_chunks >= 4 * round ? 2u : 1u;
@@ -84,20 +104,6 @@ bool codebook_ok(const splitzip_codebook* cb, int dtype) {
   }
   return members == 16;
 }
-
-// What the tests of the rarely taken paths turn: a staging area and a status area smaller than the workspace has
-// (tiles whose records do not fit their slots; batches that take several launches), and the number of groups a
-// workgroup of the finishing pass takes, which small launches would leave at one, and the bytes of tile counts the
-// finishing pass may read directly before it is given sums instead.  Set through
-// splitzip_internal_test_hooks (exported, not declared in splitzip.h); zero in normal use.
-struct TestHooks {
-  std::atomic<uint64_t> stage_bytes{0};
-  std::atomic<uint64_t> status_bytes{0};
-  std::atomic<uint32_t> finish_groups{0};
-  std::atomic<uint64_t> direct_bytes{0};
-  bool any() const { return stage_bytes || status_bytes || finish_groups || direct_bytes; }   // the two-launch path is meant
-};
-TestHooks g_hooks;
 
 // ---------------------------------------------------------------------------
 // format variants: host side
@@ -490,6 +496,13 @@ void splitzip_internal_test_hooks(uint64_t stage_bytes, uint64_t status_bytes, u
   g_hooks.finish_groups = finish_groups == 1 || finish_groups == 2 || finish_groups == 4 ? finish_groups : 0;
 }
 
+void splitzip_internal_test_launch(uint32_t cpt, uint32_t cpw, uint32_t xcd) {
+  const auto size_or_0 = [](uint32_t v) { return v == 1 || v == 2 || v == 4 || v == 8 ? v : 0u; };
+  g_hooks.cpt = size_or_0(cpt);
+  g_hooks.cpw = size_or_0(cpw);
+  g_hooks.xcd = xcd <= 2 ? xcd : 0u;
+}
+
 }  // extern "C"
 
 namespace {
@@ -617,6 +630,62 @@ void launch_small(unsigned k, hipStream_t st, const TileArgs<kBatchMax>& args) {
   }
 }
 
+// How the next tensors of a compress call are launched: a function of their lengths, the word type and the status area.
+struct CompressPlan {
+  uint32_t k;               // tensors of this launch; 0 if not even one fits
+  uint32_t cpt;             // chunks per wave and tile
+  uint64_t tiles_max;       // of the longest tensor: the dense pass has k rows of so many workgroups
+  bool small;               // one launch of compress_small_kernel
+  bool by_xcd;              // the dense pass takes its tiles in xcd_order, BF16 with fewer workgroups per CU
+  uint32_t finish_groups;   // groups of kGroup tiles per workgroup of the finishing pass
+  uint32_t finish_wgs;      // workgroups of the finishing pass per tensor
+  bool group_sums;          // the finishing pass is given sums of kSumGroup tile counts
+  uint32_t launches() const { return small ? 1u : group_sums ? 3u : tiles_max ? 2u : 1u; }
+};
+
+// items[0, n_items): what is left of the call; n_max: its longest tensor
+CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_t n_max, int dtype, uint64_t status_bytes) {
+  CompressPlan p;
+  memset(&p, 0, sizeof p);
+  // as many of the next tensors (kBatchMax at most) as find room for their counts in the status area; all of them share
+  // the tile size of the one that needs the largest
+  uint64_t chunks_all = 0;
+  for (uint32_t q = 0; q < n_items && q < kBatchMax; ++q) chunks_all += chunks_of(items[q].n_elems);
+  const uint32_t forced_cpt = g_hooks.cpt.load();
+  p.cpt = forced_cpt ? forced_cpt : pick_base_cpt(chunks_all, dtype);
+  for (; p.k < n_items && p.k < kBatchMax; ++p.k) {
+    const uint32_t need = pick_cpt(chunks_of(items[p.k].n_elems), p.cpt, status_bytes);
+    uint64_t total = 0;
+    for (uint32_t q = 0; q <= p.k && need; ++q) total += status_need(tiles_of(chunks_of(items[q].n_elems), need));
+    if (!need || total > status_bytes) break;
+    p.cpt = need;
+  }
+  for (uint32_t q = 0; q < p.k; ++q) {
+    const uint64_t tiles = tiles_of(chunks_of(items[q].n_elems), p.cpt);
+    if (tiles > p.tiles_max) p.tiles_max = tiles;
+  }
+  p.small = chunks_of(n_max) <= (dtype == SPLITZIP_BF16 ? Bf16::kSmallChunks : E5m2::kSmallChunks) && !g_hooks.any();
+  // Launches of many tiles, from 16 384 (256 MB of words) on, take them in xcd_order, and BF16 with fewer workgroups
+  // per CU (Bf16::kTileLdsPad).  us per call, in the order of the tiles and in xcd_order: BF16 1241 and
+  // 1201 (262 144 tiles), 314 and 307 (65 536), 83.2 and 82.4 (16 384); E5M2 690 and 665 (131 072), 173.4 and 171.7
+  // (32 768), 49.7 and 49.8 (8192).
+  p.by_xcd = p.tiles_max * p.k >= 16384;
+  if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2;
+  const uint32_t groups_max = (uint32_t)((p.tiles_max + kGroup - 1) / kGroup);
+  // many groups in the launch: several per workgroup, as long as the chip still gets a few workgroups per CU
+  p.finish_groups = 1;
+  while (p.finish_groups < kFinishMost && (uint64_t)groups_max * p.k / (2 * p.finish_groups) >= (uint64_t)cu_count() * 8) p.finish_groups *= 2;
+  if (const uint32_t forced = g_hooks.finish_groups.load()) p.finish_groups = forced;
+  p.finish_wgs = (groups_max + p.finish_groups - 1) / p.finish_groups;
+  // A finishing workgroup that sums all tile counts of its tensor itself reads 4 bytes per tile: fine while all
+  // workgroups of the launch together read no more than kDirectBytes that way, mostly from the L2 (one launch
+  // fewer; 64 tensors of 64 MiB: 67 MB of counts read, 1259 us per call against 1262-1292 us with the sums);
+  // beyond that they read sums of kSumGroup counts instead (tile_group_sum_kernel).
+  const uint64_t direct_budget = g_hooks.direct_bytes.load() ? g_hooks.direct_bytes.load() : kDirectBytes;
+  p.group_sums = p.tiles_max > kDirectTiles || (uint64_t)p.finish_wgs * p.k * p.tiles_max * 4 > direct_budget;
+  return p;
+}
+
 // The compress calls, all of them: n_items tensors (a host list), each under its own codebook -- the items' own (host)
 // or d_cbs[k] (device memory).  paging: table and page geometry shared by all items, or contiguous tensors (table null).
 // d_workspace: the caller's workspace, or null with own_scratch for the library's own array.
@@ -645,22 +714,12 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
 
   uint32_t i = 0;
   while (i < n_items) {
-    // one pair of launches: as many of the next tensors (kBatchMax at most) as find room for their counts in the
-    // status area; all of them share the tile size of the one that needs the largest
-    uint64_t chunks_all = 0;
-    for (uint32_t q = i; q < n_items && q < i + kBatchMax; ++q) chunks_all += chunks_of(items[q].n_elems);
-    uint32_t k = 0, cpt = pick_base_cpt(chunks_all, dtype);
-    for (; i + k < n_items && k < kBatchMax; ++k) {
-      const uint32_t need = pick_cpt(chunks_of(items[i + k].n_elems), cpt, ws.status_bytes);
-      uint64_t total = 0;
-      for (uint32_t q = 0; q <= k && need; ++q) total += status_need(tiles_of(chunks_of(items[i + q].n_elems), need));
-      if (!need || total > ws.status_bytes) break;
-      cpt = need;
-    }
+    const CompressPlan p = plan_compress(items + i, n_items - i, n_max, dtype, ws.status_bytes);
+    const uint32_t k = p.k;
     if (k == 0) return SPLITZIP_ERR_CAPACITY;   // cannot happen: every tensor fits alone
     TileArgs<kBatchMax> args;   // the first k items are filled in, and no other is looked at
     TileShared& a = args.shared;
-    uint64_t off = 0, tiles_max = 0;
+    uint64_t off = 0;
     for (uint32_t q = 0; q < k; ++q) {
       const splitzip_item& it = items[i + q];
       TileItem& to = args.item[q];
@@ -670,53 +729,36 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       to.out = static_cast<uint8_t*>(it.d_out);
       to.n = (uint32_t)it.n_elems;
       to.capacity = it.out_capacity;
-      const uint64_t tiles = tiles_of(chunks_of(it.n_elems), cpt);
       to.status_off = (uint32_t)off;
-      off += status_need(tiles);
-      if (tiles > tiles_max) tiles_max = tiles;
+      off += status_need(tiles_of(chunks_of(it.n_elems), p.cpt));
     }
     a.sizes = d_sizes + i;
     a.d_cbs = d_cbs ? d_cbs + i : nullptr;
     a.status = ws.base + kWsHeaderBytes;
     a.stage = ws.base + kWsHeaderBytes + ws.status_bytes;
     a.stage_cap = (ws.stage_bytes / k) & ~(uint64_t)255u;
-    a.cpt = cpt;
-    a.tile_shift = 2u + (uint32_t)__builtin_ctz(cpt);
+    a.cpt = p.cpt;
+    a.tile_shift = 2u + (uint32_t)__builtin_ctz(p.cpt);
     {
-      const uint64_t per_tile = tiles_max ? a.stage_cap / 4 / tiles_max : 0;
+      const uint64_t per_tile = p.tiles_max ? a.stage_cap / 4 / p.tiles_max : 0;
       a.slot_cap = (uint32_t)(per_tile < kSlotCapMost ? per_tile : kSlotCapMost);
     }
     a.paging = paging;
-    // Launches of many tiles, from 16 384 (256 MB of words) on, take them in xcd_order, and BF16 with fewer workgroups
-    // per CU (Bf16::kTileLdsPad).  us per call, in the order of the tiles and in xcd_order: BF16 1241 and
-    // 1201 (262 144 tiles), 314 and 307 (65 536), 83.2 and 82.4 (16 384); E5M2 690 and 665 (131 072), 173.4 and 171.7
-    // (32 768), 49.7 and 49.8 (8192).
-    const bool many = tiles_max * k >= 16384;
-    a.xcd_row = many ? (uint32_t)tiles_max : 0u;
-    const unsigned groups_max = (unsigned)((tiles_max + kGroup - 1) / kGroup), sums_max = (unsigned)((tiles_max + kSumGroup - 1) / kSumGroup);
-    // many groups in the launch: several per workgroup, as long as the chip still gets a few workgroups per CU
-    a.finish_groups = 1;
-    while (a.finish_groups < kFinishMost && (uint64_t)groups_max * k / (2 * a.finish_groups) >= (uint64_t)cu_count() * 8) a.finish_groups *= 2;
-    if (const uint32_t forced = g_hooks.finish_groups.load()) a.finish_groups = forced;
-    const unsigned fgroups = (groups_max + a.finish_groups - 1) / a.finish_groups;
-    // A finishing workgroup that sums all tile counts of its tensor itself reads 4 bytes per tile: fine while all
-    // workgroups of the launch together read no more than kDirectBytes that way, mostly from the L2 (one launch
-    // fewer; 64 tensors of 64 MiB: 67 MB of counts read, 1259 us per call against 1262-1292 us with the sums);
-    // beyond that they read sums of kSumGroup counts instead (tile_group_sum_kernel).
-    const uint64_t direct_budget = g_hooks.direct_bytes.load() ? g_hooks.direct_bytes.load() : kDirectBytes;
-    a.use_group_sums = tiles_max > kDirectTiles || (uint64_t)fgroups * k * tiles_max * 4 > direct_budget ? 1u : 0u;
-    const bool small = chunks_of(n_max) <= (dtype == SPLITZIP_BF16 ? Bf16::kSmallChunks : E5m2::kSmallChunks) && !g_hooks.any();
-    const unsigned pad = many && dtype == SPLITZIP_BF16 ? Bf16::kTileLdsPad : 0u;
-    if (small) {
+    a.finish_groups = p.finish_groups;
+    a.use_group_sums = p.group_sums ? 1u : 0u;
+    a.xcd_row = p.by_xcd ? (uint32_t)p.tiles_max : 0u;
+    const unsigned tiles_max = (unsigned)p.tiles_max, sums_max = (tiles_max + kSumGroup - 1) / kSumGroup;
+    const unsigned pad = p.by_xcd && dtype == SPLITZIP_BF16 ? Bf16::kTileLdsPad : 0u;
+    if (p.small) {
       if (dtype == SPLITZIP_BF16) launch_small<Bf16>(k, st, args);
       else launch_small<E5m2>(k, st, args);
     } else if (k == 1) {
       const TileArgs<1> one = {args.shared, {args.item[0]}};
-      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>((unsigned)tiles_max, fgroups, sums_max, 1, pad, st, one);
-      else launch_compress<E5m2>((unsigned)tiles_max, fgroups, sums_max, 1, pad, st, one);
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, 1, pad, st, one);
+      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, 1, pad, st, one);
     } else {
-      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>((unsigned)tiles_max, fgroups, sums_max, k, pad, st, args);
-      else launch_compress<E5m2>((unsigned)tiles_max, fgroups, sums_max, k, pad, st, args);
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, k, pad, st, args);
+      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, k, pad, st, args);
     }
     if (hipGetLastError() != hipSuccess) return SPLITZIP_ERR_HIP;
     i += k;
@@ -846,6 +888,31 @@ int splitzip_decompress_own(const void* d_comp, size_t comp_bytes, uint64_t n_el
 
 namespace {
 
+// how up to kBatchMax streams of a batch decompress call are launched, by the lengths of what they decode to
+struct DecompressPlan {
+  uint32_t cpw;        // chunks per wave
+  uint32_t wgs;        // workgroups per stream: what the longest needs
+  uint32_t by_xcd;     // they take their tiles in xcd_order
+};
+DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtype) {
+  uint64_t chunks_all = 0, chunks_max = 0;
+  for (uint32_t q = 0; q < k; ++q) {
+    const uint64_t c = chunks_of(items[q].n_elems);
+    chunks_all += c;
+    if (c > chunks_max) chunks_max = c;
+  }
+  DecompressPlan p;
+  p.cpw = pick_decompress_cpw(chunks_all, dtype);
+  p.wgs = (uint32_t)((chunks_max + (uint64_t)kWaves * p.cpw - 1) / (kWaves * p.cpw));
+  if (p.wgs < 1) p.wgs = 1;
+  // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 86.7 and 86.4
+  // (16 384), 46.0 and 45.9 (8192); BF16 1258 and 1237 (262 144), 1172 and 1152 (240 064), but 620 and 624 (131 072)
+  // and 301 and 301 (65 536).
+  p.by_xcd = (uint64_t)p.wgs * k >= (dtype == SPLITZIP_BF16 ? 196608u : 16384u) ? 1u : 0u;
+  if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2 ? 1u : 0u;
+  return p;
+}
+
 // the batch decompress calls; paging: table and page geometry shared by all items, or contiguous tensors (table null)
 // d_cbs (nullable): n_items codebooks in device memory, used instead of the items' own
 int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dtype, const Words& paging, uint64_t paged_room,
@@ -866,7 +933,6 @@ int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dty
     DecompressBatchArgs a;
     memset(&a, 0, sizeof a);
     uint32_t k = 0;
-    uint64_t chunks_all = 0, chunks_max = 0;
     for (; i + k < n_items && k < kBatchMax; ++k) {
       const splitzip_ditem& it = items[i + k];
       if (!d_cbs && !own_dec) memcpy(a.dec[k], it.cb->dec, 16);
@@ -874,24 +940,17 @@ int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dty
       a.item[k].out = static_cast<uint8_t*>(it.d_out);
       a.item[k].n = it.n_elems;
       a.item[k].comp_bytes = it.comp_bytes;
-      const uint64_t c = (it.n_elems + kChunk - 1) / kChunk;
-      chunks_all += c;
-      if (c > chunks_max) chunks_max = c;
     }
     a.sizes = d_sizes;
     a.d_cbs = d_cbs ? d_cbs + i : nullptr;
     a.own_dec = own_dec ? 1u : 0u;
     a.dtype = (uint32_t)dtype;
     a.paging = paging;
-    a.cpw = pick_decompress_cpw(chunks_all, dtype);
+    const DecompressPlan p = plan_decompress(items + i, k, dtype);
+    a.cpw = p.cpw;
+    a.by_xcd = p.by_xcd;
     a.reg_patch_max = kRegPatchDefault;
-    uint64_t gx = (chunks_max + (uint64_t)kWaves * a.cpw - 1) / (kWaves * a.cpw);
-    if (gx < 1) gx = 1;
-    // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 86.7 and 86.4
-    // (16 384), 46.0 and 45.9 (8192); BF16 1258 and 1237 (262 144), 1172 and 1152 (240 064), but 620 and 624 (131 072)
-    // and 301 and 301 (65 536).
-    a.by_xcd = gx * k >= (dtype == SPLITZIP_BF16 ? 196608u : 16384u) ? 1u : 0u;
-    const dim3 grid((unsigned)gx, k);
+    const dim3 grid(p.wgs, k);
     if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL(decompress_batch_kernel<DBf16>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), a);
     else hipLaunchKernelGGL(decompress_batch_kernel<DE5m2>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), a);
     if (hipGetLastError() != hipSuccess) return SPLITZIP_ERR_HIP;
@@ -982,6 +1041,20 @@ int splitzip_decompress_batch_paged(const splitzip_ditem* items, uint32_t n_item
   Words w;
   if (!dtype_ok(dtype) || !paging_geometry(paging, dtype, &w)) return SPLITZIP_ERR_INVALID_ARG;
   return decompress_batch_impl(items, n_items, dtype, w, (uint64_t)paging->n_blocks * paging->block_elems, nullptr, false, d_sizes, stream);
+}
+
+// the plan of a call's first launch, for tests of the rules (exported, not declared in splitzip.h): only the items' n_elems are read
+void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_items, int dtype, uint32_t out[8]) {
+  uint64_t n_max = 0;
+  for (uint32_t q = 0; q < n_items; ++q)
+    if (items[q].n_elems > n_max) n_max = items[q].n_elems;
+  const CompressPlan p = plan_compress(items, n_items, n_max, dtype, kStatusBytes);
+  const uint32_t v[8] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small};
+  memcpy(out, v, sizeof v);
+}
+void splitzip_internal_decompress_plan(const splitzip_ditem* items, uint32_t n_items, int dtype, uint32_t out[3]) {
+  const DecompressPlan p = plan_decompress(items, n_items < kBatchMax ? n_items : kBatchMax, dtype);
+  out[0] = p.cpw; out[1] = p.wgs; out[2] = p.by_xcd;
 }
 
 int splitzip_traffic_probe(const void* d_src, size_t read_bytes, void* d_dst, size_t write_bytes, void* stream) {
