@@ -135,6 +135,8 @@ def lib():
         L.splitzip_internal_compress_plan.argtypes = [C.POINTER(_CItem), C.c_uint32, i, C.POINTER(C.c_uint32)]
         L.splitzip_internal_decompress_plan.restype = None
         L.splitzip_internal_decompress_plan.argtypes = [C.POINTER(_CDItem), C.c_uint32, i, C.POINTER(C.c_uint32)]
+        L.splitzip_internal_xcd_tile.restype = C.c_uint32
+        L.splitzip_internal_xcd_tile.argtypes = [C.c_uint32, C.c_uint32]
         L.splitzip_traffic_probe.restype = i
         L.splitzip_traffic_probe.argtypes = [vp, sz, vp, sz, vp]
         L.splitzip_traffic_probe_shape.restype = i
@@ -374,6 +376,11 @@ def internal_decompress_plan(n_elems, dtype: int) -> dict:
         it.n_elems = n
     lib().splitzip_internal_decompress_plan(items, len(n_elems), dtype, out)
     return dict(zip(("cpw", "workgroups", "by_xcd"), out))
+
+
+def internal_xcd_tile(workgroup: int, n_tiles: int) -> int:
+    """The tile that a workgroup of a tensor of n_tiles tiles takes in a launch that goes by XCDs (for tests)."""
+    return int(lib().splitzip_internal_xcd_tile(workgroup, n_tiles))
 
 
 def noalloc_max_elems() -> int:

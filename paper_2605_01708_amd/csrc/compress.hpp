@@ -462,7 +462,7 @@ struct TileShared {
   uint32_t slot_cap;              // records per tile slot (the same for all tensors of the launch)
   uint32_t finish_groups;         // groups of kGroup tiles per workgroup of the finishing pass, 1 to kFinishMost
   uint32_t use_group_sums;        // the finishing pass reads sums of kSumGroup tile counts (tile_group_sum_kernel) instead of all tile counts
-  uint32_t xcd_row;               // not 0: the dense pass takes its tiles in xcd_order, and this is its workgroups per tensor
+  uint32_t by_xcd;                // the dense pass takes its tiles in xcd_order
   __device__ inline u32x4 dec16_of(const TileItem& it, uint32_t k) const { return d_cbs ? load_dec16(d_cbs[k].dec) : dec16_from(it.dec); }
 };
 template <uint32_t N>
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
   args_arrived(args, item, a, it);
   const TileGeom G = tile_geom(a, it, item, F::DT);
   const Planes& P = G.P;
-  const uint32_t t = a.xcd_row ? xcd_order(blockIdx.x, a.xcd_row) : blockIdx.x;
+  const uint32_t t = a.by_xcd ? xcd_order(blockIdx.x, G.n_tiles) : blockIdx.x;
   if (t >= G.n_tiles) return;
   const uint32_t r0 = t << a.tile_shift, nb = P.n_chunks - r0 < G.tile_chunks ? P.n_chunks - r0 : G.tile_chunks;
   const uint32_t w0 = (uint32_t)wave * a.cpt;                                   // the wave's first chunk inside the tile

@@ -419,7 +419,7 @@ __global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const Decomp
   const DBatchItem it = b.item[blockIdx.y];
   const Layout L = make_layout(it.n, (int)b.dtype);
   const uint32_t n_tiles = (uint32_t)((L.n_chunks + (uint64_t)kWaves * b.cpw - 1) / (kWaves * b.cpw));
-  const uint32_t tile = b.by_xcd ? xcd_order(blockIdx.x, gridDim.x) : blockIdx.x;
+  const uint32_t tile = b.by_xcd ? xcd_order(blockIdx.x, n_tiles) : blockIdx.x;
   if (tile >= (n_tiles ? n_tiles : 1u)) return;
   DecompressArgs a;
   a.comp = it.comp;

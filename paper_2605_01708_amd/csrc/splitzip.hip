@@ -746,7 +746,7 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     a.paging = paging;
     a.finish_groups = p.finish_groups;
     a.use_group_sums = p.group_sums ? 1u : 0u;
-    a.xcd_row = p.by_xcd ? (uint32_t)p.tiles_max : 0u;
+    a.by_xcd = p.by_xcd ? 1u : 0u;
     const unsigned tiles_max = (unsigned)p.tiles_max, sums_max = (tiles_max + kSumGroup - 1) / kSumGroup;
     const unsigned pad = p.by_xcd && dtype == SPLITZIP_BF16 ? Bf16::kTileLdsPad : 0u;
     if (p.small) {
@@ -1052,6 +1052,8 @@ void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_item
   const uint32_t v[8] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small};
   memcpy(out, v, sizeof v);
 }
+// the tile that workgroup b of a tensor of n tiles takes in a launch by XCDs
+uint32_t splitzip_internal_xcd_tile(uint32_t b, uint32_t n) { return xcd_order(b, n); }
 void splitzip_internal_decompress_plan(const splitzip_ditem* items, uint32_t n_items, int dtype, uint32_t out[3]) {
   const DecompressPlan p = plan_decompress(items, n_items < kBatchMax ? n_items : kBatchMax, dtype);
   out[0] = p.cpw; out[1] = p.wgs; out[2] = p.by_xcd;

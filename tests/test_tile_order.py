@@ -8,6 +8,18 @@ import kv_synth
 import paper_2605_01708_amd as sz
 
 
+@pytest.mark.parametrize("n", [0, 1, 25, 64, 127, 128, 129, 200, 255, 256, 1000, 4096, 4099])
+def test_every_tensor_is_spread_over_all_xcds(n):
+    """A row of a launch has as many workgroups as its longest tensor has tiles.  Whatever the row, the first n workgroups
+    take the n tiles, the others none, and the hardware's 8 XCDs (workgroups dealt out in turn) get equal shares."""
+    order = [sz.internal_xcd_tile(b, n) for b in range(max(2 * n, 4200))]
+    assert sorted(order[:n]) == list(range(n)) and all(t >= n for t in order[n:])
+    share = [sum(1 for t in order[x::8] if t < n) for x in range(8)]
+    assert max(share) - min(share) <= 1
+    whole = n // 128 * 128   # runs of 16 tiles to an XCD in the whole windows
+    assert all(order.index(t) % 8 == (t // 16) % 8 for t in range(whole))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
 def test_batches_in_xcd_order_equal_single_calls(dtype):
