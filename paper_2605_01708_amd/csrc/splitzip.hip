@@ -660,16 +660,21 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
     if (!need || total > status_bytes) break;
     p.cpt = need;
   }
+  uint64_t tiles_all = 0;
   for (uint32_t q = 0; q < p.k; ++q) {
     const uint64_t tiles = tiles_of(chunks_of(items[q].n_elems), p.cpt);
+    tiles_all += tiles;
     if (tiles > p.tiles_max) p.tiles_max = tiles;
   }
   p.small = chunks_of(n_max) <= (dtype == SPLITZIP_BF16 ? Bf16::kSmallChunks : E5m2::kSmallChunks) && !g_hooks.any();
-  // Launches of many tiles, from 16 384 (256 MB of words) on, take them in xcd_order, and BF16 with fewer workgroups
-  // per CU (Bf16::kTileLdsPad).  us per call, in the order of the tiles and in xcd_order: BF16 1241 and
-  // 1201 (262 144 tiles), 314 and 307 (65 536), 83.2 and 82.4 (16 384); E5M2 690 and 665 (131 072), 173.4 and 171.7
-  // (32 768), 49.7 and 49.8 (8192).
-  p.by_xcd = p.tiles_max * p.k >= 16384;
+  // Launches of many tiles, from 16 384 on, take them in xcd_order, and BF16 with fewer workgroups per CU
+  // (Bf16::kTileLdsPad).  us per call, in the order of the tiles and in xcd_order: BF16 (16 KB tiles) 1241 and 1201
+  // (262 144 tiles), 161.8 and 157.7 (32 768), 83.0 and 80.8 (16 384), 43.8 and 43.6 (8192); E5M2, tiles of 8 KB 176.2
+  // and 172.4 (65 536), 49.3 and 48.7 (16 384), 29.0 and 28.7 (8192), of 16 KB 690 and 665 (131 072).  What counts are
+  // the tiles that there are: where the tensors differ in length, most of a launch's workgroups may have none, and they
+  // take longer to pass by that way (BF16, one tensor of 13 000 chunks beside 63 of two: 35.1 and 40.6; 16 of 8192
+  // beside 48 of 16: 91.5 and 95.6; but 32 of 16 384 beside 32 of 16: 328 and 321).
+  p.by_xcd = tiles_all >= 16384 && p.tiles_max * p.k <= 2 * tiles_all;
   if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2;
   const uint32_t groups_max = (uint32_t)((p.tiles_max + kGroup - 1) / kGroup);
   // many groups in the launch: several per workgroup, as long as the chip still gets a few workgroups per CU
@@ -905,10 +910,13 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
   p.cpw = pick_decompress_cpw(chunks_all, dtype);
   p.wgs = (uint32_t)((chunks_max + (uint64_t)kWaves * p.cpw - 1) / (kWaves * p.cpw));
   if (p.wgs < 1) p.wgs = 1;
-  // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 86.7 and 86.4
+  // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 88.1 and 87.1
   // (16 384), 46.0 and 45.9 (8192); BF16 1258 and 1237 (262 144), 1172 and 1152 (240 064), but 620 and 624 (131 072)
-  // and 301 and 301 (65 536).
-  p.by_xcd = (uint64_t)p.wgs * k >= (dtype == SPLITZIP_BF16 ? 196608u : 16384u) ? 1u : 0u;
+  // and 301 and 301 (65 536).  As in plan_compress, by the workgroups that have a tile (BF16, one stream of 32 768
+  // chunks beside 63 of two: 97.3 and 111.1).
+  uint64_t wgs_all = 0;
+  for (uint32_t q = 0; q < k; ++q) wgs_all += (chunks_of(items[q].n_elems) + (uint64_t)kWaves * p.cpw - 1) / (kWaves * p.cpw);
+  p.by_xcd = wgs_all >= (dtype == SPLITZIP_BF16 ? 196608u : 16384u) && (uint64_t)p.wgs * k <= 2 * wgs_all ? 1u : 0u;
   if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2 ? 1u : 0u;
   return p;
 }
