@@ -135,7 +135,8 @@ size_t splitzip_total_bytes(uint64_t n_elems, uint64_t n_escapes, int dtype);
 size_t splitzip_compress_bound(uint64_t n_elems, int dtype);
 
 /* Device scratch of a compress call of up to n_elems: a status area of 4 MiB
- * (the escape count of every 16 KB tile of the tensor) and a staging area of
+ * (the escape count of every tile of the tensor, 4 to 16 KB of words or, in
+ * very large tensors, more) and a staging area of
  * n_elems bytes and a little more (the tiles' escape records until their rank
  * in the stream is known).  A compress call is two kernel launches (one for
  * tensors of a few dozen chunks, which a workgroup does by itself): the first
@@ -161,7 +162,7 @@ int splitzip_workspace_init(void* d_workspace, size_t workspace_bytes, void* str
  * enqueued.  If the fixed part fits but the escapes do not, everything that
  * fits is written, status gets SPLITZIP_STATUS_OVERFLOW and total_bytes is
  * the size a retry needs.  n_elems == 0 is valid (header and one offset).
- * Two launches on `stream` (three above 32 Mi elements of BF16; one where no
+ * Two launches on `stream` (three above about 180 Mi elements; one where no
  * tensor of the call has more than 40 chunks of BF16 or 48 of E5M2).
  * The output is a pure function of (input, codebook): independent of
  * scheduling, capacity slack and earlier calls. */

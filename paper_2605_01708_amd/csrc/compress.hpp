@@ -431,8 +431,7 @@ constexpr uint32_t kFinishMost = 4;         // groups per workgroup of the finis
 constexpr uint32_t kSlotAhead = 16;         // threads per tile that fetch records before the finishing pass knows the counts, two records each
 constexpr uint32_t kTileStageCap = 256;     // escapes a wave can stage in LDS
 constexpr uint32_t kSlotCapMost = 1024;     // records per tile slot, at most
-constexpr uint32_t kDirectTiles = 4096;     // up to this many tiles per tensor the finishing pass sums the tile counts itself ...
-constexpr uint64_t kDirectBytes = 128ull << 20;   // ... if all its workgroups together read no more than this many bytes of counts
+constexpr uint64_t kDirectBytes = 128ull << 20;   // the finishing pass sums the tile counts itself if all its workgroups together read no more than this many bytes of them
 constexpr uint32_t kSumGroup = 64;          // beyond: sums of this many tile counts, by tile_group_sum_kernel
 constexpr uint32_t kBatchMax = 64;          // tensors per launch: their descriptors travel as kernel arguments
 constexpr uint32_t kRedo = 0x80000000u;     // in a tile's count: its records are not in its slot
@@ -630,7 +629,7 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
   if (t == G.n_tiles - 1 && tid > 0 && tid < 4 && (t & 3u) + tid < 4) G.counts[t + tid] = 0;
 }
 
-// sums of kSumGroup tile counts each, for tensors of more than kDirectTiles tiles (one wave per sum)
+// sums of kSumGroup tile counts each, for launches beyond kDirectBytes (one wave per sum)
 template <typename F, uint32_t N>
 __global__ __launch_bounds__(64) void tile_group_sum_kernel(const TileArgs<N> args) {
   TileShared a;

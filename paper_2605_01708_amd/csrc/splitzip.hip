@@ -683,11 +683,13 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   if (const uint32_t forced = g_hooks.finish_groups.load()) p.finish_groups = forced;
   p.finish_wgs = (groups_max + p.finish_groups - 1) / p.finish_groups;
   // A finishing workgroup that sums all tile counts of its tensor itself reads 4 bytes per tile: fine while all
-  // workgroups of the launch together read no more than kDirectBytes that way, mostly from the L2 (one launch
-  // fewer; 64 tensors of 64 MiB: 67 MB of counts read, 1259 us per call against 1262-1292 us with the sums);
-  // beyond that they read sums of kSumGroup counts instead (tile_group_sum_kernel).
+  // workgroups of the launch together read no more than kDirectBytes that way, mostly from the L2, and one launch fewer;
+  // beyond that they read sums of kSumGroup counts instead (tile_group_sum_kernel).  us per call, with the sums and
+  // without, and the MB of counts read without: one BF16 tensor 18.4 and 16.9 (16 385 chunks, 4), 27.6 and 26.1 (32 769,
+  // 4), 65.6 and 65.1 (100 000, 39); one E5M2 tensor 20.1 and 18.6 (32 769, 4), 30.2 and 29.1 (65 537, 17), 49.2 and
+  // 48.9 (131 072, 67); 64 BF16 tensors of 64 MiB 1262-1292 and 1259 (67).
   const uint64_t direct_budget = g_hooks.direct_bytes.load() ? g_hooks.direct_bytes.load() : kDirectBytes;
-  p.group_sums = p.tiles_max > kDirectTiles || (uint64_t)p.finish_wgs * p.k * p.tiles_max * 4 > direct_budget;
+  p.group_sums = (uint64_t)p.finish_wgs * p.k * p.tiles_max * 4 > direct_budget;
   return p;
 }
 

@@ -24,3 +24,15 @@ def test_tiles_that_are_not_there_do_not_make_a_launch_long(dtype):
         assert not decompress_plan(dtype, chunks)["by_xcd"], chunks
     for chunks in ([32768] * 64, [32768] * 63 + [5]):
         assert compress_plan(dtype, chunks)["by_xcd"] and decompress_plan(dtype, chunks)["by_xcd"]
+
+
+@pytest.mark.parametrize("dtype", FORMATS)
+def test_a_third_launch_only_where_the_counts_are_many(dtype):
+    """The finishing pass sums the tile counts itself, with no launch in between, until its workgroups would together read
+    128 MB of them: 23 169 tiles, 8 chunks each, whatever smaller tiles a shorter tensor has."""
+    assert compress_plan(dtype, [40 if dtype == sz.BF16 else 48])["launches"] == 1
+    for chunks in (49, 6144, 6145, 16384, 16385, 18000, 20480, 20481, 32768, 32769, 40000, 49152, 65536, 65537, 131072, 185344):
+        assert compress_plan(dtype, [chunks])["launches"] == 2, chunks
+    for chunks in (185345, 200000, 400000):
+        assert compress_plan(dtype, [chunks])["launches"] == 3, chunks
+    assert compress_plan(dtype, [32768] * 64)["launches"] == 2
