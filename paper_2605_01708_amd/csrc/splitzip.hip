@@ -601,9 +601,17 @@ uint32_t pick_cpt(uint64_t chunks, uint32_t at_least, uint64_t status_bytes) {
 //         (16 384), 18.2 / 18.6 (19 200), 27.7 / 25.2 (32 768)
 //   E5M2  one / two / four: 6.4 / 6.9 / 8.0 (100), 8.0 / 8.2 / 9.6 (4096), 9.3 / 9.1 / 10.9 (8192), 12.9 / 12.0 / 14.3
 //         (16 384), two / four: 17.6 / 18.8 (32 768), 167.6 / 170.1 (524 288), 338.3 / 336.3 (1 Mi), 666 / 661 (2 Mi)
-uint32_t pick_base_cpt(uint64_t chunks, int dtype) {
-  if (dtype == SPLITZIP_BF16) return chunks <= 20480 ? 1u : 2u;
-  return chunks <= 6144 ? 1u : chunks <= 786432 ? 2u : 4u;
+// Tensors that differ in length: the launch has a row of workgroups per tensor, as long as the longest (chunks_padded in
+// all), and passes by a workgroup without a tile at about four in a nanosecond.  From 48 of them per CU on the next size
+// is better: us by chunks per wave, BF16 one / two: 8.6 / 8.9 (600 chunks beside 63 tensors of 5: 9371 without a tile),
+// 12.7 / 10.9 (1500 beside 63 of 50: 22 837), 26.1 / 21.4 (20 000 beside seven of two), 59.1 / 35.2 (13 000 beside 63 of
+// two); E5M2 two / four: 10.8 / 11.4 (1500 beside 63 of 50: 11 418), 57.9 / 56.7 (32 of 4096 beside 32 of 512: 14 336),
+// 17.4 / 16.7 (20 000 beside seven of two: 17 498), 33.7 / 21.3 (13 000 beside 63 of two).
+uint32_t pick_base_cpt(uint64_t chunks, uint64_t chunks_padded, int dtype) {
+  const uint32_t most = dtype == SPLITZIP_BF16 ? Bf16::kCpt : E5m2::kCpt;
+  uint32_t cpt = dtype == SPLITZIP_BF16 ? (chunks <= 20480 ? 1u : 2u) : chunks <= 6144 ? 1u : chunks <= 786432 ? 2u : 4u;
+  while (cpt < most && (chunks_padded - chunks) / (4 * cpt) > (uint64_t)cu_count() * 48) cpt *= 2;
+  return cpt;
 }
 
 // the launches of k tensors: dense pass (one workgroup per tile, started by the hardware in the tiles' order), sums if
@@ -649,11 +657,16 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   memset(&p, 0, sizeof p);
   // as many of the next tensors (kBatchMax at most) as find room for their counts in the status area; all of them share
   // the tile size of the one that needs the largest
-  uint64_t chunks_all = 0;
-  for (uint32_t q = 0; q < n_items && q < kBatchMax; ++q) chunks_all += chunks_of(items[q].n_elems);
+  const uint32_t k_most = n_items < kBatchMax ? n_items : kBatchMax;
+  uint64_t chunks_all = 0, chunks_max = 0;
+  for (uint32_t q = 0; q < k_most; ++q) {
+    const uint64_t c = chunks_of(items[q].n_elems);
+    chunks_all += c;
+    if (c > chunks_max) chunks_max = c;
+  }
   const uint32_t forced_cpt = g_hooks.cpt.load();
-  p.cpt = forced_cpt ? forced_cpt : pick_base_cpt(chunks_all, dtype);
-  for (; p.k < n_items && p.k < kBatchMax; ++p.k) {
+  p.cpt = forced_cpt ? forced_cpt : pick_base_cpt(chunks_all, chunks_max * k_most, dtype);
+  for (; p.k < k_most; ++p.k) {
     const uint32_t need = pick_cpt(chunks_of(items[p.k].n_elems), p.cpt, status_bytes);
     uint64_t total = 0;
     for (uint32_t q = 0; q <= p.k && need; ++q) total += status_need(tiles_of(chunks_of(items[q].n_elems), need));

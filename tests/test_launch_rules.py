@@ -36,3 +36,14 @@ def test_a_third_launch_only_where_the_counts_are_many(dtype):
     for chunks in (185345, 200000, 400000):
         assert compress_plan(dtype, [chunks])["launches"] == 3, chunks
     assert compress_plan(dtype, [32768] * 64)["launches"] == 2
+
+
+@pytest.mark.parametrize("dtype,most", [(sz.BF16, 2), (sz.FP8_E5M2, 4)])
+def test_tiles_where_the_tensors_differ_in_length(dtype, most):
+    """Workgroups without a tile cost a launch, too: batches with many of them take the largest tiles, whatever the tiles
+    that a launch of their chunks would take; a few do not matter."""
+    for chunks in ([13000] + [2] * 63, [32768] + [2] * 63, [8192] + [100] * 63, [8192] * 4 + [200] * 60, [3000] + [2] * 63,
+                   [20000] + [2] * 7, [4096] * 32 + [512] * 32, [2] * 63 + [13000] + [5] * 100):
+        assert compress_plan(dtype, chunks)["cpt"] == most, chunks
+    for chunks in ([600] + [5] * 63, [100] * 40 + [60] * 24, [2048], [49]):
+        assert compress_plan(dtype, chunks)["cpt"] == 1, chunks
