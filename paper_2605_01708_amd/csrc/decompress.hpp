@@ -405,10 +405,10 @@ struct DecompressBatchArgs {
   DBatchItem item[kBatchMax];
   splitzip_sizes* sizes;   // nullable; one record, status bits sticky
   uint32_t cpw, dtype, reg_patch_max;
-  Words paging;            // as in CompressBatchArgs
+  uint32_t by_xcd;         // the workgroups take their tiles in xcd_order
+  Words paging;            // as in the compress calls' TileShared
   uint8_t dec[kBatchMax][16];   // every stream's codebook
   const splitzip_codebook* d_cbs;   // nullable: n_items codebooks in device memory, used instead of dec
-  uint32_t by_xcd;         // the workgroups take their tiles in xcd_order
   uint32_t own_dec;        // 1: every stream is decoded with the 16 decode entries of its own header
 };
 
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const Decomp
   __shared__ __attribute__((aligned(16))) uint32_t lds_chunk[kWaves * F::kTileDwords];
   const DBatchItem it = b.item[blockIdx.y];
   const Layout L = make_layout(it.n, (int)b.dtype);
-  const uint32_t n_tiles = (uint32_t)((L.n_chunks + (uint64_t)kWaves * b.cpw - 1) / (kWaves * b.cpw));
+  const uint32_t n_tiles = ((uint32_t)L.n_chunks + kWaves * b.cpw - 1) / (kWaves * b.cpw);   // 32 bits: a launch may have many workgroups without a tile
   const uint32_t tile = b.by_xcd ? xcd_order(blockIdx.x, n_tiles) : blockIdx.x;
   if (tile >= (n_tiles ? n_tiles : 1u)) return;
   DecompressArgs a;

@@ -82,9 +82,9 @@ TestHooks g_hooks;
 //         19.8 / 15.9 / 14.2 (32 768); four / five / eight: 45.9 / 46.9 / 47.6 (131 072), 657 / 678 / 671 (2 Mi).  The
 //         longest launches take eight all the same: in the first 20 ms of load after a pause four took 705 to 765 us
 //         there, eight 668 to 688.
-uint32_t pick_decompress_cpw(uint64_t n_chunks, int dtype) {
+uint32_t pick_decompress_cpw(uint64_t n_chunks, int dtype, uint64_t cus) {
   if (const uint32_t forced = g_hooks.cpw.load()) return forced;
-  const uint64_t round = (uint64_t)cu_count() * 8;   // workgroups resident at a time
+  const uint64_t round = cus * 8;   // workgroups resident at a time
   if (dtype == SPLITZIP_BF16) return (n_chunks >= 2 * round && n_chunks <= 8 * round) || n_chunks >= 56 * round ? 2u : 1u;
   return n_chunks >= 512 * round ? 8u : n_chunks >= 8 * round ? 4u : n_chunks >= 4 * round ? 2u : 1u;
 }
@@ -607,10 +607,10 @@ uint32_t pick_cpt(uint64_t chunks, uint32_t at_least, uint64_t status_bytes) {
 // 12.7 / 10.9 (1500 beside 63 of 50: 22 837), 26.1 / 21.4 (20 000 beside seven of two), 59.1 / 35.2 (13 000 beside 63 of
 // two); E5M2 two / four: 10.8 / 11.4 (1500 beside 63 of 50: 11 418), 57.9 / 56.7 (32 of 4096 beside 32 of 512: 14 336),
 // 17.4 / 16.7 (20 000 beside seven of two: 17 498), 33.7 / 21.3 (13 000 beside 63 of two).
-uint32_t pick_base_cpt(uint64_t chunks, uint64_t chunks_padded, int dtype) {
+uint32_t pick_base_cpt(uint64_t chunks, uint64_t chunks_padded, int dtype, uint64_t cus) {
   const uint32_t most = dtype == SPLITZIP_BF16 ? Bf16::kCpt : E5m2::kCpt;
   uint32_t cpt = dtype == SPLITZIP_BF16 ? (chunks <= 20480 ? 1u : 2u) : chunks <= 6144 ? 1u : chunks <= 786432 ? 2u : 4u;
-  while (cpt < most && (chunks_padded - chunks) / (4 * cpt) > (uint64_t)cu_count() * 48) cpt *= 2;
+  while (cpt < most && (chunks_padded - chunks) / (4 * cpt) > cus * 48) cpt *= 2;
   return cpt;
 }
 
@@ -657,6 +657,7 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   memset(&p, 0, sizeof p);
   // as many of the next tensors (kBatchMax at most) as find room for their counts in the status area; all of them share
   // the tile size of the one that needs the largest
+  const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
   const uint32_t k_most = n_items < kBatchMax ? n_items : kBatchMax;
   uint64_t chunks_all = 0, chunks_max = 0;
   for (uint32_t q = 0; q < k_most; ++q) {
@@ -665,7 +666,7 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
     if (c > chunks_max) chunks_max = c;
   }
   const uint32_t forced_cpt = g_hooks.cpt.load();
-  p.cpt = forced_cpt ? forced_cpt : pick_base_cpt(chunks_all, chunks_max * k_most, dtype);
+  p.cpt = forced_cpt ? forced_cpt : pick_base_cpt(chunks_all, chunks_max * k_most, dtype, cus);
   for (; p.k < k_most; ++p.k) {
     const uint32_t need = pick_cpt(chunks_of(items[p.k].n_elems), p.cpt, status_bytes);
     uint64_t total = 0;
@@ -692,7 +693,7 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   const uint32_t groups_max = (uint32_t)((p.tiles_max + kGroup - 1) / kGroup);
   // many groups in the launch: several per workgroup, as long as the chip still gets a few workgroups per CU
   p.finish_groups = 1;
-  while (p.finish_groups < kFinishMost && (uint64_t)groups_max * p.k / (2 * p.finish_groups) >= (uint64_t)cu_count() * 8) p.finish_groups *= 2;
+  while (p.finish_groups < kFinishMost && (uint64_t)groups_max * p.k / (2 * p.finish_groups) >= cus * 8) p.finish_groups *= 2;
   if (const uint32_t forced = g_hooks.finish_groups.load()) p.finish_groups = forced;
   p.finish_wgs = (groups_max + p.finish_groups - 1) / p.finish_groups;
   // A finishing workgroup that sums all tile counts of its tensor itself reads 4 bytes per tile: fine while all
@@ -821,7 +822,7 @@ int decompress_impl(const void* d_comp, size_t comp_bytes, uint64_t n_elems, int
   a.sizes = d_sizes;
   a.off_tab = L.off_tab; a.off_sm = L.off_sm; a.off_code = L.off_code; a.off_pos = L.off_pos;
   a.sm_bytes = L.sm_bytes; a.code_bytes = L.code_bytes;
-  a.cpw = pick_decompress_cpw(L.n_chunks, dtype);
+  a.cpw = pick_decompress_cpw(L.n_chunks, dtype, (uint64_t)cu_count());
   a.reg_patch_max = kRegPatchDefault;
   a.n_chunks = (uint32_t)L.n_chunks;
   a.n_tiles = (uint32_t)((L.n_chunks + (uint64_t)kWaves * a.cpw - 1) / (kWaves * a.cpw));
@@ -922,7 +923,18 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
     if (c > chunks_max) chunks_max = c;
   }
   DecompressPlan p;
-  p.cpw = pick_decompress_cpw(chunks_all, dtype);
+  const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
+  p.cpw = pick_decompress_cpw(chunks_all, dtype, cus);
+  // Streams that differ in length, as in pick_base_cpt: more chunks per wave where many of the launch's workgroups have
+  // none.  us by chunks per wave, BF16 one / two: 7.1 / 6.0 (600 chunks beside 63 streams of 5: 9371 without a tile), 18.8
+  // / 12.1 (3000 beside 63 of two), 24.3 / 19.0 (20 000 beside seven of two); E5M2 two / four: 6.2 / 7.1 (600 beside 63 of
+  // 5: 4686), 10.1 / 9.5 (1500 beside 63 of 50: 11 418), 42.5 / 24.8 (13 000 beside 63 of two), four / eight: 26.1 / 29.1
+  // (8192 beside 63 of 100: 31 862), 24.8 / 16.0 (13 000 beside 63 of two: 51 184); where the streams fill the chip anyway
+  // 37.9 / 34.7 (two of 9000 beside 62 of 1000: 31 000).
+  const uint32_t most = dtype == SPLITZIP_BF16 ? 2u : 8u;
+  const uint64_t none = chunks_max * k - chunks_all;   // chunks that the padded grid has room for and the streams do not have
+  if (!g_hooks.cpw.load())
+    while (p.cpw < most && none / (kWaves * p.cpw) > cus * (p.cpw < 4 ? 32u : chunks_all < 256 * cus ? 160u : 96u)) p.cpw *= 2;
   p.wgs = (uint32_t)((chunks_max + (uint64_t)kWaves * p.cpw - 1) / (kWaves * p.cpw));
   if (p.wgs < 1) p.wgs = 1;
   // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 88.1 and 87.1
@@ -930,7 +942,8 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
   // and 301 and 301 (65 536).  As in plan_compress, by the workgroups that have a tile (BF16, one stream of 32 768
   // chunks beside 63 of two: 97.3 and 111.1).
   uint64_t wgs_all = 0;
-  for (uint32_t q = 0; q < k; ++q) wgs_all += (chunks_of(items[q].n_elems) + (uint64_t)kWaves * p.cpw - 1) / (kWaves * p.cpw);
+  const uint32_t shift = (uint32_t)__builtin_ctz(kWaves * p.cpw);
+  for (uint32_t q = 0; q < k; ++q) wgs_all += (chunks_of(items[q].n_elems) + kWaves * p.cpw - 1) >> shift;
   p.by_xcd = wgs_all >= (dtype == SPLITZIP_BF16 ? 196608u : 16384u) && (uint64_t)p.wgs * k <= 2 * wgs_all ? 1u : 0u;
   if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2 ? 1u : 0u;
   return p;

@@ -47,3 +47,9 @@ def test_tiles_where_the_tensors_differ_in_length(dtype, most):
         assert compress_plan(dtype, chunks)["cpt"] == most, chunks
     for chunks in ([600] + [5] * 63, [100] * 40 + [60] * 24, [2048], [49]):
         assert compress_plan(dtype, chunks)["cpt"] == 1, chunks
+    # and so do batches to decode
+    large = {sz.BF16: 2, sz.FP8_E5M2: 4}[dtype]
+    for chunks in ([13000] + [2] * 63, [32768] + [2] * 63, [8192] + [100] * 63, [8192] * 4 + [200] * 60, [3000] + [2] * 63, [20000] + [2] * 7):
+        assert decompress_plan(dtype, chunks)["cpw"] >= large, chunks
+    for chunks in ([40] * 40 + [20] * 24, [2048], [49]):
+        assert decompress_plan(dtype, chunks)["cpw"] == 1, chunks
