@@ -439,7 +439,8 @@ constexpr uint32_t kMore = 1u;              // in a group's mark of the finishin
 static_assert(kGroup * kSlotAhead == kTileThreads, "every thread fetches records of one tile ahead");
 
 // The arguments of a launch: what all its tensors share, then the tensors (N: room for kBatchMax of them, or for the
-// one of a single call, whose two launches then carry 144 bytes instead of 3.2 KB each).  A workgroup needs the first part and one
+// one of a single call, whose two launches then carry 144 bytes instead of 3.2 KB each; those start on a cache line on the
+// host, too: wherever else the stack put them, the runtime's copy of them took 2 us longer or not from build to build).  A workgroup needs the first part and one
 // tensor's, 144 bytes; both are fetched whole before anything is done with them (args_arrived).
 struct TileItem {
   const uint8_t* in;
@@ -465,7 +466,7 @@ struct TileShared {
   __device__ inline u32x4 dec16_of(const TileItem& it, uint32_t k) const { return d_cbs ? load_dec16(d_cbs[k].dec) : dec16_from(it.dec); }
 };
 template <uint32_t N>
-struct TileArgs {
+struct alignas(N == 1 ? 16 : 64) TileArgs {
   TileShared shared;
   TileItem item[N];
 };

@@ -582,7 +582,7 @@ int workspace_view(void* d_workspace, size_t workspace_bytes, uint64_t n_max, in
 }
 
 uint64_t chunks_of(uint64_t n) { return (n + kChunk - 1) / kChunk; }
-uint64_t tiles_of(uint64_t chunks, uint32_t cpt) { return (chunks + 4ull * cpt - 1) / (4ull * cpt); }
+uint64_t tiles_of(uint64_t chunks, uint32_t cpt) { return (chunks + 4ull * cpt - 1) >> (2 + __builtin_ctz(cpt)); }   // cpt: a power of two
 // bytes of the status area a tensor of `tiles` tiles takes: a count per tile, a sum per group of tiles
 uint64_t status_need(uint64_t tiles) { return a256(4 * tiles + 4 * ((tiles + kSumGroup - 1) / kSumGroup)); }
 
@@ -667,11 +667,14 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   }
   const uint32_t forced_cpt = g_hooks.cpt.load();
   p.cpt = forced_cpt ? forced_cpt : pick_base_cpt(chunks_all, chunks_max * k_most, dtype, cus);
+  uint64_t taken = 0;   // of the status area, by the tensors so far
   for (; p.k < k_most; ++p.k) {
     const uint32_t need = pick_cpt(chunks_of(items[p.k].n_elems), p.cpt, status_bytes);
-    uint64_t total = 0;
-    for (uint32_t q = 0; q <= p.k && need; ++q) total += status_need(tiles_of(chunks_of(items[q].n_elems), need));
-    if (!need || total > status_bytes) break;
+    if (!need) break;
+    uint64_t total = need == p.cpt ? taken : 0;
+    for (uint32_t q = need == p.cpt ? p.k : 0; q <= p.k; ++q) total += status_need(tiles_of(chunks_of(items[q].n_elems), need));
+    if (total > status_bytes) break;
+    taken = total;
     p.cpt = need;
   }
   uint64_t tiles_all = 0;
