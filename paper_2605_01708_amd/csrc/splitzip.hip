@@ -78,14 +78,16 @@ TestHooks g_hooks;
 //   BF16  4.1 / 4.8 (2048 chunks), 5.7 / 5.5 (4096), 8.1 / 7.5 (8192), 13.3 / 12.8 (16 384), 15.5 / 16.2 (20 000),
 //         22.5 / 23.0 (32 768), 59.5 / 60.0 (98 304), 81.9 / 79.5 (131 072), 1325 / 1229 (2 Mi); three: worse everywhere.
 //         Two up to what is resident at once (eight workgroups of eight chunks per CU) and again for long launches.
+//         Several streams in a launch: 16.3 / 16.3 (64 of 300), 24.7 / 24.0 (64 of 512), 43.6 / 42.7 (8 of 8192), 44.2 / 42.9
+//         (64 of 1024), 65.0 / 62.3 (64 of 1536): two again from 32 768 on.
 //   E5M2  with one / two / four: 4.2 / 4.8 / 6.1 (2048), 6.8 / 6.8 / 7.3 (8192), 11.5 / 9.7 / 9.5 (16 384),
 //         19.8 / 15.9 / 14.2 (32 768); four / five / eight: 45.9 / 46.9 / 47.6 (131 072), 657 / 678 / 671 (2 Mi).  The
 //         longest launches take eight all the same: in the first 20 ms of load after a pause four took 705 to 765 us
 //         there, eight 668 to 688.
-uint32_t pick_decompress_cpw(uint64_t n_chunks, int dtype, uint64_t cus) {
+uint32_t pick_decompress_cpw(uint64_t n_chunks, bool several, int dtype, uint64_t cus) {
   if (const uint32_t forced = g_hooks.cpw.load()) return forced;
   const uint64_t round = cus * 8;   // workgroups resident at a time
-  if (dtype == SPLITZIP_BF16) return (n_chunks >= 2 * round && n_chunks <= 8 * round) || n_chunks >= 56 * round ? 2u : 1u;
+  if (dtype == SPLITZIP_BF16) return (n_chunks >= 2 * round && n_chunks <= 8 * round) || n_chunks >= (several ? 16 : 56) * round ? 2u : 1u;
   return n_chunks >= 512 * round ? 8u : n_chunks >= 8 * round ? 4u : n_chunks >= 4 * round ? 2u : 1u;
 }
 
@@ -825,7 +827,7 @@ int decompress_impl(const void* d_comp, size_t comp_bytes, uint64_t n_elems, int
   a.sizes = d_sizes;
   a.off_tab = L.off_tab; a.off_sm = L.off_sm; a.off_code = L.off_code; a.off_pos = L.off_pos;
   a.sm_bytes = L.sm_bytes; a.code_bytes = L.code_bytes;
-  a.cpw = pick_decompress_cpw(L.n_chunks, dtype, (uint64_t)cu_count());
+  a.cpw = pick_decompress_cpw(L.n_chunks, false, dtype, (uint64_t)cu_count());
   a.reg_patch_max = kRegPatchDefault;
   a.n_chunks = (uint32_t)L.n_chunks;
   a.n_tiles = (uint32_t)((L.n_chunks + (uint64_t)kWaves * a.cpw - 1) / (kWaves * a.cpw));
@@ -927,7 +929,7 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
   }
   DecompressPlan p;
   const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
-  p.cpw = pick_decompress_cpw(chunks_all, dtype, cus);
+  p.cpw = pick_decompress_cpw(chunks_all, k > 1, dtype, cus);
   // Streams that differ in length, as in pick_base_cpt: more chunks per wave where many of the launch's workgroups have
   // none.  us by chunks per wave, BF16 one / two: 7.1 / 6.0 (600 chunks beside 63 streams of 5: 9371 without a tile), 18.8
   // / 12.1 (3000 beside 63 of two), 24.3 / 19.0 (20 000 beside seven of two); E5M2 two / four: 6.2 / 7.1 (600 beside 63 of

@@ -53,3 +53,11 @@ def test_tiles_where_the_tensors_differ_in_length(dtype, most):
         assert decompress_plan(dtype, chunks)["cpw"] >= large, chunks
     for chunks in ([40] * 40 + [20] * 24, [2048], [49]):
         assert decompress_plan(dtype, chunks)["cpw"] == 1, chunks
+
+
+def test_chunks_per_wave_of_several_streams():
+    """A long BF16 stream takes two chunks per wave from 114 688 on, several in a launch from 32 768 on."""
+    for chunks in ([512] * 64, [1024] * 64, [8192] * 8, [32768] * 2, [1700] * 64):
+        assert decompress_plan(sz.BF16, chunks)["cpw"] == 2, chunks
+    for chunks in ([32768], [65536], [100000], [300] * 64, [3000], [40] * 64):
+        assert decompress_plan(sz.BF16, chunks)["cpw"] == 1, chunks
