@@ -75,7 +75,7 @@ TestHooks g_hooks;
 
 // Chunks per wave of a decompress launch over n_chunks chunks in all; us per call with one / two chunks per wave, or
 // as said, one call after the other on one stream:
-//   BF16  4.1 / 4.8 (2048 chunks), 5.7 / 5.5 (4096), 8.1 / 7.5 (8192), 13.3 / 12.8 (16 384), 15.5 / 16.2 (20 000),
+//   BF16  4.1 / 4.8 (2048 chunks), 5.1 / 5.6 (4096), 6.3 / 6.1 (5000), 7.1 / 6.4 (6144), 8.1 / 7.5 (8192), 13.3 / 12.8 (16 384), 15.5 / 16.2 (20 000),
 //         22.5 / 23.0 (32 768), 59.5 / 60.0 (98 304), 81.9 / 79.5 (131 072), 1325 / 1229 (2 Mi); three: worse everywhere.
 //         Two up to what is resident at once (eight workgroups of eight chunks per CU) and again for long launches.
 //         Several streams in a launch: 16.3 / 16.3 (64 of 300), 24.7 / 24.0 (64 of 512), 43.6 / 42.7 (8 of 8192), 44.2 / 42.9
@@ -87,7 +87,7 @@ TestHooks g_hooks;
 uint32_t pick_decompress_cpw(uint64_t n_chunks, bool several, int dtype, uint64_t cus) {
   if (const uint32_t forced = g_hooks.cpw.load()) return forced;
   const uint64_t round = cus * 8;   // workgroups resident at a time
-  if (dtype == SPLITZIP_BF16) return (n_chunks >= 2 * round && n_chunks <= 8 * round) || n_chunks >= (several ? 16 : 56) * round ? 2u : 1u;
+  if (dtype == SPLITZIP_BF16) return (n_chunks >= 5 * round / 2 && n_chunks <= 8 * round) || n_chunks >= (several ? 16 : 56) * round ? 2u : 1u;
   return n_chunks >= 512 * round ? 8u : n_chunks >= 8 * round ? 4u : n_chunks >= 4 * round ? 2u : 1u;
 }
 

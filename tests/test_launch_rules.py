@@ -61,3 +61,5 @@ def test_chunks_per_wave_of_several_streams():
         assert decompress_plan(sz.BF16, chunks)["cpw"] == 2, chunks
     for chunks in ([32768], [65536], [100000], [300] * 64, [3000], [40] * 64):
         assert decompress_plan(sz.BF16, chunks)["cpw"] == 1, chunks
+    # and a stream that just fills the chip from 5120 on
+    assert [decompress_plan(sz.BF16, [c])["cpw"] for c in (4096, 5119, 5120, 16384, 16385)] == [1, 1, 2, 2, 1]
