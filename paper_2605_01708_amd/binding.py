@@ -369,11 +369,11 @@ def internal_compress_plan(n_elems, dtype: int) -> dict:
     return dict(zip(("tensors", "cpt", "tiles_max", "launches", "by_xcd", "finish_groups", "group_sums", "small"), out))
 
 
-def internal_decompress_plan(n_elems, dtype: int) -> dict:
-    """The same for a batch decompress call."""
+def internal_decompress_plan(n_elems, dtype: int, comp_bytes=None) -> dict:
+    """The same for a batch decompress call (comp_bytes: of the streams; by default those of streams without escapes)."""
     items, out = (_CDItem * len(n_elems))(), (C.c_uint32 * 3)()
-    for it, n in zip(items, n_elems):
-        it.n_elems = n
+    for k, (it, n) in enumerate(zip(items, n_elems)):
+        it.n_elems, it.comp_bytes = n, fixed_bytes(n, dtype) if comp_bytes is None else comp_bytes[k]
     lib().splitzip_internal_decompress_plan(items, len(n_elems), dtype, out)
     return dict(zip(("cpw", "workgroups", "by_xcd"), out))
 

@@ -73,6 +73,10 @@ struct TestHooks {
 };
 TestHooks g_hooks;
 
+// Whether more than one element in 16 may have escaped, by the bytes that the caller says it holds beyond the fixed part
+// of its streams (three per record): the device alone knows the number.
+bool many_escapes(uint64_t bytes_beyond, uint64_t n_elems) { return bytes_beyond * 16 > n_elems * 3; }
+
 // Chunks per wave of a decompress launch over n_chunks chunks in all; us per call with one / two chunks per wave, or
 // as said, one call after the other on one stream:
 //   BF16  4.1 / 4.8 (2048 chunks), 5.1 / 5.6 (4096), 6.3 / 6.1 (5000), 7.1 / 6.4 (6144), 8.1 / 7.5 (8192), 13.3 / 12.8 (16 384), 15.5 / 16.2 (20 000),
@@ -84,11 +88,19 @@ TestHooks g_hooks;
 //         19.8 / 15.9 / 14.2 (32 768); four / five / eight: 45.9 / 46.9 / 47.6 (131 072), 657 / 678 / 671 (2 Mi).  The
 //         longest launches take eight all the same: in the first 20 ms of load after a pause four took 705 to 765 us
 //         there, eight 668 to 688.
-uint32_t pick_decompress_cpw(uint64_t n_chunks, bool several, int dtype, uint64_t cus) {
+// Streams with many escapes keep a wave busy with its chunks' records, one chunk after the other, so the larger pieces
+// pay from somewhat longer streams on.  Random words in 15 / 40 % of the places (14 / 37 % escapes for BF16, 8 / 20 % for
+// E5M2), device us:
+//   BF16  one 8.1 / 10.5, two 9.2 / 13.7 (8192); one 11.7 / 16.1, two 10.0 / 14.5 (10 240); one 15.1 / 24.4, two 13.1 / 25.9
+//         (16 384); with 7 % escapes one 7.3, two 7.9 (8192), at 6 % the same.
+//   E5M2  one 7.2 / 8.1, two 7.5 / 9.2 (8192); one 10.3 / 12.6, two 9.1 / 10.2 (12 288); two 10.2 / 11.6, four 12.4 / 16.3
+//         (16 384); two 15.5 / 21.0, four 15.1 / 20.4 (24 576).
+//   Beyond, it depends on their number which is better, by 5 % either way.
+uint32_t pick_decompress_cpw(uint64_t n_chunks, bool several, bool escapes, int dtype, uint64_t cus) {
   if (const uint32_t forced = g_hooks.cpw.load()) return forced;
   const uint64_t round = cus * 8;   // workgroups resident at a time
-  if (dtype == SPLITZIP_BF16) return (n_chunks >= 5 * round / 2 && n_chunks <= 8 * round) || n_chunks >= (several ? 16 : 56) * round ? 2u : 1u;
-  return n_chunks >= 512 * round ? 8u : n_chunks >= 8 * round ? 4u : n_chunks >= 4 * round ? 2u : 1u;
+  if (dtype == SPLITZIP_BF16) return (n_chunks >= (escapes ? 9 : 5) * round / 2 && n_chunks <= 8 * round) || n_chunks >= (several ? 16 : 56) * round ? 2u : 1u;
+  return n_chunks >= 512 * round ? 8u : n_chunks >= (escapes ? 10 : 8) * round ? 4u : n_chunks >= (escapes ? 5 : 4) * round ? 2u : 1u;
 }
 
 // tables must describe one bijection between 16 codes and 16 distinct exponents
@@ -827,7 +839,7 @@ int decompress_impl(const void* d_comp, size_t comp_bytes, uint64_t n_elems, int
   a.sizes = d_sizes;
   a.off_tab = L.off_tab; a.off_sm = L.off_sm; a.off_code = L.off_code; a.off_pos = L.off_pos;
   a.sm_bytes = L.sm_bytes; a.code_bytes = L.code_bytes;
-  a.cpw = pick_decompress_cpw(L.n_chunks, false, dtype, (uint64_t)cu_count());
+  a.cpw = pick_decompress_cpw(L.n_chunks, false, many_escapes(comp_bytes - splitzip_fixed_bytes(n_elems, dtype), n_elems), dtype, (uint64_t)cu_count());
   a.reg_patch_max = kRegPatchDefault;
   a.n_chunks = (uint32_t)L.n_chunks;
   a.n_tiles = (uint32_t)((L.n_chunks + (uint64_t)kWaves * a.cpw - 1) / (kWaves * a.cpw));
@@ -921,15 +933,17 @@ struct DecompressPlan {
   uint32_t by_xcd;     // they take their tiles in xcd_order
 };
 DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtype) {
-  uint64_t chunks_all = 0, chunks_max = 0;
+  uint64_t chunks_all = 0, chunks_max = 0, n_all = 0, beyond = 0;
   for (uint32_t q = 0; q < k; ++q) {
-    const uint64_t c = chunks_of(items[q].n_elems);
+    const uint64_t c = chunks_of(items[q].n_elems), fixed = splitzip_fixed_bytes(items[q].n_elems, dtype);
     chunks_all += c;
     if (c > chunks_max) chunks_max = c;
+    n_all += items[q].n_elems;
+    if (items[q].comp_bytes > fixed) beyond += items[q].comp_bytes - fixed;
   }
   DecompressPlan p;
   const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
-  p.cpw = pick_decompress_cpw(chunks_all, k > 1, dtype, cus);
+  p.cpw = pick_decompress_cpw(chunks_all, k > 1, many_escapes(beyond, n_all), dtype, cus);
   // Streams that differ in length, as in pick_base_cpt: more chunks per wave where many of the launch's workgroups have
   // none.  us by chunks per wave, BF16 one / two: 7.1 / 6.0 (600 chunks beside 63 streams of 5: 9371 without a tile), 18.8
   // / 12.1 (3000 beside 63 of two), 24.3 / 19.0 (20 000 beside seven of two); E5M2 two / four: 6.2 / 7.1 (600 beside 63 of

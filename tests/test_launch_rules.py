@@ -63,3 +63,18 @@ def test_chunks_per_wave_of_several_streams():
         assert decompress_plan(sz.BF16, chunks)["cpw"] == 1, chunks
     # and a stream that just fills the chip from 5120 on
     assert [decompress_plan(sz.BF16, [c])["cpw"] for c in (4096, 5119, 5120, 16384, 16385)] == [1, 1, 2, 2, 1]
+
+
+def test_chunks_per_wave_of_streams_with_many_escapes():
+    """Above one escape in 16 elements, as the streams' lengths tell, launches that just fill the chip keep to fewer chunks
+    per wave; the rule for few escapes holds up to there."""
+    def cpw(dtype, chunks, share):
+        n = [c * 1024 for c in chunks]
+        return sz.internal_decompress_plan(n, dtype, [sz.total_bytes(v, v // share, dtype) for v in n])["cpw"]
+    for share in (1, 4, 14):
+        assert [cpw(sz.BF16, [c], share) for c in (4096, 6144, 8192, 12288, 16384, 65536)] == [1, 1, 1, 2, 2, 1]
+        assert cpw(sz.BF16, [2048] * 4, share) == 1
+        assert [cpw(sz.FP8_E5M2, [c], share) for c in (4096, 8192, 12288, 16384, 24576, 65536)] == [1, 1, 2, 2, 4, 4]
+    for share in (17, 50, 1000):
+        assert [cpw(sz.BF16, [c], share) for c in (4096, 6144, 8192, 12288, 16384, 65536)] == [1, 2, 2, 2, 2, 1]
+        assert [cpw(sz.FP8_E5M2, [c], share) for c in (4096, 8192, 12288, 16384, 24576, 65536)] == [1, 2, 2, 4, 4, 4]
