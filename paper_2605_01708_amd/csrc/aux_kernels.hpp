@@ -14,9 +14,9 @@
 // lanes that count the same exponent -- most of them, the distribution being what it is -- to one bank: 39 % of
 // the LDS cycles were conflict cycles.)  The waves of a workgroup share the copies, hence atomic adds.
 // Non-zero totals go to the global bins at the end.
-// Workgroup wg of the n_wgs that share the sample.
+// Workgroup wg of the n_wgs that share the sample; they begin at its vector `start` (below their number) and go round.
 template <bool BF16>
-__device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* hist, uint32_t wg, uint32_t n_wgs) {
+__device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* hist, uint32_t wg, uint32_t n_wgs, uint64_t start) {
   constexpr int BINS = BF16 ? 256 : 32;
   __shared__ __attribute__((aligned(16))) uint32_t bins[BINS * 64];
   const int tid = threadIdx.x;
@@ -40,15 +40,16 @@ __device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* h
   };
   // four vectors per thread in flight: the loads of a step are all issued before the first is counted
   const uint64_t step = (uint64_t)n_wgs * 1024;
+  const auto at = [&](uint64_t i) { i += start; return v + (i < nvec ? i : i - nvec); };
   uint64_t i = wg * 1024ull + tid;
   for (; i + 3 * step < nvec; i += 4 * step) {
     u32x4 q[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) q[u] = ld_stream(v + i + u * step);
+    for (int u = 0; u < 4; ++u) q[u] = ld_stream(at(i + u * step));
 #pragma unroll
     for (int u = 0; u < 4; ++u) count(q[u]);
   }
-  for (; i < nvec; i += step) count(ld_stream(v + i));
+  for (; i < nvec; i += step) count(ld_stream(at(i)));
   // the words behind the last whole vector, by workgroup 0
   if (wg == 0) {
     for (uint64_t i = nvec * 16 + (uint64_t)tid * (BF16 ? 2 : 1); i < bytes; i += 1024 * (BF16 ? 2 : 1)) {
@@ -71,7 +72,7 @@ __device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* h
 
 template <bool BF16>
 __global__ __launch_bounds__(1024) void histogram_kernel(const uint8_t* in, uint64_t n, uint64_t* hist) {
-  histogram_body<BF16>(in, n, hist, blockIdx.x, gridDim.x);
+  histogram_body<BF16>(in, n, hist, blockIdx.x, gridDim.x, 0);
 }
 
 // The same for several samples in one launch: the workgroups [first[k], first[k + 1]) count sample k into hists + 256 k.
@@ -90,7 +91,12 @@ __global__ __launch_bounds__(1024) void histogram_batch_kernel(const HistBatchAr
 #pragma unroll
   for (uint32_t step = kHistMost / 2; step; step >>= 1)
     if (a.first[k + step] <= blockIdx.x) k += step;
-  histogram_body<BF16>(a.in[k], a.n[k], hists + 256 * k, blockIdx.x - a.first[k], a.first[k + 1] - a.first[k]);
+  // Samples of equal length, side by side in memory, would be read in step, at addresses a power of two apart: every one
+  // starts at another fraction of its length (64 KB and more of it; multiples of the golden ratio).  us per call from the
+  // start and this way: E5M2 8 of 16 MiB 34.7 and 27.7, 64 of 4 MiB 57.0 and 49.3; BF16 16 of 16 MiB 57.0 and 51.0.
+  const uint64_t nvec = a.n[k] * (BF16 ? 2 : 1) / 16;
+  const uint64_t start = nvec >= 4096 ? (nvec * ((k * 40503u) & 0xffffu) >> 16) & ~63ull : 0;
+  histogram_body<BF16>(a.in[k], a.n[k], hists + 256 * k, blockIdx.x - a.first[k], a.first[k + 1] - a.first[k], start);
 }
 
 __global__ void zero_words_kernel(uint64_t* p, uint64_t nwords) {

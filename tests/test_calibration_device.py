@@ -30,7 +30,8 @@ def test_ranking_of_counts(dtype, n):
 
 @pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
 @pytest.mark.parametrize("sizes", [[0], [1], [0, 0, 5], [3000000, 1, 0, 17, 4096], [70000 * k + 13 for k in range(64)],
-                                   [8191, 8192, 8193] * 30, [16 * 1024 * 4 * 3 + 5, 12]])
+                                   [8191, 8192, 8193] * 30, [16 * 1024 * 4 * 3 + 5, 12],
+                                   [1 << 18] * 9 + [(1 << 18) + 13] * 8, [65535, 65536, 65537, 32767, 32769] * 4])
 def test_batches_count_every_word_once(dtype, sizes):
     gen = kv_synth.kv_bf16 if dtype == sz.BF16 else kv_synth.kv_e5m2
     pool = gen(max(sizes) // 1024 + 2, 9, device="cuda")
