@@ -1040,6 +1040,7 @@ int splitzip_calibrate_batch_device(const splitzip_item* items, uint32_t n_items
   if (n_items == 0) return SPLITZIP_OK;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, d_hists, 256ull * n_items);
+  const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
   for (uint32_t i = 0; i < n_items; i += kHistMost) {
     HistBatchArgs a;
     memset(&a, 0, sizeof a);
@@ -1054,7 +1055,7 @@ int splitzip_calibrate_batch_device(const splitzip_item* items, uint32_t n_items
       a.n[q] = items[i + q].n_elems;
       // its share of one workgroup per CU, but at least four vectors per thread of it, and one workgroup at least
       const uint64_t nvec = (a.n[q] * (dtype == SPLITZIP_BF16 ? 2 : 1) + 15) / 16;
-      uint64_t w = all ? (uint64_t)cu_count() * a.n[q] / all : 0;
+      uint64_t w = all ? cus * a.n[q] / all : 0;
       if (w > (nvec + 4 * 1024 - 1) / (4 * 1024)) w = (nvec + 4 * 1024 - 1) / (4 * 1024);
       wgs += w ? (uint32_t)w : 1u;
     }
