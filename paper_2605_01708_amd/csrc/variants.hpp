@@ -651,7 +651,9 @@ __device__ inline bool v_check_header(const VArgs& a, uint32_t hw, uint32_t* m_o
 // is stored from the registers.  In the absolute mode the correction is left to v_scatter_kernel.
 // One 64 MiB BF16 tensor: 24.1 us under 3-bit codes (32.0 us with the planes picked apart element by element from LDS),
 // 22.3 us in the main format.
-template <int DT, int CB, int MODE, int CS>
+// MANY (sentinel mode): more than a quarter of the elements escaped.  4 Mi random words of BF16, top-15: 9.0 us, against
+// 11.1 one sentinel after the other; 32 Mi of them 40 and 52; but 27.5 and 23.7 with 1 % escapes.
+template <int DT, int CB, int MODE, int CS, bool MANY = false>
 __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
   using F = VFmt<DT>;
   // escape mode, chunk size and position width are compile-time here: none of the format's choices costs a branch
@@ -758,6 +760,51 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
   }
   if (MODE == SPLITZIP_ESC_SENTINEL) any = __ballot((sent[0] | sent[1]) != 0) != 0;
 
+  // Sentinels in many places: a lane's eight at a time, in registers -- the exponent goes where the decode table left none,
+  // no code all ones being in the codebook -- and every exponent asked for before the first is used: those beyond a
+  // chunk's first 64 come from memory.
+  if constexpr (MANY) {
+#pragma unroll
+    for (uint32_t q = 0; q < per_blk; ++q) s_val[wave][64 * q + lane] = (uint8_t)rec_e[q];
+    v_lds_settle();
+    uint32_t carry = 0;
+#pragma unroll
+    for (uint32_t s = 0; s < 2; ++s) {
+      // rank of every sentinel inside its chunk, then its exponent from the chunk's values
+      uint32_t excl, low;
+      const uint32_t tot = v_sparse_excl(__popc(sent[s]), excl, low);
+      const uint32_t q = CS == 10 ? 0u : 2 * s + (lane >> 5);   // the lane's chunk inside the block
+      uint32_t lo = rec_lo[0], n_q = rec_n[0], rank = excl + carry;
+      if (CS == 8) {
+        const uint32_t q0 = (2 * s) & (per_blk - 1), q1 = (2 * s + 1) & (per_blk - 1);
+        lo = lane < 32 ? rec_lo[q0] : rec_lo[q1];
+        n_q = lane < 32 ? rec_n[q0] : rec_n[q1];
+        rank = lane < 32 ? excl : excl - low;
+      } else {
+        carry = tot;
+      }
+      const uint64_t hi = c_first + q < a.n_chunks ? (uint64_t)(uint32_t)(lo + n_q) : 0u;   // the offset behind the chunk's
+      uint32_t e[8];
+#pragma unroll
+      for (uint32_t j = 0; j < 8; ++j) {
+        e[j] = 0;
+        if ((sent[s] >> (CB * j)) & 1u) {
+          const uint64_t r = (uint64_t)(uint32_t)(lo + rank);
+          if (r < hi && r < M) e[j] = rank < 64 && r >= lo ? (uint32_t)s_val[wave][64 * q + rank] : v_value(a, off_val, r);
+          else bad = true;
+          ++rank;
+        }
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < 8; ++j) {
+        if (e[j] >= (uint32_t)F::EXPS) { bad = true; e[j] = 0; }
+        if (F::ES == 2) o[s][j >> 1] |= e[j] << (F::LO + 16 * (j & 1));
+        else o[s][(j >> 2) & (F::NW - 1)] |= e[j] << (F::LO + 8 * (j & 3));
+      }
+    }
+    any = 0;
+  }
+
   uint32_t* tile = s_tile[wave];
   if (any || !full) {
 #pragma unroll
@@ -775,12 +822,12 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
         *t = (uint8_t)F::combine(F::signmant(*t), e);
       }
     };
-    if (MODE == SPLITZIP_ESC_SENTINEL) {
+    if (MODE == SPLITZIP_ESC_SENTINEL && !MANY) {
 #pragma unroll
       for (uint32_t q = 0; q < per_blk; ++q) s_val[wave][64 * q + lane] = (uint8_t)rec_e[q];
     }
     v_lds_settle();
-    if (MODE == SPLITZIP_ESC_SENTINEL) {
+    if (MODE == SPLITZIP_ESC_SENTINEL && !MANY) {
       uint32_t carry = 0;
 #pragma unroll
       for (uint32_t s = 0; s < 2; ++s) {

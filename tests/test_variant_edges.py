@@ -77,3 +77,44 @@ def test_tensors_of_many_workgroups(chunk):
     y, st = torch.empty_like(x), sz.new_sizes()
     sz.variant_decompress(out, vt, n, v, cbv, y, st)
     assert sz.read_sizes(st)[2] == 0 and torch.equal(y, x)
+
+
+@pytest.mark.parametrize("dt,cb,k,chunk,vb", [(sz.BF16, 4, 15, 1024, 0), (sz.BF16, 4, 10, 256, 0), (sz.BF16, 3, 7, 1024, 0), (sz.FP8_E5M2, 4, 15, 256, 0),
+                                              (sz.FP8_E5M2, 3, 7, 1024, 5), (sz.FP8_E5M2, 3, 5, 256, 5), (sz.FP8_E4M3, 4, 12, 1024, 4), (sz.FP8_E4M3, 3, 7, 256, 0)])
+def test_both_ways_to_put_sentinels_right(dt, cb, k, chunk, vb):
+    """A stream longer than a quarter or half of its elements escaped would make it is decoded by another kernel; the
+    length given decides, so any stream can be sent both ways: the same words, and the same verdict on what is wrong."""
+    v, o = sz.variant(dt, cb, k, sz.ESC_SENTINEL, chunk, vb), ov.variant(dt, cb, k, ov.ESC_SENTINEL, chunk, vb)
+    rng = np.random.default_rng(11)
+    bits, raw = (16, np.uint16) if dt == sz.BF16 else (8, np.uint8)
+    random = rng.integers(0, 1 << bits, 9 * 1024, dtype=np.uint32).astype(raw)
+    gen = {sz.BF16: kv_synth.kv_bf16, sz.FP8_E5M2: kv_synth.kv_e5m2, sz.FP8_E4M3: kv_synth.kv_e4m3}[dt]
+    usual = kv_synth.to_numpy_words(gen(9, 4)).copy()
+    dec, _ = ov.calibrate(usual, o.dtype, k)
+    mixed = np.where((np.arange(usual.size) // 64) % 3 == 0, random, usual).astype(raw)
+    for name, x in (("usual", usual), ("random", random), ("mixed", mixed)):
+        for n in (x.size, x.size - 1021, 7, 1024):
+            blob, m = ov.compress(x[:n].copy(), o, dec)
+            cbv = sz.variant_codebook_from_dec(list(dec), v)
+            bound = sz.variant_compress_bound(n, v)
+            buf = torch.zeros(bound, dtype=torch.uint8, device="cuda")
+            buf[:blob.size] = dev(blob)
+
+            def decode(stream, length):
+                y, st = torch.full((n + 64,), 0x5A, dtype=torch.int16 if dt == sz.BF16 else torch.uint8, device="cuda"), sz.new_sizes()
+                sz.variant_decompress(stream, length, n, v, cbv, y, st)
+                return y, sz.read_sizes(st)
+
+            for length in (blob.size, bound):
+                y, (total, got_m, status) = decode(buf, length)
+                print(f"case {name} n={n} m={m} length={length}", flush=True)
+                assert (total, got_m, status) == (blob.size, m, 0)
+                assert np.array_equal(y[:n].cpu().numpy().view(raw), x[:n]) and bool((y[n:] == 0x5A).all())
+            # wrong streams: an offset moved, codes turned into sentinels without a value
+            off_sm = (64 + 4 * (-(-n // chunk) + 1) + 255) // 256 * 256
+            sm_bytes = (n * {sz.BF16: 8, sz.FP8_E5M2: 3, sz.FP8_E4M3: 4}[dt] + 7) // 8
+            off_code = off_sm + (sm_bytes + 255) // 256 * 256
+            for at, byte in ((64, 1), (67, 0x80), (off_code, 0xFF), (off_code + n * cb // 16, 0xFF)):
+                bad = buf.clone()
+                bad[at] = byte
+                assert decode(bad, blob.size)[1] == decode(bad, bound)[1], (name, n, at)
