@@ -518,9 +518,10 @@ def test_batch_calibrated_on_the_device(dtype):
 
 @pytest.fixture
 def hooks():
-    """the library's test hooks (small staging and status areas); off again afterwards"""
+    """the library's test hooks (small staging and status areas); off again afterwards, forced launch shapes too"""
     yield sz.internal_test_hooks
     sz.internal_test_hooks()
+    sz.internal_test_launch()
 
 
 def test_compress_beside_other_work_on_the_device():
@@ -642,16 +643,19 @@ def test_batch_that_takes_several_launches(hooks, dtype):
 
 
 @pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
+@pytest.mark.parametrize("cpt", [1, 2, 4])
 @pytest.mark.parametrize("groups,stage,direct", [(2, 0, 0), (4, 0, 1), (4, 8192, 0), (1, 0, 1), (2, 8192, 1)])
-def test_finishing_pass_with_several_groups_per_workgroup(hooks, dtype, groups, stage, direct):
+def test_finishing_pass_with_several_groups_per_workgroup(hooks, dtype, groups, stage, direct, cpt):
     """Large launches give every workgroup of the finishing pass two or four groups of 16 tiles; forced here on a
     batch of tensors whose group counts are everything but multiples of four (none, one, a group and a tile, ...),
     once with a staging area so small that tiles are encoded again by the finishing pass; direct = 1: the finishing
-    pass is given sums of 64 tile counts (as in large launches) instead of reading the counts itself"""
+    pass is given sums of 64 tile counts (as in large launches) instead of reading the counts itself; tiles of all the sizes
+    that launches take"""
     hooks(finish_groups=groups, stage_bytes=stage, direct_bytes=direct)
+    sz.internal_test_launch(cpt=cpt)
     cb_or = calibrated(dtype)
     cb = gpu_codebook(cb_or)
-    per_group = 128 if dtype == sz.BF16 else 256     # chunks per group of 16 tiles
+    per_group = 16 * 4 * cpt     # chunks per group of 16 tiles
     chunks = [11 * per_group - 60, per_group - 1, per_group, per_group + 1, 1, 0, 4 * per_group + 9, 8 * per_group, 3]
     xs_np = []
     for k, c in enumerate(chunks):
@@ -825,3 +829,28 @@ def test_more_tensors_than_one_launch_takes():
         assert sz.read_sizes(st)[2] == 0
         for k, (y, t) in enumerate(zip(ys, xs)):
             assert torch.equal(y, t), f"{how}: item {k} round trip"
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_more_long_tensors_than_one_launch_takes(dtype):
+    """The same with tensors that no workgroup does by itself: the second launch's dense and finishing passes take their
+    codebooks, records and sizes from the 65th on."""
+    chunks = 49     # one more than the most a workgroup does by itself
+    xs = [words_tensor(synth(dtype, chunks + 1, 300 + k, layer=k % 7, kind="KV"[k % 2])[: chunks * 1024 - 11 * (k % 5)].copy()) for k in range(67)]
+    dcbs = sz.DeviceCodebooks(67, dtype)
+    sz.CalibrateBatchDevice(xs, dcbs).launch()
+    outs = [torch.full((sz.compress_bound(x.numel(), dtype),), POISON, dtype=torch.uint8, device="cuda") for x in xs]
+    ws, rec = sz.Workspace(chunks * 1024, dtype), sz.new_sizes_array(67)
+    sz.CompressBatchDcb(xs, dcbs, outs).launch(ws, rec)
+    torch.cuda.synchronize()
+    got = sz.read_sizes_array(rec)
+    for k, x in enumerate(xs):
+        x_np = kv_synth.to_numpy_words(x)
+        ref, m = oracle.compress(x_np, oracle.codebook_from_dec(np.array(dcbs.to_host(k).dec, np.uint8), DT[dtype]))
+        assert got[k] == (ref.size, m, 0), k
+        assert np.array_equal(outs[k][: ref.size].cpu().numpy(), ref), k
+        assert bool((outs[k][ref.size:] == POISON).all())
+    ys, st = [torch.zeros_like(x) for x in xs], sz.new_sizes()
+    sz.DecompressBatchDcb(outs, [g[0] for g in got], [x.numel() for x in xs], dcbs, ys).launch(st)
+    assert sz.read_sizes(st)[2] == 0
+    assert all(torch.equal(x, y) for x, y in zip(xs, ys))
