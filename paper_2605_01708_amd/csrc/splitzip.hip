@@ -952,15 +952,18 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
   const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
   p.cpw = pick_decompress_cpw(chunks_all, k > 1, many_escapes(beyond, n_all), dtype, cus);
   // Streams that differ in length, as in pick_base_cpt: more chunks per wave where many of the launch's workgroups have
-  // none.  us by chunks per wave, BF16 one / two: 7.1 / 6.0 (600 chunks beside 63 streams of 5: 9371 without a tile), 18.8
-  // / 12.1 (3000 beside 63 of two), 24.3 / 19.0 (20 000 beside seven of two); E5M2 two / four: 6.2 / 7.1 (600 beside 63 of
-  // 5: 4686), 10.1 / 9.5 (1500 beside 63 of 50: 11 418), 42.5 / 24.8 (13 000 beside 63 of two), four / eight: 26.1 / 29.1
-  // (8192 beside 63 of 100: 31 862), 24.8 / 16.0 (13 000 beside 63 of two: 51 184); where the streams fill the chip anyway
-  // 37.9 / 34.7 (two of 9000 beside 62 of 1000: 31 000).
-  const uint32_t most = dtype == SPLITZIP_BF16 ? 2u : 8u;
+  // none.  us by chunks per wave, BF16 one / two: 7.1 / 6.2 (600 chunks beside 63 streams of 5: 9371 without a tile), 18.8
+  // / 12.1 (3000 beside 63 of two), 24.3 / 19.0 (20 000 beside seven of two), two / four, where the streams are a small part
+  // of it: 45.8 / 45.6 (four of 8192 beside 60 of 200: 60 000), 97.3 / 61.5 (32 768 beside 63 of two); E5M2 two / four: 6.2 /
+  // 7.1 (600 beside 63 of 5: 4686), 10.1 / 9.5 (1500 beside 63 of 50: 11 418), 42.5 / 24.8 (13 000 beside 63 of two), four /
+  // eight: 26.1 / 29.1 (8192 beside 63 of 100: 31 862), 24.8 / 16.0 (13 000 beside 63 of two: 51 184); where the streams fill
+  // the chip anyway 37.9 / 34.7 (two of 9000 beside 62 of 1000: 31 000).
   const uint64_t none = chunks_max * k - chunks_all;   // chunks that the padded grid has room for and the streams do not have
-  if (!g_hooks.cpw.load())
-    while (p.cpw < most && none / (kWaves * p.cpw) > cus * (p.cpw < 4 ? 32u : chunks_all < 256 * cus ? 160u : 96u)) p.cpw *= 2;
+  if (!g_hooks.cpw.load()) {
+    const uint32_t most = dtype == SPLITZIP_FP8_E5M2 ? 8u : none > 8 * chunks_all ? 4u : 2u;
+    const auto limit = [&](uint32_t cpw) { return dtype == SPLITZIP_BF16 ? (cpw < 2 ? 32u : 224u) : cpw < 4 ? 32u : chunks_all < 256 * cus ? 160u : 96u; };
+    while (p.cpw < most && none / (kWaves * p.cpw) > cus * limit(p.cpw)) p.cpw *= 2;
+  }
   p.wgs = (uint32_t)((chunks_max + (uint64_t)kWaves * p.cpw - 1) / (kWaves * p.cpw));
   if (p.wgs < 1) p.wgs = 1;
   // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 88.1 and 87.1
