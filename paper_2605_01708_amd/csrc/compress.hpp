@@ -363,8 +363,8 @@ struct E5m2 {
 #pragma unroll
     for (int d = 0; d < 4; ++d) asm volatile("" : "+v"(r.w[d]));
   }
-  // a tile of 16 chunks is 16 KB of words here; eight workgroups per CU (730 us for 64 tensors of 32 MiB
-  // against 750 us with six and 790 us with five)
+  // a tile of 4 cpt chunks: 16 KB of words in the longest launches and in padded ones, 4 or 8 KB below (pick_base_cpt); eight workgroups per CU (730 us for 64 tensors of 32 MiB against 750 us with six and
+  // 790 us with five)
   static constexpr uint32_t kCpt = 4;
   static constexpr uint32_t kSmallChunks = 48;
   static constexpr int kWavesPerSimd = 8;

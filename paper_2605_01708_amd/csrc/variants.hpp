@@ -373,30 +373,19 @@ __global__ __launch_bounds__(kThreads) void v_dense_kernel(const VArgs a) {
 
 constexpr uint32_t kVScanTile = 1024;   // counts per workgroup of the summing kernel
 
-// sum of 1024 values, one per thread, in every thread (two barriers)
-__device__ inline uint32_t v_block_sum(uint32_t v, uint32_t* s_wave /*16*/, uint32_t& incl_out, uint32_t& before_out) {
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t incl = wave_incl_scan(v);
-  __syncthreads();   // s_wave may still be read from an earlier call
-  if (lane == 63) s_wave[wave] = incl;
-  __syncthreads();
-  uint32_t before = 0, all = 0;
-  for (uint32_t w = 0; w < 16; ++w) {
-    if (w < wave) before += s_wave[w];
-    all += s_wave[w];
-  }
-  incl_out = incl;
-  before_out = before;
-  return all;
-}
-
 // compress pass 2, for tensors of more than kVDirectSums workgroups: the escapes of every tile of 1024 chunks
 __global__ __launch_bounds__(1024) void v_tile_sum_kernel(const VArgs a) {
   __shared__ uint32_t s_wave[16];
   const uint64_t c = (uint64_t)blockIdx.x * kVScanTile + threadIdx.x;
-  uint32_t incl, before;
-  const uint32_t all = v_block_sum(c < a.n_chunks ? a.counts[c] : 0u, s_wave, incl, before);
-  if (threadIdx.x == 0) a.tile_sums[blockIdx.x] = all;
+  const uint32_t sum = wave_last(wave_incl_scan(c < a.n_chunks ? a.counts[c] : 0u));
+  if ((threadIdx.x & 63u) == 0) s_wave[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t all = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < 16; ++w) all += s_wave[w];
+    a.tile_sums[blockIdx.x] = all;
+  }
   // the finishing pass reads whole vectors of four sums
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x > 0 && threadIdx.x < 4 && (blockIdx.x & 3u) + threadIdx.x < 4) a.tile_sums[blockIdx.x + threadIdx.x] = 0;
 }
