@@ -439,8 +439,7 @@ constexpr uint32_t kMore = 1u;              // in a group's mark of the finishin
 static_assert(kGroup * kSlotAhead == kTileThreads, "every thread fetches records of one tile ahead");
 
 // The arguments of a launch: what all its tensors share, then the tensors (N: room for kBatchMax of them, or for the
-// one of a single call, whose two launches then carry 144 bytes instead of 3.2 KB each; those start on a cache line on the
-// host, too: wherever else the stack put them, the runtime's copy of them took 2 us longer or not from build to build).  A workgroup needs the first part and one
+// one of a single call, whose two launches then carry 144 bytes instead of 3.2 KB each).  A workgroup needs the first part and one
 // tensor's, 144 bytes; both are fetched whole before anything is done with them (args_arrived).
 struct TileItem {
   const uint8_t* in;

@@ -401,7 +401,7 @@ struct DBatchItem {
   uint8_t* out;
   uint64_t n, comp_bytes;
 };
-struct alignas(64) DecompressBatchArgs {   // 3.2 KB: aligned for the host's sake, see TileArgs
+struct alignas(64) DecompressBatchArgs {
   DBatchItem item[kBatchMax];
   splitzip_sizes* sizes;   // nullable; one record, status bits sticky
   uint32_t cpw, dtype, reg_patch_max;
