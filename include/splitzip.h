@@ -179,8 +179,8 @@ int splitzip_compress(const void* d_in, uint64_t n_elems, int dtype, const split
  * allocating library routine).  Same arguments otherwise, same stream bytes
  * and sizes record as splitzip_compress.  Limit: n_elems <=
  * splitzip_noalloc_max_elems() = 2^30; beyond it SPLITZIP_ERR_UNSUPPORTED and
- * nothing is enqueued.  (Tensors above 64 Mi elements get tiles larger than
- * 16 KB so that their counts fit, and a tile whose escape records outgrow its
+ * nothing is enqueued.  (Tensors above 500 Mi elements get larger tiles so
+ * that their counts fit, and a tile whose escape records outgrow its
  * share of the staging area -- a few dozen per tile at 64 MiB of BF16 -- is
  * encoded a second time by the finishing launch: correct at any escape rate,
  * slower above a few percent.)  All calls on one GPU share that GPU's array:
@@ -194,7 +194,9 @@ int splitzip_compress_noalloc(const void* d_in, uint64_t n_elems, int dtype, con
 /* Section 3.2, decoding path: nibble unpack, 16-entry table, recombination by
  * eq. (2), then the sparse overwrite of the exponent field at every recorded
  * escape position.
- *   d_comp      the stream, comp_bytes readable bytes, 16-byte aligned
+ *   d_comp      the stream, comp_bytes readable bytes, 16-byte aligned.  The
+ *               stream's own length serves best: what it leaves beyond the
+ *               fixed part is also how many escapes the launch is shaped for
  *   d_out       n_elems words, 16-byte aligned
  *   d_sizes     nullable.  total_bytes / n_escapes are copied from the header;
  *               status bits are OR-ed into the existing value (sticky), so the
@@ -368,7 +370,8 @@ int splitzip_decompress_batch_paged(const splitzip_ditem* items, uint32_t n_item
  * chunks, and E4M3 words.  These calls exist to measure those formats beside
  * the main one on the same device; they run through one generic set of kernels
  * (dense pass with per-chunk counts and staged escape records, finishing
- * pass; dense decode with the correction applied in LDS) that is NOT the tuned
+ * pass; dense decode with the correction applied in LDS or, to streams full of
+ * sentinels, in registers) that is NOT the tuned
  * path of splitzip_compress
  * and splitzip_decompress.  The main format is one of the variants, so all of
  * them can be compared through the same kernels.

@@ -3,8 +3,8 @@
 //   common.hpp      stream layout, wave scan, agent-scope accesses
 //   compress.hpp    dense transform (paper section 3.2 eq. (1), encode table, nibble pack, planes)
 //                   fused with escape detection, counting and position-ordered compaction
-//                   (appendix "Quad64 Vectorized Encoding" fuses only the counting); one launch
-//                   per tensor, or one launch for a batch of tensors
+//                   (appendix "Quad64 Vectorized Encoding" fuses only the counting); two launches
+//                   for a tensor or up to 64 of them, one for small tensors
 //   decompress.hpp  nibble unpack, decode table, eq. (2), scatter correction in registers; one
 //                   launch per tensor or per batch
 //   aux_kernels.hpp calibration histogram (section 3.3), workspace initialisation, traffic probe

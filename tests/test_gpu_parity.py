@@ -771,8 +771,8 @@ def test_full_size_tensors_through_the_batch_calls(dtype):
 
 
 def test_batch_tensor_larger_than_a_full_group():
-    """an E5M2 tensor of 70 Mi elements has more chunks than the largest group the batch kernel forms can share at 64
-    per workgroup: the grid is cut down to one group of that size; a small tensor rides in the same launch"""
+    """an E5M2 tensor of 70 Mi elements, thousands of tiles and hundreds of groups of them, and a small tensor that rides in
+    the same launch, most of whose row of workgroups has no tile"""
     dtype = sz.FP8_E5M2
     cb_or = calibrated(dtype, seed=1, tokens=1024, layer=0, kind="K")
     cb = gpu_codebook(cb_or)
