@@ -23,8 +23,7 @@ __device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* h
   for (int i = tid; i < BINS * 16; i += 1024) reinterpret_cast<u32x4*>(bins)[i] = u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
   uint32_t* mine = bins + (tid & 63);
-  const uint64_t bytes = n * (BF16 ? 2 : 1);
-  const uint32_t nvec = (uint32_t)(bytes / 16);   // a sample has fewer than 2^32 elements
+  const uint64_t bytes = n * (BF16 ? 2 : 1), nvec = bytes / 16;
   const u32x4* v = reinterpret_cast<const u32x4*>(in);
   auto count = [&](const u32x4& q) {
     const uint32_t w[4] = {q.x, q.y, q.z, q.w};
@@ -40,20 +39,29 @@ __device__ inline void histogram_body(const uint8_t* in, uint64_t n, uint64_t* h
     }
   };
   // four vectors per thread in flight: the loads of a step are all issued before the first is counted
-  const uint32_t step = n_wgs * 1024;
-  const auto at = [&](uint32_t i) { i += start; return v + (i < nvec ? i : i - nvec); };
-  uint32_t i = wg * 1024 + tid;
-  for (; i + 3 * step < nvec; i += 4 * step) {
-    u32x4 q[4];
+  const uint64_t step = (uint64_t)n_wgs * 1024;
+  const auto from_to_end = [&](const auto& at) {
+    uint64_t i = wg * 1024ull + tid;
+    for (; i + 3 * step < nvec; i += 4 * step) {
+      u32x4 q[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) q[u] = ld_stream(at(i + u * step));
+      for (int u = 0; u < 4; ++u) q[u] = ld_stream(at(i + u * step));
 #pragma unroll
-    for (int u = 0; u < 4; ++u) count(q[u]);
+      for (int u = 0; u < 4; ++u) count(q[u]);
+    }
+    for (; i < nvec; i += step) count(ld_stream(at(i)));
+  };
+  if (start) {
+    from_to_end([&](uint64_t i) {
+      const uint32_t p = (uint32_t)i + start;   // a sample has fewer than 2^30 vectors
+      return v + (p < (uint32_t)nvec ? p : p - (uint32_t)nvec);
+    });
+  } else {
+    from_to_end([&](uint64_t i) { return v + i; });
   }
-  for (; i < nvec; i += step) count(ld_stream(at(i)));
   // the words behind the last whole vector, by workgroup 0
   if (wg == 0) {
-    for (uint64_t i = nvec * 16ull + (uint64_t)tid * (BF16 ? 2 : 1); i < bytes; i += 1024 * (BF16 ? 2 : 1)) {
+    for (uint64_t i = nvec * 16 + (uint64_t)tid * (BF16 ? 2 : 1); i < bytes; i += 1024 * (BF16 ? 2 : 1)) {
       const uint32_t e = BF16 ? ((uint32_t)(in[i] | (in[i + 1] << 8)) >> 7) & 0xffu : ((uint32_t)in[i] >> 2) & 31u;
       atomicAdd(&mine[e * 64], 1u);
     }
@@ -84,23 +92,25 @@ constexpr uint32_t kHistMost = 64;
 struct HistBatchArgs {
   const uint8_t* in[kHistMost];
   uint64_t n[kHistMost];
+  uint32_t start[kHistMost];       // see histogram_start
   uint32_t first[kHistMost + 1];   // behind the last sample: its end, up to the last entry
 };
+// The vector that the workgroups of sample k (of nvec vectors) begin at.  Samples that begin a multiple of 1 MiB apart
+// (equal lengths that are powers of two, allocations of their own) would be read in step, all of them at the same place of
+// their MiB: each of those starts 17 KB further in than the one before it, up to 256 KB.  us per call from the start and
+// this way: E5M2 8 of 16 MiB 31.4-34.7 and 30.5, 64 of 4 MiB 55.6 and 51.3; BF16 16 of 16 MiB 57.0 and 52.8.  (Others gain
+// nothing by it: 100 of 1999 KiB read that way and then compressed and decompressed 197 us, 195 without.)
+inline uint32_t histogram_start(const void* first, const void* in, uint32_t k, uint64_t nvec) {
+  const bool in_step = ((reinterpret_cast<uintptr_t>(in) - reinterpret_cast<uintptr_t>(first)) & ((1u << 20) - 1u)) == 0;
+  return in_step && nvec >= 4096 ? (k * 1088u) & (nvec < 16384 ? 4095u : 16383u) : 0u;
+}
 template <bool BF16>
 __global__ __launch_bounds__(1024) void histogram_batch_kernel(const HistBatchArgs a, uint64_t* hists) {
   uint32_t k = 0;   // the last sample that starts at or before this workgroup
 #pragma unroll
   for (uint32_t step = kHistMost / 2; step; step >>= 1)
     if (a.first[k + step] <= blockIdx.x) k += step;
-  // Samples that begin a multiple of 1 MiB apart (equal lengths that are powers of two, allocations of their own) would be
-  // read in step, all of them at the same place of their MiB: each of those starts 17 KB further in than the one before
-  // it, up to 256 KB.  us per call from the start and this way: E5M2 8 of 16 MiB 34.7 and 30.1, 64 of 4 MiB 57.1 and 51.5;
-  // BF16 16 of 16 MiB 57.0 and 52.8.  (Others gain nothing by it: 100 of 1999 KiB read that way and then compressed
-  // and decompressed 197 us, 195 without.)
-  const uint32_t nvec = (uint32_t)(a.n[k] * (BF16 ? 2 : 1) / 16);
-  const bool in_step = ((reinterpret_cast<uint64_t>(a.in[k]) - reinterpret_cast<uint64_t>(a.in[0])) & ((1u << 20) - 1u)) == 0;
-  const uint32_t start = in_step && nvec >= 4096 ? (k * 1088u) & (nvec < 16384 ? 4095u : 16383u) : 0u;
-  histogram_body<BF16>(a.in[k], a.n[k], hists + 256 * k, blockIdx.x - a.first[k], a.first[k + 1] - a.first[k], start);
+  histogram_body<BF16>(a.in[k], a.n[k], hists + 256 * k, blockIdx.x - a.first[k], a.first[k + 1] - a.first[k], a.start[k]);
 }
 
 __global__ void zero_words_kernel(uint64_t* p, uint64_t nwords) {

@@ -1075,6 +1075,7 @@ int splitzip_calibrate_batch_device(const splitzip_item* items, uint32_t n_items
       a.n[q] = items[i + q].n_elems;
       // its share of one workgroup per CU, but at least four vectors per thread of it, and one workgroup at least
       const uint64_t nvec = (a.n[q] * (dtype == SPLITZIP_BF16 ? 2 : 1) + 15) / 16;
+      a.start[q] = histogram_start(a.in[0], a.in[q], q, a.n[q] * (dtype == SPLITZIP_BF16 ? 2 : 1) / 16);
       uint64_t w = all ? cus * a.n[q] / all : 0;
       if (w > (nvec + 4 * 1024 - 1) / (4 * 1024)) w = (nvec + 4 * 1024 - 1) / (4 * 1024);
       wgs += w ? (uint32_t)w : 1u;
