@@ -83,18 +83,20 @@ __device__ inline uint8_t* chunk_at(const Words& w, uint64_t cbase, uint32_t pag
   return w.base + (uint64_t)page * w.page_stride + ES * (cbase & ((1ull << w.page_shift) - 1));
 }
 
-// The hardware deals workgroups to the 8 XCDs in turn.  xcd_order renumbers the workgroups of a tensor of n tiles, 128
-// at a time, so that every XCD works on runs of 16 tiles in a row (256 KB of BF16 words) while the window that the whole
-// chip works on stays as compact as before; the last n % 128 keep their numbers, and so do workgroups beyond n, which
-// have no tile (n is the tensor's own count, not the launch row's: a window that the tensor only begins would leave its
-// tiles to the first few XCDs -- BF16, 4 tensors of 8192 chunks beside 60 of 200, compress: 62.1 us that way, 49.2 this way).
+// The hardware deals workgroups to the 8 XCDs in turn.  xcd_order renumbers the workgroups of a tensor, 128 at a
+// time, so that every XCD works on runs of 16 tiles in a row (256 KB of BF16 words) while the window that the whole
+// chip works on stays as compact as before; those behind the last whole window keep their numbers, also the ones that
+// have no tile (`last` is the tensor's own last tile, not the launch row's: a window that the tensor only begins would
+// leave its tiles to the first few XCDs -- BF16, 4 tensors of 8192 chunks beside 60 of 200, compress: 62.1 us that way,
+// 49.2 this way).
 // Worth it for launches of many tiles (the rules are at the launches); runs of 8 tiles or fewer were slower than no
 // order at all, runs of 64 gained as much for compress but lost for the decoders.
 constexpr uint32_t kXcds = 8, kXcdRun = 16;
-__host__ __device__ inline uint32_t xcd_order(uint32_t b, uint32_t n) {
-  const uint32_t in = b & (kXcds * kXcdRun - 1u), base = b - in;
-  return base + kXcds * kXcdRun <= n ? base + (in % kXcds) * kXcdRun + in / kXcds : b;
+constexpr uint32_t kXcdWindow = kXcds * kXcdRun;
+__host__ __device__ inline uint32_t xcd_place(uint32_t b) {
+  return (b & ~(kXcdWindow - 1u)) + (b % kXcds) * kXcdRun + (b % kXcdWindow) / kXcds;
 }
+__host__ __device__ inline uint32_t xcd_order(uint32_t b, uint32_t last) { return last >= (b | (kXcdWindow - 1u)) ? xcd_place(b) : b; }
 
 template <typename T>
 __device__ inline T ld_stream(const T* p) { return __builtin_nontemporal_load(p); }

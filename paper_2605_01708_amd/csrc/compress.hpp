@@ -539,7 +539,12 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
   args_arrived(args, item, a, it);
   const TileGeom G = tile_geom(a, it, item, F::DT);
   const Planes& P = G.P;
-  const uint32_t t = a.by_xcd ? xcd_order(blockIdx.x, G.n_tiles) : blockIdx.x;
+  // xcd_order, written out as one condition with the last tile straight from the length: as a call under by_xcd, or with
+  // G.n_tiles - 1, the registers of what follows are laid out differently and it comes out slower (us per call: BF16, 3
+  // tensors of 5937 chunks 17.1 and 16.7, 4 of 1999 paged 11.1 and 10.9; E5M2, 3 of 5937 13.3 and 13.2).  Without
+  // elements there is no last tile, and no tile either.
+  const uint32_t t = a.by_xcd && ((it.n - 1u) >> (10 + a.tile_shift)) >= (blockIdx.x | (kXcdWindow - 1u))
+                         ? xcd_place(blockIdx.x) : blockIdx.x;
   if (t >= G.n_tiles) return;
   const uint32_t r0 = t << a.tile_shift, nb = P.n_chunks - r0 < G.tile_chunks ? P.n_chunks - r0 : G.tile_chunks;
   const uint32_t w0 = (uint32_t)wave * a.cpt;                                   // the wave's first chunk inside the tile

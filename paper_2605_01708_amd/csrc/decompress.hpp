@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const Decomp
   // (in 32 bits, or by a shift, a workgroup without a tile leaves 12 to 25 % earlier, but the code that follows comes out
   // different: 8 tensors of 16 384 chunks with 7 escapes each 80.8-81.2 us instead of 80.1)
   const uint32_t n_tiles = (uint32_t)((L.n_chunks + (uint64_t)kWaves * b.cpw - 1) / (kWaves * b.cpw));
-  const uint32_t tile = b.by_xcd ? xcd_order(blockIdx.x, n_tiles) : blockIdx.x;
+  const uint32_t tile = b.by_xcd ? xcd_order(blockIdx.x, n_tiles - 1) : blockIdx.x;
   if (tile >= (n_tiles ? n_tiles : 1u)) return;
   DecompressArgs a;
   a.comp = it.comp;

@@ -1130,7 +1130,7 @@ void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_item
   memcpy(out, v, sizeof v);
 }
 // the tile that workgroup b of a tensor of n tiles takes in a launch by XCDs
-uint32_t splitzip_internal_xcd_tile(uint32_t b, uint32_t n) { return xcd_order(b, n); }
+uint32_t splitzip_internal_xcd_tile(uint32_t b, uint32_t n) { return xcd_order(b, n - 1); }
 void splitzip_internal_decompress_plan(const splitzip_ditem* items, uint32_t n_items, int dtype, uint32_t out[3]) {
   const DecompressPlan p = plan_decompress(items, n_items < kBatchMax ? n_items : kBatchMax, dtype);
   out[0] = p.cpw; out[1] = p.wgs; out[2] = p.by_xcd;
