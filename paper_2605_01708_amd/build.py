@@ -1,14 +1,20 @@
-"""Builds libsplitzip.so (HIP kernels + C ABI) for gfx950, in-tree, with hipcc."""
+"""Builds, in-tree, libsplitzip.so (HIP kernels + C ABI) for gfx950 with hipcc, and _fastcall.so, the binding's short way
+into it, with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
+
+import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc", "splitzip.hip")
 INC = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libsplitzip.so")
+FAST_SRC = os.path.join(HERE, "csrc", "fastcall.cpp")
+FAST = os.path.join(HERE, "_fastcall.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
@@ -23,7 +29,22 @@ def build(verbose: bool = False, extra_flags=()) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
+    build_fastcall(verbose)
     return LIB
+
+
+def build_fastcall(verbose: bool = False) -> str:
+    at = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INC, "-I", os.path.join(at, "include"),
+           "-I", os.path.join(at, "include", "torch", "csrc", "api", "include"), "-I", os.path.join(rocm, "include"),
+           "-I", sysconfig.get_paths()["include"], FAST_SRC, "-o", FAST, "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu",
+           "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    return FAST
 
 
 if __name__ == "__main__":

@@ -1,0 +1,298 @@
+// The short way from Python into libsplitzip.so for the calls that a serving loop repeats: what the ctypes binding does
+// with a call's arguments, done here in one step (argument marshalling only; the library does everything else).
+//
+// A small call is bound by the host: one launch costs it 2.3 us, and marshalling a compress call in Python and ctypes
+// cost 2.3 us on top of its two launches (numel, element_size, is_contiguous, data_ptr of four tensors: 1.3; ctypes:
+// 1.0), a decompress call 2.0 on top of one; this way it is 0.7 a call.  compress + decompress of a 4 MiB tensor, enqueued one
+// after the other: 11.9 us, now 8.5.
+//
+// Only the plain form of every argument is taken -- tensors that are torch.Tensor itself, on the GPU, Python integers,
+// the binding's own ctypes structures, no torch function mode watching -- and only if the checks of the Python side hold.
+// Anything else is left to the general way in binding.py, which also raises the errors: a function here answers the
+// library's code (0 or negative), or 1 if it has done nothing.
+#include <Python.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/hip/HIPStream.h>
+#include <dlfcn.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <cstdint>
+#include <type_traits>
+#include <utility>
+
+#include "splitzip.h"
+
+namespace {
+
+constexpr int kNotTaken = 1;
+constexpr int kMost = 12;   // arguments of an entry point, at most
+
+// the library's function called with its own types, from as many 64-bit words
+template <typename A>
+A arg(uint64_t w) {
+  if constexpr (std::is_pointer_v<A>) return reinterpret_cast<A>(static_cast<uintptr_t>(w));
+  else return static_cast<A>(w);
+}
+template <typename F>
+struct Caller;
+template <typename... A>
+struct Caller<int(A...)> {
+  static constexpr int kArgs = sizeof...(A);
+  static_assert(kArgs <= kMost, "room for the words");
+  template <size_t... I>
+  static int with(void* fn, const uint64_t* w, std::index_sequence<I...>) { return reinterpret_cast<int (*)(A...)>(fn)(arg<A>(w[I])...); }
+  static int call(void* fn, const uint64_t* w) { return with(fn, w, std::index_sequence_for<A...>()); }
+};
+
+// What a call's Python arguments are, a letter each (two letters where it says "and"), and the words they become:
+//   W  words, a contiguous tensor: address and number of elements; the size of one is compared with the dtype that a
+//      C, V or D names
+//   P  a tensor: its address            p  the same, or None: null
+//   R  room, a tensor, and its capacity in bytes or None (all of it): address, bytes
+//   Y  room for decoded words, a contiguous tensor of at least the elements that the N before it says: its address
+//   I  an integer                       N  the same: the elements of a stream
+//   D  an integer: the dtype
+//   A  a ctypes array of items: its address                G  a page geometry: its address
+//   C  a codebook: its dtype and its address               K  a codebook: its address alone
+//   V  a format of the variants: its address
+//   S  a stream's handle, or None: the current one
+struct Entry {
+  const char* name;
+  const char* spec;
+  int n_words;
+  int (*call)(void*, const uint64_t*);
+};
+#define ENTRY(NAME, SPEC) {#NAME, SPEC, Caller<decltype(NAME)>::kArgs, &Caller<decltype(NAME)>::call}
+const Entry kEntries[] = {
+    ENTRY(splitzip_compress, "WCRPIPS"),
+    ENTRY(splitzip_decompress, "PINCYpS"),
+    ENTRY(splitzip_compress_noalloc, "WCRPS"),
+    ENTRY(splitzip_compress_dcb, "WDPRPIPS"),
+    ENTRY(splitzip_decompress_dcb, "PINDPYpS"),
+    ENTRY(splitzip_decompress_own, "PINDYpS"),
+    ENTRY(splitzip_compress_paged, "GICRPIPS"),
+    ENTRY(splitzip_decompress_paged, "PIICGpS"),
+    ENTRY(splitzip_compress_batch, "AIIPIPS"),
+    ENTRY(splitzip_decompress_batch, "AIIPS"),
+    ENTRY(splitzip_compress_batch_dcb, "AIIPPIPS"),
+    ENTRY(splitzip_decompress_batch_dcb, "AIIPPS"),
+    ENTRY(splitzip_decompress_batch_own, "AIIPS"),
+    ENTRY(splitzip_compress_batch_paged, "AIIGPIPS"),
+    ENTRY(splitzip_decompress_batch_paged, "AIIGPS"),
+    ENTRY(splitzip_calibrate_batch_device, "AIIPPS"),
+    ENTRY(splitzip_variant_compress, "WVKRRPS"),
+    ENTRY(splitzip_variant_decompress, "PINVKYpS"),
+};
+#undef ENTRY
+
+// the binding's ctypes structures, as bind was given them
+struct Types {
+  PyObject *codebook, *variant, *paged;
+};
+struct Bound {
+  void* fn;
+  const Entry* entry;
+  Types types;   // references held
+};
+
+struct Refused {};   // thrown where an argument is not of the plain form
+
+const at::Tensor& tensor(PyObject* o) {
+  if (!THPVariable_CheckExact(o)) throw Refused();
+  const at::Tensor& t = THPVariable_Unpack(o);
+  if (!t.is_cuda() || t.layout() != at::kStrided) throw Refused();   // on the GPU: its runtime is up, there is a current stream
+  return t;
+}
+uint64_t integer(PyObject* o) {
+  if (!PyLong_CheckExact(o)) throw Refused();
+  const unsigned long long v = PyLong_AsUnsignedLongLong(o);
+  if (v == static_cast<unsigned long long>(-1) && PyErr_Occurred()) {
+    PyErr_Clear();
+    throw Refused();
+  }
+  return v;
+}
+// the memory of a ctypes object, held until the call has returned
+struct Views {
+  Py_buffer held[4];
+  int n = 0;
+  void* of(PyObject* o, const PyObject* type, Py_ssize_t least) {
+    if (type && reinterpret_cast<const PyObject*>(Py_TYPE(o)) != type) throw Refused();
+    if (n == 4 || PyObject_GetBuffer(o, &held[n], PyBUF_SIMPLE | PyBUF_WRITABLE) != 0) {
+      PyErr_Clear();
+      throw Refused();
+    }
+    ++n;
+    if (held[n - 1].len < least) throw Refused();
+    return held[n - 1].buf;
+  }
+  ~Views() {
+    for (int i = 0; i < n; ++i) PyBuffer_Release(&held[i]);
+  }
+};
+int64_t bytes_per_word(uint64_t dtype) { return dtype == SPLITZIP_BF16 ? 2 : 1; }
+
+int run(const Bound& b, PyObject* const* a, Py_ssize_t n_args) {
+  if (at::impl::torch_function_mode_enabled()) throw Refused();
+  Views views;
+  uint64_t w[kMost];
+  int n = 0;
+  Py_ssize_t i = 0;
+  int64_t word_size = 0, expected = 0;   // bytes of a word, of the tensor and by the dtype
+  uint64_t elems = 0;
+  const auto next = [&]() -> PyObject* {
+    if (i >= n_args) throw Refused();
+    return a[i++];
+  };
+  const auto word = [&](uint64_t v) {
+    if (n >= b.entry->n_words) throw Refused();
+    w[n++] = v;
+  };
+  const auto address = [](const void* p) { return static_cast<uint64_t>(reinterpret_cast<uintptr_t>(p)); };
+  for (const char* s = b.entry->spec; *s; ++s) {
+    PyObject* o = next();
+    switch (*s) {
+      case 'W': {
+        const at::Tensor& t = tensor(o);
+        if (!t.is_contiguous()) throw Refused();
+        word_size = t.element_size();
+        word(address(t.data_ptr()));
+        word(static_cast<uint64_t>(t.numel()));
+        break;
+      }
+      case 'Y': {
+        const at::Tensor& t = tensor(o);
+        if (!t.is_contiguous() || static_cast<uint64_t>(t.numel()) < elems) throw Refused();
+        word_size = t.element_size();
+        word(address(t.data_ptr()));
+        break;
+      }
+      case 'p':
+        word(o == Py_None ? 0 : address(tensor(o).data_ptr()));
+        break;
+      case 'P':
+        word(address(tensor(o).data_ptr()));
+        break;
+      case 'R': {
+        const at::Tensor& t = tensor(o);
+        PyObject* cap = next();
+        word(address(t.data_ptr()));
+        word(cap == Py_None ? static_cast<uint64_t>(t.numel() * t.element_size()) : integer(cap));
+        break;
+      }
+      case 'N':
+        elems = integer(o);
+        if (elems >> 63) throw Refused();
+        word(elems);
+        break;
+      case 'I':
+        word(integer(o));
+        break;
+      case 'D':
+        word(integer(o));
+        expected = bytes_per_word(w[n - 1]);
+        break;
+      case 'A':
+        word(address(views.of(o, nullptr, 1)));
+        break;
+      case 'G':
+        word(address(views.of(o, b.types.paged, sizeof(splitzip_paged))));
+        break;
+      case 'K':
+        word(address(views.of(o, b.types.codebook, sizeof(splitzip_codebook))));
+        break;
+      case 'C': {
+        const void* cb = views.of(o, b.types.codebook, sizeof(splitzip_codebook));
+        const uint32_t dtype = static_cast<const splitzip_codebook*>(cb)->dtype;
+        expected = bytes_per_word(dtype);
+        word(dtype);
+        word(address(cb));
+        break;
+      }
+      case 'V': {
+        const void* v = views.of(o, b.types.variant, sizeof(splitzip_variant));
+        expected = bytes_per_word(static_cast<const splitzip_variant*>(v)->dtype);
+        word(address(v));
+        break;
+      }
+      case 'S':
+        word(o == Py_None ? address(c10::hip::getCurrentHIPStream().stream()) : integer(o));
+        break;
+      default:
+        throw Refused();
+    }
+  }
+  if (i != n_args || n != b.entry->n_words || (word_size && word_size != expected)) throw Refused();
+  int rc;
+  Py_BEGIN_ALLOW_THREADS
+  rc = b.entry->call(b.fn, w);
+  Py_END_ALLOW_THREADS
+  return rc;
+}
+
+PyObject* fastcall(PyObject* self, PyObject* const* a, Py_ssize_t n) {
+  const Bound* b = static_cast<const Bound*>(PyCapsule_GetPointer(self, nullptr));
+  if (!b) return nullptr;
+  int rc = kNotTaken;
+  try {
+    rc = run(*b, a, n);
+  } catch (...) {   // Refused, or what torch throws for a tensor without memory of its own: the general way says what is wrong
+    PyErr_Clear();
+  }
+  return PyLong_FromLong(rc);
+}
+PyMethodDef kFastcall = {"fastcall", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(fastcall)), METH_FASTCALL, nullptr};
+
+void forget(PyObject* capsule) {
+  Bound* b = static_cast<Bound*>(PyCapsule_GetPointer(capsule, nullptr));
+  Py_DECREF(b->types.codebook);
+  Py_DECREF(b->types.variant);
+  Py_DECREF(b->types.paged);
+  delete b;
+}
+
+// bind(handle, codebook, variant, paged): the entry points of the library that ctypes holds by this handle, name ->
+// function, for the binding's structures of these types
+PyObject* bind(PyObject*, PyObject* args) {
+  PyObject* handle = nullptr;
+  Types types;
+  if (!PyArg_ParseTuple(args, "OOOO", &handle, &types.codebook, &types.variant, &types.paged)) return nullptr;
+  void* lib = PyLong_AsVoidPtr(handle);
+  if (!lib && PyErr_Occurred()) return nullptr;
+  PyObject* out = PyDict_New();
+  if (!out) return nullptr;
+  for (const Entry& e : kEntries) {
+    void* fn = dlsym(lib, e.name);
+    if (!fn) {
+      PyErr_Format(PyExc_ImportError, "libsplitzip.so has no %s", e.name);
+      Py_DECREF(out);
+      return nullptr;
+    }
+    Bound* b = new Bound{fn, &e, types};
+    PyObject* capsule = PyCapsule_New(b, nullptr, nullptr);
+    if (capsule) {
+      Py_INCREF(types.codebook);
+      Py_INCREF(types.variant);
+      Py_INCREF(types.paged);
+      PyCapsule_SetDestructor(capsule, forget);
+    } else {
+      delete b;
+    }
+    PyObject* f = capsule ? PyCFunction_NewEx(&kFastcall, capsule, nullptr) : nullptr;
+    Py_XDECREF(capsule);
+    const int failed = f ? PyDict_SetItemString(out, e.name, f) : -1;
+    Py_XDECREF(f);
+    if (failed) {
+      Py_DECREF(out);
+      return nullptr;
+    }
+  }
+  return out;
+}
+
+PyMethodDef kMethods[] = {{"bind", bind, METH_VARARGS, "bind(handle, codebook, variant, paged): {name: function} for a libsplitzip.so that is loaded"}, {nullptr, nullptr, 0, nullptr}};
+PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&kModule); }

@@ -1,0 +1,157 @@
+"""The binding's short way (lib().fast) against its general way: what it takes gives the same streams, words and records,
+what it does not take is left to the general way, errors included."""
+import numpy as np
+import pytest
+import torch
+
+import kv_synth
+import paper_2605_01708_amd as sz
+from paper_2605_01708_amd import binding
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+def _general(monkeypatch):
+    """every function of lib().fast answers that it has done nothing"""
+    L = sz.lib()
+    for name in vars(L.fast):
+        monkeypatch.setattr(L.fast, name, lambda *a: binding._NOT_TAKEN)
+
+
+def test_other_forms_are_not_taken():
+    cb = sz.codebook_from_dec(range(100, 116), sz.BF16)
+    x, out, rec = torch.zeros(64, dtype=torch.int16), torch.zeros(4096, dtype=torch.uint8), torch.zeros(3, dtype=torch.int64)
+    f = sz.lib().fast
+    assert f.splitzip_compress(x, cb.c, out, None, out, 1 << 24, rec, 0) == 1                     # host tensors
+    assert f.splitzip_compress(x.as_subclass(Sub), cb.c, out, None, out, 1 << 24, rec, 0) == 1    # another class
+    assert f.splitzip_compress(None, None, None) == 1 and f.splitzip_compress() == 1              # not enough of them
+    assert f.splitzip_decompress(out, 2.0, 64, cb.c, x, None, 0) == 1                             # not an integer
+    with pytest.raises(AttributeError):
+        sz.decompress(None, 4096, 64, cb, x, None, stream=torch.zeros(1))
+    with pytest.raises(ValueError):
+        sz.compress(x.view(torch.uint8), cb, out, type("W", (), {"buf": out, "nbytes": 4096}), rec)
+    with pytest.raises(ValueError):
+        sz.decompress(out, 4096, 65, cb, x)
+
+
+def test_every_function_has_its_library_function():
+    for name in vars(sz.lib().fast):
+        assert hasattr(sz.lib(), name)
+
+
+def test_codebooks_of_a_batch_are_all_looked_at():
+    """a bad codebook is refused wherever it stands among good ones"""
+    good = [sz.codebook_from_dec(range(100 + q, 116 + q), sz.BF16) for q in range(3)]
+    bad = sz.codebook_from_dec(range(100, 116), sz.BF16)
+    bad.c.member[100] = 0
+    x, out = torch.zeros(64, dtype=torch.int16), torch.zeros(8192, dtype=torch.uint8)
+    base = (out.data_ptr() + 15) & ~15
+    for at in range(6):
+        cbs = [good[(q * 7) % 3] for q in range(6)]
+        cbs[at] = bad
+        items = (binding._CItem * 6)()
+        ditems = (binding._CDItem * 6)()
+        for q, cb in enumerate(cbs):
+            items[q] = binding._CItem(base, 64, base, 4096, binding.C.pointer(cb.c))
+            ditems[q] = binding._CDItem(base, 4096, 64, base, binding.C.pointer(cb.c))
+        assert sz.lib().splitzip_compress_batch(items, 6, sz.BF16, base, 1 << 30, base, None) == -1
+        assert sz.lib().splitzip_decompress_batch(ditems, 6, sz.BF16, base, None) == -1
+    del x
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
+@pytest.mark.parametrize("form", ["plain", "capacity", "stream", "parameter", "subclass", "shaped", "mode"])
+def test_both_ways_give_the_same(dtype, form, monkeypatch):
+    gen = kv_synth.kv_bf16 if dtype == sz.BF16 else kv_synth.kv_e5m2
+    x = gen(70, 5)[:-11].contiguous()
+    cb = sz.calibrate(gen(64, 1), dtype)
+    v = sz.variant(dtype, 3, 8)
+    vcb = sz.variant_calibrate(gen(64, 1), v)
+    n = x.numel()
+    xd = x.cuda()
+    shaped = xd.view(1, n) if form == "shaped" else xd
+    if form == "subclass":
+        shaped = xd.as_subclass(Sub)
+    if form == "parameter":
+        shaped = torch.nn.Parameter(xd, requires_grad=False)
+    stream = torch.cuda.Stream() if form == "stream" else None
+    bound = sz.compress_bound(n, dtype)
+    taken = []
+
+    def all_calls():
+        torch.cuda.synchronize()
+        ws = sz.Workspace(n, dtype)
+        vws = torch.empty(sz.variant_workspace_bytes(n, v), dtype=torch.uint8, device="cuda")
+        outs = [torch.zeros(max(bound, sz.variant_compress_bound(n, v)) + 64, dtype=torch.uint8, device="cuda") for _ in range(5)]
+        recs = [sz.new_sizes() for _ in range(5)]
+        brec, drec = sz.new_sizes_array(2), sz.new_sizes()
+        ys = [torch.zeros_like(xd) for _ in range(4)]
+        d_cbs = sz.DeviceCodebooks(2, dtype)
+        cap = bound if form == "capacity" else None
+        torch.cuda.synchronize()
+        sz.compress(shaped, cb, outs[0], ws, recs[0], stream, cap)
+        sz.compress_noalloc(shaped, cb, outs[1], recs[1], stream, cap)
+        sz.variant_compress(shaped, v, vcb, outs[2], vws, recs[2], stream)
+        sz.CalibrateBatchDevice([xd, xd], d_cbs).launch(stream)
+        sz.CompressBatchDcb([xd, xd], d_cbs, outs[3:5]).launch(ws, brec, stream)
+        torch.cuda.synchronize()
+        sizes = [sz.read_sizes(r)[0] for r in recs[:3]] + [r[0] for r in sz.read_sizes_array(brec)]
+        sz.decompress(outs[0], sizes[0], n, cb, ys[0], drec, stream)
+        sz.decompress_own(outs[1], sizes[1], n, dtype, ys[1], None, stream)
+        sz.variant_decompress(outs[2], sizes[2], n, v, vcb, ys[2], None, stream)
+        sz.DecompressBatchOwn(outs[3:4], sizes[3:4], [n], dtype, ys[3:4]).launch(drec, stream)
+        torch.cuda.synchronize()
+        return [t.cpu() for t in outs + recs + [brec, d_cbs.buf, d_cbs.hists, drec[2:]] + ys] + sizes
+
+    L = sz.lib()
+    real = L.fast.splitzip_compress
+    monkeypatch.setattr(L.fast, "splitzip_compress", lambda *a: taken.append(real(*a)) or taken[-1])
+    if form == "mode":
+        class Watch(torch.overrides.TorchFunctionMode):
+            def __torch_function__(self, func, types, args=(), kwargs=None):
+                return func(*args, **(kwargs or {}))
+        with Watch():
+            fast = all_calls()
+    else:
+        fast = all_calls()
+    assert taken == [1 if form in ("subclass", "mode") else 0]
+    _general(monkeypatch)
+    general = all_calls()
+    for a, b in zip(fast, general):
+        assert torch.equal(a, b) if torch.is_tensor(a) else a == b
+    for y in fast[-9:-5]:
+        assert np.array_equal(kv_synth.to_numpy_words(y), kv_synth.to_numpy_words(x))
+
+
+@pytest.mark.gpu
+def test_refusals_are_those_of_the_general_way(monkeypatch):
+    x = kv_synth.kv_bf16(8, 0).cuda()
+    n = x.numel()
+    cb = sz.calibrate(kv_synth.kv_bf16(8, 1), sz.BF16)
+    ws = sz.Workspace(n, sz.BF16)
+    out, rec = torch.zeros(sz.compress_bound(n, sz.BF16), dtype=torch.uint8, device="cuda"), sz.new_sizes()
+    calls = [
+        lambda: sz.compress(x.view(-1)[::2], cb, out, ws, rec),                     # not contiguous
+        lambda: sz.compress(x.view(torch.uint8), cb, out, ws, rec),                 # another word size
+        lambda: sz.compress(x, cb, out, ws, rec, capacity=100),                     # too small
+        lambda: sz.compress(x.view(-1)[1:], cb, out, ws, rec),                      # not aligned
+        lambda: sz.decompress(out, sz.fixed_bytes(n, sz.BF16), n, cb, x.view(-1)[:-1], rec),   # too short
+        lambda: sz.decompress(out, 10, n, cb, x, rec),
+        lambda: sz.decompress(out, 4096, -1, cb, x, rec),
+        lambda: sz.compress(x, cb, out, ws, None),
+    ]
+
+    def answers():
+        got = []
+        for call in calls:
+            with pytest.raises(Exception) as e:
+                call()
+            got.append((type(e.value), getattr(e.value, "code", None)))
+        return got
+
+    fast = answers()
+    _general(monkeypatch)
+    assert fast == answers()
