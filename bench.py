@@ -246,7 +246,7 @@ class Workload:
                 "compress_frac_of_peak": round(self.alg_bytes / (mean(ms_c) * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
                 "decompress_frac_of_peak": round(self.alg_bytes / (mean(ms_d) * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
                 "calls_per_pass": launches,
-                "kernels": [compress_kernels(self.dtype, self.n, self.nt), f"decompress_batch_kernel<D{f}>"],
+                "kernels": [compress_kernels(self.dtype, self.n, self.nt), f"decompress_kernel<D{f}, .., 64>"],
             },
             "per_tensor_calls": {
                 "compress_GBps": round(self.raw_bytes / c1_us * 1e-3, 1), "compress_us": round(c1_us, 2),
@@ -254,7 +254,7 @@ class Workload:
                 "decompress_GBps": round(self.raw_bytes / d1_us * 1e-3, 1), "decompress_us": round(d1_us, 2),
                 "decompress_frac_of_peak": round(alg1 / d1_us * 1e-3 / HBM_PEAK_GBPS, 4),
                 "algorithmic_bytes_per_call": int(alg1),
-                "kernels": [compress_kernels(self.dtype, self.n), f"decompress_kernel<D{f}>"],
+                "kernels": [compress_kernels(self.dtype, self.n), f"decompress_kernel<D{f}, .., 1>"],
                 "how": "one call per tensor, back to back on one stream; HIP events around the pass",
             },
         }
@@ -394,7 +394,7 @@ def main():
             "launch_us": round(mean(ms_c) * 1e3 / launches, 2), "algorithmic_bytes_per_launch": int(alg_bytes / launches),
         },
         "roofline_decompress": {
-            "kernel": f"decompress_batch_kernel<D{fmt}>",
+            "kernel": f"decompress_kernel<D{fmt}, .., 64>",
             "bound": "hbm", "achieved": round(d_ach, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
             "frac": round(d_ach / HBM_PEAK_GBPS, 4), "traffic": None, "traffic_source": None,
             "launch_us": round(mean(ms_d) * 1e3 / launches, 2), "algorithmic_bytes_per_launch": int(alg_bytes / launches),
@@ -403,7 +403,7 @@ def main():
             "what": "splitzip_compress / splitzip_decompress, one tensor per call, back to back on one stream",
             "compress": {"kernel": compress_kernels(dtype, W.n), "bound": "hbm", "achieved": round(alg1 / c1_us * 1e-3, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                          "frac": round(alg1 / c1_us * 1e-3 / HBM_PEAK_GBPS, 4), "launch_us": round(c1_us, 2), "algorithmic_bytes_per_launch": int(alg1)},
-            "decompress": {"kernel": f"decompress_kernel<D{fmt}>", "bound": "hbm", "achieved": round(alg1 / d1_us * 1e-3, 1), "peak": HBM_PEAK_GBPS,
+            "decompress": {"kernel": f"decompress_kernel<D{fmt}, .., 1>", "bound": "hbm", "achieved": round(alg1 / d1_us * 1e-3, 1), "peak": HBM_PEAK_GBPS,
                            "unit": "GB/s", "frac": round(alg1 / d1_us * 1e-3 / HBM_PEAK_GBPS, 4), "launch_us": round(d1_us, 2),
                            "algorithmic_bytes_per_launch": int(alg1)},
         },

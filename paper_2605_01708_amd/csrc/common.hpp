@@ -6,6 +6,7 @@
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 
 constexpr uint32_t kChunk = 1024;
 constexpr uint32_t kHalf = 512;
@@ -69,6 +70,13 @@ __host__ __device__ inline Words item_words(const Words& paging, const void* bas
 // device helpers
 // ---------------------------------------------------------------------------
 
+// The same address, known to lie in global memory.  The compiler sees that by itself for a pointer that it reads from the
+// kernel's arguments, but not for one that has been through a register (args_arrived) or that is chosen between the
+// arguments and memory: accesses through those are flat ones, which count as LDS accesses too -- the wait in front of an
+// LDS-only barrier is then one for every load on its way -- and take no scalar base.
+template <typename T>
+__device__ inline T* as_global(T* p) { return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uintptr_t>(p); }
+
 // pool page of the chunk with index `chunk` (only for a paged tensor)
 __device__ inline uint32_t page_of_chunk(const Words& w, uint64_t chunk) {
   const uint32_t page = w.table[chunk >> (w.page_shift - 10)];
@@ -103,6 +111,19 @@ __device__ inline T ld_stream(const T* p) { return __builtin_nontemporal_load(p)
 template <typename T>
 __device__ inline void st_stream(T* p, T v) { __builtin_nontemporal_store(v, p); }
 
+// Consecutive bytes as a buffer (base and length wave-uniform): an access is base + a 32-bit offset, loads beyond the end
+// give zeros and fetch nothing -- so a load need not stand behind a condition.
+constexpr int kStream = 2;   // cache bits of an access: non-temporal
+__device__ inline __amdgpu_buffer_rsrc_t run_of(const uint8_t* base, uint32_t bytes) {
+  // (into a scalar register by hand: a clamp of two scalars is a vector instruction, and a description with a word in a vector
+  // register makes a loop around every access)
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+}
+__device__ inline u32x2 ld_run8(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b64(run, off, 0, kStream); }
+__device__ inline uint32_t ld_run4(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b32(run, off, 0, kStream); }
+__device__ inline uint16_t ld_run2(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b16(run, off, 0, 0); }
+__device__ inline uint8_t ld_run1(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b8(run, off, 0, 0); }
+
 // v_perm_b32: result byte i = byte sel[i] of the 8-byte pool {hi:4..7, lo:0..3}; 0x0c gives 0x00.
 __device__ inline uint32_t byte_perm(uint32_t hi, uint32_t lo, uint32_t sel) {
   return __builtin_amdgcn_perm(hi, lo, sel);
@@ -118,6 +139,11 @@ __device__ inline uint32_t wave_incl_scan(uint32_t v) {
   v += __builtin_amdgcn_update_dpp(0u, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
   v += __builtin_amdgcn_update_dpp(0u, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
   return v;
+}
+
+// the value of the lane below; lane 0 gets `first`
+__device__ inline uint32_t lane_before(uint32_t v, uint32_t first) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138, 0xf, 0xf, false);   // wave_shr:1
 }
 
 __device__ inline uint32_t wave_last(uint32_t v) { return __builtin_amdgcn_readlane(v, 63); }
@@ -144,10 +170,11 @@ __device__ inline u32x4 load_dec16(const uint8_t* dec) {
   asm volatile("s_load_dwordx4 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(sp) : "memory");
   return v;
 }
-// entry k (0..15, may differ from lane to lane) of the 16 in v
+// entry k (0..15, may differ from lane to lane) of the 16 in v: two byte permutes, of the lower and of the upper eight
 __device__ inline uint32_t dec16_at(const u32x4& v, uint32_t k) {
-  const uint32_t d = k < 8 ? (k < 4 ? v.x : v.y) : (k < 12 ? v.z : v.w);
-  return (d >> ((k & 3u) * 8u)) & 0xffu;
+  const uint32_t sel = (k & 7u) | 0x0c0c0c00u;   // 0x0c: a zero byte
+  const uint32_t low = byte_perm(v.y, v.x, sel), high = byte_perm(v.w, v.z, sel);
+  return k < 8 ? low : high;
 }
 
 // Exclusive prefix sum over the lanes of small counts c that are zero in most lanes (escapes per lane), and their

@@ -1,4 +1,4 @@
-// SplitZip for MI355X: the decompress kernels (dense decode of both formats, scatter correction in registers, single-tensor and batch kernels).
+// SplitZip for MI355X: the decompress kernel (dense decode of both formats, scatter correction in LDS; one stream or a batch).
 // Part of the single translation unit splitzip.hip (included inside its anonymous namespace).
 #ifndef SPLITZIP_DECOMPRESS_HPP
 #define SPLITZIP_DECOMPRESS_HPP
@@ -7,37 +7,61 @@
 // decompress
 // ---------------------------------------------------------------------------
 
-struct DecompressArgs {
+// The arguments of a launch: what all its streams share, then the streams (N: room for kBatchMax of them, or for the one
+// of a single call).  blockIdx.y picks the stream, blockIdx.x the tile.  What a wave needs of the layout before its first
+// load comes ready: with a tile per workgroup, a scalar instruction of the beginning is one per wave.
+struct DItem {
   const uint8_t* comp;
-  Words w;                 // where the decoded words go
-  uint64_t n, comp_bytes;
-  splitzip_sizes* sizes;   // nullable
-  uint64_t off_tab, off_sm, off_code, off_pos, sm_bytes, code_bytes;
-  uint32_t n_chunks, n_tiles, cpw, dtype;
-  uint32_t reg_patch_max;  // chunks with at most this many escapes are corrected in registers, the others in an LDS tile
-  const uint8_t* d_dec;    // nullable: the 16 decode entries in device memory, used instead of dec
-  uint8_t dec[16];
+  uint8_t* out;
+  uint32_t n;
+  uint32_t most;           // escapes that the stream has room for, n at most
+  uint32_t code256, pos256;   // where the code plane and the positions start, in units of 256 bytes
+  uint8_t dec[16];         // its codebook
 };
+struct DShared {
+  splitzip_sizes* sizes;   // nullable; one record, status bits sticky
+  const splitzip_codebook* d_cbs;   // nullable: codebooks in device memory, one per stream, used instead of dec
+  Words paging;            // table and page geometry shared by all tensors (table null: contiguous tensors); base unused
+  uint32_t by_xcd;         // the workgroups take their tiles in xcd_order
+  uint32_t own_dec;        // 1: every stream is decoded with the 16 decode entries of its own header
+  uint32_t reserved[2];
+};
+template <uint32_t N>
+struct alignas(N == 1 ? 16 : 64) DArgs {
+  DShared shared;
+  DItem item[N];
+};
+static_assert(sizeof(DShared) == 64 && sizeof(DItem) == 48, "whole 16-byte words for the copies of decompress_kernel");
 
-__device__ inline void flag_bad(const DecompressArgs& a) {
-  if (a.sizes) atomicOr(&a.sizes->status, SPLITZIP_STATUS_BAD_STREAM);
+// a stream of comp_bytes bytes (at least what it takes without escapes) as the kernel is told of it; dec left alone
+inline void describe_stream(const void* comp, uint64_t comp_bytes, void* out, uint64_t n, int dtype, DItem* it) {
+  const Layout L = make_layout(n, dtype);
+  it->comp = static_cast<const uint8_t*>(comp);
+  it->out = static_cast<uint8_t*>(out);
+  it->n = (uint32_t)n;
+  it->code256 = (uint32_t)(L.off_code >> 8);
+  it->pos256 = (uint32_t)(L.off_pos >> 8);
+  // the largest m with off_pos + a256(2 m) + m <= comp_bytes: 128 records take 384 bytes, in all or in part
+  const uint64_t room = comp_bytes - L.off_pos, whole = room / 384, rest = room - 384 * whole;
+  const uint64_t m = 128 * whole + (rest > 256 ? rest - 256 : 0);
+  it->most = (uint32_t)(m < n ? m : n);
 }
 
-// header checks: one thread of workgroup 0
-// dec: the 16 decode entries the caller's codebook has, four to a word
-__device__ void decompress_check_header(const DecompressArgs& a, const u32x4& dec, uint32_t M) {
-  const uint32_t* h = reinterpret_cast<const uint32_t*>(a.comp);
-  const uint64_t n = h[4] | ((uint64_t)h[5] << 32), m = h[6] | ((uint64_t)h[7] << 32);
-  const uint64_t total = h[8] | ((uint64_t)h[9] << 32);
-  bool ok = h[0] == 0x31505a53u && h[1] == (1u | (a.dtype << 16) | (4u << 24)) && h[2] == kChunk &&
-            h[3] == 0 && n == a.n && m == M && total == a.off_pos + a256(2 * m) + m &&
-            total <= a.comp_bytes && h[14] == 0 && h[15] == 0;
-  ok = ok && h[10] == dec.x && h[11] == dec.y && h[12] == dec.z && h[13] == dec.w;   // the 16 entries, four to a word
-  if (!ok) flag_bad(a);
-  if (a.sizes) {
-    a.sizes->total_bytes = total;
-    a.sizes->n_escapes = m;
+// header checks, by one wave of the stream's first tile: lane i < 16 holds word i of the header in hw
+// dec: the 16 decode entries the caller's codebook has, four to a word; M: as the table states it
+__device__ inline bool decompress_check_header(const DItem& it, uint32_t dtype, uint32_t hw, const u32x4& dec, uint32_t M, splitzip_sizes* sizes, int lane) {
+  uint32_t h[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) h[i] = __builtin_amdgcn_readlane(hw, i);
+  const uint64_t m = h[6] | ((uint64_t)h[7] << 32), total = h[8] | ((uint64_t)h[9] << 32);
+  if (sizes && lane == 0) {
+    sizes->total_bytes = total;
+    sizes->n_escapes = m;
   }
+  // (that total lies inside the stream follows from M <= most)
+  return h[0] == 0x31505a53u && h[1] == (1u | (dtype << 16) | (4u << 24)) && h[2] == kChunk && h[3] == 0 && h[4] == it.n && h[5] == 0 &&
+         m == M && M <= it.most && total == ((uint64_t)it.pos256 << 8) + a256(2 * m) + m && h[14] == 0 && h[15] == 0 &&
+         h[10] == dec.x && h[11] == dec.y && h[12] == dec.z && h[13] == dec.w;   // the 16 entries, four to a word
 }
 
 // BF16: the plane words of one chunk as a wave holds them, two half-chunks of 8 elements per lane each
@@ -45,20 +69,18 @@ struct PlanesBf16 {
   u32x2 sm[2];
   uint32_t cd[2];
 };
-template <bool FULL>
-__device__ inline void load_planes_bf16(const DecompressArgs& a, uint64_t cbase, int lane, PlanesBf16& in) {
+// The planes of a wave's j-th chunk, out of the runs that hold those of all its chunks (a load that reaches beyond gives
+// zeros, so no load stands behind a condition, and the compiler knows how many are on their way).
+__device__ inline void load_planes(__amdgpu_buffer_rsrc_t sm, __amdgpu_buffer_rsrc_t cd, int j, int lane, PlanesBf16& in) {
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const uint64_t g0 = cbase + h * kHalf + lane * 8;
-    in.sm[h] = u32x2{0u, 0u};
-    in.cd[h] = 0;
-    if (FULL || g0 < a256(a.sm_bytes)) in.sm[h] = ld_stream(reinterpret_cast<const u32x2*>(a.comp + a.off_sm + g0));
-    if (FULL || (g0 >> 1) < a256(a.code_bytes))
-      in.cd[h] = ld_stream(reinterpret_cast<const uint32_t*>(a.comp + a.off_code + (g0 >> 1)));
+    in.sm[h] = ld_run8(sm, 8u * (uint32_t)lane + (uint32_t)(j * kChunk + h * kHalf));
+    in.cd[h] = ld_run4(cd, 4u * (uint32_t)lane + (uint32_t)(j * kChunk + h * kHalf) / 2);
   }
 }
 // dense decode into registers: o[4 h + d] holds elements 2 d and 2 d + 1 of the lane's group in half h
-__device__ inline void decode_chunk_bf16(const PlanesBf16& in, const uint32_t* tbl, uint32_t (&o)[8]) {
+__device__ inline u32x8 decode_chunk_bf16(const PlanesBf16& in, const uint32_t* tbl) {
+  u32x8 o;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const uint32_t smw[2] = {in.sm[h].x, in.sm[h].y};
@@ -71,26 +93,7 @@ __device__ inline void decode_chunk_bf16(const PlanesBf16& in, const uint32_t* t
       o[4 * h + b] = (p & 0x807f807fu) | tbl[cb];
     }
   }
-}
-
-template <bool FULL>
-__device__ inline void store_chunk_bf16(const DecompressArgs& a, uint8_t* cptr, uint64_t cbase, int lane, const uint32_t (&o)[8]) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const uint64_t g0 = cbase + h * kHalf + lane * 8;
-    uint32_t nvalid = 8;
-    if (!FULL) nvalid = g0 >= a.n ? 0u : (uint32_t)(a.n - g0 < 8 ? a.n - g0 : 8);
-    if (FULL || nvalid == 8) {
-      st_stream(reinterpret_cast<u32x4*>(cptr) + (uint32_t)(h * 64 + lane), u32x4{o[4 * h], o[4 * h + 1], o[4 * h + 2], o[4 * h + 3]});
-    } else {
-      uint16_t* q = reinterpret_cast<uint16_t*>(cptr + 2 * (g0 - cbase));
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        if ((uint32_t)(2 * d) < nvalid) q[2 * d] = (uint16_t)o[4 * h + d];
-        if ((uint32_t)(2 * d + 1) < nvalid) q[2 * d + 1] = (uint16_t)(o[4 * h + d] >> 16);
-      }
-    }
-  }
+  return o;
 }
 
 // E5M2: the plane words of one chunk as a wave holds them, 16 elements per lane.  Lanes 2p and 2p+1 share 12
@@ -99,20 +102,13 @@ __device__ inline void store_chunk_bf16(const DecompressArgs& a, uint8_t* cptr, 
 struct PlanesE5m2 {
   u32x2 sm, cd;
 };
-template <bool FULL>
-__device__ inline void load_planes_e5m2(const DecompressArgs& a, uint64_t cbase, int lane, PlanesE5m2& in) {
-  const uint64_t g0 = cbase + lane * 16;
-  const uint64_t off = (cbase / 8) * 3 + (uint32_t)(lane >> 1) * 12 + ((lane & 1) ? 4u : 0u);
-  const uint8_t* src = a.comp + a.off_sm + off;
-  const uint64_t sm_end = a256(a.sm_bytes);   // a multiple of 256; off is a multiple of 4
-  in.sm = u32x2{0u, 0u};
-  in.cd = u32x2{0u, 0u};
-  if (FULL || off + 8 <= sm_end) in.sm = ld_stream(reinterpret_cast<const u32x2*>(src));
-  else if (off + 4 <= sm_end) in.sm.x = ld_stream(reinterpret_cast<const uint32_t*>(src));
-  if (FULL || (g0 >> 1) < a256(a.code_bytes)) in.cd = ld_stream(reinterpret_cast<const u32x2*>(a.comp + a.off_code + (g0 >> 1)));
+__device__ inline void load_planes(__amdgpu_buffer_rsrc_t sm, __amdgpu_buffer_rsrc_t cd, int j, int lane, PlanesE5m2& in) {
+  in.sm = ld_run8(sm, (uint32_t)(lane >> 1) * 12u + (uint32_t)(lane & 1) * 4u + (uint32_t)(j * 384));
+  in.cd = ld_run8(cd, 8u * (uint32_t)lane + (uint32_t)(j * kHalf));
 }
 // dense decode into registers: o[d] holds elements 4 d .. 4 d + 3
-__device__ inline void decode_chunk_e5m2(const PlanesE5m2& in, const uint32_t* tbl, int lane, uint32_t (&o)[4]) {
+__device__ inline u32x4 decode_chunk_e5m2(const PlanesE5m2& in, const uint32_t* tbl, int lane) {
+  u32x4 o;
   // the lane's 48 plane bits: the even lane's start at its first byte, the odd lane's two bytes further on
   const uint32_t lo = (lane & 1) ? (in.sm.x >> 16) | (in.sm.y << 16) : in.sm.x;
   const uint32_t hi = (lane & 1) ? in.sm.y >> 16 : in.sm.y & 0xffffu;
@@ -124,321 +120,246 @@ __device__ inline void decode_chunk_e5m2(const PlanesE5m2& in, const uint32_t* t
     const uint32_t c01 = (cdw[d >> 1] >> (16 * (d & 1))) & 0xffu, c23 = (cdw[d >> 1] >> (16 * (d & 1) + 8)) & 0xffu;
     o[d] = unpack3_e5m2(r[d]) | tbl[c01] | (tbl[c23] << 16);
   }
+  return o;
 }
 
-template <bool FULL>
-__device__ inline void store_chunk_e5m2(const DecompressArgs& a, uint8_t* cptr, uint64_t cbase, int lane, const uint32_t (&o)[4]) {
-  const uint64_t g0 = cbase + lane * 16;
-  uint32_t nvalid = 16;
-  if (!FULL) nvalid = g0 >= a.n ? 0u : (uint32_t)(a.n - g0 < 16 ? a.n - g0 : 16);
-  if (FULL || nvalid == 16) {
-    st_stream(reinterpret_cast<u32x4*>(cptr) + (uint32_t)lane, u32x4{o[0], o[1], o[2], o[3]});
-  } else {
-    uint8_t* q = cptr + (g0 - cbase);
-#pragma unroll
-    for (int j = 0; j < 16; ++j)
-      if ((uint32_t)j < nvalid) q[j] = (uint8_t)(o[j >> 2] >> (8 * (j & 3)));
-  }
-}
-
-// in-register scatter correction: dword r of the owning lane gets (o & ~mask) | bits; r is
-// wave-uniform, so the choice of the register is a scalar branch
-template <int R>
-__device__ inline void patch_regs(uint32_t (&o)[R], uint32_t r, bool mine, uint32_t mask, uint32_t bits) {
-#pragma unroll
-  for (int q = 0; q < R; ++q)
-    if (r == (uint32_t)q && mine) o[q] = (o[q] & ~mask) | bits;
+// one dword of an LDS tile gets bits in the places of mask
+__device__ inline void patch_dword(uint32_t* d, uint32_t mask, uint32_t bits) {
+  __hip_atomic_fetch_and(d, ~mask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  __hip_atomic_fetch_or(d, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 // the two formats as seen by the decompress kernel
 struct DBf16 {
+  static constexpr int DT = SPLITZIP_BF16;
   static constexpr int ES = 2;   // bytes per word
-  static constexpr int kPlanesAhead = 2;   // chunks whose planes are on their way while one is decoded
-  struct Out { uint32_t o[8]; };
+  static constexpr uint32_t kSmBytes = kChunk;   // bytes of a chunk's sign+mantissa plane
+  // bytes of it, CPW chunks at most, that a section of so many times 256 holds from chunk c on
+  template <int CPW>
+  __device__ static inline uint32_t sm_left(uint32_t section256, uint32_t c) {
+    const int32_t left = (int32_t)section256 - (int32_t)(4 * c);
+    return (uint32_t)(left < 0 ? 0 : left > 4 * CPW ? 4 * CPW : left) << 8;
+  }
+  typedef PlanesBf16 In;
+  typedef u32x8 Out;
   // table entry for a code byte: both exponents in place for one dword of output
   __device__ static inline uint32_t table(int cb, const u32x4& dec) { return (dec16_at(dec, cb & 15) << 7) | (dec16_at(dec, cb >> 4) << 23); }
-  __device__ static inline uint32_t table(int cb, const uint8_t* dec) { return ((uint32_t)dec[cb & 15] << 7) | ((uint32_t)dec[cb >> 4] << 23); }
-  // The decode table is built from entries held in scalar registers: it is ready, and the barrier behind it
-  // passed, while the table entries and planes are still on their way (a 64 MiB tensor: 23.1 us against 23.8 us
-  // with the entries read by vector loads, which return behind everything asked for before them).
-  static constexpr bool kScalarDec = true;
-  __device__ static inline bool full(const DecompressArgs& a, uint64_t cbase) { return cbase + kChunk <= a.n; }
-  typedef PlanesBf16 In;
-  template <bool FULL>
-  __device__ static inline void load(const DecompressArgs& a, uint64_t cbase, int lane, In& in) { load_planes_bf16<FULL>(a, cbase, lane, in); }
-  __device__ static inline void decode(const In& in, const uint32_t* tbl, int lane, Out& r) { decode_chunk_bf16(in, tbl, r.o); }
-  __device__ static inline void arrived(In& in) {
-    asm volatile("" : "+v"(in.sm[0].x), "+v"(in.sm[0].y), "+v"(in.sm[1].x), "+v"(in.sm[1].y), "+v"(in.cd[0]), "+v"(in.cd[1]));
+  __device__ static inline Out decode(const In& in, const uint32_t* tbl, int) { return decode_chunk_bf16(in, tbl); }
+  __device__ static inline void store(uint8_t* cptr, int lane, Out o) {
+    st_stream(reinterpret_cast<u32x4*>(cptr) + (uint32_t)lane, u32x4{o[0], o[1], o[2], o[3]});
+    st_stream(reinterpret_cast<u32x4*>(cptr) + (uint32_t)(64 + lane), u32x4{o[4], o[5], o[6], o[7]});
   }
-  template <bool FULL>
-  __device__ static inline void store(const DecompressArgs& a, uint8_t* cptr, uint64_t cbase, int lane, const Out& r) { store_chunk_bf16<FULL>(a, cptr, cbase, lane, r.o); }
-  // the scatter correction of the element at chunk position pos (wave-uniform), in the registers of the lane that holds it
-  __device__ static inline bool patch_reg(Out& r, int lane, uint32_t pos, uint32_t val) {
-    const uint32_t q = pos & 511u, e = q & 7u, sh = 16u * (e & 1u);
-    patch_regs<8>(r.o, 4u * (pos >> 9) + (e >> 1), (uint32_t)lane == (q >> 3), 0x7f80u << sh, val << (7u + sh));
-    return true;
-  }
-  // The chunk as an LDS tile in element order (2 KB), for chunks with many escapes: registers -> tile, the
+  // The chunk as an LDS tile in element order (2 KB), for chunks with escapes: registers -> tile, the
   // correction of one element by one lane, tile -> registers.
   static constexpr uint32_t kTileDwords = 512;
-  __device__ static inline void to_tile(const Out& r, uint32_t* tile, int lane) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) reinterpret_cast<u32x4*>(tile)[h * 64 + lane] = u32x4{r.o[4 * h], r.o[4 * h + 1], r.o[4 * h + 2], r.o[4 * h + 3]};
+  __device__ static inline void to_tile(Out o, uint32_t* tile, int lane) {
+    reinterpret_cast<u32x4*>(tile)[lane] = u32x4{o[0], o[1], o[2], o[3]};
+    reinterpret_cast<u32x4*>(tile)[64 + lane] = u32x4{o[4], o[5], o[6], o[7]};
   }
-  __device__ static inline void from_tile(Out& r, const uint32_t* tile, int lane) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const u32x4 v = reinterpret_cast<const u32x4*>(tile)[h * 64 + lane];
-      r.o[4 * h] = v.x; r.o[4 * h + 1] = v.y; r.o[4 * h + 2] = v.z; r.o[4 * h + 3] = v.w;
-    }
+  __device__ static inline Out from_tile(const uint32_t* tile, int lane) {
+    const u32x4 a = reinterpret_cast<const u32x4*>(tile)[lane], b = reinterpret_cast<const u32x4*>(tile)[64 + lane];
+    return Out{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
   }
   __device__ static inline bool patch_tile(uint32_t* tile, uint32_t pos, uint32_t val) {
-    uint16_t* t = reinterpret_cast<uint16_t*>(tile) + pos;
-    *t = (uint16_t)((*t & ~0x7f80u) | (val << 7));
+    const uint32_t sh = 16 * (pos & 1u);
+    patch_dword(tile + (pos >> 1), 0x7f80u << sh, val << (7 + sh));
     return true;
   }
 };
 struct DE5m2 {
+  static constexpr int DT = SPLITZIP_FP8_E5M2;
   static constexpr int ES = 1;
-  static constexpr int kPlanesAhead = 1;
-  struct Out { uint32_t o[4]; };
-  __device__ static inline uint32_t table(int cb, const u32x4& dec) { return (dec16_at(dec, cb & 15) << 2) | (dec16_at(dec, cb >> 4) << 10); }
-  __device__ static inline uint32_t table(int cb, const uint8_t* dec) { return ((uint32_t)dec[cb & 15] << 2) | ((uint32_t)dec[cb >> 4] << 10); }
-  // E5M2 reads the entries with vector loads (a 32 MiB tensor: 14.7 us; 16.1 us with the entries in scalar registers)
-  static constexpr bool kScalarDec = false;
-  __device__ static inline bool full(const DecompressArgs& a, uint64_t cbase) { return cbase + kChunk < a.n; }
+  static constexpr uint32_t kSmBytes = 3 * kChunk / 8;
+  template <int CPW>
+  __device__ static inline uint32_t sm_left(uint32_t section256, uint32_t c) {
+    const int32_t left = (int32_t)(section256 << 8) - (int32_t)(384 * c);   // below 2^31: three bits per element
+    // a lane's eight bytes may reach over the section's end: into the code plane behind it, not out of the run
+    return (uint32_t)(left <= 0 ? 0 : left + 8 > 384 * CPW ? 384 * CPW : left + 8);
+  }
   typedef PlanesE5m2 In;
-  template <bool FULL>
-  __device__ static inline void load(const DecompressArgs& a, uint64_t cbase, int lane, In& in) { load_planes_e5m2<FULL>(a, cbase, lane, in); }
-  __device__ static inline void decode(const In& in, const uint32_t* tbl, int lane, Out& r) { decode_chunk_e5m2(in, tbl, lane, r.o); }
-  __device__ static inline void arrived(In& in) { asm volatile("" : "+v"(in.sm.x), "+v"(in.sm.y), "+v"(in.cd.x), "+v"(in.cd.y)); }
-  template <bool FULL>
-  __device__ static inline void store(const DecompressArgs& a, uint8_t* cptr, uint64_t cbase, int lane, const Out& r) { store_chunk_e5m2<FULL>(a, cptr, cbase, lane, r.o); }
-  __device__ static inline bool patch_reg(Out& r, int lane, uint32_t pos, uint32_t val) {
-    if (val > 31u) return false;
-    const uint32_t e = pos & 15u, sh = 8u * (e & 3u);
-    patch_regs<4>(r.o, e >> 2, (uint32_t)lane == (pos >> 4), 0x7cu << sh, val << (2u + sh));
-    return true;
-  }
+  typedef u32x4 Out;
+  __device__ static inline uint32_t table(int cb, const u32x4& dec) { return (dec16_at(dec, cb & 15) << 2) | (dec16_at(dec, cb >> 4) << 10); }
+  __device__ static inline Out decode(const In& in, const uint32_t* tbl, int lane) { return decode_chunk_e5m2(in, tbl, lane); }
+  __device__ static inline void store(uint8_t* cptr, int lane, Out o) { st_stream(reinterpret_cast<u32x4*>(cptr) + (uint32_t)lane, o); }
   static constexpr uint32_t kTileDwords = 256;
-  __device__ static inline void to_tile(const Out& r, uint32_t* tile, int lane) {
-    reinterpret_cast<u32x4*>(tile)[lane] = u32x4{r.o[0], r.o[1], r.o[2], r.o[3]};
-  }
-  __device__ static inline void from_tile(Out& r, const uint32_t* tile, int lane) {
-    const u32x4 v = reinterpret_cast<const u32x4*>(tile)[lane];
-    r.o[0] = v.x; r.o[1] = v.y; r.o[2] = v.z; r.o[3] = v.w;
-  }
+  __device__ static inline void to_tile(Out o, uint32_t* tile, int lane) { reinterpret_cast<u32x4*>(tile)[lane] = o; }
+  __device__ static inline Out from_tile(const uint32_t* tile, int lane) { return reinterpret_cast<const u32x4*>(tile)[lane]; }
   __device__ static inline bool patch_tile(uint32_t* tile, uint32_t pos, uint32_t val) {
     if (val > 31u) return false;
-    uint8_t* t = reinterpret_cast<uint8_t*>(tile) + pos;
-    *t = (uint8_t)((*t & ~0x7cu) | (val << 2));
+    const uint32_t sh = 8 * (pos & 3u);
+    patch_dword(tile + (pos >> 2), 0x7cu << sh, val << (2 + sh));
     return true;
   }
 };
 
-constexpr uint32_t kRegPatchDefault = 4;   // escapes of a chunk that are still applied in registers
+// A wave's LDS accesses are carried out in program order; this keeps the compiler from reordering accesses it takes for
+// unrelated because they go through different types.
+__device__ inline void lds_in_order() { asm volatile("" ::: "memory"); }
 
-// a wave's LDS accesses are carried out in program order; this keeps the compiler from reordering accesses it
-// takes for unrelated because they go through different types
-__device__ inline void lds_settle() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
-// one workgroup: tile `tile` of the tensor described by a (4 waves x cpw chunks); lds_chunk: kTileDwords per wave
-template <typename F>
-__device__ inline void decompress_tile(const DecompressArgs& a, const u32x4& dec, const uint8_t* dec_ptr, uint32_t tile, uint32_t* tbl,
-                                       uint32_t* lds_chunk) {
+// One workgroup: a tile of 4 waves x CPW chunks of one stream.
+// What bounds it: long launches the memory (64 BF16 tensors of 64 MiB 1172 us, 6.4 TB/s; 64 E5M2 tensors of 32 MiB 619 us, 6.5
+// TB/s); short ones the trips to memory that a wave makes one after the other, and the instructions of its beginning.  Until
+// a wave asked for everything at once -- it waited for M before its first plane, and for memory once per chunk -- they took
+// 1196 and 670 us, one tensor of 64 MiB 23.2 (21.0 now), 64 of 2 MiB 42.7 (39.0), 100 chunks 3.4 (2.2).
+// A wave asks for everything it can name before it waits for anything: the slice of the offset table, then the planes of
+// its CPW chunks; the decode table is built meanwhile.  The table entries arrive first, and the escape records of all those
+// chunks, which follow one another in the stream, are one run: two loads of it travel while the planes do.
+template <typename F, int CPW, uint32_t N>
+__global__ __launch_bounds__(kThreads) void decompress_kernel(const DArgs<N> args) {
+  __shared__ uint32_t tbl[256];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_chunk[kWaves * F::kTileDwords];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t* tab = reinterpret_cast<const uint32_t*>(a.comp + a.off_tab);
-  const uint32_t cpw = a.cpw;
-  const uint32_t wave_chunk0 = (tile * kWaves + wave) * cpw;
-  // first of all the loads everything else waits for: this wave's slice of the offset table (lane c
-  // <-> its chunk c, one entry more for the end) and M as the table states it
-  const uint32_t my_tab = (uint32_t)lane <= cpw && wave_chunk0 + lane <= a.n_chunks ? tab[wave_chunk0 + lane] : 0u;
-  uint32_t M = tab[a.n_chunks];
-  // paged tensor: the pool pages of the wave's chunks, lane c <-> its chunk c
-  uint32_t my_pages = 0;
-  if (a.w.table && (uint32_t)lane < cpw && wave_chunk0 + lane < a.n_chunks) my_pages = page_of_chunk(a.w, wave_chunk0 + lane);
-
-  // The wave's chunks; only the tensor's last chunk can be ragged, and it is the last of its wave.
-  const uint32_t mine = wave_chunk0 < a.n_chunks ? (a.n_chunks - wave_chunk0 < cpw ? a.n_chunks - wave_chunk0 : cpw) : 0u;
-  const bool last_ragged = mine > 0 && !F::full(a, (uint64_t)(wave_chunk0 + mine - 1) * kChunk);
-  const uint32_t fast = mine - (last_ragged ? 1u : 0u);
-  // everything chunk c needs from memory: its planes and the first 64 of its records, one lane each
-  struct Fetched {
-    typename F::In in;
-    uint32_t pos, val;
-  };
-  Fetched cur, nxt;
-  // The planes of the wave's first chunk depend on nothing that is loaded: they are asked for right behind the
-  // table entries, and the decode table is built while both are on their way (the barrier below is for LDS only).
-  if (fast > 0) F::template load<true>(a, (uint64_t)wave_chunk0 * kChunk, lane, cur.in);
-  if (F::kPlanesAhead == 2 && fast > 1) F::template load<true>(a, (uint64_t)(wave_chunk0 + 1) * kChunk, lane, nxt.in);   // and those of its second
-  tbl[tid] = F::kScalarDec ? F::table(tid, dec) : F::table(tid, dec_ptr);
-
-  // escapes are only trusted if their sections lie inside the stream
-  const uint64_t off_val = a.off_pos + a256(2ull * M);
-  const bool esc_ok = M <= a.n && off_val + M <= a.comp_bytes;
-  if (tile == 0 && tid == 0) {
-    u32x4 d = dec;
-    if (!F::kScalarDec) {
-      const uint32_t* dp = reinterpret_cast<const uint32_t*>(dec_ptr);   // 4-byte aligned wherever the entries lie
-      d = u32x4{dp[0], dp[1], dp[2], dp[3]};
-    }
-    decompress_check_header(a, d, M);
-    if (!esc_ok) flag_bad(a);
+  DShared b;
+  DItem it;
+  {
+    // whole and once, as in args_arrived
+    u32x4 x[4], y[3];
+    __builtin_memcpy(x, &args.shared, 64);
+    __builtin_memcpy(y, &args.item[blockIdx.y], 48);
+    asm volatile("" : "+s"(x[0]), "+s"(x[1]), "+s"(x[2]), "+s"(x[3]), "+s"(y[0]), "+s"(y[1]), "+s"(y[2]));
+    __builtin_memcpy(&b, x, 64);
+    __builtin_memcpy(&it, y, 48);
   }
-  if (!esc_ok) M = 0;
-  const uint16_t* pos_arr = reinterpret_cast<const uint16_t*>(a.comp + a.off_pos);
-  const uint8_t* val_arr = a.comp + off_val;
-  lds_barrier();
-
-  // escape records of the wave's c-th chunk: first record and count, from the offset table (0 records if the entries are inconsistent)
-  auto records = [&](uint32_t c, uint32_t& lo, bool& valid) -> uint32_t {
-    const uint64_t cbase = (uint64_t)(wave_chunk0 + c) * kChunk;
-    const uint32_t hi = __builtin_amdgcn_readlane(my_tab, c + 1);
-    lo = __builtin_amdgcn_readlane(my_tab, c);
-    const uint32_t clen = (uint32_t)(a.n - cbase < kChunk ? a.n - cbase : kChunk);
-    valid = hi >= lo && hi - lo <= clen && hi <= M;
-    return valid ? hi - lo : 0u;
-  };
-  auto fetch_records = [&](uint32_t c, Fetched& f) {
-    uint32_t lo;
-    bool valid;
-    const uint32_t cnt = records(c, lo, valid);
-    f.pos = 0; f.val = 0;
-    if ((uint32_t)lane < cnt) {
-      f.pos = pos_arr[lo + lane];
-      f.val = val_arr[lo + lane];
-    }
-  };
-  auto fetch = [&](uint32_t c, Fetched& f, auto complete) {
-    fetch_records(c, f);
-    F::template load<decltype(complete)::value>(a, (uint64_t)(wave_chunk0 + c) * kChunk, lane, f.in);
-  };
-  // A few escapes, the usual case, are applied to the decoded words in registers, one after the other; more
-  // of them are applied in parallel, one lane each, to the chunk laid out in LDS.  Either way every word is
-  // stored once.
-  auto chunk = [&](uint32_t c, const Fetched& f, auto complete) {
-    constexpr bool FULL = decltype(complete)::value;
-    const uint64_t cbase = (uint64_t)(wave_chunk0 + c) * kChunk;
-    uint32_t lo;
-    bool esc_valid;
-    const uint32_t cnt = records(c, lo, esc_valid);
-    const uint32_t clen = (uint32_t)(a.n - cbase < kChunk ? a.n - cbase : kChunk);
-    if (!esc_valid && lane == 0) flag_bad(a);
-    typename F::Out r;
-    F::decode(f.in, tbl, lane, r);
-    if (cnt > 0 && cnt <= a.reg_patch_max) {
-      uint32_t floor = 0;   // a chunk's positions ascend: each must lie above the one before it
-      for (uint32_t j = 0; j < cnt; ++j) {
-        const uint32_t p = __builtin_amdgcn_readlane(f.pos, j), v = __builtin_amdgcn_readlane(f.val, j);
-        if (p >= clen || p < floor || !F::patch_reg(r, lane, p, v)) {
-          if (lane == 0) flag_bad(a);
-        }
-        floor = p + 1;
-      }
-    }
-    if (cnt > a.reg_patch_max) {
-      uint32_t* t = lds_chunk + (uint32_t)wave * F::kTileDwords;
-      F::to_tile(r, t, lane);
-      lds_settle();
-      for (uint32_t j = lane; j < cnt; j += 64) {
-        uint32_t p = f.pos, v = f.val;
-        if (j >= 64) {
-          p = pos_arr[lo + j];
-          v = val_arr[lo + j];
-        }
-        // a chunk's positions ascend: the record before this one (the lane below holds it, or memory does)
-        uint32_t before = (uint32_t)__shfl_up((int)p, 1);
-        if (lane == 0 && j > 0) before = pos_arr[lo + j - 1];
-        if (p >= clen || (j > 0 && p <= before) || !F::patch_tile(t, p, v)) flag_bad(a);
-      }
-      lds_settle();
-      F::from_tile(r, t, lane);
-      lds_settle();   // the tile is written again for the wave's next chunk
-    }
-    uint8_t* cptr = chunk_at<F::ES>(a.w, cbase, __builtin_amdgcn_readlane(my_pages, c));
-    F::template store<FULL>(a, cptr, cbase, lane, r);
-  };
-  // BF16: planes are asked for two chunks ahead and records one chunk ahead (they need the table entries, the
-  // planes need nothing); E5M2, whose kernel is short of instruction slots rather than of bytes in flight: both
-  // one chunk ahead (two ahead: 0.65 instead of 0.70 of the HBM peak).  The first chunk is awaited before the loop, and the ragged chunk stays out of it altogether,
-  // its loads included: the compiler's wait at the bottom of an iteration then covers the next chunk's loads but
-  // not the store issued after them, and no wait stands in front of the loads.
-  if (fast > 0) {
-    fetch_records(0, cur);
-    F::arrived(cur.in);
-    asm volatile("" : "+v"(cur.pos), "+v"(cur.val));
-  }
-  for (uint32_t c = 0; c < fast; ++c) {
-    if (F::kPlanesAhead == 2) {
-      if (c + 1 < fast) fetch_records(c + 1, nxt);
-    } else {
-      if (c + 1 < fast) fetch(c + 1, nxt, std::true_type{});
-    }
-    chunk(c, cur, std::true_type{});
-    cur = nxt;
-    if (F::kPlanesAhead == 2 && c + 2 < fast) F::template load<true>(a, (uint64_t)(wave_chunk0 + c + 2) * kChunk, lane, nxt.in);
-  }
-  if (last_ragged) {
-    fetch(mine - 1, cur, std::false_type{});
-    chunk(mine - 1, cur, std::false_type{});
-  }
-}
-
-template <typename F>
-__global__ __launch_bounds__(kThreads) void decompress_kernel(const DecompressArgs a) {
-  __shared__ uint32_t tbl[256];
-  __shared__ __attribute__((aligned(16))) uint32_t lds_chunk[kWaves * F::kTileDwords];
-  u32x4 dec16 = u32x4{0u, 0u, 0u, 0u};
-  if (F::kScalarDec) dec16 = a.d_dec ? load_dec16(a.d_dec) : dec16_from(a.dec);
-  decompress_tile<F>(a, dec16, a.d_dec ? a.d_dec : a.dec, blockIdx.x, tbl, lds_chunk);
-}
-
-// several streams in one launch: blockIdx.y picks the stream, blockIdx.x the tile
-struct DBatchItem {
-  const uint8_t* comp;
-  uint8_t* out;
-  uint64_t n, comp_bytes;
-};
-struct alignas(64) DecompressBatchArgs {
-  DBatchItem item[kBatchMax];
-  splitzip_sizes* sizes;   // nullable; one record, status bits sticky
-  uint32_t cpw, dtype, reg_patch_max;
-  uint32_t by_xcd;         // the workgroups take their tiles in xcd_order
-  Words paging;            // as in the compress calls' TileShared
-  uint8_t dec[kBatchMax][16];   // every stream's codebook
-  const splitzip_codebook* d_cbs;   // nullable: n_items codebooks in device memory, used instead of dec
-  uint32_t own_dec;        // 1: every stream is decoded with the 16 decode entries of its own header
-};
-
-template <typename F>
-__global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const DecompressBatchArgs b) {
-  __shared__ uint32_t tbl[256];
-  __shared__ __attribute__((aligned(16))) uint32_t lds_chunk[kWaves * F::kTileDwords];
-  const DBatchItem it = b.item[blockIdx.y];
-  const Layout L = make_layout(it.n, (int)b.dtype);
-  // (in 32 bits, or by a shift, a workgroup without a tile leaves 12 to 25 % earlier, but the code that follows comes out
-  // different: 8 tensors of 16 384 chunks with 7 escapes each 80.8-81.2 us instead of 80.1)
-  const uint32_t n_tiles = (uint32_t)((L.n_chunks + (uint64_t)kWaves * b.cpw - 1) / (kWaves * b.cpw));
+  const uint32_t n_chunks = (uint32_t)(((uint64_t)it.n + kChunk - 1) / kChunk);
+  constexpr uint32_t kTileShift = CPW == 1 ? 2 : CPW == 2 ? 3 : CPW == 4 ? 4 : 5;
+  const uint32_t n_tiles = (n_chunks + (1u << kTileShift) - 1u) >> kTileShift;
   const uint32_t tile = b.by_xcd ? xcd_order(blockIdx.x, n_tiles - 1) : blockIdx.x;
   if (tile >= (n_tiles ? n_tiles : 1u)) return;
-  DecompressArgs a;
-  a.comp = it.comp;
-  a.w = item_words(b.paging, it.out);
-  a.n = it.n;
-  a.comp_bytes = it.comp_bytes;
-  a.sizes = b.sizes;
-  a.off_tab = L.off_tab; a.off_sm = L.off_sm; a.off_code = L.off_code; a.off_pos = L.off_pos;
-  a.sm_bytes = L.sm_bytes; a.code_bytes = L.code_bytes;
-  a.n_chunks = (uint32_t)L.n_chunks;
-  a.n_tiles = n_tiles;
-  a.cpw = b.cpw;
-  a.dtype = b.dtype;
-  a.reg_patch_max = b.reg_patch_max;
-  u32x4 dec16 = u32x4{0u, 0u, 0u, 0u};
-  if (F::kScalarDec) dec16 = b.own_dec ? load_dec16(it.comp + kHeaderDecOffset) : b.d_cbs ? load_dec16(b.d_cbs[blockIdx.y].dec) : dec16_from(b.dec[blockIdx.y]);
-  decompress_tile<F>(a, dec16, b.own_dec ? it.comp + kHeaderDecOffset : b.d_cbs ? b.d_cbs[blockIdx.y].dec : b.dec[blockIdx.y], tile, tbl, lds_chunk);   // a.dec stays unset: the table comes from the kernel arguments
+  const uint8_t* comp = as_global(it.comp);
+  Words w = item_words(b.paging, as_global(it.out));
+  w.table = as_global(b.paging.table);
+  splitzip_sizes* const sizes = as_global(b.sizes);
+  const u32x4 dec = b.own_dec ? load_dec16(it.comp + kHeaderDecOffset) : b.d_cbs ? load_dec16(b.d_cbs[blockIdx.y].dec) : dec16_from(it.dec);
+
+  // The stream's first wave also looks at the header: lane i holds its word i, asked for before anything else.
+  const uint32_t c0 = (tile * kWaves + wave) * CPW;   // the wave's first chunk
+  const bool checks = c0 == 0;
+  uint32_t hw = 0;
+  if (checks) hw = reinterpret_cast<const uint32_t*>(comp)[lane & 15];
+  // This wave's slice of the offset table, lane c <-> its chunk c, one entry more for the end, and M as the table states
+  // it (its last entry) in the lanes behind.  One load without a condition: M as a load of its own, the same for all
+  // lanes, was waited for on the spot, before any of the planes had been asked for.
+  const uint32_t entry = c0 + lane < n_chunks ? c0 + lane : n_chunks;
+  const uint32_t my_tab = *reinterpret_cast<const uint32_t*>(comp + (kHeaderBytes + 4u * (lane <= CPW ? entry : n_chunks)));
+  // the runs of both planes, up to the padded end of their sections: of no length for a wave without chunks
+  const uint32_t sm256 = (kHeaderBytes + 4u * (n_chunks + 1) + 255u) >> 8;
+  const auto sm = run_of(comp + ((uint64_t)sm256 << 8) + (uint64_t)c0 * F::kSmBytes, F::template sm_left<CPW>(it.code256 - sm256, c0));
+  const int32_t cd_left = (int32_t)(it.pos256 - it.code256) - (int32_t)(2 * c0);
+  const auto cd = run_of(comp + ((uint64_t)it.code256 << 8) + (uint64_t)c0 * (kChunk / 2), (uint32_t)(cd_left < 0 ? 0 : cd_left > 2 * CPW ? 2 * CPW : cd_left) << 8);
+  typename F::In in[CPW];
+#pragma unroll
+  for (int j = 0; j < CPW; ++j) {
+    load_planes(sm, cd, j, lane, in[j]);
+    // Chunk by chunk, where the compiler would ask for one plane of both first: a stream of 12 288 chunks 8.7 us instead of
+    // 9.3.  (Launches of many rounds, mostly of several streams, are 1 to 2 % slower that way, E5M2 4 to 5 %.)
+    if (F::ES == 2 && CPW == 2 && N == 1) __builtin_amdgcn_sched_barrier(0);
+  }
+  tbl[tid] = F::table(tid, dec);
+  lds_barrier();
+
+  const uint32_t stated = __builtin_amdgcn_readlane(my_tab, 63);   // a wave has fewer than 63 chunks
+  // escapes are only trusted if their sections lie inside the stream
+  const uint32_t M = stated <= it.most ? stated : 0u;
+  const uint16_t* pos_arr = reinterpret_cast<const uint16_t*>(comp + ((uint64_t)it.pos256 << 8));
+  const uint8_t* val_arr = reinterpret_cast<const uint8_t*>(pos_arr) + a256(2ull * stated);
+  // The records of these chunks: the first 128 of the run that they are if the table is in order (it ends with M for the lanes behind).
+  const uint32_t run0 = __builtin_amdgcn_readlane(my_tab, 0), run1 = __builtin_amdgcn_readlane(my_tab, CPW);
+  const uint32_t run = run1 >= run0 && run1 <= M ? (run1 - run0 < 128u ? run1 - run0 : 128u) : 0u;
+  uint16_t pos[2];
+  uint8_t val[2];
+  {
+    const auto pr = run_of(reinterpret_cast<const uint8_t*>(pos_arr + run0), 2u * run), vr = run_of(val_arr + run0, run);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      pos[q] = ld_run2(pr, 2u * (uint32_t)lane + 128u * q);
+      val[q] = ld_run1(vr, (uint32_t)lane + 64u * q);
+    }
+  }
+  // paged tensor: the pool pages of the wave's chunks, lane c <-> its chunk c (entries beyond the pool are clamped where they are used)
+  uint32_t my_pages = 0;
+  if (w.table && n_chunks) my_pages = w.table[(c0 + lane < n_chunks ? c0 + lane : 0u) >> (w.page_shift - 10)];
+  bool bad = checks && !decompress_check_header(it, F::DT, hw, dec, stated, sizes, lane);   // an inconsistent header or record
+
+  // lane c <-> chunk c: its records, none if its entries are inconsistent; where they start in the run; how many of them the
+  // run holds.  Once for all chunks: the scalar unit, which the four SIMDs share, is what short chunks keep busiest.
+  const bool has = lane < CPW && c0 + lane < n_chunks;
+  const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)my_tab, 0x101, 0xf, 0xf, false);   // row_shl:1, the entry behind
+  const uint32_t my_left = it.n - (c0 + lane) * kChunk, my_len = my_left < kChunk ? my_left : kChunk;
+  const bool valid = next >= my_tab && next - my_tab <= my_len && next <= M;
+  bad = bad || (has && !valid);
+  const uint32_t my_cnt = has && valid ? next - my_tab : 0u, my_at = my_tab - run0;
+  const uint32_t my_here = my_at < run ? (my_cnt < run - my_at ? my_cnt : run - my_at) : 0u;
+  const uint32_t n_full = it.n / kChunk;   // complete chunks
+  uint8_t* const out0 = w.base + (uint64_t)F::ES * c0 * kChunk;   // (contiguous words)
+
+#pragma unroll
+  for (int j = 0; j < CPW; ++j) {
+    if (c0 + j >= n_chunks) break;
+    const bool full = c0 + j < n_full;
+    typename F::Out r = F::decode(in[j], tbl, lane);
+    uint32_t* t = lds_chunk + (uint32_t)wave * F::kTileDwords;
+    const uint32_t cnt = __builtin_amdgcn_readlane(my_cnt, j);
+    if (cnt > 0) {
+      // The chunk laid out in LDS, its records applied to it by a lane each, and back: every word is stored once.  (One
+      // after the other in registers, which of them by its number, an escape is 22 instructions of the scalar unit.)
+      const uint32_t at = __builtin_amdgcn_readlane(my_at, j), here = __builtin_amdgcn_readlane(my_here, j);
+      const uint32_t clen = full ? kChunk : it.n - (c0 + j) * kChunk;
+      F::to_tile(r, t, lane);
+      lds_in_order();
+      // a chunk's positions ascend: each must lie above the one before it
+      auto apply = [&](uint32_t k, uint32_t limit, uint32_t p, uint32_t before, uint32_t v) {
+        if (k < limit && (p >= clen || (k > 0 && p <= before) || !F::patch_tile(t, p, v))) bad = true;
+      };
+      // lane and register <-> record of the run
+      apply(lane - at, here, pos[0], lane_before(pos[0], 0u), val[0]);
+      if (at + here > 64) apply(64 + lane - at, here, pos[1], lane_before(pos[1], (uint32_t)__builtin_amdgcn_readlane((uint32_t)pos[0], 63)), val[1]);
+      // the others, four times 64 on their way at a time
+      if (here < cnt) {
+        const uint32_t lo = run0 + at;
+#pragma unroll 1
+        for (uint32_t k0 = here; k0 < cnt; k0 += 256) {
+          const auto pr = run_of(reinterpret_cast<const uint8_t*>(pos_arr + lo + k0), 2u * (cnt - k0)), vr = run_of(val_arr + lo + k0, cnt - k0);
+          uint16_t p[4];
+          uint8_t v[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            p[q] = ld_run2(pr, 2u * (uint32_t)lane + 128u * q);
+            v[q] = ld_run1(vr, (uint32_t)lane + 64u * q);
+          }
+          uint32_t carry = k0 ? pos_arr[lo + k0 - 1] : 0u;   // the position in front of these
+#pragma unroll
+          for (uint32_t q = 0; q < 4; ++q) {
+            apply(k0 + 64 * q + lane, cnt, p[q], lane_before(p[q], carry), v[q]);
+            carry = (uint32_t)__builtin_amdgcn_readlane((uint32_t)p[q], 63);
+          }
+        }
+      }
+      lds_in_order();
+      r = F::from_tile(t, lane);
+      lds_in_order();
+    }
+    uint8_t* cptr = out0 + F::ES * j * kChunk;
+    if (w.table) {
+      uint32_t page = __builtin_amdgcn_readlane(my_pages, j);
+      page = page < w.n_pages ? page : w.n_pages - 1;   // a bad table entry never leaves the pool
+      cptr = chunk_at<F::ES>(w, (uint64_t)(c0 + j) * kChunk, page);
+    }
+    if (full) {
+      F::store(cptr, lane, r);
+    } else {
+      // the tensor's ragged end, word by word out of the LDS tile
+      const uint32_t clen = it.n - (c0 + j) * kChunk;
+      F::to_tile(r, t, lane);
+      lds_in_order();
+#pragma unroll 1
+      for (uint32_t i = lane; i < clen; i += 64) {
+        if (F::ES == 2) reinterpret_cast<uint16_t*>(cptr)[i] = reinterpret_cast<const uint16_t*>(t)[i];
+        else cptr[i] = reinterpret_cast<const uint8_t*>(t)[i];
+      }
+    }
+  }
+  if (bad && sizes) atomicOr(&sizes->status, SPLITZIP_STATUS_BAD_STREAM);
 }
 
 #endif  // SPLITZIP_DECOMPRESS_HPP

@@ -87,30 +87,23 @@ TestHooks g_hooks;
 // of its streams (three per record): the device alone knows the number.
 bool many_escapes(uint64_t bytes_beyond, uint64_t n_elems) { return bytes_beyond * 16 > n_elems * 3; }
 
-// Chunks per wave of a decompress launch over n_chunks chunks in all; us per call with one / two chunks per wave, or
-// as said, one call after the other on one stream:
-//   BF16  4.1 / 4.8 (2048 chunks), 5.1 / 5.6 (4096), 6.3 / 6.1 (5000), 7.1 / 6.4 (6144), 8.1 / 7.5 (8192), 13.3 / 12.8 (16 384), 15.5 / 16.2 (20 000),
-//         22.5 / 23.0 (32 768), 59.5 / 60.0 (98 304), 81.9 / 79.5 (131 072), 1325 / 1229 (2 Mi); three: worse everywhere.
-//         Two up to what is resident at once (eight workgroups of eight chunks per CU) and again for long launches.
-//         Several streams in a launch: 16.3 / 16.3 (64 of 300), 24.7 / 24.0 (64 of 512), 43.6 / 42.7 (8 of 8192), 44.2 / 42.9
-//         (64 of 1024), 65.0 / 62.3 (64 of 1536): two again from 32 768 on.
-//   E5M2  with one / two / four: 4.2 / 4.8 / 6.1 (2048), 6.8 / 6.8 / 7.3 (8192), 11.5 / 9.7 / 9.5 (16 384),
-//         19.8 / 15.9 / 14.2 (32 768); four / five / eight: 45.9 / 46.9 / 47.6 (131 072), 657 / 678 / 671 (2 Mi).  The
-//         longest launches take eight all the same: in the first 20 ms of load after a pause four took 705 to 765 us
-//         there, eight 668 to 688.
+// Chunks per wave of a decompress launch over n_chunks chunks in all; device us per call with one / two / four chunks per
+// wave, all of whose planes a wave asks for at once:
+//   BF16  2.6 / 3.1 / 4.0 (512 chunks), 3.9 / 4.2 / 4.5 (4096), 5.1 / 4.9 / 5.5 (6144), 6.4 / 5.8 / 6.1 (8192), 11.7 / 11.5 /
+//         10.5 (16 384), 13.7 / 14.2 / 13.9 (20 000), 21.1 / 21.3 / 21.1 (32 768), 39.0 / 38.6 / 39.9 (65 536), 75.2 / 74.0 /
+//         76.0 (131 072).  Two up to what is resident at once (eight workgroups of eight chunks per CU) and again for long
+//         launches, in those of several streams from 32 768 on; in the longest, with fewer workgroups per CU
+//         (plan_decompress), 1228 / 1187 / 1246 (2 Mi).
+//   E5M2  2.6 / 3.0 / 3.7 (512), 5.4 / 4.9 / 5.1 (8192), 8.1 / 8.0 / 7.4 (16 384), 13.9 / 13.1 / 13.2 (32 768), 46.6 / 40.5 / 41.7
+//         (128 000), 180 / 155.5 / 159.6 (524 288), 722 / 636 / 650 and, with fewer workgroups per CU, 619 with four (2 Mi).
 // Streams with many escapes keep a wave busy with its chunks' records, one chunk after the other, so the larger pieces
-// pay from somewhat longer streams on.  Random words in 15 / 40 % of the places (14 / 37 % escapes for BF16, 8 / 20 % for
-// E5M2), device us:
-//   BF16  one 8.1 / 10.5, two 9.2 / 13.7 (8192); one 11.7 / 16.1, two 10.0 / 14.5 (10 240); one 15.1 / 24.4, two 13.1 / 25.9
-//         (16 384); with 7 % escapes one 7.3, two 7.9 (8192), at 6 % the same.
-//   E5M2  one 7.2 / 8.1, two 7.5 / 9.2 (8192); one 10.3 / 12.6, two 9.1 / 10.2 (12 288); two 10.2 / 11.6, four 12.4 / 16.3
-//         (16 384); two 15.5 / 21.0, four 15.1 / 20.4 (24 576).
-//   Beyond, it depends on their number which is better, by 5 % either way.
+// pay from somewhat longer streams on (random words: BF16, 4096 chunks, 8.1 / 11.1 / 17.3).
 uint32_t pick_decompress_cpw(uint64_t n_chunks, bool several, bool escapes, int dtype, uint64_t cus) {
   if (const uint32_t forced = g_hooks.cpw.load()) return forced;
   const uint64_t round = cus * 8;   // workgroups resident at a time
   if (dtype == SPLITZIP_BF16) return (n_chunks >= (escapes ? 9 : 5) * round / 2 && n_chunks <= 8 * round) || n_chunks >= (several ? 16 : 56) * round ? 2u : 1u;
-  return n_chunks >= 512 * round ? 8u : n_chunks >= (escapes ? 10 : 8) * round ? 4u : n_chunks >= (escapes ? 5 : 4) * round ? 2u : 1u;
+  if (n_chunks >= 40 * round && n_chunks < 512 * round) return 2;
+  return n_chunks >= (escapes ? 10 : 8) * round ? 4u : n_chunks >= (escapes ? 5 : 4) * round ? 2u : 1u;
 }
 
 // tables must describe one bijection between 16 codes and 16 distinct exponents
@@ -849,6 +842,68 @@ int compress_one(const Words& in, uint64_t n_elems, int dtype, const splitzip_co
   return compress_launch(&it, 1, dtype, in, in.table ? n_elems : 0, d_cb, d_workspace, workspace_bytes, own_scratch, d_sizes, stream);
 }
 
+constexpr unsigned kDecodeLdsPad = 22800;   // five workgroups of the decoder per CU
+
+template <typename F, uint32_t N>
+void launch_decompress(uint32_t cpw, dim3 grid, unsigned lds_pad, hipStream_t st, const DArgs<N>& args) {
+  if (cpw == 1) launch(decompress_kernel<F, 1, N>, grid, dim3(kThreads), lds_pad, st, args);
+  else if (cpw == 2) launch(decompress_kernel<F, 2, N>, grid, dim3(kThreads), lds_pad, st, args);
+  else if (cpw == 4) launch(decompress_kernel<F, 4, N>, grid, dim3(kThreads), lds_pad, st, args);
+  else launch(decompress_kernel<F, 8, N>, grid, dim3(kThreads), lds_pad, st, args);
+}
+
+// how up to kBatchMax streams of a decompress call are launched, by the lengths of what they decode to
+struct DecompressPlan {
+  uint32_t cpw;        // chunks per wave
+  uint32_t wgs;        // workgroups per stream: what the longest needs
+  uint32_t by_xcd;     // they take their tiles in xcd_order
+  uint32_t lds_pad;    // unused LDS asked for at the launch: fewer workgroups per CU
+};
+DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtype) {
+  uint64_t chunks_all = 0, chunks_max = 0, n_all = 0, beyond = 0;
+  for (uint32_t q = 0; q < k; ++q) {
+    const uint64_t c = chunks_of(items[q].n_elems), fixed = splitzip_fixed_bytes(items[q].n_elems, dtype);
+    chunks_all += c;
+    if (c > chunks_max) chunks_max = c;
+    n_all += items[q].n_elems;
+    if (items[q].comp_bytes > fixed) beyond += items[q].comp_bytes - fixed;
+  }
+  DecompressPlan p;
+  const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
+  p.cpw = pick_decompress_cpw(chunks_all, k > 1, many_escapes(beyond, n_all), dtype, cus);
+  // Streams that differ in length, as in pick_base_cpt: more chunks per wave where many of the launch's workgroups have
+  // none.  us by chunks per wave, BF16 one / two: 7.1 / 6.2 (600 chunks beside 63 streams of 5: 9371 without a tile), 18.8
+  // / 12.1 (3000 beside 63 of two), 24.3 / 19.0 (20 000 beside seven of two), two / four, where the streams are a small part
+  // of it: 45.8 / 45.6 (four of 8192 beside 60 of 200: 60 000), 97.3 / 61.5 (32 768 beside 63 of two); E5M2 two / four: 6.2 /
+  // 7.1 (600 beside 63 of 5: 4686), 10.1 / 9.5 (1500 beside 63 of 50: 11 418), 42.5 / 24.8 (13 000 beside 63 of two), four /
+  // eight: 26.1 / 29.1 (8192 beside 63 of 100: 31 862), 24.8 / 16.0 (13 000 beside 63 of two: 51 184); where the streams fill
+  // the chip anyway 37.9 / 34.7 (two of 9000 beside 62 of 1000: 31 000).
+  const uint64_t none = chunks_max * k - chunks_all;   // chunks that the padded grid has room for and the streams do not have
+  if (!g_hooks.cpw.load()) {
+    const uint32_t most = dtype == SPLITZIP_FP8_E5M2 ? 8u : none > 8 * chunks_all ? 4u : 2u;
+    const auto limit = [&](uint32_t cpw) { return dtype == SPLITZIP_BF16 ? (cpw < 2 ? 32u : 224u) : cpw < 4 ? 32u : chunks_all < 256 * cus ? 160u : 96u; };
+    while (p.cpw < most && none / (kWaves * p.cpw) > cus * limit(p.cpw)) p.cpw *= 2;
+  }
+  p.wgs = (uint32_t)((chunks_max + (uint64_t)kWaves * p.cpw - 1) / (kWaves * p.cpw));
+  if (p.wgs < 1) p.wgs = 1;
+  // Launches of many workgroups, from 16 384 on, take their tiles in xcd_order.  us per call, in the order of the tiles and
+  // that way: BF16 606.6 and 599.2 (262 144 workgroups), 302.6 and 298.8 (65 536 of two chunks per wave), 74.9 and 72.9
+  // (32 768), 73.6 both (16 000); E5M2 663 and 641 (131 072), 154.6 and 154.3 (65 536), 40.4 both (16 000).  As in
+  // plan_compress, by the workgroups that have a tile (BF16, one stream of 32 768 chunks beside 63 of two, with another
+  // decoder: 97.3 and 111.1).
+  uint64_t wgs_all = 0;
+  const uint32_t shift = (uint32_t)__builtin_ctz(kWaves * p.cpw);
+  for (uint32_t q = 0; q < k; ++q) wgs_all += (chunks_of(items[q].n_elems) + kWaves * p.cpw - 1) >> shift;
+  p.by_xcd = wgs_all >= 16384u && (uint64_t)p.wgs * k <= 2 * wgs_all ? 1u : 0u;
+  if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2 ? 1u : 0u;
+  // Fewer workgroups per CU, five instead of eight, where a launch is long and its waves have much on their way.  us per call
+  // with eight / six / five / four: BF16, two chunks per wave, 1240 / 1184 / 1172 / 1170 (2 Mi chunks), 300.9 / 295.5 / 292.8 /
+  // 293.1 (524 288), 75.9 / 75.2 / 74.1 / 74.1 (131 072 with seven escapes each), with one chunk 1224 / 1198 / 1231 / 1231; E5M2,
+  // four chunks, 648 / 637 / 619 / 632 (2 Mi), 158.8 / 157.7 / 156.7 / 158.1 (524 288), with two 635 / 638 / 678 / 751.
+  p.lds_pad = p.by_xcd && p.cpw == (dtype == SPLITZIP_BF16 ? 2u : 4u) ? kDecodeLdsPad : 0u;
+  return p;
+}
+
 // splitzip_decompress with the codebook either on the host (cb) or in device memory (d_cb); the words contiguous or paged
 int decompress_impl(const void* d_comp, size_t comp_bytes, uint64_t n_elems, int dtype, const splitzip_codebook* cb,
                     const splitzip_codebook* d_cb, const Words& out, splitzip_sizes* d_sizes, void* stream) {
@@ -860,27 +915,22 @@ int decompress_impl(const void* d_comp, size_t comp_bytes, uint64_t n_elems, int
   if (n_elems >> 32) return SPLITZIP_ERR_UNSUPPORTED;
   if (comp_bytes < splitzip_fixed_bytes(n_elems, dtype)) return SPLITZIP_ERR_CAPACITY;
 
-  const Layout L = make_layout(n_elems, dtype);
-  DecompressArgs a;
-  memset(&a, 0, sizeof a);
-  a.comp = static_cast<const uint8_t*>(d_comp);
-  a.w = out;
-  a.n = n_elems;
-  a.comp_bytes = comp_bytes;
+  DArgs<1> args;
+  DShared& a = args.shared;
+  DItem& to = args.item[0];
+  describe_stream(d_comp, comp_bytes, out.base, n_elems, dtype, &to);
+  if (!d_cb) memcpy(to.dec, cb->dec, 16);
+  else memset(to.dec, 0, 16);
   a.sizes = d_sizes;
-  a.off_tab = L.off_tab; a.off_sm = L.off_sm; a.off_code = L.off_code; a.off_pos = L.off_pos;
-  a.sm_bytes = L.sm_bytes; a.code_bytes = L.code_bytes;
-  a.cpw = pick_decompress_cpw(L.n_chunks, false, many_escapes(comp_bytes - splitzip_fixed_bytes(n_elems, dtype), n_elems), dtype, (uint64_t)cu_count());
-  a.reg_patch_max = kRegPatchDefault;
-  a.n_chunks = (uint32_t)L.n_chunks;
-  a.n_tiles = (uint32_t)((L.n_chunks + (uint64_t)kWaves * a.cpw - 1) / (kWaves * a.cpw));
-  a.dtype = (uint32_t)dtype;
-  a.d_dec = d_cb ? d_cb->dec : nullptr;   // an address in device memory, not read here
-  if (!d_cb) memcpy(a.dec, cb->dec, 16);
-
-  const unsigned grid = a.n_tiles ? a.n_tiles : 1u;
-  if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL(decompress_kernel<DBf16>, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(stream), a);
-  else hipLaunchKernelGGL(decompress_kernel<DE5m2>, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(stream), a);
+  a.d_cbs = d_cb;   // an address in device memory, not read here
+  a.paging = out;
+  a.reserved[0] = a.reserved[1] = 0;
+  a.own_dec = 0;
+  const splitzip_ditem item = {d_comp, comp_bytes, n_elems, out.base, nullptr};
+  const DecompressPlan p = plan_decompress(&item, 1, dtype);
+  a.by_xcd = p.by_xcd;
+  if (dtype == SPLITZIP_BF16) launch_decompress<DBf16>(p.cpw, dim3(p.wgs), p.lds_pad, static_cast<hipStream_t>(stream), args);
+  else launch_decompress<DE5m2>(p.cpw, dim3(p.wgs), p.lds_pad, static_cast<hipStream_t>(stream), args);
   return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
 }
 
@@ -957,51 +1007,6 @@ int splitzip_decompress_own(const void* d_comp, size_t comp_bytes, uint64_t n_el
 
 namespace {
 
-// how up to kBatchMax streams of a batch decompress call are launched, by the lengths of what they decode to
-struct DecompressPlan {
-  uint32_t cpw;        // chunks per wave
-  uint32_t wgs;        // workgroups per stream: what the longest needs
-  uint32_t by_xcd;     // they take their tiles in xcd_order
-};
-DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtype) {
-  uint64_t chunks_all = 0, chunks_max = 0, n_all = 0, beyond = 0;
-  for (uint32_t q = 0; q < k; ++q) {
-    const uint64_t c = chunks_of(items[q].n_elems), fixed = splitzip_fixed_bytes(items[q].n_elems, dtype);
-    chunks_all += c;
-    if (c > chunks_max) chunks_max = c;
-    n_all += items[q].n_elems;
-    if (items[q].comp_bytes > fixed) beyond += items[q].comp_bytes - fixed;
-  }
-  DecompressPlan p;
-  const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
-  p.cpw = pick_decompress_cpw(chunks_all, k > 1, many_escapes(beyond, n_all), dtype, cus);
-  // Streams that differ in length, as in pick_base_cpt: more chunks per wave where many of the launch's workgroups have
-  // none.  us by chunks per wave, BF16 one / two: 7.1 / 6.2 (600 chunks beside 63 streams of 5: 9371 without a tile), 18.8
-  // / 12.1 (3000 beside 63 of two), 24.3 / 19.0 (20 000 beside seven of two), two / four, where the streams are a small part
-  // of it: 45.8 / 45.6 (four of 8192 beside 60 of 200: 60 000), 97.3 / 61.5 (32 768 beside 63 of two); E5M2 two / four: 6.2 /
-  // 7.1 (600 beside 63 of 5: 4686), 10.1 / 9.5 (1500 beside 63 of 50: 11 418), 42.5 / 24.8 (13 000 beside 63 of two), four /
-  // eight: 26.1 / 29.1 (8192 beside 63 of 100: 31 862), 24.8 / 16.0 (13 000 beside 63 of two: 51 184); where the streams fill
-  // the chip anyway 37.9 / 34.7 (two of 9000 beside 62 of 1000: 31 000).
-  const uint64_t none = chunks_max * k - chunks_all;   // chunks that the padded grid has room for and the streams do not have
-  if (!g_hooks.cpw.load()) {
-    const uint32_t most = dtype == SPLITZIP_FP8_E5M2 ? 8u : none > 8 * chunks_all ? 4u : 2u;
-    const auto limit = [&](uint32_t cpw) { return dtype == SPLITZIP_BF16 ? (cpw < 2 ? 32u : 224u) : cpw < 4 ? 32u : chunks_all < 256 * cus ? 160u : 96u; };
-    while (p.cpw < most && none / (kWaves * p.cpw) > cus * limit(p.cpw)) p.cpw *= 2;
-  }
-  p.wgs = (uint32_t)((chunks_max + (uint64_t)kWaves * p.cpw - 1) / (kWaves * p.cpw));
-  if (p.wgs < 1) p.wgs = 1;
-  // us per call, in the order of the tiles and in xcd_order: E5M2 686 and 670 (65 536 workgroups), 88.1 and 87.1
-  // (16 384), 46.0 and 45.9 (8192); BF16 1258 and 1237 (262 144), 1172 and 1152 (240 064), but 620 and 624 (131 072)
-  // and 301 and 301 (65 536).  As in plan_compress, by the workgroups that have a tile (BF16, one stream of 32 768
-  // chunks beside 63 of two: 97.3 and 111.1).
-  uint64_t wgs_all = 0;
-  const uint32_t shift = (uint32_t)__builtin_ctz(kWaves * p.cpw);
-  for (uint32_t q = 0; q < k; ++q) wgs_all += (chunks_of(items[q].n_elems) + kWaves * p.cpw - 1) >> shift;
-  p.by_xcd = wgs_all >= (dtype == SPLITZIP_BF16 ? 196608u : 16384u) && (uint64_t)p.wgs * k <= 2 * wgs_all ? 1u : 0u;
-  if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2 ? 1u : 0u;
-  return p;
-}
-
 // the batch decompress calls; paging: table and page geometry shared by all items, or contiguous tensors (table null)
 // d_cbs (nullable): n_items codebooks in device memory, used instead of the items' own
 int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dtype, const Words& paging, uint64_t paged_room,
@@ -1020,29 +1025,26 @@ int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dty
   }
   uint32_t i = 0;
   while (i < n_items) {
-    DecompressBatchArgs a;
-    memset(&a, 0, sizeof a);
+    DArgs<kBatchMax> args;   // the first k items are filled in, and no other is looked at
+    DShared& a = args.shared;
     uint32_t k = 0;
     for (; i + k < n_items && k < kBatchMax; ++k) {
       const splitzip_ditem& it = items[i + k];
-      if (!d_cbs && !own_dec) memcpy(a.dec[k], it.cb->dec, 16);
-      a.item[k].comp = static_cast<const uint8_t*>(it.d_comp);
-      a.item[k].out = static_cast<uint8_t*>(it.d_out);
-      a.item[k].n = it.n_elems;
-      a.item[k].comp_bytes = it.comp_bytes;
+      DItem& to = args.item[k];
+      if (!d_cbs && !own_dec) memcpy(to.dec, it.cb->dec, 16);
+      else memset(to.dec, 0, 16);
+      describe_stream(it.d_comp, it.comp_bytes, it.d_out, it.n_elems, dtype, &to);
     }
     a.sizes = d_sizes;
     a.d_cbs = d_cbs ? d_cbs + i : nullptr;
     a.own_dec = own_dec ? 1u : 0u;
-    a.dtype = (uint32_t)dtype;
     a.paging = paging;
     const DecompressPlan p = plan_decompress(items + i, k, dtype);
-    a.cpw = p.cpw;
+    a.reserved[0] = a.reserved[1] = 0;
     a.by_xcd = p.by_xcd;
-    a.reg_patch_max = kRegPatchDefault;
     const dim3 grid(p.wgs, k);
-    if (dtype == SPLITZIP_BF16) launch(decompress_batch_kernel<DBf16>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), a);
-    else launch(decompress_batch_kernel<DE5m2>, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), a);
+    if (dtype == SPLITZIP_BF16) launch_decompress<DBf16>(p.cpw, grid, p.lds_pad, static_cast<hipStream_t>(stream), args);
+    else launch_decompress<DE5m2>(p.cpw, grid, p.lds_pad, static_cast<hipStream_t>(stream), args);
     if (hipGetLastError() != hipSuccess) return SPLITZIP_ERR_HIP;
     i += k;
   }
