@@ -83,6 +83,11 @@ __device__ inline uint32_t page_of_chunk(const Words& w, uint64_t chunk) {
   return page < w.n_pages ? page : w.n_pages - 1;   // a bad table entry never leaves the pool
 }
 
+// the same for a chunk that is the whole wave's, in a scalar register: the chunk's address is one then as well
+__device__ inline uint32_t page_of_wave_chunk(const Words& w, uint64_t chunk) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)page_of_chunk(w, chunk));
+}
+
 // address of the first element of the chunk that starts at element cbase; `page` is its pool page, read earlier
 // with page_of_chunk (ignored for a contiguous tensor)
 template <int ES>
@@ -113,16 +118,25 @@ __device__ inline void st_stream(T* p, T v) { __builtin_nontemporal_store(v, p);
 
 // Consecutive bytes as a buffer (base and length wave-uniform): an access is base + a 32-bit offset, loads beyond the end
 // give zeros and fetch nothing -- so a load need not stand behind a condition.
-constexpr int kStream = 2;   // cache bits of an access: non-temporal
+// The instructions take cache bits that a pointer's access has no name for: kThrough for stores that go through the L2 as
+// they are written, where streaming stores stay in it until something pushes them out.
+constexpr int kStream = 2, kThrough = 2 | 16;   // nt; nt sc1
 __device__ inline __amdgpu_buffer_rsrc_t run_of(const uint8_t* base, uint32_t bytes) {
   // (into a scalar register by hand: a clamp of two scalars is a vector instruction, and a description with a word in a vector
   // register makes a loop around every access)
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
+__device__ inline u32x4 ld_run16(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(run, off, 0, kStream); }
 __device__ inline u32x2 ld_run8(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b64(run, off, 0, kStream); }
 __device__ inline uint32_t ld_run4(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b32(run, off, 0, kStream); }
 __device__ inline uint16_t ld_run2(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b16(run, off, 0, 0); }
 __device__ inline uint8_t ld_run1(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b8(run, off, 0, 0); }
+template <typename T>
+__device__ inline void st_run(__amdgpu_buffer_rsrc_t run, uint32_t off, T v) {
+  if constexpr (std::is_same<T, u32x3>::value) __builtin_amdgcn_raw_buffer_store_b96(v, run, off, 0, kThrough);
+  else if constexpr (std::is_same<T, u32x2>::value) __builtin_amdgcn_raw_buffer_store_b64(v, run, off, 0, kThrough);
+  else __builtin_amdgcn_raw_buffer_store_b32(v, run, off, 0, kThrough);
+}
 
 // v_perm_b32: result byte i = byte sel[i] of the 8-byte pool {hi:4..7, lo:0..3}; 0x0c gives 0x00.
 __device__ inline uint32_t byte_perm(uint32_t hi, uint32_t lo, uint32_t sel) {

@@ -113,8 +113,8 @@ __device__ inline void emit_half_bf16(uint32_t* park, const uint32_t (&w)[4], ui
 }
 
 // One chunk's words into registers: lane l holds elements [8 l, 8 l + 8) of each half-chunk.
-// Elements past N read as zero.
-template <bool FULL>
+// Elements past N read as zero.  LONG: kTileLong.
+template <bool FULL, bool LONG>
 __device__ inline void load_chunk_bf16(const Planes& a, const uint8_t* cptr, uint64_t cbase, int lane, uint32_t (&w)[2][4]) {
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -123,7 +123,7 @@ __device__ inline void load_chunk_bf16(const Planes& a, const uint8_t* cptr, uin
     if (!FULL) nvalid = g0 >= a.n ? 0u : (uint32_t)(a.n - g0 < 8 ? a.n - g0 : 8);
     if (FULL) {
       // chunk pointer (wave-uniform) + a 32-bit lane offset: no 64-bit vector arithmetic
-      const u32x4 v = ld_stream(reinterpret_cast<const u32x4*>(cptr) + (uint32_t)(h * 64 + lane));
+      const u32x4 v = LONG ? ld_run16(run_of(cptr, 2 * kChunk), 16u * (uint32_t)(h * 64 + lane)) : ld_stream(reinterpret_cast<const u32x4*>(cptr) + (uint32_t)(h * 64 + lane));
       w[h][0] = v.x; w[h][1] = v.y; w[h][2] = v.z; w[h][3] = v.w;
     } else if (nvalid == 8) {
       const u32x4 v = ld_stream(reinterpret_cast<const u32x4*>(cptr + 2 * (g0 - cbase)));
@@ -143,7 +143,7 @@ __device__ inline void load_chunk_bf16(const Planes& a, const uint8_t* cptr, uin
 // One chunk by one wave, its words in w: dense transform, (optionally) plane stores, escape
 // ranks inside the chunk, escape records into `sink` starting at rank `base`.
 // Returns the chunk's escape count (wave-uniform).
-template <bool FULL, bool STORE, typename Sink>
+template <bool FULL, bool STORE, bool LONG, typename Sink>
 __device__ inline uint32_t process_chunk_bf16(const Planes& a, const uint16_t* lut, uint32_t* park,
                                               uint64_t cbase, int lane, const uint32_t (&w)[2][4], uint32_t base,
                                               const Sink& sink) {
@@ -164,7 +164,10 @@ __device__ inline uint32_t process_chunk_bf16(const Planes& a, const uint16_t* l
     if (STORE) {
       // Sections are padded to 256 bytes and a lane's group never straddles the padded end, so
       // whole-group stores also write the zero padding.
-      if (FULL) {
+      if (FULL && LONG) {
+        st_run(run_of(a.out + a.off_sm + cbase, kChunk), 8u * (uint32_t)(h * 64 + lane), sm);
+        st_run(run_of(a.out + a.off_code + (cbase >> 1), kChunk / 2), 4u * (uint32_t)(h * 64 + lane), code);
+      } else if (FULL) {
         st_stream(reinterpret_cast<u32x2*>(a.out + a.off_sm + cbase) + (uint32_t)(h * 64 + lane), sm);
         st_stream(reinterpret_cast<uint32_t*>(a.out + a.off_code + (cbase >> 1)) + (uint32_t)(h * 64 + lane), code);
       } else {
@@ -202,13 +205,13 @@ __device__ inline uint32_t unpack3_e5m2(uint32_t r) {
   return ((t & 0x04040404u) << 5) | (t & 0x03030303u);
 }
 
-template <bool FULL>
+template <bool FULL, bool LONG>
 __device__ inline void load_chunk_e5m2(const Planes& a, const uint8_t* cptr, uint64_t cbase, int lane, uint32_t (&w)[4]) {
   const uint64_t g0 = cbase + lane * 16;
   uint32_t nvalid = 16;
   if (!FULL) nvalid = g0 >= a.n ? 0u : (uint32_t)(a.n - g0 < 16 ? a.n - g0 : 16);
   if (FULL) {
-    const u32x4 v = ld_stream(reinterpret_cast<const u32x4*>(cptr) + (uint32_t)lane);
+    const u32x4 v = LONG ? ld_run16(run_of(cptr, kChunk), 16u * (uint32_t)lane) : ld_stream(reinterpret_cast<const u32x4*>(cptr) + (uint32_t)lane);
     w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
   } else if (nvalid == 16) {
     const u32x4 v = ld_stream(reinterpret_cast<const u32x4*>(cptr + (g0 - cbase)));
@@ -226,7 +229,7 @@ __device__ inline void load_chunk_e5m2(const Planes& a, const uint8_t* cptr, uin
   }
 }
 
-template <bool FULL, bool STORE, typename Sink>
+template <bool FULL, bool STORE, bool LONG, typename Sink>
 __device__ inline uint32_t process_chunk_e5m2(const Planes& a, const uint16_t* lut, uint32_t* park,
                                               uint64_t cbase, int lane, const uint32_t (&w)[4], uint32_t base,
                                               const Sink& sink) {
@@ -284,8 +287,13 @@ __device__ inline uint32_t process_chunk_e5m2(const Planes& a, const uint16_t* l
       const uint32_t lo_dn = __builtin_amdgcn_mov_dpp(lo, 0xA0, 0xf, 0xf, false);
       const uint32_t hi_dn = __builtin_amdgcn_mov_dpp(hi, 0xA0, 0xf, 0xf, false);
       d0 = lo_dn; d1 = (hi_dn & 0xffffu) | (lo_up << 16);
-      st_stream(reinterpret_cast<u32x3*>(sm_dst), u32x3{d0, d1, d2});
-      st_stream(reinterpret_cast<u32x2*>(a.out + a.off_code + (cbase >> 1)) + (uint32_t)lane, u32x2{code[0], code[1]});
+      if (LONG) {
+        st_run(run_of(sm_chunk_ptr, 3 * kChunk / 8), (uint32_t)(lane >> 1) * 12u, u32x3{d0, d1, d2});
+        st_run(run_of(a.out + a.off_code + (cbase >> 1), kChunk / 2), 8u * (uint32_t)lane, u32x2{code[0], code[1]});
+      } else {
+        st_stream(reinterpret_cast<u32x3*>(sm_dst), u32x3{d0, d1, d2});
+        st_stream(reinterpret_cast<u32x2*>(a.out + a.off_code + (cbase >> 1)) + (uint32_t)lane, u32x2{code[0], code[1]});
+      }
     } else {
       // dword by dword up to the padded end of each plane; the pad can reach 128 bytes past the
       // chunk's own 384 plane bytes
@@ -341,18 +349,17 @@ struct Bf16 {
   // (8192), 26.5 / 26.9 / 27.1 (4096: one tensor), 17.4 / 18.1 / 18.0 (2048); unused LDS asked for at the launch sets
   // the number (compress_launch).
   static constexpr uint32_t kCpt = 2;
-  static constexpr int kWavesPerSimd = 8;
   static constexpr uint32_t kTileLdsPad = 22000;   // five workgroups per CU
   static constexpr uint32_t kSmallChunks = 40;
   static constexpr int kLutShift = 0;       // the LDS encode table holds the entry of exponent e in slot e
   // a chunk goes the fast way if it is complete (then nothing of a pad is its business: N is a multiple of 1024 there)
   __device__ static inline bool full(const Planes& a, uint64_t cbase) { return cbase + kChunk <= a.n; }
-  template <bool FULL>
-  __device__ static inline void load(const Planes& a, const uint8_t* cptr, uint64_t cbase, int lane, Regs& r) { load_chunk_bf16<FULL>(a, cptr, cbase, lane, r.w); }
-  template <bool FULL, bool STORE, typename Sink>
+  template <bool FULL, bool LONG = false>
+  __device__ static inline void load(const Planes& a, const uint8_t* cptr, uint64_t cbase, int lane, Regs& r) { load_chunk_bf16<FULL, LONG>(a, cptr, cbase, lane, r.w); }
+  template <bool FULL, bool STORE, bool LONG = false, typename Sink>
   __device__ static inline uint32_t process(const Planes& a, const uint16_t* lut, uint32_t* park, uint64_t cbase,
                                             int lane, const Regs& r, uint32_t base, const Sink& sink) {
-    return process_chunk_bf16<FULL, STORE>(a, lut, park, cbase, lane, r.w, base, sink);
+    return process_chunk_bf16<FULL, STORE, LONG>(a, lut, park, cbase, lane, r.w, base, sink);
   }
 };
 struct E5m2 {
@@ -367,18 +374,17 @@ struct E5m2 {
   // 790 us with five)
   static constexpr uint32_t kCpt = 4;
   static constexpr uint32_t kSmallChunks = 48;
-  static constexpr int kWavesPerSimd = 8;
   // The LDS encode table holds the entry of exponent e in slots 2 e and 2 e + 1: its byte offset is then
   // the word's byte with the sign and mantissa bits masked off, one instruction per element.
   static constexpr int kLutShift = 1;
   // the tensor's last chunk always goes the careful way: 384 plane bytes per chunk leave a pad behind an odd chunk count
   __device__ static inline bool full(const Planes& a, uint64_t cbase) { return cbase + kChunk < a.n; }
-  template <bool FULL>
-  __device__ static inline void load(const Planes& a, const uint8_t* cptr, uint64_t cbase, int lane, Regs& r) { load_chunk_e5m2<FULL>(a, cptr, cbase, lane, r.w); }
-  template <bool FULL, bool STORE, typename Sink>
+  template <bool FULL, bool LONG = false>
+  __device__ static inline void load(const Planes& a, const uint8_t* cptr, uint64_t cbase, int lane, Regs& r) { load_chunk_e5m2<FULL, LONG>(a, cptr, cbase, lane, r.w); }
+  template <bool FULL, bool STORE, bool LONG = false, typename Sink>
   __device__ static inline uint32_t process(const Planes& a, const uint16_t* lut, uint32_t* park, uint64_t cbase,
                                             int lane, const Regs& r, uint32_t base, const Sink& sink) {
-    return process_chunk_e5m2<FULL, STORE>(a, lut, park, cbase, lane, r.w, base, sink);
+    return process_chunk_e5m2<FULL, STORE, LONG>(a, lut, park, cbase, lane, r.w, base, sink);
   }
 };
 
@@ -483,6 +489,13 @@ __device__ inline void args_arrived(const TileArgs<N>& args, uint32_t item, Tile
   asm volatile("" : "+s"(x[0]), "+s"(x[1]), "+s"(x[2]), "+s"(x[3]), "+s"(x[4]), "+s"(x[5]), "+s"(y[0]), "+s"(y[1]), "+s"(y[2]));
   __builtin_memcpy(&a, x, 96);
   __builtin_memcpy(&it, y, 48);
+  a.sizes = as_global(a.sizes);
+  a.status = as_global(a.status);
+  a.stage = as_global(a.stage);
+  a.d_cbs = as_global(a.d_cbs);
+  a.paging.table = as_global(a.paging.table);
+  it.in = as_global(it.in);
+  it.out = as_global(it.out);
 }
 
 // what both passes derive from the arguments for one tensor
@@ -521,10 +534,18 @@ __device__ inline void build_encode_table(uint16_t* lut, const u32x4& d, int tid
 // a barrier for LDS traffic only: global loads that are on their way stay on their way
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// What the dense pass is built for.  kTileOnce: a wave has CPT chunks, so that no loop over the chunks is left (its
+// constants and copies of registers were 2 to 5 % of a call; us, with a loop and without: E5M2, 16 384 chunks 12.6 and
+// 11.7, 64 tensors of 100 chunks 9.6 and 9.0; BF16, 128 chunks 6.0 and 5.8).  kTileLong: that in a launch that memory
+// alone bounds: addresses are a scalar and an offset, and stores go through the L2 as they are written; short launches
+// lose by it.  kTileLoop: a wave has more chunks, CPT of them at a time (very large tensors, whose counts would not fit).
+constexpr int kTileOnce = 0, kTileLong = 1, kTileLoop = 2;
+
 // CPT: chunks of a wave whose loads are issued together, before anything else happens in the workgroup.  Wave w of
 // the tile owns the chunks [w cpt, w cpt + cpt) of the tile.
-template <typename F, int CPT, uint32_t N>
-__global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_kernel(const TileArgs<N> args) {
+template <typename F, int CPT, uint32_t N, int KIND>
+__global__ __launch_bounds__(kTileThreads) void compress_tile_kernel(const TileArgs<N> args) {
+  constexpr bool LONG = KIND == kTileLong;
   constexpr int NW = kTileThreads / 64;
   __shared__ uint16_t lut[256];
   __shared__ uint16_t stage_pk[NW][kTileStageCap];
@@ -537,6 +558,10 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
   TileShared a;
   TileItem it;
   args_arrived(args, item, a, it);
+  if (KIND != kTileLoop) {
+    a.cpt = CPT;
+    a.tile_shift = CPT == 1 ? 2 : CPT == 2 ? 3 : 4;
+  }
   const TileGeom G = tile_geom(a, it, item, F::DT);
   const Planes& P = G.P;
   // xcd_order, written out as one condition with the last tile straight from the length: as a call under by_xcd, or with
@@ -563,8 +588,8 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
 #pragma unroll
       for (int j = 0; j < CPT; ++j) {
         const uint64_t cbase = (uint64_t)(r0 + w0 + it0 + j) * kChunk;
-        const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_chunk(P.w, r0 + w0 + it0 + j) : 0u);
-        F::template load<true>(P, cptr, cbase, lane, w[j]);
+        const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_wave_chunk(P.w, r0 + w0 + it0 + j) : 0u);
+        F::template load<true, LONG>(P, cptr, cbase, lane, w[j]);
       }
     };
     // the words first: the table is built while they are on their way
@@ -576,7 +601,7 @@ __global__ __launch_bounds__(kTileThreads, F::kWavesPerSimd) void compress_tile_
 #pragma unroll
       for (int j = 0; j < CPT; ++j) {
         if ((uint32_t)lane == it0 + j) my_start = wave_count;
-        wave_count += F::template process<true, true>(P, lut, park, (uint64_t)(r0 + w0 + it0 + j) * kChunk, lane, w[j], wave_count, lds);
+        wave_count += F::template process<true, true, LONG>(P, lut, park, (uint64_t)(r0 + w0 + it0 + j) * kChunk, lane, w[j], wave_count, lds);
       }
     }
   } else {

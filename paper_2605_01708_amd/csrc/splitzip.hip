@@ -654,12 +654,14 @@ uint32_t pick_base_cpt(uint64_t chunks, uint64_t chunks_padded, int dtype, uint6
 // the launches of k tensors: dense pass (one workgroup per tile, started by the hardware in the tiles' order), sums if
 // the finishing pass wants them, finishing pass
 template <typename F, uint32_t N>
-void launch_compress(unsigned tiles, unsigned finish_wgs, unsigned sums, unsigned k, unsigned lds_pad, hipStream_t st, const TileArgs<N>& args) {
+void launch_compress(unsigned tiles, unsigned finish_wgs, unsigned sums, unsigned k, bool is_long, unsigned lds_pad, hipStream_t st, const TileArgs<N>& args) {
   if (tiles) {
     const dim3 grid(tiles, k), block(kTileThreads);
-    if (args.shared.cpt == 1) launch(compress_tile_kernel<F, 1, N>, grid, block, lds_pad, st, args);
-    else if (args.shared.cpt == 2 || F::kCpt == 2) launch(compress_tile_kernel<F, 2, N>, grid, block, lds_pad, st, args);
-    else launch(compress_tile_kernel<F, F::kCpt, N>, grid, block, lds_pad, st, args);
+    const uint32_t cpt = args.shared.cpt;
+    if (cpt == 1) launch(compress_tile_kernel<F, 1, N, kTileOnce>, grid, block, lds_pad, st, args);
+    else if (cpt == 2) launch(is_long ? compress_tile_kernel<F, 2, N, kTileLong> : compress_tile_kernel<F, 2, N, kTileOnce>, grid, block, lds_pad, st, args);
+    else if (cpt == F::kCpt) launch(is_long ? compress_tile_kernel<F, F::kCpt, N, kTileLong> : compress_tile_kernel<F, F::kCpt, N, kTileOnce>, grid, block, lds_pad, st, args);
+    else launch(compress_tile_kernel<F, F::kCpt, N, kTileLoop>, grid, block, lds_pad, st, args);
     if (args.shared.use_group_sums) launch(tile_group_sum_kernel<F, N>, dim3(sums, k), dim3(64), 0, st, args);
   }
   launch(compress_finish_kernel<F, N>, dim3(finish_wgs ? finish_wgs : 1u, k), dim3(kTileThreads), 0, st, args);
@@ -682,6 +684,7 @@ struct CompressPlan {
   uint64_t tiles_max;       // of the longest tensor: the dense pass has k rows of so many workgroups
   bool small;               // one launch of compress_small_kernel
   bool by_xcd;              // the dense pass takes its tiles in xcd_order, BF16 with fewer workgroups per CU
+  bool is_long;             // the dense pass stores through the L2 (kTileLong)
   uint32_t finish_groups;   // groups of kGroup tiles per workgroup of the finishing pass
   uint32_t finish_wgs;      // workgroups of the finishing pass per tensor
   bool group_sums;          // the finishing pass is given sums of kSumGroup tile counts
@@ -730,6 +733,11 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   // beside 48 of 16: 91.5 and 95.6; but 32 of 16 384 beside 32 of 16: 328 and 321).
   p.by_xcd = tiles_all >= 16384 && p.tiles_max * p.k <= 2 * tiles_all;
   if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2;
+  // Launches that memory alone bounds store through the L2 (kTileLong).  us per call, without and with:
+  // BF16 21.0 and 21.2 (3072 tiles), 25.6 and 25.7 (4096), 35.05 and 34.98 (6144), 82.2 and 80.9 (16 384), 158.2 and
+  // 155.8 (32 768), 563 and 561 (122 880); E5M2 11.9 and 12.3 (2048), 17.6 and 17.7 (4096), 23.19 and 23.06 (6144),
+  // 28.2 and 27.9 (8192), 89.2 and 88.5 (32 768).
+  p.is_long = tiles_all >= 6144;
   const uint32_t groups_max = (uint32_t)((p.tiles_max + kGroup - 1) / kGroup);
   // many groups in the launch: several per workgroup, as long as the chip still gets a few workgroups per CU
   p.finish_groups = 1;
@@ -816,11 +824,11 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       else launch_small<E5m2>(k, st, args);
     } else if (k == 1) {
       const TileArgs<1> one = {args.shared, {args.item[0]}};
-      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, 1, pad, st, one);
-      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, 1, pad, st, one);
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, 1, p.is_long, pad, st, one);
+      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, 1, p.is_long, pad, st, one);
     } else {
-      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, k, pad, st, args);
-      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, k, pad, st, args);
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, args);
+      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, args);
     }
     if (hipGetLastError() != hipSuccess) return SPLITZIP_ERR_HIP;
     i += k;
