@@ -211,9 +211,9 @@ void variant_tables(const splitzip_variant* v, const splitzip_codebook* cb, VArg
       default: hipLaunchKernelGGL((KERNEL<SPLITZIP_FP8_E4M3, 4>), grid, block, 0, st, args); break;                \
     }                                                                                                              \
   } while (0)
-#define SPLITZIP_V_DISPATCH1(KERNEL, grid, block, st, args)                                                        \
+#define SPLITZIP_V_DISPATCH1(KERNEL, dtype, grid, block, st, args)                                                 \
   do {                                                                                                             \
-    switch ((args).dtype) {                                                                                        \
+    switch (dtype) {                                                                                        \
       case SPLITZIP_BF16: hipLaunchKernelGGL((KERNEL<SPLITZIP_BF16>), grid, block, 0, st, args); break;            \
       case SPLITZIP_FP8_E5M2: hipLaunchKernelGGL((KERNEL<SPLITZIP_FP8_E5M2>), grid, block, 0, st, args); break;    \
       default: hipLaunchKernelGGL((KERNEL<SPLITZIP_FP8_E4M3>), grid, block, 0, st, args); break;                   \
@@ -232,20 +232,20 @@ void launch_v_finish(dim3 g, hipStream_t st, const VArgs& a) {
 }
 
 template <int DT, int CB>
-void launch_v_decode(unsigned grid, hipStream_t st, const VArgs& a) {
+void launch_v_decode(unsigned grid, hipStream_t st, uint32_t mode, uint32_t chunk_shift, const VDecodeArgs& a) {
   const dim3 g(grid), b(kThreads);
-  if (a.mode == SPLITZIP_ESC_POS) {
-    if (a.chunk_shift == 10) hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_POS, 10>), g, b, 0, st, a);
+  if (mode == SPLITZIP_ESC_POS) {
+    if (chunk_shift == 10) hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_POS, 10>), g, b, 0, st, a);
     else hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_POS, 8>), g, b, 0, st, a);
-  } else if (a.mode == SPLITZIP_ESC_SENTINEL) {
+  } else if (mode == SPLITZIP_ESC_SENTINEL) {
     // By what the caller says it holds beyond the fixed part, a value per escape: more than a quarter of the elements, or
     // half of them where values are packed and take two loads each (32 Mi words of E5M2, top-7, 5 bits: a fifth
     // escaped, 45.1 us and 52.8 this way; about half 57.8 and 58.3; all that random words make escape 62.5 and 60.4).
     const uint64_t values = (a.capacity - a.off_pos) * 8 / a.val_bits;
     const bool many = values > (a.val_bits == 8 ? a.n / 4 : a.n / 2);
-    if (many && a.chunk_shift == 10) hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_SENTINEL, 10, true>), g, b, 0, st, a);
+    if (many && chunk_shift == 10) hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_SENTINEL, 10, true>), g, b, 0, st, a);
     else if (many) hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_SENTINEL, 8, true>), g, b, 0, st, a);
-    else if (a.chunk_shift == 10) hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_SENTINEL, 10>), g, b, 0, st, a);
+    else if (chunk_shift == 10) hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_SENTINEL, 10>), g, b, 0, st, a);
     else hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_SENTINEL, 8>), g, b, 0, st, a);
   } else {
     hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_ABS32, 10>), g, b, 0, st, a);
@@ -393,25 +393,38 @@ int splitzip_variant_decompress(const void* d_comp, size_t comp_bytes, uint64_t 
   if (n_elems >> 32) return SPLITZIP_ERR_UNSUPPORTED;
   if (comp_bytes < splitzip_variant_total_bytes(n_elems, 0, v)) return SPLITZIP_ERR_CAPACITY;
 
-  VArgs a;
-  variant_layout(n_elems, v, &a);
+  VArgs l;
+  variant_layout(n_elems, v, &l);
+  variant_tables(v, cb, &l);
+  VDecodeArgs a;
   a.in = static_cast<const uint8_t*>(d_comp);
   a.out = static_cast<uint8_t*>(d_out);
-  a.capacity = comp_bytes;
   a.sizes = d_sizes;
-  a.offs = const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(a.in + a.off_tab));   // read only; unused in the absolute mode
-  variant_tables(v, cb, &a);
+  a.capacity = comp_bytes;
+  a.n = (uint32_t)n_elems;
+  a.n_chunks = (uint32_t)l.n_chunks;
+  a.k = l.k;
+  a.val_bits = l.val_bits;
+  a.off_pos = l.off_pos;
+  a.tab = reinterpret_cast<const uint32_t*>(a.in + l.off_tab);
+  a.sm = n_elems ? a.in + l.off_sm : a.in;
+  a.code = n_elems ? a.in + l.off_code : a.in;
+  a.sm_last = n_elems ? (uint32_t)(a256(l.sm_bytes) - v_sm_bits(l.dtype) / 8 * 4 - 4) : 0u;   // a load is 8 bytes of 8-bit fields, 4 of narrower ones
+  a.code_last = n_elems ? (uint32_t)(a256(l.code_bytes) - 4) : 0u;
+  a.pos = a.in + l.off_pos;
+  memcpy(a.hdr, l.hdr, sizeof a.hdr);
+  memcpy(a.dec, l.dec, sizeof a.dec);
 
   const hipStream_t st = static_cast<hipStream_t>(stream);
   const uint64_t blocks = (n_elems + kVBlock - 1) / kVBlock;
   const unsigned grid = blocks ? (unsigned)((blocks + kWaves - 1) / kWaves) : 1u;
-  switch ((int)a.dtype * 2 + (a.code_bits == 4 ? 1 : 0)) {
-    case 0: launch_v_decode<SPLITZIP_BF16, 3>(grid, st, a); break;
-    case 1: launch_v_decode<SPLITZIP_BF16, 4>(grid, st, a); break;
-    case 2: launch_v_decode<SPLITZIP_FP8_E5M2, 3>(grid, st, a); break;
-    case 3: launch_v_decode<SPLITZIP_FP8_E5M2, 4>(grid, st, a); break;
-    case 4: launch_v_decode<SPLITZIP_FP8_E4M3, 3>(grid, st, a); break;
-    default: launch_v_decode<SPLITZIP_FP8_E4M3, 4>(grid, st, a); break;
+  switch ((int)l.dtype * 2 + (l.code_bits == 4 ? 1 : 0)) {
+    case 0: launch_v_decode<SPLITZIP_BF16, 3>(grid, st, l.mode, l.chunk_shift, a); break;
+    case 1: launch_v_decode<SPLITZIP_BF16, 4>(grid, st, l.mode, l.chunk_shift, a); break;
+    case 2: launch_v_decode<SPLITZIP_FP8_E5M2, 3>(grid, st, l.mode, l.chunk_shift, a); break;
+    case 3: launch_v_decode<SPLITZIP_FP8_E5M2, 4>(grid, st, l.mode, l.chunk_shift, a); break;
+    case 4: launch_v_decode<SPLITZIP_FP8_E4M3, 3>(grid, st, l.mode, l.chunk_shift, a); break;
+    default: launch_v_decode<SPLITZIP_FP8_E4M3, 4>(grid, st, l.mode, l.chunk_shift, a); break;
   }
   if (v->escape_mode == SPLITZIP_ESC_ABS32 && n_elems) {
     // M is known to the device only: a grid that strides over whatever the header says
@@ -419,7 +432,7 @@ int splitzip_variant_decompress(const void* d_comp, size_t comp_bytes, uint64_t 
     uint64_t g = (most + kThreads - 1) / kThreads;
     const uint64_t cap = (uint64_t)cu_count() * 8;
     if (g > cap) g = cap;
-    if (g) SPLITZIP_V_DISPATCH1(v_scatter_kernel, dim3((unsigned)g), dim3(kThreads), st, a);
+    if (g) SPLITZIP_V_DISPATCH1(v_scatter_kernel, l.dtype, dim3((unsigned)g), dim3(kThreads), st, a);
   }
   return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
 }

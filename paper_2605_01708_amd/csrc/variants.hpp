@@ -204,20 +204,18 @@ __device__ inline void v_store_plane(uint8_t* plane, uint64_t off, uint64_t end,
     if (q < 3 && (FULL || off + at < end)) st_stream(reinterpret_cast<uint32_t*>(plane + off + at), d);
   }
 }
-// what v_store_plane wrote, as it comes from memory; v_plane_fields makes a lane's eight fields of it
-template <int NB, bool FULL>
-__device__ inline void v_load_plane(const uint8_t* plane, uint64_t off, uint64_t end, uint32_t lane, uint32_t (&v)[2]) {
-  v[0] = 0; v[1] = 0;
+// What v_store_plane wrote, as it comes from memory; v_plane_fields makes a lane's eight fields of it.  No load stands
+// behind a condition: a lane beyond the section's end reads its last bytes (last: where the last load may start).
+template <int NB>
+__device__ inline void v_load_plane(const uint8_t* plane, uint32_t off, uint32_t last, uint32_t lane, uint32_t (&v)[2]) {
+  const uint32_t q = lane & 3u;   // of 3-bit fields lane 3 of a quad reads its neighbour's dword
+  const uint32_t want = off + (NB == 8 ? 8u * lane : NB == 4 ? 4u * lane : (lane >> 2) * 12u + 4u * (q < 3 ? q : 2u)), at = want < last ? want : last;
+  v[1] = 0;
   if (NB == 8) {
-    if (FULL || off + 8 * lane < end) {
-      const u32x2 x = ld_stream(reinterpret_cast<const u32x2*>(plane + off) + lane);
-      v[0] = x.x; v[1] = x.y;
-    }
-  } else if (NB == 4) {
-    if (FULL || off + 4 * lane < end) v[0] = ld_stream(reinterpret_cast<const uint32_t*>(plane + off) + lane);
+    const u32x2 x = ld_stream(reinterpret_cast<const u32x2*>(plane + at));
+    v[0] = x.x; v[1] = x.y;
   } else {
-    const uint32_t q = lane & 3u, at = (lane >> 2) * 12 + 4 * (q < 3 ? q : 2u);   // lane 3 reads its neighbour's dword
-    if (FULL || off + at < end) v[0] = ld_stream(reinterpret_cast<const uint32_t*>(plane + off + at));
+    v[0] = ld_stream(reinterpret_cast<const uint32_t*>(plane + at));
   }
 }
 template <int NB>
@@ -602,34 +600,79 @@ __global__ __launch_bounds__(kThreads) void v_pack_kernel(const VArgs a) {
 
 // ---- decompress -----------------------------------------------------------------------------
 
-// escape value idx of a stream whose value section starts at off_val (the section is known to lie inside the stream)
-__device__ inline uint32_t v_value(const VArgs& a, uint64_t off_val, uint64_t idx) {
-  if (a.val_bits == 8) return a.in[off_val + idx];
-  const uint64_t bit = idx * a.val_bits;
+// What the decode kernel is told, ready to be used: with a block of 1024 elements per wave, a scalar instruction of the
+// beginning is one per block, and the four SIMDs share the scalar unit.
+struct VDecodeArgs {
+  const uint8_t* in;
+  uint8_t* out;
+  const uint8_t* sm;       // the stream's sections (of an empty tensor: the stream)
+  const uint8_t* code;
+  const uint32_t* tab;     // unused in the absolute mode
+  const uint8_t* pos;
+  splitzip_sizes* sizes;   // nullable
+  uint64_t capacity, off_pos;
+  uint32_t n, n_chunks, sm_last, code_last;   // see v_load_plane
+  uint32_t k, val_bits;
+  uint32_t hdr[16];        // as in VArgs
+  uint8_t dec[16];
+};
+static_assert(sizeof(VDecodeArgs) == 176, "whole 16-byte words for the copy of v_decode_kernel");
+
+// escape value idx of a stream whose value section starts at val (the section is known to lie inside the stream)
+__device__ inline uint32_t v_value(const uint8_t* val, uint32_t bits, uint64_t idx) {
+  if (bits == 8) return val[idx];
+  const uint64_t bit = idx * bits;
   const uint32_t sh = (uint32_t)(bit & 7u);
-  uint32_t v = a.in[off_val + (bit >> 3)] >> sh;
-  if (sh + a.val_bits > 8) v |= (uint32_t)a.in[off_val + (bit >> 3) + 1] << (8 - sh);
-  return v & ((1u << a.val_bits) - 1u);
+  uint32_t v = val[bit >> 3] >> sh;
+  if (sh + bits > 8) v |= (uint32_t)val[(bit >> 3) + 1] << (8 - sh);
+  return v & ((1u << bits) - 1u);
 }
+
+// The values of the count records from lo on, all of them inside the section, as a run: value i, or nothing in particular
+// from count on.  Narrow values (FP8, as wide as the exponent field) take two loads, the second of which fetches nothing
+// for values that are bytes; what was loaded is made a value where it is used (of), so that nothing waits for it.
+template <int DT>
+struct VValues {
+  __amdgpu_buffer_rsrc_t run, next;
+  uint32_t bit0, bits;   // of the run's first byte, where value 0 starts
+  struct Loaded { uint32_t low, high; };
+  __device__ inline VValues(const uint8_t* val, uint32_t val_bits, uint32_t lo, uint32_t count) {
+    bits = VFmt<DT>::ES == 2 ? 8u : val_bits;
+    const uint64_t first = (uint64_t)lo * bits;
+    bit0 = VFmt<DT>::ES == 2 ? 0u : (uint32_t)first & 7u;
+    const uint32_t bytes = VFmt<DT>::ES == 2 || !count ? count : (bit0 + count * bits + 7u) >> 3;
+    run = run_of(val + (first >> 3), bytes);
+    if (VFmt<DT>::ES == 1) next = run_of(val + (first >> 3) + 1, bits == 8 || !bytes ? 0u : bytes - 1);
+  }
+  __device__ inline Loaded at(uint32_t i) const {
+    const uint32_t byte = VFmt<DT>::ES == 2 ? i : (bit0 + i * bits) >> 3;
+    return Loaded{ld_run1(run, byte), VFmt<DT>::ES == 2 ? 0u : (uint32_t)ld_run1(next, byte)};
+  }
+  __device__ inline uint32_t of(const Loaded& x, uint32_t i) const {
+    if (VFmt<DT>::ES == 2) return x.low;
+    return ((x.low | (x.high << 8)) >> ((bit0 + i * bits) & 7u)) & ((1u << bits) - 1u);
+  }
+};
 
 // an inconsistent header or record: sticky bit in the caller's sizes record (nullable)
-__device__ inline void v_flag_bad(const VArgs& a) {
-  if (a.sizes) atomicOr(&a.sizes->status, SPLITZIP_STATUS_BAD_STREAM);
+__device__ inline void v_flag_bad(splitzip_sizes* sizes) {
+  if (sizes) atomicOr(&sizes->status, SPLITZIP_STATUS_BAD_STREAM);
 }
 
-// The header as every wave reads it: lane i < 16 holds word i.  Words 6..9 (M, total) are checked against the
-// layout, the others against what the call expects (word by word with scalar compares: the expected words are kernel
-// arguments, and a vector load of them would return behind the loads of the planes).  Wave-uniform result; M through
-// m_out.
-__device__ inline bool v_check_header(const VArgs& a, uint32_t hw, uint32_t* m_out) {
-  bool words_ok = true;
+// The header as every wave reads it: lane i holds word i & 15.  Compared with what the call expects and, words 6 to 9 (M,
+// total), with what follows from M; all words at once, the expected ones put into lanes (one after the other in the scalar
+// unit they were 60 instructions of a wave).  Wave-uniform result; M through m_out.
+template <uint32_t PB>
+__device__ inline bool v_check_header(const VDecodeArgs& a, uint32_t hw, uint32_t* m_out) {
+  const uint32_t M = (uint32_t)__builtin_amdgcn_readlane((int)hw, 6);
+  const uint64_t total = a.off_pos + a256((uint64_t)PB * M) + v_val_bytes(M, a.val_bits);
+  uint32_t want = hw;
+  const uint32_t word = threadIdx.x & 15u;
 #pragma unroll
   for (int i = 0; i < 16; ++i)
-    if (i < 6 || i > 9) words_ok = words_ok && (uint32_t)__builtin_amdgcn_readlane(hw, i) == a.hdr[i];
-  const uint64_t M = (uint32_t)__builtin_amdgcn_readlane(hw, 6) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hw, 7) << 32);
-  const uint64_t total = (uint32_t)__builtin_amdgcn_readlane(hw, 8) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hw, 9) << 32);
-  *m_out = (uint32_t)M;
-  return words_ok && M <= a.n && total == a.off_pos + a256(a.pos_bytes * M) + v_val_bytes(M, a.val_bits) && total <= a.capacity;
+    if (i != 6) want = word == (uint32_t)i ? (i == 7 ? 0u : i == 8 ? (uint32_t)total : i == 9 ? (uint32_t)(total >> 32) : a.hdr[i]) : want;
+  *m_out = M;
+  return (__ballot(want != hw) == 0) & (M <= a.n) & (total <= a.capacity);
 }
 
 // One block of 1024 elements per wave.  Everything that depends on nothing -- the header, the offsets of the
@@ -638,86 +681,108 @@ __device__ inline bool v_check_header(const VArgs& a, uint32_t hw, uint32_t* m_o
 // table entry.  A block with records goes through an LDS tile, where they are applied a lane each (in the sentinel
 // mode by the lane that holds the sentinel, its exponent from the chunk's first 64 values in LDS); a block without
 // is stored from the registers.  In the absolute mode the correction is left to v_scatter_kernel.
-// One 64 MiB BF16 tensor: 24.1 us under 3-bit codes (32.0 us with the planes picked apart element by element from LDS),
-// 22.3 us in the main format.
+// Bound by the trips to memory of a wave that has one block, and before that by the scalar unit: 300 scalar instructions a
+// wave, 128 waves a CU.  With the sections' addresses in the arguments, offsets kept in lanes and all of the header compared
+// at once it takes, us before and now: a 64 MiB BF16 tensor top-8 22.9 and 20.6 (records ahead: 128 instead of 64, a third of
+// the blocks have more), with chunks of 256 31.6 and 21.2, 4 Mi elements 5.1 and 3.9; 32 Mi elements of E4M3 top-8 with 4-bit
+// values 21.6 and 15.5.  Loads that are given as bounded runs instead took 24.4: a run is five scalar instructions.
 // MANY (sentinel mode): more than a quarter of the elements escaped.  4 Mi random words of BF16, top-15: 9.0 us, against
 // 11.1 one sentinel after the other; 32 Mi of them 40 and 52; but 27.5 and 23.7 with 1 % escapes.
 template <int DT, int CB, int MODE, int CS, bool MANY = false>
-__global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
+__global__ __launch_bounds__(kThreads) void v_decode_kernel(const VDecodeArgs args) {
   using F = VFmt<DT>;
   // escape mode, chunk size and position width are compile-time here: none of the format's choices costs a branch
   constexpr uint32_t PB = MODE == SPLITZIP_ESC_POS ? (CS == 10 ? 2u : 1u) : MODE == SPLITZIP_ESC_ABS32 ? 4u : 0u;
   constexpr uint32_t kPairs = 1u << (2 * CB), kPairMask = kPairs - 1u, per_blk = kVBlock >> CS, chunk = 1u << CS;
+  constexpr uint32_t kAhead = MODE == SPLITZIP_ESC_POS && CS == 10 ? 128 : 64;   // records of a chunk that are asked for before they are counted on
   __shared__ uint32_t tbl[kPairs];
   __shared__ __attribute__((aligned(16))) uint32_t s_tile[kWaves][kVBlock * F::ES / 4];
   __shared__ uint8_t s_val[kWaves][MODE == SPLITZIP_ESC_SENTINEL ? 64 * per_blk : 1];
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-  const uint64_t blk = (uint64_t)blockIdx.x * kWaves + wave;
-  const bool live = blk * kVBlock < a.n, full = (blk + 1) * kVBlock <= a.n;
-  const uint64_t c_first = blk * per_blk;
+  VDecodeArgs a;
+  {
+    // whole and once, as in args_arrived
+    u32x4 x[11];
+    __builtin_memcpy(x, &args, sizeof args);
+    asm volatile("" : "+s"(x[0]), "+s"(x[1]), "+s"(x[2]), "+s"(x[3]), "+s"(x[4]), "+s"(x[5]), "+s"(x[6]), "+s"(x[7]), "+s"(x[8]), "+s"(x[9]), "+s"(x[10]));
+    __builtin_memcpy(&a, x, sizeof args);
+  }
+  const uint8_t* const in = as_global(a.in);
+  uint8_t* const out = as_global(a.out);
+  splitzip_sizes* const sizes = as_global(a.sizes);
+  const uint32_t blk = blockIdx.x * kWaves + wave, n_full = a.n / kVBlock, rest = a.n % kVBlock;
+  const bool full = blk < n_full, live = full || (blk == n_full && rest);
+  const uint32_t in_block = full ? kVBlock : live ? rest : 0u;   // elements of the block
+  const uint32_t c_first = blk * per_blk;
 
-  const uint32_t hw = lane < 16 ? reinterpret_cast<const uint32_t*>(a.in)[lane] : 0u;
-  uint32_t my_off = 0;   // lane q holds the offset of chunk c_first + q
-  if (live && MODE != SPLITZIP_ESC_ABS32 && lane <= per_blk && c_first + lane <= a.n_chunks)
-    my_off = a.offs[c_first + lane];
-  // the block's slices of both planes (the sections are padded, so nothing past them is read)
+  const uint32_t hw = reinterpret_cast<const uint32_t*>(in)[lane & 15u];
+  uint32_t my_off = 0;   // lane q holds the offset of chunk c_first + q, of the last entry at most
+  if (MODE != SPLITZIP_ESC_ABS32) {
+    const uint32_t c = c_first + (lane <= per_blk ? lane : per_blk);
+    my_off = as_global(a.tab)[c < a.n_chunks ? c : a.n_chunks];
+  }
+  // the block's slices of both planes
   uint32_t sm[2][2], cd[2][2];
 #pragma unroll
   for (uint32_t s = 0; s < 2; ++s) {
-    const uint64_t g = blk * kVBlock + s * kVStep;
-    if (full) {
-      v_load_plane<F::SB, true>(a.in + a.off_sm, g / 8 * F::SB, 0, lane, sm[s]);
-      v_load_plane<CB, true>(a.in + a.off_code, g / 8 * CB, 0, lane, cd[s]);
-    } else {
-      v_load_plane<F::SB, false>(a.in + a.off_sm, g / 8 * F::SB, a256(a.sm_bytes), lane, sm[s]);
-      v_load_plane<CB, false>(a.in + a.off_code, g / 8 * CB, a256(a.code_bytes), lane, cd[s]);
-    }
+    v_load_plane<F::SB>(as_global(a.sm), blk * (kVBlock / 8 * F::SB) + s * (kVStep / 8 * F::SB), a.sm_last, lane, sm[s]);
+    v_load_plane<CB>(as_global(a.code), blk * (kVBlock / 8 * CB) + s * (kVStep / 8 * CB), a.code_last, lane, cd[s]);
   }
   // the decode table: both exponents of a pair of codes in place (entries beyond k are zero)
   if (tid < kPairs) {
-    const u32x4 d = v_dec16(a);
+    const u32x4 d = dec16_from(a.dec);
     tbl[tid] = F::pair(dec16_at(d, tid & ((1u << CB) - 1u)), dec16_at(d, tid >> CB));
   }
   uint32_t M;
-  const bool ok = v_check_header(a, hw, &M);
+  const bool ok = v_check_header<PB>(a, hw, &M);
   if (blockIdx.x == 0 && tid == 0) {
-    if (a.sizes) {
-      a.sizes->total_bytes = (uint32_t)__builtin_amdgcn_readlane(hw, 8) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hw, 9) << 32);
-      a.sizes->n_escapes = M;
+    if (sizes) {
+      sizes->total_bytes = (uint32_t)__builtin_amdgcn_readlane(hw, 8) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hw, 9) << 32);
+      sizes->n_escapes = M;
     }
-    if (!ok) v_flag_bad(a);
+    if (!ok) v_flag_bad(sizes);
   }
   lds_barrier();            // the table (an LDS-only barrier: the planes stay on their way)
   if (!ok || !live) return;   // nothing of a stream with a bad header is followed
-  const uint64_t off_val = a.off_pos + a256((uint64_t)PB * M);
+  const uint8_t* const pos_sec = as_global(a.pos);
+  const uint8_t* const val = pos_sec + a256((uint64_t)PB * M);
   constexpr uint32_t sentinel = (1u << CB) - 1u;
   // codes the codebook does not have can only occur if it leaves some unused (wave-uniform: no per-element work otherwise)
   const bool check_codes = a.k + (MODE == SPLITZIP_ESC_SENTINEL ? 1u : 0u) < (1u << CB);
   bool bad = false;
 
-  // the first 64 records of every chunk of the block are fetched now (in the sentinel mode: values without positions)
-  uint32_t rec_p[per_blk], rec_e[per_blk], rec_lo[per_blk], rec_n[per_blk], any = 0;
+  // lane q <-> the block's chunk q: how many elements and how many records it has, no records if its entries are inconsistent
+  // (sentinels are looked at one by one)
+  uint32_t my_n = 0;
+  if (MODE != SPLITZIP_ESC_ABS32) {
+    const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)my_off, 0x101, 0xf, 0xf, false);   // row_shl:1, the entry behind
+    const uint32_t left = in_block - (lane << CS), len = left < chunk ? left : chunk;
+    const bool has = lane < per_blk && (lane << CS) < in_block, valid = next >= my_off && next - my_off <= len && next <= M;
+    if (MODE == SPLITZIP_ESC_POS) bad = has && !valid;
+    my_n = has && (valid || MODE == SPLITZIP_ESC_SENTINEL) ? next - my_off : 0u;
+    my_off = has ? my_off : 0u;
+  }
+  // the first kAhead records of every chunk of the block are asked for now (in the sentinel mode: values without positions)
+  typename VValues<DT>::Loaded rec_e[per_blk][kAhead / 64];
+  uint32_t rec_p[per_blk][kAhead / 64], rec_lo[per_blk], rec_n[per_blk], any = 0;
 #pragma unroll
   for (uint32_t q = 0; q < per_blk; ++q) {
-    rec_p[q] = 0; rec_e[q] = 0; rec_lo[q] = 0; rec_n[q] = 0;
-    if (MODE == SPLITZIP_ESC_ABS32 || c_first + q >= a.n_chunks) continue;
-    const uint32_t lo = __builtin_amdgcn_readlane(my_off, q), hi = __builtin_amdgcn_readlane(my_off, q + 1);
-    const uint64_t first = (c_first + q) << CS, len = first + chunk <= a.n ? chunk : a.n - first;
-    rec_lo[q] = lo;
-    if (hi < lo || hi - lo > len || hi > M) {
-      bad = bad || MODE == SPLITZIP_ESC_POS;   // sentinels are looked at one by one
-      if (MODE == SPLITZIP_ESC_POS) continue;
+    rec_lo[q] = __builtin_amdgcn_readlane(my_off, q);
+    rec_n[q] = __builtin_amdgcn_readlane(my_n, q);
+    if (MODE == SPLITZIP_ESC_ABS32) continue;
+    any |= rec_n[q];
+    uint32_t here = rec_n[q] < kAhead ? rec_n[q] : kAhead;
+    if (MODE == SPLITZIP_ESC_SENTINEL) {   // records beyond M are no part of the stream, and an entry may lie behind the next
+      const uint32_t hi = rec_lo[q] + rec_n[q], to = hi < M ? hi : M;
+      here = to <= rec_lo[q] ? 0u : to - rec_lo[q] < kAhead ? to - rec_lo[q] : kAhead;
     }
-    rec_n[q] = hi - lo;
-    any |= hi - lo;
-    if (MODE == SPLITZIP_ESC_POS) {
-      if (lane < hi - lo) {
-        rec_p[q] = PB == 2 ? reinterpret_cast<const uint16_t*>(a.in + a.off_pos)[lo + lane] : a.in[a.off_pos + lo + lane];
-        rec_e[q] = v_value(a, off_val, lo + lane);
-      }
-    } else if ((uint64_t)lo + lane < hi && (uint64_t)lo + lane < M) {
-      rec_e[q] = v_value(a, off_val, (uint64_t)lo + lane);
+    const auto pr = run_of(pos_sec + (uint64_t)PB * rec_lo[q], PB * here);
+    const VValues<DT> vals(val, a.val_bits, rec_lo[q], here);
+#pragma unroll
+    for (uint32_t r = 0; r < kAhead / 64; ++r) {
+      rec_p[q][r] = PB == 2 ? ld_run2(pr, 2u * lane + 128u * r) : PB == 1 ? ld_run1(pr, lane + 64u * r) : 0u;
+      rec_e[q][r] = vals.at(lane + 64u * r);
     }
   }
 
@@ -727,7 +792,7 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
   for (uint32_t s = 0; s < 2; ++s) {
     v_plane_fields<F::SB>(sm[s], lane);
     v_plane_fields<CB>(cd[s], lane);
-    const uint32_t c = cd[s][0], nv = full ? 8u : v_nvalid(a, blk * kVBlock + s * kVStep + lane * 8);
+    const uint32_t c = cd[s][0], from = s * kVStep + lane * 8, nv = in_block <= from ? 0u : in_block - from < 8 ? in_block - from : 8u;   // of the lane's elements
     F::unpack(sm[s], o[s]);
 #pragma unroll
     for (uint32_t b = 0; b < 4; ++b) {
@@ -754,7 +819,7 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
   // chunk's first 64 come from memory.
   if constexpr (MANY) {
 #pragma unroll
-    for (uint32_t q = 0; q < per_blk; ++q) s_val[wave][64 * q + lane] = (uint8_t)rec_e[q];
+    for (uint32_t q = 0; q < per_blk; ++q) s_val[wave][64 * q + lane] = (uint8_t)VValues<DT>(val, a.val_bits, rec_lo[q], 0).of(rec_e[q][0], lane);
     v_lds_settle();
     uint32_t carry = 0;
 #pragma unroll
@@ -772,14 +837,14 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
       } else {
         carry = tot;
       }
-      const uint64_t hi = c_first + q < a.n_chunks ? (uint64_t)(uint32_t)(lo + n_q) : 0u;   // the offset behind the chunk's
+      const uint64_t hi = c_first + q < a.n_chunks ? lo + n_q : 0u;   // the offset behind the chunk's
       uint32_t e[8];
 #pragma unroll
       for (uint32_t j = 0; j < 8; ++j) {
         e[j] = 0;
         if ((sent[s] >> (CB * j)) & 1u) {
           const uint64_t r = (uint64_t)(uint32_t)(lo + rank);
-          if (r < hi && r < M) e[j] = rank < 64 && r >= lo ? (uint32_t)s_val[wave][64 * q + rank] : v_value(a, off_val, r);
+          if (r < hi && r < M) e[j] = rank < 64 && r >= lo ? (uint32_t)s_val[wave][64 * q + rank] : v_value(val, a.val_bits, r);
           else bad = true;
           ++rank;
         }
@@ -813,7 +878,7 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
     };
     if (MODE == SPLITZIP_ESC_SENTINEL && !MANY) {
 #pragma unroll
-      for (uint32_t q = 0; q < per_blk; ++q) s_val[wave][64 * q + lane] = (uint8_t)rec_e[q];
+      for (uint32_t q = 0; q < per_blk; ++q) s_val[wave][64 * q + lane] = (uint8_t)VValues<DT>(val, a.val_bits, rec_lo[q], 0).of(rec_e[q][0], lane);
     }
     v_lds_settle();
     if (MODE == SPLITZIP_ESC_SENTINEL && !MANY) {
@@ -833,14 +898,14 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
         } else {
           carry = tot;
         }
-        const uint64_t hi = c_first + q < a.n_chunks ? (uint64_t)(uint32_t)(lo + n_q) : 0u;   // the offset behind the chunk's
+        const uint64_t hi = c_first + q < a.n_chunks ? lo + n_q : 0u;   // the offset behind the chunk's
         uint32_t m = sent[s];
         while (m) {
           const uint32_t bit = (uint32_t)__ffs(m) - 1u, j = CB == 4 ? bit >> 2 : (bit * 11u) >> 5;   // bit / CB
           m &= m - 1;
           const uint64_t r = (uint64_t)(uint32_t)(lo + rank);
           uint32_t e = 0;
-          if (r < hi && r < M) e = rank < 64 && r >= lo ? (uint32_t)s_val[wave][64 * q + rank] : v_value(a, off_val, r);
+          if (r < hi && r < M) e = rank < 64 && r >= lo ? (uint32_t)s_val[wave][64 * q + rank] : v_value(val, a.val_bits, r);
           else bad = true;
           if (e >= (uint32_t)F::EXPS) { bad = true; e = 0; }
           patch(s * kVStep + lane * 8 + j, e);
@@ -853,18 +918,30 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
 #pragma unroll
       for (uint32_t q = 0; q < per_blk; ++q) {
         if (rec_n[q] == 0) continue;
-        const uint64_t first = (c_first + q) << CS, len = first + chunk <= a.n ? chunk : a.n - first;
-        for (uint32_t i = lane; i < rec_n[q]; i += 64) {
-          uint32_t p = rec_p[q], e = rec_e[q];
-          if (i >= 64) {   // a chunk with more than 64 escapes: the rest is fetched here
-            p = PB == 2 ? reinterpret_cast<const uint16_t*>(a.in + a.off_pos)[rec_lo[q] + i] : a.in[a.off_pos + rec_lo[q] + i];
-            e = v_value(a, off_val, rec_lo[q] + i);
-          }
-          // a chunk's positions ascend: the record before this one (the lane below holds it, or memory does)
-          uint32_t before = (uint32_t)__shfl_up((int)p, 1);
-          if (lane == 0 && i > 0) before = PB == 2 ? reinterpret_cast<const uint16_t*>(a.in + a.off_pos)[rec_lo[q] + i - 1] : a.in[a.off_pos + rec_lo[q] + i - 1];
-          if (p >= len || (i > 0 && p <= before) || e >= (uint32_t)F::EXPS) { bad = true; continue; }
-          patch(q * chunk + p, e);
+        const uint32_t left = in_block - (q << CS), len = left < chunk ? left : chunk;
+        // a chunk's positions ascend: each must lie above the one before it
+        auto apply = [&](uint32_t i, uint32_t p, uint32_t before, uint32_t e) {
+          if (i >= rec_n[q]) return;
+          if (p >= len || (i > 0 && p <= before) || e >= (uint32_t)F::EXPS) bad = true;
+          else patch(q * chunk + p, e);
+        };
+        uint32_t carry = 0;   // the position in front of a round's first
+        const VValues<DT> ahead(val, a.val_bits, rec_lo[q], 0);
+#pragma unroll
+        for (uint32_t r = 0; r < kAhead / 64; ++r) {
+          if (r > 0 && rec_n[q] <= 64 * r) break;
+          apply(64 * r + lane, rec_p[q][r], lane_before(rec_p[q][r], carry), ahead.of(rec_e[q][r], 64 * r + lane));
+          carry = (uint32_t)__builtin_amdgcn_readlane(rec_p[q][r], 63);
+        }
+        // the others, 64 at a time
+#pragma unroll 1
+        for (uint32_t i0 = kAhead; i0 < rec_n[q]; i0 += 64) {
+          const uint32_t lo = rec_lo[q] + i0, left = rec_n[q] - i0;
+          const auto pr = run_of(pos_sec + (uint64_t)PB * lo, PB * left);
+          const VValues<DT> vals(val, a.val_bits, lo, left);
+          const uint32_t p = PB == 2 ? ld_run2(pr, 2u * lane) : ld_run1(pr, lane), e = vals.of(vals.at(lane), lane);
+          apply(i0 + lane, p, lane_before(p, carry), e);
+          carry = (uint32_t)__builtin_amdgcn_readlane(p, 63);
         }
       }
     }
@@ -881,36 +958,36 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VArgs a) {
     }
   }
 
-  const uint64_t e0 = blk * kVBlock;
+  uint8_t* const dst = out + (uint64_t)F::ES * kVBlock * blk;
   if (full) {
 #pragma unroll
     for (uint32_t s = 0; s < 2; ++s) {
-      if (F::ES == 2) st_stream(reinterpret_cast<u32x4*>(a.out + 2 * e0) + s * 64 + lane, u32x4{o[s][0], o[s][1], o[s][F::NW - 2], o[s][F::NW - 1]});
-      else st_stream(reinterpret_cast<u32x2*>(a.out + e0) + s * 64 + lane, u32x2{o[s][0], o[s][1]});
+      if (F::ES == 2) st_stream(reinterpret_cast<u32x4*>(dst) + s * 64 + lane, u32x4{o[s][0], o[s][1], o[s][F::NW - 2], o[s][F::NW - 1]});
+      else st_stream(reinterpret_cast<u32x2*>(dst) + s * 64 + lane, u32x2{o[s][0], o[s][1]});
     }
   } else {
-    for (uint32_t i = lane; e0 + i < a.n; i += 64) {
-      if (F::ES == 2) reinterpret_cast<uint16_t*>(a.out)[e0 + i] = reinterpret_cast<const uint16_t*>(tile)[i];
-      else a.out[e0 + i] = reinterpret_cast<const uint8_t*>(tile)[i];
+#pragma unroll 1
+    for (uint32_t i = lane; i < rest; i += 64) {
+      if (F::ES == 2) reinterpret_cast<uint16_t*>(dst)[i] = reinterpret_cast<const uint16_t*>(tile)[i];
+      else dst[i] = reinterpret_cast<const uint8_t*>(tile)[i];
     }
   }
-  if (bad) v_flag_bad(a);
+  if (bad) v_flag_bad(sizes);
 }
 
 // absolute mode: every record overwrites the exponent field of its element (runs after v_decode_kernel)
 template <int DT>
-__global__ __launch_bounds__(kThreads) void v_scatter_kernel(const VArgs a) {
+__global__ __launch_bounds__(kThreads) void v_scatter_kernel(const VDecodeArgs a) {
   using F = VFmt<DT>;
-  const int lane = threadIdx.x & 63;
   uint32_t M;
-  if (!v_check_header(a, lane < 16 ? reinterpret_cast<const uint32_t*>(a.in)[lane] : 0u, &M)) return;
-  const uint64_t off_val = a.off_pos + a256(4ull * M);
+  if (!v_check_header<4>(a, reinterpret_cast<const uint32_t*>(a.in)[threadIdx.x & 15], &M)) return;
+  const uint32_t* pos = reinterpret_cast<const uint32_t*>(a.pos);
+  const uint8_t* val = a.pos + a256(4ull * M);
   bool bad = false;
   for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < M; i += (uint64_t)gridDim.x * kThreads) {
-    const uint64_t p = reinterpret_cast<const uint32_t*>(a.in + a.off_pos)[i];
-    const uint32_t e = v_value(a, off_val, i);
+    const uint32_t p = pos[i], e = v_value(val, a.val_bits, i);
     // the element indices ascend
-    if (p >= a.n || e >= (uint32_t)F::EXPS || (i > 0 && p <= reinterpret_cast<const uint32_t*>(a.in + a.off_pos)[i - 1])) { bad = true; continue; }
+    if (p >= a.n || e >= (uint32_t)F::EXPS || (i > 0 && p <= pos[i - 1])) { bad = true; continue; }
     if (F::ES == 2) {
       uint16_t* t = reinterpret_cast<uint16_t*>(a.out) + p;
       *t = (uint16_t)F::combine(F::signmant(*t), e);
@@ -918,7 +995,7 @@ __global__ __launch_bounds__(kThreads) void v_scatter_kernel(const VArgs a) {
       a.out[p] = (uint8_t)F::combine(F::signmant(a.out[p]), e);
     }
   }
-  if (bad) v_flag_bad(a);
+  if (bad) v_flag_bad(a.sizes);
 }
 
 #endif  // SPLITZIP_VARIANTS_HPP
