@@ -126,9 +126,11 @@ __device__ inline __amdgpu_buffer_rsrc_t run_of(const uint8_t* base, uint32_t by
   // register makes a loop around every access)
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
-__device__ inline u32x4 ld_run16(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(run, off, 0, kStream); }
+template <int CACHE = kStream>
+__device__ inline u32x4 ld_run16(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(run, off, 0, CACHE); }
 __device__ inline u32x2 ld_run8(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b64(run, off, 0, kStream); }
-__device__ inline uint32_t ld_run4(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b32(run, off, 0, kStream); }
+template <int CACHE = kStream>
+__device__ inline uint32_t ld_run4(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b32(run, off, 0, CACHE); }
 __device__ inline uint16_t ld_run2(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b16(run, off, 0, 0); }
 __device__ inline uint8_t ld_run1(__amdgpu_buffer_rsrc_t run, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b8(run, off, 0, 0); }
 template <typename T>

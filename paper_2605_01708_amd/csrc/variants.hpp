@@ -139,6 +139,24 @@ __device__ inline u32x4 v_dec16(const VArgs& a) {
   return u32x4{w[0], w[1], w[2], w[3]};
 }
 
+// A compress kernel's own copy of the arguments, those it needs fetched at once (as in args_arrived): the compiler would
+// fetch each where it is used first, half a dozen trips one after the other in a kernel of a few microseconds.
+__device__ inline VArgs v_args_arrived(const VArgs& args) {
+  VArgs a = args;
+  asm volatile("" : "+s"(a.in), "+s"(a.out), "+s"(a.capacity), "+s"(a.n), "+s"(a.k), "+s"(a.mode), "+s"(a.chunk_shift), "+s"(a.val_bits), "+s"(a.val_stage),
+               "+s"(a.n_chunks), "+s"(a.off_sm), "+s"(a.off_code), "+s"(a.off_pos), "+s"(a.counts), "+s"(a.offs), "+s"(a.slots));
+  asm volatile("" : "+s"(a.wg_sums), "+s"(a.sums), "+s"(a.n_sums), "+s"(a.sum_shift), "+s"(a.ahead), "+s"(a.escape_code));
+  a.in = as_global(a.in);
+  a.out = as_global(a.out);
+  a.val_stage = as_global(a.val_stage);
+  a.counts = as_global(a.counts);
+  a.offs = as_global(a.offs);
+  a.slots = as_global(a.slots);
+  a.wg_sums = as_global(a.wg_sums);
+  a.sums = as_global(a.sums);
+  return a;
+}
+
 // how many of the eight elements starting at g0 exist (the valid ones are always a prefix of the group)
 __device__ inline uint32_t v_nvalid(const VArgs& a, uint64_t g0) {
   return g0 >= a.n ? 0u : (a.n - g0 < 8 ? (uint32_t)(a.n - g0) : 8u);
@@ -422,92 +440,100 @@ struct VSink {
 
 // Compress pass 3: one workgroup per kVFinishBlocks blocks.  It sums the counts (the whole tensor's: M; those before
 // its blocks: its first rank), writes its chunks' entries of the offset table, and moves its blocks' records from
-// their slots to their ranks, a wave per block and eight blocks per wave: nothing but trips to memory, so the first
-// a.ahead records of every block are asked for before the counts are there and the others all at once behind them.
-// A block with more records than its slot holds is encoded once more from the words.  (Ranks searched and records
-// fetched one at a time per thread took 17.2 us for the two million records of a 64 MiB tensor under a top-8 codebook;
-// this takes 9.4 us, and 7.1 us with 0.1 % escapes.)
+// their slots to their ranks, a wave per block and eight blocks per wave: nothing but trips to memory, so the arguments, the
+// counts of the wave's blocks, the first a.ahead records of every block and the sums are asked for at once; the others as
+// soon as the wave's own counts are there, all before the one barrier.
+// A block with more records than its slot holds is encoded once more from the words.  (For the two million records of a
+// 64 MiB tensor under a top-8 codebook 9.2 us when the counts went through LDS and every load stood behind a condition --
+// each was waited for before the next was asked for -- and 7.0 now; 6.4 and 5.3 with 0.1 % escapes.)
 // Workgroup 0 also writes the header, the sizes record and the zero padding.
 template <int DT, int PB>
-__global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs a) {
+__global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs args) {
   using F = VFmt<DT>;
+  const VArgs a = v_args_arrived(args);
   constexpr uint32_t kPerWave = kVFinishBlocks / kWaves;
   __shared__ uint32_t lut[256];
   __shared__ uint32_t s_part[3][kWaves];
-  __shared__ uint32_t s_bp[kVFinishBlocks + 1];   // escapes of the group's blocks before each block
   const uint32_t tid = threadIdx.x, lane = tid & 63, g = blockIdx.x;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   const uint32_t cpb_shift = 10u - a.chunk_shift;   // log2 of the chunks per block: 0 or 2
-  const uint64_t n_blocks = (a.n + kVBlock - 1) / kVBlock;
-  const uint64_t blk0 = (uint64_t)g * kVFinishBlocks, c0 = blk0 << cpb_shift;
-  const uint64_t blocks_here = n_blocks > blk0 ? (n_blocks - blk0 < kVFinishBlocks ? n_blocks - blk0 : kVFinishBlocks) : 0;
+  const uint32_t n_blocks = (uint32_t)((a.n + kVBlock - 1) / kVBlock);
+  const uint32_t blk0 = g * kVFinishBlocks + wave * kPerWave;   // the wave's first block
+  const uint32_t blocks_here = n_blocks > blk0 ? (n_blocks - blk0 < kPerWave ? n_blocks - blk0 : kPerWave) : 0;
+  const uint64_t c0 = (uint64_t)g * kVFinishBlocks << cpb_shift;   // the group's first chunk
+  // Every load is one of a bounded run, at an offset beyond its end where a lane wants none: behind conditions, the first
+  // use of each was waited for before the next was asked for.
+  constexpr uint32_t kNone = 0xfffffff0u;
+  // the wave's chunks, one per lane (8 or 32 of them), then the first records of its blocks
+  const uint64_t my_c = ((uint64_t)blk0 << cpb_shift) + lane;
+  const bool have = lane < (kPerWave << cpb_shift) && my_c < a.n_chunks;
+  const uint32_t mine = ld_run4<0>(run_of(reinterpret_cast<const uint8_t*>(a.counts), 4u * (uint32_t)a.n_chunks), have ? 4u * (uint32_t)my_c : kNone);
   uint32_t rec[kPerWave], rec2[kPerWave];
+  const uint32_t* const slots = a.slots + (uint64_t)blk0 * kVSlotCap;
+  const auto slot_run = run_of(reinterpret_cast<const uint8_t*>(slots), 4u * kVSlotCap * blocks_here);
+  const uint32_t first_off = lane < a.ahead ? 4u * lane : kNone;
 #pragma unroll
-  for (uint32_t q = 0; q < kPerWave; ++q) {
-    const uint32_t b = wave * kPerWave + q;
-    rec[q] = b < blocks_here && lane < a.ahead ? a.slots[(blk0 + b) * kVSlotCap + lane] : 0u;
-  }
-  // the group's chunks, one per thread (32 or 128 of them)
-  const uint64_t my_c = c0 + tid;
-  const bool have = tid < (kVFinishBlocks << cpb_shift) && my_c < a.n_chunks;
-  const uint32_t mine = have ? a.counts[my_c] : 0u;
+  for (uint32_t q = 0; q < kPerWave; ++q) rec[q] = ld_run4<0>(slot_run, first_off == kNone ? kNone : first_off + 4u * kVSlotCap * q);
   // escapes before the group's first chunk and in the whole tensor: by the sums that lie before it entirely, the rest by chunk
   uint32_t before = 0, all = 0;
   const uint64_t whole = c0 >> a.sum_shift;
-  const u32x4* sv = reinterpret_cast<const u32x4*>(a.sums);   // 16-byte aligned; what the last vector holds behind the sums is zero
+  // 16-byte aligned; what the last vector holds behind the sums is zero
   const uint32_t nvec = (a.n_sums + 3) / 4, v_first = (uint32_t)(whole / 4);
-  for (uint32_t v0 = 0; v0 < nvec; v0 += 4 * kThreads) {
-    u32x4 v[4];
+  const auto sum_run = run_of(reinterpret_cast<const uint8_t*>(a.sums), 16u * nvec);
+  u32x4 v[4];
+  auto fetch = [&](uint32_t v0) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const uint32_t idx = v0 + q * kThreads + tid;
-      v[q] = idx < nvec ? sv[idx] : u32x4{0u, 0u, 0u, 0u};
+      v[q] = ld_run16<0>(sum_run, 16u * (v0 + q * kThreads + tid));
     }
+  };
+  fetch(0);
+  v_build_encode_table(a, lut, tid);
+  // what the wave's chunks hold before each lane's, and with it where each of its blocks starts: the rest of their records
+  // is asked for at once as well (top-8: a block in three has more than 64)
+  const uint32_t incl = wave_incl_scan(mine), wave_total = wave_last(incl), my_excl = incl - mine;
+  auto starts = [&](uint32_t q) { return q < kPerWave ? (uint32_t)__builtin_amdgcn_readlane(my_excl, q << cpb_shift) : wave_total; };
+  uint32_t bp[kPerWave + 1];   // wave-uniform: escapes of the wave's blocks before each block
+#pragma unroll
+  for (uint32_t q = 0; q <= kPerWave; ++q) bp[q] = starts(q);
+#pragma unroll
+  for (uint32_t q = 0; q < kPerWave; ++q) {
+    const uint32_t n_b = bp[q + 1] - bp[q], i = a.ahead + lane;
+    rec2[q] = ld_run4<0>(slot_run, n_b <= kVSlotCap && i < n_b ? 4u * (kVSlotCap * q + i) : kNone);
+  }
+  for (uint32_t v0 = 0;;) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const uint32_t sum = v[q].x + v[q].y + v[q].z + v[q].w;
       all += sum;
       before += v0 + q * kThreads + tid < v_first ? sum : 0u;
     }
+    v0 += 4 * kThreads;
+    if (v0 >= nvec) break;
+    fetch(v0);
   }
   if (tid < (whole & 3u)) before += a.sums[4 * v_first + tid];   // sums of the vector that the group starts in
   for (uint64_t c = (whole << a.sum_shift) + tid; c < c0 && c < a.n_chunks; c += kThreads) before += a.counts[c];
-  const uint32_t incl = wave_incl_scan(mine);
   before = wave_last(wave_incl_scan(before));
   all = wave_last(wave_incl_scan(all));
   if (lane == 63) {
-    s_part[0][wave] = incl;
+    s_part[0][wave] = wave_total;
     s_part[1][wave] = before;
     s_part[2][wave] = all;
   }
   __syncthreads();
-  uint32_t first = 0, M = 0, waves_before = 0, group_total = 0;
+  uint32_t first = 0, M = 0;   // the rank of the wave's first record; all records of the tensor
 #pragma unroll
   for (uint32_t w = 0; w < kWaves; ++w) {
-    waves_before += w < wave ? s_part[0][w] : 0u;
-    group_total += s_part[0][w];
-    first += s_part[1][w];
+    first += s_part[1][w] + (w < wave ? s_part[0][w] : 0u);
     M += s_part[2][w];
   }
-  const uint32_t excl = waves_before + incl - mine;   // escapes of the group before this thread's chunk
-  if (have && (tid & ((1u << cpb_shift) - 1u)) == 0) s_bp[tid >> cpb_shift] = excl;
-  // blocks behind the tensor's last start where the group ends
-  if (tid >= blocks_here && tid <= kVFinishBlocks) s_bp[tid] = group_total;
-  v_build_encode_table(a, lut, tid);
-  __syncthreads();
-  if (have && a.mode != SPLITZIP_ESC_ABS32) a.offs[my_c] = first + excl;
+  first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+  M = (uint32_t)__builtin_amdgcn_readfirstlane((int)M);
+  if (have && a.mode != SPLITZIP_ESC_ABS32) a.offs[my_c] = first + my_excl;
   const VSink<PB> sink(a, M);
 
-  uint32_t bp[kPerWave + 1];   // wave-uniform: the wave's blocks
-#pragma unroll
-  for (uint32_t q = 0; q <= kPerWave; ++q) bp[q] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_bp[wave * kPerWave + q]);
-#pragma unroll
-  for (uint32_t q = 0; q < kPerWave; ++q) {
-    const uint32_t n_b = bp[q + 1] - bp[q], i = a.ahead + lane;
-    rec2[q] = 0;
-    if (n_b <= kVSlotCap && i < n_b) rec2[q] = a.slots[(blk0 + wave * kPerWave + q) * kVSlotCap + i];
-  }
-  const uint32_t elem0 = (uint32_t)(blk0 + wave * kPerWave) * kVBlock;   // fewer than 2^32 elements
+  const uint32_t elem0 = blk0 * kVBlock;   // fewer than 2^32 elements
   uint32_t many = 0;   // a block with more records than the two fetches took, or more than its slot holds
 #pragma unroll
   for (uint32_t q = 0; q < kPerWave; ++q) {
@@ -521,21 +547,23 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs a) {
   if (many) {
 #pragma unroll 1
     for (uint32_t q = 0; q < kPerWave; ++q) {
-      const uint32_t b = wave * kPerWave + q, from = s_bp[b], n_b = s_bp[b + 1] - from;
+      const uint32_t from = starts(q), n_b = starts(q + 1) - from;
       if (n_b > kVSlotCap) continue;
+#pragma unroll 1
       for (uint32_t i = a.ahead + 64 + lane; i < n_b; i += 64) {
-        const uint32_t r = a.slots[(blk0 + b) * kVSlotCap + i];
+        const uint32_t r = slots[q * kVSlotCap + i];
         sink.put(first + from + i, elem0 + q * kVBlock + (r & 0xffffu), r >> 16);
       }
     }
     // blocks whose records did not fit their slots
 #pragma unroll 1
-    for (uint32_t b = wave * kPerWave; b < (wave + 1) * kPerWave && b < blocks_here; ++b) {
-      if (s_bp[b + 1] - s_bp[b] <= kVSlotCap) continue;
-      uint32_t rank = first + s_bp[b];
+    for (uint32_t q = 0; q < blocks_here; ++q) {
+      const uint32_t from = starts(q);
+      if (starts(q + 1) - from <= kVSlotCap) continue;
+      uint32_t rank = first + from;
 #pragma unroll 1
       for (uint32_t s = 0; s < 2; ++s) {
-        const uint64_t g0 = (blk0 + b) * kVBlock + s * kVStep + lane * 8;
+        const uint64_t g0 = (uint64_t)(blk0 + q) * kVBlock + s * kVStep + lane * 8;
         uint32_t w[F::NW];
         v_load8<DT, false>(a, g0, w);
         uint32_t esc = 0;
@@ -561,13 +589,13 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs a) {
   // zero padding: behind the table, behind what the dense pass covered of each plane, behind the positions
   const uint64_t tab_end = a.mode == SPLITZIP_ESC_ABS32 ? kHeaderBytes : a.off_tab + 4 * (a.n_chunks + 1);
   for (uint64_t i = tab_end + tid; i < a.off_sm; i += kThreads) a.out[i] = 0;
-  const uint64_t sm_cov = n_blocks * (kVBlock / 8) * v_sm_bits(a.dtype), code_cov = n_blocks * (kVBlock / 8) * a.code_bits;
+  const uint64_t sm_cov = (uint64_t)n_blocks * (kVBlock / 8) * v_sm_bits(a.dtype), code_cov = (uint64_t)n_blocks * (kVBlock / 8) * a.code_bits;
   for (uint64_t i = sm_cov + tid; i < a256(a.sm_bytes); i += kThreads) a.out[a.off_sm + i] = 0;
   for (uint64_t i = code_cov + tid; i < a256(a.code_bytes); i += kThreads) a.out[a.off_code + i] = 0;
   for (uint64_t i = (uint64_t)a.pos_bytes * M + tid; i < pos_sec; i += kThreads)
     if (a.off_pos + i < a.capacity) a.out[a.off_pos + i] = 0;
   if (tid < 16) {
-    uint32_t w = a.hdr[tid];
+    uint32_t w = args.hdr[tid];
     if (tid == 6) w = M;
     if (tid == 8) w = (uint32_t)total;
     if (tid == 9) w = (uint32_t)(total >> 32);
