@@ -672,16 +672,16 @@ __global__ __launch_bounds__(64) void tile_group_sum_kernel(const TileArgs<N> ar
   if (threadIdx.x == 0) G.group_sums[g] = sum;
 }
 
-template <typename F, uint32_t N>
-__global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const TileArgs<N> args) {
+template <typename F, uint32_t N, uint32_t GROUPS>
+__global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const TileArgs<N> args) {
   constexpr int NW = kTileThreads / 64;
-  static_assert(kFinishMost <= NW, "one wave scans the counts of one group");
+  static_assert(GROUPS <= kFinishMost && kFinishMost <= NW, "one wave scans the counts of one group");
   __shared__ uint16_t lut[256];
   __shared__ u32x4 s_park[kTileThreads];
-  __shared__ uint32_t s_cnt[kFinishMost][kGroup];       // the counts of the groups' tiles, redo mark included
-  __shared__ uint32_t s_tp[kFinishMost][kGroup + 1];    // escapes of a group's tiles before each tile
+  __shared__ uint32_t s_cnt[GROUPS][kGroup];       // the counts of the groups' tiles, redo mark included
+  __shared__ uint32_t s_tp[GROUPS][kGroup + 1];    // escapes of a group's tiles before each tile
   __shared__ uint32_t s_red[2 * NW];
-  __shared__ uint32_t s_mark[kFinishMost];              // kMore: a group has a tile with more records than were fetched ahead; kRedo: one that is encoded again
+  __shared__ uint32_t s_mark[GROUPS];              // kMore: a group has a tile with more records than were fetched ahead; kRedo: one that is encoded again
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t item = blockIdx.y;
@@ -691,12 +691,12 @@ __global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const 
   const TileGeom G = tile_geom(a, it, item, F::DT);
   const Planes& P = G.P;
   const uint32_t n_groups = (G.n_tiles + kGroup - 1) / kGroup;
-  // the workgroup's groups: [g0, g0 + ng) -- a.finish_groups of them in a row (1 to kFinishMost: a launch of many
+  // the workgroup's groups: [g0, g0 + ng) -- GROUPS of them in a row (1 to kFinishMost: a launch of many
   // groups gives every workgroup several, so that fewer rounds of workgroups pass through the chip; each round
   // costs the same few trips to memory whatever it carries)
-  const uint32_t g0 = blockIdx.x * a.finish_groups;
+  const uint32_t g0 = blockIdx.x * GROUPS;
   if (g0 >= (n_groups ? n_groups : 1u)) return;   // a tensor without elements still gets its header
-  const uint32_t ng = n_groups - g0 < a.finish_groups ? (n_groups > g0 ? n_groups - g0 : 1u) : a.finish_groups;
+  const uint32_t ng = n_groups - g0 < GROUPS ? (n_groups > g0 ? n_groups - g0 : 1u) : GROUPS;
   uint32_t* park = reinterpret_cast<uint32_t*>(&s_park[tid]);
   uint32_t* tab = reinterpret_cast<uint32_t*>(P.out + P.off_tab);
   const uint32_t group_entries = kGroup << a.tile_shift;
@@ -704,25 +704,53 @@ __global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const 
   // Everything whose address does not depend on the counts is fetched at once: the counts themselves, the
   // groups' table entries (one per thread and group, or a few) and the first 2 kSlotAhead records of every tile's slot
   // (two per thread: hardly a tile has more, so hardly a workgroup has to go to memory once more after the barrier).
+  // No load stands behind a condition: each is one of a bounded run, at an offset beyond its end where a thread wants none
+  // (guarded one by one, each by a few scalar instructions and a branch, and with a condition per group where the groups
+  // are the kernel's own now, a call took 0.4 us more: BF16, 128 chunks 5.83 and 5.44, 16 384 16.3 and 15.7; E5M2, 4096
+  // chunks 7.56 and 7.14).
+  constexpr uint32_t kNone = 0xfffffff0u;
+  const uint32_t t_first = g0 * kGroup, c_first = t_first << a.tile_shift;   // the workgroup's first tile and chunk
+  const uint32_t tiles_here = G.n_tiles > t_first ? (G.n_tiles - t_first < GROUPS * kGroup ? G.n_tiles - t_first : GROUPS * kGroup) : 0u;
+  const uint32_t chunks_here = P.n_chunks > c_first ? (P.n_chunks - c_first < GROUPS * group_entries ? P.n_chunks - c_first : GROUPS * group_entries) : 0u;
   // wave q: the counts of the tiles of group q
-  const uint32_t t_mine = (g0 + (uint32_t)wave) * kGroup + lane;
-  const uint32_t c_mine = (uint32_t)wave < ng && (uint32_t)lane < kGroup && t_mine < G.n_tiles ? G.counts[t_mine] : 0u;
-  const uint32_t sl = (uint32_t)tid / kSlotAhead, sj = (uint32_t)tid % kSlotAhead;   // tile of a group, record of the tile
-  uint32_t my_entry[kFinishMost], rec_ahead[kFinishMost], rec_ahead2[kFinishMost];
+  const auto count_run = run_of(reinterpret_cast<const uint8_t*>(G.counts + t_first), 4u * tiles_here);
+  const uint32_t c_mine = ld_run4<0>(count_run, (uint32_t)wave < GROUPS && (uint32_t)lane < kGroup ? 4u * ((uint32_t)wave * kGroup + lane) : kNone);
+  // All counts, four per load, four loads per thread on their way at a time (they start 256-byte aligned, the dense pass has
+  // cleared what the last vector holds behind them, and the first group's tiles start with a vector); none if there are
+  // sums of them.
+  const uint32_t nvec = a.use_group_sums ? 0u : (G.n_tiles + 3) / 4, v_first = t_first / 4;
+  const auto vec_run = run_of(reinterpret_cast<const uint8_t*>(G.counts), 16u * nvec);
+  u32x4 v[4];
+  auto fetch = [&](uint32_t v0) {
 #pragma unroll
-  for (uint32_t q = 0; q < kFinishMost; ++q) {
-    my_entry[q] = 0;
-    rec_ahead[q] = 0;
-    rec_ahead2[q] = 0;
-    if (q < ng) {
-      const uint32_t t0 = (g0 + q) * kGroup, c0 = t0 << a.tile_shift;
-      if (c0 + tid < P.n_chunks && (uint32_t)tid < group_entries) my_entry[q] = tab[c0 + tid];
-      if (t0 + sl < G.n_tiles && sj < a.slot_cap) rec_ahead[q] = G.slots[(uint64_t)(t0 + sl) * a.slot_cap + sj];
-      if (t0 + sl < G.n_tiles && sj + kSlotAhead < a.slot_cap) rec_ahead2[q] = G.slots[(uint64_t)(t0 + sl) * a.slot_cap + sj + kSlotAhead];
+    for (int q = 0; q < 4; ++q) v[q] = ld_run16<0>(vec_run, 16u * (v0 + q * kTileThreads + tid));
+  };
+  fetch(0);
+  const uint32_t sl = (uint32_t)tid / kSlotAhead, sj = (uint32_t)tid % kSlotAhead;   // tile of a group, record of the tile
+  uint32_t my_entry[GROUPS], rec_ahead[GROUPS], rec_ahead2[GROUPS];
+  {
+    const auto tab_run = run_of(reinterpret_cast<const uint8_t*>(tab + c_first), 4u * chunks_here);
+    const auto slot_run = run_of(reinterpret_cast<const uint8_t*>(G.slots + (uint64_t)t_first * a.slot_cap), 4u * a.slot_cap * tiles_here);
+#pragma unroll
+    for (uint32_t q = 0; q < GROUPS; ++q) {
+      const uint32_t rec = 4u * ((q * kGroup + sl) * a.slot_cap + sj);
+      my_entry[q] = ld_run4<0>(tab_run, (uint32_t)tid < group_entries ? 4u * (q * group_entries + tid) : kNone);
+      rec_ahead[q] = ld_run4<0>(slot_run, sj < a.slot_cap ? rec : kNone);
+      rec_ahead2[q] = ld_run4<0>(slot_run, sj + kSlotAhead < a.slot_cap ? rec + 4u * kSlotAhead : kNone);
     }
   }
-  const uint32_t t_first = g0 * kGroup;   // the first tile of the workgroup's first group
   uint32_t before = 0, all = 0;
+  for (uint32_t v0 = 0;;) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t sum = (v[q].x & ~kRedo) + (v[q].y & ~kRedo) + (v[q].z & ~kRedo) + (v[q].w & ~kRedo);
+      all += sum;
+      before += v0 + q * kTileThreads + tid < v_first ? sum : 0u;
+    }
+    v0 += 4 * kTileThreads;
+    if (v0 >= nvec) break;
+    fetch(v0);
+  }
   if (a.use_group_sums) {
     const uint32_t n_sums = (G.n_tiles + kSumGroup - 1) / kSumGroup, whole = t_first / kSumGroup;   // sums that lie before the first group entirely
     for (uint32_t i = tid; i < n_sums; i += kTileThreads) {
@@ -731,25 +759,6 @@ __global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const 
       before += i < whole ? c : 0u;
     }
     for (uint32_t i = whole * kSumGroup + tid; i < t_first; i += kTileThreads) before += G.counts[i] & ~kRedo;
-  } else {
-    // four counts per load, four loads per thread on their way at a time (the counts start 256-byte aligned, the dense
-    // pass has cleared what the last vector holds behind them, and the first group's tiles start with a vector)
-    const u32x4* cv = reinterpret_cast<const u32x4*>(G.counts);
-    const uint32_t nvec = (G.n_tiles + 3) / 4, v_first = t_first / 4;
-    for (uint32_t v0 = 0; v0 < nvec; v0 += 4 * kTileThreads) {
-      u32x4 v[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t idx = v0 + q * kTileThreads + tid;
-        v[q] = idx < nvec ? cv[idx] : u32x4{0u, 0u, 0u, 0u};
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t sum = (v[q].x & ~kRedo) + (v[q].y & ~kRedo) + (v[q].z & ~kRedo) + (v[q].w & ~kRedo);
-        all += sum;
-        before += v0 + q * kTileThreads + tid < v_first ? sum : 0u;
-      }
-    }
   }
   before = wave_last(wave_incl_scan(before));
   all = wave_last(wave_incl_scan(all));
@@ -768,10 +777,10 @@ __global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const 
     if (lane == 63) s_tp[wave][kGroup] = incl;
     const uint64_t more = __ballot((c & ~kRedo) > 2 * kSlotAhead && !(c & kRedo)), again = __ballot((c & kRedo) != 0);
     if (lane == 0) s_mark[wave] = (more ? kMore : 0u) | (again ? kRedo : 0u);
-  } else if ((uint32_t)wave < kFinishMost && lane == 0) {
+  } else if ((uint32_t)wave < GROUPS && lane == 0) {
     s_mark[wave] = 0;
   }
-  __syncthreads();
+  lds_barrier();   // the records and entries stay on their way
   uint32_t first = 0, M = 0;   // the rank of the first record of the group at hand; all records of the tensor
 #pragma unroll
   for (int q = 0; q < NW; ++q) {
@@ -793,7 +802,7 @@ __global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const 
   // tile's count for the mark, one LDS read after the other, was half of this kernel's time.
   uint32_t marks = 0;
 #pragma unroll
-  for (uint32_t q = 0; q < kFinishMost; ++q) marks |= s_mark[q];
+  for (uint32_t q = 0; q < GROUPS; ++q) marks |= s_mark[q];
   if (marks & kRedo) {
     build_encode_table(lut, a.dec16_of(it, item), tid, F::kLutShift);
     __syncthreads();
@@ -826,7 +835,7 @@ __global__ __launch_bounds__(kTileThreads, 7) void compress_finish_kernel(const 
   }
 
 #pragma unroll
-  for (uint32_t q = 0; q < kFinishMost; ++q) {
+  for (uint32_t q = 0; q < GROUPS; ++q) {
     if (q >= ng) break;
     const uint32_t t0 = (g0 + q) * kGroup, c0 = t0 << a.tile_shift;
     const uint32_t entries = P.n_chunks > c0 ? (P.n_chunks - c0 < group_entries ? P.n_chunks - c0 : group_entries) : 0u;

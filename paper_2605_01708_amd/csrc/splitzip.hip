@@ -677,7 +677,10 @@ void launch_compress(unsigned tiles, unsigned finish_wgs, unsigned sums, unsigne
     else launch(compress_tile_kernel<F, F::kCpt, N, kTileLoop>, grid, block, lds_pad, st, args);
     if (args.shared.use_group_sums) launch(tile_group_sum_kernel<F, N>, dim3(sums, k), dim3(64), 0, st, args);
   }
-  launch(compress_finish_kernel<F, N>, dim3(finish_wgs ? finish_wgs : 1u, k), dim3(kTileThreads), 0, st, args);
+  const dim3 grid(finish_wgs ? finish_wgs : 1u, k);
+  if (args.shared.finish_groups == 1) launch(compress_finish_kernel<F, N, 1>, grid, dim3(kTileThreads), 0, st, args);
+  else if (args.shared.finish_groups == 2) launch(compress_finish_kernel<F, N, 2>, grid, dim3(kTileThreads), 0, st, args);
+  else launch(compress_finish_kernel<F, N, 4>, grid, dim3(kTileThreads), 0, st, args);
 }
 
 template <typename F>
