@@ -73,12 +73,12 @@ const Entry kEntries[] = {
     ENTRY(splitzip_compress_paged, "GICRPIPS"),
     ENTRY(splitzip_decompress_paged, "PIICGpS"),
     ENTRY(splitzip_compress_batch, "AIIPIPS"),
-    ENTRY(splitzip_decompress_batch, "AIIPS"),
+    ENTRY(splitzip_decompress_batch, "AIIpS"),
     ENTRY(splitzip_compress_batch_dcb, "AIIPPIPS"),
-    ENTRY(splitzip_decompress_batch_dcb, "AIIPPS"),
-    ENTRY(splitzip_decompress_batch_own, "AIIPS"),
+    ENTRY(splitzip_decompress_batch_dcb, "AIIPpS"),
+    ENTRY(splitzip_decompress_batch_own, "AIIpS"),
     ENTRY(splitzip_compress_batch_paged, "AIIGPIPS"),
-    ENTRY(splitzip_decompress_batch_paged, "AIIGPS"),
+    ENTRY(splitzip_decompress_batch_paged, "AIIGpS"),
     ENTRY(splitzip_calibrate_batch_device, "AIIPPS"),
     ENTRY(splitzip_variant_compress, "WVKRRPS"),
     ENTRY(splitzip_variant_decompress, "PINVKYpS"),

@@ -61,6 +61,13 @@ def test_codebooks_of_a_batch_are_all_looked_at():
     del x
 
 
+def test_batches_are_decoded_without_a_record():
+    """the record of a batch decompress call may be left out: no reason to refuse it (no streams: nothing is launched)"""
+    f, items = sz.lib().fast, (binding._CDItem * 1)()
+    assert f.splitzip_decompress_batch(items, 0, sz.BF16, None, 0) == 0
+    assert f.splitzip_decompress_batch_own(items, 0, sz.BF16, None, 0) == 0
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
 @pytest.mark.parametrize("form", ["plain", "capacity", "stream", "parameter", "subclass", "shaped", "mode"])
