@@ -47,7 +47,8 @@ struct Caller<int(A...)> {
 // What a call's Python arguments are, a letter each (two letters where it says "and"), and the words they become:
 //   W  words, a contiguous tensor: address and number of elements; the size of one is compared with the dtype that a
 //      C, V or D names
-//   P  a tensor: its address            p  the same, or None: null
+//   P  a tensor: its address
+//   Z  a sizes record, a tensor in the GPU's memory or (pinned) in the host's: its address      z  the same, or None: null
 //   R  room, a tensor, and its capacity in bytes or None (all of it): address, bytes
 //   Y  room for decoded words, a contiguous tensor of at least the elements that the N before it says: its address
 //   I  an integer                       N  the same: the elements of a stream
@@ -64,24 +65,24 @@ struct Entry {
 };
 #define ENTRY(NAME, SPEC) {#NAME, SPEC, Caller<decltype(NAME)>::kArgs, &Caller<decltype(NAME)>::call}
 const Entry kEntries[] = {
-    ENTRY(splitzip_compress, "WCRPIPS"),
-    ENTRY(splitzip_decompress, "PINCYpS"),
-    ENTRY(splitzip_compress_noalloc, "WCRPS"),
-    ENTRY(splitzip_compress_dcb, "WDPRPIPS"),
-    ENTRY(splitzip_decompress_dcb, "PINDPYpS"),
-    ENTRY(splitzip_decompress_own, "PINDYpS"),
-    ENTRY(splitzip_compress_paged, "GICRPIPS"),
-    ENTRY(splitzip_decompress_paged, "PIICGpS"),
-    ENTRY(splitzip_compress_batch, "AIIPIPS"),
-    ENTRY(splitzip_decompress_batch, "AIIpS"),
-    ENTRY(splitzip_compress_batch_dcb, "AIIPPIPS"),
-    ENTRY(splitzip_decompress_batch_dcb, "AIIPpS"),
-    ENTRY(splitzip_decompress_batch_own, "AIIpS"),
-    ENTRY(splitzip_compress_batch_paged, "AIIGPIPS"),
-    ENTRY(splitzip_decompress_batch_paged, "AIIGpS"),
+    ENTRY(splitzip_compress, "WCRPIZS"),
+    ENTRY(splitzip_decompress, "PINCYzS"),
+    ENTRY(splitzip_compress_noalloc, "WCRZS"),
+    ENTRY(splitzip_compress_dcb, "WDPRPIZS"),
+    ENTRY(splitzip_decompress_dcb, "PINDPYzS"),
+    ENTRY(splitzip_decompress_own, "PINDYzS"),
+    ENTRY(splitzip_compress_paged, "GICRPIZS"),
+    ENTRY(splitzip_decompress_paged, "PIICGzS"),
+    ENTRY(splitzip_compress_batch, "AIIPIZS"),
+    ENTRY(splitzip_decompress_batch, "AIIzS"),
+    ENTRY(splitzip_compress_batch_dcb, "AIIPPIZS"),
+    ENTRY(splitzip_decompress_batch_dcb, "AIIPzS"),
+    ENTRY(splitzip_decompress_batch_own, "AIIzS"),
+    ENTRY(splitzip_compress_batch_paged, "AIIGPIZS"),
+    ENTRY(splitzip_decompress_batch_paged, "AIIGzS"),
     ENTRY(splitzip_calibrate_batch_device, "AIIPPS"),
-    ENTRY(splitzip_variant_compress, "WVKRRPS"),
-    ENTRY(splitzip_variant_decompress, "PINVKYpS"),
+    ENTRY(splitzip_variant_compress, "WVKRRZS"),
+    ENTRY(splitzip_variant_decompress, "PINVKYzS"),
 };
 #undef ENTRY
 
@@ -97,10 +98,10 @@ struct Bound {
 
 struct Refused {};   // thrown where an argument is not of the plain form
 
-const at::Tensor& tensor(PyObject* o) {
+const at::Tensor& tensor(PyObject* o, bool host_too = false) {
   if (!THPVariable_CheckExact(o)) throw Refused();
   const at::Tensor& t = THPVariable_Unpack(o);
-  if (!t.is_cuda() || t.layout() != at::kStrided) throw Refused();   // on the GPU: its runtime is up, there is a current stream
+  if (!(t.is_cuda() || (host_too && t.is_cpu())) || t.layout() != at::kStrided) throw Refused();
   return t;
 }
 uint64_t integer(PyObject* o) {
@@ -167,8 +168,11 @@ int run(const Bound& b, PyObject* const* a, Py_ssize_t n_args) {
         word(address(t.data_ptr()));
         break;
       }
-      case 'p':
-        word(o == Py_None ? 0 : address(tensor(o).data_ptr()));
+      case 'Z':
+        word(address(tensor(o, true).data_ptr()));
+        break;
+      case 'z':
+        word(o == Py_None ? 0 : address(tensor(o, true).data_ptr()));
         break;
       case 'P':
         word(address(tensor(o).data_ptr()));

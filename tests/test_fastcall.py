@@ -68,6 +68,13 @@ def test_batches_are_decoded_without_a_record():
     assert f.splitzip_decompress_batch_own(items, 0, sz.BF16, None, 0) == 0
 
 
+def test_a_record_in_host_memory_is_taken():
+    """a record may lie in pinned host memory (here: any host memory, no streams, nothing is launched)"""
+    f, items, rec = sz.lib().fast, (binding._CDItem * 1)(), torch.zeros(3, dtype=torch.int64)
+    assert f.splitzip_decompress_batch(items, 0, sz.BF16, rec, 0) == 0
+    assert f.splitzip_decompress_batch_own(items, 0, sz.BF16, rec, 0) == 0
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
 @pytest.mark.parametrize("form", ["plain", "capacity", "stream", "parameter", "subclass", "shaped", "mode"])
