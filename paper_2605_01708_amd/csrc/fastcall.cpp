@@ -57,14 +57,17 @@ struct Caller<int(A...)> {
 //   C  a codebook: its dtype and its address               K  a codebook: its address alone
 //   V  a format of the variants: its address
 //   S  a stream's handle, or None: the current one
+constexpr bool in(const char* set, char c) { return *set && (*set == c || in(set + 1, c)); }
+constexpr int count(const char* spec, const char* twice) { return *spec ? (in(twice, *spec) ? 2 : 1) + count(spec + 1, twice) : 0; }
+constexpr bool known(const char* spec) { return !*spec || (in("WPZzRYINDAGCKVS", *spec) && known(spec + 1)); }
 struct Entry {
   const char* name;
   const char* spec;
-  int n_words;
+  int n_words, n_args;   // of the library's function, of Python's
   int (*call)(void*, const uint64_t*);
 };
-#define ENTRY(NAME, SPEC) {#NAME, SPEC, Caller<decltype(NAME)>::kArgs, &Caller<decltype(NAME)>::call}
-const Entry kEntries[] = {
+#define ENTRY(NAME, SPEC) {#NAME, SPEC, Caller<decltype(NAME)>::kArgs, count(SPEC, "R"), &Caller<decltype(NAME)>::call}
+constexpr Entry kEntries[] = {
     ENTRY(splitzip_compress, "WCRPIZS"),
     ENTRY(splitzip_decompress, "PINCYzS"),
     ENTRY(splitzip_compress_noalloc, "WCRZS"),
@@ -85,6 +88,10 @@ const Entry kEntries[] = {
     ENTRY(splitzip_variant_decompress, "PINVKYzS"),
 };
 #undef ENTRY
+constexpr bool fit(size_t k) {
+  return k == 0 || (known(kEntries[k - 1].spec) && count(kEntries[k - 1].spec, "WRC") == kEntries[k - 1].n_words && fit(k - 1));
+}
+static_assert(fit(sizeof kEntries / sizeof kEntries[0]), "a letter for every argument of the library's functions");
 
 // the binding's ctypes structures, as bind was given them
 struct Types {
@@ -96,36 +103,33 @@ struct Bound {
   Types types;   // references held
 };
 
-struct Refused {};   // thrown where an argument is not of the plain form
-
-const at::Tensor& tensor(PyObject* o, bool host_too = false) {
-  if (!THPVariable_CheckExact(o)) throw Refused();
+// Nothing here is refused by a C++ exception: one takes 2.5 to 4 us, more than a launch, and a program that always passes
+// another form (its default device set, parameters) would pay that with every call.
+const at::Tensor* tensor(PyObject* o, bool host_too = false) {
+  if (!THPVariable_CheckExact(o)) return nullptr;
   const at::Tensor& t = THPVariable_Unpack(o);
-  if (!(t.is_cuda() || (host_too && t.is_cpu())) || t.layout() != at::kStrided) throw Refused();
-  return t;
+  return (t.is_cuda() || (host_too && t.is_cpu())) && t.layout() == at::kStrided ? &t : nullptr;
 }
-uint64_t integer(PyObject* o) {
-  if (!PyLong_CheckExact(o)) throw Refused();
-  const unsigned long long v = PyLong_AsUnsignedLongLong(o);
-  if (v == static_cast<unsigned long long>(-1) && PyErr_Occurred()) {
-    PyErr_Clear();
-    throw Refused();
-  }
-  return v;
+bool integer(PyObject* o, uint64_t* v) {
+  if (!PyLong_CheckExact(o)) return false;
+  *v = PyLong_AsUnsignedLongLong(o);
+  if (*v != ~0ull || !PyErr_Occurred()) return true;
+  PyErr_Clear();
+  return false;
 }
 // the memory of a ctypes object, held until the call has returned
 struct Views {
   Py_buffer held[4];
   int n = 0;
   void* of(PyObject* o, const PyObject* type, Py_ssize_t least) {
-    if (type && reinterpret_cast<const PyObject*>(Py_TYPE(o)) != type) throw Refused();
-    if (n == 4 || PyObject_GetBuffer(o, &held[n], PyBUF_SIMPLE | PyBUF_WRITABLE) != 0) {
+    if (type && reinterpret_cast<const PyObject*>(Py_TYPE(o)) != type) return nullptr;
+    if (n == 4 || !PyObject_CheckBuffer(o)) return nullptr;
+    if (PyObject_GetBuffer(o, &held[n], PyBUF_SIMPLE | PyBUF_WRITABLE) != 0) {
       PyErr_Clear();
-      throw Refused();
+      return nullptr;
     }
     ++n;
-    if (held[n - 1].len < least) throw Refused();
-    return held[n - 1].buf;
+    return held[n - 1].len < least ? nullptr : held[n - 1].buf;
   }
   ~Views() {
     for (int i = 0; i < n; ++i) PyBuffer_Release(&held[i]);
@@ -133,80 +137,82 @@ struct Views {
 };
 int64_t bytes_per_word(uint64_t dtype) { return dtype == SPLITZIP_BF16 ? 2 : 1; }
 
-int run(const Bound& b, PyObject* const* a, Py_ssize_t n_args) {
-  if (at::impl::torch_function_mode_enabled()) throw Refused();
+// false if an argument is not of the plain form: nothing has been done then
+bool run(const Bound& b, PyObject* const* a, Py_ssize_t n_args, int* rc) {
+  if (n_args != b.entry->n_args || at::impl::torch_function_mode_enabled()) return false;
   Views views;
   uint64_t w[kMost];
   int n = 0;
-  Py_ssize_t i = 0;
   int64_t word_size = 0, expected = 0;   // bytes of a word, of the tensor and by the dtype
-  uint64_t elems = 0;
-  const auto next = [&]() -> PyObject* {
-    if (i >= n_args) throw Refused();
-    return a[i++];
-  };
-  const auto word = [&](uint64_t v) {
-    if (n >= b.entry->n_words) throw Refused();
-    w[n++] = v;
-  };
+  uint64_t elems = 0, v = 0;
+  const auto word = [&](uint64_t x) { w[n++] = x; };
   const auto address = [](const void* p) { return static_cast<uint64_t>(reinterpret_cast<uintptr_t>(p)); };
   for (const char* s = b.entry->spec; *s; ++s) {
-    PyObject* o = next();
+    PyObject* o = *a++;
     switch (*s) {
       case 'W': {
-        const at::Tensor& t = tensor(o);
-        if (!t.is_contiguous()) throw Refused();
-        word_size = t.element_size();
-        word(address(t.data_ptr()));
-        word(static_cast<uint64_t>(t.numel()));
+        const at::Tensor* t = tensor(o);
+        if (!t || !t->is_contiguous()) return false;
+        word_size = t->element_size();
+        word(address(t->data_ptr()));
+        word(static_cast<uint64_t>(t->numel()));
         break;
       }
       case 'Y': {
-        const at::Tensor& t = tensor(o);
-        if (!t.is_contiguous() || static_cast<uint64_t>(t.numel()) < elems) throw Refused();
-        word_size = t.element_size();
-        word(address(t.data_ptr()));
+        const at::Tensor* t = tensor(o);
+        if (!t || !t->is_contiguous() || static_cast<uint64_t>(t->numel()) < elems) return false;
+        word_size = t->element_size();
+        word(address(t->data_ptr()));
         break;
       }
-      case 'Z':
-        word(address(tensor(o, true).data_ptr()));
-        break;
       case 'z':
-        word(o == Py_None ? 0 : address(tensor(o, true).data_ptr()));
+        if (o == Py_None) {
+          word(0);
+          break;
+        }
+        [[fallthrough]];
+      case 'Z':
+      case 'P': {
+        const at::Tensor* t = tensor(o, *s != 'P');
+        if (!t) return false;
+        word(address(t->data_ptr()));
         break;
-      case 'P':
-        word(address(tensor(o).data_ptr()));
-        break;
+      }
       case 'R': {
-        const at::Tensor& t = tensor(o);
-        PyObject* cap = next();
-        word(address(t.data_ptr()));
-        word(cap == Py_None ? static_cast<uint64_t>(t.numel() * t.element_size()) : integer(cap));
+        const at::Tensor* t = tensor(o);
+        PyObject* cap = *a++;
+        if (!t) return false;
+        if (cap == Py_None) v = static_cast<uint64_t>(t->numel() * t->element_size());
+        else if (!integer(cap, &v)) return false;
+        word(address(t->data_ptr()));
+        word(v);
         break;
       }
       case 'N':
-        elems = integer(o);
-        if (elems >> 63) throw Refused();
+        if (!integer(o, &elems) || elems >> 63) return false;
         word(elems);
         break;
       case 'I':
-        word(integer(o));
+        if (!integer(o, &v)) return false;
+        word(v);
         break;
       case 'D':
-        word(integer(o));
-        expected = bytes_per_word(w[n - 1]);
+        if (!integer(o, &v)) return false;
+        expected = bytes_per_word(v);
+        word(v);
         break;
       case 'A':
-        word(address(views.of(o, nullptr, 1)));
-        break;
       case 'G':
-        word(address(views.of(o, b.types.paged, sizeof(splitzip_paged))));
+      case 'K': {
+        const void* p = *s == 'A' ? views.of(o, nullptr, 1)
+                        : *s == 'G' ? views.of(o, b.types.paged, sizeof(splitzip_paged)) : views.of(o, b.types.codebook, sizeof(splitzip_codebook));
+        if (!p) return false;
+        word(address(p));
         break;
-      case 'K':
-        word(address(views.of(o, b.types.codebook, sizeof(splitzip_codebook))));
-        break;
+      }
       case 'C': {
         const void* cb = views.of(o, b.types.codebook, sizeof(splitzip_codebook));
+        if (!cb) return false;
         const uint32_t dtype = static_cast<const splitzip_codebook*>(cb)->dtype;
         expected = bytes_per_word(dtype);
         word(dtype);
@@ -214,24 +220,24 @@ int run(const Bound& b, PyObject* const* a, Py_ssize_t n_args) {
         break;
       }
       case 'V': {
-        const void* v = views.of(o, b.types.variant, sizeof(splitzip_variant));
-        expected = bytes_per_word(static_cast<const splitzip_variant*>(v)->dtype);
-        word(address(v));
+        const void* f = views.of(o, b.types.variant, sizeof(splitzip_variant));
+        if (!f) return false;
+        expected = bytes_per_word(static_cast<const splitzip_variant*>(f)->dtype);
+        word(address(f));
         break;
       }
       case 'S':
-        word(o == Py_None ? address(c10::hip::getCurrentHIPStream().stream()) : integer(o));
+        if (o == Py_None) v = address(c10::hip::getCurrentHIPStream().stream());
+        else if (!integer(o, &v)) return false;
+        word(v);
         break;
-      default:
-        throw Refused();
     }
   }
-  if (i != n_args || n != b.entry->n_words || (word_size && word_size != expected)) throw Refused();
-  int rc;
+  if (word_size && word_size != expected) return false;
   Py_BEGIN_ALLOW_THREADS
-  rc = b.entry->call(b.fn, w);
+  *rc = b.entry->call(b.fn, w);
   Py_END_ALLOW_THREADS
-  return rc;
+  return true;
 }
 
 PyObject* fastcall(PyObject* self, PyObject* const* a, Py_ssize_t n) {
@@ -239,8 +245,9 @@ PyObject* fastcall(PyObject* self, PyObject* const* a, Py_ssize_t n) {
   if (!b) return nullptr;
   int rc = kNotTaken;
   try {
-    rc = run(*b, a, n);
-  } catch (...) {   // Refused, or what torch throws for a tensor without memory of its own: the general way says what is wrong
+    if (!run(*b, a, n, &rc)) rc = kNotTaken;
+  } catch (...) {   // what torch throws for a tensor without memory of its own, or without a GPU: the general way says what is wrong
+    rc = kNotTaken;
     PyErr_Clear();
   }
   return PyLong_FromLong(rc);
