@@ -396,11 +396,11 @@ def internal_compress_plan(n_elems, dtype: int) -> dict:
 
 def internal_decompress_plan(n_elems, dtype: int, comp_bytes=None) -> dict:
     """The same for a batch decompress call (comp_bytes: of the streams; by default those of streams without escapes)."""
-    items, out = (_CDItem * len(n_elems))(), (C.c_uint32 * 3)()
+    items, out = (_CDItem * len(n_elems))(), (C.c_uint32 * 4)()
     for k, (it, n) in enumerate(zip(items, n_elems)):
         it.n_elems, it.comp_bytes = n, fixed_bytes(n, dtype) if comp_bytes is None else comp_bytes[k]
     lib().splitzip_internal_decompress_plan(items, len(n_elems), dtype, out)
-    return dict(zip(("cpw", "workgroups", "by_xcd"), out))
+    return dict(zip(("cpw", "workgroups", "by_xcd", "lds_pad"), out))
 
 
 def internal_xcd_tile(workgroup: int, n_tiles: int) -> int:

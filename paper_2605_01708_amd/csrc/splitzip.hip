@@ -924,7 +924,13 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
   // with eight / six / five / four: BF16, two chunks per wave, 1240 / 1184 / 1172 / 1170 (2 Mi chunks), 300.9 / 295.5 / 292.8 /
   // 293.1 (524 288), 75.9 / 75.2 / 74.1 / 74.1 (131 072 with seven escapes each), with one chunk 1224 / 1198 / 1231 / 1231; E5M2,
   // four chunks, 648 / 637 / 619 / 632 (2 Mi), 158.8 / 157.7 / 156.7 / 158.1 (524 288), with two 635 / 638 / 678 / 751.
-  p.lds_pad = p.by_xcd && p.cpw == (dtype == SPLITZIP_BF16 ? 2u : 4u) ? kDecodeLdsPad : 0u;
+  // Not where a wave's records outgrow the 128 that it asks for beside its planes: it then waits for memory once more, and the
+  // other workgroups of the CU are what fills that wait.  By the records per chunk, as the streams' lengths tell, with five / eight:
+  // BF16 150.2 / 152.4 (262 144 chunks in 64 streams, 58 records), 156.0 / 154.9 (67), 183.8 / 161.9 (144), 141.3 / 121.7 (200 000
+  // in one stream, 144), 508 / 400 (524 288, 384); E5M2 313.1 / 315.1 (1 Mi, 26), 327.9 / 317.8 (31), 366.7 / 341.8 (51), 514 /
+  // 432 (205).
+  const bool within = beyond * kChunk <= 3 * n_all * (dtype == SPLITZIP_BF16 ? 64u : 28u);   // three bytes per record
+  p.lds_pad = p.by_xcd && within && p.cpw == (dtype == SPLITZIP_BF16 ? 2u : 4u) ? kDecodeLdsPad : 0u;
   return p;
 }
 
@@ -1172,9 +1178,9 @@ void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_item
 }
 // the tile that workgroup b of a tensor of n tiles takes in a launch by XCDs
 uint32_t splitzip_internal_xcd_tile(uint32_t b, uint32_t n) { return xcd_order(b, n - 1); }
-void splitzip_internal_decompress_plan(const splitzip_ditem* items, uint32_t n_items, int dtype, uint32_t out[3]) {
+void splitzip_internal_decompress_plan(const splitzip_ditem* items, uint32_t n_items, int dtype, uint32_t out[4]) {
   const DecompressPlan p = plan_decompress(items, n_items < kBatchMax ? n_items : kBatchMax, dtype);
-  out[0] = p.cpw; out[1] = p.wgs; out[2] = p.by_xcd;
+  out[0] = p.cpw; out[1] = p.wgs; out[2] = p.by_xcd; out[3] = p.lds_pad;
 }
 
 int splitzip_traffic_probe(const void* d_src, size_t read_bytes, void* d_dst, size_t write_bytes, void* stream) {

@@ -78,3 +78,17 @@ def test_chunks_per_wave_of_streams_with_many_escapes():
     for share in (17, 50, 1000):
         assert [cpw(sz.BF16, [c], share) for c in (4096, 6144, 8192, 12288, 16384, 65536)] == [1, 2, 2, 2, 2, 1]
         assert [cpw(sz.FP8_E5M2, [c], share) for c in (4096, 8192, 12288, 16384, 24576, 65536)] == [1, 2, 2, 4, 4, 4]
+
+
+def test_occupancy_of_long_launches_with_many_escapes():
+    """Long launches have fewer workgroups per CU only where a wave's records fit the run that it asks for ahead."""
+    def padded(dtype, chunks, per_chunk):
+        n = [c * 1024 for c in chunks]
+        p = sz.internal_decompress_plan(n, dtype, [sz.total_bytes(v, v // 1024 * per_chunk, dtype) for v in n])
+        return p["lds_pad"] > 0
+    for chunks in ([200000], [8192] * 32, [32768] * 64):
+        assert [padded(sz.BF16, chunks, q) for q in (0, 1, 32, 63, 65, 200, 1024)] == [True] * 4 + [False] * 3
+    for chunks in ([1 << 20], [32768] * 64):
+        assert [padded(sz.FP8_E5M2, chunks, q) for q in (0, 1, 16, 27, 29, 100, 1024)] == [True] * 4 + [False] * 3
+    for dtype in FORMATS:
+        assert not padded(dtype, [2048], 0) and not padded(dtype, [32768], 0)
