@@ -77,7 +77,7 @@ struct TestHooks {
   std::atomic<uint32_t> finish_groups{0};
   std::atomic<uint64_t> direct_bytes{0};
   std::atomic<uint32_t> cpt{0};   // 1, 2, 4 or 8
-  std::atomic<uint32_t> cpw{0};   // 1, 2, 4 or 8
+  std::atomic<uint32_t> cpw{0};   // 1, 2, 4 or 8, most_cpw at most
   std::atomic<uint32_t> xcd{0};   // 1: batch launches keep the tiles' own order, 2: they take xcd_order
   bool any() const { return stage_bytes || status_bytes || finish_groups || direct_bytes || cpt || xcd; }   // the two-launch path is meant
 };
@@ -86,6 +86,9 @@ TestHooks g_hooks;
 // Whether more than one element in 16 may have escaped, by the bytes that the caller says it holds beyond the fixed part
 // of its streams (three per record): the device alone knows the number.
 bool many_escapes(uint64_t bytes_beyond, uint64_t n_elems) { return bytes_beyond * 16 > n_elems * 3; }
+
+// The most chunks per wave that a decompress launch of one stream or of several takes, and that there are kernels for.
+constexpr uint32_t most_cpw(int dtype, bool several) { return (dtype == SPLITZIP_BF16 ? 2u : 4u) << (several ? 1 : 0); }
 
 // Chunks per wave of a decompress launch over n_chunks chunks in all; device us per call with one / two / four chunks per
 // wave, all of whose planes a wave asks for at once:
@@ -99,7 +102,7 @@ bool many_escapes(uint64_t bytes_beyond, uint64_t n_elems) { return bytes_beyond
 // Streams with many escapes keep a wave busy with its chunks' records, one chunk after the other, so the larger pieces
 // pay from somewhat longer streams on (random words: BF16, 4096 chunks, 8.1 / 11.1 / 17.3).
 uint32_t pick_decompress_cpw(uint64_t n_chunks, bool several, bool escapes, int dtype, uint64_t cus) {
-  if (const uint32_t forced = g_hooks.cpw.load()) return forced;
+  if (const uint32_t forced = g_hooks.cpw.load()) return forced < most_cpw(dtype, several) ? forced : most_cpw(dtype, several);
   const uint64_t round = cus * 8;   // workgroups resident at a time
   if (dtype == SPLITZIP_BF16) return (n_chunks >= (escapes ? 9 : 5) * round / 2 && n_chunks <= 8 * round) || n_chunks >= (several ? 16 : 56) * round ? 2u : 1u;
   if (n_chunks >= 40 * round && n_chunks < 512 * round) return 2;
@@ -868,12 +871,14 @@ int compress_one(const Words& in, uint64_t n_elems, int dtype, const splitzip_co
 
 constexpr unsigned kDecodeLdsPad = 22800;   // five workgroups of the decoder per CU
 
+// cpw: most_cpw at most
 template <typename F, uint32_t N>
 void launch_decompress(uint32_t cpw, dim3 grid, unsigned lds_pad, hipStream_t st, const DArgs<N>& args) {
+  constexpr uint32_t most = most_cpw(F::DT, N > 1);
   if (cpw == 1) launch(decompress_kernel<F, 1, N>, grid, dim3(kThreads), lds_pad, st, args);
-  else if (cpw == 2) launch(decompress_kernel<F, 2, N>, grid, dim3(kThreads), lds_pad, st, args);
-  else if (cpw == 4) launch(decompress_kernel<F, 4, N>, grid, dim3(kThreads), lds_pad, st, args);
-  else launch(decompress_kernel<F, 8, N>, grid, dim3(kThreads), lds_pad, st, args);
+  else if (cpw == 2 || most == 2) launch(decompress_kernel<F, 2, N>, grid, dim3(kThreads), lds_pad, st, args);
+  else if (cpw == 4 || most == 4) launch(decompress_kernel<F, most < 4 ? 2 : 4, N>, grid, dim3(kThreads), lds_pad, st, args);
+  else launch(decompress_kernel<F, most, N>, grid, dim3(kThreads), lds_pad, st, args);
 }
 
 // how up to kBatchMax streams of a decompress call are launched, by the lengths of what they decode to
@@ -904,7 +909,7 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
   // the chip anyway 37.9 / 34.7 (two of 9000 beside 62 of 1000: 31 000).
   const uint64_t none = chunks_max * k - chunks_all;   // chunks that the padded grid has room for and the streams do not have
   if (!g_hooks.cpw.load()) {
-    const uint32_t most = dtype == SPLITZIP_FP8_E5M2 ? 8u : none > 8 * chunks_all ? 4u : 2u;
+    const uint32_t most = dtype == SPLITZIP_BF16 && none <= 8 * chunks_all ? 2u : most_cpw(dtype, k > 1);
     const auto limit = [&](uint32_t cpw) { return dtype == SPLITZIP_BF16 ? (cpw < 2 ? 32u : 224u) : cpw < 4 ? 32u : chunks_all < 256 * cus ? 160u : 96u; };
     while (p.cpw < most && none / (kWaves * p.cpw) > cus * limit(p.cpw)) p.cpw *= 2;
   }

@@ -92,3 +92,18 @@ def test_occupancy_of_long_launches_with_many_escapes():
         assert [padded(sz.FP8_E5M2, chunks, q) for q in (0, 1, 16, 27, 29, 100, 1024)] == [True] * 4 + [False] * 3
     for dtype in FORMATS:
         assert not padded(dtype, [2048], 0) and not padded(dtype, [32768], 0)
+
+
+def test_no_more_chunks_per_wave_than_the_rules_may_choose():
+    """Kernels are built for what the rules may choose: single streams up to two (BF16) and four, batches twice that."""
+    try:
+        for cpw in (1, 2, 4, 8):
+            sz.internal_test_launch(cpw=cpw)
+            for dtype, most in ((sz.BF16, 2), (sz.FP8_E5M2, 4)):
+                assert decompress_plan(dtype, [5000])["cpw"] == min(cpw, most)
+                assert decompress_plan(dtype, [5000, 3])["cpw"] == min(cpw, 2 * most)
+    finally:
+        sz.internal_test_launch()
+    for chunks in ([1 << 22], [1 << 22, 1], [1 << 20] + [1] * 63):
+        assert decompress_plan(sz.BF16, chunks)["cpw"] <= (4 if len(chunks) > 1 else 2)
+        assert decompress_plan(sz.FP8_E5M2, chunks)["cpw"] <= (8 if len(chunks) > 1 else 4)
