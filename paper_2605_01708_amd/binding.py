@@ -174,7 +174,26 @@ def lib():
         from . import _fastcall   # built beside the library; torch's own libraries are loaded by now
         L.fast = types.SimpleNamespace(**_fastcall.bind(L._handle, _CCodebook, Variant, _CPaged))
         _lib = L
+        _leave_fast_in_a_bad_fork()
     return _lib
+
+
+class _NoneTaken:
+    """lib().fast where every call goes the general way."""
+
+    def __getattr__(self, name):
+        return lambda *args: _NOT_TAKEN
+
+
+def _leave_fast_in_a_bad_fork() -> None:
+    """In a child of a process that had used the GPU before it forked, torch refuses the GPU where the general way asks it for
+    the current stream; the short way does not ask torch."""
+    if _lib is not None and getattr(torch._C, "_cuda_isInBadFork", bool)():
+        _lib.fast = _NoneTaken()
+
+
+if hasattr(os, "register_at_fork"):
+    os.register_at_fork(after_in_child=_leave_fast_in_a_bad_fork)
 
 
 def _check(rc: int, what: str):

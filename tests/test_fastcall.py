@@ -1,5 +1,6 @@
 """The binding's short way (lib().fast) against its general way: what it takes gives the same streams, words and records,
 what it does not take is left to the general way, errors included."""
+import os
 import timeit
 
 import numpy as np
@@ -86,6 +87,55 @@ def test_a_record_in_host_memory_is_taken():
     f, items, rec = sz.lib().fast, (binding._CDItem * 1)(), torch.zeros(3, dtype=torch.int64)
     assert f.splitzip_decompress_batch(items, 0, sz.BF16, rec, 0) == 0
     assert f.splitzip_decompress_batch_own(items, 0, sz.BF16, rec, 0) == 0
+
+
+def _in_a_child(what) -> int:
+    pid = os.fork()
+    if pid == 0:
+        code = 99
+        try:
+            code = what()
+        finally:
+            os._exit(code)
+    return os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1])
+
+
+def test_nothing_is_taken_in_a_fork_that_must_not_use_the_gpu(monkeypatch):
+    items = (binding._CDItem * 1)()
+
+    def taken():
+        return sz.lib().fast.splitzip_decompress_batch(items, 0, sz.BF16, None, 0)   # no streams: nothing is launched
+
+    assert taken() == 0 and _in_a_child(taken) == 0
+    monkeypatch.setattr(torch._C, "_cuda_isInBadFork", lambda: True)
+    assert _in_a_child(taken) == 1
+
+    def loaded_there():
+        binding._lib = None
+        return taken()
+    assert _in_a_child(loaded_there) == 1
+    monkeypatch.undo()
+    assert taken() == 0
+
+
+@pytest.mark.gpu
+def test_a_child_of_a_process_on_the_gpu_is_refused():
+    x = kv_synth.kv_bf16(8, 0).cuda()
+    cb = sz.calibrate(kv_synth.kv_bf16(8, 1), sz.BF16)
+    ws, rec = sz.Workspace(x.numel(), sz.BF16), sz.new_sizes()
+    out = torch.zeros(sz.compress_bound(x.numel(), sz.BF16), dtype=torch.uint8, device="cuda")
+    sz.compress(x, cb, out, ws, rec)
+    torch.cuda.synchronize()
+
+    def child():
+        if not torch._C._cuda_isInBadFork():
+            return 3   # nothing would refuse it: go no further
+        try:
+            sz.compress(x, cb, out, ws, rec)
+        except RuntimeError as e:
+            return 0 if "fork" in str(e) else 4
+        return 5
+    assert _in_a_child(child) == 0
 
 
 @pytest.mark.gpu
