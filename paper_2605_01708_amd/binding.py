@@ -2,14 +2,15 @@
 (without the ``splitzip_`` prefix); torch tensors supply device pointers and
 the current HIP stream, nothing else.
 
-The calls that a serving loop repeats go through _fastcall.so first, which marshals the plain form of their arguments
-in one step (lib().fast, by the names of the C entry points) and answers _NOT_TAKEN for any other form; the ctypes call
-behind it takes every form and raises the errors."""
+The calls that a serving loop repeats go through the extension module _fastcall first, which marshals the plain form of
+their arguments in one step (lib().fast, by the names of the C entry points) and answers _NOT_TAKEN for any other form; the
+ctypes call behind it takes every form and raises the errors, and serves every call where the module is not there."""
 from __future__ import annotations
 
 import ctypes as C
 import os
 import types
+import warnings
 
 import torch
 
@@ -171,11 +172,21 @@ def lib():
         L.splitzip_variant_compress.argtypes = [vp, u64, vrp, cbp, vp, sz, vp, sz, vp, vp]
         L.splitzip_variant_decompress.restype = i
         L.splitzip_variant_decompress.argtypes = [vp, sz, u64, vrp, cbp, vp, vp, vp]
-        from . import _fastcall   # built beside the library; torch's own libraries are loaded by now
-        L.fast = types.SimpleNamespace(**_fastcall.bind(L._handle, _CCodebook, Variant, _CPaged))
+        L.fast = _short_way(L)
         _lib = L
         _leave_fast_in_a_bad_fork()
     return _lib
+
+
+def _short_way(L):
+    """The functions of _fastcall, or, where it is not built or built for another Python or torch, none that take a call."""
+    try:
+        from . import _fastcall   # torch's own libraries are loaded by now
+        return types.SimpleNamespace(**_fastcall.bind(L._handle, _CCodebook, Variant, _CPaged, torch.__version__))
+    except ImportError as e:
+        warnings.warn(f"{e}: calls take the general way, 1 to 2 us longer each; build the short one with "
+                      "`python -m paper_2605_01708_amd.build`", RuntimeWarning, stacklevel=3)
+        return _NoneTaken()
 
 
 class _NoneTaken:

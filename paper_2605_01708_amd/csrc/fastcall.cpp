@@ -17,6 +17,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <cstring>
 #include <type_traits>
 #include <utility>
 
@@ -262,12 +263,18 @@ void forget(PyObject* capsule) {
   delete b;
 }
 
-// bind(handle, codebook, variant, paged): the entry points of the library that ctypes holds by this handle, name ->
-// function, for the binding's structures of these types
+// bind(handle, codebook, variant, paged, torch): the entry points of the library that ctypes holds by this handle, name ->
+// function, for the binding's structures of these types; an ImportError if the torch of this version is not the one that
+// this was built for (torch's headers read the fields of its tensors)
 PyObject* bind(PyObject*, PyObject* args) {
   PyObject* handle = nullptr;
   Types types;
-  if (!PyArg_ParseTuple(args, "OOOO", &handle, &types.codebook, &types.variant, &types.paged)) return nullptr;
+  const char* torch_version = nullptr;
+  if (!PyArg_ParseTuple(args, "OOOOs", &handle, &types.codebook, &types.variant, &types.paged, &torch_version)) return nullptr;
+  if (strcmp(torch_version, BUILT_FOR_TORCH) != 0) {
+    PyErr_Format(PyExc_ImportError, "_fastcall was built for torch %s, this is %s", BUILT_FOR_TORCH, torch_version);
+    return nullptr;
+  }
   void* lib = PyLong_AsVoidPtr(handle);
   if (!lib && PyErr_Occurred()) return nullptr;
   PyObject* out = PyDict_New();
@@ -301,7 +308,7 @@ PyObject* bind(PyObject*, PyObject* args) {
   return out;
 }
 
-PyMethodDef kMethods[] = {{"bind", bind, METH_VARARGS, "bind(handle, codebook, variant, paged): {name: function} for a libsplitzip.so that is loaded"}, {nullptr, nullptr, 0, nullptr}};
+PyMethodDef kMethods[] = {{"bind", bind, METH_VARARGS, "bind(handle, codebook, variant, paged, torch): {name: function} for a libsplitzip.so that is loaded"}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -1,6 +1,9 @@
 """The binding's short way (lib().fast) against its general way: what it takes gives the same streams, words and records,
 what it does not take is left to the general way, errors included."""
 import os
+import shutil
+import subprocess
+import sys
 import timeit
 
 import numpy as np
@@ -87,6 +90,56 @@ def test_a_record_in_host_memory_is_taken():
     f, items, rec = sz.lib().fast, (binding._CDItem * 1)(), torch.zeros(3, dtype=torch.int64)
     assert f.splitzip_decompress_batch(items, 0, sz.BF16, rec, 0) == 0
     assert f.splitzip_decompress_batch_own(items, 0, sz.BF16, rec, 0) == 0
+
+
+def _elsewhere(tmp_path, code, with_module=False, **env):
+    """code run on a copy of the package; what it prints"""
+    here, there = os.path.dirname(os.path.abspath(binding.__file__)), tmp_path / "paper_2605_01708_amd"
+    there.mkdir()
+    for name in os.listdir(here):
+        if name.endswith(".py") or name == "libsplitzip.so" or (with_module and name.startswith("_fastcall")):
+            shutil.copy(os.path.join(here, name), there)
+    run = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, env={**os.environ, "PYTHONPATH": str(tmp_path), **env}, capture_output=True,
+                         text=True, timeout=120)
+    assert run.returncode == 0, run.stderr
+    return run.stdout
+
+
+CALLS = """
+import warnings
+import torch
+{before}
+with warnings.catch_warnings(record=True) as told:
+    warnings.simplefilter("always")
+    import paper_2605_01708_amd as sz
+    from paper_2605_01708_amd import binding
+    L = sz.lib()
+assert binding.__file__.startswith({at!r})
+items = (binding._CDItem * 1)()
+assert L.splitzip_decompress_batch(items, 0, sz.BF16, None, 0) == 0
+assert L.fast.splitzip_decompress_batch(items, 0, sz.BF16, None, 0) == {answer}
+assert sz.calibrate(torch.zeros(64, dtype=torch.int16), sz.BF16).dec[0] == 0
+print([str(w.message) for w in told])
+"""
+
+
+def test_the_library_alone_serves_every_call(tmp_path):
+    told = _elsewhere(tmp_path, CALLS.format(before="", at=str(tmp_path), answer=1))
+    assert "paper_2605_01708_amd.build" in told
+
+
+def test_a_module_for_another_torch_is_not_used(tmp_path):
+    told = _elsewhere(tmp_path, CALLS.format(before="torch.__version__ = '0.0'", at=str(tmp_path), answer=1), with_module=True)
+    assert "built for torch " + torch.__version__ in told
+
+
+def test_the_module_of_this_torch_is_used(tmp_path):
+    assert _elsewhere(tmp_path, CALLS.format(before="", at=str(tmp_path), answer=0), with_module=True) == "[]\n"
+
+
+def test_the_library_is_built_where_the_module_cannot_be(tmp_path):
+    code = "from paper_2605_01708_amd import build as b; import os; print(b.build() == b.LIB, [n for n in os.listdir(b.HERE) if n.startswith('_fastcall')])"
+    assert _elsewhere(tmp_path, code, with_module=True, HIPCC="true", CXX="no-such-compiler") == "True []\n"
 
 
 def _in_a_child(what) -> int:
