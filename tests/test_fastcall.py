@@ -65,8 +65,10 @@ def test_codebooks_of_a_batch_are_all_looked_at():
     bad.c.member[100] = 0
     x, out = torch.zeros(64, dtype=torch.int16), torch.zeros(8192, dtype=torch.uint8)
     base = (out.data_ptr() + 15) & ~15
-    for at in range(6):
-        cbs = [good[(q * 7) % 3] for q in range(6)]
+    # three by turns: none of the two looked at last comes again; K's and V's by turns and runs of one: it does, before the
+    # bad one and behind it
+    for order, at in ((order, at) for order in ((0, 1, 2), (0, 1), (0,), (0, 0, 1, 1)) for at in range(6)):
+        cbs = [good[order[q % len(order)]] for q in range(6)]
         cbs[at] = bad
         items = (binding._CItem * 6)()
         ditems = (binding._CDItem * 6)()
@@ -209,7 +211,7 @@ def test_both_ways_give_the_same(dtype, form, monkeypatch):
         shaped = torch.nn.Parameter(xd, requires_grad=False)
     stream = torch.cuda.Stream() if form == "stream" else None
     bound = sz.compress_bound(n, dtype)
-    taken = []
+    answers = {}   # entry point -> what its short way answered, call by call
 
     def all_calls():
         torch.cuda.synchronize()
@@ -219,7 +221,17 @@ def test_both_ways_give_the_same(dtype, form, monkeypatch):
         recs = [sz.new_sizes() for _ in range(5)]
         brec, drec = sz.new_sizes_array(2), sz.new_sizes()
         ys = [torch.zeros_like(xd) for _ in range(4)]
-        d_cbs = sz.DeviceCodebooks(2, dtype)
+        d_cbs, d_cb = sz.DeviceCodebooks(2, dtype), sz.DeviceCodebook(dtype)
+        d_cb.buf.copy_(torch.from_numpy(np.frombuffer(bytes(cb.c) + bytes(-len(bytes(cb.c)) % 8), np.int64).copy()))
+        # the words in pages of 2048, in reverse, and such a pool to decode into
+        table = torch.arange(-(-n // 2048) - 1, -1, -1, dtype=torch.int32, device="cuda")
+        pool = torch.zeros(table.numel() * 2048, dtype=xd.dtype, device="cuda")
+        pool[:n] = xd.view(-1)
+        pools = [pool.view(-1, 2048).flip(0).contiguous(), torch.zeros_like(pool), torch.zeros_like(pool), torch.zeros_like(pool)]
+        paged = [sz.Paged(p, table, 2048, 2048 * xd.element_size()) for p in pools]
+        outs2 = [torch.zeros(bound + 64, dtype=torch.uint8, device="cuda") for _ in range(5)]
+        rec2, brec2 = [sz.new_sizes() for _ in range(2)], [sz.new_sizes_array(2), sz.new_sizes_array(1)]
+        ys2, spare = [torch.zeros_like(xd) for _ in range(8)], torch.zeros_like(xd)
         cap = bound if form == "capacity" else None
         torch.cuda.synchronize()
         sz.compress(shaped, cb, outs[0], ws, recs[0], stream, cap)
@@ -227,18 +239,43 @@ def test_both_ways_give_the_same(dtype, form, monkeypatch):
         sz.variant_compress(shaped, v, vcb, outs[2], vws, recs[2], stream)
         sz.CalibrateBatchDevice([xd, xd], d_cbs).launch(stream)
         sz.CompressBatchDcb([xd, xd], d_cbs, outs[3:5]).launch(ws, brec, stream)
+        sz.compress_dcb(shaped, d_cb, outs2[0], ws, rec2[0], stream, cap)
+        sz.compress_paged(paged[0], n, cb, outs2[1], ws, rec2[1], stream, cap)
+        sz.CompressBatch([xd, xd], [cb, cb], outs2[2:4]).launch(ws, brec2[0], stream)
+        sz.CompressBatchPaged([pools[0]], [n], [cb], outs2[4:5], paged[0]).launch(ws, brec2[1], stream)
         torch.cuda.synchronize()
         sizes = [sz.read_sizes(r)[0] for r in recs[:3]] + [r[0] for r in sz.read_sizes_array(brec)]
+        sizes2 = [sz.read_sizes(r)[0] for r in rec2] + [r[0] for b in brec2 for r in sz.read_sizes_array(b)]
+        assert sizes2 == sizes[:1] * 5 and all(torch.equal(o[:sizes[0]], outs[0][:sizes[0]]) for o in outs2)
         sz.decompress(outs[0], sizes[0], n, cb, ys[0], drec, stream)
         sz.decompress_own(outs[1], sizes[1], n, dtype, ys[1], None, stream)
         sz.variant_decompress(outs[2], sizes[2], n, v, vcb, ys[2], None, stream)
         sz.DecompressBatchOwn(outs[3:4], sizes[3:4], [n], dtype, ys[3:4]).launch(drec, stream)
+        for q, r in enumerate((drec, None)):   # with a record and without one
+            sz.decompress_dcb(outs2[0], sizes[0], n, d_cb, ys2[4 * q], r, stream)
+            sz.decompress_paged(outs2[1], sizes[0], n, cb, paged[1 + q], r, stream)
+            sz.DecompressBatch(outs2[2:4], sizes[:1] * 2, [n] * 2, [cb] * 2, ys2[4 * q + 1:4 * q + 3]).launch(r, stream)
+            sz.DecompressBatchDcb(outs[3:5], sizes[3:5], [n] * 2, d_cbs, [ys2[4 * q + 3], spare]).launch(r, stream)
+            sz.DecompressBatchPaged(outs2[4:5], sizes[:1], [n], [cb], pools[3:4], paged[3]).launch(r, stream)
+        sz.decompress(outs[0], sizes[0], n, cb, ys[0], None, stream)
+        sz.decompress_own(outs[1], sizes[1], n, dtype, ys[1], drec, stream)
+        sz.variant_decompress(outs[2], sizes[2], n, v, vcb, ys[2], drec, stream)
+        sz.DecompressBatchOwn(outs[3:4], sizes[3:4], [n], dtype, ys[3:4]).launch(None, stream)
         torch.cuda.synchronize()
+        for y in ys2:
+            assert torch.equal(y, xd)
+        for p in pools[1:]:
+            assert torch.equal(p.view(-1, 2048).flip(0).reshape(-1)[:n], xd.view(-1))
+        assert drec[2] == 0
         return [t.cpu() for t in outs + recs + [brec, d_cbs.buf, d_cbs.hists, drec[2:]] + ys] + sizes
 
     L = sz.lib()
-    real = L.fast.splitzip_compress
-    monkeypatch.setattr(L.fast, "splitzip_compress", lambda *a: taken.append(real(*a)) or taken[-1])
+    entries = sorted(vars(L.fast))
+    for name in entries:
+        def asked(*a, name=name, real=getattr(L.fast, name)):
+            answers.setdefault(name, []).append(real(*a))
+            return answers[name][-1]
+        monkeypatch.setattr(L.fast, name, asked)
     if form == "mode":
         class Watch(torch.overrides.TorchFunctionMode):
             def __torch_function__(self, func, types, args=(), kwargs=None):
@@ -247,7 +284,11 @@ def test_both_ways_give_the_same(dtype, form, monkeypatch):
             fast = all_calls()
     else:
         fast = all_calls()
-    assert taken == [1 if form in ("subclass", "mode") else 0]
+    # every entry point was called, and taken wherever all of its arguments had the plain form
+    assert sorted(answers) == entries and len(entries) == 18
+    of_x = ("splitzip_compress", "splitzip_compress_noalloc", "splitzip_compress_dcb", "splitzip_variant_compress")
+    for name, got in answers.items():
+        assert set(got) == {1 if form == "mode" or (form == "subclass" and name in of_x) else 0}, name
     _general(monkeypatch)
     general = all_calls()
     for a, b in zip(fast, general):
