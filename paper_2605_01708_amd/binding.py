@@ -141,6 +141,8 @@ def lib():
         L.splitzip_internal_compress_plan.argtypes = [C.POINTER(_CItem), C.c_uint32, i, C.POINTER(C.c_uint32)]
         L.splitzip_internal_decompress_plan.restype = None
         L.splitzip_internal_decompress_plan.argtypes = [C.POINTER(_CDItem), C.c_uint32, i, C.POINTER(C.c_uint32)]
+        L.splitzip_internal_stream_room.restype = C.c_uint32
+        L.splitzip_internal_stream_room.argtypes = [u64, u64, i]
         L.splitzip_internal_xcd_tile.restype = C.c_uint32
         L.splitzip_internal_xcd_tile.argtypes = [C.c_uint32, C.c_uint32]
         L.splitzip_traffic_probe.restype = i
@@ -431,6 +433,11 @@ def internal_decompress_plan(n_elems, dtype: int, comp_bytes=None) -> dict:
         it.n_elems, it.comp_bytes = n, fixed_bytes(n, dtype) if comp_bytes is None else comp_bytes[k]
     lib().splitzip_internal_decompress_plan(items, len(n_elems), dtype, out)
     return dict(zip(("cpw", "workgroups", "by_xcd", "lds_pad"), out))
+
+
+def internal_stream_room(comp_bytes: int, n_elems: int, dtype: int) -> int:
+    """The escapes that a stream of comp_bytes bytes (its fixed part at least) has room for, n_elems at most (for tests)."""
+    return int(lib().splitzip_internal_stream_room(comp_bytes, n_elems, dtype))
 
 
 def internal_xcd_tile(workgroup: int, n_tiles: int) -> int:

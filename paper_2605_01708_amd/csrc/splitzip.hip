@@ -1183,6 +1183,12 @@ void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_item
 }
 // the tile that workgroup b of a tensor of n tiles takes in a launch by XCDs
 uint32_t splitzip_internal_xcd_tile(uint32_t b, uint32_t n) { return xcd_order(b, n - 1); }
+// how many escapes a stream of comp_bytes bytes has room for, as the decoder is told
+uint32_t splitzip_internal_stream_room(uint64_t comp_bytes, uint64_t n_elems, int dtype) {
+  DItem it;
+  describe_stream(nullptr, comp_bytes, nullptr, n_elems, dtype, &it);
+  return it.most;
+}
 void splitzip_internal_decompress_plan(const splitzip_ditem* items, uint32_t n_items, int dtype, uint32_t out[4]) {
   const DecompressPlan p = plan_decompress(items, n_items < kBatchMax ? n_items : kBatchMax, dtype);
   out[0] = p.cpw; out[1] = p.wgs; out[2] = p.by_xcd; out[3] = p.lds_pad;

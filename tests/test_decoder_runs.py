@@ -7,8 +7,6 @@ import torch
 import oracle
 import paper_2605_01708_amd as sz
 
-pytestmark = pytest.mark.gpu
-
 FORMATS = [(sz.BF16, np.uint16, 0x3f80, 0x0080), (sz.FP8_E5M2, np.uint8, 0x3c, 0x04)]   # words of a member and of another exponent
 
 
@@ -40,6 +38,7 @@ COUNTS = {
 }
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("cpw", [1, 2, 4, 8])
 @pytest.mark.parametrize("case", sorted(COUNTS))
 @pytest.mark.parametrize("dtype,np_dt,member,escape", FORMATS)
@@ -70,6 +69,7 @@ def test_runs_of_records(dtype, np_dt, member, escape, case, cpw):
             sz.internal_test_launch()
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("cpw", [1, 2, 4])
 @pytest.mark.parametrize("dtype,np_dt,member,escape", FORMATS)
 def test_tables_that_are_not_in_order(dtype, np_dt, member, escape, cpw):
@@ -108,3 +108,51 @@ def test_tables_that_are_not_in_order(dtype, np_dt, member, escape, cpw):
             own = (lo, hi) == (start[c], start[c + 1]) and not refused and (entry < len(counts) or lo == hi)
             if own or refused and counts[c] == 0:
                 assert np.array_equal(got[c * 1024:c * 1024 + size], x[c * 1024:c * 1024 + size]), (entry, c)
+
+
+@pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
+def test_room_for_records_by_the_length_of_a_stream(dtype):
+    """The most records that a stream of a length holds, worked out in closed form on the host: the largest m whose total fits."""
+    for n in (0, 1, 5, 1000, 5000, 123456, 2 ** 32 - 1):
+        fixed, m = sz.fixed_bytes(n, dtype), 0
+        for more in range(2000):
+            while m < n and sz.total_bytes(n, m + 1, dtype) <= fixed + more:
+                m += 1
+            assert sz.internal_stream_room(fixed + more, n, dtype) == m
+        for m in (n // 7, n // 2, n - 129, n - 128, n - 1, n):
+            if m > 0:
+                total = sz.total_bytes(n, m, dtype)
+                assert sz.internal_stream_room(total, n, dtype) == m
+                assert sz.internal_stream_room(total - 1, n, dtype) < m
+        assert sz.internal_stream_room(sz.compress_bound(n, dtype) + 10 ** 12, n, dtype) == n
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m", [1, 126, 127, 128, 129, 130, 255, 256, 257, 1024])
+@pytest.mark.parametrize("dtype,np_dt,member,escape", FORMATS)
+def test_streams_that_are_cut_short(dtype, np_dt, member, escape, m):
+    """A stream decoded by its own length is right; one byte less than it takes, and it is flagged and its records, whose
+    sections reach over the end, are left alone: the words come out as the planes have them."""
+    cb = _codebook(dtype)
+    x = _words([m // 2, m - m // 2, 0], 77, dtype, np_dt, member, escape, m)
+    xd = torch.from_numpy(x.view(np.int16) if dtype == sz.BF16 else x).cuda()
+    out = torch.full((sz.compress_bound(x.size, dtype) + 4096,), 0xff, dtype=torch.uint8, device="cuda")   # allocated beyond the stream's end
+    rec, drec = sz.new_sizes(), sz.new_sizes()
+    sz.compress(xd, cb, out, sz.Workspace(x.size, dtype), rec, capacity=sz.compress_bound(x.size, dtype))
+    total, got_m, status = sz.read_sizes(rec)
+    assert (got_m, status) == (m, 0) and total == sz.total_bytes(x.size, m, dtype)
+    # escapes have the dummy code, that of the codebook's first exponent
+    low, shift = (0x807f, 7) if dtype == sz.BF16 else (0x83, 2)
+    exps = (x.astype(np.uint32) >> shift) & (0xff if dtype == sz.BF16 else 0x1f)
+    planes = np.where(exps < 2, (x & low) | (cb.dec[0] << shift), x).astype(np_dt)
+    for cut, want in ((0, x), (1, planes)):
+        for batch in (False, True):
+            y = torch.full((x.size + 64,), 0x55, dtype=xd.dtype, device="cuda")
+            drec.zero_()
+            if batch:
+                sz.DecompressBatch([out, out], [total, total - cut], [x.size] * 2, [cb] * 2, [torch.empty_like(y), y]).launch(drec)
+            else:
+                sz.decompress(out, total - cut, x.size, cb, y, drec)
+            torch.cuda.synchronize()
+            assert sz.read_sizes(drec) == (total, m, sz.STATUS_BAD_STREAM if cut else 0)
+            assert np.array_equal(y[:x.size].cpu().numpy().view(np_dt), want) and (y[x.size:] == 0x55).all()
