@@ -961,15 +961,24 @@ __global__ __launch_bounds__(kThreads) void v_decode_kernel(const VDecodeArgs ar
           apply(64 * r + lane, rec_p[q][r], lane_before(rec_p[q][r], carry), ahead.of(rec_e[q][r], 64 * r + lane));
           carry = (uint32_t)__builtin_amdgcn_readlane(rec_p[q][r], 63);
         }
-        // the others, 64 at a time
+        // the others, four times 64 on their way at a time
 #pragma unroll 1
-        for (uint32_t i0 = kAhead; i0 < rec_n[q]; i0 += 64) {
+        for (uint32_t i0 = kAhead; i0 < rec_n[q]; i0 += 256) {
           const uint32_t lo = rec_lo[q] + i0, left = rec_n[q] - i0;
           const auto pr = run_of(pos_sec + (uint64_t)PB * lo, PB * left);
           const VValues<DT> vals(val, a.val_bits, lo, left);
-          const uint32_t p = PB == 2 ? ld_run2(pr, 2u * lane) : ld_run1(pr, lane), e = vals.of(vals.at(lane), lane);
-          apply(i0 + lane, p, lane_before(p, carry), e);
-          carry = (uint32_t)__builtin_amdgcn_readlane(p, 63);
+          uint32_t p[4];
+          typename VValues<DT>::Loaded e[4];
+#pragma unroll
+          for (uint32_t r = 0; r < 4; ++r) {
+            p[r] = PB == 2 ? ld_run2(pr, 2u * lane + 128u * r) : ld_run1(pr, lane + 64u * r);
+            e[r] = vals.at(lane + 64u * r);
+          }
+#pragma unroll
+          for (uint32_t r = 0; r < 4; ++r) {
+            apply(i0 + 64 * r + lane, p[r], lane_before(p[r], carry), vals.of(e[r], 64 * r + lane));
+            carry = (uint32_t)__builtin_amdgcn_readlane(p[r], 63);
+          }
         }
       }
     }
