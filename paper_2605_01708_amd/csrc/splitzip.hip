@@ -234,11 +234,18 @@ void launch_v_finish(dim3 g, hipStream_t st, const VArgs& a) {
   }
 }
 
+constexpr unsigned kVDecodeLdsPad = 13800;   // unused LDS asked for at the launch: seven workgroups of v_decode_kernel per CU
+
 template <int DT, int CB>
 void launch_v_decode(unsigned grid, hipStream_t st, uint32_t mode, uint32_t chunk_shift, const VDecodeArgs& a) {
   const dim3 g(grid), b(kThreads);
   if (mode == SPLITZIP_ESC_POS) {
-    if (chunk_shift == 10) hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_POS, 10>), g, b, 0, st, a);
+    // Long launches of BF16 under 4-bit codes: seven workgroups per CU instead of eight.  us per call with eight / seven / six:
+    // 39.0 / 38.6 / 38.9 (65 536 chunks), 59.2 / 58.1 / 57.8 (98 304), 77.4 / 76.0 / 76.3 (131 072), 300.6 / 294.0 / 294.5 (524 288);
+    // 3-bit codes, sentinels and FP8 gain nothing by it (131 072 chunks: 75.3 / 76.1, 75.9 / 79.9, E5M2 50.4 / 50.6), nor do streams
+    // with more than one escape in 16 elements (98 304 chunks, 6.6 %: 60.2 / 61.5), by the bytes beyond the fixed part.
+    const unsigned pad = DT == SPLITZIP_BF16 && CB == 4 && grid >= 16384u && !many_escapes(a.capacity - a.off_pos, a.n) ? kVDecodeLdsPad : 0u;
+    if (chunk_shift == 10) hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_POS, 10>), g, b, pad, st, a);
     else hipLaunchKernelGGL((v_decode_kernel<DT, CB, SPLITZIP_ESC_POS, 8>), g, b, 0, st, a);
   } else if (mode == SPLITZIP_ESC_SENTINEL) {
     // By what the caller says it holds beyond the fixed part, a value per escape: more than a quarter of the elements, or

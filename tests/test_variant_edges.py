@@ -118,3 +118,27 @@ def test_both_ways_to_put_sentinels_right(dt, cb, k, chunk, vb):
                 bad = buf.clone()
                 bad[at] = byte
                 assert decode(bad, blob.size)[1] == decode(bad, bound)[1], (name, n, at)
+
+
+@pytest.mark.parametrize("chunks,share", [(65532, 0.0), (65533, 0.0), (65533, 0.05), (65533, 0.2), (98304, 0.0)])
+def test_long_streams_of_4_bit_codes(chunks, share):
+    """BF16 streams of 16 384 workgroups and more, with few escapes, are decoded with fewer workgroups per CU."""
+    n = chunks * 1024 - 7
+    x = kv_synth.kv_bf16(chunks, 1, device="cuda").view(-1)[:n].view(torch.int16)
+    if share:
+        x = torch.where(torch.rand(n, device="cuda") < share, torch.randint(-32768, 32767, (n,), dtype=torch.int16, device="cuda"), x)
+    x = x.contiguous()
+    v = sz.variant(sz.BF16, 4, 16, sz.ESC_POS, 1024)
+    cb = sz.variant_codebook_from_dec(sz.calibrate(kv_synth.kv_bf16(64, 1), sz.BF16).dec, v)
+    out = torch.zeros(sz.variant_total_bytes(n, n // 4, v), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(sz.variant_workspace_bytes(n, v), dtype=torch.uint8, device="cuda")
+    rec, st = sz.new_sizes(), sz.new_sizes()
+    sz.variant_compress(x, v, cb, out, ws, rec)
+    total, m, status = sz.read_sizes(rec)
+    assert status == 0 and (m > n // 16) == (share > 0.1)
+    for comp_bytes in (total, out.numel()):
+        y = torch.full((n + 64,), 0x55, dtype=torch.int16, device="cuda")
+        st.zero_()
+        sz.variant_decompress(out, comp_bytes, n, v, cb, y, st)
+        assert sz.read_sizes(st) == (total, m, 0)
+        assert torch.equal(y[:n], x) and (y[n:] == 0x55).all()
