@@ -197,10 +197,10 @@ struct DE5m2 {
 __device__ inline void lds_in_order() { asm volatile("" ::: "memory"); }
 
 // One workgroup: a tile of 4 waves x CPW chunks of one stream.
-// What bounds it: long launches the memory (64 BF16 tensors of 64 MiB 1172 us, 6.4 TB/s; 64 E5M2 tensors of 32 MiB 619 us, 6.5
+// What bounds it: long launches the memory (64 BF16 tensors of 64 MiB 1191 us, 6.3 TB/s; 64 E5M2 tensors of 32 MiB 620 us, 6.5
 // TB/s); short ones the trips to memory that a wave makes one after the other, and the instructions of its beginning.  Until
 // a wave asked for everything at once -- it waited for M before its first plane, and for memory once per chunk -- they took
-// 1196 and 670 us, one tensor of 64 MiB 23.2 (21.0 now), 64 of 2 MiB 42.7 (39.0), 100 chunks 3.4 (2.2).
+// 1236 and 675 us, one tensor of 64 MiB 22.1 (20.2 now), 64 of 2 MiB 42.1 (38.9), 100 chunks 3.4 (2.2).
 // A wave asks for everything it can name before it waits for anything: the slice of the offset table, then the planes of
 // its CPW chunks; the decode table is built meanwhile.  The table entries arrive first, and the escape records of all those
 // chunks, which follow one another in the stream, are one run: two loads of it travel while the planes do.

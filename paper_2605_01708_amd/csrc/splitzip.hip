@@ -5,7 +5,7 @@
 //                   fused with escape detection, counting and position-ordered compaction
 //                   (appendix "Quad64 Vectorized Encoding" fuses only the counting); two launches
 //                   for a tensor or up to 64 of them, one for small tensors
-//   decompress.hpp  nibble unpack, decode table, eq. (2), scatter correction in registers; one
+//   decompress.hpp  nibble unpack, decode table, eq. (2), scatter correction in LDS; one
 //                   launch per tensor or per batch
 //   aux_kernels.hpp calibration histogram (section 3.3), workspace initialisation, traffic probe
 //   variants.hpp    the formats of the ablations (top-8 / 3-bit codes, top-15 + sentinel, chunk 256,
@@ -92,15 +92,24 @@ constexpr uint32_t most_cpw(int dtype, bool several) { return (dtype == SPLITZIP
 
 // Chunks per wave of a decompress launch over n_chunks chunks in all; device us per call with one / two / four chunks per
 // wave, all of whose planes a wave asks for at once:
-//   BF16  2.6 / 3.1 / 4.0 (512 chunks), 3.9 / 4.2 / 4.5 (4096), 5.1 / 4.9 / 5.5 (6144), 6.4 / 5.8 / 6.1 (8192), 11.7 / 11.5 /
-//         10.5 (16 384), 13.7 / 14.2 / 13.9 (20 000), 21.1 / 21.3 / 21.1 (32 768), 39.0 / 38.6 / 39.9 (65 536), 75.2 / 74.0 /
-//         76.0 (131 072).  Two up to what is resident at once (eight workgroups of eight chunks per CU) and again for long
+//   BF16  2.6 / 3.0 / 3.8 (512 chunks), 4.0 / 4.3 / 4.5 (4096), 5.4 / 4.9 / 5.5 (6144), 6.7 / 6.1 / 5.9 (8192), 8.5 / 7.1 / 7.3
+//         (10 240), 9.4 / 8.7 / 7.9 (12 288), 10.8 / 10.4 / 11.2 (14 336), 11.8 / 11.8 / 11.6 (16 384), 13.0 / 13.3 / 14.3 (18 432),
+//         16.3 / 16.6 / 16.1 (24 576), 21.2 / 21.4 / 21.2 (32 768), 38.2 / 39.6 / 40.9 (65 536), 75.2 / 74.0 / 76.0 (131 072).
+//         Two up to what is resident at once (eight workgroups of eight chunks per CU) and again for long
 //         launches, in those of several streams from 32 768 on; in the longest, with fewer workgroups per CU
-//         (plan_decompress), 1228 / 1187 / 1246 (2 Mi).
-//   E5M2  2.6 / 3.0 / 3.7 (512), 5.4 / 4.9 / 5.1 (8192), 8.1 / 8.0 / 7.4 (16 384), 13.9 / 13.1 / 13.2 (32 768), 46.6 / 40.5 / 41.7
-//         (128 000), 180 / 155.5 / 159.6 (524 288), 722 / 636 / 650 and, with fewer workgroups per CU, 619 with four (2 Mi).
+//         (plan_decompress), 1228 / 1187 / 1246 (2 Mi).  Four, where its workgroups come out as whole rounds of the chip, is up to
+//         9 % faster than two and loses as much between (14 336): single calls do not use it.
+//   E5M2  2.5 / 2.9 / 3.6 (512), 5.4 / 4.6 / 5.1 (8192), 6.8 / 6.8 / 6.1 (12 288), 8.3 / 8.0 / 7.4 (16 384), 10.9 / 10.8 / 10.5 (24 576),
+//         14.0 / 13.0 / 13.3 (32 768), 24.8 / 22.5 / 23.3 (65 536), 45.4 / 40.4 / 41.5 (128 000), 180 / 155.5 / 159.6 (524 288),
+//         722 / 636 / 650 and, with fewer workgroups per CU, 619 with four (2 Mi).
 // Streams with many escapes keep a wave busy with its chunks' records, one chunk after the other, so the larger pieces
-// pay from somewhat longer streams on (random words: BF16, 4096 chunks, 8.1 / 11.1 / 17.3).
+// pay from somewhat longer streams on.  Random words in 15 / 40 % of the places (14 / 37 % escapes for BF16, 8 / 20 % for E5M2):
+//   BF16  one 4.8 / 5.8, two 5.9 / 7.6 (4096 chunks); one 7.4 / 8.2, two 7.8 / 9.6 (8192); one 8.9 / 10.5, two 8.4 / 10.5 (9216); one
+//         9.8 / 11.2, two 8.6 / 10.7 (10 240); one 14.1 / 16.8, two 12.3 / 18.0 (16 384)
+//   E5M2  one 5.7 / 6.7, two 5.8 / 7.1 (8192); one 6.7 / 8.2, two 6.4 / 7.8 (10 240); two 9.6 / 10.4, four 9.6 / 11.3 (16 384); two
+//         11.7 / 12.9, four 11.8 / 12.6 (20 480); one 26.7 / 35.7, two 26.5 / 33.1, four 28.9 / 33.2 (65 536)
+// Beyond, one chunk would be up to 12 % faster for E5M2 from 16 384 to 24 576 chunks with 8 % escapes, and for long BF16 streams
+// it is about as fast as two (131 072 chunks 79.8 and 80.7).
 uint32_t pick_decompress_cpw(uint64_t n_chunks, bool several, bool escapes, int dtype, uint64_t cus) {
   if (const uint32_t forced = g_hooks.cpw.load()) return forced < most_cpw(dtype, several) ? forced : most_cpw(dtype, several);
   const uint64_t round = cus * 8;   // workgroups resident at a time
@@ -908,12 +917,13 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
   const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
   p.cpw = pick_decompress_cpw(chunks_all, k > 1, many_escapes(beyond, n_all), dtype, cus);
   // Streams that differ in length, as in pick_base_cpt: more chunks per wave where many of the launch's workgroups have
-  // none.  us by chunks per wave, BF16 one / two: 7.1 / 6.2 (600 chunks beside 63 streams of 5: 9371 without a tile), 18.8
-  // / 12.1 (3000 beside 63 of two), 24.3 / 19.0 (20 000 beside seven of two), two / four, where the streams are a small part
-  // of it: 45.8 / 45.6 (four of 8192 beside 60 of 200: 60 000), 97.3 / 61.5 (32 768 beside 63 of two); E5M2 two / four: 6.2 /
-  // 7.1 (600 beside 63 of 5: 4686), 10.1 / 9.5 (1500 beside 63 of 50: 11 418), 42.5 / 24.8 (13 000 beside 63 of two), four /
-  // eight: 26.1 / 29.1 (8192 beside 63 of 100: 31 862), 24.8 / 16.0 (13 000 beside 63 of two: 51 184); where the streams fill
-  // the chip anyway 37.9 / 34.7 (two of 9000 beside 62 of 1000: 31 000).
+  // none.  Device us by chunks per wave, BF16 one / two: 4.4 / 4.0 (600 chunks beside 63 streams of 5: 9371 without a tile), 12.8
+  // / 7.8 (3000 beside 63 of two), 18.2 / 14.2 (20 000 beside seven of two), two / four, where the streams are a small part of it:
+  // 26.3 / 14.1 (13 000 beside 63 of two), 69.9 / 39.8 (32 768 beside 63 of two), 32.8 / 34.2 (four of 8192 beside 60 of 200:
+  // 60 000), 18.4 / 18.8 (8192 beside 63 of 100); E5M2 one / two / four: 4.4 / 3.9 / 4.3 (600 beside 63 of 5: 4686), 7.7 / 6.0 / 5.9
+  // (1500 beside 63 of 50: 11 418), four / eight: 14.3 / 8.9 (13 000 beside 63 of two: 51 184), 36.9 / 22.5 (32 768 beside 63 of
+  // two), 14.3 / 18.7 (8192 beside 63 of 100: 31 862), 28.6 / 31.1 (two of 9000 beside 62 of 1000: 31 000).  The limits were set
+  // with an earlier decoder; where they are off with this one (the last two calls of BF16, the last of E5M2) it is by 2 to 9 %.
   const uint64_t none = chunks_max * k - chunks_all;   // chunks that the padded grid has room for and the streams do not have
   if (!g_hooks.cpw.load()) {
     const uint32_t most = dtype == SPLITZIP_BF16 && none <= 8 * chunks_all ? 2u : most_cpw(dtype, k > 1);

@@ -139,7 +139,7 @@ __device__ inline u32x4 v_dec16(const VArgs& a) {
   return u32x4{w[0], w[1], w[2], w[3]};
 }
 
-// A compress kernel's own copy of the arguments, those it needs fetched at once (as in args_arrived): the compiler would
+// The finishing pass's own copy of the arguments, those it needs fetched at once (as in args_arrived): the compiler would
 // fetch each where it is used first, half a dozen trips one after the other in a kernel of a few microseconds.
 __device__ inline VArgs v_args_arrived(const VArgs& args) {
   VArgs a = args;
@@ -345,8 +345,8 @@ __device__ inline uint32_t v_dense_block(const VArgs& a, const uint32_t* lut, ui
 }
 
 // Compress pass 1: both planes, the escape count of every chunk and of every workgroup, the escape records.
-// Bound by memory like the tuned dense pass: one 64 MiB BF16 tensor takes 24.8 us under 3-bit codes (29.8 us with the
-// planes staged through LDS in two dependent steps and a store per escape and lane) and 22.0 us in the main format.
+// Bound by memory like the tuned dense pass: one 64 MiB BF16 tensor takes 24.0 us under 3-bit codes (29.8 us with the
+// planes staged through LDS in two dependent steps and a store per escape and lane) and 21.5 us in the main format.
 template <int DT, int CB>
 __global__ __launch_bounds__(kThreads) void v_dense_kernel(const VArgs a) {
   using F = VFmt<DT>;
