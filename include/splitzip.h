@@ -138,10 +138,13 @@ size_t splitzip_compress_bound(uint64_t n_elems, int dtype);
  * (the escape count of every tile of the tensor, 4 to 16 KB of words or, in
  * very large tensors, more) and a staging area of
  * n_elems bytes and a little more (the tiles' escape records until their rank
- * in the stream is known).  A compress call is two kernel launches (one for
- * tensors of a few dozen chunks, which a workgroup does by itself): the first
+ * in the stream is known).  A compress call is two kernel launches: the first
  * does the dense work tile by tile, the second ranks and places the escape
- * records; no workgroup ever waits for another, so the calls run correctly
+ * records.  Up to 2 Mi elements (4 Mi in tensors of up to 1 Mi), a call that is not captured into a graph
+ * is one launch, whose workgroups tell one another their counts; captured, that
+ * is so up to 40 chunks of BF16 or 48 of E5M2 per tensor.  No workgroup waits
+ * for another without an end (in that one launch for some 50 us at most, then
+ * its work is left to those that come after it), so the calls run correctly
  * whatever else the device is doing and however little of a launch fits the
  * device at a time.  No word of a workspace needs a defined value before a
  * call: splitzip_workspace_init exists for symmetry (it clears a small
@@ -162,8 +165,9 @@ int splitzip_workspace_init(void* d_workspace, size_t workspace_bytes, void* str
  * enqueued.  If the fixed part fits but the escapes do not, everything that
  * fits is written, status gets SPLITZIP_STATUS_OVERFLOW and total_bytes is
  * the size a retry needs.  n_elems == 0 is valid (header and one offset).
- * Two launches on `stream` (three above about 180 Mi elements; one where no
- * tensor of the call has more than 40 chunks of BF16 or 48 of E5M2).
+ * Two launches on `stream` (three above about 180 Mi elements; one up to 4
+ * Mi elements, while a graph is captured up to 40 chunks of BF16 or 48 of
+ * E5M2).
  * The output is a pure function of (input, codebook): independent of
  * scheduling, capacity slack and earlier calls. */
 int splitzip_compress(const void* d_in, uint64_t n_elems, int dtype, const splitzip_codebook* cb,

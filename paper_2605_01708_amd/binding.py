@@ -135,6 +135,8 @@ def lib():
         L.splitzip_compress_noalloc.argtypes = [vp, u64, i, cbp, vp, sz, vp, vp]
         L.splitzip_internal_test_hooks.restype = None
         L.splitzip_internal_test_hooks.argtypes = [u64, u64, C.c_uint32, u64]
+        L.splitzip_internal_test_short.restype = None
+        L.splitzip_internal_test_short.argtypes = [C.c_uint32]
         L.splitzip_internal_test_launch.restype = None
         L.splitzip_internal_test_launch.argtypes = [C.c_uint32, C.c_uint32, C.c_uint32]
         L.splitzip_internal_compress_plan.restype = None
@@ -415,6 +417,15 @@ def internal_test_launch(cpt: int = 0, cpw: int = 0, xcd: int = 0) -> None:
     of the decoders (cpw), 1, 2, 4 or 8, and the tiles' order in batch launches (xcd: 1 their own, 2 xcd_order).
     0 = by the rules."""
     lib().splitzip_internal_test_launch(cpt, cpw, xcd)
+
+
+def internal_test_short(looks: int = 0) -> None:
+    """How often a workgroup of a short compress launch looks for the others' counts before it leaves its tile to them (not
+    part of splitzip.h).  0 = as built; INTERNAL_NO_SHORT: two launches instead."""
+    lib().splitzip_internal_test_short(looks)
+
+
+INTERNAL_NO_SHORT = 0xFFFFFFFF
 
 
 def internal_compress_plan(n_elems, dtype: int) -> dict:

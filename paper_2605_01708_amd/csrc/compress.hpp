@@ -429,6 +429,7 @@ __device__ void compress_write_trailer(const Planes& a, const u32x4& dec, splitz
 // M; those before the group: its first rank), adds what lies before each tile to the tile's table entries and
 // moves the records from the slots to their ranks in the position and value arrays.  A tile with more escapes
 // than its slot (or its LDS staging) holds is encoded once more from the words, straight to the final place.
+// (Launches that are few chunks, and not captured, do both in one: compress_short_kernel.)
 // Between the passes lies a kernel boundary: no workgroup ever waits for another, nothing needs to be resident
 // together, and no word of the workspace needs a defined value before a call.
 constexpr uint32_t kTileThreads = 256;
@@ -459,12 +460,12 @@ struct TileShared {
   splitzip_sizes* sizes;          // one record per tensor
   uint8_t* status;                // per tensor: u32 count of every tile, then u32 sum of every kSumGroup tiles
   uint8_t* stage;                 // per tensor stage_cap bytes: the tiles' slots
-  uint64_t stage_cap;
+  uint64_t stage_cap;             // (compress_short_kernel, which stages nothing there: the call's tag)
   const splitzip_codebook* d_cbs; // nullable: codebooks in device memory, one per tensor, used instead of dec
   Words paging;                   // table and page geometry shared by all tensors (table null: contiguous tensors); base unused
   uint32_t cpt;                   // chunks per wave and tile, a power of two
   uint32_t tile_shift;            // log2 of the chunks per tile (4 cpt)
-  uint32_t slot_cap;              // records per tile slot (the same for all tensors of the launch)
+  uint32_t slot_cap;              // records per tile slot (the same for all tensors of the launch; compress_short_kernel: how often a workgroup looks for the others' counts)
   uint32_t finish_groups;         // groups of kGroup tiles per workgroup of the finishing pass, 1 to kFinishMost
   uint32_t use_group_sums;        // the finishing pass reads sums of kSumGroup tile counts (tile_group_sum_kernel) instead of all tile counts
   uint32_t by_xcd;                // the dense pass takes its tiles in xcd_order
@@ -874,7 +875,7 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
 }
 
 // ---- small tensors: one launch, one workgroup per tensor ----
-// Up to F::kSmallChunks chunks a tensor is one workgroup's work: 16 waves own consecutive runs of its chunks, so the
+// Up to F::kSmallChunks chunks in a captured call, and up to kSmallestShort in others, a tensor is one workgroup's work: 16 waves own consecutive runs of its chunks, so the
 // counts meet in LDS, every rank is known behind one barrier and nothing is staged outside the workgroup.  What bounds
 // such a call is the launch: the second one takes the host 2.7 us and the device 3.1 us.  Device us per call, this
 // kernel / two launches: BF16 5.2 / 6.8 (17 chunks), 6.4 / 6.7 (33), 7.3 / 6.6 (49), 10.6 / 6.6 (97); E5M2 5.6 / 7.6
@@ -947,6 +948,213 @@ __global__ __launch_bounds__(kSmallThreads) void compress_small_kernel(const Til
     }
   }
   if (wave == kSmallWaves - 1) compress_write_trailer(P, dec, a.sizes + item, M, 0u, lane);   // the wave with the fewest chunks
+}
+
+// ---- short launches: one kernel, whose workgroups tell one another their counts ----
+// What bounds a short call is its launches: the finishing pass takes the host 2.3 us, and the device 3 us and the gap in
+// front of it.  Here a workgroup takes a tile of four chunks, one per wave, as in the dense pass, tells its count to the others
+// of its tensor, waits until all counts are there, and places its own records, which have not left its LDS.
+//   A tile's word in the status area: the call's tag (47 bits, another one for every call, so that no word needs a defined
+//   value before a call), kShortLeft, kShortTaken and the count.  One atomic word says all there is to say: nothing else that
+//   a workgroup writes is read by another.  There are kShortCopies copies of a tensor's words and a workgroup reads one of
+//   them: all workgroups reading the same few lines from the device's point of coherence took longer than the work.
+//   No wait is without an end.  A workgroup that has looked a.slot_cap times (the rest of the launch does not get onto the
+//   chip) marks its tile as left, looks once more and, if counts are missing still, ends.  The mark and the count are
+//   each written, and the write waited for, before the writer looks at the other words: so whoever publishes last of all
+//   sees all counts the first time it looks, and with them the mark of every workgroup that looked for the last time
+//   before that.  Tiles left are encoded again by whichever workgroup takes them first (kShortTaken, in the first copy).
+constexpr uint32_t kShortCopies = 8;
+constexpr int kShortTagShift = 17;
+constexpr uint32_t kShortCount = 0x7fffu, kShortLeft = 0x8000u, kShortTaken = 0x10000u;
+static_assert(kTileThreads / 64 * kChunk <= kShortCount && (kShortLeft | kShortTaken | kShortCount) >> kShortTagShift == 0, "a tile's count and its marks below the tag");
+// bytes of one copy of a tensor's words; a tensor without elements has one, too
+__host__ __device__ inline uint64_t short_copy_bytes(uint64_t tiles) { return a256(8 * (tiles ? tiles : 1)); }
+
+// EACH: words that a thread looks at; a tensor has no more tiles than that many times the threads.  us of this kernel and of the two
+// launches, without the gap between those (rocprofv3's trace, BF16): 4.4 and 3.4 + 2.4 (100 chunks), 5.2 and 3.9 + 3.0 (1024).
+// Workgroups of eight waves are 0.25 us faster at 2048 chunks but get onto a busy chip late, and everyone waits for them (beside
+// elementwise kernels that fill it 22 to 27 us a call, 16.9 with four, two launches 20.2; at 4096 chunks 216 and 21); two
+// chunks per wave take 0.3 us more.  It gains most where chunks escape whole: the finishing pass encodes tiles whose
+// records outgrow their slots once more, a workgroup 16 of them (2048 chunks of random words 62 us a call, 10.8 this way).
+// The loop over tiles that were left stands behind the straight way: one loop around both cost 0.3 us, in registers.
+template <typename F, uint32_t N, int EACH>
+__global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const TileArgs<N> args) {
+  constexpr int NW = kTileThreads / 64;
+  __shared__ uint16_t lut[256];
+  __shared__ uint16_t stage_pos[NW][kChunk];   // room for all of a wave's records
+  __shared__ uint8_t stage_val[NW][kChunk];
+  __shared__ u32x4 s_park[kTileThreads];
+  __shared__ uint32_t s_cnt[NW], s_all[NW], s_before[NW], s_state[NW], s_won;
+  __shared__ uint32_t s_tile[EACH * kTileThreads];   // only where tiles were left
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t item = blockIdx.y, own = blockIdx.x;
+  TileShared a;
+  TileItem it;
+  args_arrived(args, item, a, it);
+  const Planes P = make_planes(item_words(a.paging, it.in), it.out, it.n, it.capacity, F::DT);
+  const uint32_t n_tiles = (P.n_chunks + NW - 1) / NW;
+  if (own >= (n_tiles ? n_tiles : 1u)) return;   // a tensor without elements still gets its header
+  uint64_t* words = reinterpret_cast<uint64_t*>(a.status + it.status_off);   // the first copy of them
+  const uint32_t copy = (uint32_t)(short_copy_bytes(n_tiles) / 8);            // words from one copy to the next
+  const uint64_t tag = a.stage_cap;
+  uint32_t* park = reinterpret_cast<uint32_t*>(&s_park[tid]);
+  const LdsSink lds{stage_pos[wave], stage_val[wave], 0u, kChunk};
+
+  uint32_t c = 0, count = 0;              // the wave's chunk and its escapes
+  uint32_t in_tile = 0, total = 0;        // escapes of the tile before the wave's chunk; all of them
+  // a tile's planes out and its records staged
+  auto encode = [&](uint32_t tile, bool build) {
+    c = NW * tile + wave;
+    count = 0;
+    const uint64_t cbase = (uint64_t)c * kChunk;
+    typename F::Regs w;
+    auto table = [&]() {   // while the words are on their way
+      if (!build) return;
+      build_encode_table(lut, a.dec16_of(it, item), tid, F::kLutShift);
+      lds_barrier();
+    };
+    if (F::full(P, (uint64_t)(NW * tile + NW - 1) * kChunk)) {   // all chunks of the tile are complete
+      F::template load<true>(P, chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_wave_chunk(P.w, c) : 0u), cbase, lane, w);
+      table();
+      count = F::template process<true, true>(P, lut, park, cbase, lane, w, 0u, lds);
+    } else {
+      const bool full = F::full(P, cbase);
+      if (c < P.n_chunks) {
+        const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_wave_chunk(P.w, c) : 0u);
+        if (full) F::template load<true>(P, cptr, cbase, lane, w);
+        else F::template load<false>(P, cptr, cbase, lane, w);
+      }
+      table();
+      if (c < P.n_chunks) {
+        count = full ? F::template process<true, true>(P, lut, park, cbase, lane, w, 0u, lds)
+                     : F::template process<false, true>(P, lut, park, cbase, lane, w, 0u, lds);
+      }
+    }
+    if (lane == 0) s_cnt[wave] = count;
+    lds_barrier();
+    in_tile = total = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      const uint32_t x = s_cnt[q];
+      in_tile += q < wave ? x : 0u;
+      total += x;
+    }
+  };
+
+  uint64_t v[EACH];        // thread and register <-> tile
+#pragma unroll
+  for (int q = 0; q < EACH; ++q) v[q] = tag;
+  uint32_t state = 0;      // bit 0: all counts are there; bit 1: a tile was left
+  // The own word, written at the device's point of coherence before anyone of this workgroup goes on; then the others', as
+  // often as `times` at most.
+  auto tell_and_look = [&](uint32_t mark, uint32_t times) {
+    if ((uint32_t)tid < kShortCopies) st_agent(words + tid * copy + own, tag | mark | total);
+    if (wave == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+    bool here;
+    for (;;) {
+      here = true;
+#pragma unroll
+      for (int q = 0; q < EACH; ++q)
+        if (q * kTileThreads + tid < n_tiles) v[q] = ld_agent(words + (own % kShortCopies) * copy + q * kTileThreads + tid);
+#pragma unroll
+      for (int q = 0; q < EACH; ++q) here = here && ((v[q] ^ tag) >> kShortTagShift) == 0;
+      here = __all(here);
+      if (here || --times == 0) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    uint32_t marks = 0;
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) marks |= (uint32_t)v[q];
+    const bool left = __any(marks & kShortLeft);
+    if (lane == 0) s_state[wave] = (here ? 1u : 0u) | (left ? 2u : 0u);
+  };
+  auto overall = [&]() {
+    state = 1u;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      const uint32_t x = s_state[q];
+      state = (state & (x | 2u)) | (x & 2u);
+    }
+  };
+  uint32_t first = 0, M = 0;   // escapes of the tensor before a tile; all of them
+  auto rank = [&](uint32_t tile) {   // with a barrier
+    uint32_t all = 0, before = 0;
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) {
+      const uint32_t x = (uint32_t)v[q] & kShortCount;
+      all += x;
+      before += q * kTileThreads + tid < tile ? x : 0u;
+    }
+    all = wave_last(wave_incl_scan(all));
+    before = wave_last(wave_incl_scan(before));
+    if (lane == 0) {
+      s_before[wave] = before;
+      s_all[wave] = all;
+    }
+    lds_barrier();
+    first = M = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      first += s_before[q];
+      M += s_all[q];
+    }
+  };
+  // the tile's records and table entries where they belong; the stream's header and pads with the first tile
+  auto place = [&](uint32_t tile) {
+    const uint64_t off_val = P.off_pos + a256(2ull * M);
+    FinalSink fin;
+    fin.pos = reinterpret_cast<uint16_t*>(P.out + P.off_pos);
+    fin.pos_room = room32(P.capacity, P.off_pos, 1);
+    fin.val = P.out + off_val;
+    fin.val_room = room32(P.capacity, off_val, 0);
+    const uint32_t base = first + in_tile;
+    if (c < P.n_chunks && lane == 0) reinterpret_cast<uint32_t*>(P.out + P.off_tab)[c] = base;
+    for (uint32_t i = lane; i < count; i += 64) fin.put(base + i, stage_pos[wave][i], stage_val[wave][i]);
+    if (tile == 0 && wave == NW - 1) compress_write_trailer(P, a.dec16_of(it, item), a.sizes + item, M, 0u, lane);
+  };
+  // whether a tile that was marked as left is this workgroup's now
+  auto take = [&](uint32_t tile, uint32_t told) -> bool {
+    __syncthreads();
+    if (tid == 0) {
+      uint64_t seen = tag | kShortLeft | told;
+      s_won = __hip_atomic_compare_exchange_strong(words + tile, &seen, seen | kShortTaken, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
+    }
+    __syncthreads();
+    return s_won != 0;
+  };
+
+  encode(own, true);
+  tell_and_look(0u, a.slot_cap);
+  rank(own);
+  overall();
+  if (state == 1u) {
+    place(own);
+    return;
+  }
+  bool keep = (state & 1u) != 0;
+  if (!keep) {
+    __syncthreads();
+    tell_and_look(kShortLeft, 1u);
+    rank(own);
+    overall();
+    if (!(state & 1u)) return;
+    keep = take(own, total);
+  }
+  if (keep) place(own);
+  // tiles that their workgroups have left
+#pragma unroll
+  for (int q = 0; q < EACH; ++q) s_tile[q * kTileThreads + tid] = (uint32_t)v[q] & (kShortLeft | kShortTaken | kShortCount);
+  __syncthreads();
+#pragma unroll 1
+  for (uint32_t tile = 0; tile < n_tiles; ++tile) {
+    const uint32_t told = s_tile[tile];
+    if (tile == own || !(told & kShortLeft) || (told & kShortTaken) || !take(tile, told & kShortCount)) continue;
+    encode(tile, false);
+    rank(tile);
+    place(tile);
+  }
 }
 
 #endif  // SPLITZIP_COMPRESS_HPP

@@ -4,7 +4,7 @@
 //   compress.hpp    dense transform (paper section 3.2 eq. (1), encode table, nibble pack, planes)
 //                   fused with escape detection, counting and position-ordered compaction
 //                   (appendix "Quad64 Vectorized Encoding" fuses only the counting); two launches
-//                   for a tensor or up to 64 of them, one for small tensors
+//                   for a tensor or up to 64 of them, one for few chunks
 //   decompress.hpp  nibble unpack, decode table, eq. (2), scatter correction in LDS; one
 //                   launch per tensor or per batch
 //   aux_kernels.hpp calibration histogram (section 3.3), workspace initialisation, traffic probe
@@ -19,6 +19,8 @@
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
+#include <time.h>
+#include <unistd.h>
 
 #include <atomic>
 #include <mutex>
@@ -79,8 +81,10 @@ struct TestHooks {
   std::atomic<uint32_t> cpt{0};   // 1, 2, 4 or 8
   std::atomic<uint32_t> cpw{0};   // 1, 2, 4 or 8, most_cpw at most
   std::atomic<uint32_t> xcd{0};   // 1: batch launches keep the tiles' own order, 2: they take xcd_order
+  std::atomic<uint32_t> short_looks{0};   // how often a workgroup of compress_short_kernel looks for the counts of the others; kNoShort: no such launches
   bool any() const { return stage_bytes || status_bytes || finish_groups || direct_bytes || cpt || xcd; }   // the two-launch path is meant
 };
+constexpr uint32_t kNoShort = 0xffffffffu;
 TestHooks g_hooks;
 
 // Whether more than one element in 16 may have escaped, by the bytes that the caller says it holds beyond the fixed part
@@ -565,6 +569,8 @@ void splitzip_internal_test_hooks(uint64_t stage_bytes, uint64_t status_bytes, u
   g_hooks.finish_groups = finish_groups == 1 || finish_groups == 2 || finish_groups == 4 ? finish_groups : 0;
 }
 
+void splitzip_internal_test_short(uint32_t looks) { g_hooks.short_looks = looks; }
+
 void splitzip_internal_test_launch(uint32_t cpt, uint32_t cpw, uint32_t xcd) {
   const auto size_or_0 = [](uint32_t v) { return v == 1 || v == 2 || v == 4 || v == 8 ? v : 0u; };
   g_hooks.cpt = size_or_0(cpt);
@@ -712,22 +718,81 @@ void launch_small(unsigned k, hipStream_t st, const TileArgs<kBatchMax>& args) {
   }
 }
 
+template <typename F, int EACH>
+void launch_short(unsigned tiles, unsigned k, hipStream_t st, const TileArgs<kBatchMax>& args) {
+  const dim3 grid(tiles ? tiles : 1u, k), block(kTileThreads);
+  if (k == 1) {
+    const TileArgs<1> one = {args.shared, {args.item[0]}};
+    launch(compress_short_kernel<F, 1, EACH>, grid, block, 0, st, one);
+  } else {
+    launch(compress_short_kernel<F, kBatchMax, EACH>, grid, block, 0, st, args);
+  }
+}
+
+// Somewhere in the tags' range, another place in every process and for every copy of this library.
+uint64_t first_call() {
+  timespec now;
+  clock_gettime(CLOCK_REALTIME, &now);
+  const uint64_t x = ((uint64_t)now.tv_sec * 1000000000ull + (uint64_t)now.tv_nsec) ^ (reinterpret_cast<uintptr_t>(&g_hooks) << 20) ^ ((uint64_t)getpid() << 40);
+  return x * 0x9e3779b97f4a7c15ull;
+}
+// The tag of a call of compress_short_kernel: no two calls of a process have the same one.
+uint64_t next_call_tag() {
+  static std::atomic<uint64_t> calls{first_call()};
+  uint64_t tag;
+  do tag = calls.fetch_add(1, std::memory_order_relaxed) << kShortTagShift;
+  while (!tag);   // what cleared memory holds
+  return tag;
+}
+// Whether what is enqueued now runs once: a captured launch is replayed with the tag that it was captured with.
+bool runs_once(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s == hipStreamCaptureStatusNone;
+  (void)hipGetLastError();   // the legacy stream while another one is captured: the launch will say so itself
+  return false;
+}
+
 // How the next tensors of a compress call are launched: a function of their lengths, the word type and the status area.
 struct CompressPlan {
   uint32_t k;               // tensors of this launch; 0 if not even one fits
   uint32_t cpt;             // chunks per wave and tile
   uint64_t tiles_max;       // of the longest tensor: the dense pass has k rows of so many workgroups
   bool small;               // one launch of compress_small_kernel
+  uint32_t short_each;      // one launch of compress_short_kernel, whose threads look at so many words; 0: not that
   bool by_xcd;              // the dense pass takes its tiles in xcd_order, BF16 with fewer workgroups per CU
   bool is_long;             // the dense pass stores through the L2 (kTileLong)
   uint32_t finish_groups;   // groups of kGroup tiles per workgroup of the finishing pass
   uint32_t finish_wgs;      // workgroups of the finishing pass per tensor
   bool group_sums;          // the finishing pass is given sums of kSumGroup tile counts
-  uint32_t launches() const { return small ? 1u : group_sums ? 3u : tiles_max ? 2u : 1u; }
+  uint32_t launches() const { return small || short_each ? 1u : group_sums ? 3u : tiles_max ? 2u : 1u; }
 };
 
-// items[0, n_items): what is left of the call; n_max: its longest tensor
-CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_t n_max, int dtype, uint64_t status_bytes) {
+constexpr uint32_t kShortLooks = 64;      // about 50 us
+constexpr uint32_t kSmallestShort = 16;   // shorter tensors are one workgroup's work
+uint64_t short_status_need(uint64_t tiles) { return kShortCopies * short_copy_bytes(tiles); }
+// Words that a thread of compress_short_kernel looks at if it takes these tensors (tiles_max: of the longest), else 0.
+// us per call, one behind the other, of two launches (of one workgroup per tensor up to 40 chunks) and this way: BF16 16 chunks 4.1
+// and 4.1, 24 4.6 and 4.0, 40 5.7 and 4.0, 100 7.3 and 4.1, 512 7.1 and 4.3, 1024 7.1 and 4.85, 1300 7.1 and 5.1, 2048 7.05 and 5.6, 4096 7.8
+// and 8.6; E5M2 100 7.0 and 4.0, 2048 7.1 and 5.6, 4096 7.3 and 7.5; 64 BF16 tensors of 16 chunks 4.85 and 5.0, of 40 7.2 and 6.0, of 50 8.0
+// and 5.8, of 100 9.8 and 9.7; 16 of 256 8.05 and 6.8; four of 1000 8.0 and 6.5, two of 2000 8.0 and 7.4; 8 of 1000 10.6 and 12.3, 64 of 1000
+// 42 and 101.  Every workgroup looks at all words of its tensor, so the cost grows with the square of them, and one that
+// waits keeps others from the chip.  What bounds calls of up to 500 chunks now is the host: a launch takes it 2.3 us.
+uint32_t short_each(const splitzip_item* items, uint32_t k, uint64_t status_bytes, uint64_t* tiles_max) {
+  uint64_t chunks_max = 0, chunks_all = 0, need = 0;
+  for (uint32_t q = 0; q < k; ++q) {
+    const uint64_t c = chunks_of(items[q].n_elems);
+    if (c > chunks_max) chunks_max = c;
+    chunks_all += c;
+    need += short_status_need(tiles_of(c, 1));
+  }
+  *tiles_max = tiles_of(chunks_max, 1);
+  const uint32_t each = *tiles_max <= kTileThreads ? 1u : 2u;
+  return chunks_max > kSmallestShort && chunks_all <= (each == 1 ? 4096u : 2048u) && need <= status_bytes ? each : 0u;
+}
+
+// items[0, n_items): what is left of the call; n_max: its longest tensor; once: what is enqueued runs once
+template <typename Once>
+CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_t n_max, int dtype, uint64_t status_bytes, const Once& once) {
   CompressPlan p;
   memset(&p, 0, sizeof p);
   // as many of the next tensors (kBatchMax at most) as find room for their counts in the status area; all of them share
@@ -759,6 +824,15 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
     if (tiles > p.tiles_max) p.tiles_max = tiles;
   }
   p.small = chunks_of(n_max) <= (dtype == SPLITZIP_BF16 ? Bf16::kSmallChunks : E5m2::kSmallChunks) && !g_hooks.any();
+  uint64_t short_max = 0;
+  p.short_each = g_hooks.any() || g_hooks.short_looks.load() == kNoShort ? 0u : short_each(items, p.k, status_bytes, &short_max);
+  if (p.short_each && !once()) p.short_each = 0;
+  if (p.short_each) {
+    p.small = false;
+    p.cpt = 1;
+    p.tiles_max = short_max;
+    return p;
+  }
   // Launches of many tiles, from 16 384 on, take them in xcd_order, and BF16 with fewer workgroups per CU
   // (Bf16::kTileLdsPad).  us per call, in the order of the tiles and in xcd_order: BF16 (16 KB tiles) 1241 and 1201
   // (262 144 tiles), 161.8 and 157.7 (32 768), 83.0 and 80.8 (16 384), 43.8 and 43.6 (8192); E5M2, tiles of 8 KB 176.2
@@ -819,7 +893,7 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
 
   uint32_t i = 0;
   while (i < n_items) {
-    const CompressPlan p = plan_compress(items + i, n_items - i, n_max, dtype, ws.status_bytes);
+    const CompressPlan p = plan_compress(items + i, n_items - i, n_max, dtype, ws.status_bytes, [st] { return runs_once(st); });
     const uint32_t k = p.k;
     if (k == 0) return SPLITZIP_ERR_CAPACITY;   // cannot happen: every tensor fits alone
     TileArgs<kBatchMax> args;   // the first k items are filled in, and no other is looked at
@@ -835,7 +909,8 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       to.n = (uint32_t)it.n_elems;
       to.capacity = it.out_capacity;
       to.status_off = (uint32_t)off;
-      off += status_need(tiles_of(chunks_of(it.n_elems), p.cpt));
+      const uint64_t tiles = tiles_of(chunks_of(it.n_elems), p.cpt);
+      off += p.short_each ? short_status_need(tiles) : status_need(tiles);
     }
     a.sizes = d_sizes + i;
     a.d_cbs = d_cbs ? d_cbs + i : nullptr;
@@ -854,7 +929,13 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     a.by_xcd = p.by_xcd ? 1u : 0u;
     const unsigned tiles_max = (unsigned)p.tiles_max, sums_max = (tiles_max + kSumGroup - 1) / kSumGroup;
     const unsigned pad = p.by_xcd && dtype == SPLITZIP_BF16 ? Bf16::kTileLdsPad : 0u;
-    if (p.small) {
+    if (p.short_each) {
+      a.stage_cap = next_call_tag();
+      const uint32_t looks = g_hooks.short_looks.load();
+      a.slot_cap = looks ? looks : kShortLooks;
+      if (dtype == SPLITZIP_BF16) (p.short_each == 1 ? launch_short<Bf16, 1> : launch_short<Bf16, 2>)(tiles_max, k, st, args);
+      else (p.short_each == 1 ? launch_short<E5m2, 1> : launch_short<E5m2, 2>)(tiles_max, k, st, args);
+    } else if (p.small) {
       if (dtype == SPLITZIP_BF16) launch_small<Bf16>(k, st, args);
       else launch_small<E5m2>(k, st, args);
     } else if (k == 1) {
@@ -1194,7 +1275,7 @@ void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_item
   uint64_t n_max = 0;
   for (uint32_t q = 0; q < n_items; ++q)
     if (items[q].n_elems > n_max) n_max = items[q].n_elems;
-  const CompressPlan p = plan_compress(items, n_items, n_max, dtype, kStatusBytes);
+  const CompressPlan p = plan_compress(items, n_items, n_max, dtype, kStatusBytes, [] { return false; });   // the plan under capture
   const uint32_t v[8] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small};
   memcpy(out, v, sizeof v);
 }

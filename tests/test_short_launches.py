@@ -1,0 +1,155 @@
+"""Compress calls of one launch whose workgroups tell one another their counts: the oracle's streams at the edges of its
+range and of its tiles of four chunks, in workspaces that hold anything, where workgroups leave their tiles to others, and
+byte for byte what the two launches leave where the stream does not fit."""
+import numpy as np
+import pytest
+import torch
+
+import kv_synth
+import oracle
+import paper_2605_01708_amd as sz
+
+pytestmark = pytest.mark.gpu
+FORMATS = [(sz.BF16, oracle.BF16), (sz.FP8_E5M2, oracle.E5M2)]
+
+
+@pytest.fixture
+def looks():
+    yield sz.internal_test_short
+    sz.internal_test_short()
+
+
+def words(dtype, n, seed, escapes="few"):
+    gen = kv_synth.kv_bf16 if dtype == sz.BF16 else kv_synth.kv_e5m2
+    x = gen(n // 1024 + 1, seed)[:n].contiguous()
+    if escapes == "few":
+        return x
+    rng = np.random.default_rng(seed)   # random patterns: nearly all escape; "many": in every third chunk
+    r = torch.from_numpy(rng.integers(0, 1 << (16 if dtype == sz.BF16 else 8), n).astype(np.uint16 if dtype == sz.BF16 else np.uint8).view(np.int16 if dtype == sz.BF16 else np.uint8))
+    return r if escapes == "all" else torch.where((torch.arange(n) // 1024) % 3 == 0, r, x)
+
+
+def books(dtype, odt):
+    sample = words(dtype, 64 * 1024, 1)
+    return sz.calibrate(sample, dtype), oracle.calibrate(kv_synth.to_numpy_words(sample), odt)
+
+
+def compress(x, cb, cap=None, ws=None):
+    cap = sz.compress_bound(x.numel(), cb.dtype) if cap is None else cap
+    out = torch.full((cap + 512,), 0xA5, dtype=torch.uint8, device="cuda")
+    ws, rec = sz.Workspace(x.numel(), cb.dtype) if ws is None else ws, sz.new_sizes()
+    sz.compress(x.cuda(), cb, out, ws, rec, capacity=cap)
+    return out, sz.read_sizes(rec)
+
+
+def check(x, cb, ocb, ws=None):
+    blob, m = oracle.compress(kv_synth.to_numpy_words(x), ocb)
+    out, got = compress(x, cb, ws=ws)
+    assert got == (blob.size, m, 0)
+    assert np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("dtype,odt", FORMATS)
+@pytest.mark.parametrize("chunks", [16, 17, 49, 52, 255, 257, 1023, 1024, 1025, 2047, 2048, 2049])
+def test_streams_at_the_edges(dtype, odt, chunks, looks):
+    """Lengths around a whole tile, around what a thread looks at in one go and around the range's end; every way for a
+    wave's records to leave (staged, or again from the words); each also with every workgroup but the last ones leaving."""
+    cb, ocb = books(dtype, odt)
+    for n in (chunks * 1024, chunks * 1024 - 3):
+        for escapes in ("few", "many", "all") if chunks < 1000 else ("few", "many"):
+            x = words(dtype, n, 3, escapes)
+            for limit in (0, 1) if chunks <= 1025 else (0,):
+                print(f"case {dtype} n={n} {escapes} looks={limit}", flush=True)
+                looks(limit)
+                check(x, cb, ocb)
+
+
+@pytest.mark.parametrize("dtype,odt", FORMATS)
+def test_what_the_workspace_holds(dtype, odt, looks):
+    """One workspace for calls of different lengths, and words of it overwritten in between: no value in it means anything."""
+    cb, ocb = books(dtype, odt)
+    ws = sz.Workspace(1 << 20, dtype)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    for k, n in enumerate((900 * 1024, 100 * 1024, 1024 * 1024, 60 * 1024 - 1, 1000 * 1024, 500 * 1024)):
+        if k == 2:
+            ws.buf.fill_(0xFF)
+        elif k == 3:
+            ws.buf.zero_()
+        elif k > 3:
+            ws.buf.random_(0, 256, generator=gen)
+        looks(k % 2)
+        check(words(dtype, n, k), cb, ocb, ws)
+
+
+@pytest.mark.parametrize("dtype,odt", FORMATS)
+@pytest.mark.parametrize("limit", [0, 1, 2])
+def test_batches(dtype, odt, limit, looks):
+    """Tensors of a launch have their own counts: unequal lengths, none at all, a batch of 64."""
+    cb, ocb = books(dtype, odt)
+    for sizes in ([0, 50 * 1024 + 1, 3, 0, 300 * 1024, 4096, 1024 * 257 - 5], [63 * 1024 + 7 * k for k in range(64)], [0, 60 * 1024], [1024 * 1024 - 1] * 4, [1025 * 1024, 1000 * 1024 - 1]):
+        xs = [words(dtype, n, 7 + k, "many" if k % 5 == 4 else "few") for k, n in enumerate(sizes)]
+        blobs = [oracle.compress(kv_synth.to_numpy_words(x), ocb) for x in xs]
+        outs = [torch.full((sz.compress_bound(n, dtype) + 256,), 0xA5, dtype=torch.uint8, device="cuda") for n in sizes]
+        ws, rec = sz.Workspace(max(sizes), dtype), sz.new_sizes_array(len(xs))
+        looks(limit)
+        print(f"case {dtype} batch of {len(sizes)} looks={limit}", flush=True)
+        sz.compress_batch([x.cuda() for x in xs], [cb] * len(xs), outs, ws, rec)
+        for (blob, m), out, got in zip(blobs, outs, sz.read_sizes_array(rec)):
+            assert got == (blob.size, m, 0) and np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
+@pytest.mark.parametrize("limit", [0, 1])
+def test_what_does_not_fit(dtype, limit, looks):
+    cb = sz.codebook_from_dec(list(range(16)), dtype)          # hardly anything is in this codebook
+    for n in (70 * 1024 - 9, 200 * 1024):
+        x = words(dtype, n, 5)
+        fixed, total = sz.fixed_bytes(n, dtype), compress(x, cb)[1][0]
+        for cap in (fixed, fixed + (total - fixed) // 3, total - 1, total):
+            looks(limit)
+            out, got = compress(x, cb, cap)
+            looks(sz.INTERNAL_NO_SHORT)
+            ref, want = compress(x, cb, cap)
+            assert got == want and torch.equal(out, ref)
+
+
+def test_beside_other_work_on_the_device():
+    """Another stream keeps the device busy: workgroups of a launch get onto it one after the other."""
+    cb, ocb = books(sz.BF16, oracle.BF16)
+    x = words(sz.BF16, 2048 * 1024 - 1, 3)
+    blob, m = oracle.compress(kv_synth.to_numpy_words(x), ocb)
+    xd, ws = x.cuda(), sz.Workspace(x.numel(), sz.BF16)
+    recs, outs = [sz.new_sizes() for _ in range(20)], [torch.zeros(blob.size, dtype=torch.uint8, device="cuda") for _ in range(20)]
+    busy, side = torch.ones(1 << 28, device="cuda"), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(20):
+            busy.mul_(1.0001)
+    for out, rec in zip(outs, recs):
+        sz.compress(xd, cb, out, ws, rec)
+    torch.cuda.synchronize()
+    want = torch.from_numpy(blob).cuda()
+    for out, rec in zip(outs, recs):
+        assert sz.read_sizes(rec) == (blob.size, m, 0) and torch.equal(out, want)
+
+
+def test_captured_calls_are_replayed():
+    """A captured call takes the two launches: its replays see new words and other calls on the workspace in between."""
+    cb, ocb = books(sz.BF16, oracle.BF16)
+    n = 100 * 1024 - 37
+    x, ws, rec = words(sz.BF16, n, 1).cuda(), sz.Workspace(4096 * 1024, sz.BF16), sz.new_sizes()
+    out = torch.zeros(sz.compress_bound(n, sz.BF16), dtype=torch.uint8, device="cuda")
+    sz.compress(x, cb, out, ws, rec)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sz.compress(x, cb, out, ws, rec)
+    for k in range(4):
+        y = words(sz.BF16, n, 20 + k)
+        x.copy_(y)
+        graph.replay()
+        torch.cuda.synchronize()
+        blob, m = oracle.compress(kv_synth.to_numpy_words(y), ocb)
+        assert sz.read_sizes(rec) == (blob.size, m, 0) and np.array_equal(out[:blob.size].cpu().numpy(), blob)
+        check(words(sz.BF16, (50 + 900 * (k % 2)) * 1024, k), cb, ocb, ws)
