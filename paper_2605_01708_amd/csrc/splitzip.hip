@@ -915,8 +915,12 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     a.sizes = d_sizes + i;
     a.d_cbs = d_cbs ? d_cbs + i : nullptr;
     a.status = ws.base + kWsHeaderBytes;
-    a.stage = ws.base + kWsHeaderBytes + ws.status_bytes;
-    a.stage_cap = (ws.stage_bytes / k) & ~(uint64_t)255u;
+    // The tiles' slots begin behind the words of this launch: what it leaves of the status area is as good for records.  (From the
+    // staging area alone a launch of 64 tensors gave a tile of four chunks 16 records, and outliers leave 27 there, so that nearly
+    // all tiles were encoded twice.  us per call, BF16 with 0.66 % escapes, then and now: 64 tensors of 100 chunks 31.1 and 11.0, 64 of 1000 95.2
+    // and 45.2, 48 of 2000 115 and 62, 64 of 4000 269 and 189.)
+    a.stage = a.status + off;
+    a.stage_cap = ((g_hooks.stage_bytes ? ws.stage_bytes : ws.status_bytes - off + ws.stage_bytes) / k) & ~(uint64_t)255u;
     a.cpt = p.cpt;
     a.tile_shift = 2u + (uint32_t)__builtin_ctz(p.cpt);
     {
