@@ -256,8 +256,9 @@ int splitzip_decompress_batch(const splitzip_ditem* items, uint32_t n_items, int
  * round trip): splitzip_calibrate_batch_device counts the exponents of every
  * items[k].d_in (n_elems words; d_out, out_capacity and cb are not looked at)
  * into d_hists + 256 k and ranks them into d_cbs[k], exactly as
- * splitzip_histogram and splitzip_codebook_device do for one tensor, in three
- * launches per 64 tensors.  d_hists: n_items x 256 device words, 8-byte
+ * splitzip_histogram and splitzip_codebook_device do for one tensor, in one
+ * launch (160 tensors of a call where they are short), or in two and one
+ * per 64 tensors: above 64 tensors, or for a few long ones.  d_hists: n_items x 256 device words, 8-byte
  * aligned, zeroed by the call; d_cbs: n_items splitzip_codebook in device
  * memory, 4-byte aligned.  The _batch_dcb calls are the batch calls with
  * tensor k under d_cbs[k]; the items' own cb fields are not looked at.  As

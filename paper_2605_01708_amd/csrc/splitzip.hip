@@ -1188,6 +1188,35 @@ int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dty
   return SPLITZIP_OK;
 }
 
+// workgroups that leave every thread four vectors of a sample of n words; one at least
+uint64_t most_wgs(uint64_t n, int dtype) {
+  const uint64_t w = (n * (dtype == SPLITZIP_BF16 ? 2 : 1) + 16 * 4096 - 1) / (16 * 4096);
+  return w ? w : 1;
+}
+// the arguments of a calibration launch over k samples; its workgroups
+template <uint32_t N>
+uint32_t deal_samples(const splitzip_item* items, uint32_t k, int dtype, uint64_t cus, uint64_t tag, HistBatchArgs<N>* a) {
+  uint64_t all = 0;
+  for (uint32_t q = 0; q < k; ++q) all += items[q].n_elems;
+  uint32_t wgs = 0;
+  a->tag = tag;
+  for (uint32_t q = 0; q < k; ++q) {
+    const uint64_t n = items[q].n_elems, share = all ? cus * n / all : 0, most = most_wgs(n, dtype);   // its share of one workgroup per CU
+    a->first[q] = wgs;
+    a->in[q] = static_cast<const uint8_t*>(items[q].d_in);
+    a->n[q] = n;
+    a->start[q] = histogram_start(a->in[0], a->in[q], q, n * (dtype == SPLITZIP_BF16 ? 2 : 1) / 16);
+    wgs += (uint32_t)(share > most ? most : share ? share : 1);
+  }
+  for (uint32_t q = k; q <= N; ++q) a->first[q] = wgs;   // (what else there is of samples that are not there is not looked at)
+  return wgs;
+}
+template <uint32_t N>
+void launch_calibrate(const HistBatchArgs<N>& a, uint32_t wgs, int dtype, uint64_t* hists, splitzip_codebook* d_cbs, hipStream_t st) {
+  if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL((calibrate_batch_kernel<true, N>), dim3(wgs), dim3(1024), 0, st, a, hists, d_cbs);
+  else hipLaunchKernelGGL((calibrate_batch_kernel<false, N>), dim3(wgs), dim3(1024), 0, st, a, hists, d_cbs);
+}
+
 }  // namespace
 
 extern "C" {
@@ -1213,32 +1242,42 @@ int splitzip_calibrate_batch_device(const splitzip_item* items, uint32_t n_items
   }
   if (n_items == 0) return SPLITZIP_OK;
   const hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, d_hists, 256ull * n_items);
   const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
-  for (uint32_t i = 0; i < n_items; i += kHistMost) {
-    HistBatchArgs a;
-    memset(&a, 0, sizeof a);
-    const uint32_t k = n_items - i < kHistMost ? n_items - i : kHistMost;
-    uint64_t all = 0;
-    for (uint32_t q = 0; q < k; ++q) all += items[i + q].n_elems;
-    uint32_t wgs = 0;
-    for (uint32_t q = 0; q < kHistMost; ++q) {
-      a.first[q] = wgs;
-      if (q >= k) continue;
-      a.in[q] = static_cast<const uint8_t*>(items[i + q].d_in);
-      a.n[q] = items[i + q].n_elems;
-      // its share of one workgroup per CU, but at least four vectors per thread of it, and one workgroup at least
-      const uint64_t nvec = (a.n[q] * (dtype == SPLITZIP_BF16 ? 2 : 1) + 15) / 16;
-      a.start[q] = histogram_start(a.in[0], a.in[q], q, a.n[q] * (dtype == SPLITZIP_BF16 ? 2 : 1) / 16);
-      uint64_t w = all ? cus * a.n[q] / all : 0;
-      if (w > (nvec + 4 * 1024 - 1) / (4 * 1024)) w = (nvec + 4 * 1024 - 1) / (4 * 1024);
-      wgs += w ? (uint32_t)w : 1u;
-    }
-    a.first[kHistMost] = wgs;
-    if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL(histogram_batch_kernel<true>, dim3(wgs), dim3(1024), 0, st, a, d_hists + 256ull * i);
-    else hipLaunchKernelGGL(histogram_batch_kernel<false>, dim3(wgs), dim3(1024), 0, st, a, d_hists + 256ull * i);
+  // Short samples go up to kHistMostShort to a launch, and others kHistMost: their workgroups are dealt out whole, and 256 CUs divide the better
+  // among the fewer.
+  uint64_t wgs_short = 0;
+  for (uint32_t i = 0; i < n_items; ++i) wgs_short += most_wgs(items[i].n_elems, dtype);
+  const bool are_short = wgs_short <= cus;
+  const uint32_t step = are_short && n_items > kHistMost ? kHistMostShort : kHistMost;
+  // One launch does it all where a sample has fewer than 64 workgroups; more of them, all at the one word, take longer than
+  // two more launches: us per call with one and three, BF16, 12.98 and 11.40 (4096 chunks: 128 workgroups), 24.0 and 20.3 (32 768: 256),
+  // 13.7 and 13.7 (four of 4096: 64 each), 15.25 and 15.85 (five: 51).  And not where a call takes several launches with a codebook's
+  // tail each (100 of 1000 chunks 48.0 and 45.4).
+  bool at_once = are_short || n_items <= step;
+  uint64_t all = 0;
+  for (uint32_t i = 0; at_once && !are_short && i < n_items; ++i) all += items[i].n_elems;
+  for (uint32_t i = 0; at_once && !are_short && i < n_items; ++i) {
+    const uint64_t w = all ? cus * items[i].n_elems / all : 0;
+    at_once = w < 64 || most_wgs(items[i].n_elems, dtype) < 64;
   }
-  hipLaunchKernelGGL(codebook_kernel, dim3(n_items), dim3(1024), 0, st, d_hists, exp_values(dtype), (uint32_t)dtype, d_cbs);
+  const uint64_t tag = next_call_tag() << (kCtlTagShift - kShortTagShift) | kCtlTag;
+  if (!at_once) hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, d_hists, 256ull * n_items);
+  for (uint32_t i = 0; i < n_items; i += step) {
+    const uint32_t k = n_items - i < step ? n_items - i : step;
+    uint64_t* hists = d_hists + 256ull * i;
+    if (step == kHistMost) {
+      HistBatchArgs<kHistMost> a;
+      const uint32_t wgs = deal_samples(items + i, k, dtype, cus, tag, &a);
+      if (at_once) launch_calibrate(a, wgs, dtype, hists, d_cbs + i, st);
+      else if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL(histogram_batch_kernel<true>, dim3(wgs), dim3(1024), 0, st, a, hists);
+      else hipLaunchKernelGGL(histogram_batch_kernel<false>, dim3(wgs), dim3(1024), 0, st, a, hists);
+    } else {
+      HistBatchArgs<kHistMostShort> a;
+      const uint32_t wgs = deal_samples(items + i, k, dtype, cus, tag, &a);
+      launch_calibrate(a, wgs, dtype, hists, d_cbs + i, st);
+    }
+  }
+  if (!at_once) hipLaunchKernelGGL(codebook_kernel, dim3(n_items), dim3(1024), 0, st, d_hists, exp_values(dtype), (uint32_t)dtype, d_cbs);
   return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
 }
 

@@ -1,0 +1,65 @@
+"""Calibration of a batch in one launch, whose workgroups settle among themselves who clears and who ranks: around the numbers of
+workgroups and of samples where it takes several launches instead, into buffers that hold anything, again and captured."""
+import pytest
+import torch
+
+import kv_synth
+import paper_2605_01708_amd as sz
+
+pytestmark = pytest.mark.gpu
+
+
+def check(xs, dcbs, dtype):
+    shift, values = (7, 256) if dtype == sz.BF16 else (2, 32)
+    hists = dcbs.hists.cpu()
+    for k, x in enumerate(xs):
+        want = torch.zeros(256, dtype=torch.int64)
+        want[:values] = torch.bincount(((x.to(torch.int32) >> shift) & (values - 1)).long(), minlength=values).cpu()
+        assert torch.equal(hists.view(-1, 256)[k], want), k
+        ref, got = sz.codebook_from_hist(want, dtype), dcbs.to_host(k)
+        assert (got.dec, got.enc, got.member, got.dtype) == (ref.dec, ref.enc, ref.member, ref.dtype), k
+
+
+@pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
+@pytest.mark.parametrize("per", [[63], [64], [65], [3, 0, 1], [60, 61], [1] * 65, [1] * 161, [2] * 64, [2] * 130, [5] * 70])
+def test_numbers_of_workgroups_and_samples(dtype, per):
+    """per: a sample's workgroups at most, four vectors of 16 bytes per thread each"""
+    each = 16 * 4096 // (2 if dtype == sz.BF16 else 1)
+    pool = (kv_synth.kv_bf16 if dtype == sz.BF16 else kv_synth.kv_e5m2)(max(per) * each // 1024 + 8, 3, device="cuda")
+    xs = [pool[16 * (k % 5): 16 * (k % 5) + max(0, w * each - 5 * (k % 3))].clone() for k, w in enumerate(per)]
+    dcbs = sz.DeviceCodebooks(len(xs), dtype)
+    cal = sz.CalibrateBatchDevice(xs, dcbs)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    for k in range(4):
+        if k == 1:
+            dcbs.buf.fill_(-1 if dcbs.buf.dtype.is_signed else 255)
+            dcbs.hists.fill_(-1)
+        elif k == 2:
+            dcbs.buf.view(torch.uint8).random_(0, 256, generator=gen)
+            dcbs.hists.view(torch.uint8).random_(0, 256, generator=gen)
+        cal.launch()
+        torch.cuda.synchronize()
+        check(xs, dcbs, dtype)
+
+
+@pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
+def test_captured(dtype):
+    gen = kv_synth.kv_bf16 if dtype == sz.BF16 else kv_synth.kv_e5m2
+    xs = [gen(200 + 30 * k, k, device="cuda") for k in range(3)]
+    dcbs = sz.DeviceCodebooks(3, dtype)
+    cal = sz.CalibrateBatchDevice(xs, dcbs)
+    cal.launch()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cal.launch()
+    for k in range(4):
+        for q, x in enumerate(xs):
+            x.copy_(gen(200 + 30 * q, 10 * k + q, device="cuda"))
+        graph.replay()
+        torch.cuda.synchronize()
+        check(xs, dcbs, dtype)
+        cal.launch()
+        torch.cuda.synchronize()
+        check(xs, dcbs, dtype)
