@@ -970,13 +970,143 @@ static_assert(kTileThreads / 64 * kChunk <= kShortCount && (kShortLeft | kShortT
 // bytes of one copy of a tensor's words; a tensor without elements has one, too
 __host__ __device__ inline uint64_t short_copy_bytes(uint64_t tiles) { return a256(8 * (tiles ? tiles : 1)); }
 
-// EACH: words that a thread looks at; a tensor has no more tiles than that many times the threads.  us of this kernel and of the two
+// LDS of it
+template <int EACH>
+struct ShortShared {
+  static constexpr int NW = kTileThreads / 64;
+  uint32_t all[NW], before[NW], state[NW], won;
+  uint32_t tile[EACH * kTileThreads];   // only where tiles were left
+};
+// What the workgroups of a tensor tell one another.  EACH: words that a thread looks at; a tensor has no more tiles than that many
+// times the threads.
+template <int EACH>
+struct ShortCounts {
+  static constexpr int NW = kTileThreads / 64;
+  uint64_t* words;     // the first copy of the tensor's
+  uint64_t tag;
+  uint32_t n_tiles, copy, own;   // copy: words from one copy to the next; own: the workgroup's tile
+  uint64_t v[EACH];    // thread and register <-> tile
+  uint32_t state;      // bit 0: all counts are there; bit 1: a tile was left
+  uint32_t first, M;   // escapes of the tensor before a tile; all of them
+
+  __device__ inline ShortCounts(uint64_t* at, uint64_t call, uint32_t tiles, uint32_t tile)
+      : words(at), tag(call), n_tiles(tiles), copy((uint32_t)(short_copy_bytes(tiles) / 8)), own(tile), state(0), first(0), M(0) {
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) v[q] = tag;
+  }
+  // The own word, written at the device's point of coherence before anyone of this workgroup goes on; then the others', as
+  // often as `times` at most.  rank() and overall() follow.
+  __device__ inline void tell_and_look(ShortShared<EACH>& s, uint32_t total, uint32_t mark, uint32_t times, uint32_t tid, uint32_t wave) {
+    if (tid < kShortCopies) st_agent(words + tid * copy + own, tag | mark | total);
+    if (wave == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+    bool here;
+    for (;;) {
+      here = true;
+#pragma unroll
+      for (int q = 0; q < EACH; ++q)
+        if (q * kTileThreads + tid < n_tiles) v[q] = ld_agent(words + (own % kShortCopies) * copy + q * kTileThreads + tid);
+#pragma unroll
+      for (int q = 0; q < EACH; ++q) here = here && ((v[q] ^ tag) >> kShortTagShift) == 0;
+      here = __all(here);
+      if (here || --times == 0) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    uint32_t marks = 0;
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) marks |= (uint32_t)v[q];
+    const bool left = __any(marks & kShortLeft);
+    if ((tid & 63u) == 0) s.state[wave] = (here ? 1u : 0u) | (left ? 2u : 0u);
+  }
+  // with a barrier
+  __device__ inline void rank(ShortShared<EACH>& s, uint32_t tile, uint32_t tid, uint32_t wave) {
+    uint32_t all = 0, before = 0;
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) {
+      const uint32_t x = (uint32_t)v[q] & kShortCount;
+      all += x;
+      before += q * kTileThreads + tid < tile ? x : 0u;
+    }
+    all = wave_last(wave_incl_scan(all));
+    before = wave_last(wave_incl_scan(before));
+    if ((tid & 63u) == 0) {
+      s.before[wave] = before;
+      s.all[wave] = all;
+    }
+    lds_barrier();
+    first = M = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      first += s.before[q];
+      M += s.all[q];
+    }
+  }
+  __device__ inline void overall(const ShortShared<EACH>& s) {
+    state = 1u;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      const uint32_t x = s.state[q];
+      state = (state & (x | 2u)) | (x & 2u);
+    }
+  }
+  // whether a tile that was marked as left is this workgroup's now
+  __device__ inline bool take(ShortShared<EACH>& s, uint32_t tile, uint32_t told, uint32_t tid) {
+    __syncthreads();
+    if (tid == 0) {
+      uint64_t seen = tag | kShortLeft | told;
+      s.won = __hip_atomic_compare_exchange_strong(words + tile, &seen, seen | kShortTaken, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
+    }
+    __syncthreads();
+    return s.won != 0;
+  }
+  // A workgroup's way through a launch: encode(tile, first) makes a tile and leaves its count in total, place(tile) puts its
+  // records where first and M say.
+  template <typename Encode, typename Place>
+  __device__ inline void run(ShortShared<EACH>& s, uint32_t looks, const uint32_t& total, uint32_t tid, uint32_t wave, const Encode& encode, const Place& place) {
+    encode(own, true);
+    if (n_tiles > 1) {
+      tell_and_look(s, total, 0u, looks, tid, wave);
+    } else {   // nobody to tell
+      if (tid == 0) v[0] |= total;
+      if ((tid & 63u) == 0) s.state[wave] = 1u;
+    }
+    rank(s, own, tid, wave);
+    overall(s);
+    if (state == 1u) {
+      place(own);
+      return;
+    }
+    bool keep = (state & 1u) != 0;
+    if (!keep) {
+      __syncthreads();
+      tell_and_look(s, total, kShortLeft, 1u, tid, wave);
+      rank(s, own, tid, wave);
+      overall(s);
+      if (!(state & 1u)) return;
+      keep = take(s, own, total, tid);
+    }
+    if (keep) place(own);
+    // tiles that their workgroups have left (the loop is not one with what is above: that cost 0.3 us, in registers)
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) s.tile[q * kTileThreads + tid] = (uint32_t)v[q] & (kShortLeft | kShortTaken | kShortCount);
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t tile = 0; tile < n_tiles; ++tile) {
+      const uint32_t told = s.tile[tile];
+      if (tile == own || !(told & kShortLeft) || (told & kShortTaken) || !take(s, tile, told & kShortCount, tid)) continue;
+      encode(tile, false);
+      rank(s, tile, tid, wave);
+      place(tile);
+    }
+  }
+};
+
+// us of this kernel and of the two
 // launches, without the gap between those (rocprofv3's trace, BF16): 4.4 and 3.4 + 2.4 (100 chunks), 5.2 and 3.9 + 3.0 (1024).
 // Workgroups of eight waves are 0.25 us faster at 2048 chunks but get onto a busy chip late, and everyone waits for them (beside
 // elementwise kernels that fill it 22 to 27 us a call, 16.9 with four, two launches 20.2; at 4096 chunks 216 and 21); two
 // chunks per wave take 0.3 us more.  It gains most where chunks escape whole: the finishing pass encodes tiles whose
 // records outgrow their slots once more, a workgroup 16 of them (2048 chunks of random words 62 us a call, 10.8 this way).
-// The loop over tiles that were left stands behind the straight way: one loop around both cost 0.3 us, in registers.
 template <typename F, uint32_t N, int EACH>
 __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const TileArgs<N> args) {
   constexpr int NW = kTileThreads / 64;
@@ -984,8 +1114,8 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
   __shared__ uint16_t stage_pos[NW][kChunk];   // room for all of a wave's records
   __shared__ uint8_t stage_val[NW][kChunk];
   __shared__ u32x4 s_park[kTileThreads];
-  __shared__ uint32_t s_cnt[NW], s_all[NW], s_before[NW], s_state[NW], s_won;
-  __shared__ uint32_t s_tile[EACH * kTileThreads];   // only where tiles were left
+  __shared__ uint32_t s_cnt[NW];
+  __shared__ ShortShared<EACH> s_short;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t item = blockIdx.y, own = blockIdx.x;
@@ -995,9 +1125,7 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
   const Planes P = make_planes(item_words(a.paging, it.in), it.out, it.n, it.capacity, F::DT);
   const uint32_t n_tiles = (P.n_chunks + NW - 1) / NW;
   if (own >= (n_tiles ? n_tiles : 1u)) return;   // a tensor without elements still gets its header
-  uint64_t* words = reinterpret_cast<uint64_t*>(a.status + it.status_off);   // the first copy of them
-  const uint32_t copy = (uint32_t)(short_copy_bytes(n_tiles) / 8);            // words from one copy to the next
-  const uint64_t tag = a.stage_cap;
+  ShortCounts<EACH> counts(reinterpret_cast<uint64_t*>(a.status + it.status_off), a.stage_cap, n_tiles, own);
   uint32_t* park = reinterpret_cast<uint32_t*>(&s_park[tid]);
   const LdsSink lds{stage_pos[wave], stage_val[wave], 0u, kChunk};
 
@@ -1042,119 +1170,20 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
     }
   };
 
-  uint64_t v[EACH];        // thread and register <-> tile
-#pragma unroll
-  for (int q = 0; q < EACH; ++q) v[q] = tag;
-  uint32_t state = 0;      // bit 0: all counts are there; bit 1: a tile was left
-  // The own word, written at the device's point of coherence before anyone of this workgroup goes on; then the others', as
-  // often as `times` at most.
-  auto tell_and_look = [&](uint32_t mark, uint32_t times) {
-    if ((uint32_t)tid < kShortCopies) st_agent(words + tid * copy + own, tag | mark | total);
-    if (wave == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    lds_barrier();
-    bool here;
-    for (;;) {
-      here = true;
-#pragma unroll
-      for (int q = 0; q < EACH; ++q)
-        if (q * kTileThreads + tid < n_tiles) v[q] = ld_agent(words + (own % kShortCopies) * copy + q * kTileThreads + tid);
-#pragma unroll
-      for (int q = 0; q < EACH; ++q) here = here && ((v[q] ^ tag) >> kShortTagShift) == 0;
-      here = __all(here);
-      if (here || --times == 0) break;
-      __builtin_amdgcn_s_sleep(1);
-    }
-    uint32_t marks = 0;
-#pragma unroll
-    for (int q = 0; q < EACH; ++q) marks |= (uint32_t)v[q];
-    const bool left = __any(marks & kShortLeft);
-    if (lane == 0) s_state[wave] = (here ? 1u : 0u) | (left ? 2u : 0u);
-  };
-  auto overall = [&]() {
-    state = 1u;
-#pragma unroll
-    for (int q = 0; q < NW; ++q) {
-      const uint32_t x = s_state[q];
-      state = (state & (x | 2u)) | (x & 2u);
-    }
-  };
-  uint32_t first = 0, M = 0;   // escapes of the tensor before a tile; all of them
-  auto rank = [&](uint32_t tile) {   // with a barrier
-    uint32_t all = 0, before = 0;
-#pragma unroll
-    for (int q = 0; q < EACH; ++q) {
-      const uint32_t x = (uint32_t)v[q] & kShortCount;
-      all += x;
-      before += q * kTileThreads + tid < tile ? x : 0u;
-    }
-    all = wave_last(wave_incl_scan(all));
-    before = wave_last(wave_incl_scan(before));
-    if (lane == 0) {
-      s_before[wave] = before;
-      s_all[wave] = all;
-    }
-    lds_barrier();
-    first = M = 0;
-#pragma unroll
-    for (int q = 0; q < NW; ++q) {
-      first += s_before[q];
-      M += s_all[q];
-    }
-  };
   // the tile's records and table entries where they belong; the stream's header and pads with the first tile
   auto place = [&](uint32_t tile) {
-    const uint64_t off_val = P.off_pos + a256(2ull * M);
+    const uint64_t off_val = P.off_pos + a256(2ull * counts.M);
     FinalSink fin;
     fin.pos = reinterpret_cast<uint16_t*>(P.out + P.off_pos);
     fin.pos_room = room32(P.capacity, P.off_pos, 1);
     fin.val = P.out + off_val;
     fin.val_room = room32(P.capacity, off_val, 0);
-    const uint32_t base = first + in_tile;
+    const uint32_t base = counts.first + in_tile;
     if (c < P.n_chunks && lane == 0) reinterpret_cast<uint32_t*>(P.out + P.off_tab)[c] = base;
     for (uint32_t i = lane; i < count; i += 64) fin.put(base + i, stage_pos[wave][i], stage_val[wave][i]);
-    if (tile == 0 && wave == NW - 1) compress_write_trailer(P, a.dec16_of(it, item), a.sizes + item, M, 0u, lane);
+    if (tile == 0 && wave == NW - 1) compress_write_trailer(P, a.dec16_of(it, item), a.sizes + item, counts.M, 0u, lane);
   };
-  // whether a tile that was marked as left is this workgroup's now
-  auto take = [&](uint32_t tile, uint32_t told) -> bool {
-    __syncthreads();
-    if (tid == 0) {
-      uint64_t seen = tag | kShortLeft | told;
-      s_won = __hip_atomic_compare_exchange_strong(words + tile, &seen, seen | kShortTaken, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
-    }
-    __syncthreads();
-    return s_won != 0;
-  };
-
-  encode(own, true);
-  tell_and_look(0u, a.slot_cap);
-  rank(own);
-  overall();
-  if (state == 1u) {
-    place(own);
-    return;
-  }
-  bool keep = (state & 1u) != 0;
-  if (!keep) {
-    __syncthreads();
-    tell_and_look(kShortLeft, 1u);
-    rank(own);
-    overall();
-    if (!(state & 1u)) return;
-    keep = take(own, total);
-  }
-  if (keep) place(own);
-  // tiles that their workgroups have left
-#pragma unroll
-  for (int q = 0; q < EACH; ++q) s_tile[q * kTileThreads + tid] = (uint32_t)v[q] & (kShortLeft | kShortTaken | kShortCount);
-  __syncthreads();
-#pragma unroll 1
-  for (uint32_t tile = 0; tile < n_tiles; ++tile) {
-    const uint32_t told = s_tile[tile];
-    if (tile == own || !(told & kShortLeft) || (told & kShortTaken) || !take(tile, told & kShortCount)) continue;
-    encode(tile, false);
-    rank(tile);
-    place(tile);
-  }
+  counts.run(s_short, a.slot_cap, total, (uint32_t)tid, (uint32_t)wave, encode, place);
 }
 
 #endif  // SPLITZIP_COMPRESS_HPP

@@ -151,6 +151,35 @@ struct CallCodebooks {
   }
 };
 
+// Somewhere in the tags' range, another place in every process and for every copy of this library.
+uint64_t first_call() {
+  timespec now;
+  clock_gettime(CLOCK_REALTIME, &now);
+  const uint64_t x = ((uint64_t)now.tv_sec * 1000000000ull + (uint64_t)now.tv_nsec) ^ (reinterpret_cast<uintptr_t>(&g_hooks) << 20) ^ ((uint64_t)getpid() << 40);
+  return x * 0x9e3779b97f4a7c15ull;
+}
+// The tag of a call of compress_short_kernel: no two calls of a process have the same one.
+uint64_t next_call_tag() {
+  static std::atomic<uint64_t> calls{first_call()};
+  uint64_t tag;
+  do tag = calls.fetch_add(1, std::memory_order_relaxed) << kShortTagShift;
+  while (!tag);   // what cleared memory holds
+  return tag;
+}
+// Whether what is enqueued now runs once: a captured launch is replayed with the tag that it was captured with.
+bool runs_once(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s == hipStreamCaptureStatusNone;
+  (void)hipGetLastError();   // the legacy stream while another one is captured: the launch will say so itself
+  return false;
+}
+
+constexpr uint32_t kShortLooks = 64;   // about 50 us
+uint32_t short_looks() {
+  const uint32_t forced = g_hooks.short_looks.load();
+  return forced ? forced : kShortLooks;
+}
+
 // ---------------------------------------------------------------------------
 // format variants: host side
 // ---------------------------------------------------------------------------
@@ -215,9 +244,10 @@ void variant_tables(const splitzip_variant* v, const splitzip_codebook* cb, VArg
     a->hdr[10 + i] = a->dec[4 * i] | (a->dec[4 * i + 1] << 8) | (a->dec[4 * i + 2] << 16) | ((uint32_t)a->dec[4 * i + 3] << 24);
 }
 
-#define SPLITZIP_V_DISPATCH2(KERNEL, grid, block, st, args)                                                        \
+#define SPLITZIP_V_DISPATCH2(KERNEL, grid, block, st, args) SPLITZIP_V_DISPATCH3(KERNEL, args, grid, block, st, args)
+#define SPLITZIP_V_DISPATCH3(KERNEL, v, grid, block, st, args)                                                     \
   do {                                                                                                             \
-    const int key_ = (int)(args).dtype * 2 + ((args).code_bits == 4 ? 1 : 0);                                      \
+    const int key_ = (int)(v).dtype * 2 + ((v).code_bits == 4 ? 1 : 0);                                            \
     switch (key_) {                                                                                                \
       case 0: hipLaunchKernelGGL((KERNEL<SPLITZIP_BF16, 3>), grid, block, 0, st, args); break;                     \
       case 1: hipLaunchKernelGGL((KERNEL<SPLITZIP_BF16, 4>), grid, block, 0, st, args); break;                     \
@@ -235,6 +265,20 @@ void variant_tables(const splitzip_variant* v, const splitzip_codebook* cb, VArg
       default: hipLaunchKernelGGL((KERNEL<SPLITZIP_FP8_E4M3>), grid, block, 0, st, args); break;                   \
     }                                                                                                              \
   } while (0)
+
+// Whether v_short_kernel takes a tensor of so many tiles of four blocks.  Its words lie in the blocks' slots, 2 KB
+// per tile of four blocks; a tensor of one tile has no words.
+bool variant_short(uint64_t tiles) {
+  return tiles >= 1 && tiles <= kVShortEach * kTileThreads && g_hooks.short_looks.load() != kNoShort;
+}
+
+void launch_v_pack(uint64_t n_elems, hipStream_t st, const VArgs& a) {
+  // M is known to the device only: a grid that strides over however many bytes the section has
+  uint64_t g = (v_val_bytes(n_elems, a.val_bits) + kThreads - 1) / kThreads;
+  const uint64_t cap = (uint64_t)cu_count() * 8;
+  if (g > cap) g = cap;
+  hipLaunchKernelGGL(v_pack_kernel, dim3((unsigned)g), dim3(kThreads), 0, st, a);
+}
 
 template <int DT>
 void launch_v_finish(dim3 g, hipStream_t st, const VArgs& a) {
@@ -389,6 +433,16 @@ int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip
   a.n_sums = direct ? grid : a.n_tiles;
   a.sum_shift = direct ? 2u + (10u - a.chunk_shift) : 10u;
   a.ahead = v->k <= 8 ? 64u : 16u;   // a top-8 codebook leaves about 60 records per block, a larger one one or two
+  if (variant_short(grid) && runs_once(st)) {
+    VShortArgs sa;
+    sa.a = a;
+    sa.short_words = reinterpret_cast<uint64_t*>(a.slots);
+    sa.tag = next_call_tag();
+    sa.looks = short_looks();
+    SPLITZIP_V_DISPATCH3(v_short_kernel, a, dim3(grid), dim3(kThreads), st, sa);
+    if (a.val_bits != 8) launch_v_pack(n_elems, st, a);
+    return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
+  }
   if (grid) SPLITZIP_V_DISPATCH2(v_dense_kernel, dim3(grid), dim3(kThreads), st, a);
   if (!direct) hipLaunchKernelGGL(v_tile_sum_kernel, dim3(a.n_tiles), dim3(1024), 0, st, a);
   const unsigned fgrid = (unsigned)((blocks + kVFinishBlocks - 1) / kVFinishBlocks);
@@ -398,13 +452,7 @@ int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip
     case SPLITZIP_FP8_E5M2: launch_v_finish<SPLITZIP_FP8_E5M2>(fg, st, a); break;
     default: launch_v_finish<SPLITZIP_FP8_E4M3>(fg, st, a); break;
   }
-  if (grid && a.val_bits != 8) {
-    // M is known to the device only: a grid that strides over however many bytes the section has
-    uint64_t g = (v_val_bytes(n_elems, a.val_bits) + kThreads - 1) / kThreads;
-    const uint64_t cap = (uint64_t)cu_count() * 8;
-    if (g > cap) g = cap;
-    hipLaunchKernelGGL(v_pack_kernel, dim3((unsigned)g), dim3(kThreads), 0, st, a);
-  }
+  if (grid && a.val_bits != 8) launch_v_pack(n_elems, st, a);
   return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
 }
 
@@ -729,29 +777,6 @@ void launch_short(unsigned tiles, unsigned k, hipStream_t st, const TileArgs<kBa
   }
 }
 
-// Somewhere in the tags' range, another place in every process and for every copy of this library.
-uint64_t first_call() {
-  timespec now;
-  clock_gettime(CLOCK_REALTIME, &now);
-  const uint64_t x = ((uint64_t)now.tv_sec * 1000000000ull + (uint64_t)now.tv_nsec) ^ (reinterpret_cast<uintptr_t>(&g_hooks) << 20) ^ ((uint64_t)getpid() << 40);
-  return x * 0x9e3779b97f4a7c15ull;
-}
-// The tag of a call of compress_short_kernel: no two calls of a process have the same one.
-uint64_t next_call_tag() {
-  static std::atomic<uint64_t> calls{first_call()};
-  uint64_t tag;
-  do tag = calls.fetch_add(1, std::memory_order_relaxed) << kShortTagShift;
-  while (!tag);   // what cleared memory holds
-  return tag;
-}
-// Whether what is enqueued now runs once: a captured launch is replayed with the tag that it was captured with.
-bool runs_once(hipStream_t st) {
-  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s == hipStreamCaptureStatusNone;
-  (void)hipGetLastError();   // the legacy stream while another one is captured: the launch will say so itself
-  return false;
-}
-
 // How the next tensors of a compress call are launched: a function of their lengths, the word type and the status area.
 struct CompressPlan {
   uint32_t k;               // tensors of this launch; 0 if not even one fits
@@ -767,7 +792,6 @@ struct CompressPlan {
   uint32_t launches() const { return small || short_each ? 1u : group_sums ? 3u : tiles_max ? 2u : 1u; }
 };
 
-constexpr uint32_t kShortLooks = 64;      // about 50 us
 constexpr uint32_t kSmallestShort = 16;   // shorter tensors are one workgroup's work
 uint64_t short_status_need(uint64_t tiles) { return kShortCopies * short_copy_bytes(tiles); }
 // Words that a thread of compress_short_kernel looks at if it takes these tensors (tiles_max: of the longest), else 0.
@@ -935,8 +959,7 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     const unsigned pad = p.by_xcd && dtype == SPLITZIP_BF16 ? Bf16::kTileLdsPad : 0u;
     if (p.short_each) {
       a.stage_cap = next_call_tag();
-      const uint32_t looks = g_hooks.short_looks.load();
-      a.slot_cap = looks ? looks : kShortLooks;
+      a.slot_cap = short_looks();
       if (dtype == SPLITZIP_BF16) (p.short_each == 1 ? launch_short<Bf16, 1> : launch_short<Bf16, 2>)(tiles_max, k, st, args);
       else (p.short_each == 1 ? launch_short<E5m2, 1> : launch_short<E5m2, 2>)(tiles_max, k, st, args);
     } else if (p.small) {

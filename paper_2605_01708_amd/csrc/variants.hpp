@@ -292,16 +292,14 @@ __device__ inline void v_build_encode_table(const VArgs& a, uint32_t* lut, uint3
   }
 }
 
-// One block of 1024 elements by one wave, its words in w: planes out, the escape counts of its chunks, its escape
-// records (position in the block | exponent << 16, in element order) into its slot.  Returns the block's count.
-// The positions are ranked and collected in LDS first; the records then leave 64 at a time (with 6 % escapes a
-// block has 60, and a store per element and lane was half of the kernel's time).
+// One block of 1024 elements by one wave, its words in w: planes out, the positions of its first `cap` escapes in s_pos, its words in
+// s_words if it has any.  tot: the escapes of its two steps, low: those of the lower 32 lanes.
 template <int DT, int CB, bool FULL>
-__device__ inline uint32_t v_dense_block(const VArgs& a, const uint32_t* lut, uint32_t* s_words, uint16_t* s_pos, uint64_t blk,
-                                         uint32_t lane, const uint32_t (&w)[2][VFmt<DT>::NW]) {
+__device__ inline uint32_t v_encode_block(const VArgs& a, const uint32_t* lut, uint32_t* s_words, uint16_t* s_pos, uint32_t cap, uint64_t blk,
+                                          uint32_t lane, const uint32_t (&w)[2][VFmt<DT>::NW], uint32_t (&tot)[2], uint32_t (&low)[2]) {
   using F = VFmt<DT>;
   const uint64_t sm_end = a256(a.sm_bytes), code_end = a256(a.code_bytes);
-  uint32_t esc[2], excl[2], tot[2], low[2];
+  uint32_t esc[2], excl[2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     const uint64_t g = blk * kVBlock + s * kVStep;
@@ -322,16 +320,35 @@ __device__ inline uint32_t v_dense_block(const VArgs& a, const uint32_t* lut, ui
       while (m) {
         const uint32_t bit = (uint32_t)__ffs(m) - 1u, j = CB == 4 ? bit >> 2 : (bit * 11u) >> 5;   // bit / CB
         m &= m - 1;
-        if (r < kVSlotCap) s_pos[r] = (uint16_t)(s * kVStep + lane * 8 + j);
+        if (r < cap) s_pos[r] = (uint16_t)(s * kVStep + lane * 8 + j);
         ++r;
       }
     }
     v_lds_settle();
+  }
+  return total;
+}
+// exponent of the block's element p, out of its words
+template <int DT>
+__device__ inline uint32_t v_staged_exponent(const uint32_t* s_words, uint32_t p) {
+  using F = VFmt<DT>;
+  return F::exponent(F::ES == 2 ? (uint32_t)reinterpret_cast<const uint16_t*>(s_words)[p] : (uint32_t)reinterpret_cast<const uint8_t*>(s_words)[p]);
+}
+
+// The same for the dense pass: the escape counts of its chunks, its escape
+// records (position in the block | exponent << 16, in element order) into its slot.  Returns the block's count.
+// The positions are ranked and collected in LDS first; the records then leave 64 at a time (with 6 % escapes a
+// block has 60, and a store per element and lane was half of the kernel's time).
+template <int DT, int CB, bool FULL>
+__device__ inline uint32_t v_dense_block(const VArgs& a, const uint32_t* lut, uint32_t* s_words, uint16_t* s_pos, uint64_t blk,
+                                         uint32_t lane, const uint32_t (&w)[2][VFmt<DT>::NW]) {
+  uint32_t tot[2], low[2];
+  const uint32_t total = v_encode_block<DT, CB, FULL>(a, lut, s_words, s_pos, kVSlotCap, blk, lane, w, tot, low);
+  if (total) {
     uint32_t* slot = a.slots + blk * kVSlotCap;
     for (uint32_t i = lane; i < (total < kVSlotCap ? total : kVSlotCap); i += 64) {
       const uint32_t p = s_pos[i];
-      const uint32_t x = F::ES == 2 ? (uint32_t)reinterpret_cast<const uint16_t*>(s_words)[p] : (uint32_t)reinterpret_cast<const uint8_t*>(s_words)[p];
-      slot[i] = p | (F::exponent(x) << 16);
+      slot[i] = p | (v_staged_exponent<DT>(s_words, p) << 16);
     }
   }
   if (a.chunk_shift == 10) {
@@ -411,7 +428,8 @@ constexpr uint32_t kVFinishBlocks = 32;   // blocks of 1024 elements per workgro
 // that its workgroups would together read more than 128 MB of them, and it is given sums of kVScanTile chunks.
 constexpr uint32_t kVDirectSums = 16384;
 
-// where the records of a stream go: positions of PB bytes (none in the sentinel mode), and exponents, as bytes of the
+constexpr int kVAnyPos = -1;
+// where the records of a stream go: positions of PB bytes (none in the sentinel mode; kVAnyPos: as the call says), and exponents, as bytes of the
 // stream or, if values are narrower than a byte, of the workspace (v_pack_kernel); the rooms are in records
 template <int PB>
 struct VSink {
@@ -419,24 +437,54 @@ struct VSink {
   uint8_t* val;
   uint32_t pos_room, val_room;
   uint32_t pos_mask;   // of the element index: relative to the chunk, or (absolute mode) all of it
+  uint32_t pb;
   __device__ inline VSink(const VArgs& a, uint32_t M) {
-    const uint64_t off_val = a.off_pos + a256((uint64_t)PB * M);
+    pb = PB == kVAnyPos ? a.pos_bytes : PB;
+    const uint64_t off_val = a.off_pos + a256((uint64_t)pb * M);
     pos = a.out + a.off_pos;
-    pos_room = PB == 0 ? 0 : room32(a.capacity, a.off_pos, PB == 4 ? 2 : PB == 2 ? 1 : 0);
+    pos_room = pb == 0 ? 0 : room32(a.capacity, a.off_pos, pb == 4 ? 2 : pb == 2 ? 1 : 0);
     val = a.val_bits == 8 ? a.out + off_val : a.val_stage;
     val_room = a.val_bits != 8 ? ~0u : room32(a.capacity, off_val, 0);
-    pos_mask = PB == 4 ? ~0u : (1u << a.chunk_shift) - 1u;
+    pos_mask = pb == 4 ? ~0u : (1u << a.chunk_shift) - 1u;
   }
   __device__ inline void put(uint32_t rank, uint32_t elem, uint32_t e) const {
     const uint32_t p = elem & pos_mask;
-    if (PB != 0 && rank < pos_room) {
-      if (PB == 1) pos[rank] = (uint8_t)p;
-      if (PB == 2) reinterpret_cast<uint16_t*>(pos)[rank] = (uint16_t)p;
-      if (PB == 4) reinterpret_cast<uint32_t*>(pos)[rank] = p;
+    if (pb != 0 && rank < pos_room) {
+      if (pb == 1) pos[rank] = (uint8_t)p;
+      if (pb == 2) reinterpret_cast<uint16_t*>(pos)[rank] = (uint16_t)p;
+      if (pb == 4) reinterpret_cast<uint32_t*>(pos)[rank] = p;
     }
     if (rank < val_room) val[rank] = (uint8_t)e;
   }
 };
+
+// The header, the sizes record, the table's last entry and the zero padding, by one workgroup, once M is known.
+__device__ inline void v_write_trailer(const VArgs& a, const uint32_t (&hdr)[16], uint32_t M, uint32_t tid) {
+  const uint64_t n_blocks = (a.n + kVBlock - 1) / kVBlock;
+  if (tid == 0) a.offs[a.n_chunks] = M;   // the table's last entry; in the absolute mode a word of the workspace, for v_pack_kernel
+  const uint64_t pos_sec = a256((uint64_t)a.pos_bytes * M), total = a.off_pos + pos_sec + v_val_bytes(M, a.val_bits);
+  // zero padding: behind the table, behind what the dense pass covered of each plane, behind the positions
+  const uint64_t tab_end = a.mode == SPLITZIP_ESC_ABS32 ? kHeaderBytes : a.off_tab + 4 * (a.n_chunks + 1);
+  for (uint64_t i = tab_end + tid; i < a.off_sm; i += kThreads) a.out[i] = 0;
+  const uint64_t sm_cov = n_blocks * (kVBlock / 8) * v_sm_bits(a.dtype), code_cov = n_blocks * (kVBlock / 8) * a.code_bits;
+  for (uint64_t i = sm_cov + tid; i < a256(a.sm_bytes); i += kThreads) a.out[a.off_sm + i] = 0;
+  for (uint64_t i = code_cov + tid; i < a256(a.code_bytes); i += kThreads) a.out[a.off_code + i] = 0;
+  for (uint64_t i = (uint64_t)a.pos_bytes * M + tid; i < pos_sec; i += kThreads)
+    if (a.off_pos + i < a.capacity) a.out[a.off_pos + i] = 0;
+  if (tid < 16) {
+    uint32_t w = hdr[tid];
+    if (tid == 6) w = M;
+    if (tid == 8) w = (uint32_t)total;
+    if (tid == 9) w = (uint32_t)(total >> 32);
+    reinterpret_cast<uint32_t*>(a.out)[tid] = w;
+  }
+  if (tid == 0) {
+    a.sizes->total_bytes = total;
+    a.sizes->n_escapes = M;
+    a.sizes->status = total > a.capacity ? SPLITZIP_STATUS_OVERFLOW : 0u;
+    a.sizes->reserved = 0;
+  }
+}
 
 // Compress pass 3: one workgroup per kVFinishBlocks blocks.  It sums the counts (the whole tensor's: M; those before
 // its blocks: its first rank), writes its chunks' entries of the offset table, and moves its blocks' records from
@@ -582,31 +630,81 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs args) {
       }
     }
   }
-  if (g != 0) return;
+  if (g == 0) v_write_trailer(a, args.hdr, M, tid);
+}
 
-  if (tid == 0) a.offs[a.n_chunks] = M;   // the table's last entry; in the absolute mode a word of the workspace, for v_pack_kernel
-  const uint64_t pos_sec = a256((uint64_t)a.pos_bytes * M), total = a.off_pos + pos_sec + v_val_bytes(M, a.val_bits);
-  // zero padding: behind the table, behind what the dense pass covered of each plane, behind the positions
-  const uint64_t tab_end = a.mode == SPLITZIP_ESC_ABS32 ? kHeaderBytes : a.off_tab + 4 * (a.n_chunks + 1);
-  for (uint64_t i = tab_end + tid; i < a.off_sm; i += kThreads) a.out[i] = 0;
-  const uint64_t sm_cov = (uint64_t)n_blocks * (kVBlock / 8) * v_sm_bits(a.dtype), code_cov = (uint64_t)n_blocks * (kVBlock / 8) * a.code_bits;
-  for (uint64_t i = sm_cov + tid; i < a256(a.sm_bytes); i += kThreads) a.out[a.off_sm + i] = 0;
-  for (uint64_t i = code_cov + tid; i < a256(a.code_bytes); i += kThreads) a.out[a.off_code + i] = 0;
-  for (uint64_t i = (uint64_t)a.pos_bytes * M + tid; i < pos_sec; i += kThreads)
-    if (a.off_pos + i < a.capacity) a.out[a.off_pos + i] = 0;
-  if (tid < 16) {
-    uint32_t w = args.hdr[tid];
-    if (tid == 6) w = M;
-    if (tid == 8) w = (uint32_t)total;
-    if (tid == 9) w = (uint32_t)(total >> 32);
-    reinterpret_cast<uint32_t*>(a.out)[tid] = w;
-  }
-  if (tid == 0) {
-    a.sizes->total_bytes = total;
-    a.sizes->n_escapes = M;
-    a.sizes->status = total > a.capacity ? SPLITZIP_STATUS_OVERFLOW : 0u;
-    a.sizes->reserved = 0;
-  }
+// Short calls (splitzip_variant_compress): the passes above in one launch, as in compress_short_kernel, a block per wave.
+// short_words: where the workgroups' words lie (the blocks' slots, which nothing is staged in here); tag, looks: as there.
+// us per call, two launches and this: BF16 top-8 7.8 and 4.45 (4 blocks), 8.0 and 5.2 (100), 8.2 and 5.6 (1000), 8.7 and 6.35 (2000), sentinels
+// 7.8 and 4.8 (100), 8.1 and 5.5 (2000); E5M2 7.8 and 4.9, 7.9 and 5.5, with narrow values, which v_pack_kernel still packs, 11.7 and 8.3, 12.0
+// and 9.4; random words, BF16 top-8, 1000 blocks 28.2 and 9.0.  Beyond 2048 blocks the words that every workgroup looks at cost more
+// than a launch (short_each).
+struct VShortArgs {
+  VArgs a;
+  uint64_t* short_words;
+  uint64_t tag;
+  uint32_t looks;
+};
+constexpr int kVShortEach = 2;
+template <int DT, int CB>
+__global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args) {
+  using F = VFmt<DT>;
+  static_assert(kThreads == kTileThreads, "ShortCounts");
+  __shared__ uint32_t lut[256];
+  __shared__ __attribute__((aligned(16))) uint32_t s_words[kWaves][kVBlock * F::ES / 4];
+  __shared__ uint16_t s_pos[kWaves][kVBlock];   // room for all of a wave's records
+  __shared__ uint32_t s_cnt[kWaves];
+  __shared__ ShortShared<kVShortEach> s_short;
+  const VArgs a = v_args_arrived(args.a);
+  const uint32_t tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  ShortCounts<kVShortEach> counts(args.short_words, args.tag, gridDim.x, blockIdx.x);
+  uint32_t blk = 0, count = 0, tot[2], low[2];   // the wave's block and its escapes
+  uint32_t in_tile = 0, total = 0;               // escapes of the tile before the wave's block; all of them
+  auto encode = [&](uint32_t tile, bool build) {
+    blk = tile * kWaves + wave;
+    count = tot[0] = tot[1] = low[0] = low[1] = 0;
+    const uint64_t e0 = (uint64_t)blk * kVBlock;
+    const bool live = e0 < a.n, full = e0 + kVBlock <= a.n;
+    uint32_t w[2][F::NW];
+    // the block's words first, all of them: the table is built while they are on their way
+    if (full) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) v_load8<DT, true>(a, e0 + s * kVStep + lane * 8, w[s]);
+    } else if (live) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) v_load8<DT, false>(a, e0 + s * kVStep + lane * 8, w[s]);
+    }
+    if (build) {
+      v_build_encode_table(args.a, lut, tid);
+      lds_barrier();
+    }
+    if (full) count = v_encode_block<DT, CB, true>(a, lut, s_words[wave], s_pos[wave], kVBlock, blk, lane, w, tot, low);
+    else if (live) count = v_encode_block<DT, CB, false>(a, lut, s_words[wave], s_pos[wave], kVBlock, blk, lane, w, tot, low);
+    if (lane == 0) s_cnt[wave] = count;
+    lds_barrier();
+    in_tile = total = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kWaves; ++q) {
+      const uint32_t x = s_cnt[q];
+      in_tile += q < wave ? x : 0u;
+      total += x;
+    }
+  };
+  auto place = [&](uint32_t tile) {
+    const VSink<kVAnyPos> sink(a, counts.M);
+    const uint32_t base = counts.first + in_tile;
+    const uint32_t cpb_shift = 10u - a.chunk_shift;   // log2 of the chunks per block: 0 or 2
+    const uint64_t c = ((uint64_t)blk << cpb_shift) + lane;
+    if (a.mode != SPLITZIP_ESC_ABS32 && lane < (1u << cpb_shift) && c < a.n_chunks)
+      a.offs[c] = base + (lane == 0 ? 0u : lane == 1 ? low[0] : lane == 2 ? tot[0] : tot[0] + low[1]);
+    for (uint32_t i = lane; i < count; i += 64) {
+      const uint32_t p = s_pos[wave][i];
+      sink.put(base + i, blk * kVBlock + p, v_staged_exponent<DT>(s_words[wave], p));
+    }
+    if (tile == 0) v_write_trailer(a, args.a.hdr, counts.M, tid);
+  };
+  counts.run(s_short, args.looks, total, tid, wave, encode, place);
 }
 
 // compress pass 4, for values narrower than a byte: the value section as an LSB-first bit stream of val_bits per
