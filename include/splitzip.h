@@ -165,7 +165,7 @@ int splitzip_workspace_init(void* d_workspace, size_t workspace_bytes, void* str
  * enqueued.  If the fixed part fits but the escapes do not, everything that
  * fits is written, status gets SPLITZIP_STATUS_OVERFLOW and total_bytes is
  * the size a retry needs.  n_elems == 0 is valid (header and one offset).
- * Two launches on `stream` (three above about 180 Mi elements; one up to 4
+ * Two launches on `stream` (three above about 180 Mi elements; one up to 2
  * Mi elements, while a graph is captured up to 40 chunks of BF16 or 48 of
  * E5M2).
  * The output is a pure function of (input, codebook): independent of
@@ -219,7 +219,8 @@ int splitzip_decompress(const void* d_comp, size_t comp_bytes, uint64_t n_elems,
  * Overhead with Pipeline Overlap" feeds the codec such batches).  Each item is
  * compressed exactly as splitzip_compress would (same stream bytes); what a
  * single call pays per tensor for two launches -- the ramps of the dense pass
- * and the short finishing pass -- is paid once per 64 tensors.  Every item
+ * and the short finishing pass -- is paid once per 160 tensors
+ * (64 where they differ much in length).  Every item
  * names its own codebook: per-layer codebooks (the
  * section "Ablation on Layer-Wise Coverage") cost no more than shared ones.
  * `items` is a HOST array, read before the call returns.
@@ -437,8 +438,8 @@ int splitzip_variant_codebook_from_dec(const uint8_t* dec, const splitzip_varian
  * splitzip_decompress; d_workspace needs splitzip_variant_workspace_bytes and
  * 16-byte alignment.  Two kernel launches per compress call (dense pass that
  * also stages the escape records, finishing pass; above 64 Mi elements a
- * third between them sums the counts, and one more packs values narrower than
- * a byte), one per decompress call (two in the absolute mode), all on
+ * third between them sums the counts), up to 2 Mi elements, if not captured,
+ * one that does both, and one more that packs values narrower than a byte; one per decompress call (two in the absolute mode), all on
  * `stream`. */
 int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip_variant* v,
                               const splitzip_codebook* cb, void* d_out, size_t out_capacity, void* d_workspace,

@@ -7,7 +7,7 @@
 // decompress
 // ---------------------------------------------------------------------------
 
-// The arguments of a launch: what all its streams share, then the streams (N: room for kBatchMax of them, or for the one
+// The arguments of a launch: what all its streams share, then the streams (N: room for kBatchMax or kBatchFew of them, or for the one
 // of a single call).  blockIdx.y picks the stream, blockIdx.x the tile.  What a wave needs of the layout before its first
 // load comes ready: with a tile per workgroup, a scalar instruction of the beginning is one per wave.
 struct DItem {

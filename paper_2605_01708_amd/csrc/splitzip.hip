@@ -40,6 +40,7 @@ namespace {
 // host side
 // ---------------------------------------------------------------------------
 
+uint64_t chunks_of(uint64_t n) { return (n + kChunk - 1) / kChunk; }
 bool dtype_ok(int dtype) { return dtype == SPLITZIP_BF16 || dtype == SPLITZIP_FP8_E5M2; }
 unsigned exp_values(int dtype) { return dtype == SPLITZIP_BF16 ? 256u : 32u; }
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -64,6 +65,13 @@ template <typename A>
 void launch(void (*kernel)(A), dim3 grid, dim3 block, unsigned lds, hipStream_t st, const A& args) {
   void* params[] = {const_cast<A*>(&args)};
   (void)hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, params, lds, st);
+}
+
+// the arguments of a launch of few tensors, which begin those of one of many
+template <template <uint32_t> class A>
+const A<kBatchFew>& few(const A<kBatchMax>& args) {
+  static_assert(offsetof(A<kBatchFew>, item) == offsetof(A<kBatchMax>, item) && alignof(A<kBatchFew>) == alignof(A<kBatchMax>), "one begins the other");
+  return reinterpret_cast<const A<kBatchFew>&>(args);
 }
 
 // What the tests of the rarely taken paths turn: a staging area and a status area smaller than the workspace has
@@ -158,6 +166,21 @@ uint64_t first_call() {
   const uint64_t x = ((uint64_t)now.tv_sec * 1000000000ull + (uint64_t)now.tv_nsec) ^ (reinterpret_cast<uintptr_t>(&g_hooks) << 20) ^ ((uint64_t)getpid() << 40);
   return x * 0x9e3779b97f4a7c15ull;
 }
+// The next tensors of a batch that go into one launch, of n: kBatchFew, and more up to kBatchMax as long as the launch's row
+// of workgroups per tensor, as long as the longest, leaves no more than 8192 workgroups without a tile of four chunks (2 us).
+template <typename Item>
+uint32_t tensors_of_launch(const Item* items, uint32_t n) {
+  uint64_t all = 0, most = 0;
+  uint32_t k = 0;
+  for (; k < n && k < kBatchMax; ++k) {
+    const uint64_t c = chunks_of(items[k].n_elems), longest = c > most ? c : most;
+    if (k >= kBatchFew && longest * (k + 1) - (all + c) > 4 * 8192) break;
+    all += c;
+    most = longest;
+  }
+  return k;
+}
+
 // The tag of a call of compress_short_kernel: no two calls of a process have the same one.
 uint64_t next_call_tag() {
   static std::atomic<uint64_t> calls{first_call()};
@@ -704,7 +727,6 @@ int workspace_view(void* d_workspace, size_t workspace_bytes, uint64_t n_max, in
   return SPLITZIP_OK;
 }
 
-uint64_t chunks_of(uint64_t n) { return (n + kChunk - 1) / kChunk; }
 uint64_t tiles_of(uint64_t chunks, uint32_t cpt) { return (chunks + 4ull * cpt - 1) >> (2 + __builtin_ctz(cpt)); }   // cpt: a power of two
 // bytes of the status area a tensor of `tiles` tiles takes: a count per tile, a sum per group of tiles
 uint64_t status_need(uint64_t tiles) { return a256(4 * tiles + 4 * ((tiles + kSumGroup - 1) / kSumGroup)); }
@@ -761,6 +783,8 @@ void launch_small(unsigned k, hipStream_t st, const TileArgs<kBatchMax>& args) {
   if (k == 1) {
     const TileArgs<1> one = {args.shared, {args.item[0]}};
     launch(compress_small_kernel<F, 1>, dim3(1), dim3(kSmallThreads), 0, st, one);
+  } else if (k <= kBatchFew) {
+    launch(compress_small_kernel<F, kBatchFew>, dim3(k), dim3(kSmallThreads), 0, st, few(args));
   } else {
     launch(compress_small_kernel<F, kBatchMax>, dim3(k), dim3(kSmallThreads), 0, st, args);
   }
@@ -772,6 +796,8 @@ void launch_short(unsigned tiles, unsigned k, hipStream_t st, const TileArgs<kBa
   if (k == 1) {
     const TileArgs<1> one = {args.shared, {args.item[0]}};
     launch(compress_short_kernel<F, 1, EACH>, grid, block, 0, st, one);
+  } else if (k <= kBatchFew) {
+    launch(compress_short_kernel<F, kBatchFew, EACH>, grid, block, 0, st, few(args));
   } else {
     launch(compress_short_kernel<F, kBatchMax, EACH>, grid, block, 0, st, args);
   }
@@ -819,10 +845,10 @@ template <typename Once>
 CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_t n_max, int dtype, uint64_t status_bytes, const Once& once) {
   CompressPlan p;
   memset(&p, 0, sizeof p);
-  // as many of the next tensors (kBatchMax at most) as find room for their counts in the status area; all of them share
+  // as many of the next tensors (tensors_of_launch at most) as find room for their counts in the status area; all of them share
   // the tile size of the one that needs the largest
   const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
-  const uint32_t k_most = n_items < kBatchMax ? n_items : kBatchMax;
+  const uint32_t k_most = tensors_of_launch(items, n_items);
   uint64_t chunks_all = 0, chunks_max = 0;
   for (uint32_t q = 0; q < k_most; ++q) {
     const uint64_t c = chunks_of(items[q].n_elems);
@@ -969,6 +995,9 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       const TileArgs<1> one = {args.shared, {args.item[0]}};
       if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, 1, p.is_long, pad, st, one);
       else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, 1, p.is_long, pad, st, one);
+    } else if (k <= kBatchFew) {
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, few(args));
+      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, few(args));
     } else {
       if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, args);
       else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, args);
@@ -1187,10 +1216,10 @@ int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dty
   while (i < n_items) {
     DArgs<kBatchMax> args;   // the first k items are filled in, and no other is looked at
     DShared& a = args.shared;
-    uint32_t k = 0;
-    for (; i + k < n_items && k < kBatchMax; ++k) {
-      const splitzip_ditem& it = items[i + k];
-      DItem& to = args.item[k];
+    const uint32_t k = tensors_of_launch(items + i, n_items - i);
+    for (uint32_t q = 0; q < k; ++q) {
+      const splitzip_ditem& it = items[i + q];
+      DItem& to = args.item[q];
       if (!d_cbs && !own_dec) memcpy(to.dec, it.cb->dec, 16);
       else memset(to.dec, 0, 16);
       describe_stream(it.d_comp, it.comp_bytes, it.d_out, it.n_elems, dtype, &to);
@@ -1203,8 +1232,9 @@ int decompress_batch_impl(const splitzip_ditem* items, uint32_t n_items, int dty
     a.reserved[0] = a.reserved[1] = 0;
     a.by_xcd = p.by_xcd;
     const dim3 grid(p.wgs, k);
-    if (dtype == SPLITZIP_BF16) launch_decompress<DBf16>(p.cpw, grid, p.lds_pad, static_cast<hipStream_t>(stream), args);
-    else launch_decompress<DE5m2>(p.cpw, grid, p.lds_pad, static_cast<hipStream_t>(stream), args);
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    if (dtype == SPLITZIP_BF16) k <= kBatchFew ? launch_decompress<DBf16>(p.cpw, grid, p.lds_pad, st, few(args)) : launch_decompress<DBf16>(p.cpw, grid, p.lds_pad, st, args);
+    else k <= kBatchFew ? launch_decompress<DE5m2>(p.cpw, grid, p.lds_pad, st, few(args)) : launch_decompress<DE5m2>(p.cpw, grid, p.lds_pad, st, args);
     if (hipGetLastError() != hipSuccess) return SPLITZIP_ERR_HIP;
     i += k;
   }
@@ -1354,7 +1384,7 @@ uint32_t splitzip_internal_stream_room(uint64_t comp_bytes, uint64_t n_elems, in
   return it.most;
 }
 void splitzip_internal_decompress_plan(const splitzip_ditem* items, uint32_t n_items, int dtype, uint32_t out[4]) {
-  const DecompressPlan p = plan_decompress(items, n_items < kBatchMax ? n_items : kBatchMax, dtype);
+  const DecompressPlan p = plan_decompress(items, tensors_of_launch(items, n_items), dtype);
   out[0] = p.cpw; out[1] = p.wgs; out[2] = p.by_xcd; out[3] = p.lds_pad;
 }
 

@@ -1,0 +1,50 @@
+"""Batches around what a launch takes, 64 and 160 tensors: the oracle's streams and the words back, through the launches of short
+calls and of others, of equal and of unequal lengths."""
+import numpy as np
+import pytest
+import torch
+
+import kv_synth
+import oracle
+import paper_2605_01708_amd as sz
+
+FORMATS = [(sz.BF16, oracle.BF16), (sz.FP8_E5M2, oracle.E5M2)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("short", [True, False])
+@pytest.mark.parametrize("dtype,odt", FORMATS)
+@pytest.mark.parametrize("count", [64, 65, 160, 161])
+def test_streams_and_words(dtype, odt, count, short):
+    gen = kv_synth.kv_bf16 if dtype == sz.BF16 else kv_synth.kv_e5m2
+    sample = gen(64, 1)
+    cb, ocb = sz.calibrate(sample, dtype), oracle.calibrate(kv_synth.to_numpy_words(sample), odt)
+    sizes = [(1, 17, 5, 23)[k % 4] * 1024 - 3 * (k % 7) if k % 9 else 0 for k in range(count)]
+    if not short:
+        sizes[3] = 300 * 1024 - 1
+    xs = [gen(s // 1024 + 1, k)[:s].contiguous() for k, s in enumerate(sizes)]
+    dx = [x.cuda() for x in xs]
+    blobs = [oracle.compress(kv_synth.to_numpy_words(x), ocb) for x in xs]
+    outs = [torch.full((-(-sz.compress_bound(s, dtype) // 256) * 256,), 0xA5, dtype=torch.uint8, device="cuda") for s in sizes]
+    ws, rec = sz.Workspace(max(sizes), dtype), sz.new_sizes_array(count)
+    try:
+        sz.internal_test_short(0 if short else sz.INTERNAL_NO_SHORT)
+        sz.compress_batch(dx, [cb] * count, outs, ws, rec)
+    finally:
+        sz.internal_test_short()
+    got = sz.read_sizes_array(rec)
+    for (blob, m), out, g in zip(blobs, outs, got):
+        assert g == (blob.size, m, 0) and np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == 0xA5).all())
+    ys, drec = [torch.zeros_like(x) for x in dx], sz.new_sizes()
+    sz.DecompressBatch(outs, [g[0] for g in got], sizes, [cb] * count, ys).launch(drec)
+    assert sz.read_sizes(drec)[2] == 0 and all(torch.equal(x, y) for x, y in zip(dx, ys))
+
+
+@pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
+def test_tensors_of_a_launch(dtype):
+    """More than 64 go into a launch where hardly any workgroup has no tile."""
+    def tensors(chunks):
+        return sz.internal_compress_plan([c * 1024 for c in chunks], dtype)["tensors"]
+    assert [tensors([100] * n) for n in (64, 65, 160, 161, 400)] == [64, 65, 160, 160, 160]
+    assert tensors([8192] * 64 + [2] * 96) == 68 and tensors([2] * 64 + [8192] * 96) == 64 and tensors([2000, 1900] * 80) == 160
+    assert tensors([0] * 200) == 160
