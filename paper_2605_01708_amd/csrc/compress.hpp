@@ -345,9 +345,9 @@ struct Bf16 {
   // A workgroup of four waves takes a tile of 4 cpt chunks (pick_base_cpt: 16 KB of words, less for short launches), at
   // most kCpt of a wave's chunks at a time.  Eight workgroups per CU, what the
   // registers allow, serve launches of few tiles best and five those of many: us per call with eight / five / four,
-  // 1219 / 1199 / 1203 (262 144 tiles), 309 / 306 / 307 (65 536), 81.6 / 81.6 / 82.2 (16 384), 45.1 / 45.5 / 46.0
-  // (8192), 26.5 / 26.9 / 27.1 (4096: one tensor), 17.4 / 18.1 / 18.0 (2048); unused LDS asked for at the launch sets
-  // the number (compress_launch).
+  // 1219 / 1199 / 1203 (262 144 tiles), 309 / 306 / 307 (65 536), 26.5 / 26.9 / 27.1 (4096: one tensor), 17.4 / 18.1 / 18.0
+  // (2048), and 43.0 / 42.5 (8192), 34.3 / 34.1 (6144) by a later kernel; unused LDS asked for at the launch sets the number
+  // (plan_compress).
   static constexpr uint32_t kCpt = 2;
   static constexpr uint32_t kTileLdsPad = 22000;   // five workgroups per CU
   static constexpr uint32_t kSmallChunks = 40;

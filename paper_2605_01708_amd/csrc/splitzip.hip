@@ -810,7 +810,8 @@ struct CompressPlan {
   uint64_t tiles_max;       // of the longest tensor: the dense pass has k rows of so many workgroups
   bool small;               // one launch of compress_small_kernel
   uint32_t short_each;      // one launch of compress_short_kernel, whose threads look at so many words; 0: not that
-  bool by_xcd;              // the dense pass takes its tiles in xcd_order, BF16 with fewer workgroups per CU
+  bool by_xcd;              // the dense pass takes its tiles in xcd_order
+  uint32_t lds_pad;         // unused LDS asked for at the launch of the dense pass: fewer workgroups per CU
   bool is_long;             // the dense pass stores through the L2 (kTileLong)
   uint32_t finish_groups;   // groups of kGroup tiles per workgroup of the finishing pass
   uint32_t finish_wgs;      // workgroups of the finishing pass per tensor
@@ -883,14 +884,16 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
     p.tiles_max = short_max;
     return p;
   }
-  // Launches of many tiles, from 16 384 on, take them in xcd_order, and BF16 with fewer workgroups per CU
-  // (Bf16::kTileLdsPad).  us per call, in the order of the tiles and in xcd_order: BF16 (16 KB tiles) 1241 and 1201
-  // (262 144 tiles), 161.8 and 157.7 (32 768), 83.0 and 80.8 (16 384), 43.8 and 43.6 (8192); E5M2, tiles of 8 KB 176.2
-  // and 172.4 (65 536), 49.3 and 48.7 (16 384), 29.0 and 28.7 (8192), of 16 KB 690 and 665 (131 072).  What counts are
+  // Launches of 2048 tiles and more take them in xcd_order, and BF16 from 6144 on with fewer workgroups per CU (Bf16::kTileLdsPad).  us per call,
+  // in the order of the tiles, in xcd_order and, BF16, in it with fewer workgroups: BF16 10.93 / 10.78 / 11.40 (2048 tiles: 16 tensors of 512
+  // chunks), 15.70 / 15.68 / 16.14 (4096 of one chunk per wave), 25.46 / 25.27 / 25.53 (4095), 25.07 / 25.02 / 25.28 (4096: one tensor), 34.31 /
+  // 34.33 / 34.13 (6144), 43.16 / 42.96 / 42.48 (8192), 78.1 / - / 76.4 (16 000), 1241 / - / 1201 (262 144); E5M2 11.70 / 11.66 (2048), 17.62 / 17.39 and
+  // 17.14 / 17.01 (4096), 27.42 / 26.95 (8192), 46.4 / 45.0 (16 000), 690 / 665 (131 072 of 16 KB).  What counts are
   // the tiles that there are: where the tensors differ in length, most of a launch's workgroups may have none, and they
   // take longer to pass by that way (BF16, one tensor of 13 000 chunks beside 63 of two: 35.1 and 40.6; 16 of 8192
   // beside 48 of 16: 91.5 and 95.6; but 32 of 16 384 beside 32 of 16: 328 and 321).
-  p.by_xcd = tiles_all >= 16384 && p.tiles_max * p.k <= 2 * tiles_all;
+  p.by_xcd = tiles_all >= 2048 && p.tiles_max * p.k <= 2 * tiles_all;
+  p.lds_pad = p.by_xcd && dtype == SPLITZIP_BF16 && (tiles_all >= 6144 || g_hooks.xcd.load() == 2) ? Bf16::kTileLdsPad : 0u;
   if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2;
   // Launches that memory alone bounds store through the L2 (kTileLong).  us per call, without and with:
   // BF16 21.0 and 21.2 (3072 tiles), 25.6 and 25.7 (4096), 35.05 and 34.98 (6144), 82.2 and 80.9 (16 384), 158.2 and
@@ -982,7 +985,6 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     a.use_group_sums = p.group_sums ? 1u : 0u;
     a.by_xcd = p.by_xcd ? 1u : 0u;
     const unsigned tiles_max = (unsigned)p.tiles_max, sums_max = (tiles_max + kSumGroup - 1) / kSumGroup;
-    const unsigned pad = p.by_xcd && dtype == SPLITZIP_BF16 ? Bf16::kTileLdsPad : 0u;
     if (p.short_each) {
       a.stage_cap = next_call_tag();
       a.slot_cap = short_looks();
@@ -993,14 +995,14 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       else launch_small<E5m2>(k, st, args);
     } else if (k == 1) {
       const TileArgs<1> one = {args.shared, {args.item[0]}};
-      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, 1, p.is_long, pad, st, one);
-      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, 1, p.is_long, pad, st, one);
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, 1, p.is_long, p.lds_pad, st, one);
+      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, 1, p.is_long, p.lds_pad, st, one);
     } else if (k <= kBatchFew) {
-      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, few(args));
-      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, few(args));
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, p.lds_pad, st, few(args));
+      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, p.lds_pad, st, few(args));
     } else {
-      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, args);
-      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, pad, st, args);
+      if (dtype == SPLITZIP_BF16) launch_compress<Bf16>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, p.lds_pad, st, args);
+      else launch_compress<E5m2>(tiles_max, p.finish_wgs, sums_max, k, p.is_long, p.lds_pad, st, args);
     }
     if (hipGetLastError() != hipSuccess) return SPLITZIP_ERR_HIP;
     i += k;
@@ -1069,15 +1071,16 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
   }
   p.wgs = (uint32_t)((chunks_max + (uint64_t)kWaves * p.cpw - 1) / (kWaves * p.cpw));
   if (p.wgs < 1) p.wgs = 1;
-  // Launches of many workgroups, from 16 384 on, take their tiles in xcd_order.  us per call, in the order of the tiles and
-  // that way: BF16 606.6 and 599.2 (262 144 workgroups), 302.6 and 298.8 (65 536 of two chunks per wave), 74.9 and 72.9
-  // (32 768), 73.6 both (16 000); E5M2 663 and 641 (131 072), 154.6 and 154.3 (65 536), 40.4 both (16 000).  As in
+  // Launches of 4096 workgroups and more take their tiles in xcd_order.  us per call, in the order of the tiles and that way: BF16
+  // 21.3 and 20.9 (4096 workgroups of two chunks per wave), 21.0 and 20.6 (8192 of one: a stream of 32 768 chunks), 38.8 and 38.1 (65 536 chunks), 39.2
+  // and 38.4 (64 streams of 1024), 74.0 and 72.9 (64 of 1999), 606.6 and 599.2 (262 144), but 11.8 and 12.0 (2048: one stream of 16 384 chunks); E5M2,
+  // without the fewer workgroups below, 18.66 and 18.67 (6144), 23.2 and 23.1 (8192), 663 and 641 (131 072), but 13.52 and 13.56 (2048).  As in
   // plan_compress, by the workgroups that have a tile (BF16, one stream of 32 768 chunks beside 63 of two, with another
   // decoder: 97.3 and 111.1).
   uint64_t wgs_all = 0;
   const uint32_t shift = (uint32_t)__builtin_ctz(kWaves * p.cpw);
   for (uint32_t q = 0; q < k; ++q) wgs_all += (chunks_of(items[q].n_elems) + kWaves * p.cpw - 1) >> shift;
-  p.by_xcd = wgs_all >= 16384u && (uint64_t)p.wgs * k <= 2 * wgs_all ? 1u : 0u;
+  p.by_xcd = wgs_all >= 4096u && (uint64_t)p.wgs * k <= 2 * wgs_all ? 1u : 0u;
   if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2 ? 1u : 0u;
   // Fewer workgroups per CU, five instead of eight, where a launch is long and its waves have much on their way.  us per call
   // with eight / six / five / four: BF16, two chunks per wave, 1240 / 1184 / 1172 / 1170 (2 Mi chunks), 300.9 / 295.5 / 292.8 /
@@ -1089,7 +1092,9 @@ DecompressPlan plan_decompress(const splitzip_ditem* items, uint32_t k, int dtyp
   // in one stream, 144), 508 / 400 (524 288, 384); E5M2 313.1 / 315.1 (1 Mi, 26), 327.9 / 317.8 (31), 366.7 / 341.8 (51), 514 /
   // 432 (205).
   const bool within = beyond * kChunk <= 3 * n_all * (dtype == SPLITZIP_BF16 ? 64u : 28u);   // three bytes per record
-  p.lds_pad = p.by_xcd && within && p.cpw == (dtype == SPLITZIP_BF16 ? 2u : 4u) ? kDecodeLdsPad : 0u;
+  // E5M2 from 16 384 workgroups on: 13.5 and 14.3 (2048 workgroups), 23.4 and 23.9 (4096), 28.98 and 28.93 (5513).
+  const bool enough = dtype == SPLITZIP_BF16 ? p.cpw == 2 : p.cpw == 4 && (wgs_all >= 16384u || g_hooks.xcd.load() == 2);
+  p.lds_pad = p.by_xcd && within && enough ? kDecodeLdsPad : 0u;
   return p;
 }
 
