@@ -516,7 +516,7 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs args) {
   const uint64_t my_c = ((uint64_t)blk0 << cpb_shift) + lane;
   const bool have = lane < (kPerWave << cpb_shift) && my_c < a.n_chunks;
   const uint32_t mine = ld_run4<0>(run_of(reinterpret_cast<const uint8_t*>(a.counts), 4u * (uint32_t)a.n_chunks), have ? 4u * (uint32_t)my_c : kNone);
-  uint32_t rec[kPerWave], rec2[kPerWave];
+  uint32_t rec[kPerWave], rec2[kPerWave] = {};
   const uint32_t* const slots = a.slots + (uint64_t)blk0 * kVSlotCap;
   const auto slot_run = run_of(reinterpret_cast<const uint8_t*>(slots), 4u * kVSlotCap * blocks_here);
   const uint32_t first_off = lane < a.ahead ? 4u * lane : kNone;
@@ -544,10 +544,13 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs args) {
   uint32_t bp[kPerWave + 1];   // wave-uniform: escapes of the wave's blocks before each block
 #pragma unroll
   for (uint32_t q = 0; q <= kPerWave; ++q) bp[q] = starts(q);
+  // (none, as a rule, where a codebook of 16 leaves one or two per block: 13 000 blocks 15.1 us a call, 14.7 without these loads)
+  if (a.ahead >= 64u || wave_total > a.ahead) {
 #pragma unroll
-  for (uint32_t q = 0; q < kPerWave; ++q) {
-    const uint32_t n_b = bp[q + 1] - bp[q], i = a.ahead + lane;
-    rec2[q] = ld_run4<0>(slot_run, n_b <= kVSlotCap && i < n_b ? 4u * (kVSlotCap * q + i) : kNone);
+    for (uint32_t q = 0; q < kPerWave; ++q) {
+      const uint32_t n_b = bp[q + 1] - bp[q], i = a.ahead + lane;
+      rec2[q] = ld_run4<0>(slot_run, n_b <= kVSlotCap && i < n_b ? 4u * (kVSlotCap * q + i) : kNone);
+    }
   }
   for (uint32_t v0 = 0;;) {
 #pragma unroll
