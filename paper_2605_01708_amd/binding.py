@@ -220,8 +220,9 @@ _NOT_TAKEN = 1   # what a function of lib().fast answers if it has done nothing
 
 
 def _handle(stream):
-    """What lib().fast takes for a stream: its handle, or None for the current one."""
-    return None if stream is None else int(stream.cuda_stream)
+    """What lib().fast takes for a stream, its handle; for the current one it takes None.  (The calls below have neither a
+    call of their own for that, nor one for a result of 0 or for the library that is loaded: 0.1 us each.)"""
+    return int(stream.cuda_stream)
 
 
 class Codebook:
@@ -314,10 +315,10 @@ def codebook_device(hist: torch.Tensor, dtype: int, out: DeviceCodebook | None =
 def compress_dcb(x: torch.Tensor, d_cb: DeviceCodebook, out: torch.Tensor, workspace: "Workspace", sizes: torch.Tensor,
                  stream=None, capacity: int | None = None) -> None:
     """splitzip_compress_dcb: splitzip_compress with a codebook in device memory."""
-    rc = lib().fast.splitzip_compress_dcb(x, d_cb.dtype, d_cb.buf, out, capacity, workspace.buf, workspace.nbytes, sizes,
-                                          _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_compress_dcb(x, d_cb.dtype, d_cb.buf, out, capacity, workspace.buf, workspace.nbytes, sizes,
+                                          None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_compress_dcb")
+        return _check(rc, "splitzip_compress_dcb") if rc else None
     if x.element_size() != _elem_size(d_cb.dtype) or not x.is_contiguous():
         raise ValueError("x must be a contiguous tensor of raw words of the codebook's dtype")
     cap = out.numel() * out.element_size() if capacity is None else capacity
@@ -329,9 +330,9 @@ def compress_dcb(x: torch.Tensor, d_cb: DeviceCodebook, out: torch.Tensor, works
 def decompress_dcb(comp: torch.Tensor, comp_bytes: int, n_elems: int, d_cb: DeviceCodebook, out: torch.Tensor,
                    sizes: torch.Tensor | None = None, stream=None) -> None:
     """splitzip_decompress_dcb: splitzip_decompress with a codebook in device memory."""
-    rc = lib().fast.splitzip_decompress_dcb(comp, comp_bytes, n_elems, d_cb.dtype, d_cb.buf, out, sizes, _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_decompress_dcb(comp, comp_bytes, n_elems, d_cb.dtype, d_cb.buf, out, sizes, None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_decompress_dcb")
+        return _check(rc, "splitzip_decompress_dcb") if rc else None
     if out.numel() < n_elems or out.element_size() != _elem_size(d_cb.dtype) or not out.is_contiguous():
         raise ValueError("out must be a contiguous tensor of at least n_elems raw words")
     _check(lib().splitzip_decompress_dcb(comp.data_ptr(), comp_bytes, n_elems, d_cb.dtype, d_cb.buf.data_ptr(), out.data_ptr(),
@@ -393,9 +394,9 @@ def read_sizes(sizes: torch.Tensor):
 def compress(x: torch.Tensor, cb: Codebook, out: torch.Tensor, workspace: Workspace,
              sizes: torch.Tensor, stream=None, capacity: int | None = None) -> None:
     """splitzip_compress: x (device words) -> out (device uint8), sizes written on the stream."""
-    rc = lib().fast.splitzip_compress(x, cb.c, out, capacity, workspace.buf, workspace.nbytes, sizes, _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_compress(x, cb.c, out, capacity, workspace.buf, workspace.nbytes, sizes, None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_compress")
+        return _check(rc, "splitzip_compress") if rc else None
     n = x.numel()
     if x.element_size() != _elem_size(cb.dtype) or not x.is_contiguous():
         raise ValueError("x must be a contiguous tensor of raw words of the codebook's dtype")
@@ -463,9 +464,9 @@ def noalloc_max_elems() -> int:
 def compress_noalloc(x: torch.Tensor, cb: Codebook, out: torch.Tensor, sizes: torch.Tensor, stream=None,
                      capacity: int | None = None) -> None:
     """splitzip_compress_noalloc: splitzip_compress on the library's own per-GPU scratch array instead of a workspace."""
-    rc = lib().fast.splitzip_compress_noalloc(x, cb.c, out, capacity, sizes, _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_compress_noalloc(x, cb.c, out, capacity, sizes, None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_compress_noalloc")
+        return _check(rc, "splitzip_compress_noalloc") if rc else None
     n = x.numel()
     if x.element_size() != _elem_size(cb.dtype) or not x.is_contiguous():
         raise ValueError("x must be a contiguous tensor of raw words of the codebook's dtype")
@@ -477,9 +478,9 @@ def compress_noalloc(x: torch.Tensor, cb: Codebook, out: torch.Tensor, sizes: to
 def decompress(comp: torch.Tensor, comp_bytes: int, n_elems: int, cb: Codebook, out: torch.Tensor,
                sizes: torch.Tensor | None = None, stream=None) -> None:
     """splitzip_decompress: comp (device uint8 stream) -> out (device words)."""
-    rc = lib().fast.splitzip_decompress(comp, comp_bytes, n_elems, cb.c, out, sizes, _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_decompress(comp, comp_bytes, n_elems, cb.c, out, sizes, None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_decompress")
+        return _check(rc, "splitzip_decompress") if rc else None
     if out.numel() < n_elems or out.element_size() != _elem_size(cb.dtype) or not out.is_contiguous():
         raise ValueError("out must be a contiguous tensor of at least n_elems raw words")
     _check(lib().splitzip_decompress(comp.data_ptr(), comp_bytes, n_elems, cb.dtype, C.byref(cb.c),
@@ -515,10 +516,10 @@ class CompressBatch:
             self.items[k] = _CItem(x.data_ptr(), x.numel(), out.data_ptr(), cap, C.pointer(cb.c))
 
     def launch(self, workspace: "Workspace", sizes: torch.Tensor, stream=None) -> None:
-        rc = lib().fast.splitzip_compress_batch(self.items, self.n, self.dtype, workspace.buf, workspace.nbytes, sizes,
-                                                _handle(stream))
+        rc = (_lib or lib()).fast.splitzip_compress_batch(self.items, self.n, self.dtype, workspace.buf, workspace.nbytes, sizes,
+                                                None if stream is None else _handle(stream))
         if rc != _NOT_TAKEN:
-            return _check(rc, "splitzip_compress_batch")
+            return _check(rc, "splitzip_compress_batch") if rc else None
         _check(lib().splitzip_compress_batch(self.items, self.n, self.dtype, workspace.buf.data_ptr(), workspace.nbytes,
                                              sizes.data_ptr(), _stream_ptr(stream)), "splitzip_compress_batch")
 
@@ -539,9 +540,9 @@ class DecompressBatch:
             self.items[k] = _CDItem(c.data_ptr(), cbytes, n, out.data_ptr(), C.pointer(cb.c))
 
     def launch(self, sizes: torch.Tensor | None = None, stream=None) -> None:
-        rc = lib().fast.splitzip_decompress_batch(self.items, self.n, self.dtype, sizes, _handle(stream))
+        rc = (_lib or lib()).fast.splitzip_decompress_batch(self.items, self.n, self.dtype, sizes, None if stream is None else _handle(stream))
         if rc != _NOT_TAKEN:
-            return _check(rc, "splitzip_decompress_batch")
+            return _check(rc, "splitzip_decompress_batch") if rc else None
         _check(lib().splitzip_decompress_batch(self.items, self.n, self.dtype,
                                                sizes.data_ptr() if sizes is not None else None, _stream_ptr(stream)),
                "splitzip_decompress_batch")
@@ -579,10 +580,10 @@ class CalibrateBatchDevice:
             self.items[k] = _CItem(x.data_ptr(), x.numel(), None, 0, _null_cb())
 
     def launch(self, stream=None) -> None:
-        rc = lib().fast.splitzip_calibrate_batch_device(self.items, self.n, self.dcbs.dtype, self.dcbs.hists,
-                                                        self.dcbs.buf, _handle(stream))
+        rc = (_lib or lib()).fast.splitzip_calibrate_batch_device(self.items, self.n, self.dcbs.dtype, self.dcbs.hists,
+                                                        self.dcbs.buf, None if stream is None else _handle(stream))
         if rc != _NOT_TAKEN:
-            return _check(rc, "splitzip_calibrate_batch_device")
+            return _check(rc, "splitzip_calibrate_batch_device") if rc else None
         _check(lib().splitzip_calibrate_batch_device(self.items, self.n, self.dcbs.dtype, self.dcbs.hists.data_ptr(),
                                                      self.dcbs.buf.data_ptr(), _stream_ptr(stream)), "splitzip_calibrate_batch_device")
 
@@ -603,10 +604,10 @@ class CompressBatchDcb:
             self.items[k] = _CItem(x.data_ptr(), x.numel(), out.data_ptr(), cap, _null_cb())
 
     def launch(self, workspace: "Workspace", sizes: torch.Tensor, stream=None) -> None:
-        rc = lib().fast.splitzip_compress_batch_dcb(self.items, self.n, self.dcbs.dtype, self.dcbs.buf, workspace.buf,
-                                                    workspace.nbytes, sizes, _handle(stream))
+        rc = (_lib or lib()).fast.splitzip_compress_batch_dcb(self.items, self.n, self.dcbs.dtype, self.dcbs.buf, workspace.buf,
+                                                    workspace.nbytes, sizes, None if stream is None else _handle(stream))
         if rc != _NOT_TAKEN:
-            return _check(rc, "splitzip_compress_batch_dcb")
+            return _check(rc, "splitzip_compress_batch_dcb") if rc else None
         _check(lib().splitzip_compress_batch_dcb(self.items, self.n, self.dcbs.dtype, self.dcbs.buf.data_ptr(),
                                                  workspace.buf.data_ptr(), workspace.nbytes, sizes.data_ptr(),
                                                  _stream_ptr(stream)), "splitzip_compress_batch_dcb")
@@ -627,10 +628,10 @@ class DecompressBatchDcb:
             self.items[k] = _CDItem(c.data_ptr(), cbytes, n, out.data_ptr(), _null_cb())
 
     def launch(self, sizes: torch.Tensor | None = None, stream=None) -> None:
-        rc = lib().fast.splitzip_decompress_batch_dcb(self.items, self.n, self.dcbs.dtype, self.dcbs.buf, sizes,
-                                                      _handle(stream))
+        rc = (_lib or lib()).fast.splitzip_decompress_batch_dcb(self.items, self.n, self.dcbs.dtype, self.dcbs.buf, sizes,
+                                                      None if stream is None else _handle(stream))
         if rc != _NOT_TAKEN:
-            return _check(rc, "splitzip_decompress_batch_dcb")
+            return _check(rc, "splitzip_decompress_batch_dcb") if rc else None
         _check(lib().splitzip_decompress_batch_dcb(self.items, self.n, self.dcbs.dtype, self.dcbs.buf.data_ptr(),
                                                    sizes.data_ptr() if sizes is not None else None, _stream_ptr(stream)),
                "splitzip_decompress_batch_dcb")
@@ -639,9 +640,9 @@ class DecompressBatchDcb:
 def decompress_own(comp: torch.Tensor, comp_bytes: int, n_elems: int, dtype: int, out: torch.Tensor,
                    sizes: torch.Tensor | None = None, stream=None) -> None:
     """splitzip_decompress_own: decompress with the codebook the stream carries in its header."""
-    rc = lib().fast.splitzip_decompress_own(comp, comp_bytes, n_elems, dtype, out, sizes, _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_decompress_own(comp, comp_bytes, n_elems, dtype, out, sizes, None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_decompress_own")
+        return _check(rc, "splitzip_decompress_own") if rc else None
     if out.numel() < n_elems or out.element_size() != _elem_size(dtype) or not out.is_contiguous():
         raise ValueError("out must be a contiguous tensor of at least n_elems raw words of the dtype")
     _check(lib().splitzip_decompress_own(comp.data_ptr(), comp_bytes, n_elems, dtype, out.data_ptr(),
@@ -664,9 +665,9 @@ class DecompressBatchOwn:
             self.items[k] = _CDItem(c.data_ptr(), cbytes, n, out.data_ptr(), _null_cb())
 
     def launch(self, sizes: torch.Tensor | None = None, stream=None) -> None:
-        rc = lib().fast.splitzip_decompress_batch_own(self.items, self.n, self.dtype, sizes, _handle(stream))
+        rc = (_lib or lib()).fast.splitzip_decompress_batch_own(self.items, self.n, self.dtype, sizes, None if stream is None else _handle(stream))
         if rc != _NOT_TAKEN:
-            return _check(rc, "splitzip_decompress_batch_own")
+            return _check(rc, "splitzip_decompress_batch_own") if rc else None
         _check(lib().splitzip_decompress_batch_own(self.items, self.n, self.dtype,
                                                    sizes.data_ptr() if sizes is not None else None, _stream_ptr(stream)),
                "splitzip_decompress_batch_own")
@@ -742,9 +743,9 @@ def variant_codebook_from_dec(dec, v: Variant) -> Codebook:
 def variant_compress(x: torch.Tensor, v: Variant, cb: Codebook, out: torch.Tensor, workspace: torch.Tensor,
                      sizes: torch.Tensor, stream=None, capacity: int | None = None) -> None:
     """splitzip_variant_compress; workspace is a device uint8 tensor of variant_workspace_bytes."""
-    rc = lib().fast.splitzip_variant_compress(x, v, cb.c, out, capacity, workspace, None, sizes, _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_variant_compress(x, v, cb.c, out, capacity, workspace, None, sizes, None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_variant_compress")
+        return _check(rc, "splitzip_variant_compress") if rc else None
     if x.element_size() != _elem_size(v.dtype) or not x.is_contiguous():
         raise ValueError("x must be a contiguous tensor of raw words of the variant's dtype")
     cap = out.numel() * out.element_size() if capacity is None else capacity
@@ -755,9 +756,9 @@ def variant_compress(x: torch.Tensor, v: Variant, cb: Codebook, out: torch.Tenso
 
 def variant_decompress(comp: torch.Tensor, comp_bytes: int, n_elems: int, v: Variant, cb: Codebook, out: torch.Tensor,
                        sizes: torch.Tensor | None = None, stream=None) -> None:
-    rc = lib().fast.splitzip_variant_decompress(comp, comp_bytes, n_elems, v, cb.c, out, sizes, _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_variant_decompress(comp, comp_bytes, n_elems, v, cb.c, out, sizes, None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_variant_decompress")
+        return _check(rc, "splitzip_variant_decompress") if rc else None
     if out.numel() < n_elems or out.element_size() != _elem_size(v.dtype) or not out.is_contiguous():
         raise ValueError("out must be a contiguous tensor of at least n_elems raw words")
     _check(lib().splitzip_variant_decompress(comp.data_ptr(), comp_bytes, n_elems, C.byref(v), C.byref(cb.c),
@@ -786,10 +787,10 @@ class Paged:
 
 def compress_paged(src: Paged, n_elems: int, cb: Codebook, out: torch.Tensor, workspace: Workspace,
                    sizes: torch.Tensor, stream=None, capacity: int | None = None) -> None:
-    rc = lib().fast.splitzip_compress_paged(src.c, n_elems, cb.c, out, capacity, workspace.buf, workspace.nbytes, sizes,
-                                            _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_compress_paged(src.c, n_elems, cb.c, out, capacity, workspace.buf, workspace.nbytes, sizes,
+                                            None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_compress_paged")
+        return _check(rc, "splitzip_compress_paged") if rc else None
     cap = out.numel() * out.element_size() if capacity is None else capacity
     _check(lib().splitzip_compress_paged(C.byref(src.c), n_elems, cb.dtype, C.byref(cb.c), out.data_ptr(), cap,
                                          workspace.buf.data_ptr(), workspace.nbytes, sizes.data_ptr(),
@@ -798,9 +799,9 @@ def compress_paged(src: Paged, n_elems: int, cb: Codebook, out: torch.Tensor, wo
 
 def decompress_paged(comp: torch.Tensor, comp_bytes: int, n_elems: int, cb: Codebook, dst: Paged,
                      sizes: torch.Tensor | None = None, stream=None) -> None:
-    rc = lib().fast.splitzip_decompress_paged(comp, comp_bytes, n_elems, cb.c, dst.c, sizes, _handle(stream))
+    rc = (_lib or lib()).fast.splitzip_decompress_paged(comp, comp_bytes, n_elems, cb.c, dst.c, sizes, None if stream is None else _handle(stream))
     if rc != _NOT_TAKEN:
-        return _check(rc, "splitzip_decompress_paged")
+        return _check(rc, "splitzip_decompress_paged") if rc else None
     _check(lib().splitzip_decompress_paged(comp.data_ptr(), comp_bytes, n_elems, cb.dtype, C.byref(cb.c),
                                            C.byref(dst.c), sizes.data_ptr() if sizes is not None else None,
                                            _stream_ptr(stream)), "splitzip_decompress_paged")
@@ -824,10 +825,10 @@ class CompressBatchPaged:
             self.items[k] = _CItem(pool.data_ptr(), n, out.data_ptr(), cap, C.pointer(cb.c))
 
     def launch(self, workspace: "Workspace", sizes: torch.Tensor, stream=None) -> None:
-        rc = lib().fast.splitzip_compress_batch_paged(self.items, self.n, self.dtype, self.paging.c, workspace.buf,
-                                                      workspace.nbytes, sizes, _handle(stream))
+        rc = (_lib or lib()).fast.splitzip_compress_batch_paged(self.items, self.n, self.dtype, self.paging.c, workspace.buf,
+                                                      workspace.nbytes, sizes, None if stream is None else _handle(stream))
         if rc != _NOT_TAKEN:
-            return _check(rc, "splitzip_compress_batch_paged")
+            return _check(rc, "splitzip_compress_batch_paged") if rc else None
         _check(lib().splitzip_compress_batch_paged(self.items, self.n, self.dtype, C.byref(self.paging.c),
                                                    workspace.buf.data_ptr(), workspace.nbytes, sizes.data_ptr(),
                                                    _stream_ptr(stream)), "splitzip_compress_batch_paged")
@@ -848,10 +849,10 @@ class DecompressBatchPaged:
             self.items[k] = _CDItem(c.data_ptr(), cbytes, n, pool.data_ptr(), C.pointer(cb.c))
 
     def launch(self, sizes: torch.Tensor | None = None, stream=None) -> None:
-        rc = lib().fast.splitzip_decompress_batch_paged(self.items, self.n, self.dtype, self.paging.c, sizes,
-                                                        _handle(stream))
+        rc = (_lib or lib()).fast.splitzip_decompress_batch_paged(self.items, self.n, self.dtype, self.paging.c, sizes,
+                                                        None if stream is None else _handle(stream))
         if rc != _NOT_TAKEN:
-            return _check(rc, "splitzip_decompress_batch_paged")
+            return _check(rc, "splitzip_decompress_batch_paged") if rc else None
         _check(lib().splitzip_decompress_batch_paged(self.items, self.n, self.dtype, C.byref(self.paging.c),
                                                      sizes.data_ptr() if sizes is not None else None, _stream_ptr(stream)),
                "splitzip_decompress_batch_paged")

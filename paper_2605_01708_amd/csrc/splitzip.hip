@@ -462,6 +462,7 @@ int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip
     sa.short_words = reinterpret_cast<uint64_t*>(a.slots);
     sa.tag = next_call_tag();
     sa.looks = short_looks();
+    sa.tiles = grid;
     SPLITZIP_V_DISPATCH3(v_short_kernel, a, dim3(grid), dim3(kThreads), st, sa);
     if (a.val_bits != 8) launch_v_pack(n_elems, st, a);
     return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
@@ -846,10 +847,18 @@ template <typename Once>
 CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_t n_max, int dtype, uint64_t status_bytes, const Once& once) {
   CompressPlan p;
   memset(&p, 0, sizeof p);
-  // as many of the next tensors (tensors_of_launch at most) as find room for their counts in the status area; all of them share
+  const uint32_t k_most = tensors_of_launch(items, n_items);
+  p.short_each = g_hooks.any() || g_hooks.short_looks.load() == kNoShort ? 0u : short_each(items, k_most, status_bytes, &p.tiles_max);
+  if (p.short_each && once()) {
+    p.k = k_most;
+    p.cpt = 1;
+    return p;
+  }
+  p.short_each = 0;
+  p.tiles_max = 0;
+  // as many of the next tensors as find room for their counts in the status area; all of them share
   // the tile size of the one that needs the largest
   const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
-  const uint32_t k_most = tensors_of_launch(items, n_items);
   uint64_t chunks_all = 0, chunks_max = 0;
   for (uint32_t q = 0; q < k_most; ++q) {
     const uint64_t c = chunks_of(items[q].n_elems);
@@ -875,15 +884,6 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
     if (tiles > p.tiles_max) p.tiles_max = tiles;
   }
   p.small = chunks_of(n_max) <= (dtype == SPLITZIP_BF16 ? Bf16::kSmallChunks : E5m2::kSmallChunks) && !g_hooks.any();
-  uint64_t short_max = 0;
-  p.short_each = g_hooks.any() || g_hooks.short_looks.load() == kNoShort ? 0u : short_each(items, p.k, status_bytes, &short_max);
-  if (p.short_each && !once()) p.short_each = 0;
-  if (p.short_each) {
-    p.small = false;
-    p.cpt = 1;
-    p.tiles_max = short_max;
-    return p;
-  }
   // Launches of 2048 tiles and more take them in xcd_order, and BF16 from 6144 on with fewer workgroups per CU (Bf16::kTileLdsPad).  us per call,
   // in the order of the tiles, in xcd_order and, BF16, in it with fewer workgroups: BF16 10.93 / 10.78 / 11.40 (2048 tiles: 16 tensors of 512
   // chunks), 15.70 / 15.68 / 16.14 (4096 of one chunk per wave), 25.46 / 25.27 / 25.53 (4095), 25.07 / 25.02 / 25.28 (4096: one tensor), 34.31 /
@@ -893,8 +893,8 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   // take longer to pass by that way (BF16, one tensor of 13 000 chunks beside 63 of two: 35.1 and 40.6; 16 of 8192
   // beside 48 of 16: 91.5 and 95.6; but 32 of 16 384 beside 32 of 16: 328 and 321).
   p.by_xcd = tiles_all >= 2048 && p.tiles_max * p.k <= 2 * tiles_all;
-  p.lds_pad = p.by_xcd && dtype == SPLITZIP_BF16 && (tiles_all >= 6144 || g_hooks.xcd.load() == 2) ? Bf16::kTileLdsPad : 0u;
   if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2;
+  p.lds_pad = p.by_xcd && dtype == SPLITZIP_BF16 && (tiles_all >= 6144 || g_hooks.xcd.load() == 2) ? Bf16::kTileLdsPad : 0u;
   // Launches that memory alone bounds store through the L2 (kTileLong).  us per call, without and with:
   // BF16 21.0 and 21.2 (3072 tiles), 25.6 and 25.7 (4096), 35.05 and 34.98 (6144), 82.2 and 80.9 (16 384), 158.2 and
   // 155.8 (32 768), 563 and 561 (122 880); E5M2 11.9 and 12.3 (2048), 17.6 and 17.7 (4096), 23.19 and 23.06 (6144),

@@ -637,7 +637,8 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs args) {
 }
 
 // Short calls (splitzip_variant_compress): the passes above in one launch, as in compress_short_kernel, a block per wave.
-// short_words: where the workgroups' words lie (the blocks' slots, which nothing is staged in here); tag, looks: as there.
+// short_words: where the workgroups' words lie (the blocks' slots, which nothing is staged in here); tag, looks: as there; tiles: the
+// launch's workgroups (asked for as gridDim, a launch has 256 bytes more of arguments).
 // us per call, two launches and this: BF16 top-8 7.8 and 4.45 (4 blocks), 8.0 and 5.2 (100), 8.2 and 5.6 (1000), 8.7 and 6.35 (2000), sentinels
 // 7.8 and 4.8 (100), 8.1 and 5.5 (2000); E5M2 7.8 and 4.9, 7.9 and 5.5, with narrow values, which v_pack_kernel still packs, 11.7 and 8.3, 12.0
 // and 9.4; random words, BF16 top-8, 1000 blocks 28.2 and 9.0.  Beyond 2048 blocks the words that every workgroup looks at cost more
@@ -646,7 +647,7 @@ struct VShortArgs {
   VArgs a;
   uint64_t* short_words;
   uint64_t tag;
-  uint32_t looks;
+  uint32_t looks, tiles;
 };
 constexpr int kVShortEach = 2;
 template <int DT, int CB>
@@ -661,7 +662,7 @@ __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args
   const VArgs a = v_args_arrived(args.a);
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-  ShortCounts<kVShortEach> counts(args.short_words, args.tag, gridDim.x, blockIdx.x);
+  ShortCounts<kVShortEach> counts(args.short_words, args.tag, args.tiles, blockIdx.x);
   uint32_t blk = 0, count = 0, tot[2], low[2];   // the wave's block and its escapes
   uint32_t in_tile = 0, total = 0;               // escapes of the tile before the wave's block; all of them
   auto encode = [&](uint32_t tile, bool build) {
