@@ -140,51 +140,58 @@ __device__ inline void load_chunk_bf16(const Planes& a, const uint8_t* cptr, uin
   }
 }
 
-// One chunk by one wave, its words in w: dense transform, (optionally) plane stores, escape
-// ranks inside the chunk, escape records into `sink` starting at rank `base`.
-// Returns the chunk's escape count (wave-uniform).
-template <bool FULL, bool STORE, bool LONG, typename Sink>
-__device__ inline uint32_t process_chunk_bf16(const Planes& a, const uint16_t* lut, uint32_t* park,
-                                              uint64_t cbase, int lane, const uint32_t (&w)[2][4], uint32_t base,
-                                              const Sink& sink) {
-  uint32_t F[2];
+// One chunk's planes and escapes, as a wave holds them: the lane's 8 elements of each half-chunk
+struct CodedBf16 {
+  u32x2 sm[2];
+  uint32_t code[2], F[2];     // nibbles; F: 1 for an escape
+  uint32_t excl[2], tot0;     // escapes of the lanes below, per half; all of the first half
+};
+// One chunk by one wave, its words in w, in four steps: dense transform; planes out; escapes per lane and half, ranked over the
+// wave (the chunk's count, wave-uniform, is returned); escape records into `sink` from rank `base` on, in element order:
+// half, lane, element.
+template <bool FULL>
+__device__ inline void encode_chunk_bf16(const Planes& a, const uint16_t* lut, uint64_t cbase, int lane, const uint32_t (&w)[2][4], CodedBf16& c) {
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const uint64_t g0 = cbase + h * kHalf + lane * 8;
-    u32x2 sm;
-    uint32_t code;
-    encode8_bf16(w[h], lut, sm, code, F[h]);
+    encode8_bf16(w[h], lut, c.sm[h], c.code[h], c.F[h]);
     if (!FULL) {
+      const uint64_t g0 = cbase + h * kHalf + lane * 8;
       const uint32_t nvalid = g0 >= a.n ? 0u : (uint32_t)(a.n - g0 < 8 ? a.n - g0 : 8);
       // elements past N contribute zero nibbles (their sm bytes are already 0)
       const uint32_t keep = nvalid == 8 ? ~0u : ((1u << (4 * nvalid)) - 1u);
-      code &= keep;
-      F[h] &= keep;
-    }
-    if (STORE) {
-      // Sections are padded to 256 bytes and a lane's group never straddles the padded end, so
-      // whole-group stores also write the zero padding.
-      if (FULL && LONG) {
-        st_run(run_of(a.out + a.off_sm + cbase, kChunk), 8u * (uint32_t)(h * 64 + lane), sm);
-        st_run(run_of(a.out + a.off_code + (cbase >> 1), kChunk / 2), 4u * (uint32_t)(h * 64 + lane), code);
-      } else if (FULL) {
-        st_stream(reinterpret_cast<u32x2*>(a.out + a.off_sm + cbase) + (uint32_t)(h * 64 + lane), sm);
-        st_stream(reinterpret_cast<uint32_t*>(a.out + a.off_code + (cbase >> 1)) + (uint32_t)(h * 64 + lane), code);
-      } else {
-        if (g0 < a256(a.sm_bytes)) st_stream(reinterpret_cast<u32x2*>(a.out + a.off_sm + g0), sm);
-        if ((g0 >> 1) < a256(a.code_bytes)) st_stream(reinterpret_cast<uint32_t*>(a.out + a.off_code + (g0 >> 1)), code);
-      }
+      c.code[h] &= keep;
+      c.F[h] &= keep;
     }
   }
-  // escapes per lane and half, ranked over the wave; element order inside the chunk: half, lane, element
-  uint32_t excl0, excl1;
-  const uint32_t tot0 = wave_sparse_excl(__popc(F[0]), excl0), tot1 = wave_sparse_excl(__popc(F[1]), excl1);
-  const uint32_t total = tot0 + tot1;
-  if (total) {
-    emit_half_bf16(park, w[0], F[0], base + excl0, lane * 8, sink);
-    emit_half_bf16(park, w[1], F[1], base + tot0 + excl1, kHalf + lane * 8, sink);
+}
+__device__ inline uint32_t count_chunk_bf16(CodedBf16& c) {
+  c.tot0 = wave_sparse_excl(__popc(c.F[0]), c.excl[0]);
+  return c.tot0 + wave_sparse_excl(__popc(c.F[1]), c.excl[1]);
+}
+template <bool FULL, bool LONG>
+__device__ inline void store_chunk_bf16(const Planes& a, uint64_t cbase, int lane, const CodedBf16& c) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint64_t g0 = cbase + h * kHalf + lane * 8;
+    // Sections are padded to 256 bytes and a lane's group never straddles the padded end, so
+    // whole-group stores also write the zero padding.
+    if (FULL && LONG) {
+      st_run(run_of(a.out + a.off_sm + cbase, kChunk), 8u * (uint32_t)(h * 64 + lane), c.sm[h]);
+      st_run(run_of(a.out + a.off_code + (cbase >> 1), kChunk / 2), 4u * (uint32_t)(h * 64 + lane), c.code[h]);
+    } else if (FULL) {
+      st_stream(reinterpret_cast<u32x2*>(a.out + a.off_sm + cbase) + (uint32_t)(h * 64 + lane), c.sm[h]);
+      st_stream(reinterpret_cast<uint32_t*>(a.out + a.off_code + (cbase >> 1)) + (uint32_t)(h * 64 + lane), c.code[h]);
+    } else {
+      if (g0 < a256(a.sm_bytes)) st_stream(reinterpret_cast<u32x2*>(a.out + a.off_sm + g0), c.sm[h]);
+      if ((g0 >> 1) < a256(a.code_bytes)) st_stream(reinterpret_cast<uint32_t*>(a.out + a.off_code + (g0 >> 1)), c.code[h]);
+    }
   }
-  return total;
+}
+template <typename Sink>
+__device__ inline void emit_chunk_bf16(uint32_t* park, int lane, const uint32_t (&w)[2][4], const CodedBf16& c, uint32_t total, uint32_t base, const Sink& sink) {
+  if (!total) return;
+  emit_half_bf16(park, w[0], c.F[0], base + c.excl[0], lane * 8, sink);
+  emit_half_bf16(park, w[1], c.F[1], base + c.tot0 + c.excl[1], kHalf + lane * 8, sink);
 }
 
 // ---- FP8 E5M2 (appendix "SplitZip on FP8"): byte = s eeeee mm, e = (x >> 2) & 31, a = s m1 m0 ----
@@ -229,11 +236,14 @@ __device__ inline void load_chunk_e5m2(const Planes& a, const uint8_t* cptr, uin
   }
 }
 
-template <bool FULL, bool STORE, bool LONG, typename Sink>
-__device__ inline uint32_t process_chunk_e5m2(const Planes& a, const uint16_t* lut, uint32_t* park,
-                                              uint64_t cbase, int lane, const uint32_t (&w)[4], uint32_t base,
-                                              const Sink& sink) {
-  const uint64_t g0 = cbase + lane * 16;
+struct CodedE5m2 {
+  uint32_t lo, hi;            // the lane's 48 plane bits: lo holds bits 0..31, hi bits 32..47
+  uint32_t code[2], F[2];
+  uint32_t mine, excl;        // escapes of the lane, of the lanes below
+};
+// the four steps of a chunk, as for BF16; element order inside the chunk: lane, element
+template <bool FULL>
+__device__ inline void encode_chunk_e5m2(const Planes& a, const uint16_t* lut, uint64_t cbase, int lane, const uint32_t (&w)[4], CodedE5m2& c) {
   uint32_t r[4], u[8];
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
@@ -248,78 +258,84 @@ __device__ inline uint32_t process_chunk_e5m2(const Planes& a, const uint16_t* l
     u[2 * d] = t0 + (t1 << 4);
     u[2 * d + 1] = t2 + (t3 << 4);
   }
-  // the lane's 48 plane bits: lo holds bits 0..31, hi bits 32..47
-  uint32_t lo = r[0] | (r[1] << 12) | (r[2] << 24), hi = (r[2] >> 8) | (r[3] << 4);
-  uint32_t code[2], F[2];
+  c.lo = r[0] | (r[1] << 12) | (r[2] << 24);
+  c.hi = (r[2] >> 8) | (r[3] << 4);
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const uint32_t x01 = byte_perm(u[4 * q + 1], u[4 * q], 0x05010400u), x23 = byte_perm(u[4 * q + 3], u[4 * q + 2], 0x05010400u);
-    code[q] = byte_perm(x23, x01, 0x05040100u);
-    F[q] = byte_perm(x23, x01, 0x07060302u);
+    c.code[q] = byte_perm(x23, x01, 0x05040100u);
+    c.F[q] = byte_perm(x23, x01, 0x07060302u);
+    asm volatile("" : "+v"(c.F[q]));   // made once: the compiler would make it again where it is counted and where it is used (1 to 2 % of a call)
   }
   if (!FULL) {
     // elements past N contribute zero nibbles (their plane bits are already 0)
+    const uint64_t g0 = cbase + lane * 16;
     const uint32_t nvalid = g0 >= a.n ? 0u : (uint32_t)(a.n - g0 < 16 ? a.n - g0 : 16);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const uint32_t nv = nvalid > (uint32_t)(8 * q) ? nvalid - 8 * q : 0u;
       const uint32_t keep = nv >= 8 ? ~0u : ((1u << (4 * nv)) - 1u);
-      code[q] &= keep;
-      F[q] &= keep;
+      c.code[q] &= keep;
+      c.F[q] &= keep;
     }
   }
-  if (STORE) {
-    // plane bytes of this lane pair: [12 p, 12 p + 12) of the chunk's 384
-    // quad_perm [1,1,3,3]: the odd neighbour's bits
-    // (a quad permute reads lanes of its own quad only: every lane gets a value, the old one is never kept)
-    const uint32_t lo_up = __builtin_amdgcn_mov_dpp(lo, 0xF5, 0xf, 0xf, false);
-    const uint32_t hi_up = __builtin_amdgcn_mov_dpp(hi, 0xF5, 0xf, 0xf, false);
-    const uint64_t sm_chunk = (uint64_t)(uint32_t)(cbase >> 10) * 384u;   // the chunk's plane bytes start here: a scalar product
-    const uint64_t sm_off = sm_chunk + (uint32_t)(lane >> 1) * 12;
-    uint8_t* sm_chunk_ptr = a.out + a.off_sm + sm_chunk;
-    uint8_t* sm_dst = sm_chunk_ptr + (uint32_t)(lane >> 1) * 12;
-    // the pair's 12 bytes, all in the even lane
-    uint32_t d0 = lo, d1 = (hi & 0xffffu) | (lo_up << 16), d2 = (lo_up >> 16) | (hi_up << 16);
-    if (FULL) {
-      // Both lanes of a pair write the pair's 12 bytes (quad_perm [0,0,2,2]: the even neighbour's bits): one
-      // instruction writes the chunk's 384 bytes back to back, and it is issued whatever the lane -- so the
-      // compiler can count on it when it works out how long a wave must wait for the loads issued before it.
-      const uint32_t lo_dn = __builtin_amdgcn_mov_dpp(lo, 0xA0, 0xf, 0xf, false);
-      const uint32_t hi_dn = __builtin_amdgcn_mov_dpp(hi, 0xA0, 0xf, 0xf, false);
-      d0 = lo_dn; d1 = (hi_dn & 0xffffu) | (lo_up << 16);
-      if (LONG) {
-        st_run(run_of(sm_chunk_ptr, 3 * kChunk / 8), (uint32_t)(lane >> 1) * 12u, u32x3{d0, d1, d2});
-        st_run(run_of(a.out + a.off_code + (cbase >> 1), kChunk / 2), 8u * (uint32_t)lane, u32x2{code[0], code[1]});
-      } else {
-        st_stream(reinterpret_cast<u32x3*>(sm_dst), u32x3{d0, d1, d2});
-        st_stream(reinterpret_cast<u32x2*>(a.out + a.off_code + (cbase >> 1)) + (uint32_t)lane, u32x2{code[0], code[1]});
-      }
+}
+__device__ inline uint32_t count_chunk_e5m2(CodedE5m2& c) {
+  c.mine = __popc(c.F[0]) + __popc(c.F[1]);
+  return wave_sparse_excl(c.mine, c.excl);
+}
+template <bool FULL, bool LONG>
+__device__ inline void store_chunk_e5m2(const Planes& a, uint64_t cbase, int lane, const CodedE5m2& c) {
+  const uint64_t g0 = cbase + lane * 16;
+  // plane bytes of this lane pair: [12 p, 12 p + 12) of the chunk's 384
+  // quad_perm [1,1,3,3]: the odd neighbour's bits
+  // (a quad permute reads lanes of its own quad only: every lane gets a value, the old one is never kept)
+  const uint32_t lo_up = __builtin_amdgcn_mov_dpp(c.lo, 0xF5, 0xf, 0xf, false);
+  const uint32_t hi_up = __builtin_amdgcn_mov_dpp(c.hi, 0xF5, 0xf, 0xf, false);
+  const uint64_t sm_chunk = (uint64_t)(uint32_t)(cbase >> 10) * 384u;   // the chunk's plane bytes start here: a scalar product
+  const uint64_t sm_off = sm_chunk + (uint32_t)(lane >> 1) * 12;
+  uint8_t* sm_chunk_ptr = a.out + a.off_sm + sm_chunk;
+  uint8_t* sm_dst = sm_chunk_ptr + (uint32_t)(lane >> 1) * 12;
+  // the pair's 12 bytes, all in the even lane
+  uint32_t d0 = c.lo, d1 = (c.hi & 0xffffu) | (lo_up << 16), d2 = (lo_up >> 16) | (hi_up << 16);
+  if (FULL) {
+    // Both lanes of a pair write the pair's 12 bytes (quad_perm [0,0,2,2]: the even neighbour's bits): one
+    // instruction writes the chunk's 384 bytes back to back, and it is issued whatever the lane -- so the
+    // compiler can count on it when it works out how long a wave must wait for the loads issued before it.
+    const uint32_t lo_dn = __builtin_amdgcn_mov_dpp(c.lo, 0xA0, 0xf, 0xf, false);
+    const uint32_t hi_dn = __builtin_amdgcn_mov_dpp(c.hi, 0xA0, 0xf, 0xf, false);
+    d0 = lo_dn; d1 = (hi_dn & 0xffffu) | (lo_up << 16);
+    if (LONG) {
+      st_run(run_of(sm_chunk_ptr, 3 * kChunk / 8), (uint32_t)(lane >> 1) * 12u, u32x3{d0, d1, d2});
+      st_run(run_of(a.out + a.off_code + (cbase >> 1), kChunk / 2), 8u * (uint32_t)lane, u32x2{c.code[0], c.code[1]});
     } else {
-      // dword by dword up to the padded end of each plane; the pad can reach 128 bytes past the
-      // chunk's own 384 plane bytes
-      const uint64_t sm_end = a256(a.sm_bytes);
-      if (!(lane & 1)) {
-        if (sm_off < sm_end) *reinterpret_cast<uint32_t*>(sm_dst) = d0;
-        if (sm_off + 4 < sm_end) *reinterpret_cast<uint32_t*>(sm_dst + 4) = d1;
-        if (sm_off + 8 < sm_end) *reinterpret_cast<uint32_t*>(sm_dst + 8) = d2;
-      }
-      const uint64_t past = sm_chunk + 384 + 4 * (uint32_t)lane;
-      if (lane < 32 && past < sm_end) *reinterpret_cast<uint32_t*>(a.out + a.off_sm + past) = 0;
-      if ((g0 >> 1) < a256(a.code_bytes))
-        *reinterpret_cast<u32x2*>(a.out + a.off_code + (g0 >> 1)) = u32x2{code[0], code[1]};
+      st_stream(reinterpret_cast<u32x3*>(sm_dst), u32x3{d0, d1, d2});
+      st_stream(reinterpret_cast<u32x2*>(a.out + a.off_code + (cbase >> 1)) + (uint32_t)lane, u32x2{c.code[0], c.code[1]});
     }
+  } else {
+    // dword by dword up to the padded end of each plane; the pad can reach 128 bytes past the
+    // chunk's own 384 plane bytes
+    const uint64_t sm_end = a256(a.sm_bytes);
+    if (!(lane & 1)) {
+      if (sm_off < sm_end) *reinterpret_cast<uint32_t*>(sm_dst) = d0;
+      if (sm_off + 4 < sm_end) *reinterpret_cast<uint32_t*>(sm_dst + 4) = d1;
+      if (sm_off + 8 < sm_end) *reinterpret_cast<uint32_t*>(sm_dst + 8) = d2;
+    }
+    const uint64_t past = sm_chunk + 384 + 4 * (uint32_t)lane;
+    if (lane < 32 && past < sm_end) *reinterpret_cast<uint32_t*>(a.out + a.off_sm + past) = 0;
+    if ((g0 >> 1) < a256(a.code_bytes))
+      *reinterpret_cast<u32x2*>(a.out + a.off_code + (g0 >> 1)) = u32x2{c.code[0], c.code[1]};
   }
-  const uint32_t mine = __popc(F[0]) + __popc(F[1]);
-  uint32_t excl;
-  const uint32_t total = wave_sparse_excl(mine, excl);
-  if (total && mine) {
-    // element order inside the chunk: lane, element
+}
+template <typename Sink>
+__device__ inline void emit_chunk_e5m2(uint32_t* park, int lane, const uint32_t (&w)[4], const CodedE5m2& c, uint32_t total, uint32_t base, const Sink& sink) {
+  if (total && c.mine) {
     *reinterpret_cast<u32x4*>(park) = u32x4{w[0], w[1], w[2], w[3]};
     const uint8_t* x = reinterpret_cast<const uint8_t*>(park);
-    uint32_t rr = base + excl;
+    uint32_t rr = base + c.excl;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      uint32_t m = F[q];
+      uint32_t m = c.F[q];
       while (m) {
         const uint32_t jj = 8 * q + ((uint32_t)(__ffs(m) - 1) >> 2);
         m &= m - 1;
@@ -328,7 +344,6 @@ __device__ inline uint32_t process_chunk_e5m2(const Planes& a, const uint16_t* l
       }
     }
   }
-  return total;
 }
 
 // the two formats as seen by the compress kernel
@@ -356,11 +371,14 @@ struct Bf16 {
   __device__ static inline bool full(const Planes& a, uint64_t cbase) { return cbase + kChunk <= a.n; }
   template <bool FULL, bool LONG = false>
   __device__ static inline void load(const Planes& a, const uint8_t* cptr, uint64_t cbase, int lane, Regs& r) { load_chunk_bf16<FULL, LONG>(a, cptr, cbase, lane, r.w); }
-  template <bool FULL, bool STORE, bool LONG = false, typename Sink>
-  __device__ static inline uint32_t process(const Planes& a, const uint16_t* lut, uint32_t* park, uint64_t cbase,
-                                            int lane, const Regs& r, uint32_t base, const Sink& sink) {
-    return process_chunk_bf16<FULL, STORE, LONG>(a, lut, park, cbase, lane, r.w, base, sink);
-  }
+  typedef CodedBf16 Coded;
+  template <bool FULL>
+  __device__ static inline void encode(const Planes& a, const uint16_t* lut, uint64_t cbase, int lane, const Regs& r, Coded& c) { encode_chunk_bf16<FULL>(a, lut, cbase, lane, r.w, c); }
+  __device__ static inline uint32_t count(Coded& c) { return count_chunk_bf16(c); }
+  template <bool FULL, bool LONG = false>
+  __device__ static inline void store(const Planes& a, uint64_t cbase, int lane, const Coded& c) { store_chunk_bf16<FULL, LONG>(a, cbase, lane, c); }
+  template <typename Sink>
+  __device__ static inline void emit(uint32_t* park, int lane, const Regs& r, const Coded& c, uint32_t total, uint32_t base, const Sink& sink) { emit_chunk_bf16(park, lane, r.w, c, total, base, sink); }
 };
 struct E5m2 {
   static constexpr int DT = SPLITZIP_FP8_E5M2;
@@ -381,12 +399,27 @@ struct E5m2 {
   __device__ static inline bool full(const Planes& a, uint64_t cbase) { return cbase + kChunk < a.n; }
   template <bool FULL, bool LONG = false>
   __device__ static inline void load(const Planes& a, const uint8_t* cptr, uint64_t cbase, int lane, Regs& r) { load_chunk_e5m2<FULL, LONG>(a, cptr, cbase, lane, r.w); }
-  template <bool FULL, bool STORE, bool LONG = false, typename Sink>
-  __device__ static inline uint32_t process(const Planes& a, const uint16_t* lut, uint32_t* park, uint64_t cbase,
-                                            int lane, const Regs& r, uint32_t base, const Sink& sink) {
-    return process_chunk_e5m2<FULL, STORE, LONG>(a, lut, park, cbase, lane, r.w, base, sink);
-  }
+  typedef CodedE5m2 Coded;
+  template <bool FULL>
+  __device__ static inline void encode(const Planes& a, const uint16_t* lut, uint64_t cbase, int lane, const Regs& r, Coded& c) { encode_chunk_e5m2<FULL>(a, lut, cbase, lane, r.w, c); }
+  __device__ static inline uint32_t count(Coded& c) { return count_chunk_e5m2(c); }
+  template <bool FULL, bool LONG = false>
+  __device__ static inline void store(const Planes& a, uint64_t cbase, int lane, const Coded& c) { store_chunk_e5m2<FULL, LONG>(a, cbase, lane, c); }
+  template <typename Sink>
+  __device__ static inline void emit(uint32_t* park, int lane, const Regs& r, const Coded& c, uint32_t total, uint32_t base, const Sink& sink) { emit_chunk_e5m2(park, lane, r.w, c, total, base, sink); }
 };
+
+// The steps of a chunk one after the other (planes out only if STORE): its escape count, wave-uniform.
+template <typename F, bool FULL, bool STORE, bool LONG = false, typename Sink>
+__device__ inline uint32_t process_chunk(const Planes& a, const uint16_t* lut, uint32_t* park, uint64_t cbase, int lane,
+                                         const typename F::Regs& r, uint32_t base, const Sink& sink) {
+  typename F::Coded c;
+  F::template encode<FULL>(a, lut, cbase, lane, r, c);
+  if (STORE) F::template store<FULL, LONG>(a, cbase, lane, c);
+  const uint32_t total = F::count(c);
+  F::emit(park, lane, r, c, total, base, sink);
+  return total;
+}
 
 // header, sizes record and the zero padding behind the positions: one wave, once M is known
 __device__ void compress_write_trailer(const Planes& a, const u32x4& dec, splitzip_sizes* sizes, uint32_t M,
@@ -606,7 +639,7 @@ __global__ __launch_bounds__(kTileThreads) void compress_tile_kernel(const TileA
 #pragma unroll
       for (int j = 0; j < CPT; ++j) {
         if ((uint32_t)lane == it0 + j) my_start = wave_count;
-        wave_count += F::template process<true, true, LONG>(P, lut, park, (uint64_t)(r0 + w0 + it0 + j) * kChunk, lane, w[j], wave_count, lds);
+        wave_count += process_chunk<F, true, true, LONG>(P, lut, park, (uint64_t)(r0 + w0 + it0 + j) * kChunk, lane, w[j], wave_count, lds);
       }
     }
   } else {
@@ -635,8 +668,8 @@ __global__ __launch_bounds__(kTileThreads) void compress_tile_kernel(const TileA
         if (c >= mine) break;
         const uint64_t cbase = (uint64_t)(r0 + w0 + c) * kChunk;
         if ((uint32_t)lane == c) my_start = wave_count;
-        wave_count += F::full(P, cbase) ? F::template process<true, true>(P, lut, park, cbase, lane, w[j], wave_count, lds)
-                                        : F::template process<false, true>(P, lut, park, cbase, lane, w[j], wave_count, lds);
+        wave_count += F::full(P, cbase) ? process_chunk<F, true, true>(P, lut, park, cbase, lane, w[j], wave_count, lds)
+                                        : process_chunk<F, false, true>(P, lut, park, cbase, lane, w[j], wave_count, lds);
       }
     }
   }
@@ -827,10 +860,10 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
           const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_chunk(P.w, r0 + k) : 0u);
           if (F::full(P, cbase)) {
             F::template load<true>(P, cptr, cbase, lane, w);
-            F::template process<true, false>(P, lut, park, cbase, lane, w, base, fin);
+            process_chunk<F, true, false>(P, lut, park, cbase, lane, w, base, fin);
           } else {
             F::template load<false>(P, cptr, cbase, lane, w);
-            F::template process<false, false>(P, lut, park, cbase, lane, w, base, fin);
+            process_chunk<F, false, false>(P, lut, park, cbase, lane, w, base, fin);
           }
         }
       }
@@ -923,8 +956,8 @@ __global__ __launch_bounds__(kSmallThreads) void compress_small_kernel(const Til
     if (c + 1 < mine) fetch(c + 1, nxt);   // the next chunk's words travel while this one is worked on
     const uint64_t cbase = (uint64_t)(c0 + c) * kChunk;
     if ((uint32_t)lane == c) my_start = count;
-    count += F::full(P, cbase) ? F::template process<true, true>(P, lut, park, cbase, lane, cur, count, lds)
-                               : F::template process<false, true>(P, lut, park, cbase, lane, cur, count, lds);
+    count += F::full(P, cbase) ? process_chunk<F, true, true>(P, lut, park, cbase, lane, cur, count, lds)
+                               : process_chunk<F, false, true>(P, lut, park, cbase, lane, cur, count, lds);
     cur = nxt;
   }
   if (lane == 0) s_cnt[wave] = count;
@@ -947,8 +980,8 @@ __global__ __launch_bounds__(kSmallThreads) void compress_small_kernel(const Til
       const uint64_t cbase = (uint64_t)(c0 + c) * kChunk;
       const uint32_t base = first + (uint32_t)__builtin_amdgcn_readlane(my_start, c);
       fetch(c, cur);
-      if (F::full(P, cbase)) F::template process<true, false>(P, lut, park, cbase, lane, cur, base, fin);
-      else F::template process<false, false>(P, lut, park, cbase, lane, cur, base, fin);
+      if (F::full(P, cbase)) process_chunk<F, true, false>(P, lut, park, cbase, lane, cur, base, fin);
+      else process_chunk<F, false, false>(P, lut, park, cbase, lane, cur, base, fin);
     }
   }
   if (wave == kSmallWaves - 1) compress_write_trailer(P, dec, a.sizes + item, M, 0u, lane);   // the wave with the fewest chunks
@@ -998,10 +1031,12 @@ struct ShortCounts {
 #pragma unroll
     for (int q = 0; q < EACH; ++q) v[q] = tag;
   }
-  // The own word, written at the device's point of coherence before anyone of this workgroup goes on; then the others', as
-  // often as `times` at most.  rank() and overall() follow.
-  __device__ inline void tell_and_look(ShortShared<EACH>& s, uint32_t total, uint32_t mark, uint32_t times, uint32_t tid, uint32_t wave) {
+  // The own word, written at the device's point of coherence before anyone of this workgroup looks at the others', as
+  // often as `times` at most; meanwhile() while it is on its way.  rank() and overall() follow.
+  template <typename Meanwhile>
+  __device__ inline void tell_and_look(ShortShared<EACH>& s, uint32_t total, uint32_t mark, uint32_t times, uint32_t tid, uint32_t wave, const Meanwhile& meanwhile) {
     if (tid < kShortCopies) st_agent(words + tid * copy + own, tag | mark | total);
+    meanwhile();
     if (wave == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
     bool here;
@@ -1063,14 +1098,15 @@ struct ShortCounts {
     __syncthreads();
     return s.won != 0;
   }
-  // A workgroup's way through a launch: encode(tile, first) makes a tile and leaves its count in total, place(tile) puts its
-  // records where first and M say.
-  template <typename Encode, typename Place>
-  __device__ inline void run(ShortShared<EACH>& s, uint32_t looks, const uint32_t& total, uint32_t tid, uint32_t wave, const Encode& encode, const Place& place) {
+  // A workgroup's way through a launch: encode(tile, first) makes a tile and leaves its count in total, deliver() writes its
+  // planes and stages its records, place(tile) puts those where first and M say.
+  template <typename Encode, typename Deliver, typename Place>
+  __device__ inline void run(ShortShared<EACH>& s, uint32_t looks, const uint32_t& total, uint32_t tid, uint32_t wave, const Encode& encode, const Deliver& deliver, const Place& place) {
     encode(own, true);
     if (n_tiles > 1) {
-      tell_and_look(s, total, 0u, looks, tid, wave);
+      tell_and_look(s, total, 0u, looks, tid, wave, deliver);
     } else {   // nobody to tell
+      deliver();
       if (tid == 0) v[0] |= total;
       if ((tid & 63u) == 0) s.state[wave] = 1u;
     }
@@ -1083,7 +1119,7 @@ struct ShortCounts {
     bool keep = (state & 1u) != 0;
     if (!keep) {
       __syncthreads();
-      tell_and_look(s, total, kShortLeft, 1u, tid, wave);
+      tell_and_look(s, total, kShortLeft, 1u, tid, wave, [] {});
       rank(s, own, tid, wave);
       overall(s);
       if (!(state & 1u)) return;
@@ -1099,18 +1135,20 @@ struct ShortCounts {
       const uint32_t told = s.tile[tile];
       if (tile == own || !(told & kShortLeft) || (told & kShortTaken) || !take(s, tile, told & kShortCount, tid)) continue;
       encode(tile, false);
+      deliver();
       rank(s, tile, tid, wave);
       place(tile);
     }
   }
 };
 
-// us of this kernel and of the two
-// launches, without the gap between those (rocprofv3's trace, BF16): 4.4 and 3.4 + 2.4 (100 chunks), 5.2 and 3.9 + 3.0 (1024).
+// The count is told before the planes are on
+// their way: us per call with them in front of it and behind, BF16 4.87 and 4.59 (1024 chunks), 5.74 and 5.19 (2048), E5M2 4.64 and 4.17, 5.64 and
+// 4.82.
 // Workgroups of eight waves are 0.25 us faster at 2048 chunks but get onto a busy chip late, and everyone waits for them (beside
 // elementwise kernels that fill it 22 to 27 us a call, 16.9 with four, two launches 20.2; at 4096 chunks 216 and 21); two
-// chunks per wave take 0.3 us more.  It gains most where chunks escape whole: the finishing pass encodes tiles whose
-// records outgrow their slots once more, a workgroup 16 of them (2048 chunks of random words 62 us a call, 10.8 this way).
+// chunks per wave took 0.3 us more.  It gains most where chunks escape whole: the finishing pass encodes tiles whose
+// records outgrow their slots once more, a workgroup 16 of them (2048 chunks of random words 62 us a call, 9.7 this way).
 template <typename F, uint32_t N, int EACH>
 __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const TileArgs<N> args) {
   constexpr int NW = kTileThreads / 64;
@@ -1135,21 +1173,26 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
 
   uint32_t c = 0, count = 0;              // the wave's chunk and its escapes
   uint32_t in_tile = 0, total = 0;        // escapes of the tile before the wave's chunk; all of them
-  // a tile's planes out and its records staged
+  // A tile's words and counts, then, with the count told, its planes out and its records staged: the others need the one,
+  // and the stores need not be over when they are looked for.
+  typename F::Regs w;
+  typename F::Coded coded;
+  bool whole = false;                     // all chunks of the tile are complete
   auto encode = [&](uint32_t tile, bool build) {
     c = NW * tile + wave;
     count = 0;
     const uint64_t cbase = (uint64_t)c * kChunk;
-    typename F::Regs w;
     auto table = [&]() {   // while the words are on their way
       if (!build) return;
       build_encode_table(lut, a.dec16_of(it, item), tid, F::kLutShift);
       lds_barrier();
     };
-    if (F::full(P, (uint64_t)(NW * tile + NW - 1) * kChunk)) {   // all chunks of the tile are complete
+    whole = F::full(P, (uint64_t)(NW * tile + NW - 1) * kChunk);
+    if (whole) {
       F::template load<true>(P, chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_wave_chunk(P.w, c) : 0u), cbase, lane, w);
       table();
-      count = F::template process<true, true>(P, lut, park, cbase, lane, w, 0u, lds);
+      F::template encode<true>(P, lut, cbase, lane, w, coded);
+      count = F::count(coded);
     } else {
       const bool full = F::full(P, cbase);
       if (c < P.n_chunks) {
@@ -1159,8 +1202,9 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
       }
       table();
       if (c < P.n_chunks) {
-        count = full ? F::template process<true, true>(P, lut, park, cbase, lane, w, 0u, lds)
-                     : F::template process<false, true>(P, lut, park, cbase, lane, w, 0u, lds);
+        if (full) F::template encode<true>(P, lut, cbase, lane, w, coded);
+        else F::template encode<false>(P, lut, cbase, lane, w, coded);
+        count = F::count(coded);
       }
     }
     if (lane == 0) s_cnt[wave] = count;
@@ -1172,6 +1216,12 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
       in_tile += q < wave ? x : 0u;
       total += x;
     }
+  };
+  auto deliver = [&]() {
+    const uint64_t cbase = (uint64_t)c * kChunk;
+    if (whole || (c < P.n_chunks && F::full(P, cbase))) F::template store<true>(P, cbase, lane, coded);
+    else if (c < P.n_chunks) F::template store<false>(P, cbase, lane, coded);
+    F::emit(park, lane, w, coded, count, 0u, lds);
   };
 
   // the tile's records and table entries where they belong; the stream's header and pads with the first tile
@@ -1187,7 +1237,7 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
     for (uint32_t i = lane; i < count; i += 64) fin.put(base + i, stage_pos[wave][i], stage_val[wave][i]);
     if (tile == 0 && wave == NW - 1) compress_write_trailer(P, a.dec16_of(it, item), a.sizes + item, counts.M, 0u, lane);
   };
-  counts.run(s_short, a.slot_cap, total, (uint32_t)tid, (uint32_t)wave, encode, place);
+  counts.run(s_short, a.slot_cap, total, (uint32_t)tid, (uint32_t)wave, encode, deliver, place);
 }
 
 #endif  // SPLITZIP_COMPRESS_HPP

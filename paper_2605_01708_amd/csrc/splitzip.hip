@@ -824,11 +824,11 @@ constexpr uint32_t kSmallestShort = 16;   // shorter tensors are one workgroup's
 uint64_t short_status_need(uint64_t tiles) { return kShortCopies * short_copy_bytes(tiles); }
 // Words that a thread of compress_short_kernel looks at if it takes these tensors (tiles_max: of the longest), else 0.
 // us per call, one behind the other, of two launches (of one workgroup per tensor up to 40 chunks) and this way: BF16 16 chunks 4.1
-// and 4.1, 24 4.6 and 4.0, 40 5.7 and 4.0, 100 7.3 and 4.1, 512 7.1 and 4.3, 1024 7.1 and 4.85, 1300 7.1 and 5.1, 2048 7.05 and 5.6, 4096 7.8
-// and 8.6; E5M2 100 7.0 and 4.0, 2048 7.1 and 5.6, 4096 7.3 and 7.5; 64 BF16 tensors of 16 chunks 4.85 and 5.0, of 40 7.2 and 6.0, of 50 8.0
-// and 5.8, of 100 9.8 and 9.7; 16 of 256 8.05 and 6.8; four of 1000 8.0 and 6.5, two of 2000 8.0 and 7.4; 8 of 1000 10.6 and 12.3, 64 of 1000
-// 42 and 101.  Every workgroup looks at all words of its tensor, so the cost grows with the square of them, and one that
-// waits keeps others from the chip.  What bounds calls of up to 500 chunks now is the host: a launch takes it 2.3 us.
+// and 4.1, 24 4.6 and 4.0, 40 5.7 and 4.0, 100 7.3 and 4.1, 512 7.1 and 4.3, 1024 7.1 and 4.6, 2048 7.05 and 5.2; E5M2 100 7.0 and 4.0, 1024 7.2 and 4.2,
+// 2048 7.1 and 4.8; 64 BF16 tensors of 16 chunks 4.85 and 5.0, of 40 7.2 and 6.0, of 50 8.0 and 5.8, 16 of 256 8.05 and 6.1; with the planes
+// stored before the counts are told, 4096 chunks 7.8 and 8.6, 7.3 and 7.5; 64 of 100 9.8 and 9.7; four of 1000 8.0 and 6.5, two of 2000 8.0 and 7.4; 8 of
+// 1000 10.6 and 12.3, 64 of 1000 42 and 101.  Every workgroup looks at all words of its tensor, so the cost grows with the square of
+// them, and one that waits keeps others from the chip.  What bounds calls of up to 500 chunks now is the host: a launch takes it 2.3 us.
 uint32_t short_each(const splitzip_item* items, uint32_t k, uint64_t status_bytes, uint64_t* tiles_max) {
   uint64_t chunks_max = 0, chunks_all = 0, need = 0;
   for (uint32_t q = 0; q < k; ++q) {

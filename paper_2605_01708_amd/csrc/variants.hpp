@@ -708,7 +708,7 @@ __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args
     }
     if (tile == 0) v_write_trailer(a, args.a.hdr, counts.M, tid);
   };
-  counts.run(s_short, args.looks, total, tid, wave, encode, place);
+  counts.run(s_short, args.looks, total, tid, wave, encode, [] {}, place);
 }
 
 // compress pass 4, for values narrower than a byte: the value section as an LSB-first bit stream of val_bits per
