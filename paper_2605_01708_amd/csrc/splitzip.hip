@@ -825,10 +825,12 @@ uint64_t short_status_need(uint64_t tiles) { return kShortCopies * short_copy_by
 // Words that a thread of compress_short_kernel looks at if it takes these tensors (tiles_max: of the longest), else 0.
 // us per call, one behind the other, of two launches (of one workgroup per tensor up to 40 chunks) and this way: BF16 16 chunks 4.1
 // and 4.1, 24 4.6 and 4.0, 40 5.7 and 4.0, 100 7.3 and 4.1, 512 7.1 and 4.3, 1024 7.1 and 4.6, 2048 7.05 and 5.2; E5M2 100 7.0 and 4.0, 1024 7.2 and 4.2,
-// 2048 7.1 and 4.8; 64 BF16 tensors of 16 chunks 4.85 and 5.0, of 40 7.2 and 6.0, of 50 8.0 and 5.8, 16 of 256 8.05 and 6.1; with the planes
-// stored before the counts are told, 4096 chunks 7.8 and 8.6, 7.3 and 7.5; 64 of 100 9.8 and 9.7; four of 1000 8.0 and 6.5, two of 2000 8.0 and 7.4; 8 of
-// 1000 10.6 and 12.3, 64 of 1000 42 and 101.  Every workgroup looks at all words of its tensor, so the cost grows with the square of
-// them, and one that waits keeps others from the chip.  What bounds calls of up to 500 chunks now is the host: a launch takes it 2.3 us.
+// 2048 7.1 and 4.8; BF16 2300 7.2 and 5.6, 2816 7.25 and 6.0, E5M2 2560 7.2 and 5.3; 64 BF16 tensors of 16 chunks 4.85 and 5.0, of 40 7.2 and 6.0, of 50 8.0 and 5.8, 16 of 256 8.05 and 6.1; with the planes
+// stored before the counts are told, 64 of 100 9.8 and 9.7, four of 1000 8.0 and 6.5, 8 of 1000 10.6 and 12.3, 64 of 1000 42 and 101.
+// Every workgroup looks at all words of its tensor, so the cost grows with the square of them, and one that waits keeps others from the
+// chip.  Where a tensor has more than 256 tiles the line is the busy chip: beside elementwise kernels that fill it 20.4 and 17.0 (2300 and
+// 2560 chunks), 20.4 and 17.8 (2816), 20.4 and 19.6 (3072), 20.5 and 63 (3500), beside matrix products 168 and 109 at all of them; alone,
+// 3072 7.25 and 6.2, 3500 7.6 and 7.6, E5M2 3500 7.2 and 5.85.  What bounds calls of up to 500 chunks now is the host: a launch takes it 2.3 us.
 uint32_t short_each(const splitzip_item* items, uint32_t k, uint64_t status_bytes, uint64_t* tiles_max) {
   uint64_t chunks_max = 0, chunks_all = 0, need = 0;
   for (uint32_t q = 0; q < k; ++q) {
@@ -838,8 +840,8 @@ uint32_t short_each(const splitzip_item* items, uint32_t k, uint64_t status_byte
     need += short_status_need(tiles_of(c, 1));
   }
   *tiles_max = tiles_of(chunks_max, 1);
-  const uint32_t each = *tiles_max <= kTileThreads ? 1u : 2u;
-  return chunks_max > kSmallestShort && chunks_all <= (each == 1 ? 4096u : 2048u) && need <= status_bytes ? each : 0u;
+  const uint32_t each = *tiles_max <= kTileThreads ? 1u : *tiles_max <= 2 * kTileThreads ? 2u : 3u;
+  return chunks_max > kSmallestShort && chunks_all <= (each == 1 ? 4096u : 2816u) && need <= status_bytes ? each : 0u;
 }
 
 // items[0, n_items): what is left of the call; n_max: its longest tensor; once: what is enqueued runs once
@@ -988,8 +990,8 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     if (p.short_each) {
       a.stage_cap = next_call_tag();
       a.slot_cap = short_looks();
-      if (dtype == SPLITZIP_BF16) (p.short_each == 1 ? launch_short<Bf16, 1> : launch_short<Bf16, 2>)(tiles_max, k, st, args);
-      else (p.short_each == 1 ? launch_short<E5m2, 1> : launch_short<E5m2, 2>)(tiles_max, k, st, args);
+      if (dtype == SPLITZIP_BF16) (p.short_each == 1 ? launch_short<Bf16, 1> : p.short_each == 2 ? launch_short<Bf16, 2> : launch_short<Bf16, 3>)(tiles_max, k, st, args);
+      else (p.short_each == 1 ? launch_short<E5m2, 1> : p.short_each == 2 ? launch_short<E5m2, 2> : launch_short<E5m2, 3>)(tiles_max, k, st, args);
     } else if (p.small) {
       if (dtype == SPLITZIP_BF16) launch_small<Bf16>(k, st, args);
       else launch_small<E5m2>(k, st, args);

@@ -65,6 +65,26 @@ def test_streams_at_the_edges(dtype, odt, chunks, looks):
 
 
 @pytest.mark.parametrize("dtype,odt", FORMATS)
+def test_three_words_a_thread(dtype, odt, looks):
+    """Tensors of more than 512 tiles, up to the range's end and one word beyond it, alone and with short ones."""
+    cb, ocb = books(dtype, odt)
+    for n in (2560 * 1024 + 1, 2816 * 1024, 2816 * 1024 + 1):
+        for limit in (0, 1):
+            print(f"case {dtype} n={n} looks={limit}", flush=True)
+            looks(limit)
+            check(words(dtype, n, 3, "many"), cb, ocb)
+    sizes = [2500 * 1024 - 7, 0, 300 * 1024, 16 * 1024]
+    xs = [words(dtype, n, 11 + k) for k, n in enumerate(sizes)]
+    outs = [torch.full((sz.compress_bound(n, dtype) + 256,), 0xA5, dtype=torch.uint8, device="cuda") for n in sizes]
+    ws, rec = sz.Workspace(max(sizes), dtype), sz.new_sizes_array(len(xs))
+    looks(0)
+    sz.compress_batch([x.cuda() for x in xs], [cb] * len(xs), outs, ws, rec)
+    for x, out, got in zip(xs, outs, sz.read_sizes_array(rec)):
+        blob, m = oracle.compress(kv_synth.to_numpy_words(x), ocb)
+        assert got == (blob.size, m, 0) and np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("dtype,odt", FORMATS)
 def test_what_the_workspace_holds(dtype, odt, looks):
     """One workspace for calls of different lengths, and words of it overwritten in between: no value in it means anything."""
     cb, ocb = books(dtype, odt)
