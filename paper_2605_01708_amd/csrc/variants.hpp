@@ -292,6 +292,27 @@ __device__ inline void v_build_encode_table(const VArgs& a, uint32_t* lut, uint3
   }
 }
 
+// The positions of the block's first `cap` escapes into s_pos, its words into s_words.  (The steps' arrays one by one: out
+// of a struct the dense pass's code came another way, 26.6 us instead of 26.5 for 64 MiB.)
+template <int DT, int CB>
+__device__ inline void v_stage_block(uint32_t* s_words, uint16_t* s_pos, uint32_t cap, uint32_t lane, const uint32_t (&w)[2][VFmt<DT>::NW],
+                                     const uint32_t (&esc)[2], const uint32_t (&excl)[2], const uint32_t (&tot)[2]) {
+  using F = VFmt<DT>;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    // the lane's words in its own bytes of the block's LDS copy
+    if (F::ES == 2) reinterpret_cast<u32x4*>(s_words)[s * 64 + lane] = u32x4{w[s][0], w[s][1], w[s][F::NW - 2], w[s][F::NW - 1]};
+    else reinterpret_cast<u32x2*>(s_words)[s * 64 + lane] = u32x2{w[s][0], w[s][1]};
+    uint32_t m = esc[s], r = (s ? tot[0] : 0u) + excl[s];
+    while (m) {
+      const uint32_t bit = (uint32_t)__ffs(m) - 1u, j = CB == 4 ? bit >> 2 : (bit * 11u) >> 5;   // bit / CB
+      m &= m - 1;
+      if (r < cap) s_pos[r] = (uint16_t)(s * kVStep + lane * 8 + j);
+      ++r;
+    }
+  }
+  v_lds_settle();
+}
 // One block of 1024 elements by one wave, its words in w: planes out, the positions of its first `cap` escapes in s_pos, its words in
 // s_words if it has any.  tot: the escapes of its two steps, low: those of the lower 32 lanes.
 template <int DT, int CB, bool FULL>
@@ -310,22 +331,7 @@ __device__ inline uint32_t v_encode_block(const VArgs& a, const uint32_t* lut, u
     tot[s] = v_sparse_excl(__popc(esc[s]), excl[s], low[s]);
   }
   const uint32_t total = tot[0] + tot[1];
-  if (total) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      // the lane's words in its own bytes of the block's LDS copy
-      if (F::ES == 2) reinterpret_cast<u32x4*>(s_words)[s * 64 + lane] = u32x4{w[s][0], w[s][1], w[s][F::NW - 2], w[s][F::NW - 1]};
-      else reinterpret_cast<u32x2*>(s_words)[s * 64 + lane] = u32x2{w[s][0], w[s][1]};
-      uint32_t m = esc[s], r = (s ? tot[0] : 0u) + excl[s];
-      while (m) {
-        const uint32_t bit = (uint32_t)__ffs(m) - 1u, j = CB == 4 ? bit >> 2 : (bit * 11u) >> 5;   // bit / CB
-        m &= m - 1;
-        if (r < cap) s_pos[r] = (uint16_t)(s * kVStep + lane * 8 + j);
-        ++r;
-      }
-    }
-    v_lds_settle();
-  }
+  if (total) v_stage_block<DT, CB>(s_words, s_pos, cap, lane, w, esc, excl, tot);
   return total;
 }
 // exponent of the block's element p, out of its words
@@ -639,18 +645,18 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs args) {
 // Short calls (splitzip_variant_compress): the passes above in one launch, as in compress_short_kernel, a block per wave.
 // short_words: where the workgroups' words lie (the blocks' slots, which nothing is staged in here); tag, looks: as there; tiles: the
 // launch's workgroups (asked for as gridDim, a launch has 256 bytes more of arguments).
-// us per call, two launches and this: BF16 top-8 7.8 and 4.45 (4 blocks), 8.0 and 5.2 (100), 8.2 and 5.6 (1000), 8.7 and 6.35 (2000), sentinels
-// 7.8 and 4.8 (100), 8.1 and 5.5 (2000); E5M2 7.8 and 4.9, 7.9 and 5.5, with narrow values, which v_pack_kernel still packs, 11.7 and 8.3, 12.0
-// and 9.4; random words, BF16 top-8, 1000 blocks 28.2 and 9.0.  Beyond 2048 blocks the words that every workgroup looks at cost more
-// than a launch (short_each).
+// us per call, two launches and this: BF16 top-8 7.8 and 4.4 (4 blocks), 8.0 and 5.1 (100), 8.2 and 5.3 (1000), 8.7 and 5.8 (2000), 9.3 and
+// 6.4 (2816), sentinels 7.8 and 4.3 (100), 8.1 and 5.1 (2000), 7.65 and 5.7 (2816); E5M2 7.8 and 4.4, 7.9 and 5.1, 7.5 and 5.8; with the planes
+// stored and the records staged before the count is told, BF16 top-8 5.5 (100), 6.1 (1000), 7.1 (2000).  Narrow values are still packed by
+// v_pack_kernel.  Not beyond 704 tiles, as in short_each.
 struct VShortArgs {
   VArgs a;
   uint64_t* short_words;
   uint64_t tag;
   uint32_t looks, tiles;
 };
-constexpr int kVShortEach = 2;
-template <int DT, int CB>
+constexpr uint32_t kVShortTiles = 704;
+template <int DT, int CB, int EACH>
 __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args) {
   using F = VFmt<DT>;
   static_assert(kThreads == kTileThreads, "ShortCounts");
@@ -658,19 +664,21 @@ __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args
   __shared__ __attribute__((aligned(16))) uint32_t s_words[kWaves][kVBlock * F::ES / 4];
   __shared__ uint16_t s_pos[kWaves][kVBlock];   // room for all of a wave's records
   __shared__ uint32_t s_cnt[kWaves];
-  __shared__ ShortShared<kVShortEach> s_short;
+  __shared__ ShortShared<EACH> s_short;
   const VArgs a = v_args_arrived(args.a);
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-  ShortCounts<kVShortEach> counts(args.short_words, args.tag, args.tiles, blockIdx.x);
-  uint32_t blk = 0, count = 0, tot[2], low[2];   // the wave's block and its escapes
+  ShortCounts<EACH> counts(args.short_words, args.tag, args.tiles, blockIdx.x);
+  uint32_t blk = 0, count = 0;                   // the wave's block and its escapes
+  bool live = false, full = false;
+  uint32_t w[2][F::NW];
+  uint32_t sm[2][2], code[2][2], esc[2], excl[2], tot[2], low[2];   // of the block's steps
   uint32_t in_tile = 0, total = 0;               // escapes of the tile before the wave's block; all of them
   auto encode = [&](uint32_t tile, bool build) {
     blk = tile * kWaves + wave;
     count = tot[0] = tot[1] = low[0] = low[1] = 0;
     const uint64_t e0 = (uint64_t)blk * kVBlock;
-    const bool live = e0 < a.n, full = e0 + kVBlock <= a.n;
-    uint32_t w[2][F::NW];
+    live = e0 < a.n, full = e0 + kVBlock <= a.n;
     // the block's words first, all of them: the table is built while they are on their way
     if (full) {
 #pragma unroll
@@ -683,8 +691,14 @@ __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args
       v_build_encode_table(args.a, lut, tid);
       lds_barrier();
     }
-    if (full) count = v_encode_block<DT, CB, true>(a, lut, s_words[wave], s_pos[wave], kVBlock, blk, lane, w, tot, low);
-    else if (live) count = v_encode_block<DT, CB, false>(a, lut, s_words[wave], s_pos[wave], kVBlock, blk, lane, w, tot, low);
+    if (live) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        v_encode8<DT, CB>(lut, full ? 8u : v_nvalid(a, e0 + s * kVStep + lane * 8), w[s], sm[s], code[s], esc[s]);
+        tot[s] = v_sparse_excl(__popc(esc[s]), excl[s], low[s]);
+      }
+      count = tot[0] + tot[1];
+    }
     if (lane == 0) s_cnt[wave] = count;
     lds_barrier();
     in_tile = total = 0;
@@ -694,6 +708,21 @@ __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args
       in_tile += q < wave ? x : 0u;
       total += x;
     }
+  };
+  auto deliver = [&] {
+    const uint64_t sm_end = a256(a.sm_bytes), code_end = a256(a.code_bytes);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const uint64_t sm_at = ((uint64_t)blk * kVBlock + s * kVStep) / 8 * F::SB, code_at = ((uint64_t)blk * kVBlock + s * kVStep) / 8 * CB;
+      if (full) {
+        v_store_plane<F::SB, true>(a.out + a.off_sm, sm_at, sm_end, lane, sm[s]);
+        v_store_plane<CB, true>(a.out + a.off_code, code_at, code_end, lane, code[s]);
+      } else if (live) {
+        v_store_plane<F::SB, false>(a.out + a.off_sm, sm_at, sm_end, lane, sm[s]);
+        v_store_plane<CB, false>(a.out + a.off_code, code_at, code_end, lane, code[s]);
+      }
+    }
+    if (count) v_stage_block<DT, CB>(s_words[wave], s_pos[wave], kVBlock, lane, w, esc, excl, tot);
   };
   auto place = [&](uint32_t tile) {
     const VSink<kVAnyPos> sink(a, counts.M);
@@ -708,7 +737,7 @@ __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args
     }
     if (tile == 0) v_write_trailer(a, args.a.hdr, counts.M, tid);
   };
-  counts.run(s_short, args.looks, total, tid, wave, encode, [] {}, place);
+  counts.run(s_short, args.looks, total, tid, wave, encode, deliver, place);
 }
 
 // compress pass 4, for values narrower than a byte: the value section as an LSB-first bit stream of val_bits per

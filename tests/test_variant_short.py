@@ -41,6 +41,19 @@ def test_lengths_at_the_edges(form, looks):
                 check(run, o, x, dec, f"looks {limit}")
 
 
+@pytest.mark.parametrize("form", FORMS)
+def test_three_words_a_thread(form, looks):
+    """More than 512 tiles, the range's end, and one block beyond it."""
+    v, o = sz.variant(*form), ov.variant(*form)
+    dec = np.zeros(16, np.uint8)
+    dec[:v.k] = sz.variant_calibrate(GEN[form[0]](64, 1), v).dec[:v.k]
+    for n in (2049 * 1024 - 5, 2816 * 1024, 2816 * 1024 + 1):
+        x, run = words(form[0], n, 5), Run(n, v)
+        for limit in (0, 1):
+            looks(limit)
+            check(run, o, x, dec, f"looks {limit}")
+
+
 @pytest.mark.parametrize("limit", [1, sz.INTERNAL_NO_SHORT])
 @pytest.mark.parametrize("form", FORMS)
 def test_escape_counts(form, limit, looks):
