@@ -110,9 +110,11 @@ def fmt_of(dtype):
 
 
 def compress_kernels(dtype, n, tensors=1):
-    """the kernels of a compress call over so many tensors of n elements (of its first launch: at most 64 tensors)"""
+    """the kernels of a compress call over so many tensors of n elements (of its first launch: at most 160 tensors)"""
     f = fmt_of(dtype)
-    plan = sz.internal_compress_plan([n] * min(tensors, 64), dtype)
+    plan = sz.internal_compress_plan([n] * min(tensors, 160), dtype)
+    if plan["short"]:
+        return f"compress_short_kernel<{f}>"
     if plan["small"]:
         return f"compress_small_kernel<{f}>"
     return f"compress_tile_kernel<{f}, {min(plan['cpt'], 2 if dtype == sz.BF16 else 4)}> + compress_finish_kernel<{f}>"
@@ -232,7 +234,7 @@ class Workload:
 
     def summary(self, ms_c, ms_d, c1_us, d1_us):
         """the figures every workload reports"""
-        launches = (self.nt + 63) // 64      # a batch call takes 64 tensors per pair of launches
+        launches = (self.nt + 159) // 160    # a batch call takes 160 tensors per pair of launches
         alg1 = self.alg_bytes / self.nt
         f = fmt_of(self.dtype)
         return {
@@ -282,7 +284,7 @@ def main():
     alg_bytes = W.alg_bytes
     c_ach = alg_bytes / (mean(ms_c) * 1e-3) / 1e9
     d_ach = alg_bytes / (mean(ms_d) * 1e-3) / 1e9
-    launches = (nt + 63) // 64
+    launches = (nt + 159) // 160
 
     # ---- the same pass, one call per tensor
     reps = max(2, args.steps // 2)
@@ -483,7 +485,7 @@ def streaming_calls(W, positions=64):
     of one chunk position (640 MiB, more than the last-level cache holds) serve as the ring that the 64 positions
     cycle through.  Three ways: (a) eager single calls, every call between two events on the stream (per-call
     latency as the device sees it) and a subset between host clocks with a synchronise (as a caller sees it);
-    (b) one batch call per chunk position (three pairs of launches for 160 tensors); (c) the batch calls of one chunk
+    (b) one batch call per chunk position (one pair of launches for 160 tensors); (c) the batch calls of one chunk
     position captured in a HIP graph and replayed per position."""
     nt, n = W.nt, W.n
     calls = nt * positions

@@ -430,12 +430,13 @@ INTERNAL_NO_SHORT = 0xFFFFFFFF
 
 
 def internal_compress_plan(n_elems, dtype: int) -> dict:
-    """How a compress call's first launch over tensors of these lengths is shaped (host only, for tests of the rules)."""
-    items, out = (_CItem * len(n_elems))(), (C.c_uint32 * 8)()
+    """How a compress call's first launch over tensors of these lengths is shaped under capture, and whether it is one of
+    compress_short_kernel otherwise (host only, for tests of the rules)."""
+    items, out = (_CItem * len(n_elems))(), (C.c_uint32 * 9)()
     for it, n in zip(items, n_elems):
         it.n_elems = n
     lib().splitzip_internal_compress_plan(items, len(n_elems), dtype, out)
-    return dict(zip(("tensors", "cpt", "tiles_max", "launches", "by_xcd", "finish_groups", "group_sums", "small"), out))
+    return dict(zip(("tensors", "cpt", "tiles_max", "launches", "by_xcd", "finish_groups", "group_sums", "small", "short"), out))
 
 
 def internal_decompress_plan(n_elems, dtype: int, comp_bytes=None) -> dict:

@@ -1379,12 +1379,13 @@ int splitzip_decompress_batch_paged(const splitzip_ditem* items, uint32_t n_item
 }
 
 // the plan of a call's first launch, for tests of the rules (exported, not declared in splitzip.h): only the items' n_elems are read
-void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_items, int dtype, uint32_t out[8]) {
+void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_items, int dtype, uint32_t out[9]) {
   uint64_t n_max = 0;
   for (uint32_t q = 0; q < n_items; ++q)
     if (items[q].n_elems > n_max) n_max = items[q].n_elems;
   const CompressPlan p = plan_compress(items, n_items, n_max, dtype, kStatusBytes, [] { return false; });   // the plan under capture
-  const uint32_t v[8] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small};
+  const uint32_t each = plan_compress(items, n_items, n_max, dtype, kStatusBytes, [] { return true; }).short_each;   // otherwise
+  const uint32_t v[9] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small, each};
   memcpy(out, v, sizeof v);
 }
 // the tile that workgroup b of a tensor of n tiles takes in a launch by XCDs
