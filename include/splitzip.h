@@ -261,7 +261,7 @@ int splitzip_decompress_batch(const splitzip_ditem* items, uint32_t n_items, int
  * launch (160 tensors of a call where they are short), or in two and one
  * per 64 tensors: above 64 tensors, or for a few long ones.  d_hists: n_items x 256 device words, 8-byte
  * aligned, zeroed by the call; d_cbs: n_items splitzip_codebook in device
- * memory, 4-byte aligned.  The _batch_dcb calls are the batch calls with
+ * memory, 4-byte aligned; calls that overlap in time have d_hists and d_cbs of their own.  The _batch_dcb calls are the batch calls with
  * tensor k under d_cbs[k]; the items' own cb fields are not looked at.  As
  * with the _dcb calls the host cannot check such codebooks. */
 int splitzip_calibrate_batch_device(const splitzip_item* items, uint32_t n_items, int dtype, uint64_t* d_hists,

@@ -201,12 +201,16 @@ __global__ __launch_bounds__(1024) void histogram_batch_kernel(const HistBatchAr
 // among the membership flags of the codebook to be, kCtlReady and the workgroups that have added under the call's tag:
 // whoever first sees no tag of this call there puts it there, clears the bins and says so when it has counted, and nobody
 // adds before that.  (It is running and waits for nobody, so the wait for it ends.)  In the end the word is overwritten with
-// flags, bytes of 0 and 1, which are no tag: its first bit is set.
+// flags, bytes of 0 and 1, which are no tag: its first bit is set.  Calls that overlap on the same outputs leave nothing of
+// use in them, but they end: a workgroup waits only while the word bears its own call's tag without kCtlReady, and whoever puts
+// a tag there has yet to look whether it is to add kCtlReady to it.  (By compare and exchange, as the tag: where the codebooks
+// are host memory, that is what the bus can do.)
 // Clearing by a launch in front, and ranking by one behind, made a call three launches.  us per call, BF16, then and now: 64
 // chunks 10.6 and 8.3, 1024 10.8 and 8.8, 64 samples of two 10.9 and 6.1, 64 of 100 12.0 and 10.4, 64 of 4096 88.5 and 86.5; E5M2 64 of 20 10.8 and
 // 5.1, 64 of 4096 50.2 and 48.7.
 constexpr int kCtlTagShift = 17;
 constexpr uint64_t kCtlReady = 1u << 16, kCtlTag = 1ull << 63;
+__host__ __device__ inline bool ctl_waits(uint64_t word, uint64_t tag) { return ((word ^ tag) >> kCtlTagShift) == 0 && !(word & kCtlReady); }
 template <bool BF16, uint32_t N>
 __global__ __launch_bounds__(1024) void calibrate_batch_kernel(const HistBatchArgs<N> a, uint64_t* hists, splitzip_codebook* cbs) {
   __shared__ uint64_t s_count[256];
@@ -239,9 +243,13 @@ __global__ __launch_bounds__(1024) void calibrate_batch_kernel(const HistBatchAr
         if (!minds) return;
         if (clears) {
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the bins are clear
-          if (lane == 0) (void)__hip_atomic_fetch_or(ctl, kCtlReady, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (lane == 0) {
+            uint64_t seen = a.tag;   // what it has put there
+            while (!__hip_atomic_compare_exchange_strong(ctl, &seen, seen | kCtlReady, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &&
+                   ctl_waits(seen, a.tag)) {}
+          }
         }
-        while (!(ld_agent(ctl) & kCtlReady)) __builtin_amdgcn_s_sleep(1);
+        while (ctl_waits(ld_agent(ctl), a.tag)) __builtin_amdgcn_s_sleep(1);
       },
       [&](uint32_t bin, uint32_t c) {
         if (!several) s_count[bin] = c;

@@ -1388,6 +1388,8 @@ void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_item
   const uint32_t v[9] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small, each};
   memcpy(out, v, sizeof v);
 }
+// whether a workgroup of the calibration call `tag` waits at a control word
+int splitzip_internal_calibrate_waits(uint64_t word, uint64_t tag) { return ctl_waits(word, tag); }
 // the tile that workgroup b of a tensor of n tiles takes in a launch by XCDs
 uint32_t splitzip_internal_xcd_tile(uint32_t b, uint32_t n) { return xcd_order(b, n - 1); }
 // how many escapes a stream of comp_bytes bytes has room for, as the decoder is told

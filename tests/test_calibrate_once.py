@@ -6,7 +6,6 @@ import torch
 import kv_synth
 import paper_2605_01708_amd as sz
 
-pytestmark = pytest.mark.gpu
 
 
 def check(xs, dcbs, dtype):
@@ -20,6 +19,7 @@ def check(xs, dcbs, dtype):
         assert (got.dec, got.enc, got.member, got.dtype) == (ref.dec, ref.enc, ref.member, ref.dtype), k
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
 @pytest.mark.parametrize("per", [[63], [64], [65], [3, 0, 1], [60, 61], [1] * 65, [1] * 161, [2] * 64, [2] * 130, [5] * 70])
 def test_numbers_of_workgroups_and_samples(dtype, per):
@@ -43,6 +43,7 @@ def test_numbers_of_workgroups_and_samples(dtype, per):
         check(xs, dcbs, dtype)
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
 def test_captured(dtype):
     gen = kv_synth.kv_bf16 if dtype == sz.BF16 else kv_synth.kv_e5m2
@@ -63,3 +64,31 @@ def test_captured(dtype):
         cal.launch()
         torch.cuda.synchronize()
         check(xs, dcbs, dtype)
+
+
+def test_who_waits():
+    """At a word that bears the call's tag and not yet the mark, and at no other: another call's, with the mark or without, a
+    codebook's flags, anything."""
+    tag, ready = 1 << 63 | 0x1234567 << 17, 1 << 16
+    assert all(sz.internal_calibrate_waits(tag | added, tag) for added in (0, 1, 255))
+    assert not any(sz.internal_calibrate_waits(tag | ready | added, tag) for added in (0, 1, 255))
+    for other in (tag + (1 << 17), tag - (1 << 17), tag ^ 1 << 63, tag ^ 1 << 62):
+        assert not sz.internal_calibrate_waits(other, tag) and not sz.internal_calibrate_waits(other | ready, tag)
+    for flags in (0, 0x0101010101010101, 0x0100010001000100, 0x0001000000000000, (1 << 64) - 1):
+        assert not sz.internal_calibrate_waits(flags, tag)
+
+
+@pytest.mark.gpu
+def test_calls_that_overlap_on_the_same_outputs_end():
+    """What they leave is nobody's to use; the next call on those outputs has them to itself and is right."""
+    xs = [kv_synth.kv_bf16(300 + 500 * k, k, device="cuda") for k in range(4)]
+    dcbs = sz.DeviceCodebooks(4, sz.BF16)
+    cal, streams = sz.CalibrateBatchDevice(xs, dcbs), [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for s in streams:
+            cal.launch(stream=s)
+    torch.cuda.synchronize()
+    cal.launch()
+    torch.cuda.synchronize()
+    check(xs, dcbs, sz.BF16)
