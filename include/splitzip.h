@@ -259,7 +259,9 @@ int splitzip_decompress_batch(const splitzip_ditem* items, uint32_t n_items, int
  * into d_hists + 256 k and ranks them into d_cbs[k], exactly as
  * splitzip_histogram and splitzip_codebook_device do for one tensor, in one
  * launch (160 tensors of a call where they are short), or in two and one
- * per 64 tensors: above 64 tensors, or for a few long ones.  d_hists: n_items x 256 device words, 8-byte
+ * per 64 tensors: above 64 tensors that are not short, or where one has a
+ * large share of the chip's workgroups (a BF16 tensor above 2.3 Mi elements
+ * by itself, or one of two or three, E5M2 above 4.6 Mi).  d_hists: n_items x 256 device words, 8-byte
  * aligned, zeroed by the call; d_cbs: n_items splitzip_codebook in device
  * memory, 4-byte aligned; calls that overlap in time have d_hists and d_cbs of their own.  The _batch_dcb calls are the batch calls with
  * tensor k under d_cbs[k]; the items' own cb fields are not looked at.  As

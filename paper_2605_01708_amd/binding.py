@@ -145,6 +145,8 @@ def lib():
         L.splitzip_internal_decompress_plan.argtypes = [C.POINTER(_CDItem), C.c_uint32, i, C.POINTER(C.c_uint32)]
         L.splitzip_internal_stream_room.restype = C.c_uint32
         L.splitzip_internal_stream_room.argtypes = [u64, u64, i]
+        L.splitzip_internal_calibrate_launches.restype = C.c_uint32
+        L.splitzip_internal_calibrate_launches.argtypes = [C.POINTER(_CItem), C.c_uint32, i]
         L.splitzip_internal_calibrate_waits.restype = i
         L.splitzip_internal_calibrate_waits.argtypes = [u64, u64]
         L.splitzip_internal_xcd_tile.restype = C.c_uint32
@@ -458,6 +460,14 @@ def internal_stream_room(comp_bytes: int, n_elems: int, dtype: int) -> int:
 def internal_xcd_tile(workgroup: int, n_tiles: int) -> int:
     """The tile that a workgroup of a tensor of n_tiles tiles takes in a launch that goes by XCDs (for tests)."""
     return int(lib().splitzip_internal_xcd_tile(workgroup, n_tiles))
+
+
+def internal_calibrate_launches(n_elems, dtype: int) -> int:
+    """The launches of a calibration call over samples of these lengths (host only, for tests of the rules)."""
+    items = (_CItem * len(n_elems))()
+    for it, n in zip(items, n_elems):
+        it.n_elems = n
+    return int(lib().splitzip_internal_calibrate_launches(items, len(n_elems), dtype))
 
 
 def internal_calibrate_waits(word: int, tag: int) -> bool:

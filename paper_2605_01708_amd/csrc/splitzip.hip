@@ -1258,6 +1258,37 @@ uint64_t most_wgs(uint64_t n, int dtype) {
   const uint64_t w = (n * (dtype == SPLITZIP_BF16 ? 2 : 1) + 16 * 4096 - 1) / (16 * 4096);
   return w ? w : 1;
 }
+// a sample's workgroups: its share of one per CU (all: words of all samples of the launch), but no more than most_wgs
+uint32_t wgs_of_sample(uint64_t n, uint64_t all, int dtype, uint64_t cus) {
+  const uint64_t share = all ? cus * n / all : 0, most = most_wgs(n, dtype);
+  return (uint32_t)(share > most ? most : share ? share : 1);
+}
+constexpr uint32_t kCalibrateAtOnce = 72;
+struct CalibratePlan {
+  uint32_t step;   // samples per launch
+  bool at_once;    // a launch clears, counts and ranks; or clearing and ranking are launches of their own
+  uint32_t launches(uint32_t n_items) const { return (n_items + step - 1) / step + (at_once ? 0 : 2); }
+};
+CalibratePlan plan_calibrate(const splitzip_item* items, uint32_t n_items, int dtype, uint64_t cus) {
+  // Short samples go up to kHistMostShort to a launch, and others kHistMost: their workgroups are dealt out whole, and 256 CUs divide the better
+  // among the fewer.
+  uint64_t wgs_short = 0, all = 0;
+  for (uint32_t i = 0; i < n_items; ++i) {
+    wgs_short += most_wgs(items[i].n_elems, dtype);
+    all += items[i].n_elems;
+  }
+  const bool are_short = wgs_short <= cus;
+  // One launch does it all where no sample has more than kCalibrateAtOnce workgroups; more of them, all at the one word, take longer than
+  // two more launches.  Device us per call with one and with three: BF16 9.73 and 10.09 (2048 chunks: 64 workgroups), 10.12 and 10.22 (2300: 72),
+  // 10.90 and 10.37 (2600: 82), 12.84 and 11.12 (4096: 128), 20.6 and 13.7 (8192: 256), two of 2600 11.64 and 10.79, of 4096 14.6 and 12.2, four of 4096 (64 each) 13.6 and 13.4; E5M2 8.56 and 9.40
+  // (4096: 64), 9.55 and 9.59 (5000: 79), 10.22 and 9.86 (6000: 94), 11.55 and 10.46 (8192: 128), 19.6 and 12.8 (16 384: 256).
+  // And not where a call takes several launches with a codebook's tail each (100 of 1000 chunks 45.4 and 48.0).
+  CalibratePlan p;
+  p.at_once = are_short || n_items <= kHistMost;
+  for (uint32_t i = 0; p.at_once && i < n_items; ++i) p.at_once = wgs_of_sample(items[i].n_elems, all, dtype, cus) <= kCalibrateAtOnce;
+  p.step = p.at_once && are_short && n_items > kHistMost ? kHistMostShort : kHistMost;
+  return p;
+}
 // the arguments of a calibration launch over k samples; its workgroups
 template <uint32_t N>
 uint32_t deal_samples(const splitzip_item* items, uint32_t k, int dtype, uint64_t cus, uint64_t tag, HistBatchArgs<N>* a) {
@@ -1266,12 +1297,12 @@ uint32_t deal_samples(const splitzip_item* items, uint32_t k, int dtype, uint64_
   uint32_t wgs = 0;
   a->tag = tag;
   for (uint32_t q = 0; q < k; ++q) {
-    const uint64_t n = items[q].n_elems, share = all ? cus * n / all : 0, most = most_wgs(n, dtype);   // its share of one workgroup per CU
+    const uint64_t n = items[q].n_elems;
     a->first[q] = wgs;
     a->in[q] = static_cast<const uint8_t*>(items[q].d_in);
     a->n[q] = n;
     a->start[q] = histogram_start(a->in[0], a->in[q], q, n * (dtype == SPLITZIP_BF16 ? 2 : 1) / 16);
-    wgs += (uint32_t)(share > most ? most : share ? share : 1);
+    wgs += wgs_of_sample(n, all, dtype, cus);
   }
   for (uint32_t q = k; q <= N; ++q) a->first[q] = wgs;   // (what else there is of samples that are not there is not looked at)
   return wgs;
@@ -1308,32 +1339,16 @@ int splitzip_calibrate_batch_device(const splitzip_item* items, uint32_t n_items
   if (n_items == 0) return SPLITZIP_OK;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
-  // Short samples go up to kHistMostShort to a launch, and others kHistMost: their workgroups are dealt out whole, and 256 CUs divide the better
-  // among the fewer.
-  uint64_t wgs_short = 0;
-  for (uint32_t i = 0; i < n_items; ++i) wgs_short += most_wgs(items[i].n_elems, dtype);
-  const bool are_short = wgs_short <= cus;
-  const uint32_t step = are_short && n_items > kHistMost ? kHistMostShort : kHistMost;
-  // One launch does it all where a sample has fewer than 64 workgroups; more of them, all at the one word, take longer than
-  // two more launches: us per call with one and three, BF16, 12.98 and 11.40 (4096 chunks: 128 workgroups), 24.0 and 20.3 (32 768: 256),
-  // 13.7 and 13.7 (four of 4096: 64 each), 15.25 and 15.85 (five: 51).  And not where a call takes several launches with a codebook's
-  // tail each (100 of 1000 chunks 48.0 and 45.4).
-  bool at_once = are_short || n_items <= step;
-  uint64_t all = 0;
-  for (uint32_t i = 0; at_once && !are_short && i < n_items; ++i) all += items[i].n_elems;
-  for (uint32_t i = 0; at_once && !are_short && i < n_items; ++i) {
-    const uint64_t w = all ? cus * items[i].n_elems / all : 0;
-    at_once = w < 64 || most_wgs(items[i].n_elems, dtype) < 64;
-  }
+  const CalibratePlan p = plan_calibrate(items, n_items, dtype, cus);
   const uint64_t tag = next_call_tag() << (kCtlTagShift - kShortTagShift) | kCtlTag;
-  if (!at_once) hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, d_hists, 256ull * n_items);
-  for (uint32_t i = 0; i < n_items; i += step) {
-    const uint32_t k = n_items - i < step ? n_items - i : step;
+  if (!p.at_once) hipLaunchKernelGGL(zero_words_kernel, dim3(64), dim3(256), 0, st, d_hists, 256ull * n_items);
+  for (uint32_t i = 0; i < n_items; i += p.step) {
+    const uint32_t k = n_items - i < p.step ? n_items - i : p.step;
     uint64_t* hists = d_hists + 256ull * i;
-    if (step == kHistMost) {
+    if (p.step == kHistMost) {
       HistBatchArgs<kHistMost> a;
       const uint32_t wgs = deal_samples(items + i, k, dtype, cus, tag, &a);
-      if (at_once) launch_calibrate(a, wgs, dtype, hists, d_cbs + i, st);
+      if (p.at_once) launch_calibrate(a, wgs, dtype, hists, d_cbs + i, st);
       else if (dtype == SPLITZIP_BF16) hipLaunchKernelGGL(histogram_batch_kernel<true>, dim3(wgs), dim3(1024), 0, st, a, hists);
       else hipLaunchKernelGGL(histogram_batch_kernel<false>, dim3(wgs), dim3(1024), 0, st, a, hists);
     } else {
@@ -1342,7 +1357,7 @@ int splitzip_calibrate_batch_device(const splitzip_item* items, uint32_t n_items
       launch_calibrate(a, wgs, dtype, hists, d_cbs + i, st);
     }
   }
-  if (!at_once) hipLaunchKernelGGL(codebook_kernel, dim3(n_items), dim3(1024), 0, st, d_hists, exp_values(dtype), (uint32_t)dtype, d_cbs);
+  if (!p.at_once) hipLaunchKernelGGL(codebook_kernel, dim3(n_items), dim3(1024), 0, st, d_hists, exp_values(dtype), (uint32_t)dtype, d_cbs);
   return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
 }
 
@@ -1387,6 +1402,10 @@ void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_item
   const uint32_t each = plan_compress(items, n_items, n_max, dtype, kStatusBytes, [] { return true; }).short_each;   // otherwise
   const uint32_t v[9] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small, each};
   memcpy(out, v, sizeof v);
+}
+// the launches of a calibration call on a chip of 256 CUs
+uint32_t splitzip_internal_calibrate_launches(const splitzip_item* items, uint32_t n_items, int dtype) {
+  return plan_calibrate(items, n_items, dtype, 256).launches(n_items);
 }
 // whether a workgroup of the calibration call `tag` waits at a control word
 int splitzip_internal_calibrate_waits(uint64_t word, uint64_t tag) { return ctl_waits(word, tag); }

@@ -21,7 +21,7 @@ def check(xs, dcbs, dtype):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
-@pytest.mark.parametrize("per", [[63], [64], [65], [3, 0, 1], [60, 61], [1] * 65, [1] * 161, [2] * 64, [2] * 130, [5] * 70])
+@pytest.mark.parametrize("per", [[63], [64], [65], [72], [73], [256], [72, 72, 0], [73, 5] + [1] * 70, [3, 0, 1], [60, 61], [1] * 65, [1] * 161, [2] * 64, [2] * 130, [5] * 70])
 def test_numbers_of_workgroups_and_samples(dtype, per):
     """per: a sample's workgroups at most, four vectors of 16 bytes per thread each"""
     each = 16 * 4096 // (2 if dtype == sz.BF16 else 1)
@@ -92,3 +92,18 @@ def test_calls_that_overlap_on_the_same_outputs_end():
     cal.launch()
     torch.cuda.synchronize()
     check(xs, dcbs, sz.BF16)
+
+
+@pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
+def test_launches(dtype):
+    """One where no sample has more than 72 workgroups, else one that clears, one that ranks and one per 64 samples between them;
+    samples with as many workgroups as they can have, and samples that share 256."""
+    each = 16 * 4096 // (2 if dtype == sz.BF16 else 1)
+    def launches(per):
+        return sz.internal_calibrate_launches([w * each for w in per], dtype)
+    assert [launches([w]) for w in (0, 1, 63, 72, 73, 128, 256, 257, 4096)] == [1] * 4 + [3] * 5
+    assert [launches([w, w]) for w in (1, 72, 73, 128, 300)] == [1, 1, 3, 3, 3]
+    assert launches([72, 72, 72, 0, 1]) == 1 and launches([72, 73, 5]) == 3
+    assert [launches([300] * k) for k in (1, 2, 3, 4, 64, 65)] == [3, 3, 3, 1, 1, 4]
+    assert [launches([1] * k) for k in (64, 65, 160, 161, 256, 257)] == [1, 1, 1, 2, 2, 7]
+    assert launches([73] + [1] * 100) == 4 and launches([72] + [1] * 100) == 1
