@@ -220,7 +220,8 @@ int splitzip_decompress(const void* d_comp, size_t comp_bytes, uint64_t n_elems,
  * compressed exactly as splitzip_compress would (same stream bytes); what a
  * single call pays per tensor for two launches -- the ramps of the dense pass
  * and the short finishing pass -- is paid once per 160 tensors
- * (64 where they differ much in length).  Every item
+ * (64 where they differ much in length, or where they are so long that the
+ * escape records of more would not fit the workspace).  Every item
  * names its own codebook: per-layer codebooks (the
  * section "Ablation on Layer-Wise Coverage") cost no more than shared ones.
  * `items` is a HOST array, read before the call returns.

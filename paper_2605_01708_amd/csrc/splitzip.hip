@@ -168,8 +168,9 @@ uint64_t first_call() {
 }
 // The next tensors of a batch that go into one launch, of n: kBatchFew, and more up to kBatchMax as long as the launch's row
 // of workgroups per tensor, as long as the longest, leaves no more than 8192 workgroups without a tile of four chunks (2 us).
+// most_chunks: of the longest.
 template <typename Item>
-uint32_t tensors_of_launch(const Item* items, uint32_t n) {
+uint32_t tensors_of_launch(const Item* items, uint32_t n, uint64_t* most_chunks = nullptr) {
   uint64_t all = 0, most = 0;
   uint32_t k = 0;
   for (; k < n && k < kBatchMax; ++k) {
@@ -178,7 +179,23 @@ uint32_t tensors_of_launch(const Item* items, uint32_t n) {
     all += c;
     most = longest;
   }
+  if (most_chunks) *most_chunks = most;
   return k;
+}
+// The same for a compress call.  The tensors of a launch share the workspace, which is sized for one of them: the more they are, the less
+// has a tile for its records, and tiles whose records outgrow their slots are encoded twice, 16 of them one after another.  So
+// more than kBatchFew are for launches where a chunk has room for four records, what the staging area alone leaves each of
+// kBatchFew tensors (KV tensors have one or two); others are halved or cut in three.  us per call, BF16, in launches of 64 with slots in the staging
+// area alone, of 160 and this way: 160 tensors of 4096 chunks 382 / 386 / 372 (0.12 % escapes), 418 / 479 / 376 (0.25), 523 / 629 / 400 (0.4); of 8192 745 /
+// 859 / 742, 812 / 1138 / 769, of 32 768 2972 / 3464 / 2956; 100 of 16 384 (0.25) 1016 / 1170 / 925; E5M2 160 of 8192 (0.25) 457 / 654 / 426.
+constexpr uint64_t kRecordsPerChunk = 4;
+uint32_t tensors_of_compress(const splitzip_item* items, uint32_t n, uint64_t status_bytes, uint64_t stage_bytes) {
+  uint64_t longest;
+  const uint32_t k = tensors_of_launch(items, n, &longest);
+  const uint64_t chunks = (g_hooks.stage_bytes ? stage_bytes : status_bytes + stage_bytes) / (4 * kRecordsPerChunk);   // that have so much room
+  if (k <= kBatchFew || k * longest <= chunks) return k;
+  const uint64_t fit = chunks / longest, most = fit > kBatchFew ? fit : kBatchFew, launches = (k + most - 1) / most;
+  return (uint32_t)((k + launches - 1) / launches);
 }
 
 // The tag of a call of compress_short_kernel: no two calls of a process have the same one.
@@ -851,10 +868,10 @@ uint32_t short_each(const splitzip_item* items, uint32_t k, uint64_t status_byte
 
 // items[0, n_items): what is left of the call; n_max: its longest tensor; once: what is enqueued runs once
 template <typename Once>
-CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_t n_max, int dtype, uint64_t status_bytes, const Once& once) {
+CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_t n_max, int dtype, uint64_t status_bytes, uint64_t stage_bytes, const Once& once) {
   CompressPlan p;
   memset(&p, 0, sizeof p);
-  const uint32_t k_most = tensors_of_launch(items, n_items);
+  const uint32_t k_most = tensors_of_compress(items, n_items, status_bytes, stage_bytes);
   p.short_each = g_hooks.any() || g_hooks.short_looks.load() == kNoShort ? 0u : short_each(items, k_most, status_bytes, &p.tiles_max);
   if (p.short_each && once()) {
     p.k = k_most;
@@ -953,7 +970,7 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
 
   uint32_t i = 0;
   while (i < n_items) {
-    const CompressPlan p = plan_compress(items + i, n_items - i, n_max, dtype, ws.status_bytes, [st] { return runs_once(st); });
+    const CompressPlan p = plan_compress(items + i, n_items - i, n_max, dtype, ws.status_bytes, ws.stage_bytes, [st] { return runs_once(st); });
     const uint32_t k = p.k;
     if (k == 0) return SPLITZIP_ERR_CAPACITY;   // cannot happen: every tensor fits alone
     TileArgs<kBatchMax> args;   // the first k items are filled in, and no other is looked at
@@ -1398,8 +1415,9 @@ void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_item
   uint64_t n_max = 0;
   for (uint32_t q = 0; q < n_items; ++q)
     if (items[q].n_elems > n_max) n_max = items[q].n_elems;
-  const CompressPlan p = plan_compress(items, n_items, n_max, dtype, kStatusBytes, [] { return false; });   // the plan under capture
-  const uint32_t each = plan_compress(items, n_items, n_max, dtype, kStatusBytes, [] { return true; }).short_each;   // otherwise
+  const uint64_t stage = splitzip_workspace_bytes(n_max, dtype) - kWsHeaderBytes - kStatusBytes;
+  const CompressPlan p = plan_compress(items, n_items, n_max, dtype, kStatusBytes, stage, [] { return false; });   // the plan under capture
+  const uint32_t each = plan_compress(items, n_items, n_max, dtype, kStatusBytes, stage, [] { return true; }).short_each;   // otherwise
   const uint32_t v[9] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small, each};
   memcpy(out, v, sizeof v);
 }

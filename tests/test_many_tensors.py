@@ -48,3 +48,19 @@ def test_tensors_of_a_launch(dtype):
     assert [tensors([100] * n) for n in (64, 65, 160, 161, 400)] == [64, 65, 160, 160, 160]
     assert tensors([8192] * 64 + [2] * 96) == 68 and tensors([2] * 64 + [8192] * 96) == 64 and tensors([2000, 1900] * 80) == 160
     assert tensors([0] * 200) == 160
+
+
+@pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
+def test_room_for_records(dtype):
+    """A launch takes more than 64 only where that leaves a chunk four records of the workspace, which one tensor sizes; what does
+    not go into one launch goes into equal ones."""
+    def tensors(chunks):
+        return sz.internal_compress_plan([c * 1024 for c in chunks], dtype)["tensors"]
+    for chunks in (2000, 2700, 4096, 8192, 16384, 32768, 100000):
+        for n in (65, 100, 160, 300):
+            count, room = tensors([chunks] * n), sz.workspace_bytes(chunks * 1024, dtype) // 16
+            assert count <= 64 or count * chunks <= room, (chunks, n)
+            assert count == min(n, 160) or -(-min(n, 160) // count) * max(64, room // chunks) >= min(n, 160) > (-(-min(n, 160) // count) - 1) * max(64, room // chunks), (chunks, n)
+    assert [tensors([c] * 160) for c in (2000, 4096, 8192, 16384, 32768)] == [160, 80, 80, 80, 54]
+    assert [tensors([32768] * n) for n in (64, 65, 72, 73, 100)] == [64, 65, 72, 37, 50]
+    assert tensors([32768] * 70 + [100] * 90) == 71 and tensors([8192] * 64 + [2] * 96) == 68
