@@ -68,7 +68,7 @@ enum {
   SPLITZIP_STATUS_OVERFLOW = 1u,   /* compress: escapes did not fit out_capacity; total_bytes is the size needed */
   SPLITZIP_STATUS_BAD_STREAM = 2u, /* decompress: header / offsets / positions inconsistent; offending records skipped */
   SPLITZIP_STATUS_INTERNAL = 4u    /* reserved: no call of this version sets it (earlier versions reported a timed-out
-                                      exchange between workgroups here; the kernels no longer wait for one another) */
+                                      exchange between workgroups here; now the work is left to others) */
 };
 
 /* The three calibration tables of section 3.3.  Plain data, host memory,
@@ -140,8 +140,9 @@ size_t splitzip_compress_bound(uint64_t n_elems, int dtype);
  * n_elems bytes and a little more (the tiles' escape records until their rank
  * in the stream is known).  A compress call is two kernel launches: the first
  * does the dense work tile by tile, the second ranks and places the escape
- * records.  Up to 2 Mi elements (4 Mi in tensors of up to 1 Mi), a call that is not captured into a graph
- * is one launch, whose workgroups tell one another their counts; captured, that
+ * records.  Up to 2 Mi elements in all, a call that is not captured into a graph
+ * is one launch, whose workgroups tell one another their counts (on a stream
+ * with a mask, or on part of a chip, by the share of its CUs); captured, that
  * is so up to 40 chunks of BF16 or 48 of E5M2 per tensor.  No workgroup waits
  * for another without an end (in that one launch for some 50 us at most, then
  * its work is left to those that come after it), so the calls run correctly
@@ -441,7 +442,7 @@ int splitzip_variant_codebook_from_dec(const uint8_t* dec, const splitzip_varian
  * splitzip_decompress; d_workspace needs splitzip_variant_workspace_bytes and
  * 16-byte alignment.  Two kernel launches per compress call (dense pass that
  * also stages the escape records, finishing pass; above 64 Mi elements a
- * third between them sums the counts), up to 2 Mi elements, if not captured,
+ * third between them sums the counts), up to 1 Mi elements, if not captured,
  * one that does both, and one more that packs values narrower than a byte; one per decompress call (two in the absolute mode), all on
  * `stream`. */
 int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip_variant* v,

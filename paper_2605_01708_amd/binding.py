@@ -140,7 +140,7 @@ def lib():
         L.splitzip_internal_test_launch.restype = None
         L.splitzip_internal_test_launch.argtypes = [C.c_uint32, C.c_uint32, C.c_uint32]
         L.splitzip_internal_compress_plan.restype = None
-        L.splitzip_internal_compress_plan.argtypes = [C.POINTER(_CItem), C.c_uint32, i, C.POINTER(C.c_uint32)]
+        L.splitzip_internal_compress_plan.argtypes = [C.POINTER(_CItem), C.c_uint32, i, C.c_uint32, C.POINTER(C.c_uint32)]
         L.splitzip_internal_decompress_plan.restype = None
         L.splitzip_internal_decompress_plan.argtypes = [C.POINTER(_CDItem), C.c_uint32, i, C.POINTER(C.c_uint32)]
         L.splitzip_internal_stream_room.restype = C.c_uint32
@@ -433,13 +433,13 @@ def internal_test_short(looks: int = 0) -> None:
 INTERNAL_NO_SHORT = 0xFFFFFFFF
 
 
-def internal_compress_plan(n_elems, dtype: int) -> dict:
-    """How a compress call's first launch over tensors of these lengths is shaped under capture, and whether it is one of
-    compress_short_kernel otherwise (host only, for tests of the rules)."""
+def internal_compress_plan(n_elems, dtype: int, cus: int = 256) -> dict:
+    """How a compress call's first launch over tensors of these lengths is shaped under capture, and, otherwise, the chunks per wave
+    of compress_short_kernel if that takes them on a stream of so many CUs (host only, for tests of the rules)."""
     items, out = (_CItem * len(n_elems))(), (C.c_uint32 * 9)()
     for it, n in zip(items, n_elems):
         it.n_elems = n
-    lib().splitzip_internal_compress_plan(items, len(n_elems), dtype, out)
+    lib().splitzip_internal_compress_plan(items, len(n_elems), dtype, cus, out)
     return dict(zip(("tensors", "cpt", "tiles_max", "launches", "by_xcd", "finish_groups", "group_sums", "small", "short"), out))
 
 

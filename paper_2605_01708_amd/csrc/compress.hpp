@@ -995,79 +995,60 @@ __global__ __launch_bounds__(kSmallThreads) void compress_small_kernel(const Til
 //   value before a call), kShortLeft, kShortTaken and the count.  One atomic word says all there is to say: nothing else that
 //   a workgroup writes is read by another.  There are kShortCopies copies of a tensor's words and a workgroup reads one of
 //   them: all workgroups reading the same few lines from the device's point of coherence took longer than the work.
-//   No wait is without an end.  A workgroup that has looked a.slot_cap times (the rest of the launch does not get onto the
-//   chip) marks its tile as left, looks once more and, if counts are missing still, ends.  The mark and the count are
+//   No wait is without an end.  A workgroup that has looked a.slot_cap times (50 us, in which the rest of the launch has not got onto
+//   the chip) marks its tile as left, looks once more and, if counts are missing still, ends.  The mark and the count are
 //   each written, and the write waited for, before the writer looks at the other words: so whoever publishes last of all
 //   sees all counts the first time it looks, and with them the mark of every workgroup that looked for the last time
 //   before that.  Tiles left are encoded again by whichever workgroup takes them first (kShortTaken, in the first copy).
 constexpr uint32_t kShortCopies = 8;
+constexpr uint32_t kShortMostCpt = 2;   // chunks per wave
 constexpr int kShortTagShift = 17;
 constexpr uint32_t kShortCount = 0x7fffu, kShortLeft = 0x8000u, kShortTaken = 0x10000u;
-static_assert(kTileThreads / 64 * kChunk <= kShortCount && (kShortLeft | kShortTaken | kShortCount) >> kShortTagShift == 0, "a tile's count and its marks below the tag");
+static_assert(kTileThreads / 64 * kShortMostCpt * kChunk <= kShortCount && (kShortLeft | kShortTaken | kShortCount) >> kShortTagShift == 0, "a tile's count and its marks below the tag");
 // bytes of one copy of a tensor's words; a tensor without elements has one, too
 __host__ __device__ inline uint64_t short_copy_bytes(uint64_t tiles) { return a256(8 * (tiles ? tiles : 1)); }
 
-// LDS of it
-template <int EACH>
+// LDS of it; a thread looks at one word, so a tensor has no more tiles than that
+constexpr uint32_t kShortTiles = kTileThreads;
 struct ShortShared {
   static constexpr int NW = kTileThreads / 64;
   uint32_t all[NW], before[NW], state[NW], won;
-  uint32_t tile[EACH * kTileThreads];   // only where tiles were left
+  uint32_t tile[kShortTiles];   // only where tiles were left
 };
-// What the workgroups of a tensor tell one another.  EACH: words that a thread looks at; a tensor has no more tiles than that many
-// times the threads.
-template <int EACH>
+// What the workgroups of a tensor tell one another.
 struct ShortCounts {
   static constexpr int NW = kTileThreads / 64;
   uint64_t* words;     // the first copy of the tensor's
   uint64_t tag;
   uint32_t n_tiles, copy, own;   // copy: words from one copy to the next; own: the workgroup's tile
-  uint64_t v[EACH];    // thread and register <-> tile
+  uint64_t v;          // the word of tile `tid`
   uint32_t state;      // bit 0: all counts are there; bit 1: a tile was left
   uint32_t first, M;   // escapes of the tensor before a tile; all of them
 
   __device__ inline ShortCounts(uint64_t* at, uint64_t call, uint32_t tiles, uint32_t tile)
-      : words(at), tag(call), n_tiles(tiles), copy((uint32_t)(short_copy_bytes(tiles) / 8)), own(tile), state(0), first(0), M(0) {
-#pragma unroll
-    for (int q = 0; q < EACH; ++q) v[q] = tag;
-  }
+      : words(at), tag(call), n_tiles(tiles), copy((uint32_t)(short_copy_bytes(tiles) / 8)), own(tile), v(call), state(0), first(0), M(0) {}
   // The own word, written at the device's point of coherence before anyone of this workgroup looks at the others', as
   // often as `times` at most; meanwhile() while it is on its way.  rank() and overall() follow.
   template <typename Meanwhile>
-  __device__ inline void tell_and_look(ShortShared<EACH>& s, uint32_t total, uint32_t mark, uint32_t times, uint32_t tid, uint32_t wave, const Meanwhile& meanwhile) {
+  __device__ inline void tell_and_look(ShortShared& s, uint32_t total, uint32_t mark, uint32_t times, uint32_t tid, uint32_t wave, const Meanwhile& meanwhile) {
     if (tid < kShortCopies) st_agent(words + tid * copy + own, tag | mark | total);
     meanwhile();
     if (wave == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
     bool here;
     for (;;) {
-      here = true;
-#pragma unroll
-      for (int q = 0; q < EACH; ++q)
-        if (q * kTileThreads + tid < n_tiles) v[q] = ld_agent(words + (own % kShortCopies) * copy + q * kTileThreads + tid);
-#pragma unroll
-      for (int q = 0; q < EACH; ++q) here = here && ((v[q] ^ tag) >> kShortTagShift) == 0;
-      here = __all(here);
+      if (tid < n_tiles) v = ld_agent(words + (own % kShortCopies) * copy + tid);
+      here = __all(((v ^ tag) >> kShortTagShift) == 0);
       if (here || --times == 0) break;
       __builtin_amdgcn_s_sleep(1);
     }
-    uint32_t marks = 0;
-#pragma unroll
-    for (int q = 0; q < EACH; ++q) marks |= (uint32_t)v[q];
-    const bool left = __any(marks & kShortLeft);
+    const bool left = __any((uint32_t)v & kShortLeft);
     if ((tid & 63u) == 0) s.state[wave] = (here ? 1u : 0u) | (left ? 2u : 0u);
   }
   // with a barrier
-  __device__ inline void rank(ShortShared<EACH>& s, uint32_t tile, uint32_t tid, uint32_t wave) {
-    uint32_t all = 0, before = 0;
-#pragma unroll
-    for (int q = 0; q < EACH; ++q) {
-      const uint32_t x = (uint32_t)v[q] & kShortCount;
-      all += x;
-      before += q * kTileThreads + tid < tile ? x : 0u;
-    }
-    all = wave_last(wave_incl_scan(all));
-    before = wave_last(wave_incl_scan(before));
+  __device__ inline void rank(ShortShared& s, uint32_t tile, uint32_t tid, uint32_t wave) {
+    const uint32_t x = (uint32_t)v & kShortCount;
+    const uint32_t all = wave_last(wave_incl_scan(x)), before = wave_last(wave_incl_scan(tid < tile ? x : 0u));
     if ((tid & 63u) == 0) {
       s.before[wave] = before;
       s.all[wave] = all;
@@ -1080,7 +1061,7 @@ struct ShortCounts {
       M += s.all[q];
     }
   }
-  __device__ inline void overall(const ShortShared<EACH>& s) {
+  __device__ inline void overall(const ShortShared& s) {
     state = 1u;
 #pragma unroll
     for (int q = 0; q < NW; ++q) {
@@ -1089,7 +1070,7 @@ struct ShortCounts {
     }
   }
   // whether a tile that was marked as left is this workgroup's now
-  __device__ inline bool take(ShortShared<EACH>& s, uint32_t tile, uint32_t told, uint32_t tid) {
+  __device__ inline bool take(ShortShared& s, uint32_t tile, uint32_t told, uint32_t tid) {
     __syncthreads();
     if (tid == 0) {
       uint64_t seen = tag | kShortLeft | told;
@@ -1101,13 +1082,13 @@ struct ShortCounts {
   // A workgroup's way through a launch: encode(tile, first) makes a tile and leaves its count in total, deliver() writes its
   // planes and stages its records, place(tile) puts those where first and M say.
   template <typename Encode, typename Deliver, typename Place>
-  __device__ inline void run(ShortShared<EACH>& s, uint32_t looks, const uint32_t& total, uint32_t tid, uint32_t wave, const Encode& encode, const Deliver& deliver, const Place& place) {
+  __device__ inline void run(ShortShared& s, uint32_t looks, const uint32_t& total, uint32_t tid, uint32_t wave, const Encode& encode, const Deliver& deliver, const Place& place) {
     encode(own, true);
     if (n_tiles > 1) {
       tell_and_look(s, total, 0u, looks, tid, wave, deliver);
     } else {   // nobody to tell
       deliver();
-      if (tid == 0) v[0] |= total;
+      if (tid == 0) v |= total;
       if ((tid & 63u) == 0) s.state[wave] = 1u;
     }
     rank(s, own, tid, wave);
@@ -1127,8 +1108,7 @@ struct ShortCounts {
     }
     if (keep) place(own);
     // tiles that their workgroups have left (the loop is not one with what is above: that cost 0.3 us, in registers)
-#pragma unroll
-    for (int q = 0; q < EACH; ++q) s.tile[q * kTileThreads + tid] = (uint32_t)v[q] & (kShortLeft | kShortTaken | kShortCount);
+    s.tile[tid] = (uint32_t)v & (kShortLeft | kShortTaken | kShortCount);
     __syncthreads();
 #pragma unroll 1
     for (uint32_t tile = 0; tile < n_tiles; ++tile) {
@@ -1142,22 +1122,23 @@ struct ShortCounts {
   }
 };
 
+// CPT: chunks per wave.  What a launch may not do is fill the chip: calls on other streams have theirs there (pick_short).  So one of
+// more than 256 workgroups with a chunk per wave has two, at most 128 registers each: 2048 chunks 5.2 us a call with one, 5.6 with two, and
+// on four streams side by side 5.4 and 2.1.
 // The count is told before the planes are on
-// their way: us per call with them in front of it and behind, BF16 4.87 and 4.59 (1024 chunks), 5.74 and 5.19 (2048), E5M2 4.64 and 4.17, 5.64 and
-// 4.82.
-// Workgroups of eight waves are 0.25 us faster at 2048 chunks but get onto a busy chip late, and everyone waits for them (beside
-// elementwise kernels that fill it 22 to 27 us a call, 16.9 with four, two launches 20.2; at 4096 chunks 216 and 21); two
-// chunks per wave took 0.3 us more.  It gains most where chunks escape whole: the finishing pass encodes tiles whose
-// records outgrow their slots once more, a workgroup 16 of them (2048 chunks of random words 62 us a call, 9.7 this way).
-template <typename F, uint32_t N, int EACH>
-__global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const TileArgs<N> args) {
+// their way: us per call with them in front of it and behind, BF16 4.87 and 4.59 (1024 chunks), E5M2 4.64 and 4.17.
+// Workgroups of eight waves get onto a busy chip late, and everyone waits for them (beside
+// elementwise kernels that fill it 22 to 27 us a call, 16.9 with four, two launches 20.2).  It gains most where chunks escape whole: the finishing pass encodes tiles whose
+// records outgrow their slots once more, a workgroup 16 of them (2048 chunks of random words 62 us a call, 14 this way).
+template <typename F, uint32_t N, int CPT>
+__global__ __launch_bounds__(kTileThreads, CPT == 1 ? 1 : 4) void compress_short_kernel(const TileArgs<N> args) {
   constexpr int NW = kTileThreads / 64;
   __shared__ uint16_t lut[256];
-  __shared__ uint16_t stage_pos[NW][kChunk];   // room for all of a wave's records
-  __shared__ uint8_t stage_val[NW][kChunk];
+  __shared__ uint16_t stage_pos[NW][CPT * kChunk];   // room for all of a wave's records
+  __shared__ uint8_t stage_val[NW][CPT * kChunk];
   __shared__ u32x4 s_park[kTileThreads];
   __shared__ uint32_t s_cnt[NW];
-  __shared__ ShortShared<EACH> s_short;
+  __shared__ ShortShared s_short;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t item = blockIdx.y, own = blockIdx.x;
@@ -1165,49 +1146,65 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
   TileItem it;
   args_arrived(args, item, a, it);
   const Planes P = make_planes(item_words(a.paging, it.in), it.out, it.n, it.capacity, F::DT);
-  const uint32_t n_tiles = (P.n_chunks + NW - 1) / NW;
+  const uint32_t n_tiles = (P.n_chunks + NW * CPT - 1) / (NW * CPT);
   if (own >= (n_tiles ? n_tiles : 1u)) return;   // a tensor without elements still gets its header
-  ShortCounts<EACH> counts(reinterpret_cast<uint64_t*>(a.status + it.status_off), a.stage_cap, n_tiles, own);
+  ShortCounts counts(reinterpret_cast<uint64_t*>(a.status + it.status_off), a.stage_cap, n_tiles, own);
   uint32_t* park = reinterpret_cast<uint32_t*>(&s_park[tid]);
-  const LdsSink lds{stage_pos[wave], stage_val[wave], 0u, kChunk};
+  const LdsSink lds{stage_pos[wave], stage_val[wave], 0u, CPT * kChunk};
 
-  uint32_t c = 0, count = 0;              // the wave's chunk and its escapes
-  uint32_t in_tile = 0, total = 0;        // escapes of the tile before the wave's chunk; all of them
+  uint32_t c = 0, count[CPT] = {}, mine = 0;   // the wave's first chunk, the escapes of its chunks, all of them
+  uint32_t in_tile = 0, total = 0;             // escapes of the tile before the wave's chunks; all of them
   // A tile's words and counts, then, with the count told, its planes out and its records staged: the others need the one,
   // and the stores need not be over when they are looked for.
-  typename F::Regs w;
-  typename F::Coded coded;
-  bool whole = false;                     // all chunks of the tile are complete
+  typename F::Regs w[CPT];
+  typename F::Coded coded[CPT];
+  bool whole = false;                          // all chunks of the tile are complete
   auto encode = [&](uint32_t tile, bool build) {
-    c = NW * tile + wave;
-    count = 0;
-    const uint64_t cbase = (uint64_t)c * kChunk;
+    c = CPT * (NW * tile + wave);
     auto table = [&]() {   // while the words are on their way
       if (!build) return;
       build_encode_table(lut, a.dec16_of(it, item), tid, F::kLutShift);
       lds_barrier();
     };
-    whole = F::full(P, (uint64_t)(NW * tile + NW - 1) * kChunk);
+    auto words_of = [&](int j) { return chunk_at<F::ES>(P.w, (uint64_t)(c + j) * kChunk, P.w.table ? page_of_wave_chunk(P.w, c + j) : 0u); };
+    whole = F::full(P, (uint64_t)(CPT * NW * (tile + 1) - 1) * kChunk);
     if (whole) {
-      F::template load<true>(P, chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_wave_chunk(P.w, c) : 0u), cbase, lane, w);
+#pragma unroll
+      for (int j = 0; j < CPT; ++j) F::template load<true>(P, words_of(j), (uint64_t)(c + j) * kChunk, lane, w[j]);
       table();
-      F::template encode<true>(P, lut, cbase, lane, w, coded);
-      count = F::count(coded);
+#pragma unroll
+      for (int j = 0; j < CPT; ++j) {
+        F::template encode<true>(P, lut, (uint64_t)(c + j) * kChunk, lane, w[j], coded[j]);
+        count[j] = F::count(coded[j]);
+      }
     } else {
-      const bool full = F::full(P, cbase);
-      if (c < P.n_chunks) {
-        const uint8_t* cptr = chunk_at<F::ES>(P.w, cbase, P.w.table ? page_of_wave_chunk(P.w, c) : 0u);
-        if (full) F::template load<true>(P, cptr, cbase, lane, w);
-        else F::template load<false>(P, cptr, cbase, lane, w);
+      bool full[CPT];
+#pragma unroll
+      for (int j = 0; j < CPT; ++j) {
+        const uint64_t cbase = (uint64_t)(c + j) * kChunk;
+        full[j] = F::full(P, cbase);
+        if (c + j < P.n_chunks) {
+          const uint8_t* cptr = words_of(j);
+          if (full[j]) F::template load<true>(P, cptr, cbase, lane, w[j]);
+          else F::template load<false>(P, cptr, cbase, lane, w[j]);
+        }
       }
       table();
-      if (c < P.n_chunks) {
-        if (full) F::template encode<true>(P, lut, cbase, lane, w, coded);
-        else F::template encode<false>(P, lut, cbase, lane, w, coded);
-        count = F::count(coded);
+#pragma unroll
+      for (int j = 0; j < CPT; ++j) {
+        const uint64_t cbase = (uint64_t)(c + j) * kChunk;
+        count[j] = 0;
+        if (c + j < P.n_chunks) {
+          if (full[j]) F::template encode<true>(P, lut, cbase, lane, w[j], coded[j]);
+          else F::template encode<false>(P, lut, cbase, lane, w[j], coded[j]);
+          count[j] = F::count(coded[j]);
+        }
       }
     }
-    if (lane == 0) s_cnt[wave] = count;
+    mine = 0;
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) mine += count[j];
+    if (lane == 0) s_cnt[wave] = mine;
     lds_barrier();
     in_tile = total = 0;
 #pragma unroll
@@ -1218,10 +1215,15 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
     }
   };
   auto deliver = [&]() {
-    const uint64_t cbase = (uint64_t)c * kChunk;
-    if (whole || (c < P.n_chunks && F::full(P, cbase))) F::template store<true>(P, cbase, lane, coded);
-    else if (c < P.n_chunks) F::template store<false>(P, cbase, lane, coded);
-    F::emit(park, lane, w, coded, count, 0u, lds);
+    uint32_t first = 0;
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+      const uint64_t cbase = (uint64_t)(c + j) * kChunk;
+      if (whole || (c + j < P.n_chunks && F::full(P, cbase))) F::template store<true>(P, cbase, lane, coded[j]);
+      else if (c + j < P.n_chunks) F::template store<false>(P, cbase, lane, coded[j]);
+      F::emit(park, lane, w[j], coded[j], count[j], first, lds);
+      first += count[j];
+    }
   };
 
   // the tile's records and table entries where they belong; the stream's header and pads with the first tile
@@ -1233,10 +1235,11 @@ __global__ __launch_bounds__(kTileThreads) void compress_short_kernel(const Tile
     fin.val = P.out + off_val;
     fin.val_room = room32(P.capacity, off_val, 0);
     const uint32_t base = counts.first + in_tile;
-    if (c < P.n_chunks && lane == 0) reinterpret_cast<uint32_t*>(P.out + P.off_tab)[c] = base;
-    for (uint32_t i = lane; i < count; i += 64) fin.put(base + i, stage_pos[wave][i], stage_val[wave][i]);
+    if (lane < CPT && c + lane < P.n_chunks) reinterpret_cast<uint32_t*>(P.out + P.off_tab)[c + lane] = base + (CPT > 1 && lane ? count[0] : 0u);
+    for (uint32_t i = lane; i < mine; i += 64) fin.put(base + i, stage_pos[wave][i], stage_val[wave][i]);
     if (tile == 0 && wave == NW - 1) compress_write_trailer(P, a.dec16_of(it, item), a.sizes + item, counts.M, 0u, lane);
   };
+  static_assert(CPT <= (int)kShortMostCpt, "the second chunk's entry is what the first holds");
   counts.run(s_short, a.slot_cap, total, (uint32_t)tid, (uint32_t)wave, encode, deliver, place);
 }
 

@@ -15,6 +15,7 @@
 // granule) is owned by one wave; every global access of a wave is one fully coalesced run of 16,
 // 8 or 4 bytes per lane; all plane traffic uses non-temporal loads and stores, nothing is re-used.
 #include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
 #include <stddef.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -206,12 +207,25 @@ uint64_t next_call_tag() {
   while (!tag);   // what cleared memory holds
   return tag;
 }
-// Whether what is enqueued now runs once: a captured launch is replayed with the tag that it was captured with.
-bool runs_once(hipStream_t st) {
+// How many CUs a launch of so many workgroups that is enqueued now can have, and 0 if it may run more than once: a captured launch is
+// replayed with the tag that it was captured with.
+uint64_t cus_once(hipStream_t st, uint64_t wgs) {
   hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s == hipStreamCaptureStatusNone;
-  (void)hipGetLastError();   // the legacy stream while another one is captured: the launch will say so itself
-  return false;
+  if (hipStreamIsCapturing(st, &s) != hipSuccess) {
+    (void)hipGetLastError();   // the legacy stream while another one is captured: the launch will say so itself
+    return 0;
+  }
+  if (s != hipStreamCaptureStatusNone) return 0;
+  const uint64_t all = (uint64_t)cu_count();
+  if (!st || wgs <= all / 8) return all;   // a few fit any part of a chip
+  uint32_t mask[32] = {0};   // of a stream that was made with one (the question takes 0.2 us)
+  if (all > 32 * 32 || hipExtStreamGetCUMask(st, (uint32_t)(all + 31) / 32, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return all;
+  }
+  uint64_t cus = 0;
+  for (const uint32_t w : mask) cus += (uint64_t)__builtin_popcount(w);
+  return cus && cus < all ? cus : all;
 }
 
 constexpr uint32_t kShortLooks = 64;   // about 50 us
@@ -306,14 +320,10 @@ void variant_tables(const splitzip_variant* v, const splitzip_codebook* cb, VArg
     }                                                                                                              \
   } while (0)
 
-template <int DT, int CB>
-constexpr auto v_short_two = v_short_kernel<DT, CB, 2>;   // two words a thread, 0.05 to 0.15 us faster than three
-template <int DT, int CB>
-constexpr auto v_short_three = v_short_kernel<DT, CB, 3>;
-// Whether v_short_kernel takes a tensor of so many tiles of four blocks.  Its words lie in the blocks' slots, 2 KB
+// Whether v_short_kernel takes a tensor of so many tiles of four blocks, as in pick_short.  Its words lie in the blocks' slots, 2 KB
 // per tile of four blocks; a tensor of one tile has no words.
-bool variant_short(uint64_t tiles) {
-  return tiles >= 1 && tiles <= kVShortTiles && g_hooks.short_looks.load() != kNoShort;
+bool variant_short(uint64_t tiles, hipStream_t st) {
+  return tiles >= 1 && tiles <= kShortTiles && g_hooks.short_looks.load() != kNoShort && tiles <= cus_once(st, tiles);
 }
 
 void launch_v_pack(uint64_t n_elems, hipStream_t st, const VArgs& a) {
@@ -477,15 +487,14 @@ int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip
   a.n_sums = direct ? grid : a.n_tiles;
   a.sum_shift = direct ? 2u + (10u - a.chunk_shift) : 10u;
   a.ahead = v->k <= 8 ? 64u : 16u;   // a top-8 codebook leaves about 60 records per block, a larger one one or two
-  if (variant_short(grid) && runs_once(st)) {
+  if (variant_short(grid, st)) {
     VShortArgs sa;
     sa.a = a;
     sa.short_words = reinterpret_cast<uint64_t*>(a.slots);
     sa.tag = next_call_tag();
     sa.looks = short_looks();
     sa.tiles = grid;
-    if (grid <= 2 * kTileThreads) SPLITZIP_V_DISPATCH3(v_short_two, a, dim3(grid), dim3(kThreads), st, sa);
-    else SPLITZIP_V_DISPATCH3(v_short_three, a, dim3(grid), dim3(kThreads), st, sa);
+    SPLITZIP_V_DISPATCH3(v_short_kernel, a, dim3(grid), dim3(kThreads), st, sa);
     if (a.val_bits != 8) launch_v_pack(n_elems, st, a);
     return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
   }
@@ -813,16 +822,16 @@ void launch_small(unsigned k, hipStream_t st, const TileArgs<kBatchMax>& args) {
   }
 }
 
-template <typename F, int EACH>
+template <typename F, int CPT>
 void launch_short(unsigned tiles, unsigned k, hipStream_t st, const TileArgs<kBatchMax>& args) {
   const dim3 grid(tiles ? tiles : 1u, k), block(kTileThreads);
   if (k == 1) {
     const TileArgs<1> one = {args.shared, {args.item[0]}};
-    launch(compress_short_kernel<F, 1, EACH>, grid, block, 0, st, one);
+    launch(compress_short_kernel<F, 1, CPT>, grid, block, 0, st, one);
   } else if (k <= kBatchFew) {
-    launch(compress_short_kernel<F, kBatchFew, EACH>, grid, block, 0, st, few(args));
+    launch(compress_short_kernel<F, kBatchFew, CPT>, grid, block, 0, st, few(args));
   } else {
-    launch(compress_short_kernel<F, kBatchMax, EACH>, grid, block, 0, st, args);
+    launch(compress_short_kernel<F, kBatchMax, CPT>, grid, block, 0, st, args);
   }
 }
 
@@ -832,57 +841,78 @@ struct CompressPlan {
   uint32_t cpt;             // chunks per wave and tile
   uint64_t tiles_max;       // of the longest tensor: the dense pass has k rows of so many workgroups
   bool small;               // one launch of compress_small_kernel
-  uint32_t short_each;      // one launch of compress_short_kernel, whose threads look at so many words; 0: not that
+  bool is_short;            // one launch of compress_short_kernel
   bool by_xcd;              // the dense pass takes its tiles in xcd_order
   uint32_t lds_pad;         // unused LDS asked for at the launch of the dense pass: fewer workgroups per CU
   bool is_long;             // the dense pass stores through the L2 (kTileLong)
   uint32_t finish_groups;   // groups of kGroup tiles per workgroup of the finishing pass
   uint32_t finish_wgs;      // workgroups of the finishing pass per tensor
   bool group_sums;          // the finishing pass is given sums of kSumGroup tile counts
-  uint32_t launches() const { return small || short_each ? 1u : group_sums ? 3u : tiles_max ? 2u : 1u; }
+  uint32_t launches() const { return small || is_short ? 1u : group_sums ? 3u : tiles_max ? 2u : 1u; }
 };
 
 constexpr uint32_t kSmallestShort = 16;   // shorter tensors are one workgroup's work
 uint64_t short_status_need(uint64_t tiles) { return kShortCopies * short_copy_bytes(tiles); }
-// Words that a thread of compress_short_kernel looks at if it takes these tensors (tiles_max: of the longest), else 0.
+// Chunks per wave of compress_short_kernel if it takes these tensors, else 0; wgs: its workgroups with a tile, tiles_max: of the
+// longest tensor.
 // us per call, one behind the other, of two launches (of one workgroup per tensor up to 40 chunks) and this way: BF16 16 chunks 4.1
-// and 4.1, 24 4.6 and 4.0, 40 5.7 and 4.0, 100 7.3 and 4.1, 512 7.1 and 4.3, 1024 7.1 and 4.6, 2048 7.05 and 5.2; E5M2 100 7.0 and 4.0, 1024 7.2 and 4.2,
-// 2048 7.1 and 4.8; BF16 2300 7.2 and 5.6, 2816 7.25 and 6.0, E5M2 2560 7.2 and 5.3; 64 BF16 tensors of 16 chunks 4.85 and 5.0, of 40 7.2 and 6.0, of 50 8.0 and 5.8, 16 of 256 8.05 and 6.1; with the planes
-// stored before the counts are told, 64 of 100 9.8 and 9.7, four of 1000 8.0 and 6.5, 8 of 1000 10.6 and 12.3, 64 of 1000 42 and 101.
-// Every workgroup looks at all words of its tensor, so the cost grows with the square of them, and one that waits keeps others from the
-// chip.  Where a tensor has more than 256 tiles the line is the busy chip: beside elementwise kernels that fill it 20.4 and 17.0 (2300 and
-// 2560 chunks), 20.4 and 17.8 (2816), 20.4 and 19.6 (3072), 20.5 and 63 (3500), beside matrix products 168 and 109 at all of them; alone,
-// 3072 7.25 and 6.2, 3500 7.6 and 7.6, E5M2 3500 7.2 and 5.85.  What bounds calls of up to 500 chunks now is the host: a launch takes it 2.3 us.
-uint32_t short_each(const splitzip_item* items, uint32_t k, uint64_t status_bytes, uint64_t* tiles_max) {
-  uint64_t chunks_max = 0, chunks_all = 0, need = 0;
+// and 4.1, 24 4.6 and 4.0, 40 5.7 and 4.0, 100 6.9 and 4.1, 512 7.0 and 4.2, 1024 7.1 and 4.6, and with two chunks per wave 1025 7.2 and 5.5, 2048 7.3 and
+// 5.6; E5M2 100 7.3 and 4.0, 1024 7.0 and 4.2, 2048 7.2 and 5.2; 64 BF16 tensors of 16 chunks 4.85 and 5.0, of 32 6.3 and 5.4, 16 of 100 7.1 and 5.0.
+// The line is what calls on several streams leave one another: five workgroups fit a CU (four with two chunks per wave), a
+// process has four hardware queues, and where the launches of all are not resident together they wait for workgroups that wait for the
+// chip.  us per call of four streams side by side, two launches and this way: BF16 1024 chunks (256 workgroups) 2.0 and 1.6, 1280 2.1 and 1.9, but 1536 2.3
+// and 2.3-3.8, 1792 2.4 and 4.4, 2048 2.5 and 5.4, 2816 2.8 and 75; with two chunks per wave 1536 2.3 and 2.0, 2048 2.5 and 2.1.  Of a batch the tensors
+// wait only for themselves: 16 of 100 (400 workgroups) 2.4 and 2.0, 64 of 32 (512) 2.4 and 2.3, four of 500 2.6 and 2.5, but two of 1024 2.5 and 2.8, 64 of 60
+// 3.5 and 4.3, four of 1000 3.4 and 8.2, and with two chunks per wave 64 of 60 (512) 3.5 and 3.7, four of 1000 3.4 and 4.3.
+// On a stream of 32 CUs 2048 chunks take 10 us in two launches and took 360 this way.  Beside elementwise kernels that fill the chip
+// 1000 chunks 20.2 and 16.0, 2048 20.2 and 17.6, beside matrix products 166 and 109, 165 and 110.
+// What bounds calls of up to 500 chunks now is the host: a launch takes it 2.3 us.
+uint32_t pick_short(const splitzip_item* items, uint32_t k, uint64_t status_bytes, uint64_t cus, uint64_t* wgs, uint64_t* tiles_max) {
+  uint64_t chunks_max = 0;
   for (uint32_t q = 0; q < k; ++q) {
     const uint64_t c = chunks_of(items[q].n_elems);
     if (c > chunks_max) chunks_max = c;
-    chunks_all += c;
-    need += short_status_need(tiles_of(c, 1));
   }
-  *tiles_max = tiles_of(chunks_max, 1);
-  const uint32_t each = *tiles_max <= kTileThreads ? 1u : *tiles_max <= 2 * kTileThreads ? 2u : 3u;
-  return chunks_max > kSmallestShort && chunks_all <= (each == 1 ? 4096u : 2816u) && need <= status_bytes ? each : 0u;
+  if (chunks_max <= kSmallestShort) return 0;
+  for (uint32_t cpt = 1; cpt <= kShortMostCpt; cpt *= 2) {
+    const uint64_t longest = tiles_of(chunks_max, cpt);
+    if (longest > kShortTiles || longest > cus) continue;
+    uint64_t tiles = 0, need = 0;
+    for (uint32_t q = 0; q < k; ++q) {
+      const uint64_t t = tiles_of(chunks_of(items[q].n_elems), cpt);
+      tiles += t;
+      need += short_status_need(t);
+    }
+    const bool fit = cpt > 1 ? tiles <= cus : longest <= cus / 2 ? tiles <= 2 * cus : tiles <= cus + cus / 4;
+    if (fit && need <= status_bytes) {
+      *wgs = tiles;
+      *tiles_max = longest;
+      return cpt;
+    }
+  }
+  return 0;
 }
 
-// items[0, n_items): what is left of the call; n_max: its longest tensor; once: what is enqueued runs once
+// items[0, n_items): what is left of the call; n_max: its longest tensor; once(wgs): how many CUs so many workgroups can have, 0 if what
+// is enqueued may run more than once
 template <typename Once>
 CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_t n_max, int dtype, uint64_t status_bytes, uint64_t stage_bytes, const Once& once) {
   CompressPlan p;
   memset(&p, 0, sizeof p);
   const uint32_t k_most = tensors_of_compress(items, n_items, status_bytes, stage_bytes);
-  p.short_each = g_hooks.any() || g_hooks.short_looks.load() == kNoShort ? 0u : short_each(items, k_most, status_bytes, &p.tiles_max);
-  if (p.short_each && once()) {
-    p.k = k_most;
-    p.cpt = 1;
-    return p;
+  const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
+  uint64_t wgs;
+  if (!g_hooks.any() && g_hooks.short_looks.load() != kNoShort && pick_short(items, k_most, status_bytes, cus, &wgs, &p.tiles_max)) {
+    p.cpt = pick_short(items, k_most, status_bytes, once(wgs), &wgs, &p.tiles_max);
+    if (p.cpt) {
+      p.is_short = true;
+      p.k = k_most;
+      return p;
+    }
+    p.tiles_max = 0;
   }
-  p.short_each = 0;
-  p.tiles_max = 0;
   // as many of the next tensors as find room for their counts in the status area; all of them share
   // the tile size of the one that needs the largest
-  const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
   uint64_t chunks_all = 0, chunks_max = 0;
   for (uint32_t q = 0; q < k_most; ++q) {
     const uint64_t c = chunks_of(items[q].n_elems);
@@ -970,7 +1000,7 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
 
   uint32_t i = 0;
   while (i < n_items) {
-    const CompressPlan p = plan_compress(items + i, n_items - i, n_max, dtype, ws.status_bytes, ws.stage_bytes, [st] { return runs_once(st); });
+    const CompressPlan p = plan_compress(items + i, n_items - i, n_max, dtype, ws.status_bytes, ws.stage_bytes, [st](uint64_t wgs) { return cus_once(st, wgs); });
     const uint32_t k = p.k;
     if (k == 0) return SPLITZIP_ERR_CAPACITY;   // cannot happen: every tensor fits alone
     TileArgs<kBatchMax> args;   // the first k items are filled in, and no other is looked at
@@ -987,7 +1017,7 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
       to.capacity = it.out_capacity;
       to.status_off = (uint32_t)off;
       const uint64_t tiles = tiles_of(chunks_of(it.n_elems), p.cpt);
-      off += p.short_each ? short_status_need(tiles) : status_need(tiles);
+      off += p.is_short ? short_status_need(tiles) : status_need(tiles);
     }
     a.sizes = d_sizes + i;
     a.d_cbs = d_cbs ? d_cbs + i : nullptr;
@@ -1009,11 +1039,11 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     a.use_group_sums = p.group_sums ? 1u : 0u;
     a.by_xcd = p.by_xcd ? 1u : 0u;
     const unsigned tiles_max = (unsigned)p.tiles_max, sums_max = (tiles_max + kSumGroup - 1) / kSumGroup;
-    if (p.short_each) {
+    if (p.is_short) {
       a.stage_cap = next_call_tag();
       a.slot_cap = short_looks();
-      if (dtype == SPLITZIP_BF16) (p.short_each == 1 ? launch_short<Bf16, 1> : p.short_each == 2 ? launch_short<Bf16, 2> : launch_short<Bf16, 3>)(tiles_max, k, st, args);
-      else (p.short_each == 1 ? launch_short<E5m2, 1> : p.short_each == 2 ? launch_short<E5m2, 2> : launch_short<E5m2, 3>)(tiles_max, k, st, args);
+      if (dtype == SPLITZIP_BF16) (p.cpt == 1 ? launch_short<Bf16, 1> : launch_short<Bf16, 2>)(tiles_max, k, st, args);
+      else (p.cpt == 1 ? launch_short<E5m2, 1> : launch_short<E5m2, 2>)(tiles_max, k, st, args);
     } else if (p.small) {
       if (dtype == SPLITZIP_BF16) launch_small<Bf16>(k, st, args);
       else launch_small<E5m2>(k, st, args);
@@ -1411,14 +1441,14 @@ int splitzip_decompress_batch_paged(const splitzip_ditem* items, uint32_t n_item
 }
 
 // the plan of a call's first launch, for tests of the rules (exported, not declared in splitzip.h): only the items' n_elems are read
-void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_items, int dtype, uint32_t out[9]) {
+void splitzip_internal_compress_plan(const splitzip_item* items, uint32_t n_items, int dtype, uint32_t cus, uint32_t out[9]) {
   uint64_t n_max = 0;
   for (uint32_t q = 0; q < n_items; ++q)
     if (items[q].n_elems > n_max) n_max = items[q].n_elems;
   const uint64_t stage = splitzip_workspace_bytes(n_max, dtype) - kWsHeaderBytes - kStatusBytes;
-  const CompressPlan p = plan_compress(items, n_items, n_max, dtype, kStatusBytes, stage, [] { return false; });   // the plan under capture
-  const uint32_t each = plan_compress(items, n_items, n_max, dtype, kStatusBytes, stage, [] { return true; }).short_each;   // otherwise
-  const uint32_t v[9] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small, each};
+  const CompressPlan p = plan_compress(items, n_items, n_max, dtype, kStatusBytes, stage, [](uint64_t) { return 0ull; });   // the plan under capture
+  const CompressPlan o = plan_compress(items, n_items, n_max, dtype, kStatusBytes, stage, [cus](uint64_t) { return (uint64_t)cus; });   // otherwise, where a stream has so many CUs
+  const uint32_t v[9] = {p.k, p.cpt, (uint32_t)p.tiles_max, p.launches(), p.by_xcd, p.finish_groups, p.group_sums, p.small, o.is_short ? o.cpt : 0u};
   memcpy(out, v, sizeof v);
 }
 // the launches of a calibration call on a chip of 256 CUs

@@ -645,18 +645,16 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs args) {
 // Short calls (splitzip_variant_compress): the passes above in one launch, as in compress_short_kernel, a block per wave.
 // short_words: where the workgroups' words lie (the blocks' slots, which nothing is staged in here); tag, looks: as there; tiles: the
 // launch's workgroups (asked for as gridDim, a launch has 256 bytes more of arguments).
-// us per call, two launches and this: BF16 top-8 7.8 and 4.4 (4 blocks), 8.0 and 5.1 (100), 8.2 and 5.3 (1000), 8.7 and 5.8 (2000), 9.3 and
-// 6.4 (2816), sentinels 7.8 and 4.3 (100), 8.1 and 5.1 (2000), 7.65 and 5.7 (2816); E5M2 7.8 and 4.4, 7.9 and 5.1, 7.5 and 5.8; with the planes
-// stored and the records staged before the count is told, BF16 top-8 5.5 (100), 6.1 (1000), 7.1 (2000).  Narrow values are still packed by
-// v_pack_kernel.  Not beyond 704 tiles, as in short_each.
+// us per call, two launches and this: BF16 top-8 7.8 and 4.4 (4 blocks), 8.0 and 5.1 (100), 8.2 and 5.3 (1000), sentinels 7.8 and 4.3, 8.1 and 5.1
+// (100); E5M2 7.8 and 4.4, 7.9 and 5.1; with the planes stored and the records staged before the count is told, BF16 top-8 5.5 (100), 6.1
+// (1000).  Narrow values are still packed by v_pack_kernel.  Up to 256 tiles, as with one chunk per wave in pick_short.
 struct VShortArgs {
   VArgs a;
   uint64_t* short_words;
   uint64_t tag;
   uint32_t looks, tiles;
 };
-constexpr uint32_t kVShortTiles = 704;
-template <int DT, int CB, int EACH>
+template <int DT, int CB>
 __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args) {
   using F = VFmt<DT>;
   static_assert(kThreads == kTileThreads, "ShortCounts");
@@ -664,11 +662,11 @@ __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args
   __shared__ __attribute__((aligned(16))) uint32_t s_words[kWaves][kVBlock * F::ES / 4];
   __shared__ uint16_t s_pos[kWaves][kVBlock];   // room for all of a wave's records
   __shared__ uint32_t s_cnt[kWaves];
-  __shared__ ShortShared<EACH> s_short;
+  __shared__ ShortShared s_short;
   const VArgs a = v_args_arrived(args.a);
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-  ShortCounts<EACH> counts(args.short_words, args.tag, args.tiles, blockIdx.x);
+  ShortCounts counts(args.short_words, args.tag, args.tiles, blockIdx.x);
   uint32_t blk = 0, count = 0;                   // the wave's block and its escapes
   bool live = false, full = false;
   uint32_t w[2][F::NW];

@@ -107,3 +107,25 @@ def test_no_more_chunks_per_wave_than_the_rules_may_choose():
     for chunks in ([1 << 22], [1 << 22, 1], [1 << 20] + [1] * 63):
         assert decompress_plan(sz.BF16, chunks)["cpw"] <= (4 if len(chunks) > 1 else 2)
         assert decompress_plan(sz.FP8_E5M2, chunks)["cpw"] <= (8 if len(chunks) > 1 else 4)
+
+
+@pytest.mark.parametrize("dtype", FORMATS)
+def test_short_launches_leave_others_the_chip(dtype):
+    """A compress launch whose workgroups wait for one another: chunks per wave (0: no such launch) by the tensors' lengths.  Four
+    of them, on streams side by side, are resident together, where a tensor has long rows of workgroups, and a stream's own CUs
+    are what counts."""
+    def short(chunks, cus=256):
+        return sz.internal_compress_plan([c * 1024 for c in chunks], dtype, cus)["short"]
+    assert [short([c]) for c in (16, 17, 1023, 1024, 1025, 2047, 2048, 2049, 2816, 4096)] == [0, 1, 1, 1, 2, 2, 2, 0, 0, 0]
+    assert short([1024] * 2) == 2 and short([1000] * 4) == 0 and short([2000] * 2) == 0
+    assert [short([512] * k) for k in (1, 2, 4, 5)] == [1, 1, 1, 0]
+    assert [short([32] * k) for k in (2, 64, 65)] == [1, 1, 0] and short([60] * 64) == 0 and short([100] * 16) == 1
+    assert [short([c], 32) for c in (100, 128, 129, 256, 257, 1000)] == [1, 1, 2, 2, 0, 0]
+    assert [short([c], 128) for c in (512, 513, 1024, 1025)] == [1, 2, 2, 0]
+    for cus in (256, 128, 32):
+        for chunks in [[c] for c in range(17, 3000, 13)] + [[c] * k for k in (2, 5, 16, 64) for c in range(17, 1500, 37)]:
+            cpt = short(chunks, cus)
+            if cpt:
+                tiles = [-(-c // (4 * cpt)) for c in chunks]
+                assert max(tiles) <= min(cus, 256) and sum(tiles) <= (cus if cpt > 1 else 2 * cus), (cus, chunks)
+                assert max(tiles) <= cus // 2 or 4 * sum(tiles) <= 5 * cus, (cus, chunks)

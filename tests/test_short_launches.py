@@ -1,6 +1,8 @@
 """Compress calls of one launch whose workgroups tell one another their counts: the oracle's streams at the edges of its
 range and of its tiles of four chunks, in workspaces that hold anything, where workgroups leave their tiles to others, and
 byte for byte what the two launches leave where the stream does not fit."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -52,8 +54,8 @@ def check(x, cb, ocb, ws=None):
 @pytest.mark.parametrize("dtype,odt", FORMATS)
 @pytest.mark.parametrize("chunks", [16, 17, 49, 52, 255, 257, 1023, 1024, 1025, 2047, 2048, 2049])
 def test_streams_at_the_edges(dtype, odt, chunks, looks):
-    """Lengths around a whole tile, around what a thread looks at in one go and around the range's end; every way for a
-    wave's records to leave (staged, or again from the words); each also with every workgroup but the last ones leaving."""
+    """Lengths around a whole tile, around where a wave has two chunks and around the range's end, with few, many and all words
+    escaping; each also with every workgroup but the last ones leaving."""
     cb, ocb = books(dtype, odt)
     for n in (chunks * 1024, chunks * 1024 - 3):
         for escapes in ("few", "many", "all") if chunks < 1000 else ("few", "many"):
@@ -65,23 +67,70 @@ def test_streams_at_the_edges(dtype, odt, chunks, looks):
 
 
 @pytest.mark.parametrize("dtype,odt", FORMATS)
-def test_three_words_a_thread(dtype, odt, looks):
-    """Tensors of more than 512 tiles, up to the range's end and one word beyond it, alone and with short ones."""
+def test_two_chunks_a_wave(dtype, odt, looks):
+    """Tensors of more than 256 tiles of four chunks have half as many of eight: odd ends, the range's end and one word beyond it,
+    every way for a wave's records, alone and with short ones."""
     cb, ocb = books(dtype, odt)
-    for n in (2560 * 1024 + 1, 2816 * 1024, 2816 * 1024 + 1):
-        for limit in (0, 1):
-            print(f"case {dtype} n={n} looks={limit}", flush=True)
-            looks(limit)
-            check(words(dtype, n, 3, "many"), cb, ocb)
-    sizes = [2500 * 1024 - 7, 0, 300 * 1024, 16 * 1024]
+    for n in (1024 * 1024 + 1, 1031 * 1024, 1500 * 1024 - 1025, 2048 * 1024, 2048 * 1024 + 1):
+        for escapes in ("many", "all"):
+            for limit in (0, 1, 2):
+                print(f"case {dtype} n={n} {escapes} looks={limit}", flush=True)
+                looks(limit)
+                check(words(dtype, n, 3, escapes), cb, ocb)
+    sizes = [1500 * 1024 - 7, 0, 300 * 1024, 16 * 1024, 9 * 1024 + 1]
     xs = [words(dtype, n, 11 + k) for k, n in enumerate(sizes)]
-    outs = [torch.full((sz.compress_bound(n, dtype) + 256,), 0xA5, dtype=torch.uint8, device="cuda") for n in sizes]
-    ws, rec = sz.Workspace(max(sizes), dtype), sz.new_sizes_array(len(xs))
-    looks(0)
-    sz.compress_batch([x.cuda() for x in xs], [cb] * len(xs), outs, ws, rec)
-    for x, out, got in zip(xs, outs, sz.read_sizes_array(rec)):
+    assert sz.internal_compress_plan(sizes, dtype)["short"] == 2
+    for limit in (0, 1):
+        outs = [torch.full((sz.compress_bound(n, dtype) + 256,), 0xA5, dtype=torch.uint8, device="cuda") for n in sizes]
+        ws, rec = sz.Workspace(max(sizes), dtype), sz.new_sizes_array(len(xs))
+        looks(limit)
+        sz.compress_batch([x.cuda() for x in xs], [cb] * len(xs), outs, ws, rec)
+        for x, out, got in zip(xs, outs, sz.read_sizes_array(rec)):
+            blob, m = oracle.compress(kv_synth.to_numpy_words(x), ocb)
+            assert got == (blob.size, m, 0) and np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("dtype,odt", FORMATS)
+def test_streams_side_by_side(dtype, odt):
+    """Several streams, each with a workspace of its own, keep short launches in flight together."""
+    cb, ocb = books(dtype, odt)
+    for n in (100 * 1024, 1024 * 1024, 2048 * 1024 - 5):
+        x = words(dtype, n, 3)
         blob, m = oracle.compress(kv_synth.to_numpy_words(x), ocb)
-        assert got == (blob.size, m, 0) and np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == 0xA5).all())
+        xd, want = x.cuda(), torch.from_numpy(blob).cuda()
+        lanes = [(torch.cuda.Stream(), sz.Workspace(n, dtype), [torch.zeros(blob.size, dtype=torch.uint8, device="cuda") for _ in range(6)],
+                  [sz.new_sizes() for _ in range(6)]) for _ in range(6)]
+        torch.cuda.synchronize()
+        for k in range(6):
+            for stream, ws, outs, recs in lanes:
+                sz.compress(xd, cb, outs[k], ws, recs[k], stream=stream)
+        torch.cuda.synchronize()
+        for _, _, outs, recs in lanes:
+            for out, rec in zip(outs, recs):
+                assert sz.read_sizes(rec) == (blob.size, m, 0) and torch.equal(out, want)
+
+
+@pytest.mark.parametrize("cus", [32, 8])
+def test_a_stream_of_few_compute_units(cus, looks):
+    """A stream with a mask: launches that all fit its share of the chip, and launches that do not."""
+    hip, handle = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p()
+    mask = (ctypes.c_uint32 * 8)(*[(1 << min(32, max(0, cus - 32 * k))) - 1 for k in range(8)])
+    torch.cuda.synchronize()
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, mask) == 0
+    stream = torch.cuda.ExternalStream(handle.value)
+    cb, ocb = books(sz.BF16, oracle.BF16)
+    for n in (100 * 1024 - 1, 400 * 1024, 2048 * 1024 - 3):
+        x = words(sz.BF16, n, 3)
+        blob, m = oracle.compress(kv_synth.to_numpy_words(x), ocb)
+        xd, ws, want = x.cuda(), sz.Workspace(n, sz.BF16), torch.from_numpy(blob).cuda()
+        torch.cuda.synchronize()
+        for limit in (0, 1):
+            looks(limit)
+            out, rec = torch.zeros(blob.size, dtype=torch.uint8, device="cuda"), sz.new_sizes()
+            torch.cuda.synchronize()
+            sz.compress(xd, cb, out, ws, rec, stream=stream)
+            torch.cuda.synchronize()
+            assert sz.read_sizes(rec) == (blob.size, m, 0) and torch.equal(out, want)
 
 
 @pytest.mark.parametrize("dtype,odt", FORMATS)
@@ -107,7 +156,8 @@ def test_what_the_workspace_holds(dtype, odt, looks):
 def test_batches(dtype, odt, limit, looks):
     """Tensors of a launch have their own counts: unequal lengths, none at all, a batch of 64."""
     cb, ocb = books(dtype, odt)
-    for sizes in ([0, 50 * 1024 + 1, 3, 0, 300 * 1024, 4096, 1024 * 257 - 5], [63 * 1024 + 7 * k for k in range(64)], [0, 60 * 1024], [1024 * 1024 - 1] * 4, [1025 * 1024, 1000 * 1024 - 1]):
+    for sizes in ([0, 50 * 1024 + 1, 3, 0, 300 * 1024, 4096, 1024 * 257 - 5], [63 * 1024 + 7 * k for k in range(64)], [31 * 1024 + 7 * k for k in range(64)], [0, 60 * 1024],
+                  [500 * 1024 - 1] * 4, [1024 * 1024 - 1] * 4, [1025 * 1024, 1000 * 1024 - 1]):
         xs = [words(dtype, n, 7 + k, "many" if k % 5 == 4 else "few") for k, n in enumerate(sizes)]
         blobs = [oracle.compress(kv_synth.to_numpy_words(x), ocb) for x in xs]
         outs = [torch.full((sz.compress_bound(n, dtype) + 256,), 0xA5, dtype=torch.uint8, device="cuda") for n in sizes]
@@ -123,7 +173,7 @@ def test_batches(dtype, odt, limit, looks):
 @pytest.mark.parametrize("limit", [0, 1])
 def test_what_does_not_fit(dtype, limit, looks):
     cb = sz.codebook_from_dec(list(range(16)), dtype)          # hardly anything is in this codebook
-    for n in (70 * 1024 - 9, 200 * 1024):
+    for n in (70 * 1024 - 9, 200 * 1024, 1100 * 1024 - 5):
         x = words(dtype, n, 5)
         fixed, total = sz.fixed_bytes(n, dtype), compress(x, cb)[1][0]
         for cap in (fixed, fixed + (total - fixed) // 3, total - 1, total):

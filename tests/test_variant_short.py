@@ -42,12 +42,12 @@ def test_lengths_at_the_edges(form, looks):
 
 
 @pytest.mark.parametrize("form", FORMS)
-def test_three_words_a_thread(form, looks):
-    """More than 512 tiles, the range's end, and one block beyond it."""
+def test_the_end_of_the_range(form, looks):
+    """256 tiles, and one block beyond them."""
     v, o = sz.variant(*form), ov.variant(*form)
     dec = np.zeros(16, np.uint8)
     dec[:v.k] = sz.variant_calibrate(GEN[form[0]](64, 1), v).dec[:v.k]
-    for n in (2049 * 1024 - 5, 2816 * 1024, 2816 * 1024 + 1):
+    for n in (1024 * 1024 - 5, 1024 * 1024, 1024 * 1024 + 1):
         x, run = words(form[0], n, 5), Run(n, v)
         for limit in (0, 1):
             looks(limit)
