@@ -866,6 +866,10 @@ uint64_t short_status_need(uint64_t tiles) { return kShortCopies * short_copy_by
 // 3.5 and 4.3, four of 1000 3.4 and 8.2, and with two chunks per wave 64 of 60 (512) 3.5 and 3.7, four of 1000 3.4 and 4.3.
 // On a stream of 32 CUs 2048 chunks take 10 us in two launches and took 360 this way.  Beside elementwise kernels that fill the chip
 // 1000 chunks 20.2 and 16.0, 2048 20.2 and 17.6, beside matrix products 166 and 109, 165 and 110.
+// Tensors that differ in length, as in pick_base_cpt, only that workgroups without a tile ask for more of a CU here; on 1 / 3 / 4 streams,
+// two launches and this: one of 500 chunks beside 40 of 12 (4800 workgroups without a tile) 7.6 / 3.5 / 3.0 and 6.2 / 3.0 / 2.8, 1000 beside 40 of 4 (9900) 8.8 / 4.3 /
+// 3.4 and 7.2 / 4.0 / 3.7, 1024 beside 20 of 8 (5080) 8.0 / 3.4 / 3.0 and 6.8 / 3.4 / 3.2; two chunks per wave 1500 beside 20 of 8 (3740) 8.3 / 4.0 / 3.6 and 6.9 / 3.0 / 2.8, 1024
+// beside 30 of 8 (3810) 9.1 / 4.0 / 3.5 and 8.5 / 4.3 / 4.0, beside 50 of 8 (6350) 10.6 / 7.6 / 3.5 and 11.9 / 8.6 / 4.4.
 // What bounds calls of up to 500 chunks now is the host: a launch takes it 2.3 us.
 uint32_t pick_short(const splitzip_item* items, uint32_t k, uint64_t status_bytes, uint64_t cus, uint64_t* wgs, uint64_t* tiles_max) {
   uint64_t chunks_max = 0;
@@ -884,7 +888,7 @@ uint32_t pick_short(const splitzip_item* items, uint32_t k, uint64_t status_byte
       need += short_status_need(t);
     }
     const bool fit = cpt > 1 ? tiles <= cus : longest <= cus / 2 ? tiles <= 2 * cus : tiles <= cus + cus / 4;
-    if (fit && need <= status_bytes) {
+    if (fit && longest * k - tiles <= (cpt > 1 ? 3000u : 5000u) && need <= status_bytes) {
       *wgs = tiles;
       *tiles_max = longest;
       return cpt;

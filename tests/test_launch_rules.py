@@ -129,3 +129,14 @@ def test_short_launches_leave_others_the_chip(dtype):
                 tiles = [-(-c // (4 * cpt)) for c in chunks]
                 assert max(tiles) <= min(cus, 256) and sum(tiles) <= (cus if cpt > 1 else 2 * cus), (cus, chunks)
                 assert max(tiles) <= cus // 2 or 4 * sum(tiles) <= 5 * cus, (cus, chunks)
+
+
+@pytest.mark.parametrize("dtype", FORMATS)
+def test_short_launches_of_tensors_that_differ_in_length(dtype):
+    """Workgroups without a tile: no more than 5000 of them, 3000 where they are larger."""
+    def short(chunks):
+        return sz.internal_compress_plan([c * 1024 for c in chunks], dtype)["short"]
+    assert short([500] + [12] * 40) == 1 and short([1000] + [4] * 20) == 1 and short([1024] + [8] * 10) == 1 and short([1500] + [8] * 10) == 2
+    assert short([500] + [12] * 63) == 0 and short([512] + [4] * 159) == 0 and short([1000] + [4] * 40) == 0
+    assert [short([1024] + [8] * k) for k in (20, 30, 50)] == [2, 0, 0] and [short([1500] + [8] * k) for k in (15, 20)] == [2, 0]
+    assert short([2000] + [12] * 63) == 0 and short([1024] + [40] * 63) == 0
