@@ -800,8 +800,8 @@ void launch_compress(unsigned tiles, unsigned finish_wgs, unsigned sums, unsigne
     const uint32_t cpt = args.shared.cpt;
     if (cpt == 1) launch(compress_tile_kernel<F, 1, N, kTileOnce>, grid, block, lds_pad, st, args);
     else if (cpt == 2) launch(is_long ? compress_tile_kernel<F, 2, N, kTileLong> : compress_tile_kernel<F, 2, N, kTileOnce>, grid, block, lds_pad, st, args);
-    else if (cpt == F::kCpt) launch(is_long ? compress_tile_kernel<F, F::kCpt, N, kTileLong> : compress_tile_kernel<F, F::kCpt, N, kTileOnce>, grid, block, lds_pad, st, args);
-    else launch(compress_tile_kernel<F, F::kCpt, N, kTileLoop>, grid, block, lds_pad, st, args);
+    else if (cpt == F::kCpt && (is_long || N > kBatchFew)) launch(compress_tile_kernel<F, F::kCpt, N, kTileLong>, grid, block, lds_pad, st, args);   // four chunks: many tensors are many tiles
+    else if constexpr (N <= kBatchFew) launch(cpt == F::kCpt ? compress_tile_kernel<F, F::kCpt, N, kTileOnce> : compress_tile_kernel<F, F::kCpt, N, kTileLoop>, grid, block, lds_pad, st, args);
     if (args.shared.use_group_sums) launch(tile_group_sum_kernel<F, N>, dim3(sums, k), dim3(64), 0, st, args);
   }
   const dim3 grid(finish_wgs ? finish_wgs : 1u, k);
@@ -830,7 +830,7 @@ void launch_short(unsigned tiles, unsigned k, hipStream_t st, const TileArgs<kBa
     launch(compress_short_kernel<F, 1, CPT>, grid, block, 0, st, one);
   } else if (k <= kBatchFew) {
     launch(compress_short_kernel<F, kBatchFew, CPT>, grid, block, 0, st, few(args));
-  } else {
+  } else if constexpr (CPT == 1) {   // (two chunks per wave: pick_short)
     launch(compress_short_kernel<F, kBatchMax, CPT>, grid, block, 0, st, args);
   }
 }
@@ -881,6 +881,7 @@ uint32_t pick_short(const splitzip_item* items, uint32_t k, uint64_t status_byte
   for (uint32_t cpt = 1; cpt <= kShortMostCpt; cpt *= 2) {
     const uint64_t longest = tiles_of(chunks_max, cpt);
     if (longest > kShortTiles || longest > cus) continue;
+    if (cpt > 1 && k > kBatchFew) break;   // so many rows that one would have two chunks per wave for leave more without a tile than the limit below
     uint64_t tiles = 0, need = 0;
     for (uint32_t q = 0; q < k; ++q) {
       const uint64_t t = tiles_of(chunks_of(items[q].n_elems), cpt);
@@ -928,7 +929,7 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   uint64_t taken = 0;   // of the status area, by the tensors so far
   for (; p.k < k_most; ++p.k) {
     const uint32_t need = pick_cpt(chunks_of(items[p.k].n_elems), p.cpt, status_bytes);
-    if (!need) break;
+    if (!need || (p.k >= kBatchFew && need > (dtype == SPLITZIP_BF16 ? Bf16::kCpt : E5m2::kCpt))) break;   // there is no kTileLoop for more
     uint64_t total = need == p.cpt ? taken : 0;
     for (uint32_t q = need == p.cpt ? p.k : 0; q <= p.k; ++q) total += status_need(tiles_of(chunks_of(items[q].n_elems), need));
     if (total > status_bytes) break;

@@ -140,3 +140,17 @@ def test_short_launches_of_tensors_that_differ_in_length(dtype):
     assert short([500] + [12] * 63) == 0 and short([512] + [4] * 159) == 0 and short([1000] + [4] * 40) == 0
     assert [short([1024] + [8] * k) for k in (20, 30, 50)] == [2, 0, 0] and [short([1500] + [8] * k) for k in (15, 20)] == [2, 0]
     assert short([2000] + [12] * 63) == 0 and short([1024] + [40] * 63) == 0
+
+
+@pytest.mark.parametrize("dtype", FORMATS)
+def test_launches_of_more_than_64_tensors(dtype):
+    """There are no kernels for so many with more chunks per wave than they take at once, and none of the short ones with two."""
+    try:
+        for cpt, count in ((1, 70), (2, 70), (4, 64 if dtype == sz.BF16 else 70), (8, 64)):
+            sz.internal_test_launch(cpt=cpt)
+            assert compress_plan(dtype, [100] * 70)["tensors"] == count, cpt
+    finally:
+        sz.internal_test_launch()
+    for chunks in ([c] + [1] * k for c in range(17, 2049, 11) for k in (64, 65, 80, 100, 159)):
+        plan = compress_plan(dtype, chunks)
+        assert plan["tensors"] <= 64 or plan["short"] < 2, chunks
