@@ -497,12 +497,18 @@ struct TileShared {
   splitzip_sizes* sizes;          // one record per tensor
   uint8_t* status;                // per tensor: u32 count of every tile, then u32 sum of every kSumGroup tiles
   uint8_t* stage;                 // per tensor stage_cap bytes: the tiles' slots
-  uint64_t stage_cap;             // (compress_short_kernel, which stages nothing there: the call's tag)
+  union {
+    uint64_t stage_cap;
+    uint64_t tag;                 // compress_short_kernel, which stages nothing there: the call's
+  };
   const splitzip_codebook* d_cbs; // nullable: codebooks in device memory, one per tensor, used instead of dec
   Words paging;                   // table and page geometry shared by all tensors (table null: contiguous tensors); base unused
   uint32_t cpt;                   // chunks per wave and tile, a power of two
   uint32_t tile_shift;            // log2 of the chunks per tile (4 cpt)
-  uint32_t slot_cap;              // records per tile slot (the same for all tensors of the launch; compress_short_kernel: how often a workgroup looks for the others' counts)
+  union {
+    uint32_t slot_cap;            // records per tile slot, the same for all tensors of the launch
+    uint32_t looks;               // compress_short_kernel, which has no slots: how often a workgroup looks for the others' counts
+  };
   uint32_t finish_groups;         // groups of kGroup tiles per workgroup of the finishing pass, 1 to kFinishMost
   uint32_t use_group_sums;        // the finishing pass reads sums of kSumGroup tile counts (tile_group_sum_kernel) instead of all tile counts
   uint32_t by_xcd;                // the dense pass takes its tiles in xcd_order
@@ -912,7 +918,8 @@ __global__ __launch_bounds__(kTileThreads) void compress_finish_kernel(const Til
 }
 
 // ---- small tensors: one launch, one workgroup per tensor ----
-// Up to F::kSmallChunks chunks in a captured call, and up to kSmallestShort in others, a tensor is one workgroup's work: 16 waves own consecutive runs of its chunks, so the
+// Up to F::kSmallChunks chunks a tensor is one workgroup's work in a captured call and in a batch that is too much for the short launch below
+// (pick_short), and up to kSmallestShort in every call: 16 waves own consecutive runs of its chunks, so the
 // counts meet in LDS, every rank is known behind one barrier and nothing is staged outside the workgroup.  What bounds
 // such a call is the launch: the second one takes the host 2.7 us and the device 3.1 us.  Device us per call, this
 // kernel / two launches: BF16 5.2 / 6.8 (17 chunks), 6.4 / 6.7 (33), 7.3 / 6.6 (49), 10.6 / 6.6 (97); E5M2 5.6 / 7.6
@@ -995,7 +1002,7 @@ __global__ __launch_bounds__(kSmallThreads) void compress_small_kernel(const Til
 //   value before a call), kShortLeft, kShortTaken and the count.  One atomic word says all there is to say: nothing else that
 //   a workgroup writes is read by another.  There are kShortCopies copies of a tensor's words and a workgroup reads one of
 //   them: all workgroups reading the same few lines from the device's point of coherence took longer than the work.
-//   No wait is without an end.  A workgroup that has looked a.slot_cap times (50 us, in which the rest of the launch has not got onto
+//   No wait is without an end.  A workgroup that has looked a.looks times (50 us, in which the rest of the launch has not got onto
 //   the chip) marks its tile as left, looks once more and, if counts are missing still, ends.  The mark and the count are
 //   each written, and the write waited for, before the writer looks at the other words: so whoever publishes last of all
 //   sees all counts the first time it looks, and with them the mark of every workgroup that looked for the last time
@@ -1148,7 +1155,7 @@ __global__ __launch_bounds__(kTileThreads, CPT == 1 ? 1 : 4) void compress_short
   const Planes P = make_planes(item_words(a.paging, it.in), it.out, it.n, it.capacity, F::DT);
   const uint32_t n_tiles = (P.n_chunks + NW * CPT - 1) / (NW * CPT);
   if (own >= (n_tiles ? n_tiles : 1u)) return;   // a tensor without elements still gets its header
-  ShortCounts counts(reinterpret_cast<uint64_t*>(a.status + it.status_off), a.stage_cap, n_tiles, own);
+  ShortCounts counts(reinterpret_cast<uint64_t*>(a.status + it.status_off), a.tag, n_tiles, own);
   uint32_t* park = reinterpret_cast<uint32_t*>(&s_park[tid]);
   const LdsSink lds{stage_pos[wave], stage_val[wave], 0u, CPT * kChunk};
 
@@ -1240,7 +1247,7 @@ __global__ __launch_bounds__(kTileThreads, CPT == 1 ? 1 : 4) void compress_short
     if (tile == 0 && wave == NW - 1) compress_write_trailer(P, a.dec16_of(it, item), a.sizes + item, counts.M, 0u, lane);
   };
   static_assert(CPT <= (int)kShortMostCpt, "the second chunk's entry is what the first holds");
-  counts.run(s_short, a.slot_cap, total, (uint32_t)tid, (uint32_t)wave, encode, deliver, place);
+  counts.run(s_short, a.looks, total, (uint32_t)tid, (uint32_t)wave, encode, deliver, place);
 }
 
 #endif  // SPLITZIP_COMPRESS_HPP

@@ -4,7 +4,7 @@
 //   compress.hpp    dense transform (paper section 3.2 eq. (1), encode table, nibble pack, planes)
 //                   fused with escape detection, counting and position-ordered compaction
 //                   (appendix "Quad64 Vectorized Encoding" fuses only the counting); two launches
-//                   for a tensor or up to 64 of them, one for few chunks
+//                   for a tensor or up to 160 of them, one for few chunks
 //   decompress.hpp  nibble unpack, decode table, eq. (2), scatter correction in LDS; one
 //                   launch per tensor or per batch
 //   aux_kernels.hpp calibration histogram (section 3.3), workspace initialisation, traffic probe
@@ -1045,8 +1045,8 @@ int compress_launch(const splitzip_item* items, uint32_t n_items, int dtype, con
     a.by_xcd = p.by_xcd ? 1u : 0u;
     const unsigned tiles_max = (unsigned)p.tiles_max, sums_max = (tiles_max + kSumGroup - 1) / kSumGroup;
     if (p.is_short) {
-      a.stage_cap = next_call_tag();
-      a.slot_cap = short_looks();
+      a.tag = next_call_tag();
+      a.looks = short_looks();
       if (dtype == SPLITZIP_BF16) (p.cpt == 1 ? launch_short<Bf16, 1> : launch_short<Bf16, 2>)(tiles_max, k, st, args);
       else (p.cpt == 1 ? launch_short<E5m2, 1> : launch_short<E5m2, 2>)(tiles_max, k, st, args);
     } else if (p.small) {
