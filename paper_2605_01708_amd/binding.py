@@ -136,7 +136,7 @@ def lib():
         L.splitzip_internal_test_hooks.restype = None
         L.splitzip_internal_test_hooks.argtypes = [u64, u64, C.c_uint32, u64]
         L.splitzip_internal_test_short.restype = None
-        L.splitzip_internal_test_short.argtypes = [C.c_uint32]
+        L.splitzip_internal_test_short.argtypes = [C.c_uint32, C.c_uint32]
         L.splitzip_internal_test_launch.restype = None
         L.splitzip_internal_test_launch.argtypes = [C.c_uint32, C.c_uint32, C.c_uint32]
         L.splitzip_internal_compress_plan.restype = None
@@ -424,10 +424,11 @@ def internal_test_launch(cpt: int = 0, cpw: int = 0, xcd: int = 0) -> None:
     lib().splitzip_internal_test_launch(cpt, cpw, xcd)
 
 
-def internal_test_short(looks: int = 0) -> None:
-    """How often a workgroup of a short compress launch looks for the others' counts before it leaves its tile to them (not
-    part of splitzip.h).  0 = as built; INTERNAL_NO_SHORT: two launches instead."""
-    lib().splitzip_internal_test_short(looks)
+def internal_test_short(looks: int = 0, anywhere: bool = False) -> None:
+    """How often a workgroup of a short compress launch looks for the others' counts before it leaves its tile to them, and whether
+    there are such launches on streams whose share of the device does not hold them (not part of splitzip.h).  0 = as built;
+    INTERNAL_NO_SHORT: two launches instead."""
+    lib().splitzip_internal_test_short(looks, anywhere)
 
 
 INTERNAL_NO_SHORT = 0xFFFFFFFF

@@ -91,6 +91,7 @@ struct TestHooks {
   std::atomic<uint32_t> cpw{0};   // 1, 2, 4 or 8, most_cpw at most
   std::atomic<uint32_t> xcd{0};   // 1: batch launches keep the tiles' own order, 2: they take xcd_order
   std::atomic<uint32_t> short_looks{0};   // how often a workgroup of compress_short_kernel looks for the counts of the others; kNoShort: no such launches
+  std::atomic<bool> short_anywhere{false};   // and on streams with a mask as on others
   bool any() const { return stage_bytes || status_bytes || finish_groups || direct_bytes || cpt || xcd; }   // the two-launch path is meant
 };
 constexpr uint32_t kNoShort = 0xffffffffu;
@@ -217,7 +218,7 @@ uint64_t cus_once(hipStream_t st, uint64_t wgs) {
   }
   if (s != hipStreamCaptureStatusNone) return 0;
   const uint64_t all = (uint64_t)cu_count();
-  if (!st || wgs <= all / 8) return all;   // a few fit any part of a chip
+  if (!st || wgs <= all / 8 || g_hooks.short_anywhere) return all;   // a few fit any part of a chip
   uint32_t mask[32] = {0};   // of a stream that was made with one (the question takes 0.2 us)
   if (all > 32 * 32 || hipExtStreamGetCUMask(st, (uint32_t)(all + 31) / 32, mask) != hipSuccess) {
     (void)hipGetLastError();
@@ -672,7 +673,10 @@ void splitzip_internal_test_hooks(uint64_t stage_bytes, uint64_t status_bytes, u
   g_hooks.finish_groups = finish_groups == 1 || finish_groups == 2 || finish_groups == 4 ? finish_groups : 0;
 }
 
-void splitzip_internal_test_short(uint32_t looks) { g_hooks.short_looks = looks; }
+void splitzip_internal_test_short(uint32_t looks, uint32_t anywhere) {
+  g_hooks.short_looks = looks;
+  g_hooks.short_anywhere = anywhere != 0;
+}
 
 void splitzip_internal_test_launch(uint32_t cpt, uint32_t cpw, uint32_t xcd) {
   const auto size_or_0 = [](uint32_t v) { return v == 1 || v == 2 || v == 4 || v == 8 ? v : 0u; };

@@ -525,7 +525,7 @@ def hooks():
 
 
 def test_compress_beside_other_work_on_the_device():
-    """The compress calls wait for nothing -- no workgroup for another, no launch for room on the device: with a
+    """Compress calls of two launches wait for nothing -- no workgroup for another, no launch for room on the device: with a
     long run of elementwise kernels keeping the device busy on another stream (what a prefill worker's model does
     beside the codec), single and batch calls complete and give the streams they give on a quiet device."""
     dtype = sz.BF16
@@ -796,20 +796,20 @@ def test_batch_tensor_larger_than_a_full_group():
 
 
 def test_more_tensors_than_one_launch_takes():
-    """70 small tensors: the batch calls (host codebooks, device codebooks, own headers) split them over two launches
-    of at most 64; every stream is the oracle's under the tensor's own codebook"""
+    """170 small tensors: the batch calls (host codebooks, device codebooks, own headers) split them over two launches
+    of at most 160; every stream is the oracle's under the tensor's own codebook"""
     dtype = sz.BF16
     rng = np.random.default_rng(11)
-    xs_np = [synth(dtype, 3, 200 + k, layer=k, kind="KV"[k % 2])[: int(rng.integers(1, 3000))].copy() for k in range(70)]
+    xs_np = [synth(dtype, 3, 200 + k, layer=k, kind="KV"[k % 2])[: int(rng.integers(1, 3000))].copy() for k in range(170)]
     xs = [words_tensor(x) for x in xs_np]
     cbs_or = [oracle.calibrate(x, DT[dtype]) for x in xs_np]
     refs = [oracle.compress(x, c) for x, c in zip(xs_np, cbs_or)]
     ws = sz.Workspace(4096, dtype)
-    dcbs = sz.DeviceCodebooks(70, dtype)
+    dcbs = sz.DeviceCodebooks(170, dtype)
     sz.CalibrateBatchDevice(xs, dcbs).launch()
     for how in ("host codebooks", "device codebooks"):
         outs = [torch.full((sz.compress_bound(x.size, dtype),), POISON, dtype=torch.uint8, device="cuda") for x in xs_np]
-        rec = sz.new_sizes_array(70)
+        rec = sz.new_sizes_array(170)
         if how == "host codebooks":
             sz.compress_batch(xs, [gpu_codebook(c) for c in cbs_or], outs, ws, rec)
         else:
@@ -834,13 +834,13 @@ def test_more_tensors_than_one_launch_takes():
 @pytest.mark.parametrize("dtype", DTYPES)
 def test_more_long_tensors_than_one_launch_takes(dtype):
     """The same with tensors that no workgroup does by itself: the second launch's dense and finishing passes take their
-    codebooks, records and sizes from the 65th on."""
+    codebooks, records and sizes from the 161st on."""
     chunks = 49     # one more than the most a workgroup does by itself
-    xs = [words_tensor(synth(dtype, chunks + 1, 300 + k, layer=k % 7, kind="KV"[k % 2])[: chunks * 1024 - 11 * (k % 5)].copy()) for k in range(67)]
-    dcbs = sz.DeviceCodebooks(67, dtype)
+    xs = [words_tensor(synth(dtype, chunks + 1, 300 + k, layer=k % 7, kind="KV"[k % 2])[: chunks * 1024 - 11 * (k % 5)].copy()) for k in range(167)]
+    dcbs = sz.DeviceCodebooks(167, dtype)
     sz.CalibrateBatchDevice(xs, dcbs).launch()
     outs = [torch.full((sz.compress_bound(x.numel(), dtype),), POISON, dtype=torch.uint8, device="cuda") for x in xs]
-    ws, rec = sz.Workspace(chunks * 1024, dtype), sz.new_sizes_array(67)
+    ws, rec = sz.Workspace(chunks * 1024, dtype), sz.new_sizes_array(167)
     sz.CompressBatchDcb(xs, dcbs, outs).launch(ws, rec)
     torch.cuda.synchronize()
     got = sz.read_sizes_array(rec)

@@ -1,8 +1,6 @@
 """Compress calls of one launch whose workgroups tell one another their counts: the oracle's streams at the edges of its
 range and of its tiles of four chunks, in workspaces that hold anything, where workgroups leave their tiles to others, and
 byte for byte what the two launches leave where the stream does not fit."""
-import ctypes
-
 import numpy as np
 import pytest
 import torch
@@ -10,15 +8,10 @@ import torch
 import kv_synth
 import oracle
 import paper_2605_01708_amd as sz
+from conftest import LEAVE
 
 pytestmark = pytest.mark.gpu
 FORMATS = [(sz.BF16, oracle.BF16), (sz.FP8_E5M2, oracle.E5M2)]
-
-
-@pytest.fixture
-def looks():
-    yield sz.internal_test_short
-    sz.internal_test_short()
 
 
 def words(dtype, n, seed, escapes="few"):
@@ -55,15 +48,15 @@ def check(x, cb, ocb, ws=None):
 @pytest.mark.parametrize("chunks", [16, 17, 49, 52, 255, 257, 1023, 1024, 1025, 2047, 2048, 2049])
 def test_streams_at_the_edges(dtype, odt, chunks, looks):
     """Lengths around a whole tile, around where a wave has two chunks and around the range's end, with few, many and all words
-    escaping; each also with every workgroup but the last ones leaving."""
+    escaping; each also with workgroups that leave their tiles to others, and in two launches."""
     cb, ocb = books(dtype, odt)
     for n in (chunks * 1024, chunks * 1024 - 3):
         for escapes in ("few", "many", "all") if chunks < 1000 else ("few", "many"):
             x = words(dtype, n, 3, escapes)
-            for limit in (0, 1) if chunks <= 1025 else (0,):
+            for limit in (0, LEAVE, sz.INTERNAL_NO_SHORT):
                 print(f"case {dtype} n={n} {escapes} looks={limit}", flush=True)
-                looks(limit)
-                check(x, cb, ocb)
+                with looks(limit):
+                    check(x, cb, ocb)
 
 
 @pytest.mark.parametrize("dtype,odt", FORMATS)
@@ -73,21 +66,55 @@ def test_two_chunks_a_wave(dtype, odt, looks):
     cb, ocb = books(dtype, odt)
     for n in (1024 * 1024 + 1, 1031 * 1024, 1500 * 1024 - 1025, 2048 * 1024, 2048 * 1024 + 1):
         for escapes in ("many", "all"):
-            for limit in (0, 1, 2):
+            for limit in (0, 1, LEAVE):
                 print(f"case {dtype} n={n} {escapes} looks={limit}", flush=True)
-                looks(limit)
-                check(words(dtype, n, 3, escapes), cb, ocb)
+                with looks(limit):
+                    check(words(dtype, n, 3, escapes), cb, ocb)
     sizes = [1500 * 1024 - 7, 0, 300 * 1024, 16 * 1024, 9 * 1024 + 1]
     xs = [words(dtype, n, 11 + k) for k, n in enumerate(sizes)]
     assert sz.internal_compress_plan(sizes, dtype)["short"] == 2
-    for limit in (0, 1):
+    for limit in (0, LEAVE):
         outs = [torch.full((sz.compress_bound(n, dtype) + 256,), 0xA5, dtype=torch.uint8, device="cuda") for n in sizes]
         ws, rec = sz.Workspace(max(sizes), dtype), sz.new_sizes_array(len(xs))
-        looks(limit)
-        sz.compress_batch([x.cuda() for x in xs], [cb] * len(xs), outs, ws, rec)
+        with looks(limit):
+            sz.compress_batch([x.cuda() for x in xs], [cb] * len(xs), outs, ws, rec)
         for x, out, got in zip(xs, outs, sz.read_sizes_array(rec)):
             blob, m = oracle.compress(kv_synth.to_numpy_words(x), ocb)
             assert got == (blob.size, m, 0) and np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("dtype,odt", FORMATS)
+@pytest.mark.parametrize("chunks", [300, 1024, 1100, 2048])
+def test_tiles_left_and_taken(dtype, odt, chunks, looks):
+    """Workgroups leave their tiles to those that come after them, which encode them again: out of pages, under a
+    codebook in device memory.  The words in the workspace tell of every tile whether it was left and, if so, taken."""
+    n, page = chunks * 1024 - 5, 4096
+    pages, es = -(-n // page), 2 if dtype == sz.BF16 else 1
+    table = torch.randperm(pages, generator=torch.Generator().manual_seed(4)).to(torch.int32)
+    pool = words(dtype, pages * page, 3, "many").cuda()
+    x = pool.view(pages, page)[table.long().cuda()].reshape(-1)[:n].contiguous()
+    d = sz.DeviceCodebooks(1, dtype)
+    sz.CalibrateBatchDevice([x], d).launch()
+    cb, ocb = d.to_host(0), oracle.calibrate(kv_synth.to_numpy_words(x.cpu()), odt)
+    blob, m = oracle.compress(kv_synth.to_numpy_words(x.cpu()), ocb)
+    ws, tiles = sz.Workspace(n, dtype), -(-chunks // (4 if chunks <= 1024 else 8))
+    for limit in (0, 1, LEAVE):
+        for how in ("pages", "device codebook"):
+            out, rec = torch.full((blob.size + 512,), 0xA5, dtype=torch.uint8, device="cuda"), sz.new_sizes()
+            paged = sz.Paged(pool, table.cuda(), page, page * es)
+            with looks(limit):
+                if how == "pages":
+                    sz.compress_paged(paged, n, cb, out, ws, rec)
+                else:
+                    sz.CompressBatchDcb([x], d, [out]).launch(ws, rec.view(1, 3))
+            assert sz.read_sizes(rec) == (blob.size, m, 0), (limit, how)
+            assert np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == 0xA5).all())
+            told = ws.buf[512:512 + 8 * tiles].view(torch.int64).cpu()
+            was_left, was_taken = (told & 0x8000) != 0, (told & 0x10000) != 0
+            assert torch.equal(was_left, was_taken)
+            left = int(was_left.sum())
+            print(f"case {dtype} chunks={chunks} {how}: {left} of {tiles} tiles left", flush=True)
+            assert limit != LEAVE or left > 0
 
 
 @pytest.mark.parametrize("dtype,odt", FORMATS)
@@ -110,27 +137,19 @@ def test_streams_side_by_side(dtype, odt):
                 assert sz.read_sizes(rec) == (blob.size, m, 0) and torch.equal(out, want)
 
 
-@pytest.mark.parametrize("cus", [32, 8])
-def test_a_stream_of_few_compute_units(cus, looks):
-    """A stream with a mask: launches that all fit its share of the chip, and launches that do not."""
-    hip, handle = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p()
-    mask = (ctypes.c_uint32 * 8)(*[(1 << min(32, max(0, cus - 32 * k))) - 1 for k in range(8)])
-    torch.cuda.synchronize()
-    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, mask) == 0
-    stream = torch.cuda.ExternalStream(handle.value)
+def test_a_stream_of_few_compute_units(few_cus):
+    """A stream with a mask, by the rules: calls whose workgroups its CUs hold, and calls that take two launches there."""
     cb, ocb = books(sz.BF16, oracle.BF16)
-    for n in (100 * 1024 - 1, 400 * 1024, 2048 * 1024 - 3):
+    for n in (30 * 1024 - 1, 100 * 1024 - 1, 400 * 1024, 2048 * 1024 - 3):
         x = words(sz.BF16, n, 3)
         blob, m = oracle.compress(kv_synth.to_numpy_words(x), ocb)
         xd, ws, want = x.cuda(), sz.Workspace(n, sz.BF16), torch.from_numpy(blob).cuda()
+        out, rec = torch.zeros(blob.size, dtype=torch.uint8, device="cuda"), sz.new_sizes()
         torch.cuda.synchronize()
-        for limit in (0, 1):
-            looks(limit)
-            out, rec = torch.zeros(blob.size, dtype=torch.uint8, device="cuda"), sz.new_sizes()
-            torch.cuda.synchronize()
-            sz.compress(xd, cb, out, ws, rec, stream=stream)
-            torch.cuda.synchronize()
-            assert sz.read_sizes(rec) == (blob.size, m, 0) and torch.equal(out, want)
+        for _ in range(3):
+            sz.compress(xd, cb, out, ws, rec, stream=few_cus)
+        torch.cuda.synchronize()
+        assert sz.read_sizes(rec) == (blob.size, m, 0) and torch.equal(out, want)
 
 
 @pytest.mark.parametrize("dtype,odt", FORMATS)
@@ -147,12 +166,12 @@ def test_what_the_workspace_holds(dtype, odt, looks):
             ws.buf.zero_()
         elif k > 3:
             ws.buf.random_(0, 256, generator=gen)
-        looks(k % 2)
-        check(words(dtype, n, k), cb, ocb, ws)
+        with looks(LEAVE if k % 2 else 0):
+            check(words(dtype, n, k), cb, ocb, ws)
 
 
 @pytest.mark.parametrize("dtype,odt", FORMATS)
-@pytest.mark.parametrize("limit", [0, 1, 2])
+@pytest.mark.parametrize("limit", [0, 1, LEAVE])
 def test_batches(dtype, odt, limit, looks):
     """Tensors of a launch have their own counts: unequal lengths, none at all, a batch of 64."""
     cb, ocb = books(dtype, odt)
@@ -162,25 +181,25 @@ def test_batches(dtype, odt, limit, looks):
         blobs = [oracle.compress(kv_synth.to_numpy_words(x), ocb) for x in xs]
         outs = [torch.full((sz.compress_bound(n, dtype) + 256,), 0xA5, dtype=torch.uint8, device="cuda") for n in sizes]
         ws, rec = sz.Workspace(max(sizes), dtype), sz.new_sizes_array(len(xs))
-        looks(limit)
         print(f"case {dtype} batch of {len(sizes)} looks={limit}", flush=True)
-        sz.compress_batch([x.cuda() for x in xs], [cb] * len(xs), outs, ws, rec)
+        with looks(limit):
+            sz.compress_batch([x.cuda() for x in xs], [cb] * len(xs), outs, ws, rec)
         for (blob, m), out, got in zip(blobs, outs, sz.read_sizes_array(rec)):
             assert got == (blob.size, m, 0) and np.array_equal(out[:blob.size].cpu().numpy(), blob) and bool((out[blob.size:] == 0xA5).all())
 
 
 @pytest.mark.parametrize("dtype", [sz.BF16, sz.FP8_E5M2])
-@pytest.mark.parametrize("limit", [0, 1])
+@pytest.mark.parametrize("limit", [0, LEAVE])
 def test_what_does_not_fit(dtype, limit, looks):
     cb = sz.codebook_from_dec(list(range(16)), dtype)          # hardly anything is in this codebook
     for n in (70 * 1024 - 9, 200 * 1024, 1100 * 1024 - 5):
         x = words(dtype, n, 5)
         fixed, total = sz.fixed_bytes(n, dtype), compress(x, cb)[1][0]
         for cap in (fixed, fixed + (total - fixed) // 3, total - 1, total):
-            looks(limit)
-            out, got = compress(x, cb, cap)
-            looks(sz.INTERNAL_NO_SHORT)
-            ref, want = compress(x, cb, cap)
+            with looks(limit):
+                out, got = compress(x, cb, cap)
+            with looks(sz.INTERNAL_NO_SHORT):
+                ref, want = compress(x, cb, cap)
             assert got == want and torch.equal(out, ref)
 
 

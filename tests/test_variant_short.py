@@ -1,5 +1,5 @@
 """Variant compress calls in one launch, whose workgroups tell one another their counts: lengths at the edges of its tiles of four
-blocks and of its range, every way through it (all wait, all but the last leave, two launches), what does not fit."""
+blocks and of its range, every way through it (all wait, most leave, two launches), what does not fit."""
 import numpy as np
 import pytest
 import torch
@@ -8,6 +8,7 @@ import kv_synth
 import test_variant_edges as edges
 from oracle import variants as ov
 import paper_2605_01708_amd as sz
+from conftest import LEAVE
 from test_variants import Run, check, dev
 
 pytestmark = pytest.mark.gpu
@@ -15,12 +16,6 @@ FORMS = [(sz.BF16, 4, 16, sz.ESC_POS, 1024, 0), (sz.BF16, 3, 8, sz.ESC_POS, 256,
          (sz.BF16, 3, 8, sz.ESC_ABS32, 0, 0), (sz.FP8_E5M2, 3, 8, sz.ESC_POS, 1024, 5), (sz.FP8_E5M2, 3, 7, sz.ESC_SENTINEL, 1024, 0),
          (sz.FP8_E4M3, 3, 8, sz.ESC_POS, 1024, 4), (sz.FP8_E4M3, 4, 16, sz.ESC_ABS32, 0, 4)]
 GEN = {sz.BF16: kv_synth.kv_bf16, sz.FP8_E5M2: kv_synth.kv_e5m2, sz.FP8_E4M3: kv_synth.kv_e4m3}
-
-
-@pytest.fixture
-def looks():
-    yield sz.internal_test_short
-    sz.internal_test_short()
 
 
 def words(dt, n, seed):
@@ -36,9 +31,9 @@ def test_lengths_at_the_edges(form, looks):
         for n in (blocks * 1024, blocks * 1024 - 5):
             x = words(form[0], n, blocks)
             run = Run(n, v)
-            for limit in (0, 1, sz.INTERNAL_NO_SHORT) if blocks < 300 else (0, 2):
-                looks(limit)
-                check(run, o, x, dec, f"looks {limit}")
+            for limit in (0, LEAVE, sz.INTERNAL_NO_SHORT) if blocks < 1100 else (0, LEAVE):
+                with looks(limit):
+                    check(run, o, x, dec, f"looks {limit}")
 
 
 @pytest.mark.parametrize("form", FORMS)
@@ -49,18 +44,18 @@ def test_the_end_of_the_range(form, looks):
     dec[:v.k] = sz.variant_calibrate(GEN[form[0]](64, 1), v).dec[:v.k]
     for n in (1024 * 1024 - 5, 1024 * 1024, 1024 * 1024 + 1):
         x, run = words(form[0], n, 5), Run(n, v)
-        for limit in (0, 1):
-            looks(limit)
-            check(run, o, x, dec, f"looks {limit}")
+        for limit in (0, 1, LEAVE):
+            with looks(limit):
+                check(run, o, x, dec, f"looks {limit}")
 
 
-@pytest.mark.parametrize("limit", [1, sz.INTERNAL_NO_SHORT])
+@pytest.mark.parametrize("limit", [1, LEAVE, sz.INTERNAL_NO_SHORT])
 @pytest.mark.parametrize("form", FORMS)
 def test_escape_counts(form, limit, looks):
     if form[1] == 4 and form[0] == sz.FP8_E4M3:
         return   # all exponents have a code: there are no escapes to count
-    looks(limit)
-    edges.test_escape_counts_at_the_edges_of_a_slot(*form)
+    with looks(limit):
+        edges.test_escape_counts_at_the_edges_of_a_slot(*form)
 
 
 @pytest.mark.parametrize("form", FORMS[:5])
@@ -72,11 +67,11 @@ def test_what_does_not_fit(form, looks):
     total = run.compress(x, cb)[0]
     fixed = sz.variant_total_bytes(n, 0, v)
     for cap in (fixed, fixed + (total - fixed) // 3, total - 1):
-        looks(0)
-        got = run.compress(x, cb, cap)
-        out = run.out.clone()
-        looks(sz.INTERNAL_NO_SHORT)
-        assert run.compress(x, cb, cap) == got and torch.equal(run.out, out)
+        with looks(0):
+            got = run.compress(x, cb, cap)
+            out = run.out.clone()
+        with looks(sz.INTERNAL_NO_SHORT):
+            assert run.compress(x, cb, cap) == got and torch.equal(run.out, out)
 
 
 def test_captured_calls_are_replayed():
