@@ -947,15 +947,15 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
     if (tiles > p.tiles_max) p.tiles_max = tiles;
   }
   p.small = chunks_of(n_max) <= (dtype == SPLITZIP_BF16 ? Bf16::kSmallChunks : E5m2::kSmallChunks) && !g_hooks.any();
-  // Launches of 2048 tiles and more take them in xcd_order, and BF16 from 6144 on with fewer workgroups per CU (Bf16::kTileLdsPad).  us per call,
-  // in the order of the tiles, in xcd_order and, BF16, in it with fewer workgroups: BF16 10.93 / 10.78 / 11.40 (2048 tiles: 16 tensors of 512
-  // chunks), 15.70 / 15.68 / 16.14 (4096 of one chunk per wave), 25.46 / 25.27 / 25.53 (4095), 25.07 / 25.02 / 25.28 (4096: one tensor), 34.31 /
-  // 34.33 / 34.13 (6144), 43.16 / 42.96 / 42.48 (8192), 78.1 / - / 76.4 (16 000), 1241 / - / 1201 (262 144); E5M2 11.70 / 11.66 (2048), 17.62 / 17.39 and
+  // Launches of 2048 tiles and more take them in xcd_order, BF16 where a wave has two chunks, and from 6144 on with fewer workgroups per CU (Bf16::kTileLdsPad).  us per call,
+  // in the order of the tiles, in xcd_order and, BF16, in it with fewer workgroups: BF16, one chunk per wave, 10.93 / 10.78 / 11.40 (2048 tiles: 16 tensors of 512
+  // chunks), but 11.84 / 12.18 (one tensor of 9500 chunks), 12.28 / 12.43 (9983), 12.38 / 12.59 (two of 5000), 13.61 / 13.82 (three of 4000), 15.70 / 15.68 / 16.14 (4096 tiles); two
+  // 25.46 / 25.27 / 25.53 (4095), 25.07 / 25.02 / 25.28 (4096: one tensor), 34.31 / 34.33 / 34.13 (6144), 43.16 / 42.96 / 42.48 (8192), 78.1 / - / 76.4 (16 000), 1241 / - / 1201 (262 144); E5M2 11.70 / 11.66 (2048), 17.62 / 17.39 and
   // 17.14 / 17.01 (4096), 27.42 / 26.95 (8192), 46.4 / 45.0 (16 000), 690 / 665 (131 072 of 16 KB).  What counts are
   // the tiles that there are: where the tensors differ in length, most of a launch's workgroups may have none, and they
   // take longer to pass by that way (BF16, one tensor of 13 000 chunks beside 63 of two: 35.1 and 40.6; 16 of 8192
   // beside 48 of 16: 91.5 and 95.6; but 32 of 16 384 beside 32 of 16: 328 and 321).
-  p.by_xcd = tiles_all >= 2048 && p.tiles_max * p.k <= 2 * tiles_all;
+  p.by_xcd = tiles_all >= 2048 && p.tiles_max * p.k <= 2 * tiles_all && (dtype != SPLITZIP_BF16 || p.cpt > 1);
   if (const uint32_t forced = g_hooks.xcd.load()) p.by_xcd = forced == 2;
   p.lds_pad = p.by_xcd && dtype == SPLITZIP_BF16 && (tiles_all >= 6144 || g_hooks.xcd.load() == 2) ? Bf16::kTileLdsPad : 0u;
   // Launches that memory alone bounds store through the L2 (kTileLong).  us per call, without and with:

@@ -26,6 +26,13 @@ def test_tiles_that_are_not_there_do_not_make_a_launch_long(dtype):
         assert compress_plan(dtype, chunks)["by_xcd"] and decompress_plan(dtype, chunks)["by_xcd"]
 
 
+def test_short_launches_keep_the_order_of_the_tiles():
+    """Under 2048 tiles, and where a wave has one chunk of BF16."""
+    assert [compress_plan(sz.BF16, [c])["by_xcd"] for c in (8192, 9983, 20480, 20481, 32768)] == [0, 0, 0, 1, 1]
+    assert [compress_plan(sz.BF16, [c] * k)["by_xcd"] for c, k in ((5000, 2), (1000, 10), (300, 64), (330, 64))] == [0, 0, 0, 1]
+    assert [compress_plan(sz.FP8_E5M2, [c])["by_xcd"] for c in (6144, 16376, 16384, 32768)] == [0, 0, 1, 1]
+
+
 @pytest.mark.parametrize("dtype", FORMATS)
 def test_a_third_launch_only_where_the_counts_are_many(dtype):
     """The finishing pass sums the tile counts itself, with no launch in between, until its workgroups would together read
