@@ -442,7 +442,7 @@ int splitzip_variant_codebook_from_dec(const uint8_t* dec, const splitzip_varian
  * splitzip_decompress; d_workspace needs splitzip_variant_workspace_bytes and
  * 16-byte alignment.  Two kernel launches per compress call (dense pass that
  * also stages the escape records, finishing pass; above 64 Mi elements a
- * third between them sums the counts), up to 1 Mi elements, if not captured,
+ * third between them sums the counts), up to 2 Mi elements, if not captured,
  * one that does both, and one more that packs values narrower than a byte; one per decompress call (two in the absolute mode), all on
  * `stream`. */
 int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip_variant* v,

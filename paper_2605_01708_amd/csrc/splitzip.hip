@@ -321,10 +321,17 @@ void variant_tables(const splitzip_variant* v, const splitzip_codebook* cb, VArg
     }                                                                                                              \
   } while (0)
 
-// Whether v_short_kernel takes a tensor of so many tiles of four blocks, as in pick_short.  Its words lie in the blocks' slots, 2 KB
-// per tile of four blocks; a tensor of one tile has no words.
-bool variant_short(uint64_t tiles, hipStream_t st) {
-  return tiles >= 1 && tiles <= kShortTiles && g_hooks.short_looks.load() != kNoShort && tiles <= cus_once(st, tiles);
+template <int DT, int CB>
+constexpr auto v_short_one = v_short_kernel<DT, CB, 1>;
+template <int DT, int CB>
+constexpr auto v_short_two = v_short_kernel<DT, CB, 2>;
+// Blocks per wave of v_short_kernel if it takes a tensor of so many blocks, else 0: by the launch's workgroups, as in pick_short.  Its words
+// lie in the blocks' slots, 2 KB per tile of four blocks; a tensor of one tile has no words.
+uint32_t variant_short(uint64_t blocks, hipStream_t st) {
+  if (!blocks || blocks > 2 * kWaves * kShortTiles || g_hooks.short_looks.load() == kNoShort) return 0;
+  const uint32_t bpw = blocks <= kWaves * kShortTiles ? 1 : 2;
+  const uint64_t cus = cus_once(st, (blocks + bpw * kWaves - 1) / (bpw * kWaves));
+  return blocks <= kWaves * cus && bpw == 1 ? 1 : blocks <= 2 * kWaves * cus ? 2 : 0;
 }
 
 void launch_v_pack(uint64_t n_elems, hipStream_t st, const VArgs& a) {
@@ -488,14 +495,15 @@ int splitzip_variant_compress(const void* d_in, uint64_t n_elems, const splitzip
   a.n_sums = direct ? grid : a.n_tiles;
   a.sum_shift = direct ? 2u + (10u - a.chunk_shift) : 10u;
   a.ahead = v->k <= 8 ? 64u : 16u;   // a top-8 codebook leaves about 60 records per block, a larger one one or two
-  if (variant_short(grid, st)) {
+  if (const uint32_t bpw = variant_short(blocks, st)) {
     VShortArgs sa;
     sa.a = a;
     sa.short_words = reinterpret_cast<uint64_t*>(a.slots);
     sa.tag = next_call_tag();
     sa.looks = short_looks();
-    sa.tiles = grid;
-    SPLITZIP_V_DISPATCH3(v_short_kernel, a, dim3(grid), dim3(kThreads), st, sa);
+    sa.tiles = (unsigned)((blocks + bpw * kWaves - 1) / (bpw * kWaves));
+    if (bpw == 1) SPLITZIP_V_DISPATCH3(v_short_one, a, dim3(sa.tiles), dim3(kThreads), st, sa);
+    else SPLITZIP_V_DISPATCH3(v_short_two, a, dim3(sa.tiles), dim3(kThreads), st, sa);
     if (a.val_bits != 8) launch_v_pack(n_elems, st, a);
     return hipGetLastError() == hipSuccess ? SPLITZIP_OK : SPLITZIP_ERR_HIP;
   }

@@ -642,62 +642,73 @@ __global__ __launch_bounds__(kThreads) void v_finish_kernel(const VArgs args) {
   if (g == 0) v_write_trailer(a, args.hdr, M, tid);
 }
 
-// Short calls (splitzip_variant_compress): the passes above in one launch, as in compress_short_kernel, a block per wave.
+// Short calls (splitzip_variant_compress): the passes above in one launch, as in compress_short_kernel, a block per wave or two.
 // short_words: where the workgroups' words lie (the blocks' slots, which nothing is staged in here); tag, looks: as there; tiles: the
 // launch's workgroups (asked for as gridDim, a launch has 256 bytes more of arguments).
 // us per call, two launches and this: BF16 top-8 7.8 and 4.4 (4 blocks), 8.0 and 5.1 (100), 8.2 and 5.3 (1000), sentinels 7.8 and 4.3, 8.1 and 5.1
 // (100); E5M2 7.8 and 4.4, 7.9 and 5.1; with the planes stored and the records staged before the count is told, BF16 top-8 5.5 (100), 6.1
-// (1000).  Narrow values are still packed by v_pack_kernel.  Up to 256 tiles, as with one chunk per wave in pick_short.
+// (1000).  Narrow values are still packed by v_pack_kernel.  Up to 256 workgroups, as in pick_short: on 1 / 2 / 3 / 4 streams side by side 2000 blocks in
+// two launches, with a block per wave and this way, with two, BF16 top-8 8.7 / 4.8 / 3.6 / 2.9, 6.2 / 3.5 / 3.2 / 5.2, 8.3 / 4.3 / 3.2 / 2.5, sentinels 7.7 / 4.1 / 3.1 / 2.6, 5.3 / 3.1 /
+// 2.7 / 2.9, 6.2 / 3.4 / 2.6 / 2.1.
 struct VShortArgs {
   VArgs a;
   uint64_t* short_words;
   uint64_t tag;
   uint32_t looks, tiles;
 };
-template <int DT, int CB>
-__global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args) {
+// BPW: blocks per wave.
+template <int DT, int CB, int BPW>
+__global__ __launch_bounds__(kThreads, BPW == 1 ? 1 : 4) void v_short_kernel(const VShortArgs args) {
   using F = VFmt<DT>;
   static_assert(kThreads == kTileThreads, "ShortCounts");
   __shared__ uint32_t lut[256];
-  __shared__ __attribute__((aligned(16))) uint32_t s_words[kWaves][kVBlock * F::ES / 4];
-  __shared__ uint16_t s_pos[kWaves][kVBlock];   // room for all of a wave's records
+  __shared__ __attribute__((aligned(16))) uint32_t s_words[kWaves][BPW][kVBlock * F::ES / 4];
+  __shared__ uint16_t s_pos[kWaves][BPW][kVBlock];   // room for all of a wave's records
   __shared__ uint32_t s_cnt[kWaves];
   __shared__ ShortShared s_short;
   const VArgs a = v_args_arrived(args.a);
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   ShortCounts counts(args.short_words, args.tag, args.tiles, blockIdx.x);
-  uint32_t blk = 0, count = 0;                   // the wave's block and its escapes
-  bool live = false, full = false;
-  uint32_t w[2][F::NW];
-  uint32_t sm[2][2], code[2][2], esc[2], excl[2], tot[2], low[2];   // of the block's steps
-  uint32_t in_tile = 0, total = 0;               // escapes of the tile before the wave's block; all of them
+  uint32_t blk = 0, count[BPW];                  // the wave's first block, the escapes of its blocks
+  bool live[BPW], full[BPW];
+  uint32_t w[BPW][2][F::NW];
+  uint32_t sm[BPW][2][2], code[BPW][2][2], esc[BPW][2], excl[BPW][2], tot[BPW][2], low[BPW][2];   // of the blocks' steps
+  uint32_t in_tile = 0, total = 0;               // escapes of the tile before the wave's blocks; all of them
   auto encode = [&](uint32_t tile, bool build) {
-    blk = tile * kWaves + wave;
-    count = tot[0] = tot[1] = low[0] = low[1] = 0;
-    const uint64_t e0 = (uint64_t)blk * kVBlock;
-    live = e0 < a.n, full = e0 + kVBlock <= a.n;
-    // the block's words first, all of them: the table is built while they are on their way
-    if (full) {
+    blk = (tile * kWaves + wave) * BPW;
+    // the blocks' words first, all of them: the table is built while they are on their way
 #pragma unroll
-      for (int s = 0; s < 2; ++s) v_load8<DT, true>(a, e0 + s * kVStep + lane * 8, w[s]);
-    } else if (live) {
+    for (int b = 0; b < BPW; ++b) {
+      const uint64_t e0 = (uint64_t)(blk + b) * kVBlock;
+      live[b] = e0 < a.n, full[b] = e0 + kVBlock <= a.n;
+      if (full[b]) {
 #pragma unroll
-      for (int s = 0; s < 2; ++s) v_load8<DT, false>(a, e0 + s * kVStep + lane * 8, w[s]);
+        for (int s = 0; s < 2; ++s) v_load8<DT, true>(a, e0 + s * kVStep + lane * 8, w[b][s]);
+      } else if (live[b]) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) v_load8<DT, false>(a, e0 + s * kVStep + lane * 8, w[b][s]);
+      }
     }
     if (build) {
       v_build_encode_table(args.a, lut, tid);
       lds_barrier();
     }
-    if (live) {
+    uint32_t mine = 0;
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        v_encode8<DT, CB>(lut, full ? 8u : v_nvalid(a, e0 + s * kVStep + lane * 8), w[s], sm[s], code[s], esc[s]);
-        tot[s] = v_sparse_excl(__popc(esc[s]), excl[s], low[s]);
+    for (int b = 0; b < BPW; ++b) {
+      count[b] = tot[b][0] = tot[b][1] = low[b][0] = low[b][1] = 0;
+      if (live[b]) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          v_encode8<DT, CB>(lut, full[b] ? 8u : v_nvalid(a, (uint64_t)(blk + b) * kVBlock + s * kVStep + lane * 8), w[b][s], sm[b][s], code[b][s], esc[b][s]);
+          tot[b][s] = v_sparse_excl(__popc(esc[b][s]), excl[b][s], low[b][s]);
+        }
+        count[b] = tot[b][0] + tot[b][1];
+        mine += count[b];
       }
-      count = tot[0] + tot[1];
     }
-    if (lane == 0) s_cnt[wave] = count;
+    if (lane == 0) s_cnt[wave] = mine;
     lds_barrier();
     in_tile = total = 0;
 #pragma unroll
@@ -710,28 +721,35 @@ __global__ __launch_bounds__(kThreads) void v_short_kernel(const VShortArgs args
   auto deliver = [&] {
     const uint64_t sm_end = a256(a.sm_bytes), code_end = a256(a.code_bytes);
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const uint64_t sm_at = ((uint64_t)blk * kVBlock + s * kVStep) / 8 * F::SB, code_at = ((uint64_t)blk * kVBlock + s * kVStep) / 8 * CB;
-      if (full) {
-        v_store_plane<F::SB, true>(a.out + a.off_sm, sm_at, sm_end, lane, sm[s]);
-        v_store_plane<CB, true>(a.out + a.off_code, code_at, code_end, lane, code[s]);
-      } else if (live) {
-        v_store_plane<F::SB, false>(a.out + a.off_sm, sm_at, sm_end, lane, sm[s]);
-        v_store_plane<CB, false>(a.out + a.off_code, code_at, code_end, lane, code[s]);
+    for (int b = 0; b < BPW; ++b) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const uint64_t step = ((uint64_t)(blk + b) * kVBlock + s * kVStep) / 8, sm_at = step * F::SB, code_at = step * CB;
+        if (full[b]) {
+          v_store_plane<F::SB, true>(a.out + a.off_sm, sm_at, sm_end, lane, sm[b][s]);
+          v_store_plane<CB, true>(a.out + a.off_code, code_at, code_end, lane, code[b][s]);
+        } else if (live[b]) {
+          v_store_plane<F::SB, false>(a.out + a.off_sm, sm_at, sm_end, lane, sm[b][s]);
+          v_store_plane<CB, false>(a.out + a.off_code, code_at, code_end, lane, code[b][s]);
+        }
       }
+      if (count[b]) v_stage_block<DT, CB>(s_words[wave][b], s_pos[wave][b], kVBlock, lane, w[b], esc[b], excl[b], tot[b]);
     }
-    if (count) v_stage_block<DT, CB>(s_words[wave], s_pos[wave], kVBlock, lane, w, esc, excl, tot);
   };
   auto place = [&](uint32_t tile) {
     const VSink<kVAnyPos> sink(a, counts.M);
-    const uint32_t base = counts.first + in_tile;
+    uint32_t base = counts.first + in_tile;
     const uint32_t cpb_shift = 10u - a.chunk_shift;   // log2 of the chunks per block: 0 or 2
-    const uint64_t c = ((uint64_t)blk << cpb_shift) + lane;
-    if (a.mode != SPLITZIP_ESC_ABS32 && lane < (1u << cpb_shift) && c < a.n_chunks)
-      a.offs[c] = base + (lane == 0 ? 0u : lane == 1 ? low[0] : lane == 2 ? tot[0] : tot[0] + low[1]);
-    for (uint32_t i = lane; i < count; i += 64) {
-      const uint32_t p = s_pos[wave][i];
-      sink.put(base + i, blk * kVBlock + p, v_staged_exponent<DT>(s_words[wave], p));
+#pragma unroll
+    for (int b = 0; b < BPW; ++b) {
+      const uint64_t c = ((uint64_t)(blk + b) << cpb_shift) + lane;
+      if (a.mode != SPLITZIP_ESC_ABS32 && lane < (1u << cpb_shift) && c < a.n_chunks)
+        a.offs[c] = base + (lane == 0 ? 0u : lane == 1 ? low[b][0] : lane == 2 ? tot[b][0] : tot[b][0] + low[b][1]);
+      for (uint32_t i = lane; i < count[b]; i += 64) {
+        const uint32_t p = s_pos[wave][b][i];
+        sink.put(base + i, (blk + b) * kVBlock + p, v_staged_exponent<DT>(s_words[wave][b], p));
+      }
+      base += count[b];
     }
     if (tile == 0) v_write_trailer(a, args.a.hdr, counts.M, tid);
   };

@@ -37,12 +37,12 @@ def test_lengths_at_the_edges(form, looks):
 
 
 @pytest.mark.parametrize("form", FORMS)
-def test_the_end_of_the_range(form, looks):
-    """256 tiles, and one block beyond them."""
+def test_two_blocks_a_wave(form, looks):
+    """Tensors of more than 256 tiles of four blocks have half as many of eight: the first, odd ends, the last, and one word beyond."""
     v, o = sz.variant(*form), ov.variant(*form)
     dec = np.zeros(16, np.uint8)
     dec[:v.k] = sz.variant_calibrate(GEN[form[0]](64, 1), v).dec[:v.k]
-    for n in (1024 * 1024 - 5, 1024 * 1024, 1024 * 1024 + 1):
+    for n in (1024 * 1024, 1024 * 1024 + 1, 1531 * 1024 - 5, 2045 * 1024 + 3, 2048 * 1024, 2048 * 1024 + 1):
         x, run = words(form[0], n, 5), Run(n, v)
         for limit in (0, 1, LEAVE):
             with looks(limit):
