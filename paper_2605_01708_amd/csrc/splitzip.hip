@@ -877,7 +877,8 @@ uint64_t short_status_need(uint64_t tiles) { return kShortCopies * short_copy_by
 // wait only for themselves: 16 of 100 (400 workgroups) 2.4 and 2.0, 64 of 32 (512) 2.4 and 2.3, four of 500 2.6 and 2.5, but two of 1024 2.5 and 2.8, 64 of 60
 // 3.5 and 4.3, four of 1000 3.4 and 8.2, and with two chunks per wave 64 of 60 (512) 3.5 and 3.7, four of 1000 3.4 and 4.3.
 // On a stream of 32 CUs 2048 chunks take 10 us in two launches and took 360 this way.  Beside elementwise kernels that fill the chip
-// 1000 chunks 20.2 and 16.0, 2048 20.2 and 17.6, beside matrix products 166 and 109, 165 and 110.
+// 1000 chunks 20.2 and 16.0, 2048 20.2 and 17.6, four of 500 20.8 and 15.8, 64 of 32 21.1 and 14.7; beside matrix products 166 and 109, 165 and 110, 163
+// and 103, 103 and 102.
 // Tensors that differ in length, as in pick_base_cpt, only that workgroups without a tile ask for more of a CU here; on 1 / 3 / 4 streams,
 // two launches and this: one of 500 chunks beside 40 of 12 (4800 workgroups without a tile) 7.6 / 3.5 / 3.0 and 6.2 / 3.0 / 2.8, 1000 beside 40 of 4 (9900) 8.8 / 4.3 /
 // 3.4 and 7.2 / 4.0 / 3.7, 1024 beside 20 of 8 (5080) 8.0 / 3.4 / 3.0 and 6.8 / 3.4 / 3.2; two chunks per wave 1500 beside 20 of 8 (3740) 8.3 / 4.0 / 3.6 and 6.9 / 3.0 / 2.8, 1024
