@@ -209,7 +209,9 @@ uint64_t next_call_tag() {
   return tag;
 }
 // How many CUs a launch of so many workgroups that is enqueued now can have, and 0 if it may run more than once: a captured launch is
-// replayed with the tag that it was captured with.
+// replayed with the tag that it was captured with.  Where there are few workgroups, any part of a chip has room for them, and nobody is
+// asked: for the current device 0.05 us, for a stream's mask 0.2.
+constexpr uint64_t kMostCus = 1024;
 uint64_t cus_once(hipStream_t st, uint64_t wgs) {
   hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &s) != hipSuccess) {
@@ -217,10 +219,11 @@ uint64_t cus_once(hipStream_t st, uint64_t wgs) {
     return 0;
   }
   if (s != hipStreamCaptureStatusNone) return 0;
+  if (wgs <= 32) return kMostCus;
   const uint64_t all = (uint64_t)cu_count();
-  if (!st || wgs <= all / 8 || g_hooks.short_anywhere) return all;   // a few fit any part of a chip
-  uint32_t mask[32] = {0};   // of a stream that was made with one (the question takes 0.2 us)
-  if (all > 32 * 32 || hipExtStreamGetCUMask(st, (uint32_t)(all + 31) / 32, mask) != hipSuccess) {
+  if (!st || g_hooks.short_anywhere) return all;
+  uint32_t mask[kMostCus / 32] = {0};
+  if (all > kMostCus || hipExtStreamGetCUMask(st, (uint32_t)(all + 31) / 32, mask) != hipSuccess) {
     (void)hipGetLastError();
     return all;
   }
@@ -918,9 +921,8 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   CompressPlan p;
   memset(&p, 0, sizeof p);
   const uint32_t k_most = tensors_of_compress(items, n_items, status_bytes, stage_bytes);
-  const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
   uint64_t wgs;
-  if (!g_hooks.any() && g_hooks.short_looks.load() != kNoShort && pick_short(items, k_most, status_bytes, cus, &wgs, &p.tiles_max)) {
+  if (!g_hooks.any() && g_hooks.short_looks.load() != kNoShort && pick_short(items, k_most, status_bytes, kMostCus, &wgs, &p.tiles_max)) {
     p.cpt = pick_short(items, k_most, status_bytes, once(wgs), &wgs, &p.tiles_max);
     if (p.cpt) {
       p.is_short = true;
@@ -931,6 +933,7 @@ CompressPlan plan_compress(const splitzip_item* items, uint32_t n_items, uint64_
   }
   // as many of the next tensors as find room for their counts in the status area; all of them share
   // the tile size of the one that needs the largest
+  const uint64_t cus = (uint64_t)cu_count();   // asks the runtime: once per call
   uint64_t chunks_all = 0, chunks_max = 0;
   for (uint32_t q = 0; q < k_most; ++q) {
     const uint64_t c = chunks_of(items[q].n_elems);
